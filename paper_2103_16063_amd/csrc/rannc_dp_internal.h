@@ -170,11 +170,11 @@ hipError_t launch_traceback(const ProblemDev *probs, int Q, int plan_stride, int
                             int32_t *d_replicas, const int32_t *d_levels, int64_t lds_bytes, int64_t *rec,
                             hipStream_t st);
 hipError_t launch_level_values(const ProblemDev *probs, int Q, int stride, int64_t *d_out, hipStream_t st);
-// compaction step of the block-level phase on a chain of G groups (one workgroup).  Chains whose
-// state fits LDS (kCompactLds groups) need only the listing in the workspace, longer ones keep
-// their whole state there.
+// compaction step of the block-level phase on a chain of G groups (one workgroup).  Short chains are
+// held in LDS; longer ones keep arrays of G + 1 entries in the workspace: three of 8 bytes and two of 4
+constexpr size_t compact_array_bytes(int G, int entry) { return ((size_t)(G + 1) * entry + 255) / 256 * 256; }
+// (the size callers have been given since the first version of the step; more than the arrays need)
 constexpr int kCompactLds = 1600;
-// bytes of one index list: room for the next power of two above G (the bitonic listing pads to it)
 constexpr size_t compact_order_bytes(int G) {
   size_t P = 1;
   while (P < (size_t)G) P <<= 1;

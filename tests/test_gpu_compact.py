@@ -56,6 +56,27 @@ def test_compact_matches_the_oracle(seed, G, k, M):
             assert n == min(k, G)                        # memory never refuses: k blocks are reached
 
 
+# the three layouts of the kernel's state (all in LDS, times in LDS, all in the workspace) at their
+# edges, on chains whose turns are independent (random), strictly one after the other (ascending,
+# descending) or decided by position alone (equal), with a walk that stops at k in its middle
+@pytest.mark.parametrize("G", [1, 2, 63, 64, 65, 257, 1600, 1601, 16384, 16385, 65535])
+@pytest.mark.parametrize("order", ["random", "ascending", "descending", "equal"])
+def test_compact_state_layouts(G, order):
+    if G > 20000 and order in ("ascending", "descending"):
+        G = 17000   # one turn per round: keep it short
+    g = np.random.default_rng(G)
+    t = {"random": g.integers(0, 1 << 40, G), "ascending": np.arange(G) * 3, "descending": np.arange(G)[::-1] * 3,
+         "equal": np.full(G, 7)}[order]
+    p, a = g.integers(0, 50, G), g.integers(0, 50, G)
+    for k, M, walks in ((1, 10**9, 0), (max(1, (3 * G) // 4), 10**9, 0), (max(1, G // 3), 130, 2)):
+        rc, n, st, d_end, d_out = gpu_compact(t, p, a, k, M, walks)
+        assert rc == B.OK and st == B.PROBLEM_OK
+        end, tt, pp, aa = oracle.compact(t, p, a, k, M, max_passes=walks)
+        assert n == len(end) and np.array_equal(d_end.cpu().numpy()[:n], end)
+        for have, want in zip(d_out, (tt, pp, aa)):
+            assert np.array_equal(have.cpu().numpy()[:n], want)
+
+
 def test_compact_status_and_rejections():
     t, p, a = np.array([3, 1, 2]), np.array([1, 1, 1]), np.array([1, 1, 1])
     neg = t.copy(); neg[1] = -1
