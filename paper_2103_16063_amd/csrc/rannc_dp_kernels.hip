@@ -483,45 +483,100 @@ __global__ __launch_bounds__(256) void runs_kernel(const ProblemDev *__restrict_
 // together in LDS, and one transposed pass of device-scope atomicMin into V[s] (pre-filled with
 // INF) combines the items of a chunk: min is order-independent, so the result is deterministic.
 // ---------------------------------------------------------------------------------------
-// One row's sorted merge: x := the DP largest elements of merge(a, c), sorted descending, for the
-// lane's stage; all INF for a lane without work (`off` = INF there, 0 elsewhere).
-//
-// x[DP-1-m] = c[m+1]: reversed, so that max(a, x) is a bitonic sequence; then log2(DP) compare-
-// exchange stages.  Replica counts beyond rl cannot occur at this level and rank below everything
-// that matters in the merge.  NG = ceil(rl / 8) is a compile-time number, so that the reads of a
-// row are one straight run of independent loads: the groups of eight rows beyond it are taken as
-// 0, and inside the last group the row index is clamped to rl-1 (the repeated value keeps the
-// sequence sorted, stays below rank D-1, and costs no memory traffic).  `unit` points at the
-// lane's column, or for a lane without work at the column of a lane that has some (every load
-// instruction then touches only lines that are needed); such a lane is switched off by folding
-// `off` into the first maximum, which makes its whole result INF.
-template <typename VT, int DP, int NG, typename AP>
-__device__ __forceinline__ void row_merge(VT (&x)[DP], const VT RANNC_GLOBAL *__restrict__ unit, AP arow,
-                                          VT off, int rl) {
+// Sorting a bitonic sequence (descending, then ascending) of H values into descending order.
+// A bitonic sequence of LEN = F * m values, read as F rows of m, has this property for any F: sorting
+// each of the m columns leaves F bitonic rows, every value of a row >= every value of the next one (a
+// 0/1 bitonic sequence puts its zeros into cyclically consecutive places, so the zero counts of the
+// columns differ by at most one and the rows with both values come out bitonic; Nakatani et al., K-way
+// bitonic sort).  With F = 3 a column is max3 / med3 / min3: one instruction per value for log2(3) =
+// 1.58 binary levels, where the binary form pays one per level.  LEN is the product of twos and threes
+// that costs least for H, with LEN - H places in front that count as infinite: a column with such a
+// place needs fewer operations, or none.  H = 64: 246 instead of 384 operations, 56: 220, 48: 183, 40:
+// 138, 32: 100 instead of 160, 24: 72, 16: 45 instead of 64, 8: 16 instead of 24.  64-bit values have no
+// three-operand form: there the columns are pairs, of the power of two above H.
+__device__ __forceinline__ uint32_t vmed3(uint32_t a, uint32_t b, uint32_t c) {
+  uint32_t r;
+  asm("v_med3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+
+// position p of the sequence is x[AT + p]; the first PAD positions are the infinite ones (not stored)
+template <int LEN, int PAD, int AT, typename VT, int H> __device__ __forceinline__ void bitonic_rows(VT (&)[H]) {}
+template <int LEN, int PAD, int AT, int F, int... REST, typename VT, int H>
+__device__ __forceinline__ void bitonic_rows(VT (&x)[H]) {
+  if constexpr (LEN > 1 && PAD < LEN) {
+    constexpr int m = LEN / F;
+    static_assert(m * F == LEN, "the factors multiply to the length");
 #pragma unroll
-  for (int m = 0; m < DP; ++m) {
-    if (m < 8 * (NG - 1)) x[DP - 1 - m] = unit[m * 64];
-    else if (m == 8 * (NG - 1)) x[DP - 1 - m] = unit[m * 64];       // 8(NG-1) <= rl-1: never clamped
-    else if (m < 8 * NG) x[DP - 1 - m] = unit[min(m, rl - 1) * 64];  // wave-uniform clamp
-    else x[DP - 1 - m] = (VT)0;
+    for (int q = 0; q < m; ++q) {
+      if constexpr (F == 2) {
+        if (q >= PAD) {
+          const VT a = x[AT + q], b = x[AT + q + m];
+          x[AT + q] = vmax(a, b);
+          x[AT + q + m] = vmin(a, b);
+        }
+      } else {
+        if (q >= PAD) {
+          const VT a = x[AT + q], b = x[AT + q + m], c = x[AT + q + 2 * m];
+          x[AT + q] = vmax(vmax(a, b), c);
+          x[AT + q + m] = vmed3(a, b, c);
+          x[AT + q + 2 * m] = vmin(vmin(a, b), c);
+        } else if (q + m >= PAD) {
+          const VT a = x[AT + q + m], b = x[AT + q + 2 * m];
+          x[AT + q + m] = vmax(a, b);
+          x[AT + q + 2 * m] = vmin(a, b);
+        }
+      }
+    }
+    bitonic_rows<m, (PAD < m ? PAD : m), AT, REST...>(x);
+    bitonic_rows<m, (PAD < m ? 0 : PAD - m < m ? PAD - m : m), AT + m, REST...>(x);
+    if constexpr (F == 3) bitonic_rows<m, (PAD < 2 * m ? 0 : PAD - 2 * m), AT + 2 * m, REST...>(x);
   }
+}
+template <typename VT, int H> __device__ __forceinline__ void bitonic_sort(VT (&x)[H]) {
+  static_assert(H % 8 == 0 && H >= 8 && H <= 64, "merge widths");
+  if constexpr (sizeof(VT) == 8) {
+    if constexpr (H == 8) bitonic_rows<8, 0, 0, 2, 2, 2>(x);
+    else if constexpr (H == 16) bitonic_rows<16, 0, 0, 2, 2, 2, 2>(x);
+    else if constexpr (H <= 32) bitonic_rows<32, 32 - H, H - 32, 2, 2, 2, 2, 2>(x);
+    else bitonic_rows<64, 64 - H, H - 64, 2, 2, 2, 2, 2, 2>(x);
+  } else {
+    if constexpr (H == 8) bitonic_rows<9, 1, -1, 3, 3>(x);
+    else if constexpr (H == 16) bitonic_rows<18, 2, -2, 2, 3, 3>(x);
+    else if constexpr (H == 24) bitonic_rows<27, 3, -3, 3, 3, 3>(x);
+    else if constexpr (H <= 48) bitonic_rows<54, 54 - H, H - 54, 2, 3, 3, 3>(x);
+    else bitonic_rows<81, 81 - H, H - 81, 3, 3, 3, 3>(x);
+  }
+}
+
+// Width of the merge.  The first s-2 entries of a[] are INF (s-1 stages need s-1 devices) and only
+// rl = D-s+1 replica counts and device totals are left, so the merge of a[sig .. sig+H-1] with c[1..H]
+// for any H >= rl gives every value the level needs: its t-th output is W[d] for d - 1 = t + 1 + sig
+// (the sig skipped entries are the sig largest of the full merge).  sig = min(s-2, DP-H) skips only
+// INF and stays inside the row of DP entries.  H is rl rounded up to a multiple of eight.
+__device__ __forceinline__ int merge_shift(int s, int DP, int H) { return min(s - 2, DP - H); }
+
+// One row's sorted merge: x := the H largest elements of merge(a, c), sorted descending, for the
+// lane's stage (`arow` points at a[sig]); all INF for a lane without work (`off` = INF there, 0
+// elsewhere).
+//
+// x[H-1-m] = c[m+1]: reversed, so that max(a, x) is a bitonic sequence.  H is a compile-time number, so
+// that the reads of a row are one straight run of independent loads; inside the last group of eight
+// the row index is clamped to rl-1 (the repeated value keeps the sequence sorted, stays below rank
+// D-1, and costs no memory traffic).  `unit` points at the lane's column, or for a lane without work
+// at the column of a lane that has some (every load instruction then touches only lines that are
+// needed); such a lane is switched off by folding `off` into the first maximum, which makes its whole
+// result INF.
+template <typename VT, int H, typename AP>
+__device__ __forceinline__ void row_merge(VT (&x)[H], const VT RANNC_GLOBAL *__restrict__ unit, AP arow, VT off, int rl) {
 #pragma unroll
-  for (int q = 0; q < DP; ++q) {
+  for (int m = 0; m < H; ++m) x[H - 1 - m] = unit[(m <= H - 8 ? m : min(m, rl - 1)) * 64];  // H-8 <= rl-1; wave-uniform clamp
+#pragma unroll
+  for (int q = 0; q < H; ++q) {
     if constexpr (std::is_same<AP, const VT RANNC_GLOBAL *>::value) x[q] = vmax(vmax_su(arow[q], x[q]), off);
     else x[q] = vmax(vmax(arow[q], x[q]), off);
   }
-#pragma unroll
-  for (int h = DP / 2; h >= 1; h >>= 1) {
-#pragma unroll
-    for (int q = 0; q < DP; ++q) {
-      if ((q & h) == 0) {
-        const VT hi = vmax(x[q], x[q + h]);
-        const VT lo = vmin(x[q], x[q + h]);
-        x[q] = hi;
-        x[q + h] = lo;
-      }
-    }
-  }
+  bitonic_sort(x);
 }
 
 // The same for a level kernel that recomputes the stage times instead of reading their table (32-bit
@@ -584,64 +639,51 @@ constexpr int64_t kDirectWideMaxTime = (int64_t)1 << 40;
 struct InPlaceRow {};
 
 // entry r = ODD << SH and the ones it is the parent of
-template <typename VT, int DP, int NG, int ODD, int SH, typename AP>
-__device__ __forceinline__ void direct_chain(VT (&x)[DP], AP arow, VT q_odd, int mlo, int mhi) {
+template <typename VT, int H, int ODD, int SH, typename AP>
+__device__ __forceinline__ void direct_chain(VT (&x)[H], AP arow, VT q_odd, int mlo, int mhi) {
   constexpr int R = ODD << SH, M = R - 1;
-  if constexpr (R <= 8 * NG && R <= DP) {
+  if constexpr (R <= H) {
     const VT h = SH == 0 ? q_odd : (q_odd + (VT)((1u << SH) - 1u)) >> SH;
     const VT inf = DirectArith<VT>::inf_if(M < 32 ? mlo : mhi, M);
-    if constexpr (std::is_same<AP, InPlaceRow>::value) x[DP - 1 - M] = vmax(vmax(x[DP - 1 - M], h), inf);
-    else x[DP - 1 - M] = vmax(vmax((VT)arow[DP - 1 - M], h), inf);
-    direct_chain<VT, DP, NG, ODD, SH + 1, AP>(x, arow, q_odd, mlo, mhi);
+    if constexpr (std::is_same<AP, InPlaceRow>::value) x[H - 1 - M] = vmax(vmax(x[H - 1 - M], h), inf);
+    else x[H - 1 - M] = vmax(vmax((VT)arow[H - 1 - M], h), inf);
+    direct_chain<VT, H, ODD, SH + 1, AP>(x, arow, q_odd, mlo, mhi);
   }
 }
 
 // t = x + (r/2 - 1 + r * offset) for the odd r = 2K + 1; the next odd r adds 1 + 2 * offset (exact:
 // every t is a multiple of the offset inside the 53 bits), so one constant serves all entries
-template <typename VT, int DP, int NG, typename AP, int K = 0>
-__device__ __forceinline__ void direct_entries(VT (&x)[DP], AP arow, double t, const DirectConsts &k, int mlo,
-                                               int mhi) {
+template <typename VT, int H, typename AP, int K = 0>
+__device__ __forceinline__ void direct_entries(VT (&x)[H], AP arow, double t, const DirectConsts &k, int mlo, int mhi) {
   constexpr int ODD = 2 * K + 1;
-  if constexpr (ODD <= 8 * NG && ODD <= DP) {
+  if constexpr (ODD <= H) {
     const double y = __builtin_fma(t, k.inv[K], k.magic);
-    direct_chain<VT, DP, NG, ODD, 0, AP>(x, arow, DirectArith<VT>::quotient(y), mlo, mhi);
-    direct_entries<VT, DP, NG, AP, K + 1>(x, arow, t + (1.0 + 2.0 * DirectArith<VT>::kOffset), k, mlo, mhi);
+    direct_chain<VT, H, ODD, 0, AP>(x, arow, DirectArith<VT>::quotient(y), mlo, mhi);
+    direct_entries<VT, H, AP, K + 1>(x, arow, t + (1.0 + 2.0 * DirectArith<VT>::kOffset), k, mlo, mhi);
   }
 }
 
-template <typename VT, int DP, int NG, typename AP>
-__device__ __forceinline__ void row_merge_direct(VT (&x)[DP], AP arow, VT tij, int rmn, const DirectConsts &k) {
+template <typename VT, int H, typename AP>
+__device__ __forceinline__ void row_merge_direct(VT (&x)[H], AP arow, VT tij, int rmn, const DirectConsts &k) {
   // bit r-1 set for r < rmn: these replica counts do not fit (all of them for rmn = 255)
   const unsigned long long below = rmn > 64 ? ~0ull : ((1ull << (rmn - 1)) - 1ull);
-  if constexpr (!std::is_same<AP, InPlaceRow>::value) {
-#pragma unroll
-    for (int m = 8 * NG; m < DP; ++m) x[DP - 1 - m] = arow[DP - 1 - m];  // max(a, 0): replica counts not needed
-  }
-  direct_entries<VT, DP, NG, AP>(x, arow, (double)tij + (DirectArith<VT>::kOffset - 0.5), k, (int)(uint32_t)below,
-                                 (int)(uint32_t)(below >> 32));
-#pragma unroll
-  for (int h = DP / 2; h >= 1; h >>= 1) {
-#pragma unroll
-    for (int q = 0; q < DP; ++q) {
-      if ((q & h) == 0) {
-        const VT hi = vmax(x[q], x[q + h]);
-        const VT lo = vmin(x[q], x[q + h]);
-        x[q] = hi;
-        x[q + h] = lo;
-      }
-    }
-  }
+  direct_entries<VT, H, AP>(x, arow, (double)tij + (DirectArith<VT>::kOffset - 0.5), k, (int)(uint32_t)below,
+                            (int)(uint32_t)(below >> 32));
+  bitonic_sort(x);
 }
 
 // merge_rows for the recomputing level kernel: no table reads; per row one scalar read of T[i], the
 // lane's rmin byte and the a[] row.
-template <int DP, int NG>
-__device__ __forceinline__ bool merge_rows_direct(uint32_t (&acc)[DP], uint32_t *tile, const ProblemDev &pr, const int s,
+// H: width of the merge (multiple of eight, at least rl); LS: row stride of the tile, whose entry t is
+// output t of the merge.
+template <int H, int LS, int HMAX>
+__device__ __forceinline__ bool merge_rows_direct(uint32_t (&acc)[HMAX], uint32_t *tile, const ProblemDev &pr, const int s,
                                                   const int c, const int i0, const int i_hi, const int lane,
                                                   const int wave, const DirectConsts &k) {
   using VT = uint32_t;
   constexpr VT INF = Lim<VT>::inf;
-  const int N = pr.N, D = pr.D, nch = pr.nch;
+  const int N = pr.N, D = pr.D, DP = pr.DP, nch = pr.nch;
+  const int sig = merge_shift(s, DP, H);
   const int jj = 64 * c + lane;
   const int64_t lvl = (int64_t)(N + 1) * DP;
   const VT RANNC_GLOBAL *__restrict__ Vprev = gptr((const VT *)pr.V) + (int64_t)(s - 2) * lvl;
@@ -667,7 +709,7 @@ __device__ __forceinline__ bool merge_rows_direct(uint32_t (&acc)[DP], uint32_t 
     // full wave instead of two half-empty ones.  Every lane reads its own row of V[s-1] (straight
     // into the registers it is merged in), prefix sum and rmin byte.  The lanes of the second row
     // do not own their column, so their merge goes straight into the workgroup's tile.
-    typedef uint32_t Quad __attribute__((ext_vector_type(4)));
+    typedef uint32_t Quad __attribute__((ext_vector_type(4), aligned(4)));  // (a[sig] is any word of the row)
     struct Pair { VT alast; int rmn; int64_t Ti, Tc; int row, col; };
     auto load_pair = [&](int p) -> Pair {
       const int pc = min(max(p, 0), 32);
@@ -694,20 +736,20 @@ __device__ __forceinline__ bool merge_rows_direct(uint32_t (&acc)[DP], uint32_t 
       cur = load_pair(p + kMergeWaves);
       if (__ballot(act) != 0ull) {
         any = true;
-        VT x[DP];
-        const Quad RANNC_GLOBAL *ap = (const Quad RANNC_GLOBAL *)(Vprev + (int64_t)rc * DP);
+        VT x[H];
+        const Quad RANNC_GLOBAL *ap = (const Quad RANNC_GLOBAL *)(Vprev + (int64_t)rc * DP + sig);
 #pragma unroll
-        for (int g = 0; g < DP / 4; ++g) {
+        for (int g = 0; g < H / 4; ++g) {
           const Quad v = ap[g];
           x[4 * g] = v.x; x[4 * g + 1] = v.y; x[4 * g + 2] = v.z; x[4 * g + 3] = v.w;
         }
-        row_merge_direct<uint32_t, DP, NG, InPlaceRow>(x, InPlaceRow(), tij, rmn, k);
+        row_merge_direct<uint32_t, H, InPlaceRow>(x, InPlaceRow(), tij, rmn, k);
         if (col == lane) {
 #pragma unroll
-          for (int t = 0; t < DP; ++t) acc[t] = vmin(acc[t], x[t]);
+          for (int t = 0; t < H; ++t) acc[t] = vmin(acc[t], x[t]);
         } else if (act) {
 #pragma unroll
-          for (int t = 0; t < DP; ++t) atomicMin(&tile[col * (DP + 1) + t], x[t]);
+          for (int t = 0; t < H; ++t) atomicMin(&tile[col * LS + t], x[t]);
         }
       }
       p += kMergeWaves;
@@ -723,10 +765,10 @@ __device__ __forceinline__ bool merge_rows_direct(uint32_t (&acc)[DP], uint32_t 
     cur = load_flags(i + kMergeWaves);  // the next row's
     if (__ballot(act) != 0ull) {
       any = true;
-      VT x[DP];
-      row_merge_direct<uint32_t, DP, NG, const uint32_t RANNC_GLOBAL *>(x, Vprev + (int64_t)i * DP, tij, rmn, k);
+      VT x[H];
+      row_merge_direct<uint32_t, H, const uint32_t RANNC_GLOBAL *>(x, Vprev + (int64_t)i * DP + sig, tij, rmn, k);
 #pragma unroll
-      for (int t = 0; t < DP; ++t) acc[t] = vmin(acc[t], x[t]);
+      for (int t = 0; t < H; ++t) acc[t] = vmin(acc[t], x[t]);
     }
     i += kMergeWaves;
   }
@@ -735,9 +777,11 @@ __device__ __forceinline__ bool merge_rows_direct(uint32_t (&acc)[DP], uint32_t 
 
 // Waves per SIMD the level kernel is compiled for: the two value arrays of the widest 32-bit case
 // fit the 168 registers of three waves per SIMD (the compiler left alone takes one more); the
-// recomputing kernel also keeps 32 reciprocals in registers and runs two waves per SIMD.
-template <typename VT, int DP, bool DIRECT> constexpr int merge_waves_per_simd() {
-  return DP == 64 ? (sizeof(VT) == 4 ? (DIRECT ? 2 : 3) : 2) : (DP == 32 && DIRECT) ? 4 : 1;
+// recomputing kernel also keeps a reciprocal per odd replica count in registers.
+template <typename VT, int HMAX, bool DIRECT> constexpr int merge_waves_per_simd() {
+  if (sizeof(VT) == 8) return HMAX == 64 ? 3 : 1;
+  if (DIRECT) return HMAX >= 48 ? 2 : HMAX == 32 ? 4 : 1;
+  return HMAX == 64 ? 3 : 1;
 }
 
 // The rows i0+wave, i0+wave+4, ... <= i_hi of one work item, folded into acc (running minimum of the
@@ -745,12 +789,13 @@ template <typename VT, int DP, bool DIRECT> constexpr int merge_waves_per_simd()
 // ROWFOLD: the sorted merge of every row goes straight into the lane's row of the workgroup's LDS
 // tile instead of a running minimum in registers (64-bit values at DP = 64: two value arrays would
 // take all 256 registers of a wave and leave one wave per SIMD).
-template <typename VT, int DP, int NG, bool ROWFOLD>
-__device__ __forceinline__ bool merge_rows(VT (&acc)[DP], VT *tile_lane, const ProblemDev &pr, const int s,
+template <typename VT, int H, bool ROWFOLD, int HMAX>
+__device__ __forceinline__ bool merge_rows(VT (&acc)[HMAX], VT *tile_lane, const ProblemDev &pr, const int s,
                                            const int c, const int i0, const int i_hi, const int lane,
                                            const int wave) {
   constexpr VT INF = Lim<VT>::inf;
-  const int N = pr.N, D = pr.D, nch = pr.nch;
+  const int N = pr.N, D = pr.D, DP = pr.DP, nch = pr.nch;
+  const int sig = merge_shift(s, DP, H);
   const int jj = 64 * c + lane;
   const int64_t lvl = (int64_t)(N + 1) * DP;
   const VT RANNC_GLOBAL *__restrict__ Vprev = gptr((const VT *)pr.V) + (int64_t)(s - 2) * lvl;
@@ -782,18 +827,18 @@ __device__ __forceinline__ bool merge_rows(VT (&acc)[DP], VT *tile_lane, const P
     const unsigned long long work = __ballot(act);
     if (work != 0ull) {
       any = true;
-      VT x[DP];
+      VT x[H];
       const int col = act ? lane : __ffsll((long long)work) - 1;  // a lane without work reads a needed column
-      row_merge<VT, DP, NG, const VT RANNC_GLOBAL *>(x, cost + ubase * 64 * D + col, Vprev + (int64_t)i * DP,
-                                                     act ? (VT)0 : INF, rl);
+      row_merge<VT, H, const VT RANNC_GLOBAL *>(x, cost + ubase * 64 * D + col, Vprev + (int64_t)i * DP + sig,
+                                                act ? (VT)0 : INF, rl);
       if constexpr (ROWFOLD) {
         if (act) {
 #pragma unroll
-          for (int t = 0; t < DP; ++t) atomicMin(&tile_lane[t], x[t]);
+          for (int t = 0; t < H; ++t) atomicMin(&tile_lane[t], x[t]);
         }
       } else {
 #pragma unroll
-        for (int t = 0; t < DP; ++t) acc[t] = vmin(acc[t], x[t]);
+        for (int t = 0; t < H; ++t) acc[t] = vmin(acc[t], x[t]);
       }
     }
     i += kMergeWaves;
@@ -801,10 +846,12 @@ __device__ __forceinline__ bool merge_rows(VT (&acc)[DP], VT *tile_lane, const P
   return any;
 }
 
-template <typename VT, int DP, bool DIRECT>
+// HMAX: the widest merge this kernel holds registers for (the host takes the smallest one that covers
+// the launch: narrow levels run with more waves per SIMD); each search takes the width it needs.
+template <typename VT, int HMAX, bool DIRECT>
 __device__ __forceinline__ void level_merge_body(const ProblemDev &pr, const int s, const int item) {
   if (s > pr.S_eff) return;
-  const int N = pr.N, D = pr.D;
+  const int N = pr.N, D = pr.D, DP = pr.DP;
   const int32_t RANNC_GLOBAL *__restrict__ runs = gptr((const int32_t *)pr.runs);
   if (item >= runs[0]) return;
   const unsigned desc = (unsigned)runs[1 + item];
@@ -820,39 +867,40 @@ __device__ __forceinline__ void level_merge_body(const ProblemDev &pr, const int
   VT RANNC_GLOBAL *Vcur = gptr((VT *)pr.V) + (int64_t)(s - 1) * (int64_t)(N + 1) * DP;
 
   // acc[t] = running minimum over this wave's rows of the sorted merge
-  constexpr bool ROWFOLD = sizeof(VT) == 8 && DP == 64;
+  constexpr bool ROWFOLD = sizeof(VT) == 8 && HMAX >= 48;
   constexpr bool EARLY_TILE = ROWFOLD || DIRECT;  // rows fold into the tile while the row loop runs
-  __shared__ VT tile[64 * (DP + 1)];
-  [[maybe_unused]] VT acc[DP];
+  constexpr int LS = HMAX + 1;
+  __shared__ VT tile[64 * LS];
+  [[maybe_unused]] VT acc[HMAX];
   if constexpr (EARLY_TILE) {
-    for (int e = threadIdx.x; e < 64 * (DP + 1); e += 64 * kMergeWaves) tile[e] = INF;
+    for (int e = threadIdx.x; e < 64 * LS; e += 64 * kMergeWaves) tile[e] = INF;
     __syncthreads();
   }
   if constexpr (!ROWFOLD) {
 #pragma unroll
-    for (int t = 0; t < DP; ++t) acc[t] = INF;
+    for (int t = 0; t < HMAX; ++t) acc[t] = INF;
   }
   bool any = false;
-  const int ng = (D - s + 1 + 7) >> 3;  // eight-row groups of a unit that this level needs
+  const int ng = (D - s + 1 + 7) >> 3;  // width of the merge in groups of eight
   if constexpr (DIRECT) {
-    // stage times recomputed: groups in pairs (fewer variants; a group more costs a few instructions)
     DirectConsts k;
     direct_consts_init(k);
-#define RANNC_ROWS(K)                                                                              \
-  case K:                                                                                          \
-    if constexpr (8 * K <= DP || (K == 1 && DP == 8))                                              \
-      any = merge_rows_direct<DP, (8 * K <= DP ? K : 1)>(acc, tile, pr, s, c, i0, i_hi, lane, wave, k);  \
+#define RANNC_ROWS(K)                                                                          \
+  case K:                                                                                      \
+    if constexpr (8 * K <= HMAX)                                                               \
+      any = merge_rows_direct<8 * K, LS>(acc, tile, pr, s, c, i0, i_hi, lane, wave, k);        \
     break;
-    switch (DP == 8 ? 1 : ((ng + 1) & ~1)) {
-      RANNC_ROWS(1) RANNC_ROWS(2) RANNC_ROWS(4) RANNC_ROWS(6) RANNC_ROWS(8)
+    switch (ng) {
+      RANNC_ROWS(1) RANNC_ROWS(2) RANNC_ROWS(3) RANNC_ROWS(4)
+      RANNC_ROWS(5) RANNC_ROWS(6) RANNC_ROWS(7) RANNC_ROWS(8)
       default: break;
     }
 #undef RANNC_ROWS
   } else {
-#define RANNC_ROWS(K)                                                                     \
-  case K:                                                                                 \
-    if constexpr (8 * K <= DP)                                                            \
-      any = merge_rows<VT, DP, K, ROWFOLD>(acc, tile + lane * (DP + 1), pr, s, c, i0, i_hi, lane, wave); \
+#define RANNC_ROWS(K)                                                                               \
+  case K:                                                                                           \
+    if constexpr (8 * K <= HMAX)                                                                    \
+      any = merge_rows<VT, 8 * K, ROWFOLD>(acc, tile + lane * LS, pr, s, c, i0, i_hi, lane, wave);  \
     break;
     switch (ng) {
       RANNC_ROWS(1) RANNC_ROWS(2) RANNC_ROWS(3) RANNC_ROWS(4)
@@ -862,48 +910,52 @@ __device__ __forceinline__ void level_merge_body(const ProblemDev &pr, const int
 #undef RANNC_ROWS
   }
 
-  // acc[t] is W[d = t+2]; V rows are indexed by d-1 = t+1.  Fold the waves in LDS, then
+  // acc[t] is W[d = t+2+sig]; V rows are indexed by d-1 = t+1+sig.  Fold the waves in LDS, then
   // write transposed so that one atomic instruction covers consecutive d of one column.
   if constexpr (ROWFOLD) {
     if (__syncthreads_or(any) == 0) return;
   } else {
     if constexpr (!EARLY_TILE)
-      for (int e = threadIdx.x; e < 64 * (DP + 1); e += 64 * kMergeWaves) tile[e] = INF;
+      for (int e = threadIdx.x; e < 64 * LS; e += 64 * kMergeWaves) tile[e] = INF;
     if (__syncthreads_or(any) == 0) return;
     if (any) {
 #pragma unroll
-      for (int t = 0; t < DP; ++t) atomicMin(&tile[lane * (DP + 1) + t], acc[t]);  // folding INF in is a no-op
+      for (int t = 0; t < HMAX; ++t)
+        if (t < 8 * ng) atomicMin(&tile[lane * LS + t], acc[t]);  // folding INF in is a no-op
     }
     __syncthreads();
   }
-  constexpr int RPP = 64 * kMergeWaves / DP;  // rows per pass
-  const int t = threadIdx.x & (DP - 1);
-  for (int row = threadIdx.x / DP; row < 64; row += RPP) {
-    const VT v = tile[row * (DP + 1) + t];
+  const int sig = merge_shift(s, DP, 8 * ng);
+  constexpr int WT = HMAX > 32 ? 64 : HMAX > 16 ? 32 : HMAX;  // threads per column
+  constexpr int RPP = 64 * kMergeWaves / WT;                  // columns per pass
+  const int t = threadIdx.x & (WT - 1);
+  if (t >= HMAX || t + 1 + sig > D - 1) return;
+  for (int row = threadIdx.x / WT; row < 64; row += RPP) {
+    const VT v = tile[row * LS + t];
     const int j = 64 * c + row + 1;
-    if (t + 1 <= D - 1 && j <= N && j >= s && v != INF) global_min(&Vcur[(int64_t)j * DP + t + 1], v);
+    if (j <= N && j >= s && v != INF) global_min(&Vcur[(int64_t)j * DP + t + 1 + sig], v);
   }
 }
 
-template <typename VT, int DP, bool DIRECT>
-__global__ __launch_bounds__(64 * kMergeWaves) __attribute__((amdgpu_waves_per_eu(merge_waves_per_simd<VT, DP, DIRECT>())))
+template <typename VT, int HMAX, bool DIRECT>
+__global__ __launch_bounds__(64 * kMergeWaves) __attribute__((amdgpu_waves_per_eu(merge_waves_per_simd<VT, HMAX, DIRECT>())))
 void level_merge_kernel(const ProblemDev *__restrict__ probs, const int s, const int search_major) {
   // Workgroups go to the eight XCDs round-robin in the order of their linear index.  With the items
   // of a search next to each other (search_major) and, say, four items per search, item k of every
   // search lands on XCDs k and k + 4: the XCDs with the long items finish last and those with the
   // empty ones idle (config 5: 176 against 121 us per level).  In a launch of the recomputing form
   // over several searches the search index therefore runs fastest: every XCD gets every kind of item.
-  if (search_major) level_merge_body<VT, DP, DIRECT>(probs[blockIdx.z], s, (int)blockIdx.x);
-  else level_merge_body<VT, DP, DIRECT>(probs[blockIdx.x], s, (int)blockIdx.z);
+  if (search_major) level_merge_body<VT, HMAX, DIRECT>(probs[blockIdx.z], s, (int)blockIdx.x);
+  else level_merge_body<VT, HMAX, DIRECT>(probs[blockIdx.x], s, (int)blockIdx.z);
 }
 
 // The same for a launch over ONE search, with the descriptor as a kernel argument: a workgroup then
 // starts with its fields in scalar registers instead of fetching them through the descriptor
 // array's pointer, one memory round trip less in a launch that consists of a few of them.
-template <typename VT, int DP, bool DIRECT>
-__global__ __launch_bounds__(64 * kMergeWaves) __attribute__((amdgpu_waves_per_eu(merge_waves_per_simd<VT, DP, DIRECT>())))
+template <typename VT, int HMAX, bool DIRECT>
+__global__ __launch_bounds__(64 * kMergeWaves) __attribute__((amdgpu_waves_per_eu(merge_waves_per_simd<VT, HMAX, DIRECT>())))
 void level_merge_one_kernel(const ProblemDev pr, const int s) {
-  level_merge_body<VT, DP, DIRECT>(pr, s, (int)blockIdx.x);
+  level_merge_body<VT, HMAX, DIRECT>(pr, s, (int)blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1087,17 +1139,12 @@ void solve_small_kernel(
         const bool act = valid && rmn <= rl && row >= s - 1 && row >= s_wlo[c] && prev[row * LS + D - 1] != INF;
         if (__ballot(act) == 0ull) continue;
         const VT tij = (VT)(sT[min(jj + 1, N)] - sT[row]);
-        // Narrower merge at late levels.  The first s-2 entries of a[] are INF (s-1 stages need s-1
-        // devices) and only rl = D-s+1 replica counts and device totals are left, so the merge of
-        // a[sig..sig+H-1] with c[1..H] on a network of H >= rl inputs gives every value the level
-        // needs: its t-th output is W[d] for d - 1 = t + 1 + sig (the sig skipped entries are the
-        // sig largest of the full merge).  sig <= s-2 skips only INF, sig <= DP-H stays inside the row.
 #define RANNC_ROW(HH)                                                                                \
   {                                                                                                  \
     constexpr int H = (HH) <= DP ? (HH) : DP;                                                        \
-    const int sig = H < DP ? min(s - 2, DP - H) : 0;                                                 \
+    const int sig = merge_shift(s, DP, H);                                                           \
     VT x[H];                                                                                         \
-    row_merge_direct<VT, H, (H >= 8 ? H / 8 : 1), const VT *>(x, prev + row * LS + sig, tij, act ? rmn : 255, kc); \
+    row_merge_direct<VT, H, const VT *>(x, prev + row * LS + sig, tij, act ? rmn : 255, kc); \
     if (act && jj + 1 >= s) {                                                                        \
       /* no test per entry: columns D.. hold 0 and keep it, column DP (t + 1 + sig <= DP) is padding */ \
       VT *dst = cur + (jj + 1) * LS + 1 + sig;                                                       \
@@ -1106,6 +1153,7 @@ void solve_small_kernel(
   }
         if (rl <= 8) RANNC_ROW(8)
         else if (rl <= 16) RANNC_ROW(16)
+        else if (rl <= 24) RANNC_ROW(24)
         else RANNC_ROW(32)
 #undef RANNC_ROW
       }
@@ -1115,7 +1163,6 @@ void solve_small_kernel(
         if (i < s - 1 || i < s_wlo[c] || 64 * c + 64 < s) continue;
         if (prev[i * LS + D - 1] == INF) continue;  // no (s-1)-stage plan covers blocks 1..i
         const int jj = 64 * c + lane;
-        VT x[DP];
         const int64_t u = unit_index(nch, i, c);
         int rmn = 255;
         if (jj >= i && jj < N) rmn = rmin[u * 64 + lane];
@@ -1123,11 +1170,20 @@ void solve_small_kernel(
         if (__ballot(act) == 0ull) continue;
         const int col = act ? lane : __ffsll((long long)__ballot(act)) - 1;
         const VT RANNC_GLOBAL *unit = cost + u * 64 * D + col;
-        const VT *arow = prev + i * LS;
         const VT off = act ? (VT)0 : INF;
-#define RANNC_ROW(K)                                                                   \
-  case K:                                                                              \
-    if constexpr (8 * K <= DP) row_merge<VT, DP, K, const VT *>(x, unit, arow, off, rl); \
+#define RANNC_ROW(K)                                                                                  \
+  case K:                                                                                             \
+    if constexpr (8 * K <= DP) {                                                                      \
+      constexpr int H = 8 * K;                                                                        \
+      const int sig = merge_shift(s, DP, H);                                                          \
+      VT x[H];                                                                                        \
+      row_merge<VT, H, const VT *>(x, unit, prev + i * LS + sig, off, rl);                            \
+      /* (no test per entry, as above; folding INF in is a no-op) */                                  \
+      if (act && jj + 1 >= s) {                                                                       \
+        VT *dst = cur + (jj + 1) * LS + 1 + sig;                                                      \
+        _Pragma("unroll") for (int t = 0; t < H; ++t) atomicMin(&dst[t], x[t]);                       \
+      }                                                                                               \
+    }                                                                                                 \
     break;
         switch ((rl + 7) >> 3) {
           RANNC_ROW(1) RANNC_ROW(2) RANNC_ROW(3) RANNC_ROW(4)
@@ -1135,12 +1191,6 @@ void solve_small_kernel(
           default: break;
         }
 #undef RANNC_ROW
-        if (act && jj + 1 >= s) {
-          // unconditional: folding INF in is a no-op and costs less than testing for it
-#pragma unroll
-          for (int t = 0; t < DP - 1; ++t)
-            if (t + 1 <= D - 1) atomicMin(&cur[(jj + 1) * LS + t + 1], x[t]);
-        }
       }
     }
     if constexpr (DIRECT) {
@@ -1754,13 +1804,15 @@ hipError_t launch_build(const ProblemDev *p, const LaunchShape &sh, int bits, in
   return hipGetLastError();
 }
 
-template <typename VT, int DP, bool DIRECT>
+template <typename VT, int HMAX, bool DIRECT>
 static void merge_go(const ProblemDev *p, const LaunchShape &sh, int s, int items, const ProblemDev *host_one,
                      hipStream_t st) {
-  if (host_one && sh.nprob == 1) {
-    hipLaunchKernelGGL((level_merge_one_kernel<VT, DP, DIRECT>), dim3((unsigned)items, 1, 1), dim3(64 * kMergeWaves), 0,
-                       st, *host_one, s);
-    return;
+  if constexpr (HMAX >= 32) {
+    if (host_one && sh.nprob == 1) {
+      hipLaunchKernelGGL((level_merge_one_kernel<VT, HMAX, DIRECT>), dim3((unsigned)items, 1, 1), dim3(64 * kMergeWaves),
+                         0, st, *host_one, s);
+      return;
+    }
   }
   for (int q0 = 0; q0 < sh.nprob; q0 += 65535) {
     const int nq = min(65535, sh.nprob - q0);
@@ -1768,23 +1820,25 @@ static void merge_go(const ProblemDev *p, const LaunchShape &sh, int s, int item
     // then read neighbouring units of few tables instead of one unit each of hundreds of tables,
     // which measured 10 % slower on config 5)
     if (DIRECT && nq > 1 && items <= 65535)
-      hipLaunchKernelGGL((level_merge_kernel<VT, DP, DIRECT>), dim3(nq, 1, (unsigned)items), dim3(64 * kMergeWaves), 0,
+      hipLaunchKernelGGL((level_merge_kernel<VT, HMAX, DIRECT>), dim3(nq, 1, (unsigned)items), dim3(64 * kMergeWaves), 0,
                          st, p + q0, s, 0);
     else
-      hipLaunchKernelGGL((level_merge_kernel<VT, DP, DIRECT>), dim3((unsigned)items, 1, nq), dim3(64 * kMergeWaves), 0,
+      hipLaunchKernelGGL((level_merge_kernel<VT, HMAX, DIRECT>), dim3((unsigned)items, 1, nq), dim3(64 * kMergeWaves), 0,
                          st, p + q0, s, 1);
   }
 }
 
-hipError_t launch_level_merge(const ProblemDev *p, const LaunchShape &sh, int bits, int DP, int s, bool recompute,
+hipError_t launch_level_merge(const ProblemDev *p, const LaunchShape &sh, int bits, int s, bool recompute,
                               int items, const ProblemDev *host_one, hipStream_t st) {
   if (recompute && bits != 32) return hipErrorInvalidValue;
-#define GO(B, T, X)                                                            \
-  if (bits == B && recompute == X) {                                           \
-    if (DP == 8) merge_go<T, 8, X>(p, sh, s, items, host_one, st);               \
-    else if (DP == 16) merge_go<T, 16, X>(p, sh, s, items, host_one, st);        \
-    else if (DP == 32) merge_go<T, 32, X>(p, sh, s, items, host_one, st);        \
-    else merge_go<T, 64, X>(p, sh, s, items, host_one, st);                      \
+  const int need = sh.max_D - s + 1;  // widest merge of the launch
+#define GO(B, T, X)                                                                       \
+  if (bits == B && recompute == X) {                                                      \
+    if (need <= 8) merge_go<T, 8, X>(p, sh, s, items, host_one, st);                      \
+    else if (need <= 16) merge_go<T, 16, X>(p, sh, s, items, host_one, st);               \
+    else if (need <= 32) merge_go<T, 32, X>(p, sh, s, items, host_one, st);               \
+    else if (need <= 48) merge_go<T, 48, X>(p, sh, s, items, host_one, st);               \
+    else merge_go<T, 64, X>(p, sh, s, items, host_one, st);                               \
   }
   GO(32, uint32_t, false)
   GO(32, uint32_t, true)
