@@ -55,16 +55,12 @@ constexpr int kMergeWaves = 4;
 constexpr int kMergeMinRows = 4;
 constexpr int kMergeRows8From = 6144;
 constexpr int kMergeRows16From = 16384;
-// From this many rows in a launch on, a 32-bit search without a communication term has its stage
-// times recomputed in the level kernel (RANNC_DP_ALGO_AUTO): the launch then runs many rounds of
-// workgroups and is bound by throughput, where recomputing beats reading the table; below, the
-// level is a single round bound by latency, where the shorter table kernel wins.
-constexpr int kRecomputeRowsFrom = 32768;
-// A launch over SEVERAL searches recomputes from far fewer rows on: it needs no stage-time table
-// built in front, and measured ahead of the table form from 2 700 rows (outer driver at 192 blocks)
-// upwards at every memory tightness, by 1 to 14 %; below (two or three small searches) the table form
-// keeps its edge.
-constexpr int kRecomputeRowsFromMany = 2048;
+// From this many rows (unpruned) in a launch on, a 32-bit search without a communication term has its
+// stage times recomputed in the level kernel (RANNC_DP_ALGO_AUTO), which also saves building their
+// table.  Measured per solve, table against recomputed: 1024 blocks at 64 devices 410 / 397 us where
+// memory binds and 800 / 555 us where it does not, 700 blocks at 48 devices 289 / 268 us, 300 at 64
+// (1 500 rows) 233 / 227, 251 at 24 (640 rows) 146 / 147, 96 at 16 the table form by some microseconds.
+constexpr int kRecomputeRowsFrom = 1024;
 
 __host__ __device__ inline int dp_class(int D) { return D <= 8 ? 8 : D <= 16 ? 16 : D <= 32 ? 32 : 64; }
 

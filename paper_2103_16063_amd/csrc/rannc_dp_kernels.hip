@@ -407,11 +407,11 @@ __global__ __launch_bounds__(256) void runs_kernel(const ProblemDev *__restrict_
           }
         }
         // one large search of the recomputing form with many rounds: the largest items that still
-        // leave three rounds, by the rows that are really there (the host, which fixes the size for
+        // leave one and a half rounds, by the rows that are really there (the host, which fixes the size for
         // a launch over many searches, cannot see the pruning of a single one)
         if (!one_round && paired && batch == 1)
           for (int k = NC - 1; k > pick; --k)
-            if (count[k] >= 3 * slots) { pick = k; break; }
+            if (2 * count[k] >= 3 * slots) { pick = k; break; }
       }
       rows = 4 * (pick + 1);
     }
@@ -591,8 +591,9 @@ __device__ __forceinline__ void row_merge(VT (&x)[H], const VT RANNC_GLOBAL *__r
 // between k - 1/2 and k + 1/2 for k = floor((x + r - 1) / r): the addition of 1.5 * 2^52 rounds it to
 // that integer and leaves k in the low word of the sum.  Even replica counts follow from
 // ceil(x / 2r) = ceil(ceil(x / r) / 2): an add and a shift.  Two full-rate instructions per entry.
-// The 32 reciprocals and 1.5 * 2^52 live in vector registers for the whole kernel (as immediate
-// operands they would need one scalar register pair each, which do not exist in that number).
+// The reciprocals live in scalar register pairs for the whole kernel and 1.5 * 2^52 in a vector
+// register pair (an instruction takes one scalar operand): the rows of V[s-1] come out of LDS, so the
+// scalar registers are free for them.
 // The INF below rmn comes from a per-lane bit mask (bit r-1 set for r < rmn), one bit-field extract
 // per entry, folded into the first maximum of the merge together with a[].
 struct DirectConsts {
@@ -603,7 +604,7 @@ __device__ __forceinline__ void direct_consts_init(DirectConsts &k) {
 #pragma unroll
   for (int q = 0; q < 32; ++q) {
     k.inv[q] = 1.0 / (double)(2 * q + 1);
-    asm("" : "+v"(k.inv[q]));  // a register, not an immediate (not volatile: no memory effects)
+    asm("" : "+s"(k.inv[q]));  // a register, not an immediate (not volatile: no memory effects)
   }
   k.magic = 0x1.8p52;
   asm("" : "+v"(k.magic));
@@ -672,116 +673,106 @@ __device__ __forceinline__ void row_merge_direct(VT (&x)[H], AP arow, VT tij, in
   bitonic_sort(x);
 }
 
-// merge_rows for the recomputing level kernel: no table reads; per row one scalar read of T[i], the
-// lane's rmin byte and the a[] row.
+// The rows of one work item of the recomputing level kernel.  Everything the item reads is copied
+// into LDS first, with one round of independent loads (the rows of V[s-1], the rmin bytes and the
+// prefix sums of its rows); the row loop then waits for nothing outside the compute unit.  (With each
+// row's V[s-1] fetched by scalar loads where it was needed, the loop of a search of 1024 blocks at 64
+// devices took 12.4 us of a launch whose instructions account for 6.)  Every row's merge goes straight
+// into the item's LDS tile: a running minimum in registers costs as many instructions per row as the
+// LDS does, and as many registers as the merge itself (1024 blocks: 306 -> 279 us for 31 levels where
+// memory binds, 506 -> 474 us where it does not; 512 searches of 128 blocks at 64 devices 92 -> 82 us).
 // H: width of the merge (multiple of eight, at least rl); LS: row stride of the tile, whose entry t is
-// output t of the merge.
+// output t of the merge.  Returns whether any row of this wave had work.
+constexpr int kItemRows = 66;  // most rows of V[s-1] an item reads: 64, or 2 x 33 for the pairs of a diagonal block
+template <int HMAX> struct ItemRows {
+  static constexpr int AS = HMAX + 4;  // row stride of the copied rows: 16-byte aligned, rows on different banks
+  uint32_t a[kItemRows * AS];
+  uint8_t rmin[kItemRows * 64];
+  int64_t T[kItemRows], Tcol[64];  // prefix sums of the rows and of the chunk's columns
+};
+
 template <int H, int LS, int HMAX>
-__device__ __forceinline__ bool merge_rows_direct(uint32_t (&acc)[HMAX], uint32_t *tile, const ProblemDev &pr, const int s,
+__device__ __forceinline__ bool merge_rows_direct(uint32_t *tile, ItemRows<HMAX> &it, const ProblemDev &pr, const int s,
                                                   const int c, const int i0, const int i_hi, const int lane,
                                                   const int wave, const DirectConsts &k) {
   using VT = uint32_t;
   constexpr VT INF = Lim<VT>::inf;
+  constexpr int AS = ItemRows<HMAX>::AS, NT = 64 * kMergeWaves;
+  typedef uint32_t Quad __attribute__((ext_vector_type(4)));
+  typedef uint32_t QuadAny __attribute__((ext_vector_type(4), aligned(4)));  // (a[sig] is any word of the row)
   const int N = pr.N, D = pr.D, DP = pr.DP, nch = pr.nch;
   const int sig = merge_shift(s, DP, H);
-  const int jj = 64 * c + lane;
   const int64_t lvl = (int64_t)(N + 1) * DP;
-  const VT RANNC_GLOBAL *__restrict__ Vprev = gptr((const VT *)pr.V) + (int64_t)(s - 2) * lvl;
+  const VT RANNC_GLOBAL *__restrict__ Vprev = gptr((const VT *)pr.V) + (int64_t)(s - 2) * lvl + sig;
   const uint8_t RANNC_GLOBAL *__restrict__ rmin = gptr((const uint8_t *)pr.rmin);
   const int64_t RANNC_GLOBAL *__restrict__ T = gptr((const int64_t *)pr.T);
   const int rl = D - s + 1;
-  const int64_t Tj = T[min(jj + 1, N)];  // the lane's column (clamped: lanes beyond N have no work)
-  // only the loads happen here, unconditionally; the values are looked at one iteration later (see
-  // merge_rows)
-  struct Row { VT alast; int rmn; int64_t Ti; };
-  auto load_flags = [&](int i) -> Row {
-    const int ic = min(max(i, s - 1), i_hi);
+  // Diagonal block: the listed row 64c+p stands for the pair of rows 64c+p (lanes p.. with their own
+  // columns) and 64c+64-p (the p columns from 64-p on, on the lanes below p): one pass of a full wave
+  // instead of two half-empty ones.
+  const bool diag = i0 >= 64 * c;
+  const int n = i_hi - i0 + 1, p0 = i0 - 64 * c, p1 = i_hi - 64 * c;
+  const int staged = diag ? 2 * n : n;  // the second rows 64-p1 .. 64-p0 of the pairs behind the first ones
+  auto row_of = [&](int e) {
+    const int row = e < n ? i0 + e : 64 * c + 64 - p1 + (e - n);
+    return min(min(row, 64 * c + 63), N - 1);  // (p = 0 has no second row; rows beyond the chain have no work)
+  };
+  for (int e = threadIdx.x; e < staged * (H / 4); e += NT) {
+    const int row = e / (H / 4), q = e % (H / 4);
+    const QuadAny v = *(const QuadAny RANNC_GLOBAL *)(Vprev + (int64_t)row_of(row) * DP + 4 * q);
+    *(Quad *)&it.a[row * AS + 4 * q] = (Quad)v;
+  }
+  for (int e = threadIdx.x; e < staged * 4; e += NT)
+    *(Quad *)&it.rmin[e * 16] = *(const Quad RANNC_GLOBAL *)(rmin + unit_index(nch, row_of(e >> 2), c) * 64 + (e & 3) * 16);
+  for (int e = threadIdx.x; e < staged; e += NT) it.T[e] = T[row_of(e)];
+  if (threadIdx.x < 64) it.Tcol[threadIdx.x] = T[min(64 * c + lane + 1, N)];  // (clamped: columns beyond N have no work)
+  __syncthreads();
+  bool any = false;
+  // what decides whether a row has work is read one row ahead
+  struct Row { VT alast; int rmn; int64_t Ti; int e, row, col; };
+  auto look = [&](int x) -> Row {
     Row r;
-    r.alast = Vprev[(int64_t)ic * DP + D - 1];
-    r.Ti = T[ic];
-    r.rmn = rmin[unit_index(nch, ic, c) * 64 + lane];
+    const int xc = min(x, n - 1);
+    r.e = xc; r.row = i0 + xc; r.col = lane;
+    if (diag) {
+      const int p = p0 + xc;
+      if (lane < p) { r.e = n + p1 - p; r.row = p < 32 ? 64 * c + 64 - p : N; r.col = lane + 64 - p; }  // rows 64c and 64c+32 have no partner
+    }
+    // an (s-1)-stage plan on at most D-1 devices covers blocks 1..row iff the last of them is finite
+    r.alast = it.a[r.e * AS + D - 2 - sig];
+    r.rmn = it.rmin[r.e * 64 + r.col];
+    r.Ti = it.T[r.e];
     return r;
   };
-  bool any = false;
-  if (i0 >= 64 * c) {
-    // Diagonal block: the listed row 64c+p stands for the pair of rows 64c+p (lanes p.. with their
-    // own columns) and 64c+64-p (the p columns from 64-p on, on the lanes below p): one pass of a
-    // full wave instead of two half-empty ones.  Every lane reads its own row of V[s-1] (straight
-    // into the registers it is merged in), prefix sum and rmin byte.  The lanes of the second row
-    // do not own their column, so their merge goes straight into the workgroup's tile.
-    typedef uint32_t Quad __attribute__((ext_vector_type(4), aligned(4)));  // (a[sig] is any word of the row)
-    struct Pair { VT alast; int rmn; int64_t Ti, Tc; int row, col; };
-    auto load_pair = [&](int p) -> Pair {
-      const int pc = min(max(p, 0), 32);
-      const bool second = lane < pc && pc < 32;  // rows 64c and 64c+32 have no partner
-      Pair r;
-      r.col = second ? lane + 64 - pc : lane;
-      r.row = lane >= pc ? 64 * c + pc : second ? 64 * c + 64 - pc : -1;
-      const int rc = min(max(r.row, s - 1), N - 1);  // in range for the reads; the row itself decides below
-      r.alast = Vprev[(int64_t)rc * DP + D - 1];
-      r.Ti = T[rc];
-      r.Tc = T[min(64 * c + r.col + 1, N)];
-      r.rmn = rmin[unit_index(nch, rc, c) * 64 + r.col];
-      return r;
-    };
-    int p = i0 - 64 * c + wave;
-    const int p_hi = i_hi - 64 * c;
-    Pair cur = load_pair(p);
-    while (p <= p_hi) {  // wave-uniform
-      const int row = cur.row, col = cur.col;
-      const bool act = row >= s - 1 && row < N && 64 * c + col < N && cur.alast != INF && cur.rmn <= rl;
-      const uint32_t tij = (uint32_t)(cur.Tc - cur.Ti);
-      const int rmn = act ? cur.rmn : 255;
-      const int rc = min(max(row, s - 1), N - 1);
-      cur = load_pair(p + kMergeWaves);
-      if (__ballot(act) != 0ull) {
-        any = true;
-        VT x[H];
-        const Quad RANNC_GLOBAL *ap = (const Quad RANNC_GLOBAL *)(Vprev + (int64_t)rc * DP + sig);
+  int x = wave;
+  Row cur = look(x);
+  while (x < n) {  // wave-uniform
+    const Row r = cur;
+    const bool act = r.row >= s - 1 && r.row < N && 64 * c + r.col < N && r.alast != INF && r.rmn <= rl;
+    cur = look(x + kMergeWaves);
+    x += kMergeWaves;
+    if (__ballot(act) == 0ull) continue;
+    any = true;
+    const uint32_t tij = (uint32_t)(it.Tcol[r.col] - r.Ti);
+    VT w[H];
 #pragma unroll
-        for (int g = 0; g < H / 4; ++g) {
-          const Quad v = ap[g];
-          x[4 * g] = v.x; x[4 * g + 1] = v.y; x[4 * g + 2] = v.z; x[4 * g + 3] = v.w;
-        }
-        row_merge_direct<uint32_t, H, InPlaceRow>(x, InPlaceRow(), tij, rmn, k);
-        if (col == lane) {
-#pragma unroll
-          for (int t = 0; t < H; ++t) acc[t] = vmin(acc[t], x[t]);
-        } else if (act) {
-#pragma unroll
-          for (int t = 0; t < H; ++t) atomicMin(&tile[col * LS + t], x[t]);
-        }
-      }
-      p += kMergeWaves;
+    for (int g = 0; g < H / 4; ++g) {
+      const Quad v = *(const Quad *)&it.a[r.e * AS + 4 * g];
+      w[4 * g] = v.x; w[4 * g + 1] = v.y; w[4 * g + 2] = v.z; w[4 * g + 3] = v.w;
     }
-    return any;
-  }
-  int i = i0 + wave;
-  Row cur = load_flags(i);
-  while (i <= i_hi) {  // wave-uniform
-    const bool act = i >= s - 1 && cur.alast != INF && jj >= i && jj < N && cur.rmn <= rl;
-    const uint32_t tij = (uint32_t)(Tj - cur.Ti);
-    const int rmn = act ? cur.rmn : 255;
-    cur = load_flags(i + kMergeWaves);  // the next row's
-    if (__ballot(act) != 0ull) {
-      any = true;
-      VT x[H];
-      row_merge_direct<uint32_t, H, const uint32_t RANNC_GLOBAL *>(x, Vprev + (int64_t)i * DP + sig, tij, rmn, k);
+    row_merge_direct<uint32_t, H, InPlaceRow>(w, InPlaceRow(), tij, r.rmn, k);
+    if (act) {
 #pragma unroll
-      for (int t = 0; t < H; ++t) acc[t] = vmin(acc[t], x[t]);
+      for (int t = 0; t < H; ++t) atomicMin(&tile[r.col * LS + t], w[t]);
     }
-    i += kMergeWaves;
   }
   return any;
 }
 
 // Waves per SIMD the level kernel is compiled for: the two value arrays of the widest 32-bit case
-// fit the 168 registers of three waves per SIMD (the compiler left alone takes one more); the
-// recomputing kernel also keeps a reciprocal per odd replica count in registers.
+// fit the 168 registers of three waves per SIMD (the compiler left alone takes one more).
 template <typename VT, int HMAX, bool DIRECT> constexpr int merge_waves_per_simd() {
-  if (sizeof(VT) == 8) return HMAX == 64 ? 3 : 1;
-  if (DIRECT) return HMAX >= 48 ? 2 : HMAX == 32 ? 4 : 1;
-  return HMAX == 64 ? 3 : 1;
+  return HMAX == 64 && !DIRECT ? 3 : 1;
 }
 
 // The rows i0+wave, i0+wave+4, ... <= i_hi of one work item, folded into acc (running minimum of the
@@ -867,16 +858,15 @@ __device__ __forceinline__ void level_merge_body(const ProblemDev &pr, const int
   VT RANNC_GLOBAL *Vcur = gptr((VT *)pr.V) + (int64_t)(s - 1) * (int64_t)(N + 1) * DP;
 
   // acc[t] = running minimum over this wave's rows of the sorted merge
-  constexpr bool ROWFOLD = sizeof(VT) == 8 && HMAX >= 48;
-  constexpr bool EARLY_TILE = ROWFOLD || DIRECT;  // rows fold into the tile while the row loop runs
+  constexpr bool ROWFOLD = DIRECT || (sizeof(VT) == 8 && HMAX >= 48);  // rows fold into the tile while the row loop runs
+  constexpr int NT = 64 * kMergeWaves;
   constexpr int LS = HMAX + 1;
   __shared__ VT tile[64 * LS];
   [[maybe_unused]] VT acc[HMAX];
-  if constexpr (EARLY_TILE) {
-    for (int e = threadIdx.x; e < 64 * LS; e += 64 * kMergeWaves) tile[e] = INF;
-    __syncthreads();
-  }
-  if constexpr (!ROWFOLD) {
+  if constexpr (ROWFOLD) {
+    for (int e = threadIdx.x; e < 64 * LS; e += NT) tile[e] = INF;
+    if constexpr (!DIRECT) __syncthreads();  // (the recomputing form meets at a barrier before its row loop)
+  } else {
 #pragma unroll
     for (int t = 0; t < HMAX; ++t) acc[t] = INF;
   }
@@ -885,10 +875,11 @@ __device__ __forceinline__ void level_merge_body(const ProblemDev &pr, const int
   if constexpr (DIRECT) {
     DirectConsts k;
     direct_consts_init(k);
-#define RANNC_ROWS(K)                                                                          \
+    __shared__ __align__(16) ItemRows<HMAX> rows_in;
+#define RANNC_ROWS(K)                                                                            \
   case K:                                                                                      \
     if constexpr (8 * K <= HMAX)                                                               \
-      any = merge_rows_direct<8 * K, LS>(acc, tile, pr, s, c, i0, i_hi, lane, wave, k);        \
+      any = merge_rows_direct<8 * K, LS>(tile, rows_in, pr, s, c, i0, i_hi, lane, wave, k);      \
     break;
     switch (ng) {
       RANNC_ROWS(1) RANNC_ROWS(2) RANNC_ROWS(3) RANNC_ROWS(4)
@@ -915,8 +906,7 @@ __device__ __forceinline__ void level_merge_body(const ProblemDev &pr, const int
   if constexpr (ROWFOLD) {
     if (__syncthreads_or(any) == 0) return;
   } else {
-    if constexpr (!EARLY_TILE)
-      for (int e = threadIdx.x; e < 64 * LS; e += 64 * kMergeWaves) tile[e] = INF;
+    for (int e = threadIdx.x; e < 64 * LS; e += NT) tile[e] = INF;
     if (__syncthreads_or(any) == 0) return;
     if (any) {
 #pragma unroll
@@ -927,7 +917,7 @@ __device__ __forceinline__ void level_merge_body(const ProblemDev &pr, const int
   }
   const int sig = merge_shift(s, DP, 8 * ng);
   constexpr int WT = HMAX > 32 ? 64 : HMAX > 16 ? 32 : HMAX;  // threads per column
-  constexpr int RPP = 64 * kMergeWaves / WT;                  // columns per pass
+  constexpr int RPP = NT / WT;                                // columns per pass
   const int t = threadIdx.x & (WT - 1);
   if (t >= HMAX || t + 1 + sig > D - 1) return;
   for (int row = threadIdx.x / WT; row < 64; row += RPP) {
@@ -1739,13 +1729,14 @@ int merge_grid_items(const LaunchShape &sh, int rows_per_item, int slots, bool p
     const int64_t launch_rows = merge_launch_rows(sh);
     rows = launch_rows >= kMergeRows16From ? 16 : launch_rows >= kMergeRows8From ? 8 : kMergeMinRows;
     // A launch of the recomputing form over several searches with many rounds of workgroups: the
-    // largest items that still leave three rounds if nothing is pruned, the same size for every
-    // search of the launch.  Clearing the tile, the fold and the atomics are paid per item, and with
-    // three rounds the partly filled last one costs little (config 5: 16 -> 64 rows, 157 -> 115 us
-    // per level; the table form, bound by its reads, gains nothing: 100 -> 107 us at 32 devices).
+    // largest items that still fill the device one and a quarter times if nothing is pruned, the same
+    // size for every search of the launch.  Copying the rows in, clearing the tile and the atomics are
+    // paid per item (config 5: 16 -> 64 rows, 157 -> 115 us per level when an item held its minimum in
+    // registers; six workgroups per compute unit at 32 devices since: one and a quarter rounds 2.13 ms
+    // for all levels, two 2.13, three 2.25; over ragged batches of 100 to 1 500 searches within 5 %).
     if (paired && sh.nprob > 1 && items_at(rows) * sh.nprob > slots)
       for (int r = 64; r > rows; r -= 4)
-        if (items_at(r) * sh.nprob >= 3ll * slots) { rows = r; *rows_for_list = r; break; }
+        if (4 * items_at(r) * sh.nprob >= 5ll * slots) { rows = r; *rows_for_list = r; break; }
   }
   return (int)items_at(rows);
 }
@@ -1760,7 +1751,7 @@ hipError_t launch_runs(const ProblemDev *probs, int Q, int rows_per_item, int ma
 // registers of its four waves, one per SIMD; see the kernel's resource usage).
 int merge_workgroups_per_cu(int bits, int DP, bool recompute) {
   if (bits == 32) {
-    if (recompute) return DP == 64 ? 2 : DP == 32 ? 4 : DP == 16 ? 5 : 8;
+    if (recompute) return DP == 64 ? 4 : DP == 32 ? 6 : 8;
     return DP == 64 ? 3 : DP == 32 ? 4 : DP == 16 ? 6 : 8;
   }
   return DP == 64 ? 2 : DP == 32 ? 3 : DP == 16 ? 4 : 8;
@@ -1774,11 +1765,14 @@ hipError_t launch_windows(const ProblemDev *probs, const LaunchShape &sh, hipStr
   return hipGetLastError();
 }
 
-constexpr int kBuildRowsFitOnly = 8;  // rows per wave when only the fits-in-memory part is built
+constexpr int kBuildRowsFitOnly = 8;  // rows per wave when only the fits-in-memory part is built ...
+constexpr int kBuildFewWaves = 1024;  // ... by at least this many waves
 
 template <typename VT, int DP>
 static void build_go(const ProblemDev *p, const LaunchShape &sh, int parts, hipStream_t st) {
-  const int rows = (parts & 2) ? 1 : kBuildRowsFitOnly;
+  // (a small launch is a wave's latency: one row each while that leaves compute units without a workgroup)
+  const int64_t waves8 = (int64_t)sh.nprob * sh.max_nch * ((sh.max_N + kBuildRowsFitOnly - 1) / kBuildRowsFitOnly);
+  const int rows = (parts & 2) || waves8 < kBuildFewWaves ? 1 : kBuildRowsFitOnly;
   const int per_group = kBuildWaves * rows;
   for (int q0 = 0; q0 < sh.nprob; q0 += 65535) {
     const int nq = min(65535, sh.nprob - q0);
