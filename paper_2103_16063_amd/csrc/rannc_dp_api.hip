@@ -547,22 +547,17 @@ int rannc_dp_solve(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream, i
     const ProblemDev *cp = dp + cls_start[k];
     const hipStream_t st = cs[k];  // this class's stream
     if (fused[k]) continue;
-    ok = rannc::launch_prefix(cp, sh.nprob, st) == hipSuccess;
-    ok = ok && rannc::launch_fill(cp, sh.nprob, st) == hipSuccess;
-    ok = ok && rannc::launch_build(cp, sh, h->bits, kClasses[k], recompute_cls[k] ? 1 : 3, st) == hipSuccess;
-    ok = ok && rannc::launch_windows(cp, sh, st) == hipSuccess;  // also used by traceback
-    if (split) {
-      ok = ok && rannc::launch_split_level1(cp, sh, h->bits, st) == hipSuccess;
-      if (split_fast) ok = ok && rannc::launch_runs(cp, sh.nprob, rannc::split_rows_per_item(sh, h->n_cus), 0, 0, false, st) == hipSuccess;
-    }
-    if (scan || split) continue;
     // Rows per item of the level kernel: chosen on the device from the size of the windows unless
     // the handle fixes it, or the host does for a launch of many rounds (merge_grid_items).
     const int slots = h->n_cus * rannc::merge_workgroups_per_cu(h->bits, kClasses[k], recompute_cls[k]);
     int rows_for_list = -1;
-    merge_items[k] = rannc::merge_grid_items(sh, rannc::merge_rows_per_item(h->tune_spw), slots, recompute_cls[k],
-                                             &rows_for_list);
-    ok = ok && rannc::launch_runs(cp, sh.nprob, rows_for_list, merge_items[k], slots, recompute_cls[k], st) == hipSuccess;
+    if (split) rows_for_list = rannc::split_rows_per_item(sh, h->n_cus);
+    else
+      merge_items[k] = rannc::merge_grid_items(sh, rannc::merge_rows_per_item(h->tune_spw), slots, recompute_cls[k],
+                                               &rows_for_list);
+    ok = rannc::launch_setup(cp, sh.nprob, rows_for_list, merge_items[k], slots, recompute_cls[k], st) == hipSuccess;
+    ok = ok && rannc::launch_build(cp, sh, h->bits, kClasses[k], recompute_cls[k] ? 1 : 3, st) == hipSuccess;
+    if (split) ok = ok && rannc::launch_split_level1(cp, sh, h->bits, st) == hipSuccess;
   }
   if (timing) ok = ok && hipEventRecord(h->ev[1], st) == hipSuccess;
   int max_levels = 0;

@@ -106,26 +106,24 @@ struct LaunchShape {
 
 // Kernel launchers (rannc_dp_kernels.hip, rannc_dp_split.hip, rannc_dp_compact.hip).  All enqueue on `st` and return the launch status.
 // `probs` points at the first ProblemDev of the launch; problems of one launch are contiguous.
-hipError_t launch_prefix(const ProblemDev *probs, int Q, hipStream_t st);
-hipError_t launch_fill(const ProblemDev *probs, int Q, hipStream_t st);
 // parts: 1 = fits-in-memory tables (rmin, ufit) and level 1 of V, 2 = the stage-time table, 3 = both
 hipError_t launch_build(const ProblemDev *probs, const LaunchShape &sh, int bits, int DP, int parts, hipStream_t st);
-hipError_t launch_windows(const ProblemDev *probs, const LaunchShape &sh, hipStream_t st);
+// prefix sums, validation, initial V, windows and work list of the searches of a launch.
 // rows_per_item: > 0 fixed, 0 chosen on the device for the split-objective kernel, -1 for the
 // sorted-merge kernel (then the smallest item size whose item count fits max_items)
 // slots: workgroups of the level kernel that the device holds at a time
 // paired: the list for the level kernel that recomputes the stage times (diagonal blocks as row pairs)
-hipError_t launch_runs(const ProblemDev *probs, int Q, int rows_per_item, int max_items, int slots, bool paired,
-                       hipStream_t st);
+hipError_t launch_setup(const ProblemDev *probs, int Q, int rows_per_item, int max_items, int slots, bool paired,
+                        hipStream_t st);
 int merge_workgroups_per_cu(int bits, int DP, bool recompute);
 int merge_rows_per_item(int rows_per_wave);
-// rows_for_list: what launch_runs is to be given as rows_per_item (the size the host fixed, or -1)
+// rows_for_list: what launch_setup is to be given as rows_per_item (the size the host fixed, or -1)
 int merge_grid_items(const LaunchShape &sh, int rows_per_item, int slots, bool paired, int *rows_for_list);
 // rows of the searches of a launch if nothing is pruned (every chunk c holds rows 0 .. 64c+63)
 int64_t merge_launch_rows(const LaunchShape &sh);
 // recompute: the level kernel computes the stage times from the prefix sums instead of reading
 // their table (32-bit values only)
-// items: merge_grid_items of the launch, the value launch_runs was given
+// items: merge_grid_items of the launch, the value launch_setup was given
 // host_one: for a launch over one search, a host copy of its descriptor (passed by value), or null
 hipError_t launch_level_merge(const ProblemDev *probs, const LaunchShape &sh, int bits, int s,
                               bool recompute, int items, const ProblemDev *host_one, hipStream_t st);
@@ -145,7 +143,7 @@ hipError_t launch_level_scan(const ProblemDev *probs, const LaunchShape &sh, int
 hipError_t launch_split_level1(const ProblemDev *probs, const LaunchShape &sh, int bits, hipStream_t st);
 hipError_t launch_level_split(const ProblemDev *probs, const LaunchShape &sh, int bits, int s, int write_v,
                               int32_t *arg_i, int32_t *arg_d, hipStream_t st);
-// needs the key table and the work list made by launch_runs(..., split_rows_per_item(), ...); with
+// needs the key table and the work list made by launch_setup(..., split_rows_per_item(), ...); with
 // 64-bit tables only for time bounds up to kSplitPackedMax (the packed winner holds 42 value bits)
 constexpr int64_t kSplitPackedMax = (1LL << 42) - 2;
 // rows per work item: 1 or 2 for a launch whose rows (unpruned) then still fit one round of workgroups

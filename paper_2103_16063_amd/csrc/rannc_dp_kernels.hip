@@ -14,115 +14,6 @@
 namespace rannc {
 
 // ---------------------------------------------------------------------------------------
-// Prefix sums T, P, A of the block inputs (the sums over a stage's members that stand in
-// for profile(), Sec. IV-D) and input validation.  One workgroup per problem.
-// ---------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void prefix_kernel(const ProblemDev *__restrict__ probs) {
-  const ProblemDev pr = probs[blockIdx.x];
-  __shared__ uint64_t part[4][256];
-  __shared__ int flags;
-  __shared__ unsigned long long max_cut;
-  const int N = pr.N, tid = threadIdx.x;
-  const int seg = (N + 255) / 256;
-  const int lo = min(tid * seg, N), hi = min(lo + seg, N);
-  if (tid == 0) { flags = 0; max_cut = 0ull; }
-  __syncthreads();
-  const int64_t *in[4] = {pr.t, pr.p, pr.a, pr.tb};
-  int64_t *out[4] = {pr.T, pr.P, pr.A, pr.TB};
-  const int nw = pr.tb ? 4 : 3;  // backward times only with the split objective
-  int myflags = 0;
-#pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    if (w >= nw) break;
-    uint64_t s = 0;
-    for (int k = lo; k < hi; ++k) {
-      int64_t v = in[w][k];
-      if (v < 0) { myflags |= 1; v = 0; }
-      uint64_t u = (uint64_t)v;
-      if (u >= kSumLimit) { myflags |= 2; u = kSumLimit; }
-      s = s + u; if (s > kSumLimit) s = kSumLimit;
-    }
-    part[w][tid] = s;
-  }
-  __syncthreads();
-  // inclusive scan of the 256 segment sums (saturating add is associative on [0, limit])
-  for (int off = 1; off < 256; off <<= 1) {
-    uint64_t add[4];
-#pragma unroll
-    for (int w = 0; w < 4; ++w) add[w] = (w < nw && tid >= off) ? part[w][tid - off] : 0;
-    __syncthreads();
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      if (w >= nw) break;
-      uint64_t v = part[w][tid] + add[w];
-      part[w][tid] = v > kSumLimit ? kSumLimit : v;
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    if (w >= nw) break;
-    uint64_t run = tid ? part[w][tid - 1] : 0;  // sum of the segments before this thread's
-    if (tid == 0) out[w][0] = 0;
-    for (int k = lo; k < hi; ++k) {
-      int64_t v = in[w][k];
-      uint64_t u = v < 0 ? 0 : (uint64_t)v;
-      if (u > kSumLimit) u = kSumLimit;
-      run += u; if (run > kSumLimit) run = kSumLimit;
-      if (run >= kSumLimit) myflags |= 2;
-      out[w][k + 1] = (int64_t)run;
-    }
-  }
-  if (pr.o) {  // per-cut send time; the last block has no follower
-    unsigned long long mc = 0ull;
-    if (tid == 0) pr.C[0] = 0;
-    for (int k = lo; k < hi; ++k) {
-      const uint64_t c = cut_time(pr.o[k], pr.bw, myflags);
-      pr.C[k + 1] = (k + 1 < N) ? (int64_t)c : 0;
-      if (k + 1 < N && c > mc) mc = c;
-    }
-    if (mc) atomicMax(&max_cut, mc);
-  }
-  if (myflags) atomicOr(&flags, myflags);
-  __syncthreads();
-  if (tid == 0) {
-    int st = RANNC_DP_PROBLEM_OK;
-    if (flags & 1) st = RANNC_DP_PROBLEM_NEGATIVE_INPUT;
-    else if (flags & 2) st = RANNC_DP_PROBLEM_SUM_OVERFLOW;
-    else if ((uint64_t)pr.T[N] + (pr.tb ? (uint64_t)pr.TB[N] : 0ull) + max_cut > (uint64_t)pr.time_limit)
-      st = RANNC_DP_PROBLEM_TIME_TOO_LARGE;  // a value is at most forward + send + backward time of all blocks
-    *pr.status = st;
-  }
-}
-
-// ---------------------------------------------------------------------------------------
-// Initial state: every V entry "no plan" (padding columns d > D hold 0 so that padded rows stay
-// sorted).
-// ---------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void fill_kernel(const ProblemDev *__restrict__ probs) {
-  const ProblemDev pr = probs[blockIdx.y];
-  const int64_t total = (int64_t)pr.S_eff * (pr.N + 1) * pr.DP;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (pr.keys) {  // packed winners of the split level kernel: "none"
-    const int64_t nk = (int64_t)(pr.N + 1) * pr.DP;
-    for (int64_t e = t0; e < nk; e += stride) ((unsigned long long *)pr.keys)[e] = ~0ull;
-  }
-  void *tabs[3] = {pr.V, pr.VF, pr.VB};
-  for (int w = 0; w < (pr.VF ? 3 : 1); ++w) {
-    if (pr.bits == 32) {
-      uint32_t *V = (uint32_t *)tabs[w];
-      for (int64_t e = t0; e < total; e += stride)
-        V[e] = ((int)(e & (pr.DP - 1)) < pr.D) ? Lim<uint32_t>::inf : 0u;
-    } else {
-      uint64_t *V = (uint64_t *)tabs[w];
-      for (int64_t e = t0; e < total; e += stride)
-        V[e] = ((int)(e & (pr.DP - 1)) < pr.D) ? Lim<uint64_t>::inf : 0ull;
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------------------
 // Stage-time and fits-in-memory tables: h(i,j,r) and the m(i,j,r) <= M rule of Sec. III-C for
 // every stage (i,j) and replica count r.  One wave per unit (row i, 64-column chunk c), four
 // rows per workgroup; a lane
@@ -303,27 +194,17 @@ void build_kernel(const ProblemDev *__restrict__ probs, const int parts, const i
 }
 
 // ---------------------------------------------------------------------------------------
+// Everything a search needs in front of its tables, one launch: prefix sums T, P, A of the block
+// inputs (the sums over a stage's members that stand in for profile(), Sec. IV-D), input validation,
+// the windows and the work list of the level kernels (workgroup 0 of a search), and the initial state
+// of V (the other workgroups of the search).
+//
 // Window of the level kernels: wlo[c] = first row i that holds a stage into chunk c that fits for
-// some r <= D (0x7fffffff if none).  Rows below it are never visited.  One workgroup per
-// (chunk, problem); no global atomics (same-address atomics serialise badly).
-// ---------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void windows_kernel(const ProblemDev *__restrict__ probs) {
-  const ProblemDev &pr = probs[blockIdx.y];
-  const int c = blockIdx.x, nch = pr.nch;
-  if (c >= nch) return;
-  __shared__ int first;
-  if (threadIdx.x == 0) first = kNoRow;
-  __syncthreads();
-  const int hi = min(64 * c + 63, pr.N - 1);
-  int mine = kNoRow;
-  for (int i = threadIdx.x; i <= hi; i += 256)
-    if (pr.ufit[unit_index(nch, i, c)]) { mine = i; break; }  // rows ascend
-  if (mine != kNoRow) atomicMin(&first, mine);
-  __syncthreads();
-  if (threadIdx.x == 0) pr.wlo[c] = first;
-}
-
-// ---------------------------------------------------------------------------------------
+// some r <= D (0x7fffffff if none).  Rows below it are never visited.  Memory grows with the stage,
+// so row i <= 64c has such a stage iff the one that ends at the chunk's first column fits, and if row
+// 64c has one then so has every row from the first such row on: a binary search.  (If the chunk's
+// first block fits no device by itself, the first later block that does starts the window.)
+//
 // Work list of the level kernels: the rows wlo[c] .. min(64c+63, N-1) of every chunk, cut into
 // items of consecutive rows, listed chunk by chunk.  A compact list keeps the workgroups that have
 // work at the front of the grid.  The number of rows of an item travels in the top bits of its
@@ -338,18 +219,25 @@ __global__ __launch_bounds__(256) void windows_kernel(const ProblemDev *__restri
 // brings it down to one round is taken instead, provided the round still fills half the device:
 // the round is then as full as it can be, and no compute unit is left with one workgroup more
 // than its neighbours.  (For a launch of many rounds, hundreds of searches, the host fixes the item
-// size for all of them: merge_grid_items.)  One workgroup per problem.
-// ---------------------------------------------------------------------------------------
+// size for all of them: merge_grid_items.)
 // paired (the level kernel that recomputes the stage times): inside the diagonal block of a chunk
 // (rows 64c .. 64c+63, where row 64c+p has work only in the lanes from p on) the list holds the
 // rows p = 0 .. 32 only; the kernel treats row 64c+p as the PAIR of rows 64c+p and 64c+64-p, whose
 // lanes with work add up to exactly one wave.  The rows in front of the block and the listed rows
 // of the block form two segments, and no item crosses from one into the other; the last item of a
 // segment carries the number of rows that are left.
+//
+// Bound by latency (a chain of a few memory round trips and barriers).  As four launches, with the
+// windows found by scanning a flag per unit that the table builder had written, this took 15 us on the
+// device at 96 blocks and 24 us at 1024, and every launch costs the host 3 us more.
+// ---------------------------------------------------------------------------------------
+constexpr int kSetupThreads = 256;
+constexpr int kSetupLdsN = 1024;  // up to this many blocks the windows are searched in LDS
+
 struct RunSegments { int lo0, n0, lo1, n1; };
-__device__ __forceinline__ RunSegments run_segments(const ProblemDev &pr, int c, int paired) {
+__device__ __forceinline__ RunSegments run_segments(const ProblemDev &pr, int c, int lo, int paired) {
   RunSegments g;
-  const int lo = pr.wlo[c], hi = min(64 * c + 63, pr.N - 1);
+  const int hi = min(64 * c + 63, pr.N - 1);
   g.lo0 = lo; g.n0 = lo <= hi ? hi - lo + 1 : 0; g.lo1 = 0; g.n1 = 0;
   if (paired && lo <= hi && hi >= 64 * c) {
     const int w = max(lo, 64 * c) - 64 * c, hmax = hi - 64 * c;  // window start and last row inside the block
@@ -363,17 +251,192 @@ __device__ __forceinline__ RunSegments run_segments(const ProblemDev &pr, int c,
   return g;
 }
 
-__global__ __launch_bounds__(256) void runs_kernel(const ProblemDev *__restrict__ probs, int rows, int max_items,
-                                                    int batch, int slots, int paired) {
-  const ProblemDev &pr = probs[blockIdx.x];
+// whether bytes P (not divided) + ceil(A / D) fit M
+__device__ __forceinline__ bool fits_at(uint64_t P, uint64_t A, uint64_t M, int D) {
+  if (P > M) return false;
+  const uint64_t slack = M - P;
+  return A <= slack * (uint64_t)D || __umul64hi(slack, (uint64_t)D) != 0;  // ceil(A/D) <= slack  <=>  A <= slack D
+}
+
+// inclusive sums over the workgroup, saturating at the limit (associative on [0, limit]), of NW values per thread
+template <int NW> __device__ __forceinline__ void setup_scan(uint64_t (&v)[NW], uint64_t (*part)[NW]) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const uint64_t x = __shfl_up(v[w], o);
+      if (lane >= o) v[w] = min(v[w] + x, kSumLimit);
+    }
+  }
+  if (lane == 63)
+#pragma unroll
+    for (int w = 0; w < NW; ++w) part[wave][w] = v[w];
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kSetupThreads / 64 - 1; ++k)
+    if (k < wave)
+#pragma unroll
+      for (int w = 0; w < NW; ++w) v[w] = min(v[w] + part[k][w], kSumLimit);
+}
+
+__device__ void setup_fill(const ProblemDev &pr, int64_t t0, int64_t stride) {
+  // every V entry "no plan" (padding columns d > D hold 0 so that padded rows stay sorted)
+  typedef uint32_t Quad __attribute__((ext_vector_type(4)));
+  if (pr.keys) {  // packed winners of the split level kernel: "none"
+    const int64_t nk = (int64_t)(pr.N + 1) * pr.DP;
+    for (int64_t e = t0; e < nk; e += stride) ((unsigned long long *)pr.keys)[e] = ~0ull;
+  }
+  void *tabs[3] = {pr.V, pr.VF, pr.VB};
+  const int words = pr.DP * (pr.bits / 32), used = pr.D * (pr.bits / 32);  // of a row, 32-bit
+  const int64_t quads = (int64_t)pr.S_eff * (pr.N + 1) * words / 4;
+  for (int w = 0; w < (pr.VF ? 3 : 1); ++w) {
+    Quad RANNC_GLOBAL *V = (Quad RANNC_GLOBAL *)gptr((uint32_t *)tabs[w]);
+    for (int64_t e = t0; e < quads; e += stride) {
+      const int at = (int)((4 * e) & (words - 1));
+      Quad q;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t inf = pr.bits == 32 ? Lim<uint32_t>::inf : (k & 1) ? (uint32_t)(Lim<uint64_t>::inf >> 32) : 0u;
+        q[k] = at + k < used ? inf : 0u;
+      }
+      V[e] = q;
+    }
+  }
+}
+
+__global__ __launch_bounds__(kSetupThreads) void setup_kernel(const ProblemDev *__restrict__ probs, int rows,
+                                                             int max_items, int batch, int slots, int paired) {
+  const ProblemDev &pr = probs[blockIdx.y];
+  const int N = pr.N, tid = threadIdx.x;
+  if (blockIdx.x > 0) {
+    setup_fill(pr, (int64_t)(blockIdx.x - 1) * kSetupThreads + tid, (int64_t)(gridDim.x - 1) * kSetupThreads);
+    return;
+  }
+  constexpr int U = 4;  // entries per thread and tile
+  __shared__ uint64_t part[kSetupThreads / 64][4], last[4];
+  __shared__ uint64_t sP[kSetupLdsN + 1], sA[kSetupLdsN + 1];
+  __shared__ int flags;
+  __shared__ unsigned long long max_cut;
+  if (tid == 0) { flags = 0; max_cut = 0ull; sP[0] = 0; sA[0] = 0; }
+  const int64_t RANNC_GLOBAL *in[4] = {gptr(pr.t), gptr(pr.p), gptr(pr.a), gptr(pr.tb)};
+  int64_t RANNC_GLOBAL *out[4] = {gptr(pr.T), gptr(pr.P), gptr(pr.A), gptr(pr.TB)};
+  const bool bwd = pr.tb != nullptr;  // backward times only with the split objective
+  const bool in_lds = N <= kSetupLdsN;
+  int myflags = 0;
+  if (tid == 0) {
+    out[0][0] = out[1][0] = out[2][0] = 0;
+    if (bwd) out[3][0] = 0;
+    if (pr.o) pr.C[0] = 0;
+  }
+  uint64_t carry[4] = {0, 0, 0, 0};
+  unsigned long long mc = 0ull;
+  for (int base = 0; base < N; base += U * kSetupThreads) {
+    const int k0 = base + U * tid;
+    uint64_t v[4][U], sum[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+      if (w < 3 || bwd)
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[w][u] = (uint64_t)in[w][min(k0 + u, N - 1)];
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+      if (w < 3 || bwd)
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          uint64_t x = k0 + u < N ? v[w][u] : 0;
+          if ((int64_t)x < 0) { myflags |= 1; x = 0; }
+          if (x >= kSumLimit) { myflags |= 2; x = kSumLimit; }
+          v[w][u] = x;
+          sum[w] = min(sum[w] + x, kSumLimit);
+        }
+    uint64_t run[4] = {sum[0], sum[1], sum[2], sum[3]};
+    __syncthreads();  // (part and last are free again)
+    setup_scan<4>(run, part);
+    if (tid == kSetupThreads - 1)
+#pragma unroll
+      for (int w = 0; w < 4; ++w) last[w] = run[w];
+    // back to the sum in front of this thread's entries: from the neighbour's inclusive sum
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+      if (w < 3 || bwd) {
+        uint64_t at = __shfl_up(run[w], 1);
+        if ((tid & 63) == 0) {
+          at = 0;
+          for (int k = 0; k < (tid >> 6); ++k) at = min(at + part[k][w], kSumLimit);
+        }
+        at = min(at + carry[w], kSumLimit);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          at = min(at + v[w][u], kSumLimit);
+          if (k0 + u < N) {
+            if (at >= kSumLimit) myflags |= 2;
+            out[w][k0 + u + 1] = (int64_t)at;
+            if (in_lds && w == 1) sP[k0 + u + 1] = at;
+            if (in_lds && w == 2) sA[k0 + u + 1] = at;
+          }
+        }
+      }
+    if (pr.o) {  // per-cut send time; the last block has no follower
+      for (int u = 0; u < U; ++u) {
+        const int k = k0 + u;
+        if (k >= N) break;
+        const uint64_t c = cut_time(pr.o[k], pr.bw, myflags);
+        pr.C[k + 1] = (k + 1 < N) ? (int64_t)c : 0;
+        if (k + 1 < N && c > mc) mc = c;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < 4; ++w) carry[w] = min(carry[w] + last[w], kSumLimit);
+  }
+  if (mc) atomicMax(&max_cut, mc);
+  if (myflags) atomicOr(&flags, myflags);
+  __syncthreads();  // the sums in memory are visible to the whole workgroup as well
+  if (tid == 0) {
+    int st = RANNC_DP_PROBLEM_OK;
+    if (flags & 1) st = RANNC_DP_PROBLEM_NEGATIVE_INPUT;
+    else if (flags & 2) st = RANNC_DP_PROBLEM_SUM_OVERFLOW;
+    else if (carry[0] + (bwd ? carry[3] : 0ull) + max_cut > (uint64_t)pr.time_limit)
+      st = RANNC_DP_PROBLEM_TIME_TOO_LARGE;  // a value is at most forward + send + backward time of all blocks
+    *pr.status = st;
+  }
+
+  // ---- windows ----
   __shared__ int start[1025];  // nch <= 1024 (N <= 65535)
-  __shared__ RunSegments seg[1024];  // every chunk's segments, computed once (one read of wlo per chunk)
+  __shared__ RunSegments seg[1024];  // every chunk's segments
   constexpr int NC = 16;  // candidate item sizes 4, 8, ..., 64 rows
   __shared__ int total_rows, count[NC];
-  const int nch = pr.nch, tid = threadIdx.x;
-  int32_t *const runs = pr.runs;  // (read once: the stores below would make the compiler fetch it again)
-  for (int c = tid; c < nch; c += 256) seg[c] = run_segments(pr, c, paired);
+  const int nch = pr.nch, D = pr.D;
+  const uint64_t M = (uint64_t)pr.M;
+  auto window = [&](auto P, auto A) {
+    for (int c = tid; c < nch; c += kSetupThreads) {
+      const int j = 64 * c + 1;  // the chunk's first column, for the rows up to 64c
+      const uint64_t Pj = P[j], Aj = A[j];
+      int lo = 64 * c;
+      if (fits_at(Pj - P[lo], Aj - A[lo], M, D)) {
+        int below = -1;  // the largest row known not to fit
+        while (lo - below > 1) {
+          const int mid = (lo + below) >> 1;
+          if (fits_at(Pj - P[mid], Aj - A[mid], M, D)) lo = mid;
+          else below = mid;
+        }
+      } else {
+        const int hi = min(64 * c + 63, N - 1);
+        for (++lo; lo <= hi; ++lo)
+          if (fits_at(P[lo + 1] - P[lo], A[lo + 1] - A[lo], M, D)) break;
+        if (lo > hi) lo = kNoRow;
+      }
+      pr.wlo[c] = lo;
+      seg[c] = run_segments(pr, c, lo, paired);
+    }
+  };
+  if (in_lds) window((const uint64_t *)sP, (const uint64_t *)sA);
+  else window((const uint64_t RANNC_GLOBAL *)out[1], (const uint64_t RANNC_GLOBAL *)out[2]);
   __syncthreads();
+
+  // ---- work list ----
+  int32_t *const runs = pr.runs;  // (read once: the stores below would make the compiler fetch it again)
   if (rows <= 0) {
     if (tid < NC) count[tid] = 0;
     if (tid == 0) total_rows = 0;
@@ -382,7 +445,7 @@ __global__ __launch_bounds__(256) void runs_kernel(const ProblemDev *__restrict_
     {
       const int k = tid % NC, r = 4 * (k + 1);
       int mine = 0, cnt = 0;
-      for (int c = tid / NC; c < nch; c += 256 / NC) {
+      for (int c = tid / NC; c < nch; c += kSetupThreads / NC) {
         const RunSegments g = seg[c];
         mine += g.n0 + g.n1;
         cnt += (g.n0 + r - 1) / r + (g.n1 + r - 1) / r;
@@ -419,7 +482,7 @@ __global__ __launch_bounds__(256) void runs_kernel(const ProblemDev *__restrict_
   // per chunk: items of the two segments, and their rows dealt evenly over them (33 rows in items
   // of up to 16: three items of 11, not 16 + 16 + 1); seg[c] is reused for {items0, per0, lo1, per1}
   __shared__ int n0_of[1024], n1_of[1024];
-  for (int c = tid; c < nch; c += 256) {
+  for (int c = tid; c < nch; c += kSetupThreads) {
     const RunSegments g = seg[c];
     const int items0 = (g.n0 + rows - 1) / rows, items1 = (g.n1 + rows - 1) / rows;
     start[c + 1] = items0 + items1;  // items of chunk c
@@ -432,13 +495,14 @@ __global__ __launch_bounds__(256) void runs_kernel(const ProblemDev *__restrict_
   }
   __syncthreads();
   if (tid == 0) {
+    int sum = 0;
     start[0] = 0;
-    for (int c = 0; c < nch; ++c) start[c + 1] += start[c];
-    runs[0] = start[nch];
+    for (int c = 1; c <= nch; ++c) { sum += start[c]; start[c] = sum; }
+    runs[0] = sum;
   }
   __syncthreads();
   const int total = start[nch];
-  for (int e = tid; e < total; e += 256) {
+  for (int e = tid; e < total; e += kSetupThreads) {
     int lo = 0, hi = nch - 1;  // the chunk whose items contain e: start[c] <= e < start[c + 1]
     while (lo < hi) {
       const int mid = (lo + hi) >> 1;
@@ -1003,14 +1067,14 @@ void solve_small_kernel(
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-  // ---- prefix sums and validation (as prefix_kernel) ----
+  // ---- prefix sums and validation (as setup_kernel) ----
   if (tid == 0) {
     s_flags = 0; s_wlo[0] = kNoRow; s_wlo[1] = kNoRow; s_max_cut = 0ull; sC[0] = 0;
     if (pr.o) pr.C[0] = 0;
   }
   int myflags = 0;
   __syncthreads();
-  if (tid < N && pr.o) {  // per-cut send time (as prefix_kernel)
+  if (tid < N && pr.o) {  // per-cut send time (as setup_kernel)
     const uint64_t c = cut_time(pr.o[tid], pr.bw, myflags);
     sC[tid + 1] = (tid + 1 < N) ? (int64_t)c : 0;
     pr.C[tid + 1] = sC[tid + 1];  // plan recovery values the stages from the prefix sums in memory
@@ -1679,16 +1743,13 @@ __global__ __launch_bounds__(256) void arg_init_kernel(const ProblemDev *__restr
 // ---------------------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------------------
-hipError_t launch_prefix(const ProblemDev *probs, int Q, hipStream_t st) {
-  hipLaunchKernelGGL(prefix_kernel, dim3(Q), dim3(256), 0, st, probs);
-  return hipGetLastError();
-}
-
-hipError_t launch_fill(const ProblemDev *probs, int Q, hipStream_t st) {
-  const int per = Q >= 256 ? 4 : Q >= 16 ? 32 : 256;
+hipError_t launch_setup(const ProblemDev *probs, int Q, int rows_per_item, int max_items, int slots, bool paired,
+                        hipStream_t st) {
+  const int fill = Q >= 256 ? 4 : Q >= 16 ? 16 : 128;  // workgroups that fill a search's V
   for (int q0 = 0; q0 < Q; q0 += 65535) {
     const int nq = min(65535, Q - q0);
-    hipLaunchKernelGGL(fill_kernel, dim3(per, nq), dim3(256), 0, st, probs + q0);
+    hipLaunchKernelGGL(setup_kernel, dim3(1 + fill, nq), dim3(kSetupThreads), 0, st, probs + q0, rows_per_item, max_items,
+                       Q, slots, paired ? 1 : 0);
   }
   return hipGetLastError();
 }
@@ -1741,12 +1802,6 @@ int merge_grid_items(const LaunchShape &sh, int rows_per_item, int slots, bool p
   return (int)items_at(rows);
 }
 
-hipError_t launch_runs(const ProblemDev *probs, int Q, int rows_per_item, int max_items, int slots, bool paired,
-                       hipStream_t st) {
-  hipLaunchKernelGGL(runs_kernel, dim3(Q), dim3(256), 0, st, probs, rows_per_item, max_items, Q, slots, paired ? 1 : 0);
-  return hipGetLastError();
-}
-
 // Workgroups of the sorted-merge level kernel that one compute unit holds at a time (by the
 // registers of its four waves, one per SIMD; see the kernel's resource usage).
 int merge_workgroups_per_cu(int bits, int DP, bool recompute) {
@@ -1755,14 +1810,6 @@ int merge_workgroups_per_cu(int bits, int DP, bool recompute) {
     return DP == 64 ? 3 : DP == 32 ? 4 : DP == 16 ? 6 : 8;
   }
   return DP == 64 ? 2 : DP == 32 ? 3 : DP == 16 ? 4 : 8;
-}
-
-hipError_t launch_windows(const ProblemDev *probs, const LaunchShape &sh, hipStream_t st) {
-  for (int q0 = 0; q0 < sh.nprob; q0 += 65535) {
-    const int nq = min(65535, sh.nprob - q0);
-    hipLaunchKernelGGL(windows_kernel, dim3(sh.max_nch, nq), dim3(256), 0, st, probs + q0);
-  }
-  return hipGetLastError();
 }
 
 constexpr int kBuildRowsFitOnly = 8;  // rows per wave when only the fits-in-memory part is built ...
