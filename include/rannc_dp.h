@@ -178,8 +178,8 @@ RANNC_DP_API int rannc_dp_create(const rannc_dp_limits_t *limits, void *d_worksp
  *   d_est_iter_ns DEVICE int64[Q] or NULL: (MB + s* - 1) * opt, the fill-and-drain time of one
  *                synchronous pipeline iteration (Fig. 1), saturating at INT64_MAX
  *   d_status     DEVICE int32[Q] or NULL: RANNC_DP_PROBLEM_* per problem
- * Searches of different device-count classes (D <= 8, 16, 32, 64) of one batch may run on streams
- * of the handle; they start after the work already on hip_stream and hip_stream is made to wait
+ * Searches of different device-count classes (D <= 8, 16, 32, 64) of one batch of more than 64 searches
+ * may run on streams of the handle (smaller batches run as one group); they start after the work already on hip_stream and hip_stream is made to wait
  * for them, so for the caller everything is ordered on hip_stream as if it ran there.
  * Host-side argument errors are returned before anything is enqueued. */
 RANNC_DP_API int rannc_dp_solve(rannc_dp_t *h, const rannc_dp_batch_t *batch, void *hip_stream,
@@ -193,6 +193,21 @@ RANNC_DP_API int rannc_dp_solve(rannc_dp_t *h, const rannc_dp_batch_t *batch, vo
  * plan_stride must be >= min(S_q,N_q,D_q) for every problem of the batch. */
 RANNC_DP_API int rannc_dp_traceback(rannc_dp_t *h, void *hip_stream, int32_t plan_stride,
                        int32_t *d_stage_end, int32_t *d_replicas);
+
+/* rannc_dp_solve and rannc_dp_traceback as one call that returns with the results in host memory (a
+ * program that wants the plan next pays for fewer launches, no copies, and no wait for the stream's
+ * own completion).  Both buffers hold, Q = n_problems, each array at the next multiple of 8 bytes:
+ *   int64 opt[Q], int64 est_iter_ns[Q], int32 n_stages[Q], int32 status[Q],
+ *   int32 stage_end[Q*plan_stride], int32 replicas[Q*plan_stride]
+ * with the meaning they have above.
+ *   d_results  DEVICE, h_results HOST (pinned memory is copied to faster in large batches), 8-byte aligned,
+ *              results_bytes bytes each
+ * Synchronous: everything before it on hip_stream has completed when it returns.  Its first use on a
+ * handle (and any later use with a larger batch) allocates pinned host memory, freed by destroy.
+ * Errors as rannc_dp_solve and rannc_dp_traceback; INVALID_ARG if results_bytes is too small. */
+RANNC_DP_API int rannc_dp_solve_to_host(rannc_dp_t *h, const rannc_dp_batch_t *batch, void *hip_stream,
+                                        int32_t plan_stride, void *d_results, void *h_results,
+                                        size_t results_bytes);
 
 /* As rannc_dp_traceback, but for problem q the plan of EXACTLY d_levels[q] stages is recovered
  * (Algorithm 1's own answer for a given S: the boundaries and replica counts behind V[S][|B|][D]) when

@@ -35,7 +35,7 @@ EXPORTS = ["rannc_dp_workspace_bytes", "rannc_dp_workspace_bytes_for", "rannc_dp
            "rannc_dp_traceback_at", "rannc_dp_level_values", "rannc_dp_form_stage_problems",
            "rannc_dp_form_stage_scratch_bytes", "rannc_dp_form_stage",
            "rannc_dp_compact_workspace_bytes", "rannc_dp_compact", "rannc_dp_compact_static",
-           "rannc_dp_solve_info"]
+           "rannc_dp_solve_info", "rannc_dp_solve_to_host"]
 
 
 class Limits(C.Structure):
@@ -127,6 +127,8 @@ def lib():
         L.rannc_dp_form_stage.argtypes = [vp, C.POINTER(FormStageIn), vp, vp, sz,
                                           C.POINTER(FormStageOut), vp, vp, C.c_int32]
         L.rannc_dp_form_stage.restype = C.c_int
+        L.rannc_dp_solve_to_host.argtypes = [vp, C.POINTER(Batch), vp, C.c_int32, vp, vp, sz]
+        L.rannc_dp_solve_to_host.restype = C.c_int
         L.rannc_dp_solve_info.argtypes = [vp, C.POINTER(SolveInfo)]
         L.rannc_dp_solve_info.restype = C.c_int
         L.rannc_dp_compact_workspace_bytes.argtypes = [C.c_int32]
@@ -212,6 +214,12 @@ def rannc_dp_solve(handle, batch: HostBatch, stream, d_opt, d_n_stages, d_est_it
     return lib().rannc_dp_solve(handle, C.byref(batch.struct) if batch is not None else None,
                                 _ptr(stream), _ptr(d_opt), _ptr(d_n_stages), _ptr(d_est_iter_ns),
                                 _ptr(d_status))
+
+
+def rannc_dp_solve_to_host(handle, batch: HostBatch, stream, plan_stride: int, d_results, h_results,
+                           results_bytes: int) -> int:
+    return lib().rannc_dp_solve_to_host(handle, C.byref(batch.struct) if batch is not None else None, _ptr(stream),
+                                        int(plan_stride), _ptr(d_results), _ptr(h_results), int(results_bytes))
 
 
 def rannc_dp_traceback(handle, stream, plan_stride: int, d_stage_end, d_replicas) -> int:
@@ -365,7 +373,9 @@ class Session:
             return (cut(0, torch.int64, (Q,)), cut(1, torch.int64, (Q,)), cut(2, torch.int32, (Q,)),
                     cut(3, torch.int32, (Q,)), cut(4, torch.int32, (Q, PS)), cut(5, torch.int32, (Q, PS)))
         self.d_opt, self.d_est, self.d_ns, self.d_status, self.d_se, self.d_rp = views(self._out_dev)
-        self._h_views = views(self._out_host)
+        self._h_views = [v.numpy() for v in views(self._out_host)]
+        self._to_host = (self.h, C.byref(self.hb.struct), self.plan_stride, self._out_dev.data_ptr(),
+                         self._out_host.data_ptr(), int(offs[-1]))
 
     def stream(self):
         return self.torch.cuda.current_stream(self.dev).cuda_stream
@@ -382,12 +392,12 @@ class Session:
             raise RanncDpError(rc, "rannc_dp_traceback")
 
     def run(self):
-        """solve + traceback + ONE copy of all results to (pinned) host memory."""
-        self.solve()
-        self.traceback()
-        self._out_host.copy_(self._out_dev, non_blocking=True)
-        self.torch.cuda.current_stream(self.dev).synchronize()
-        opt, est, ns, status, se, rp = (v.numpy().copy() for v in self._h_views)
+        """solve + traceback with all results in host memory, as one call."""
+        h, batch, stride, d_out, h_out, nbytes = self._to_host
+        rc = lib().rannc_dp_solve_to_host(h, batch, self.stream(), stride, d_out, h_out, nbytes)
+        if rc != OK:
+            raise RanncDpError(rc, "rannc_dp_solve_to_host")
+        opt, est, ns, status, se, rp = (v.copy() for v in self._h_views)
         return {"opt": opt, "n_stages": ns, "est_iter_ns": est, "status": status, "stage_end": se, "replicas": rp}
 
     def table(self, which: int, q: int) -> np.ndarray:

@@ -32,10 +32,22 @@ struct Sizes {  // bytes of one problem's regions inside the workspace
   }
 };
 
+// A batch of at most this many searches runs as ONE group: its V rows are padded to the widest
+// device-count class of the batch, so that every launch covers all of its searches.  Few searches do
+// not fill the device, a level costs what a launch costs, and a launch per class and level costs the
+// host 3 us each (outer driver at 512 blocks, three classes: 75 launches for 31 levels).  The merges are
+// as wide as each search's level needs anyway.
+constexpr int kOneGroupMax = 64;
+int group_dp(const rannc_dp_batch_t *b) {
+  if (b->n_problems > kOneGroupMax) return 0;
+  int D = 1;
+  for (int q = 0; q < b->n_problems; ++q) D = std::max(D, b->n_devices[q]);
+  return rannc::dp_class(D);
+}
+
 // false on arithmetic overflow
-bool problem_sizes(int N, int D, int S_eff, int bits, bool split, bool packed, Sizes *o) {
+bool problem_sizes(int N, int D, int DP, int S_eff, int bits, bool split, bool packed, Sizes *o) {
   const int nch = (N + 63) / 64;
-  const int DP = rannc::dp_class(D);
   const size_t esz = bits / 8;
   const unsigned __int128 rows = (unsigned __int128)rannc::units_before(nch, N) * 64;
   const unsigned __int128 cost = rows * (unsigned)D * esz;
@@ -102,6 +114,7 @@ struct rannc_dp {
   size_t ws_bytes;
   // pinned staging for the per-problem descriptors and problem lists, reused round-robin
   char *staging[kStagingSlots];
+  char *staging_dev[kStagingSlots];  // the address the device reads it through, or null
   hipEvent_t staging_free[kStagingSlots];
   bool staging_used[kStagingSlots];
   size_t staging_bytes;
@@ -121,6 +134,10 @@ struct rannc_dp {
   // the others run on streams of the handle (default priority), forked from and joined to the
   // caller's stream with events.  Off while per-phase timing is on (the phases are timed on the
   // caller's stream) and with RANNC_DP_STREAMS=0.
+  char *res_pin;         // pinned host mirror of a batch's results, written by the kernels (grown on demand)
+  char *res_pin_dev;     // its device address
+  size_t res_pin_bytes;
+  uint64_t seq;          // of the calls that poll for their results
   char *fs_pin;          // pinned host mirror of the outer driver's device scratch (grown on demand)
   char *fs_pin_dev;      // the address the device reads and writes the mirror through, or null
   size_t fs_pin_bytes;
@@ -156,7 +173,9 @@ size_t rannc_dp_workspace_bytes(const rannc_dp_limits_t *l) {
   if (!limits_ok(l)) return 0;
   Sizes sz;
   const int S_eff = std::min(l->max_stages, std::min(l->max_blocks, l->max_devices));
-  if (!problem_sizes(l->max_blocks, l->max_devices, S_eff, bits_of(l), split_of(l), packed_of(l), &sz)) return 0;
+  if (!problem_sizes(l->max_blocks, l->max_devices, rannc::dp_class(l->max_devices), S_eff, bits_of(l), split_of(l),
+                     packed_of(l), &sz))
+    return 0;
   const unsigned __int128 tot =
       (unsigned __int128)sz.total() * (unsigned)l->max_problems + header_bytes(l->max_problems);
   if (tot > ((unsigned __int128)1 << 47)) return 0;
@@ -166,10 +185,13 @@ size_t rannc_dp_workspace_bytes(const rannc_dp_limits_t *l) {
 size_t rannc_dp_workspace_bytes_for(const rannc_dp_limits_t *l, const rannc_dp_batch_t *b) {
   if (!limits_ok(l) || check_batch(l, b) != RANNC_DP_OK) return 0;
   size_t tot = header_bytes(l->max_problems);
+  const int all = group_dp(b);
   for (int q = 0; q < b->n_problems; ++q) {
     Sizes sz;
     const int S_eff = std::min(b->max_stages[q], std::min(b->n_blocks[q], b->n_devices[q]));
-    if (!problem_sizes(b->n_blocks[q], b->n_devices[q], S_eff, bits_of(l), split_of(l), packed_of(l), &sz)) return 0;
+    if (!problem_sizes(b->n_blocks[q], b->n_devices[q], all ? all : rannc::dp_class(b->n_devices[q]), S_eff, bits_of(l),
+                       split_of(l), packed_of(l), &sz))
+      return 0;
     tot += sz.total();
     if (tot > ((size_t)1 << 47)) return 0;
   }
@@ -211,6 +233,10 @@ int rannc_dp_create(const rannc_dp_limits_t *l, void *d_workspace, size_t worksp
   h->fused_small = l->one_launch_small == 1 ? 0 : l->one_launch_small == 2 ? 2 : 1;
   if (const char *e = std::getenv("RANNC_DP_FUSED_SMALL")) h->fused_small = std::atoi(e);
   h->d_probs = (ProblemDev *)h->ws;
+  h->res_pin = nullptr;
+  h->res_pin_dev = nullptr;
+  h->res_pin_bytes = 0;
+  h->seq = 0;
   h->fs_pin = nullptr;
   h->fs_pin_dev = nullptr;
   h->fs_pin_bytes = 0;
@@ -221,8 +247,12 @@ int rannc_dp_create(const rannc_dp_limits_t *l, void *d_workspace, size_t worksp
   bool ok = true;
   for (int k = 0; k < kStagingSlots && ok; ++k) {
     h->staging_used[k] = false;
-    ok = hipHostMalloc((void **)&h->staging[k], h->staging_bytes, hipHostMallocDefault) == hipSuccess;
+    ok = hipHostMalloc((void **)&h->staging[k], h->staging_bytes, hipHostMallocMapped | hipHostMallocPortable) == hipSuccess;
     if (ok) ++made_staging;
+    if (ok && hipHostGetDevicePointer((void **)&h->staging_dev[k], h->staging[k], 0) != hipSuccess) {
+      (void)hipGetLastError();
+      h->staging_dev[k] = nullptr;
+    }
   }
   for (int k = 0; k < kStagingSlots && ok; ++k) {
     ok = hipEventCreateWithFlags(&h->staging_free[k], hipEventDisableTiming) == hipSuccess;
@@ -274,6 +304,7 @@ void rannc_dp_destroy(rannc_dp_t *h) {
   }
   (void)hipEventDestroy(h->fork_ev);
   if (h->fs_pin) (void)hipHostFree(h->fs_pin);
+  if (h->res_pin) (void)hipHostFree(h->res_pin);
   delete h;
 }
 
@@ -293,8 +324,10 @@ int rannc_dp_get_timing(rannc_dp_t *h, float *out_ms, int32_t *out_level_launche
   return RANNC_DP_OK;
 }
 
-int rannc_dp_solve(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream, int64_t *d_opt,
-                   int32_t *d_n_stages, int64_t *d_est_iter_ns, int32_t *d_status) {
+// chosen != null: the caller waits for the batch before the handle is used again, and the plan recovery
+// behind it can choose the stage counts; *chosen = whether that has been done here already.
+static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream, int64_t *d_opt, int32_t *d_n_stages,
+                      int64_t *d_est_iter_ns, int32_t *d_status, bool *chosen) {
   if (!h || !d_opt || !d_n_stages) return RANNC_DP_INVALID_ARG;
   int rc = check_batch(&h->lim, b);
   if (rc != RANNC_DP_OK) return rc;
@@ -315,16 +348,20 @@ int rannc_dp_solve(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream, i
   } catch (...) {
     return RANNC_DP_NO_HOST_MEMORY;
   }
+  // (a handle told to run every small search as one launch keeps the classes apart: the form of that
+  // kernel depends on the class)
+  const int all = h->fused_small == 2 ? 0 : group_dp(b);
+  auto dp_of = [&](int q) { return all ? all : rannc::dp_class(b->n_devices[q]); };
   int cls_start[5] = {0, 0, 0, 0, 0};
   for (int q = 0; q < Q; ++q)
     for (int k = 0; k < 4; ++k)
-      if (rannc::dp_class(b->n_devices[q]) == kClasses[k]) ++cls_start[k + 1];
+      if (dp_of(q) == kClasses[k]) ++cls_start[k + 1];
   for (int k = 0; k < 4; ++k) cls_start[k + 1] += cls_start[k];
   {
     int next[4] = {cls_start[0], cls_start[1], cls_start[2], cls_start[3]};
     for (int q = 0; q < Q; ++q)
       for (int k = 0; k < 4; ++k)
-        if (rannc::dp_class(b->n_devices[q]) == kClasses[k]) pos_of[q] = next[k]++;
+        if (dp_of(q) == kClasses[k]) pos_of[q] = next[k]++;
   }
 
   // ---- workspace layout -------------------------------------------------------------
@@ -335,12 +372,12 @@ int rannc_dp_solve(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream, i
     const int N = b->n_blocks[q], D = b->n_devices[q];
     const int S_eff = std::min(b->max_stages[q], std::min(N, D));
     Sizes sz;
-    if (!problem_sizes(N, D, S_eff, h->bits, split, packed_of(&h->lim), &sz)) return RANNC_DP_OVERFLOW;
+    if (!problem_sizes(N, D, dp_of(q), S_eff, h->bits, split, packed_of(&h->lim), &sz)) return RANNC_DP_OVERFLOW;
     if (off + sz.total() > h->ws_bytes) return RANNC_DP_WORKSPACE_TOO_SMALL;
     ProblemDev &p = probs[pos_of[q]];
     std::memset(&p, 0, sizeof(p));
     p.N = N; p.D = D; p.S_eff = S_eff; p.MB = b->n_microbatches[q];
-    p.DP = rannc::dp_class(D);
+    p.DP = dp_of(q);
     p.nch = (N + 63) / 64;
     p.bits = h->bits;
     p.q = q;
@@ -394,15 +431,26 @@ int rannc_dp_solve(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream, i
   const size_t probs_bytes = (size_t)Q * sizeof(ProblemDev);
   std::memcpy(h->staging[slot], probs.data(), probs_bytes);
   h->solved = false;
-  if (hipMemcpyAsync(h->ws, h->staging[slot], probs_bytes, hipMemcpyHostToDevice, st) != hipSuccess ||
-      hipEventRecord(h->staging_free[slot], st) != hipSuccess) {
-    (void)hipGetLastError();
-    return RANNC_DP_HIP_ERROR;
+  // one group: its first launch reads the descriptors out of the staging memory and stores them
+  const bool in_place = all != 0 && h->staging_dev[slot] != nullptr;
+  h->staging_used[slot] = false;
+  if (!in_place) {
+    if (hipMemcpyAsync(h->ws, h->staging[slot], probs_bytes, hipMemcpyHostToDevice, st) != hipSuccess ||
+        hipEventRecord(h->staging_free[slot], st) != hipSuccess) {
+      (void)hipGetLastError();
+      return RANNC_DP_HIP_ERROR;
+    }
+    h->staging_used[slot] = true;
   }
-  h->staging_used[slot] = true;
+  auto staging_read = [&]() -> bool {  // behind the launch that has read the staging memory
+    if (!in_place || chosen) return true;  // (a caller that waits has the slot back by then)
+    h->staging_used[slot] = hipEventRecord(h->staging_free[slot], st) == hipSuccess;
+    return h->staging_used[slot];
+  };
 
   // ---- kernels ---------------------------------------------------------------------------
-  const ProblemDev *dp = h->d_probs;
+  ProblemDev *const dp = h->d_probs;
+  const ProblemDev *const src = in_place ? (const ProblemDev *)h->staging_dev[slot] : dp;
   const bool scan = h->lim.algo == RANNC_DP_ALGO_SCAN;
   // split objective: packed-key kernel wherever a cell's winner fits a 64-bit word (all 32-bit
   // handles, 64-bit ones up to 2^42 - 2 ns); RANNC_DP_ALGO_SCAN and larger time bounds take the
@@ -544,7 +592,7 @@ int rannc_dp_solve(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream, i
   for (int k = 0; k < 4 && ok; ++k) {
     const LaunchShape &sh = shape[k];
     if (!sh.nprob) continue;
-    const ProblemDev *cp = dp + cls_start[k];
+    ProblemDev *cp = dp + cls_start[k];
     const hipStream_t st = cs[k];  // this class's stream
     if (fused[k]) continue;
     // Rows per item of the level kernel: chosen on the device from the size of the windows unless
@@ -555,7 +603,9 @@ int rannc_dp_solve(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream, i
     else
       merge_items[k] = rannc::merge_grid_items(sh, rannc::merge_rows_per_item(h->tune_spw), slots, recompute_cls[k],
                                                &rows_for_list);
-    ok = rannc::launch_setup(cp, sh.nprob, rows_for_list, merge_items[k], slots, recompute_cls[k], st) == hipSuccess;
+    ok = rannc::launch_setup(src + cls_start[k], cp, sh.nprob, rows_for_list, merge_items[k], slots, recompute_cls[k], st) ==
+         hipSuccess;
+    ok = ok && staging_read();
     ok = ok && rannc::launch_build(cp, sh, h->bits, kClasses[k], recompute_cls[k] ? 1 : 3, st) == hipSuccess;
     if (split) ok = ok && rannc::launch_split_level1(cp, sh, h->bits, st) == hipSuccess;
   }
@@ -563,8 +613,9 @@ int rannc_dp_solve(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream, i
   int max_levels = 0;
   for (int k = 0; k < 4; ++k) {
     if (fused[k]) {
-      ok = ok && rannc::launch_solve_small(dp + cls_start[k], shape[k].nprob, h->bits, kClasses[k], fused_direct[k], d_opt,
+      ok = ok && rannc::launch_solve_small(src + cls_start[k], dp + cls_start[k], shape[k].nprob, h->bits, kClasses[k], fused_direct[k], d_opt,
                                            d_n_stages, d_est_iter_ns, d_status, cs[k]) == hipSuccess;
+      ok = ok && staging_read();
       h->level_launches++;
     } else {
       max_levels = std::max(max_levels, shape[k].max_S_eff);
@@ -593,8 +644,11 @@ int rannc_dp_solve(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream, i
     }
   }
   if (timing) ok = ok && hipEventRecord(h->ev[2], st) == hipSuccess;
+  bool choose_later = chosen && all && !timing;
+  for (int k = 0; k < 4; ++k) choose_later = choose_later && !(shape[k].nprob && fused[k]);
+  if (chosen) *chosen = !choose_later;
   for (int k = 0; k < 4 && ok; ++k)
-    if (shape[k].nprob && !fused[k])
+    if (shape[k].nprob && !fused[k] && !choose_later)
       ok = rannc::launch_select(dp + cls_start[k], shape[k].nprob, d_opt, d_n_stages, d_est_iter_ns,
                                 d_status, cs[k]) == hipSuccess;
   for (int a = 0; a < n_aux && ok; ++a)  // join: the caller's stream continues after every class
@@ -608,22 +662,35 @@ int rannc_dp_solve(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream, i
     return RANNC_DP_HIP_ERROR;
   }
   h->ev_valid = timing;
+  int kernel_of[4];
   for (int k = 0; k < 4; ++k) {
     h->no_times[k] = fused[k] ? fused_direct[k] : recompute_cls[k];
-    h->info.n_problems[k] = shape[k].nprob;
-    h->info.level_kernel[k] = !shape[k].nprob ? RANNC_DP_KERNEL_NONE
-                              : fused[k]      ? (fused_direct[k] ? RANNC_DP_KERNEL_ONE_LAUNCH_RECOMPUTE : RANNC_DP_KERNEL_ONE_LAUNCH)
-                              : split_fast    ? RANNC_DP_KERNEL_SPLIT
-                              : split         ? RANNC_DP_KERNEL_SPLIT_SCAN
-                              : scan          ? RANNC_DP_KERNEL_SCAN
-                              : recompute_cls[k] ? RANNC_DP_KERNEL_MERGE_RECOMPUTE
-                                                 : RANNC_DP_KERNEL_MERGE_TABLE;
+    kernel_of[k] = fused[k]           ? (fused_direct[k] ? RANNC_DP_KERNEL_ONE_LAUNCH_RECOMPUTE : RANNC_DP_KERNEL_ONE_LAUNCH)
+                   : split_fast       ? RANNC_DP_KERNEL_SPLIT
+                   : split            ? RANNC_DP_KERNEL_SPLIT_SCAN
+                   : scan             ? RANNC_DP_KERNEL_SCAN
+                   : recompute_cls[k] ? RANNC_DP_KERNEL_MERGE_RECOMPUTE
+                                      : RANNC_DP_KERNEL_MERGE_TABLE;
+    h->info.n_problems[k] = 0;
+    h->info.level_kernel[k] = RANNC_DP_KERNEL_NONE;
+  }
+  for (int q = 0; q < Q; ++q) {  // reported by the searches' own classes, also where they ran as one group
+    int own = 0, ran = 0;
+    while (kClasses[own] != rannc::dp_class(b->n_devices[q])) ++own;
+    while (kClasses[ran] != dp_of(q)) ++ran;
+    h->info.n_problems[own]++;
+    h->info.level_kernel[own] = kernel_of[ran];
   }
   h->host_probs.swap(probs);
   h->pos_of.swap(pos_of);
   h->Q = Q;
   h->solved = true;
   return RANNC_DP_OK;
+}
+
+int rannc_dp_solve(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream, int64_t *d_opt,
+                   int32_t *d_n_stages, int64_t *d_est_iter_ns, int32_t *d_status) {
+  return solve_impl(h, b, hip_stream, d_opt, d_n_stages, d_est_iter_ns, d_status, nullptr);
 }
 
 constexpr int kTracebackStagedMaxProblems = 64;
@@ -637,10 +704,10 @@ int rannc_dp_solve_info(rannc_dp_t *h, rannc_dp_solve_info_t *out) {
   return RANNC_DP_OK;
 }
 
-// rec: the outer driver's result record on the device (the chosen search's plan is also written
-// behind it), or null
 static int traceback_impl(rannc_dp_t *h, void *hip_stream, const int32_t *d_levels, int32_t plan_stride,
-                          int32_t *d_stage_end, int32_t *d_replicas, int64_t *d_rec) {
+                          int32_t *d_stage_end, int32_t *d_replicas,
+                          const rannc::FormStageIn *form_stage,
+                          const rannc::PlanResults *results = nullptr, bool choose = false) {
   if (!h || !d_stage_end || !d_replicas || plan_stride < 1) return RANNC_DP_INVALID_ARG;
   if (!h->solved) return RANNC_DP_BAD_STATE;
   // A few small min-max searches: the walk runs out of LDS (one round of reads instead of one
@@ -656,8 +723,8 @@ static int traceback_impl(rannc_dp_t *h, void *hip_stream, const int32_t *d_leve
     lds_bytes = std::max(lds_bytes, need);
   }
   if (!staged) lds_bytes = 0;
-  if (rannc::launch_traceback(h->d_probs, h->Q, plan_stride, d_stage_end, d_replicas, d_levels, lds_bytes, d_rec,
-                              (hipStream_t)hip_stream) != hipSuccess) {
+  if (rannc::launch_traceback(h->d_probs, h->Q, plan_stride, d_stage_end, d_replicas, d_levels, lds_bytes, form_stage,
+                              results, choose, (hipStream_t)hip_stream) != hipSuccess) {
     (void)hipGetLastError();
     return RANNC_DP_HIP_ERROR;
   }
@@ -672,6 +739,121 @@ int rannc_dp_traceback_at(rannc_dp_t *h, void *hip_stream, const int32_t *d_leve
 int rannc_dp_traceback(rannc_dp_t *h, void *hip_stream, int32_t plan_stride, int32_t *d_stage_end,
                        int32_t *d_replicas) {
   return rannc_dp_traceback_at(h, hip_stream, nullptr, plan_stride, d_stage_end, d_replicas);
+}
+
+// ---- solve + plan recovery + results in host memory, as one call --------------------------------
+namespace {
+
+// Waits until every flag word holds seq: the last kernel of the call stores them behind its results
+// in pinned host memory, which the host sees some microseconds before the stream reports completion.
+// The stream is asked now and then, so that a failed launch ends the wait.
+int wait_flags(hipStream_t st, const uint64_t *flags, int n, uint64_t seq) {
+  for (int q = 0; q < n; ++q) {
+    for (unsigned spins = 1; __atomic_load_n(&flags[q], __ATOMIC_ACQUIRE) != seq; ++spins) {
+      __builtin_ia32_pause();
+      if (spins % 8192) continue;
+      const hipError_t e = hipStreamQuery(st);
+      if (e == hipErrorNotReady) { (void)hipGetLastError(); continue; }
+      if (e != hipSuccess || __atomic_load_n(&flags[q], __ATOMIC_ACQUIRE) != seq) {
+        (void)hipGetLastError();
+        return RANNC_DP_HIP_ERROR;
+      }
+    }
+  }
+  // (the runtime retires a stream's finished commands when it is asked to wait)
+  if (seq % 64 == 0 && hipStreamSynchronize(st) != hipSuccess) {
+    (void)hipGetLastError();
+    return RANNC_DP_HIP_ERROR;
+  }
+  return RANNC_DP_OK;
+}
+
+struct ResultLayout {  // offsets of the arrays of one result buffer
+  size_t opt, est, n_stages, status, stage_end, replicas, total;
+  ResultLayout(size_t Q, size_t stride) {
+    auto a8 = [](size_t x) { return (x + 7) / 8 * 8; };
+    opt = 0;
+    est = opt + 8 * Q;
+    n_stages = est + 8 * Q;
+    status = n_stages + a8(4 * Q);
+    stage_end = status + a8(4 * Q);
+    replicas = stage_end + a8(4 * Q * stride);
+    total = replicas + a8(4 * Q * stride);
+  }
+};
+
+// batches of up to this many searches write their results to host memory themselves
+constexpr int kPollMaxProblems = 64;
+
+}  // namespace
+
+int rannc_dp_solve_to_host(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream, int32_t plan_stride,
+                           void *d_results, void *h_results, size_t results_bytes) {
+  if (!h || !b || !d_results || !h_results || plan_stride < 1 || ((uintptr_t)d_results % 8) || ((uintptr_t)h_results % 8))
+    return RANNC_DP_INVALID_ARG;
+  int rc = check_batch(&h->lim, b);
+  if (rc != RANNC_DP_OK) return rc;
+  const int Q = b->n_problems;
+  for (int q = 0; q < Q; ++q)
+    if (std::min(b->max_stages[q], std::min(b->n_blocks[q], b->n_devices[q])) > plan_stride) return RANNC_DP_INVALID_ARG;
+  const ResultLayout at((size_t)Q, (size_t)plan_stride);
+  if (results_bytes < at.total) return RANNC_DP_INVALID_ARG;
+  hipStream_t st = (hipStream_t)hip_stream;
+  char *d = (char *)d_results;
+  rannc::PlanResults r = {};
+  r.d_opt = (int64_t *)(d + at.opt); r.d_est = (int64_t *)(d + at.est);
+  r.d_n_stages = (int32_t *)(d + at.n_stages); r.d_status = (int32_t *)(d + at.status);
+  r.d_stage_end = (int32_t *)(d + at.stage_end); r.d_replicas = (int32_t *)(d + at.replicas);
+  bool poll = Q <= kPollMaxProblems;
+  const size_t need = at.total + 8 * (size_t)Q;
+  if (poll && h->res_pin_bytes < need) {
+    if (h->res_pin) {  // (no earlier call is under way: they all waited)
+      (void)hipHostFree(h->res_pin);
+      h->res_pin = nullptr;
+      h->res_pin_bytes = 0;
+    }
+    if (hipHostMalloc((void **)&h->res_pin, need, hipHostMallocMapped | hipHostMallocPortable) != hipSuccess) {
+      (void)hipGetLastError();
+      h->res_pin = nullptr;
+      return RANNC_DP_NO_HOST_MEMORY;
+    }
+    h->res_pin_bytes = need;
+    std::memset(h->res_pin, 0, need);
+    if (hipHostGetDevicePointer((void **)&h->res_pin_dev, h->res_pin, 0) != hipSuccess) {
+      (void)hipGetLastError();
+      h->res_pin_dev = nullptr;
+    }
+  }
+  poll = poll && h->res_pin_dev;
+  uint64_t *flags = nullptr;
+  if (poll) {
+    char *m = h->res_pin_dev;
+    r.h_opt = (int64_t *)(m + at.opt); r.h_est = (int64_t *)(m + at.est);
+    r.h_n_stages = (int32_t *)(m + at.n_stages); r.h_status = (int32_t *)(m + at.status);
+    r.h_stage_end = (int32_t *)(m + at.stage_end); r.h_replicas = (int32_t *)(m + at.replicas);
+    r.h_flag = (uint64_t *)(m + at.total);
+    r.seq = ++h->seq;
+    flags = (uint64_t *)(h->res_pin + at.total);
+  }
+  bool chosen = false;
+  rc = solve_impl(h, b, hip_stream, r.d_opt, r.d_n_stages, r.d_est, r.d_status, &chosen);
+  if (rc == RANNC_DP_OK)
+    rc = traceback_impl(h, hip_stream, nullptr, plan_stride, r.d_stage_end, r.d_replicas, nullptr, &r, !chosen);
+  if (rc == RANNC_DP_OK && !poll &&
+      (hipMemcpyAsync(h_results, d_results, at.total, hipMemcpyDeviceToHost, st) != hipSuccess ||
+       hipStreamSynchronize(st) != hipSuccess)) {
+    (void)hipGetLastError();
+    rc = RANNC_DP_HIP_ERROR;
+  }
+  if (rc != RANNC_DP_OK) {
+    (void)hipStreamSynchronize(st);  // the staging memory may be refilled by the next call
+    return rc;
+  }
+  if (!poll) return RANNC_DP_OK;
+  rc = wait_flags(st, flags, Q, r.seq);
+  if (rc != RANNC_DP_OK) return rc;
+  std::memcpy(h_results, h->res_pin, at.total);
+  return RANNC_DP_OK;
 }
 
 int rannc_dp_level_values(rannc_dp_t *h, void *hip_stream, int32_t stride, int64_t *d_values) {
@@ -775,7 +957,8 @@ int rannc_dp_form_stage(rannc_dp_t *h, const rannc_dp_form_stage_in_t *in, void 
   hipStream_t st = (hipStream_t)hip_stream;
   // pinned host mirror of the device scratch: same layout, so inputs go up and results come down
   // in one copy each
-  if (h->fs_pin_bytes < need) {
+  const size_t pin_need = need + 8;  // and the flag word behind it
+  if (h->fs_pin_bytes < pin_need) {
     if (h->fs_pin) {
       if (hipStreamSynchronize(st) != hipSuccess) return RANNC_DP_HIP_ERROR;  // an earlier call's copies
       (void)hipHostFree(h->fs_pin);
@@ -783,12 +966,13 @@ int rannc_dp_form_stage(rannc_dp_t *h, const rannc_dp_form_stage_in_t *in, void 
       h->fs_pin_dev = nullptr;
       h->fs_pin_bytes = 0;
     }
-    if (hipHostMalloc((void **)&h->fs_pin, need, hipHostMallocMapped | hipHostMallocPortable) != hipSuccess) {
+    if (hipHostMalloc((void **)&h->fs_pin, pin_need, hipHostMallocMapped | hipHostMallocPortable) != hipSuccess) {
       (void)hipGetLastError();
       h->fs_pin = nullptr;
       return RANNC_DP_NO_HOST_MEMORY;
     }
-    h->fs_pin_bytes = need;
+    h->fs_pin_bytes = pin_need;
+    std::memset(h->fs_pin, 0, pin_need);
     // the device's view of the mirror; without one the call copies in both directions
     if (hipHostGetDevicePointer((void **)&h->fs_pin_dev, h->fs_pin, 0) != hipSuccess) {
       (void)hipGetLastError();
@@ -867,7 +1051,7 @@ int rannc_dp_form_stage(rannc_dp_t *h, const rannc_dp_form_stage_in_t *in, void 
   const char *src = in_place ? pin_dev : dev;
   int64_t *d_opt = (int64_t *)(dev + o_opt);
   int32_t *d_ns = (int32_t *)(dev + o_ns), *d_st = d_ns + Q;
-  int32_t *d_lev = (int32_t *)(dev + o_lev), *d_se = (int32_t *)(dev + o_se), *d_rp = (int32_t *)(dev + o_rp);
+  int32_t *d_se = (int32_t *)(dev + o_se), *d_rp = (int32_t *)(dev + o_rp);
   const int32_t *d_pn = (const int32_t *)(src + o_pair), *d_pm = d_pn + Q;
   // the result record and the chosen plan behind it are written by the kernels straight into the
   // mirror (they only write it): no copy down, the wait for the stream is all that is left
@@ -881,28 +1065,32 @@ int rannc_dp_form_stage(rannc_dp_t *h, const rannc_dp_form_stage_in_t *in, void 
   b.bandwidth_bytes_per_us = comm ? hbw.data() : nullptr;
   b.cut_bytes = comm ? (const int64_t *)(src + o_o) : nullptr;
   b.time_bwd_ns = split ? (const int64_t *)(src + o_b) : nullptr;
-  // Everything on the device, in stream order: the batched search, Algorithm 2's loops over the
-  // values V[S][N][D] of every search and S (first n, then first S with a feasible MB; among those
-  // the smallest (MB + S - 1) * V, the first found among equals), and the plan of the chosen
-  // (n, MB, S), which the plan recovery also writes behind the record.  Three launches behind the
-  // search's own, one copy down, one wait.
-  h->call_total_bound = max_total < lim ? (int64_t)max_total : 0;
-  int rc = rannc_dp_solve(h, &b, hip_stream, d_opt, d_ns, nullptr, d_st);
-  h->call_total_bound = 0;
-  if (rc == RANNC_DP_OK &&
-      rannc::launch_form_stage_select(h->d_probs, Q, stride, N, in->n_nodes, in->devices_per_node, d_pn, d_pm,
-                                      d_lev, d_rec, st) != hipSuccess) {
-    (void)hipGetLastError();
-    rc = RANNC_DP_HIP_ERROR;
+  // Everything on the device, in stream order: the batched search, then one launch that runs Algorithm
+  // 2's loops over the values V[S][N][D] of every search and S (first n, then first S with a feasible
+  // MB; among those the smallest (MB + S - 1) * V, the first found among equals), recovers the plan of
+  // the chosen (n, MB, S) and writes record, plan and flag word into the mirror.
+  rannc::FormStageIn f = {};
+  f.Q = Q; f.N = N; f.devices_per_node = in->devices_per_node;
+  f.pair_n = d_pn; f.pair_mb = d_pm;
+  f.rec = d_rec;
+  if (pin_dev) {
+    f.flag = (uint64_t *)(pin_dev + need);
+    f.seq = ++h->seq;
   }
-  if (rc == RANNC_DP_OK) rc = traceback_impl(h, hip_stream, d_lev, stride, d_se, d_rp, d_rec);
+  bool chosen = false;
+  h->call_total_bound = max_total < lim ? (int64_t)max_total : 0;
+  int rc = solve_impl(h, &b, hip_stream, d_opt, d_ns, nullptr, d_st, &chosen);
+  h->call_total_bound = 0;
+  if (rc == RANNC_DP_OK) rc = traceback_impl(h, hip_stream, nullptr, stride, d_se, d_rp, &f);
   if (rc != RANNC_DP_OK) {
     (void)hipStreamSynchronize(st);  // the mirror may be refilled by the next call
     return rc;
   }
-  if ((!pin_dev && hipMemcpyAsync(pin + o_rec, dev + o_rec, 6 * 8 + (size_t)stride * 8, hipMemcpyDeviceToHost, st) !=
-                       hipSuccess) ||
-      hipStreamSynchronize(st) != hipSuccess) {
+  if (pin_dev) {
+    rc = wait_flags(st, (const uint64_t *)(pin + need), 1, f.seq);
+    if (rc != RANNC_DP_OK) return rc;
+  } else if (hipMemcpyAsync(pin + o_rec, dev + o_rec, 6 * 8 + (size_t)stride * 8, hipMemcpyDeviceToHost, st) != hipSuccess ||
+             hipStreamSynchronize(st) != hipSuccess) {
     (void)hipGetLastError();
     return RANNC_DP_HIP_ERROR;
   }

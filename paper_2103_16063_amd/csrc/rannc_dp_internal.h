@@ -96,6 +96,26 @@ struct ProblemDev {
   int64_t *res;                // res[0] = opt (int64, INT64_MAX if none), res[1] = n_stages
 };
 
+// Result arrays of a batch, on the device and (h_*, or null) in pinned host memory; h_flag[q] = seq is
+// stored behind the results of search q.
+struct PlanResults {
+  int64_t *d_opt, *d_est;
+  int32_t *d_n_stages, *d_status, *d_stage_end, *d_replicas;
+  int64_t *h_opt, *h_est;
+  int32_t *h_n_stages, *h_status, *h_stage_end, *h_replicas;
+  uint64_t *h_flag, seq;
+};
+
+// Outer driver: what Algorithm 2's loops over a solved batch need, and where the result goes (rec: 6
+// int64 {q, S, bad status, 0, V, estimate}, then 2*stride int32 of plan; device memory or pinned host
+// memory; flag (or null) = seq is stored behind it).
+struct FormStageIn {
+  int Q, N, devices_per_node;
+  const int32_t *pair_n, *pair_mb;  // node count and microbatch count of every search
+  int64_t *rec;
+  uint64_t *flag, seq;
+};
+
 struct LaunchShape {
   int nprob;     // problems in the launch (blockIdx.z runs over them)
   int max_N;     // largest N among them
@@ -113,7 +133,9 @@ hipError_t launch_build(const ProblemDev *probs, const LaunchShape &sh, int bits
 // sorted-merge kernel (then the smallest item size whose item count fits max_items)
 // slots: workgroups of the level kernel that the device holds at a time
 // paired: the list for the level kernel that recomputes the stage times (diagonal blocks as row pairs)
-hipError_t launch_setup(const ProblemDev *probs, int Q, int rows_per_item, int max_items, int slots, bool paired,
+// src: the descriptors, in device memory (probs itself) or in pinned host memory the device can read;
+// the launch then also stores them to probs
+hipError_t launch_setup(const ProblemDev *src, ProblemDev *probs, int Q, int rows_per_item, int max_items, int slots, bool paired,
                         hipStream_t st);
 int merge_workgroups_per_cu(int bits, int DP, bool recompute);
 int merge_rows_per_item(int rows_per_wave);
@@ -133,7 +155,8 @@ int small_max_blocks();
 // small_can_recompute says so, and only for searches without a communication term);
 // max_total_time: the largest total time a search of the launch can have without being flagged
 bool small_can_recompute(int bits, int DP, int64_t max_total_time);
-hipError_t launch_solve_small(const ProblemDev *probs, int Q, int bits, int DP, bool direct, int64_t *d_opt,
+// src: as in launch_setup
+hipError_t launch_solve_small(const ProblemDev *src, ProblemDev *probs, int Q, int bits, int DP, bool direct, int64_t *d_opt,
                               int32_t *d_n_stages, int64_t *d_est, int32_t *d_status, hipStream_t st);
 hipError_t launch_level_scan(const ProblemDev *probs, const LaunchShape &sh, int bits, int s,
                              int write_v, int32_t *arg_i, int32_t *arg_d, hipStream_t st);
@@ -159,10 +182,13 @@ hipError_t launch_select(const ProblemDev *probs, int Q, int64_t *d_opt, int32_t
 // launch must be a min-max search with traceback_lds_bytes(...) <= lds_bytes <= kTracebackLdsMax
 constexpr int kTracebackLdsMax = 150 * 1024;
 int64_t traceback_lds_bytes(int N, int DP, int S_eff, int bits);
-// rec != null: the plan of the search that rec[0] names is also written behind the six words of rec
+// form_stage != null: the outer driver's loops over the values of the batch are run first, and only the
+// plan of the search they choose is recovered, by one workgroup
+// results != null: choose = the stage count of every search is chosen here (launch_select is not
+// needed); h_flag != null = the results also go to the host's mirror
 hipError_t launch_traceback(const ProblemDev *probs, int Q, int plan_stride, int32_t *d_stage_end,
-                            int32_t *d_replicas, const int32_t *d_levels, int64_t lds_bytes, int64_t *rec,
-                            hipStream_t st);
+                            int32_t *d_replicas, const int32_t *d_levels, int64_t lds_bytes,
+                            const FormStageIn *form_stage, const PlanResults *results, bool choose, hipStream_t st);
 hipError_t launch_level_values(const ProblemDev *probs, int Q, int stride, int64_t *d_out, hipStream_t st);
 // compaction step of the block-level phase on a chain of G groups (one workgroup).  Short chains are
 // held in LDS; longer ones keep arrays of G + 1 entries in the workspace: three of 8 bytes and two of 4
@@ -181,11 +207,6 @@ constexpr size_t compact_workspace_bytes(int G) {
 hipError_t launch_compact(int G, int k, int64_t M, int max_walks, const int64_t *t, const int64_t *p,
                           const int64_t *a, void *ws, int32_t *n_out, int32_t *block_end, int64_t *t_out,
                           int64_t *p_out, int64_t *a_out, int32_t *status, hipStream_t st);
-// outer driver: Algorithm 2's loops over the values of a solved batch, and the chosen plan packed
-// behind the result record (rec: 6 int64 {q, S, bad status, 0, V, estimate}, then 2*stride int32)
-hipError_t launch_form_stage_select(const ProblemDev *probs, int Q, int stride, int N, int n_nodes,
-                                    int devices_per_node, const int32_t *pair_n, const int32_t *pair_mb,
-                                    int32_t *levels, int64_t *rec, hipStream_t st);
 hipError_t launch_export(const ProblemDev *prob, int which, int bits, void *d_dst, hipStream_t st);
 
 

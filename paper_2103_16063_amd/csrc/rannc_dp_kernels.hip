@@ -232,6 +232,28 @@ void build_kernel(const ProblemDev *__restrict__ probs, const int parts, const i
 // device at 96 blocks and 24 us at 1024, and every launch costs the host 3 us more.
 // ---------------------------------------------------------------------------------------
 constexpr int kSetupThreads = 256;
+
+// The descriptor of a search, by the first kernel that runs for it.  For a few searches the host does
+// not copy the descriptors to the device: `src` is its pinned staging memory, each workgroup fetches
+// its descriptor from there once, and the workgroup that owns the search (`keep`) stores it where the
+// later kernels read it (dst; src == dst: it is there already).  A copy in front of the first kernel
+// costs the host 6 us and the stream 4.  The words go through LDS into scalar registers, so that the
+// fields stay wave-uniform.  lds: sizeof(ProblemDev) bytes.
+__device__ __forceinline__ ProblemDev fetch_problem(const ProblemDev *src, ProblemDev *dst, bool keep, uint32_t *lds) {
+  constexpr int W = (int)sizeof(ProblemDev) / 4;
+  static_assert(W <= 64 && sizeof(ProblemDev) % 8 == 0, "a word per lane");
+  if (threadIdx.x < W / 2) {
+    const uint64_t w = ((const uint64_t *)src)[threadIdx.x];
+    ((uint64_t *)lds)[threadIdx.x] = w;
+    if (keep && src != dst) ((uint64_t *)dst)[threadIdx.x] = w;
+  }
+  __syncthreads();
+  const uint32_t mine = lds[min((int)(threadIdx.x & 63), W - 1)];
+  union { ProblemDev p; uint32_t u[W]; } x;
+#pragma unroll
+  for (int k = 0; k < W; ++k) x.u[k] = (uint32_t)__builtin_amdgcn_readlane((int)mine, k);
+  return x.p;
+}
 constexpr int kSetupLdsN = 1024;  // up to this many blocks the windows are searched in LDS
 
 struct RunSegments { int lo0, n0, lo1, n1; };
@@ -305,9 +327,10 @@ __device__ void setup_fill(const ProblemDev &pr, int64_t t0, int64_t stride) {
   }
 }
 
-__global__ __launch_bounds__(kSetupThreads) void setup_kernel(const ProblemDev *__restrict__ probs, int rows,
+__global__ __launch_bounds__(kSetupThreads) void setup_kernel(const ProblemDev *src, ProblemDev *probs, int rows,
                                                              int max_items, int batch, int slots, int paired) {
-  const ProblemDev &pr = probs[blockIdx.y];
+  __shared__ __align__(8) uint32_t desc[sizeof(ProblemDev) / 4];
+  const ProblemDev pr = fetch_problem(src + blockIdx.y, probs + blockIdx.y, blockIdx.x == 0, desc);
   const int N = pr.N, tid = threadIdx.x;
   if (blockIdx.x > 0) {
     setup_fill(pr, (int64_t)(blockIdx.x - 1) * kSetupThreads + tid, (int64_t)(gridDim.x - 1) * kSetupThreads);
@@ -1042,9 +1065,10 @@ template <typename VT, int DP, bool DIRECT> constexpr int small_waves_per_simd()
 template <typename VT, int DP, bool DIRECT>
 __global__ __launch_bounds__((64 * small_waves<VT, DP>())) __attribute__((amdgpu_waves_per_eu((small_waves_per_simd<VT, DP, DIRECT>()))))
 void solve_small_kernel(
-    const ProblemDev *__restrict__ probs, int64_t *d_opt, int32_t *d_n_stages, int64_t *d_est,
+    const ProblemDev *src, ProblemDev *probs, int64_t *d_opt, int32_t *d_n_stages, int64_t *d_est,
     int32_t *d_status) {
-  const ProblemDev &pr = probs[blockIdx.x];
+  __shared__ __align__(8) uint32_t desc[sizeof(ProblemDev) / 4];
+  const ProblemDev pr = fetch_problem(src + blockIdx.x, probs + blockIdx.x, true, desc);
   constexpr VT INF = Lim<VT>::inf;
   constexpr int LS = DP + 1;  // row stride of a level in LDS: lanes (= columns) hit different banks
   constexpr int kSmallWaves = small_waves<VT, DP>();
@@ -1410,11 +1434,10 @@ __device__ __forceinline__ void select_finish(const ProblemDev &pr, int64_t v, i
   if (d_status) d_status[q] = st;
 }
 
-__global__ __launch_bounds__(64) void select_kernel(const ProblemDev *__restrict__ probs,
-                                                    int64_t *d_opt, int32_t *d_n_stages,
-                                                    int64_t *d_est, int32_t *d_status) {
-  const ProblemDev &pr = probs[blockIdx.x];
-  const int lane = threadIdx.x;
+// one wave
+__device__ __forceinline__ void select_body(const ProblemDev &pr, int64_t *d_opt, int32_t *d_n_stages, int64_t *d_est,
+                                            int32_t *d_status) {
+  const int lane = threadIdx.x & 63;
   const int st = *pr.status;
   int64_t v = INT64_MAX;
   if (st == 0 && lane < pr.S_eff) {
@@ -1429,6 +1452,12 @@ __global__ __launch_bounds__(64) void select_kernel(const ProblemDev *__restrict
     }
   }
   select_finish(pr, v, st, d_opt, d_n_stages, d_est, d_status);
+}
+
+__global__ __launch_bounds__(64) void select_kernel(const ProblemDev *__restrict__ probs,
+                                                    int64_t *d_opt, int32_t *d_n_stages,
+                                                    int64_t *d_est, int32_t *d_status) {
+  select_body(probs[blockIdx.x], d_opt, d_n_stages, d_est, d_status);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1607,24 +1636,159 @@ __device__ void traceback_body(const ProblemDev &pr, int plan_stride, int32_t *s
 
 constexpr int kTracebackThreads = 1024;
 
-// The plan of the one search the outer driver chose (the only one whose entry of the level array is
-// not negative), copied behind its result record.  The record may live in host memory: it is only
-// written here.
-__device__ __forceinline__ void plan_to_record(int plan_stride, const int32_t *se, const int32_t *rp, int64_t *rec) {
-  __syncthreads();  // the walk's stores, by this workgroup's first thread, are visible to all of it
-  int32_t *plan = (int32_t *)(rec + 6);
-  for (int u = threadIdx.x; u < plan_stride; u += blockDim.x) {
-    plan[u] = se[u];
-    plan[plan_stride + u] = rp[u];
+// Outer driver (Algorithm 2 "form_stage" of Sec. III-C), the loops over the solved batch: node
+// counts n = 1, 2, 4, ... in turn, for each the stage counts S ascending over
+// (devices_per_node*(n-1), devices_per_node*n], and for the first S that any search of that n can
+// realise (V[S][N][D] finite), the search with the smallest (MB + S - 1) * V, the first one in
+// batch order among equals.  That is the lexicographic minimum of (n, S, estimate, search index)
+// over all feasible (search, S) pairs, S inside the range of the search's n: one wave, a lane per
+// search (in rounds of 64) reads its values straight from the value tables (all reads of a lane
+// are independent), then one reduction over the wave.
+// Writes the record {q, S, first bad status in batch order or 0, 0, V, estimate} and the plan area
+// behind it (-1 everywhere; the plan recovery, in the same launch, fills in the chosen search's).
+// q = -1: infeasible.  Returns the chosen search's place in probs (-1: none) and its S.
+struct FormStageChoice { int at, S; };
+__device__ __forceinline__ FormStageChoice form_stage_choose(const ProblemDev *__restrict__ probs, const FormStageIn &f,
+                                                             int stride) {
+  constexpr int NONE = 0x7fffffff;
+  constexpr int kMaxRange = 64;  // devices_per_node <= RANNC_DP_MAX_DEVICES
+  const int lane = threadIdx.x & 63;
+  int32_t *plan = (int32_t *)(f.rec + 6);
+  for (int u = lane; u < 2 * stride; u += 64) plan[u] = -1;
+  int bad_q = NONE, bad_st = 0;
+  int best_k = NONE, best_q = NONE, best_p = -1;  // k = n << 16 | S
+  int64_t best_e = INT64_MAX, best_v = 0;
+  for (int p = lane; p < f.Q; p += 64) {
+    const ProblemDev &pr = probs[p];
+    const int q = pr.q;
+    const int st = *pr.status;
+    if (st != 0) {
+      if (q < bad_q) { bad_q = q; bad_st = st; }
+      continue;
+    }
+    const int n = f.pair_n[q];
+    const int64_t mb = f.pair_mb[q];
+    const int lo = f.devices_per_node * (n - 1) + 1;
+    const int hi = min(min(f.devices_per_node * n, f.N), pr.S_eff);
+    const int64_t lvl = (int64_t)(pr.N + 1) * pr.DP, cell = (int64_t)pr.N * pr.DP + pr.D - 1;
+    // the first S of the range that this search can realise (a smaller S always wins for one n);
+    // eight values in flight at a time
+    for (int S0 = lo; S0 <= hi && S0 < lo + kMaxRange; S0 += 8) {
+      int64_t v[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const int64_t e = (min(S0 + k, hi) - 1) * lvl + cell;
+        if (pr.bits == 32) {
+          const uint32_t u = ((const uint32_t *)pr.V)[e];
+          v[k] = (u == Lim<uint32_t>::inf) ? INT64_MAX : (int64_t)u;
+        } else {
+          const uint64_t u = ((const uint64_t *)pr.V)[e];
+          v[k] = (u == Lim<uint64_t>::inf) ? INT64_MAX : (int64_t)u;
+        }
+      }
+      int64_t val = INT64_MAX;
+      int S = 0;
+#pragma unroll
+      for (int k = 7; k >= 0; --k)
+        if (S0 + k <= hi && S0 + k < lo + kMaxRange && v[k] != INT64_MAX) { val = v[k]; S = S0 + k; }
+      if (S == 0) continue;
+      const int64_t m = mb + S - 1;
+      const int64_t e = (val != 0 && m > INT64_MAX / val) ? INT64_MAX : m * val;
+      const int k = n << 16 | S;
+      if (k < best_k || (k == best_k && (e < best_e || (e == best_e && q < best_q)))) {
+        best_k = k; best_e = e; best_v = val; best_q = q; best_p = p;
+      }
+      break;
+    }
   }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    const int ok = __shfl_xor(best_k, o), oq = __shfl_xor(best_q, o), op = __shfl_xor(best_p, o);
+    const int64_t oe = __shfl_xor(best_e, o), ov = __shfl_xor(best_v, o);
+    if (ok < best_k || (ok == best_k && (oe < best_e || (oe == best_e && oq < best_q)))) {
+      best_k = ok; best_e = oe; best_v = ov; best_q = oq; best_p = op;
+    }
+    const int obq = __shfl_xor(bad_q, o), obs = __shfl_xor(bad_st, o);
+    if (obq < bad_q) { bad_q = obq; bad_st = obs; }
+  }
+  const bool found = bad_q == NONE && best_q != NONE;
+  if (lane == 0) {
+    f.rec[0] = found ? best_q : -1;
+    f.rec[1] = found ? (best_k & 0xffff) : 0;
+    f.rec[2] = bad_q == NONE ? 0 : bad_st;
+    f.rec[3] = 0;
+    f.rec[4] = found ? best_v : 0;
+    f.rec[5] = found ? best_e : 0;
+  }
+  FormStageChoice c;
+  c.at = found ? best_p : -1;
+  c.S = found ? (best_k & 0xffff) : 0;
+  return c;
+}
+
+// The chosen search's plan, copied behind the record (which may live in host memory: it is only
+// written here), and the flag word that tells the host.
+__device__ __forceinline__ void plan_to_record(int plan_stride, const int32_t *se, const int32_t *rp, const FormStageIn &f) {
+  __syncthreads();  // the walk's stores, by this workgroup's first thread, are visible to all of it
+  int32_t *plan = (int32_t *)(f.rec + 6);
+  if (se)
+    for (int u = threadIdx.x; u < plan_stride; u += blockDim.x) {
+      plan[u] = se[u];
+      plan[plan_stride + u] = rp[u];
+    }
+  if (!f.flag) return;
+  __threadfence_system();
+  __syncthreads();
+  if (threadIdx.x == 0) __hip_atomic_store(f.flag, f.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// The whole workgroup: the first wave makes the choice; false (and the record is complete) if there is none.
+__device__ __forceinline__ bool form_stage_picked(const ProblemDev *__restrict__ probs, const FormStageIn &f, int stride,
+                                                  FormStageChoice &pick) {
+  if (threadIdx.x < 64) {
+    const FormStageChoice c = form_stage_choose(probs, f, stride);
+    if (threadIdx.x == 0) pick = c;
+  }
+  __syncthreads();
+  if (pick.at >= 0) return true;
+  plan_to_record(stride, nullptr, nullptr, f);
+  return false;
+}
+
+// The results of one search, copied to the host's mirror of the result buffer; behind them the
+// search's flag word tells the host, which polls it, that they are there.
+__device__ __forceinline__ void results_to_host(const ProblemDev &pr, int Q, int plan_stride, const PlanResults &r) {
+  __syncthreads();  // this workgroup's stores to the device's buffer are visible to all of it
+  const int q = pr.q, tid = threadIdx.x;
+  if (tid == 0) r.h_opt[q] = r.d_opt[q];
+  if (tid == 1) r.h_est[q] = r.d_est[q];
+  if (tid == 2) r.h_n_stages[q] = r.d_n_stages[q];
+  if (tid == 3) r.h_status[q] = r.d_status[q];
+  for (int u = tid; u < plan_stride; u += blockDim.x) {
+    r.h_stage_end[(int64_t)q * plan_stride + u] = r.d_stage_end[(int64_t)q * plan_stride + u];
+    r.h_replicas[(int64_t)q * plan_stride + u] = r.d_replicas[(int64_t)q * plan_stride + u];
+  }
+  __threadfence_system();
+  __syncthreads();
+  if (tid == 0) __hip_atomic_store(&r.h_flag[q], r.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// choose: the choice of the stage count (select_kernel) is made here, by the first wave, instead of in
+// a launch of its own.
+__device__ __forceinline__ void traceback_choose(const ProblemDev &pr, const PlanResults &r) {
+  if (threadIdx.x < 64) select_body(pr, r.d_opt, r.d_n_stages, r.d_est, r.d_status);
+  __syncthreads();
 }
 
 __global__ __launch_bounds__(kTracebackThreads) void traceback_kernel(
     const ProblemDev *__restrict__ probs, int plan_stride, int32_t *d_stage_end, int32_t *d_replicas,
-    const int32_t *__restrict__ d_levels, int64_t *rec) {
+    const int32_t *__restrict__ d_levels, const FormStageIn fs, const PlanResults results, int choose) {
   __shared__ unsigned int best_key;
-  const ProblemDev pr = probs[blockIdx.x];  // by value: no reloads after the plan stores
-  const int forced = d_levels ? d_levels[pr.q] : 0;
+  __shared__ FormStageChoice pick;
+  if (fs.rec && !form_stage_picked(probs, fs, plan_stride, pick)) return;
+  const ProblemDev pr = probs[fs.rec ? pick.at : (int)blockIdx.x];  // by value: no reloads after the plan stores
+  if (choose) traceback_choose(pr, results);
+  const int forced = fs.rec ? pick.S : d_levels ? d_levels[pr.q] : 0;
   int32_t *se = d_stage_end + (int64_t)pr.q * plan_stride;
   int32_t *rp = d_replicas + (int64_t)pr.q * plan_stride;
 #define GO(T)                                                                                    \
@@ -1639,18 +1803,22 @@ __global__ __launch_bounds__(kTracebackThreads) void traceback_kernel(
     else traceback_split_body<uint64_t>(pr, plan_stride, se, rp, &best_key, forced);
   } else if (pr.bits == 32) { GO(uint32_t) } else { GO(uint64_t) }
 #undef GO
-  if (rec && d_levels && forced >= 0) plan_to_record(plan_stride, se, rp, rec);
+  if (fs.rec) plan_to_record(plan_stride, se, rp, fs);
+  if (results.h_flag) results_to_host(pr, gridDim.x, plan_stride, results);
 }
 
 // Plan recovery out of LDS, for launches of few, small min-max searches (the host checks that every
 // search of the launch fits traceback_lds_bytes() into the dynamic LDS it passes).
 __global__ __launch_bounds__(kTracebackThreads) void traceback_lds_kernel(
     const ProblemDev *__restrict__ probs, int plan_stride, int32_t *d_stage_end, int32_t *d_replicas,
-    const int32_t *__restrict__ d_levels, int64_t *rec) {
+    const int32_t *__restrict__ d_levels, const FormStageIn fs, const PlanResults results, int choose) {
   __shared__ unsigned int best_key;
+  __shared__ FormStageChoice pick;
   extern __shared__ __align__(16) char staged[];
-  const ProblemDev pr = probs[blockIdx.x];
-  const int forced = d_levels ? d_levels[pr.q] : 0;
+  if (fs.rec && !form_stage_picked(probs, fs, plan_stride, pick)) return;
+  const ProblemDev pr = probs[fs.rec ? pick.at : (int)blockIdx.x];
+  if (choose) traceback_choose(pr, results);
+  const int forced = fs.rec ? pick.S : d_levels ? d_levels[pr.q] : 0;
   int32_t *se = d_stage_end + (int64_t)pr.q * plan_stride;
   int32_t *rp = d_replicas + (int64_t)pr.q * plan_stride;
 #define GO(T)                                                                                   \
@@ -1662,7 +1830,8 @@ __global__ __launch_bounds__(kTracebackThreads) void traceback_lds_kernel(
   }
   if (pr.bits == 32) { GO(uint32_t) } else { GO(uint64_t) }
 #undef GO
-  if (rec && d_levels && forced >= 0) plan_to_record(plan_stride, se, rp, rec);
+  if (fs.rec) plan_to_record(plan_stride, se, rp, fs);
+  if (results.h_flag) results_to_host(pr, gridDim.x, plan_stride, results);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1743,13 +1912,13 @@ __global__ __launch_bounds__(256) void arg_init_kernel(const ProblemDev *__restr
 // ---------------------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------------------
-hipError_t launch_setup(const ProblemDev *probs, int Q, int rows_per_item, int max_items, int slots, bool paired,
-                        hipStream_t st) {
+hipError_t launch_setup(const ProblemDev *src, ProblemDev *probs, int Q, int rows_per_item, int max_items, int slots,
+                        bool paired, hipStream_t st) {
   const int fill = Q >= 256 ? 4 : Q >= 16 ? 16 : 128;  // workgroups that fill a search's V
   for (int q0 = 0; q0 < Q; q0 += 65535) {
     const int nq = min(65535, Q - q0);
-    hipLaunchKernelGGL(setup_kernel, dim3(1 + fill, nq), dim3(kSetupThreads), 0, st, probs + q0, rows_per_item, max_items,
-                       Q, slots, paired ? 1 : 0);
+    hipLaunchKernelGGL(setup_kernel, dim3(1 + fill, nq), dim3(kSetupThreads), 0, st, src + q0, probs + q0, rows_per_item,
+                       max_items, Q, slots, paired ? 1 : 0);
   }
   return hipGetLastError();
 }
@@ -1897,12 +2066,12 @@ bool small_can_recompute(int bits, int DP, int64_t max_total_time) {
   return DP <= 32 && (bits == 32 || max_total_time <= kDirectWideMaxTime);
 }
 
-hipError_t launch_solve_small(const ProblemDev *p, int Q, int bits, int DP, bool direct, int64_t *d_opt,
+hipError_t launch_solve_small(const ProblemDev *src, ProblemDev *p, int Q, int bits, int DP, bool direct, int64_t *d_opt,
                               int32_t *d_n_stages, int64_t *d_est, int32_t *d_status, hipStream_t st) {
   if (direct && DP > 32) return hipErrorInvalidValue;
 #define GO(B, T, W, X)                                                                                 \
   if (bits == B && DP == W && direct == X)                                                             \
-    hipLaunchKernelGGL((solve_small_kernel<T, W, X>), dim3(Q), dim3(64 * small_waves<T, W>()), 0, st, p, d_opt, \
+    hipLaunchKernelGGL((solve_small_kernel<T, W, X>), dim3(Q), dim3(64 * small_waves<T, W>()), 0, st, src, p, d_opt, \
                        d_n_stages, d_est, d_status);
   GO(32, uint32_t, 8, false) GO(32, uint32_t, 16, false) GO(32, uint32_t, 32, false) GO(32, uint32_t, 64, false)
   GO(64, uint64_t, 8, false) GO(64, uint64_t, 16, false) GO(64, uint64_t, 32, false) GO(64, uint64_t, 64, false)
@@ -1941,8 +2110,13 @@ int64_t traceback_lds_bytes(int N, int DP, int S_eff, int bits) {
 }
 
 hipError_t launch_traceback(const ProblemDev *p, int Q, int plan_stride, int32_t *d_stage_end,
-                            int32_t *d_replicas, const int32_t *d_levels, int64_t lds_bytes, int64_t *rec,
-                            hipStream_t st) {
+                            int32_t *d_replicas, const int32_t *d_levels, int64_t lds_bytes,
+                            const FormStageIn *form_stage, const PlanResults *results, bool choose, hipStream_t st) {
+  const PlanResults none = {};
+  const PlanResults &r = results ? *results : none;
+  const FormStageIn no_choice = {};
+  const FormStageIn &f = form_stage ? *form_stage : no_choice;
+  if (form_stage) Q = 1;
   if (lds_bytes > 0) {
     // more than the default 64 KiB of dynamic LDS has to be asked for once
     static const hipError_t attr = hipFuncSetAttribute((const void *)traceback_lds_kernel,
@@ -1950,10 +2124,10 @@ hipError_t launch_traceback(const ProblemDev *p, int Q, int plan_stride, int32_t
     if (attr != hipSuccess) return attr;
     if (lds_bytes > kTracebackLdsMax) return hipErrorInvalidValue;
     hipLaunchKernelGGL(traceback_lds_kernel, dim3(Q), dim3(kTracebackThreads), (size_t)lds_bytes, st, p, plan_stride,
-                       d_stage_end, d_replicas, d_levels, rec);
+                       d_stage_end, d_replicas, d_levels, f, r, choose ? 1 : 0);
   } else {
     hipLaunchKernelGGL(traceback_kernel, dim3(Q), dim3(kTracebackThreads), 0, st, p, plan_stride, d_stage_end,
-                       d_replicas, d_levels, rec);
+                       d_replicas, d_levels, f, r, choose ? 1 : 0);
   }
   return hipGetLastError();
 }
@@ -1983,95 +2157,6 @@ __global__ __launch_bounds__(64) void level_values_kernel(const ProblemDev *__re
 
 hipError_t launch_level_values(const ProblemDev *p, int Q, int stride, int64_t *d_out, hipStream_t st) {
   hipLaunchKernelGGL(level_values_kernel, dim3(Q), dim3(64), 0, st, p, stride, d_out);
-  return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------------------
-// Outer driver (Algorithm 2 "form_stage" of Sec. III-C), the loops over the solved batch: node
-// counts n = 1, 2, 4, ... in turn, for each the stage counts S ascending over
-// (devices_per_node*(n-1), devices_per_node*n], and for the first S that any search of that n can
-// realise (V[S][N][D] finite), the search with the smallest (MB + S - 1) * V, the first one in
-// batch order among equals.  That is the lexicographic minimum of (n, S, estimate, search index)
-// over all feasible (search, S) pairs, S inside the range of the search's n: one wave, a lane per
-// search (in rounds of 64) reads its values straight from the value tables (all reads of a lane
-// are independent), then one reduction over the wave.
-// Writes the record {q, S, first bad status in batch order or 0, 0, V, estimate}, the plan area
-// behind it (-1 everywhere; the plan recovery fills in the chosen search's), and the level array
-// of the plan recovery (S at the chosen search, -1 = no plan wanted elsewhere).  q = -1: infeasible.
-// ---------------------------------------------------------------------------------------
-__global__ __launch_bounds__(64) void form_stage_select_kernel(
-    const ProblemDev *__restrict__ probs, int Q, int stride, int N, int n_nodes, int devices_per_node,
-    const int32_t *__restrict__ pair_n, const int32_t *__restrict__ pair_mb, int32_t *__restrict__ levels,
-    int64_t *__restrict__ rec) {
-  constexpr int NONE = 0x7fffffff;
-  constexpr int kMaxRange = 64;  // devices_per_node <= RANNC_DP_MAX_DEVICES
-  const int lane = threadIdx.x;
-  int32_t *plan = (int32_t *)(rec + 6);
-  for (int u = lane; u < 2 * stride; u += 64) plan[u] = -1;
-  int bad_q = NONE, bad_st = 0;
-  int best_k = NONE, best_q = NONE;  // k = n << 16 | S
-  int64_t best_e = INT64_MAX, best_v = 0;
-  for (int p = lane; p < Q; p += 64) {
-    const ProblemDev &pr = probs[p];
-    const int q = pr.q;
-    levels[q] = -1;  // only the chosen search's plan is recovered
-    const int st = *pr.status;
-    if (st != 0) {
-      if (q < bad_q) { bad_q = q; bad_st = st; }
-      continue;
-    }
-    const int n = pair_n[q];
-    const int64_t mb = pair_mb[q];
-    const int lo = devices_per_node * (n - 1) + 1;
-    const int hi = min(min(devices_per_node * n, N), pr.S_eff);
-    const int64_t lvl = (int64_t)(pr.N + 1) * pr.DP, cell = (int64_t)pr.N * pr.DP + pr.D - 1;
-    // the first S of the range that this search can realise (a smaller S always wins for one n)
-    for (int S = lo; S <= hi && S < lo + kMaxRange; ++S) {
-      int64_t v;
-      if (pr.bits == 32) {
-        const uint32_t u = ((const uint32_t *)pr.V)[(S - 1) * lvl + cell];
-        v = (u == Lim<uint32_t>::inf) ? INT64_MAX : (int64_t)u;
-      } else {
-        const uint64_t u = ((const uint64_t *)pr.V)[(S - 1) * lvl + cell];
-        v = (u == Lim<uint64_t>::inf) ? INT64_MAX : (int64_t)u;
-      }
-      if (v == INT64_MAX) continue;
-      const int64_t f = mb + S - 1;
-      const int64_t e = (v != 0 && f > INT64_MAX / v) ? INT64_MAX : f * v;
-      const int k = n << 16 | S;
-      if (k < best_k || (k == best_k && (e < best_e || (e == best_e && q < best_q)))) {
-        best_k = k; best_e = e; best_v = v; best_q = q;
-      }
-      break;
-    }
-  }
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    const int ok = __shfl_xor(best_k, o), oq = __shfl_xor(best_q, o);
-    const int64_t oe = __shfl_xor(best_e, o), ov = __shfl_xor(best_v, o);
-    if (ok < best_k || (ok == best_k && (oe < best_e || (oe == best_e && oq < best_q)))) {
-      best_k = ok; best_e = oe; best_v = ov; best_q = oq;
-    }
-    const int obq = __shfl_xor(bad_q, o), obs = __shfl_xor(bad_st, o);
-    if (obq < bad_q) { bad_q = obq; bad_st = obs; }
-  }
-  if (lane == 0) {
-    const bool found = bad_q == NONE && best_q != NONE;
-    if (found) levels[best_q] = best_k & 0xffff;
-    rec[0] = found ? best_q : -1;
-    rec[1] = found ? (best_k & 0xffff) : 0;
-    rec[2] = bad_q == NONE ? 0 : bad_st;
-    rec[3] = 0;
-    rec[4] = found ? best_v : 0;
-    rec[5] = found ? best_e : 0;
-  }
-}
-
-hipError_t launch_form_stage_select(const ProblemDev *probs, int Q, int stride, int N, int n_nodes,
-                                    int devices_per_node, const int32_t *pair_n, const int32_t *pair_mb,
-                                    int32_t *levels, int64_t *rec, hipStream_t st) {
-  hipLaunchKernelGGL(form_stage_select_kernel, dim3(1), dim3(64), 0, st, probs, Q, stride, N, n_nodes, devices_per_node,
-                     pair_n, pair_mb, levels, rec);
   return hipGetLastError();
 }
 

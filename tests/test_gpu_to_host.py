@@ -1,0 +1,61 @@
+"""rannc_dp_solve_to_host (solve, plan recovery and the results in host memory as one call) against the
+two calls it stands for, around the batch size up to which a batch runs as one group and writes its
+results to host memory itself."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2103_16063_amd import binding as B
+from paper_2103_16063_amd import synth
+from tests.gpu_util import assert_results_match
+
+pytestmark = pytest.mark.gpu
+
+
+def _mixed(Q):
+    g = np.random.default_rng(Q)
+    out = []
+    for q in range(Q):
+        N = int(g.integers(1, 140))
+        p = synth.random_small(600 + q, N, int(g.choice([1, 5, 8, 13, 16, 31, 32, 48, 64])), int(g.integers(1, 9)),
+                               tight=float(g.choice([0.6, 1.2, 3.0, 50.0])))
+        if q % 11 == 5:
+            p["act_bytes"] = p["act_bytes"].copy()
+            p["act_bytes"][N // 2] = -1    # a flagged search among good ones
+        out.append(p)
+    return out
+
+
+@pytest.mark.parametrize("split", [False, True])
+@pytest.mark.parametrize("Q", [1, 2, 63, 64, 65])
+def test_same_as_solve_and_traceback(Q, split):
+    probs = _mixed(Q)
+    if split:
+        probs = [synth.with_backward_times(p, 3, tmax=50) for p in probs]
+    with B.Session(synth.concat_batch(probs)) as s:
+        for _ in range(3):   # the second and third call reuse staging memory and mirror
+            res = s.run()
+        s.d_opt.fill_(-3); s.d_se.fill_(-3)
+        s.solve()
+        s.traceback()
+        torch.cuda.synchronize()
+        for key, t in (("opt", s.d_opt), ("est_iter_ns", s.d_est), ("n_stages", s.d_ns), ("status", s.d_status),
+                       ("stage_end", s.d_se), ("replicas", s.d_rp)):
+            assert np.array_equal(res[key], t.cpu().numpy()), key
+        good = [q for q in range(Q) if res["status"][q] == B.PROBLEM_OK]
+        assert len(good) < Q or Q < 6
+        if not split:
+            assert_results_match([probs[q] for q in good], {k: v[good] for k, v in res.items()})
+
+
+def test_rejections():
+    with B.Session(synth.concat_batch([synth.random_small(1, 20, 4, 3)])) as s:
+        n = s._out_host.numel()
+        call = lambda **k: B.rannc_dp_solve_to_host(s.h, s.hb, s.stream(), k.get("stride", s.plan_stride),
+                                                    k.get("d", s._out_dev), k.get("h", s._out_host), k.get("n", n))
+        assert call() == B.OK
+        assert call(n=n - 1) == B.INVALID_ARG
+        assert call(stride=s.plan_stride - 1) == B.INVALID_ARG
+        assert call(d=None) == B.INVALID_ARG and call(h=None) == B.INVALID_ARG
+        assert call(d=s._out_dev.data_ptr() + 4) == B.INVALID_ARG
+        assert B.rannc_dp_solve_to_host(None, s.hb, s.stream(), 4, s._out_dev, s._out_host, n) == B.INVALID_ARG
