@@ -420,6 +420,8 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
         sh.max_nch = std::max(sh.max_nch, p.nch);
         sh.max_D = std::max(sh.max_D, p.D);
         sh.max_S_eff = std::max(sh.max_S_eff, p.S_eff);
+        if (rannc::dp_class(D) == p.DP)
+          for (int c = 0; c < p.nch; ++c) sh.wide_rows += std::min(64 * c + 64, N);
       }
   }
 
@@ -599,14 +601,14 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
     // the handle fixes it, or the host does for a launch of many rounds (merge_grid_items).
     const int slots = h->n_cus * rannc::merge_workgroups_per_cu(h->bits, kClasses[k], recompute_cls[k]);
     int rows_for_list = -1;
-    if (split) rows_for_list = rannc::split_rows_per_item(sh, h->n_cus);
+    if (split) rows_for_list = rannc::split_rows_per_item(sh, kClasses[k]);
     else
       merge_items[k] = rannc::merge_grid_items(sh, rannc::merge_rows_per_item(h->tune_spw), slots, recompute_cls[k],
                                                &rows_for_list);
     ok = rannc::launch_setup(src + cls_start[k], cp, sh.nprob, rows_for_list, merge_items[k], slots, recompute_cls[k], st) ==
          hipSuccess;
     ok = ok && staging_read();
-    ok = ok && rannc::launch_build(cp, sh, h->bits, kClasses[k], recompute_cls[k] ? 1 : 3, st) == hipSuccess;
+    ok = ok && rannc::launch_build(cp, sh, h->bits, kClasses[k], recompute_cls[k] || split_fast ? 1 : 3, st) == hipSuccess;
     if (split) ok = ok && rannc::launch_split_level1(cp, sh, h->bits, st) == hipSuccess;
   }
   if (timing) ok = ok && hipEventRecord(h->ev[1], st) == hipSuccess;
@@ -628,7 +630,7 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
       const hipStream_t st = cs[k];
       if (split_fast)
         ok = rannc::launch_level_split_fast(dp + cls_start[k], sh, h->bits, kClasses[k], s,
-                                            rannc::split_rows_per_item(sh, h->n_cus), st) == hipSuccess;
+                                            rannc::split_rows_per_item(sh, kClasses[k]), st) == hipSuccess;
       else if (split)
         ok = rannc::launch_level_split(dp + cls_start[k], sh, h->bits, s, 1, nullptr, nullptr, st) ==
              hipSuccess;
@@ -664,7 +666,7 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
   h->ev_valid = timing;
   int kernel_of[4];
   for (int k = 0; k < 4; ++k) {
-    h->no_times[k] = fused[k] ? fused_direct[k] : recompute_cls[k];
+    h->no_times[k] = fused[k] ? fused_direct[k] : recompute_cls[k] || split_fast;
     kernel_of[k] = fused[k]           ? (fused_direct[k] ? RANNC_DP_KERNEL_ONE_LAUNCH_RECOMPUTE : RANNC_DP_KERNEL_ONE_LAUNCH)
                    : split_fast       ? RANNC_DP_KERNEL_SPLIT
                    : split            ? RANNC_DP_KERNEL_SPLIT_SCAN
@@ -1226,16 +1228,16 @@ int rannc_dp_read_table(rannc_dp_t *h, int which, int32_t problem, void *d_dst, 
   bool ok = true;
   int cls = 0;
   while (cls < 3 && p.DP != (8 << cls)) ++cls;
-  if (h->no_times[cls] && (which == RANNC_DP_TABLE_COST || which == RANNC_DP_TABLE_ARG_I || which == RANNC_DP_TABLE_ARG_D)) {
+  if (h->no_times[cls] && (which == RANNC_DP_TABLE_COST || which == RANNC_DP_TABLE_COST_BWD || which == RANNC_DP_TABLE_ARG_I || which == RANNC_DP_TABLE_ARG_D)) {
     // the solve recomputed the stage times instead of tabulating them: tabulate this search's now
     LaunchShape one;
-    one.nprob = 1; one.max_N = p.N; one.max_nch = p.nch; one.max_D = p.D; one.max_S_eff = p.S_eff;
+    one.nprob = 1; one.max_N = p.N; one.max_nch = p.nch; one.max_D = p.D; one.max_S_eff = p.S_eff; one.wide_rows = 0;
     ok = rannc::launch_build(h->d_probs + pos, one, p.bits, p.DP, 2, st) == hipSuccess;
   }
   ok = ok && rannc::launch_export(h->d_probs + pos, which, p.bits, d_dst, st) == hipSuccess;
   if (which == RANNC_DP_TABLE_ARG_I || which == RANNC_DP_TABLE_ARG_D) {
     LaunchShape sh;
-    sh.nprob = 1; sh.max_N = p.N; sh.max_nch = p.nch; sh.max_D = p.D; sh.max_S_eff = p.S_eff;
+    sh.nprob = 1; sh.max_N = p.N; sh.max_nch = p.nch; sh.max_D = p.D; sh.max_S_eff = p.S_eff; sh.wide_rows = 0;
     int32_t *ai = which == RANNC_DP_TABLE_ARG_I ? (int32_t *)d_dst : nullptr;
     int32_t *ad = which == RANNC_DP_TABLE_ARG_D ? (int32_t *)d_dst : nullptr;
     for (int s = 2; s <= p.S_eff && ok; ++s)

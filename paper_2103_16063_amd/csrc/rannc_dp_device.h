@@ -65,6 +65,34 @@ __device__ __forceinline__ uint64_t lane_bcast(uint64_t v, int q) {
   return ((uint64_t)hi << 32) | lo;
 }
 
+// ceil(x / r) for any 1 <= r <= 64 from the correctly rounded reciprocal 1/r, in double precision:
+//     t = x + (r/2 - 1 + r o)     y = t (1/r) + 1.5 2^52     (one fused multiply-add)
+// t / r = (x + r - 1)/r - 1/2 + o, and the fraction of (x + r - 1)/r is at most 63/64, so t (1/r) lies
+// between k - 1/2 + o and k + 1/2 - (1/64 - o) for k = ceil(x / r); the addition rounds it to k, which
+// is then the low part of the sum, as long as t is exact and the product is off by less than o.
+// 32-bit x: o = 2^-18 (t a multiple of 2^-18 below 2^33; product off by less than 2^-20).  64-bit x up to
+// 2^44: o = 2^-8 (t a multiple of 2^-8 below 2^45: 53 bits; off by less than 2^-9).
+template <typename VT> struct CeilDiv;
+template <> struct CeilDiv<uint32_t> {
+  static constexpr double kOffset = 0x1p-18;
+  static __device__ __forceinline__ uint32_t at(double t, double inv) {
+    return (uint32_t)__double_as_longlong(__builtin_fma(t, inv, 0x1.8p52));
+  }
+};
+template <> struct CeilDiv<uint64_t> {
+  static constexpr double kOffset = 0x1p-8;
+  static __device__ __forceinline__ uint64_t at(double t, double inv) {
+    return (uint64_t)__double_as_longlong(__builtin_fma(t, inv, 0x1.8p52)) & ((1ull << 51) - 1ull);
+  }
+};
+template <typename VT> __device__ __forceinline__ double ceil_div_offset(int r) {
+  return 0.5 * (double)r - 1.0 + (double)r * CeilDiv<VT>::kOffset;
+}
+template <typename VT> __device__ __forceinline__ VT ceil_div(VT x, int r, double inv) {
+  return CeilDiv<VT>::at((double)x + ceil_div_offset<VT>(r), inv);
+}
+constexpr int64_t kCeilDivMax = (int64_t)1 << 44;
+
 static constexpr uint64_t kSumLimit = 1ull << 62;
 static constexpr uint64_t kCutLimit = (kSumLimit - 1) / 1000;  // largest bytes of a cut: 1000 * bytes < 2^62
 
@@ -80,9 +108,8 @@ __device__ __forceinline__ uint64_t cut_time(int64_t bytes, int64_t bw, int &fla
 }
 static constexpr int kNoRow = 0x7fffffff;
 
-// Split-objective level kernel: waves per workgroup, and the smallest work item the adaptive work
-// list makes for it (rows of one chunk); the work-list kernel needs both.
+// Split-objective level kernel: waves per workgroup (each takes every eighth device total; sixteen
+// measured slower).
 constexpr int kSplitWaves = 8;
-constexpr int kSplitMinRows = 4;  // smallest work item the adaptive work list makes (rows of one chunk)
 
 }  // namespace rannc

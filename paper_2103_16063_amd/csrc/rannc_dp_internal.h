@@ -41,7 +41,7 @@ __host__ __device__ inline int64_t unit_index(int nch, int i, int c) {
 // upper bound on the number of work items ("runs") of one level: every chunk's rows cut into
 // groups of at least 4 rows (chunk c has at most 64(c+1) rows), or, for a search of at most
 // kSplitSmallRows rows, into items of one or two rows (split_rows_per_item)
-constexpr int kSplitSmallRows = 1024;
+constexpr int kSplitSmallRows = 16384;
 __host__ __device__ inline int64_t max_runs(int nch) {
   const int64_t by4 = 8LL * nch * (nch + 1), rows = 32LL * nch * (nch + 1);
   const int64_t small = rows < kSplitSmallRows + nch ? rows : kSplitSmallRows + nch;
@@ -122,6 +122,7 @@ struct LaunchShape {
   int max_nch;   // largest nch among them
   int max_D;
   int max_S_eff;
+  int64_t wide_rows;  // rows (unpruned) of the searches of its widest device-count class
 };
 
 // Kernel launchers (rannc_dp_kernels.hip, rannc_dp_split.hip, rannc_dp_compact.hip).  All enqueue on `st` and return the launch status.
@@ -129,8 +130,8 @@ struct LaunchShape {
 // parts: 1 = fits-in-memory tables (rmin, ufit) and level 1 of V, 2 = the stage-time table, 3 = both
 hipError_t launch_build(const ProblemDev *probs, const LaunchShape &sh, int bits, int DP, int parts, hipStream_t st);
 // prefix sums, validation, initial V, windows and work list of the searches of a launch.
-// rows_per_item: > 0 fixed, 0 chosen on the device for the split-objective kernel, -1 for the
-// sorted-merge kernel (then the smallest item size whose item count fits max_items)
+// rows_per_item: > 0 fixed, -1 chosen on the device for the sorted-merge kernel (the smallest item size
+// whose item count fits max_items)
 // slots: workgroups of the level kernel that the device holds at a time
 // paired: the list for the level kernel that recomputes the stage times (diagonal blocks as row pairs)
 // src: the descriptors, in device memory (probs itself) or in pinned host memory the device can read;
@@ -169,10 +170,8 @@ hipError_t launch_level_split(const ProblemDev *probs, const LaunchShape &sh, in
 // needs the key table and the work list made by launch_setup(..., split_rows_per_item(), ...); with
 // 64-bit tables only for time bounds up to kSplitPackedMax (the packed winner holds 42 value bits)
 constexpr int64_t kSplitPackedMax = (1LL << 42) - 2;
-// rows per work item: 1 or 2 for a launch whose rows (unpruned) then still fit one round of workgroups
-// (a short chain of rows per workgroup: the launch is bound by latency), else 0 = chosen on the
-// device from the size of the windows (4, 8 or 16); the level launcher is given the same value
-int split_rows_per_item(const LaunchShape &sh, int n_cus);
+// rows per work item of a launch; the level launcher is given the same value
+int split_rows_per_item(const LaunchShape &sh, int DP);
 hipError_t launch_level_split_fast(const ProblemDev *probs, const LaunchShape &sh, int bits, int DP, int s,
                                    int rows_per_item, hipStream_t st);
 hipError_t launch_select(const ProblemDev *probs, int Q, int64_t *d_opt, int32_t *d_n_stages,

@@ -209,7 +209,6 @@ void build_kernel(const ProblemDev *__restrict__ probs, const int parts, const i
 // items of consecutive rows, listed chunk by chunk.  A compact list keeps the workgroups that have
 // work at the front of the grid.  The number of rows of an item travels in the top bits of its
 // descriptor: (rows - 1) << 26 | c << 16 | first row.  rows > 0: items of that many rows.
-// rows = 0 (split-objective level kernel): 16, 8 or 4 rows, from the size of all windows together.
 // rows = -1 (sorted-merge level kernel): the smallest multiple of 4 (up to 64) whose item count
 // fits max_items, the grid the host launches (sized for the rows of an unpruned search: small
 // items, i.e. many workgroups and a short critical path, when pruning leaves few rows; large ones,
@@ -429,7 +428,7 @@ __global__ __launch_bounds__(kSetupThreads) void setup_kernel(const ProblemDev *
   __shared__ int start[1025];  // nch <= 1024 (N <= 65535)
   __shared__ RunSegments seg[1024];  // every chunk's segments
   constexpr int NC = 16;  // candidate item sizes 4, 8, ..., 64 rows
-  __shared__ int total_rows, count[NC];
+  __shared__ int count[NC];
   const int nch = pr.nch, D = pr.D;
   const uint64_t M = (uint64_t)pr.M;
   auto window = [&](auto P, auto A) {
@@ -462,24 +461,19 @@ __global__ __launch_bounds__(kSetupThreads) void setup_kernel(const ProblemDev *
   int32_t *const runs = pr.runs;  // (read once: the stores below would make the compiler fetch it again)
   if (rows <= 0) {
     if (tid < NC) count[tid] = 0;
-    if (tid == 0) total_rows = 0;
     __syncthreads();
     // thread t counts the items of candidate size 4 (t % 16 + 1) over the chunks t / 16, t / 16 + 16, ...
     {
       const int k = tid % NC, r = 4 * (k + 1);
-      int mine = 0, cnt = 0;
+      int cnt = 0;
       for (int c = tid / NC; c < nch; c += kSetupThreads / NC) {
         const RunSegments g = seg[c];
-        mine += g.n0 + g.n1;
         cnt += (g.n0 + r - 1) / r + (g.n1 + r - 1) / r;
       }
-      if (k == 0 && mine) atomicAdd(&total_rows, mine);
       if (cnt) atomicAdd(&count[k], cnt);
     }
     __syncthreads();
-    if (rows == 0) {
-      rows = total_rows >= 16 * 1024 ? 16 : total_rows >= 8 * 1024 ? 8 : kSplitMinRows;
-    } else {
+    {
       int pick = NC - 1;
       for (int k = NC - 1; k >= 0; --k)
         if (count[k] <= max_items) pick = k;
@@ -1357,7 +1351,15 @@ __device__ void traceback_split_body(const ProblemDev &pr, int plan_stride, int3
   const int tid = threadIdx.x;
   const int64_t lvl = (int64_t)(N + 1) * DP;
   const VT *V = (const VT *)pr.V, *VF = (const VT *)pr.VF, *VB = (const VT *)pr.VB;
-  const VT *costf = (const VT *)pr.cost, *costb = (const VT *)pr.costb;
+  // the stage times are valued from the prefix sums (the level kernel has not built their tables)
+  __shared__ double inv[64];
+  if (tid < 64) inv[tid] = 1.0 / (double)(tid + 1);
+  const bool quick = pr.time_limit <= kCeilDivMax;
+  __syncthreads();
+  auto share = [&](int64_t x, int r) -> VT {
+    if (quick) return ceil_div<VT>((VT)x, r, inv[r - 1]);
+    return (VT)(((uint64_t)x + (uint64_t)(r - 1)) / (uint64_t)r);
+  };
   int ns = (*pr.status == 0 && forced >= 0) ? (int)pr.res[1] : 0;  // forced < 0: no plan wanted
   if (forced > 0 && *pr.status == 0)
     ns = (forced <= pr.S_eff && V[(int64_t)(forced - 1) * lvl + (int64_t)N * DP + D - 1] != INF) ? forced : 0;
@@ -1369,6 +1371,7 @@ __device__ void traceback_split_body(const ProblemDev &pr, int plan_stride, int3
     __syncthreads();
     const VT v = V[(int64_t)(s - 1) * lvl + (int64_t)j * DP + d - 1];
     const int jj = j - 1, c = jj >> 6;
+    const int64_t Tj = pr.T[j], TBj = pr.TB[j], Cj = pr.C ? pr.C[j] : 0;
     const int nd = d - (s - 1);                       // d' = s-1 .. d-1
     const int total = (j - (s - 1)) * nd;             // i = s-1 .. j-1
     unsigned mine = 0xFFFFFFFFu;
@@ -1379,8 +1382,8 @@ __device__ void traceback_split_body(const ProblemDev &pr, int plan_stride, int3
       const int64_t u = unit_index(nch, i, c);
       const int r = d - dp;
       if (r < (int)pr.rmin[u * 64 + (jj & 63)]) continue;
-      const int64_t te = (u * D + (r - 1)) * 64 + (jj & 63);
-      const VT f = vmax(VF[pc], costf[te]), b = vmax(VB[pc], costb[te]);
+      const VT hf = share(Tj - pr.T[i], r) + (Cj ? share(Cj, r) : (VT)0), hb = share(TBj - pr.TB[i], r);
+      const VT f = vmax(VF[pc], hf), b = vmax(VB[pc], hb);
       if ((VT)(f + b) == v) mine = ((unsigned)i << 8) | (unsigned)dp;  // (i, d') ascends with e
     }
     if (mine != 0xFFFFFFFFu) atomicMin(best_key, mine);

@@ -3,6 +3,7 @@
 // level kernel with its finalize step, and their launchers.  Plan recovery for this objective is
 // part of the traceback kernel (rannc_dp_kernels.hip).
 #include "rannc_dp_device.h"
+#include <algorithm>
 
 namespace rannc {
 
@@ -22,12 +23,13 @@ __global__ __launch_bounds__(64) void split_level1_kernel(const ProblemDev *__re
   if (c >= pr.nch || d > pr.D) return;
   const int lane = threadIdx.x, jj = 64 * c + lane;
   if (jj >= pr.N) return;
-  const int D = pr.D, DP = pr.DP;
+  const int DP = pr.DP;
   const int64_t u = unit_index(pr.nch, 0, c);
   const int64_t e = (int64_t)(jj + 1) * DP + d - 1;
   if (d < (int)pr.rmin[u * 64 + lane]) return;  // stays "no plan"
-  const VT f = ((const VT *)pr.cost)[(u * D + (d - 1)) * 64 + lane];
-  const VT b = ((const VT *)pr.costb)[(u * D + (d - 1)) * 64 + lane];
+  auto share = [&](int64_t x) { return (VT)(((uint64_t)x + (uint64_t)(d - 1)) / (uint64_t)d); };
+  const VT f = share(pr.T[jj + 1]) + (pr.C ? share(pr.C[jj + 1]) : (VT)0);
+  const VT b = share(pr.TB[jj + 1]);
   ((VT *)pr.V)[e] = f + b;
   ((VT *)pr.VF)[e] = f;
   ((VT *)pr.VB)[e] = b;
@@ -88,92 +90,173 @@ __global__ __launch_bounds__(64) void level_split_kernel(const ProblemDev *__res
   if (arg_d) arg_d[e] = bd;
 }
 
-// Fast form of the same level for 32-bit tables.  The kept candidate of a cell is the smallest
-// (sum, i, d') in lexicographic order, so partial results over disjoint sets of rows combine
-// with a 64-bit atomicMin on the packed triple.  Work item (one workgroup of eight waves) = 16
-// consecutive rows of one chunk's window, from the same work list as the merge kernel.  Per row the
-// two stage-time units are staged in LDS once ([r][lane], conflict-free), the eight waves share
-// them and split the device totals d between them (d = s + wave, s + wave + 8, ...): a lane keeps
-// the running best of its column for each of its wave's d in registers.  The row of the previous
-// level (values, carried maxima) is wave-uniform: scalar loads, one per d', shared by all d.
-// split_finalize_kernel then turns the packed winners of the level into V and the two carried
-// maxima, and clears the key table for the next level.
+// Fast form of the same level.  The kept candidate of a cell is the smallest (sum, i, d') in
+// lexicographic order, so partial results over disjoint sets of rows combine with a 64-bit atomicMin on
+// the packed triple.  Work item (one workgroup of eight waves) = some consecutive rows of one chunk's
+// window, from the same work list as the merge kernel.  Per row the workgroup computes the two stage
+// times of every replica count from the prefix sums ([r][lane] in LDS, conflict-free, INF where the
+// stage does not fit; two buffers, so that a row costs one barrier), and the eight waves split the device
+// totals d between them (d = s + wave, s + wave + 8, ...): a lane keeps the running best of its column
+// for each of its wave's d in registers.  The carried maxima of the row of the previous level are held
+// one d' per lane and broadcast by lane reads.  split_finalize_kernel then turns the packed winners
+// of the level into V and the two carried maxima, and clears the key table for the next level.
+//
+// Bound by vector instructions (four per candidate) and, for few rows, by latency.  With the stage times
+// read from their two tables (built in front), items of four rows, d' in the key and every wave holding
+// the totals of the whole class, a level of the outer driver at 96 blocks (24 searches, 31 levels) read
+// 63 MB and took 22.5 us on average (call 906 -> 575 us), and 1024 blocks at 64 devices 9.6 ms (now 5.5).
+// Packed winner of a cell: (sum, i) in one 64-bit word whose unsigned order is the lexicographic order
+// of the pair.  32-bit tables: 32 + 32 bits.  64-bit tables: 48 + 16 bits, the sums stay below 2^42 - 1
+// (kSplitPackedMax, a bound of the quotient as well).  d' is not carried: the level's inner loop is four
+// operations per candidate without it and six with it, and the finalize step finds the first d' of row
+// i whose sum is the cell's value.
+template <typename VT> __device__ __forceinline__ unsigned long long split_pack(VT v, uint32_t i);
+template <> __device__ __forceinline__ unsigned long long split_pack<uint32_t>(uint32_t v, uint32_t i) {
+  return ((unsigned long long)v << 32) | i;
+}
+template <> __device__ __forceinline__ unsigned long long split_pack<uint64_t>(uint64_t v, uint32_t i) {
+  return (v << 16) | i;
+}
+template <typename VT> __device__ __forceinline__ int split_key_i(unsigned long long k) { return (int)(k & 0xFFFFull); }
+template <typename VT> __device__ __forceinline__ VT split_key_v(unsigned long long k) {
+  return sizeof(VT) == 4 ? (VT)(k >> 32) : (VT)(k >> 16);
+}
+
+// Stage time of a stage that does not fit: a sum with it is never below it, and orders as any other
+// value.  (32-bit sums saturate; 64-bit ones must stay below the pattern of infinity.)
+template <typename VT> constexpr VT split_nofit() { return sizeof(VT) == 8 ? (VT)((uint64_t)1 << 61) : Lim<VT>::inf; }
+__device__ __forceinline__ uint32_t split_sum(uint32_t f, uint32_t b) { return __builtin_elementwise_add_sat(f, b); }
+__device__ __forceinline__ uint64_t split_sum(uint64_t f, uint64_t b) { return f + b; }
 
 // Candidates d' = lo..hi of one staged row against the device totals d_k, k >= K0, of this wave
-// (all of them lie above hi, so every (d', k) pair is a candidate).  lim[k] = d_k - rmin of the
-// lane's stage (below 0 if d_k > D or nothing fits): the stage fits iff d' <= lim[k].
-// Packed winner of a cell: (sum, i, d') in one 64-bit word whose unsigned order is the lexicographic
-// order of the triple.  32-bit tables: 32 + 24 + 8 bits.  64-bit tables: 42 + 16 + 6 bits, which is
-// why the packed kernel serves 64-bit handles only up to a time bound of 2^42 - 2 ns (73 minutes);
-// the 32-bit key of the running best is always (i << 8) | d'.
-template <typename VT> __device__ __forceinline__ unsigned long long split_pack(VT v, uint32_t key);
-template <> __device__ __forceinline__ unsigned long long split_pack<uint32_t>(uint32_t v, uint32_t key) {
-  return ((unsigned long long)v << 32) | key;
-}
-template <> __device__ __forceinline__ unsigned long long split_pack<uint64_t>(uint64_t v, uint32_t key) {
-  return (v << 22) | ((unsigned long long)(key >> 8) << 6) | (key & 63u);
-}
-template <typename VT> __device__ __forceinline__ int split_key_i(unsigned long long k) {
-  return sizeof(VT) == 4 ? (int)((k >> 8) & 0xFFFFFFull) : (int)((k >> 6) & 0xFFFFull);
-}
-template <typename VT> __device__ __forceinline__ int split_key_d(unsigned long long k) {
-  return sizeof(VT) == 4 ? (int)(k & 0xFFull) : (int)(k & 63ull);
-}
-template <typename VT> __device__ __forceinline__ VT split_key_v(unsigned long long k) {
-  return sizeof(VT) == 4 ? (VT)(k >> 32) : (VT)(k >> 22);
-}
-
-template <typename VT, int DP, int K0>
-__device__ __forceinline__ void split_segment(int lo, int hi, int d0, int i, int lane,
-                                              const VT RANNC_GLOBAL *__restrict__ Frow,
-                                              const VT RANNC_GLOBAL *__restrict__ Brow,
-                                              const VT *sf, const VT *sb,
-                                              const int (&lim)[DP / kSplitWaves],
-                                              VT (&best_v)[DP / kSplitWaves],
-                                              uint32_t (&best_key)[DP / kSplitWaves]) {
-  constexpr int KP = DP / kSplitWaves;
+// (all of them lie above hi, so every (d', k) pair is a candidate).
+template <typename VT, int KP, int K0>
+__device__ __forceinline__ void split_segment(int lo, int hi, int d0, int lane, VT F, VT B, const VT *sf, const VT *sb,
+                                              VT (&row_v)[KP]) {
+#pragma unroll 4
   for (int dp = lo; dp <= hi; ++dp) {
-    const VT af = Frow[dp - 1], ab = Brow[dp - 1];  // wave-uniform
-    const uint32_t key = ((uint32_t)i << 8) | (uint32_t)dp;
+    const VT af = lane_bcast(F, dp - 1), ab = lane_bcast(B, dp - 1);
 #pragma unroll
     for (int k = K0; k < KP; ++k) {
-      const int r = d0 + kSplitWaves * k - dp;  // >= 1; at most DP (rows beyond the staged ones hold
-                                                // stale values, masked by lim)
-      const VT f = vmax(af, sf[(r - 1) * 64 + lane]);
-      const VT b = vmax(ab, sb[(r - 1) * 64 + lane]);
-      const VT v = f + b;
-      const bool ok = (dp <= lim[k]) & (v < best_v[k]);
-      best_v[k] = ok ? v : best_v[k];
-      best_key[k] = ok ? key : best_key[k];
+      const int r = d0 + kSplitWaves * k - dp;  // >= 1; beyond the staged ones only for totals above D
+      row_v[k] = vmin(row_v[k], split_sum(vmax(af, sf[(r - 1) * 64 + lane]), vmax(ab, sb[(r - 1) * 64 + lane])));
     }
   }
 }
 
-template <typename VT, int DP, int K0>
-__device__ __forceinline__ void split_row(int dlo, int D, int d0, int i, int lane,
-                                          const VT RANNC_GLOBAL *__restrict__ Frow,
-                                          const VT RANNC_GLOBAL *__restrict__ Brow,
-                                          const VT *sf, const VT *sb,
-                                          const int (&lim)[DP / kSplitWaves],
-                                          VT (&best_v)[DP / kSplitWaves],
-                                          uint32_t (&best_key)[DP / kSplitWaves]) {
-  if constexpr (K0 < DP / kSplitWaves) {
+template <typename VT, int KP, int K0>
+__device__ __forceinline__ void split_row(int dlo, int D, int d0, int lane, VT F, VT B, const VT *sf, const VT *sb,
+                                          VT (&row_v)[KP]) {
+  if constexpr (K0 < KP) {
     // d' in [d_{K0-1}, d_{K0} - 1]: exactly the totals d_k with k >= K0 lie above it
     const int lo = K0 == 0 ? dlo : max(dlo, d0 + kSplitWaves * (K0 - 1));
     const int hi = min(d0 + kSplitWaves * K0 - 1, D - 1);
-    split_segment<VT, DP, K0>(lo, hi, d0, i, lane, Frow, Brow, sf, sb, lim, best_v, best_key);
-    split_row<VT, DP, K0 + 1>(dlo, D, d0, i, lane, Frow, Brow, sf, sb, lim, best_v, best_key);
+    split_segment<VT, KP, K0>(lo, hi, d0, lane, F, B, sf, sb, row_v);
+    split_row<VT, KP, K0 + 1>(dlo, D, d0, lane, F, B, sf, sb, row_v);
+  }
+}
+
+// The rows of one work item.  KP: device totals per wave, and replica counts it computes the times of:
+// the D-s+1 totals (and counts) that are left at level s, over eight waves.
+template <typename VT, int DP, int KP>
+__device__ __forceinline__ void split_rows(const ProblemDev &pr, const int s, const int c, const int i_lo, const int i_hi,
+                                           VT (*sf)[DP * 64], VT (*sb)[DP * 64], const int n_buf) {
+  constexpr VT INF = Lim<VT>::inf;
+  const int N = pr.N, D = pr.D, nch = pr.nch;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int jj = 64 * c + lane;
+  const int64_t lvl = (int64_t)(N + 1) * pr.DP;
+  const VT RANNC_GLOBAL *__restrict__ Fprev = gptr((const VT *)pr.VF) + (int64_t)(s - 2) * lvl;
+  const VT RANNC_GLOBAL *__restrict__ Bprev = gptr((const VT *)pr.VB) + (int64_t)(s - 2) * lvl;
+  const uint8_t RANNC_GLOBAL *__restrict__ rmin = gptr((const uint8_t *)pr.rmin);
+  const int64_t RANNC_GLOBAL *__restrict__ T = gptr((const int64_t *)pr.T);
+  const int64_t RANNC_GLOBAL *__restrict__ TB = gptr((const int64_t *)pr.TB);
+  const int rl = D - s + 1;  // replicas left for stage s when s-1 devices are spent earlier
+  const int d0 = s + wave;   // this wave's device totals: d0, d0 + 8, ...
+  struct Row { VT F, B; int rmn; };
+  auto load = [&](int i) -> Row {  // the next row's, while one is worked on (clamped into the item)
+    const int ic = min(i, i_hi);
+    Row r;
+    r.F = Fprev[(int64_t)ic * pr.DP + min(lane, D - 1)];  // lane q holds d' = q + 1
+    r.B = Bprev[(int64_t)ic * pr.DP + min(lane, D - 1)];
+    r.rmn = rmin[unit_index(nch, ic, c) * 64 + lane];
+    return r;
+  };
+  Row cur = load(i_lo);
+  const int jc = min(jj + 1, N);  // (lanes beyond N compute times nobody looks at)
+  const int64_t Tj = T[jc], TBj = TB[jc];
+  // the prefix sums of the item's rows (at most 64), a row per lane: scalar loads would be waited for at
+  // every barrier
+  const int64_t Trow = T[min(i_lo + lane, N)], TBrow = TB[min(i_lo + lane, N)];
+  VT hc[KP];       // send time of the cut behind the lane's column, per replica count of this wave
+  double inv[KP];  // 1 / r
+#pragma unroll
+  for (int k = 0; k < KP; ++k) {
+    inv[k] = 1.0 / (double)(wave + kSplitWaves * k + 1);
+    hc[k] = 0;
+  }
+  if (pr.C) {
+    const VT Cj = (VT)gptr((const int64_t *)pr.C)[jc];
+#pragma unroll
+    for (int k = 0; k < KP; ++k) hc[k] = ceil_div<VT>(Cj, wave + kSplitWaves * k + 1, inv[k]);
+  }
+  VT best_v[KP];
+  uint32_t best_i[KP];
+#pragma unroll
+  for (int k = 0; k < KP; ++k) { best_v[k] = INF; best_i[k] = 0; }
+
+  int buf = 0;
+  for (int i = i_lo; i <= i_hi; ++i) {  // every condition below is uniform over the workgroup
+    const Row r = cur;
+    cur = load(i + 1);
+    const bool fit = jj >= i && jj < N && r.rmn <= rl;
+    // first d' with a plan of s-1 stages over blocks 1..i (finite values are a suffix of the row)
+    const unsigned long long fin = __ballot(lane < D - 1 && r.F != INF);
+    if (fin == 0ull || __ballot(fit) == 0ull) continue;
+    const int dlo = max(s - 1, __ffsll((long long)fin));
+    VT *const f = sf[buf], *const b = sb[buf];
+    const double xf = (double)(VT)(Tj - (int64_t)lane_bcast((uint64_t)Trow, i - i_lo));
+    const double xb = (double)(VT)(TBj - (int64_t)lane_bcast((uint64_t)TBrow, i - i_lo));
+#pragma unroll
+    for (int k = 0; k < KP; ++k) {
+      const int n = wave + kSplitWaves * k + 1;  // replicas
+      const double o = ceil_div_offset<VT>(n);
+      const bool ok = fit && n >= r.rmn;
+      f[(n - 1) * 64 + lane] = ok ? (VT)(CeilDiv<VT>::at(xf + o, inv[k]) + hc[k]) : split_nofit<VT>();
+      b[(n - 1) * 64 + lane] = ok ? CeilDiv<VT>::at(xb + o, inv[k]) : split_nofit<VT>();
+    }
+    lds_barrier();
+    VT row_v[KP];
+#pragma unroll
+    for (int k = 0; k < KP; ++k) row_v[k] = INF;
+    split_row<VT, KP, 0>(dlo, D, d0, lane, r.F, r.B, f, b, row_v);
+#pragma unroll
+    for (int k = 0; k < KP; ++k) {  // rows ascend: an equal sum keeps the earlier one
+      const bool ok = row_v[k] < best_v[k];
+      best_v[k] = ok ? row_v[k] : best_v[k];
+      best_i[k] = ok ? (uint32_t)i : best_i[k];
+    }
+    if (n_buf == 2) buf ^= 1;  // (rewritten behind the next row's barrier, which every wave reaches after its reads)
+    else lds_barrier();
+  }
+  if (jj >= N || jj + 1 < s) return;
+  unsigned long long RANNC_GLOBAL *K = gptr((unsigned long long *)pr.keys);
+#pragma unroll
+  for (int k = 0; k < KP; ++k) {
+    const int dk = d0 + kSplitWaves * k;
+    if (dk <= D && best_v[k] < split_nofit<VT>())
+      (void)__hip_atomic_fetch_min(&K[(int64_t)(dk - 1) * (N + 1) + jj + 1], split_pack<VT>(best_v[k], best_i[k]),
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
 template <typename VT, int DP>
 __global__ __launch_bounds__(64 * kSplitWaves) void level_split_fast_kernel(
     const ProblemDev *__restrict__ probs, const int s) {
-  constexpr VT INF = Lim<VT>::inf;
-  constexpr int KP = DP / kSplitWaves;  // device totals per wave
   const ProblemDev &pr = probs[blockIdx.z];
   if (s > pr.S_eff) return;
-  const int N = pr.N, D = pr.D, nch = pr.nch;
+  const int N = pr.N;
   const int32_t RANNC_GLOBAL *__restrict__ runs = gptr((const int32_t *)pr.runs);
   if ((int)blockIdx.x >= runs[0]) return;
   const unsigned desc = (unsigned)runs[1 + blockIdx.x];
@@ -182,78 +265,78 @@ __global__ __launch_bounds__(64 * kSplitWaves) void level_split_fast_kernel(
   const int i_hi = min(min(i0 + rows - 1, 64 * c + 63), N - 1);
   const int i_lo = max(i0, s - 1);
   if (i_hi < i_lo) return;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int jj = 64 * c + lane;
-  const int64_t lvl = (int64_t)(N + 1) * DP;
-  const VT RANNC_GLOBAL *__restrict__ Vprev = gptr((const VT *)pr.V) + (int64_t)(s - 2) * lvl;
-  const VT RANNC_GLOBAL *__restrict__ Fprev = gptr((const VT *)pr.VF) + (int64_t)(s - 2) * lvl;
-  const VT RANNC_GLOBAL *__restrict__ Bprev = gptr((const VT *)pr.VB) + (int64_t)(s - 2) * lvl;
-  const VT RANNC_GLOBAL *__restrict__ costf = gptr((const VT *)pr.cost);
-  const VT RANNC_GLOBAL *__restrict__ costb = gptr((const VT *)pr.costb);
-  const uint8_t RANNC_GLOBAL *__restrict__ rmin = gptr((const uint8_t *)pr.rmin);
-  const uint8_t RANNC_GLOBAL *__restrict__ ufit = gptr((const uint8_t *)pr.ufit);
-  const int rl = D - s + 1;  // replicas left for stage s when s-1 devices are spent earlier
-  const int d0 = s + wave;   // this wave's device totals: d0, d0 + 8, ...
-  __shared__ VT sf[DP * 64], sb[DP * 64];
-
-  VT best_v[KP];
-  uint32_t best_key[KP];
-#pragma unroll
-  for (int k = 0; k < KP; ++k) { best_v[k] = INF; best_key[k] = 0xFFFFFFFFu; }
-
-  for (int i = i_lo; i <= i_hi; ++i) {  // every condition below is uniform over the workgroup
-    if (Vprev[(int64_t)i * DP + D - 2] == INF) continue;  // no (s-1)-stage plan over blocks 1..i
-    const int64_t u = unit_index(nch, i, c);
-    if (!ufit[u]) continue;  // no stage of this unit fits: its rows were never written
-    __syncthreads();  // the previous row's reads of the staged units are done
-    for (int e = tid; e < rl * 64; e += 64 * kSplitWaves) {
-      sf[e] = costf[u * 64 * D + e];
-      sb[e] = costb[u * 64 * D + e];
-    }
-    const int rmn = (jj >= i && jj < N) ? (int)rmin[u * 64 + lane] : 255;
-    // first d' with a plan (finite values are a suffix of the row)
-    const VT av = (lane < D) ? Vprev[(int64_t)i * DP + lane] : INF;
-    const unsigned long long fin = __ballot(av != INF);
-    const int dlo = max(s - 1, __ffsll((long long)fin));  // lane q holds d' = q + 1
-    int lim[KP];
-#pragma unroll
-    for (int k = 0; k < KP; ++k) lim[k] = (d0 + kSplitWaves * k <= D) ? d0 + kSplitWaves * k - rmn : -1;
-    __syncthreads();
-    split_row<VT, DP, 0>(dlo, D, d0, i, lane, Fprev + (int64_t)i * DP, Bprev + (int64_t)i * DP, sf, sb, lim,
-                     best_v, best_key);
+  constexpr int BUF = 4 * DP * 64 * (int)sizeof(VT) <= 64 * 1024 ? 2 : 1;
+  __shared__ VT sf[BUF][DP * 64], sb[BUF][DP * 64];
+#define RANNC_ROWS(K)                                                                              \
+  case K:                                                                                          \
+    if constexpr (kSplitWaves * K <= DP) split_rows<VT, DP, K>(pr, s, c, i_lo, i_hi, sf, sb, BUF); \
+    break;
+  switch ((pr.D - s + kSplitWaves) / kSplitWaves) {
+    RANNC_ROWS(1) RANNC_ROWS(2) RANNC_ROWS(3) RANNC_ROWS(4)
+    RANNC_ROWS(5) RANNC_ROWS(6) RANNC_ROWS(7) RANNC_ROWS(8)
+    default: break;
   }
-  if (jj >= N || jj + 1 < s) return;
-  unsigned long long RANNC_GLOBAL *K = gptr((unsigned long long *)pr.keys);
-#pragma unroll
-  for (int k = 0; k < KP; ++k) {
-    const int dk = d0 + kSplitWaves * k;
-    if (dk <= D && best_v[k] != INF)
-      (void)__hip_atomic_fetch_min(&K[(int64_t)(dk - 1) * (N + 1) + jj + 1], split_pack<VT>(best_v[k], best_key[k]),
-                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+#undef RANNC_ROWS
 }
 
+// Packed winners of level s into V and the two carried maxima; clears the key table for the next level.
+// Eight lanes per cell look for the first d' of the winner's row i whose sum is the cell's value (there is
+// one), each at every eighth d'.  Bound by latency: the key, then one round of reads.
+constexpr int kFinalizeLanes = 8;
 template <typename VT>
 __global__ __launch_bounds__(256) void split_finalize_kernel(const ProblemDev *__restrict__ probs, const int s) {
   const ProblemDev &pr = probs[blockIdx.z];
   if (s > pr.S_eff) return;
-  const int N = pr.N, D = pr.D, DP = pr.DP, nch = pr.nch;
-  const int j = blockIdx.x * 256 + threadIdx.x, d = blockIdx.y + 1;
-  if (j > N || d > D) return;
+  __shared__ double inv[65];
+  const int N = pr.N, D = pr.D, DP = pr.DP;
+  const int sub = threadIdx.x & (kFinalizeLanes - 1);
+  const int j = blockIdx.x * (256 / kFinalizeLanes) + (int)(threadIdx.x / kFinalizeLanes), d = blockIdx.y + 1;
   unsigned long long *K = (unsigned long long *)pr.keys + (int64_t)(d - 1) * (N + 1) + j;
-  const unsigned long long key = *K;
-  if (key == ~0ull) return;  // no candidate: the cell keeps "no plan"
-  *K = ~0ull;                // ready for the next level
-  const int i = split_key_i<VT>(key), dp = split_key_d<VT>(key);
-  const int jj = j - 1;
+  const unsigned long long key = j <= N && d <= D ? *K : ~0ull;
+  if (threadIdx.x < 64) inv[threadIdx.x + 1] = 1.0 / (double)(threadIdx.x + 1);
+  __syncthreads();
+  if (key == ~0ull) return;  // no candidate: the cell keeps "no plan" (the eight lanes of a cell agree)
+  const int i = split_key_i<VT>(key);
+  const VT v = split_key_v<VT>(key);
   const int64_t lvl = (int64_t)(N + 1) * DP;
-  const int64_t pc = (int64_t)(s - 2) * lvl + (int64_t)i * DP + dp - 1;
-  const int64_t te = (unit_index(nch, i, jj >> 6) * D + (d - dp - 1)) * 64 + (jj & 63);
-  const int64_t e = (int64_t)(s - 1) * lvl + (int64_t)j * DP + d - 1;
-  ((VT *)pr.V)[e] = split_key_v<VT>(key);
-  ((VT *)pr.VF)[e] = vmax(((const VT *)pr.VF)[pc], ((const VT *)pr.cost)[te]);
-  ((VT *)pr.VB)[e] = vmax(((const VT *)pr.VB)[pc], ((const VT *)pr.costb)[te]);
+  const VT RANNC_GLOBAL *F = gptr((const VT *)pr.VF) + (int64_t)(s - 2) * lvl + (int64_t)i * DP - 1;
+  const VT RANNC_GLOBAL *B = gptr((const VT *)pr.VB) + (int64_t)(s - 2) * lvl + (int64_t)i * DP - 1;
+  const int rmn = (int)pr.rmin[unit_index(pr.nch, i, (j - 1) >> 6) * 64 + ((j - 1) & 63)];
+  const VT xf = (VT)(pr.T[j] - pr.T[i]), xb = (VT)(pr.TB[j] - pr.TB[i]), xc = pr.C ? (VT)pr.C[j] : (VT)0;
+#pragma unroll 1
+  for (int d1 = s - 1 + sub; d1 - sub <= d - 1; d1 += 2 * kFinalizeLanes) {
+    VT f[2], b[2];
+    unsigned mine = 0;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int dp = min(d1 + u * kFinalizeLanes, d - 1);
+      f[u] = F[dp];
+      b[u] = B[dp];
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int dp = d1 + u * kFinalizeLanes, r = max(d - dp, 1);
+      const double in = inv[r];
+      f[u] = vmax(f[u], (VT)(ceil_div<VT>(xf, r, in) + (xc ? ceil_div<VT>(xc, r, in) : (VT)0)));
+      b[u] = vmax(b[u], ceil_div<VT>(xb, r, in));
+      if (dp <= d - 1 && r >= rmn && split_sum(f[u], b[u]) == v) mine |= 1u << u;
+    }
+    // the smallest d' of the two rounds of eight
+    const int base = (threadIdx.x & 63) & ~(kFinalizeLanes - 1);
+    const unsigned m0 = (unsigned)(__ballot(mine & 1u) >> base) & ((1u << kFinalizeLanes) - 1u);
+    const unsigned m1 = (unsigned)(__ballot(mine & 2u) >> base) & ((1u << kFinalizeLanes) - 1u);
+    if (m0 | m1) {
+      const int u = m0 ? 0 : 1;
+      if (sub == __ffs((int)(m0 ? m0 : m1)) - 1) {
+        const int64_t e = (int64_t)(s - 1) * lvl + (int64_t)j * DP + d - 1;
+        ((VT *)pr.V)[e] = v;
+        ((VT *)pr.VF)[e] = u ? f[1] : f[0];
+        ((VT *)pr.VB)[e] = u ? b[1] : b[0];
+        *K = ~0ull;  // ready for the next level
+      }
+      break;
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -284,10 +367,19 @@ hipError_t launch_level_split(const ProblemDev *p, const LaunchShape &sh, int bi
   return hipGetLastError();
 }
 
-int split_rows_per_item(const LaunchShape &sh, int n_cus) {
-  // two workgroups of eight waves per compute unit; the work list has room for kSplitSmallRows such items
-  const int64_t rows = merge_launch_rows(sh), slots = std::min<int64_t>(2ll * n_cus, kSplitSmallRows / 2);
-  return rows <= slots ? 1 : rows <= 2 * slots ? 2 : 0;
+// A workgroup's rows are a chain, and every workgroup pays DP x 64 atomics of 8 bytes behind it (about 5 ps
+// each over the launch): as few rows as leave about this many workgroups.  Measured per call, items of
+// 1 / 2 / 3 / 4 / 8 rows: 256 blocks at 32 devices (640 rows) 283 / 271 / 293 / - / - us, 400 at 32 (1 744
+// rows) 796 / 559 / 540 / - / -, outer driver at 96 blocks (1 440 rows of its 32-device searches) 575 / 582 /
+// 621 / - / -, 1024 at 64 (8 704 rows) 10.8 / 6.8 / 5.5 / 5.5 / 5.9 ms where memory never binds and 2.8 /
+// 2.1 / 2.1 / - / 2.8 where it does, 900 at 16 (7 620 rows) 937 / 551 / 429 / 404 / 377 us, 300 at 8 (940 rows)
+// 166 / 137 / 133 / 135 / 146.
+int split_rows_per_item(const LaunchShape &sh, int DP) {
+  const int64_t groups = DP == 8 ? 256 : DP == 64 ? 2560 : 1024;
+  const int64_t rows = std::min<int64_t>(16, (sh.wide_rows + groups - 1) / groups);
+  int64_t most = 0;  // rows of the largest search: its list has room for single-row items up to a size
+  for (int c = 0; c < sh.max_nch; ++c) most += std::min(64 * c + 64, sh.max_N);
+  return (int)std::max<int64_t>(most > kSplitSmallRows ? 4 : 1, rows);
 }
 
 template <typename VT>
@@ -299,14 +391,14 @@ static void split_fast_go(const ProblemDev *p, const LaunchShape &sh, int DP, in
     else if (DP == 16) hipLaunchKernelGGL((level_split_fast_kernel<VT, 16>), grid, block, 0, st, p + q0, s);
     else if (DP == 32) hipLaunchKernelGGL((level_split_fast_kernel<VT, 32>), grid, block, 0, st, p + q0, s);
     else hipLaunchKernelGGL((level_split_fast_kernel<VT, 64>), grid, block, 0, st, p + q0, s);
-    hipLaunchKernelGGL((split_finalize_kernel<VT>), dim3((sh.max_N + 256) / 256, sh.max_D, nq), dim3(256), 0, st,
+    hipLaunchKernelGGL((split_finalize_kernel<VT>), dim3((sh.max_N + 256 / kFinalizeLanes) / (256 / kFinalizeLanes), sh.max_D, nq), dim3(256), 0, st,
                        p + q0, s);
   }
 }
 
 hipError_t launch_level_split_fast(const ProblemDev *p, const LaunchShape &sh, int bits, int DP, int s,
                                    int rows_per_item, hipStream_t st) {
-  const int per = rows_per_item > 0 ? rows_per_item : kSplitMinRows;
+  const int per = rows_per_item;
   int64_t items = 0;  // upper bound on the items of any problem of the launch
   for (int c = 0; c < sh.max_nch; ++c) items += (min(64 * c + 64, sh.max_N) + per - 1) / per;
   if (bits == 32) split_fast_go<uint32_t>(p, sh, DP, s, items, st);
