@@ -458,10 +458,14 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
   // handles, 64-bit ones up to 2^42 - 2 ns); RANNC_DP_ALGO_SCAN and larger time bounds take the
   // literal one
   const bool split_fast = split && !scan && packed_of(&h->lim);
+  // what the host knows about the total time of a search of this batch: the handle's bound, or the
+  // outer driver's own sum over the inputs it has just scaled
+  const int64_t total_bound = h->call_total_bound > 0 ? std::min(h->call_total_bound, h->lim.max_total_time_ns)
+                                                      : h->lim.max_total_time_ns;
   // stage times recomputed inside the level kernel instead of read from their table: where it
   // applies, on request, or (AUTO) for the classes whose launches are large enough to be bound by
   // throughput
-  const bool can_recompute = !scan && !split && h->bits == 32 && !b->cut_bytes;
+  const bool can_recompute = !scan && !split && !b->cut_bytes && rannc::can_recompute_times(h->bits, total_bound);
   bool recompute_cls[4];
   for (int k = 0; k < 4; ++k)
     recompute_cls[k] = can_recompute && (h->lim.algo == RANNC_DP_ALGO_RECOMPUTE ||
@@ -472,10 +476,6 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
   h->ev_valid = false;
   h->level_launches = 0;
   if (timing) ok = ok && hipEventRecord(h->ev[0], st) == hipSuccess;
-  // what the host knows about the total time of a search of this batch: the handle's bound, or the
-  // outer driver's own sum over the inputs it has just scaled
-  const int64_t total_bound = h->call_total_bound > 0 ? std::min(h->call_total_bound, h->lim.max_total_time_ns)
-                                                      : h->lim.max_total_time_ns;
   bool fused[4] = {false, false, false, false};
   bool fused_direct[4] = {false, false, false, false};  // one-launch kernel that recomputes the stage times
   // estimated time of a class of few small searches (us): as one launch with recomputed stage times
@@ -600,13 +600,14 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
     // Rows per item of the level kernel: chosen on the device from the size of the windows unless
     // the handle fixes it, or the host does for a launch of many rounds (merge_grid_items).
     const int slots = h->n_cus * rannc::merge_workgroups_per_cu(h->bits, kClasses[k], recompute_cls[k]);
+    const int max_rows = recompute_cls[k] ? rannc::merge_max_rows(h->bits) : 64;
     int rows_for_list = -1;
     if (split) rows_for_list = rannc::split_rows_per_item(sh, kClasses[k]);
     else
       merge_items[k] = rannc::merge_grid_items(sh, rannc::merge_rows_per_item(h->tune_spw), slots, recompute_cls[k],
-                                               &rows_for_list);
-    ok = rannc::launch_setup(src + cls_start[k], cp, sh.nprob, rows_for_list, merge_items[k], slots, recompute_cls[k], st) ==
-         hipSuccess;
+                                               max_rows, &rows_for_list);
+    ok = rannc::launch_setup(src + cls_start[k], cp, sh.nprob, rows_for_list, merge_items[k], slots, recompute_cls[k],
+                             max_rows, st) == hipSuccess;
     ok = ok && staging_read();
     ok = ok && rannc::launch_build(cp, sh, h->bits, kClasses[k], recompute_cls[k] || split_fast ? 1 : 3, st) == hipSuccess;
     if (split) ok = ok && rannc::launch_split_level1(cp, sh, h->bits, st) == hipSuccess;

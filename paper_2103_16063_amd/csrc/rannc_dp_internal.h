@@ -53,9 +53,11 @@ __host__ __device__ inline int64_t max_runs(int nch) {
 // kMergeRows16From rows (unpruned), of 8 from kMergeRows8From, of 4 below.
 constexpr int kMergeWaves = 4;
 constexpr int kMergeMinRows = 4;
+// largest work item (rows): the recomputing form holds the item's rows in LDS
+__host__ __device__ constexpr int merge_max_rows(int bits) { return bits == 64 ? 32 : 64; }
 constexpr int kMergeRows8From = 6144;
 constexpr int kMergeRows16From = 16384;
-// From this many rows (unpruned) in a launch on, a 32-bit search without a communication term has its
+// From this many rows (unpruned) in a launch on, a search without a communication term has its
 // stage times recomputed in the level kernel (RANNC_DP_ALGO_AUTO), which also saves building their
 // table.  Measured per solve, table against recomputed: 1024 blocks at 64 devices 410 / 397 us where
 // memory binds and 800 / 555 us where it does not, 700 blocks at 48 devices 289 / 268 us, 300 at 64
@@ -137,15 +139,15 @@ hipError_t launch_build(const ProblemDev *probs, const LaunchShape &sh, int bits
 // src: the descriptors, in device memory (probs itself) or in pinned host memory the device can read;
 // the launch then also stores them to probs
 hipError_t launch_setup(const ProblemDev *src, ProblemDev *probs, int Q, int rows_per_item, int max_items, int slots, bool paired,
-                        hipStream_t st);
+                        int max_rows, hipStream_t st);
 int merge_workgroups_per_cu(int bits, int DP, bool recompute);
 int merge_rows_per_item(int rows_per_wave);
 // rows_for_list: what launch_setup is to be given as rows_per_item (the size the host fixed, or -1)
-int merge_grid_items(const LaunchShape &sh, int rows_per_item, int slots, bool paired, int *rows_for_list);
+int merge_grid_items(const LaunchShape &sh, int rows_per_item, int slots, bool paired, int max_rows, int *rows_for_list);
 // rows of the searches of a launch if nothing is pruned (every chunk c holds rows 0 .. 64c+63)
 int64_t merge_launch_rows(const LaunchShape &sh);
 // recompute: the level kernel computes the stage times from the prefix sums instead of reading
-// their table (32-bit values only)
+// their table (where can_recompute_times says so)
 // items: merge_grid_items of the launch, the value launch_setup was given
 // host_one: for a launch over one search, a host copy of its descriptor (passed by value), or null
 hipError_t launch_level_merge(const ProblemDev *probs, const LaunchShape &sh, int bits, int s,
@@ -156,6 +158,8 @@ int small_max_blocks();
 // small_can_recompute says so, and only for searches without a communication term);
 // max_total_time: the largest total time a search of the launch can have without being flagged
 bool small_can_recompute(int bits, int DP, int64_t max_total_time);
+// whether the level kernel can recompute the stage times
+bool can_recompute_times(int bits, int64_t max_total_time);
 // src: as in launch_setup
 hipError_t launch_solve_small(const ProblemDev *src, ProblemDev *probs, int Q, int bits, int DP, bool direct, int64_t *d_opt,
                               int32_t *d_n_stages, int64_t *d_est, int32_t *d_status, hipStream_t st);

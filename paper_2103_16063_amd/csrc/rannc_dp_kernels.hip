@@ -327,7 +327,8 @@ __device__ void setup_fill(const ProblemDev &pr, int64_t t0, int64_t stride) {
 }
 
 __global__ __launch_bounds__(kSetupThreads) void setup_kernel(const ProblemDev *src, ProblemDev *probs, int rows,
-                                                             int max_items, int batch, int slots, int paired) {
+                                                             int max_items, int batch, int slots, int paired,
+                                                             int max_rows) {
   __shared__ __align__(8) uint32_t desc[sizeof(ProblemDev) / 4];
   const ProblemDev pr = fetch_problem(src + blockIdx.y, probs + blockIdx.y, blockIdx.x == 0, desc);
   const int N = pr.N, tid = threadIdx.x;
@@ -427,7 +428,8 @@ __global__ __launch_bounds__(kSetupThreads) void setup_kernel(const ProblemDev *
   // ---- windows ----
   __shared__ int start[1025];  // nch <= 1024 (N <= 65535)
   __shared__ RunSegments seg[1024];  // every chunk's segments
-  constexpr int NC = 16;  // candidate item sizes 4, 8, ..., 64 rows
+  constexpr int NC = 16;  // candidate item sizes 4, 8, ..., 64 rows, up to max_rows
+  const int most = max_rows / 4;
   __shared__ int count[NC];
   const int nch = pr.nch, D = pr.D;
   const uint64_t M = (uint64_t)pr.M;
@@ -474,12 +476,12 @@ __global__ __launch_bounds__(kSetupThreads) void setup_kernel(const ProblemDev *
     }
     __syncthreads();
     {
-      int pick = NC - 1;
-      for (int k = NC - 1; k >= 0; --k)
+      int pick = most - 1;
+      for (int k = most - 1; k >= 0; --k)
         if (count[k] <= max_items) pick = k;
       if ((long long)count[pick] * batch > slots) {
         bool one_round = false;
-        for (int k = pick + 1; k < NC; ++k) {
+        for (int k = pick + 1; k < most; ++k) {
           const long long then = (long long)count[k] * batch;
           if (then <= slots) {
             if (2 * then >= slots) { pick = k; one_round = true; }
@@ -490,7 +492,7 @@ __global__ __launch_bounds__(kSetupThreads) void setup_kernel(const ProblemDev *
         // leave one and a half rounds, by the rows that are really there (the host, which fixes the size for
         // a launch over many searches, cannot see the pruning of a single one)
         if (!one_round && paired && batch == 1)
-          for (int k = NC - 1; k > pick; --k)
+          for (int k = most - 1; k > pick; --k)
             if (2 * count[k] >= 3 * slots) { pick = k; break; }
       }
       rows = 4 * (pick + 1);
@@ -764,23 +766,25 @@ __device__ __forceinline__ void row_merge_direct(VT (&x)[H], AP arow, VT tij, in
 // memory binds, 506 -> 474 us where it does not; 512 searches of 128 blocks at 64 devices 92 -> 82 us).
 // H: width of the merge (multiple of eight, at least rl); LS: row stride of the tile, whose entry t is
 // output t of the merge.  Returns whether any row of this wave had work.
-constexpr int kItemRows = 66;  // most rows of V[s-1] an item reads: 64, or 2 x 33 for the pairs of a diagonal block
-template <int HMAX> struct ItemRows {
-  static constexpr int AS = HMAX + 4;  // row stride of the copied rows: 16-byte aligned, rows on different banks
-  uint32_t a[kItemRows * AS];
-  uint8_t rmin[kItemRows * 64];
-  int64_t T[kItemRows], Tcol[64];  // prefix sums of the rows and of the chunk's columns
+// Most rows of V[s-1] an item reads: those of the largest item, or twice the pairs of half a diagonal block.
+template <typename VT> constexpr int item_rows() { return merge_max_rows(8 * sizeof(VT)) + 2; }
+template <typename VT, int HMAX> struct ItemRows {
+  static constexpr int E = 16 / (int)sizeof(VT);  // values per 16 bytes
+  static constexpr int AS = HMAX + E;             // row stride of the copied rows: 16-byte aligned, rows on different banks
+  VT a[item_rows<VT>() * AS];
+  uint8_t rmin[item_rows<VT>() * 64];
+  int64_t T[item_rows<VT>()], Tcol[64];  // prefix sums of the rows and of the chunk's columns
 };
 
-template <int H, int LS, int HMAX>
-__device__ __forceinline__ bool merge_rows_direct(uint32_t *tile, ItemRows<HMAX> &it, const ProblemDev &pr, const int s,
+template <typename VT, int H, int LS, int HMAX>
+__device__ __forceinline__ bool merge_rows_direct(VT *tile, ItemRows<VT, HMAX> &it, const ProblemDev &pr, const int s,
                                                   const int c, const int i0, const int i_hi, const int lane,
                                                   const int wave, const DirectConsts &k) {
-  using VT = uint32_t;
   constexpr VT INF = Lim<VT>::inf;
-  constexpr int AS = ItemRows<HMAX>::AS, NT = 64 * kMergeWaves;
+  constexpr int E = ItemRows<VT, HMAX>::E, AS = ItemRows<VT, HMAX>::AS, NT = 64 * kMergeWaves;
   typedef uint32_t Quad __attribute__((ext_vector_type(4)));
-  typedef uint32_t QuadAny __attribute__((ext_vector_type(4), aligned(4)));  // (a[sig] is any word of the row)
+  typedef VT Values __attribute__((ext_vector_type(E)));
+  typedef VT ValuesAny __attribute__((ext_vector_type(E), aligned(sizeof(VT))));  // (a[sig] is any value of the row)
   const int N = pr.N, D = pr.D, DP = pr.DP, nch = pr.nch;
   const int sig = merge_shift(s, DP, H);
   const int64_t lvl = (int64_t)(N + 1) * DP;
@@ -798,10 +802,10 @@ __device__ __forceinline__ bool merge_rows_direct(uint32_t *tile, ItemRows<HMAX>
     const int row = e < n ? i0 + e : 64 * c + 64 - p1 + (e - n);
     return min(min(row, 64 * c + 63), N - 1);  // (p = 0 has no second row; rows beyond the chain have no work)
   };
-  for (int e = threadIdx.x; e < staged * (H / 4); e += NT) {
-    const int row = e / (H / 4), q = e % (H / 4);
-    const QuadAny v = *(const QuadAny RANNC_GLOBAL *)(Vprev + (int64_t)row_of(row) * DP + 4 * q);
-    *(Quad *)&it.a[row * AS + 4 * q] = (Quad)v;
+  for (int e = threadIdx.x; e < staged * (H / E); e += NT) {
+    const int row = e / (H / E), q = e % (H / E);
+    const ValuesAny v = *(const ValuesAny RANNC_GLOBAL *)(Vprev + (int64_t)row_of(row) * DP + E * q);
+    *(Values *)&it.a[row * AS + E * q] = (Values)v;
   }
   for (int e = threadIdx.x; e < staged * 4; e += NT)
     *(Quad *)&it.rmin[e * 16] = *(const Quad RANNC_GLOBAL *)(rmin + unit_index(nch, row_of(e >> 2), c) * 64 + (e & 3) * 16);
@@ -834,14 +838,15 @@ __device__ __forceinline__ bool merge_rows_direct(uint32_t *tile, ItemRows<HMAX>
     x += kMergeWaves;
     if (__ballot(act) == 0ull) continue;
     any = true;
-    const uint32_t tij = (uint32_t)(it.Tcol[r.col] - r.Ti);
+    const VT tij = (VT)(it.Tcol[r.col] - r.Ti);
     VT w[H];
 #pragma unroll
-    for (int g = 0; g < H / 4; ++g) {
-      const Quad v = *(const Quad *)&it.a[r.e * AS + 4 * g];
-      w[4 * g] = v.x; w[4 * g + 1] = v.y; w[4 * g + 2] = v.z; w[4 * g + 3] = v.w;
+    for (int g = 0; g < H / E; ++g) {
+      const Values v = *(const Values *)&it.a[r.e * AS + E * g];
+#pragma unroll
+      for (int u = 0; u < E; ++u) w[E * g + u] = v[u];
     }
-    row_merge_direct<uint32_t, H, InPlaceRow>(w, InPlaceRow(), tij, r.rmn, k);
+    row_merge_direct<VT, H, InPlaceRow>(w, InPlaceRow(), tij, r.rmn, k);
     if (act) {
 #pragma unroll
       for (int t = 0; t < H; ++t) atomicMin(&tile[r.col * LS + t], w[t]);
@@ -853,7 +858,7 @@ __device__ __forceinline__ bool merge_rows_direct(uint32_t *tile, ItemRows<HMAX>
 // Waves per SIMD the level kernel is compiled for: the two value arrays of the widest 32-bit case
 // fit the 168 registers of three waves per SIMD (the compiler left alone takes one more).
 template <typename VT, int HMAX, bool DIRECT> constexpr int merge_waves_per_simd() {
-  return HMAX == 64 && !DIRECT ? 3 : 1;
+  return HMAX == 64 && (!DIRECT || sizeof(VT) == 8) ? 3 : 1;
 }
 
 // The rows i0+wave, i0+wave+4, ... <= i_hi of one work item, folded into acc (running minimum of the
@@ -956,11 +961,11 @@ __device__ __forceinline__ void level_merge_body(const ProblemDev &pr, const int
   if constexpr (DIRECT) {
     DirectConsts k;
     direct_consts_init(k);
-    __shared__ __align__(16) ItemRows<HMAX> rows_in;
+    __shared__ __align__(16) ItemRows<VT, HMAX> rows_in;
 #define RANNC_ROWS(K)                                                                            \
   case K:                                                                                      \
     if constexpr (8 * K <= HMAX)                                                               \
-      any = merge_rows_direct<8 * K, LS>(tile, rows_in, pr, s, c, i0, i_hi, lane, wave, k);      \
+      any = merge_rows_direct<VT, 8 * K, LS>(tile, rows_in, pr, s, c, i0, i_hi, lane, wave, k);  \
     break;
     switch (ng) {
       RANNC_ROWS(1) RANNC_ROWS(2) RANNC_ROWS(3) RANNC_ROWS(4)
@@ -1916,12 +1921,12 @@ __global__ __launch_bounds__(256) void arg_init_kernel(const ProblemDev *__restr
 // Launchers
 // ---------------------------------------------------------------------------------------
 hipError_t launch_setup(const ProblemDev *src, ProblemDev *probs, int Q, int rows_per_item, int max_items, int slots,
-                        bool paired, hipStream_t st) {
+                        bool paired, int max_rows, hipStream_t st) {
   const int fill = Q >= 256 ? 4 : Q >= 16 ? 16 : 128;  // workgroups that fill a search's V
   for (int q0 = 0; q0 < Q; q0 += 65535) {
     const int nq = min(65535, Q - q0);
     hipLaunchKernelGGL(setup_kernel, dim3(1 + fill, nq), dim3(kSetupThreads), 0, st, src + q0, probs + q0, rows_per_item,
-                       max_items, Q, slots, paired ? 1 : 0);
+                       max_items, Q, slots, paired ? 1 : 0, max_rows);
   }
   return hipGetLastError();
 }
@@ -1942,7 +1947,7 @@ int64_t merge_launch_rows(const LaunchShape &sh) {
   return all_rows * sh.nprob;
 }
 
-int merge_grid_items(const LaunchShape &sh, int rows_per_item, int slots, bool paired, int *rows_for_list) {
+int merge_grid_items(const LaunchShape &sh, int rows_per_item, int slots, bool paired, int max_rows, int *rows_for_list) {
   // items of the largest search of the launch if nothing is pruned, in items of `rows` rows: the
   // segments of run_segments for windows that start at row 0 (a pruned window has no more rows in
   // either segment, so no more items at any size)
@@ -1956,8 +1961,8 @@ int merge_grid_items(const LaunchShape &sh, int rows_per_item, int slots, bool p
     }
     return std::max<int64_t>(1, items);
   };
-  int rows = rows_per_item;
-  *rows_for_list = rows_per_item;
+  int rows = std::min(rows_per_item, max_rows);
+  *rows_for_list = rows;
   if (rows <= 0) {
     const int64_t launch_rows = merge_launch_rows(sh);
     rows = launch_rows >= kMergeRows16From ? 16 : launch_rows >= kMergeRows8From ? 8 : kMergeMinRows;
@@ -1968,7 +1973,7 @@ int merge_grid_items(const LaunchShape &sh, int rows_per_item, int slots, bool p
     // registers; six workgroups per compute unit at 32 devices since: one and a quarter rounds 2.13 ms
     // for all levels, two 2.13, three 2.25; over ragged batches of 100 to 1 500 searches within 5 %).
     if (paired && sh.nprob > 1 && items_at(rows) * sh.nprob > slots)
-      for (int r = 64; r > rows; r -= 4)
+      for (int r = max_rows; r > rows; r -= 4)
         if (4 * items_at(r) * sh.nprob >= 5ll * slots) { rows = r; *rows_for_list = r; break; }
   }
   return (int)items_at(rows);
@@ -1981,6 +1986,7 @@ int merge_workgroups_per_cu(int bits, int DP, bool recompute) {
     if (recompute) return DP == 64 ? 4 : DP == 32 ? 6 : 8;
     return DP == 64 ? 3 : DP == 32 ? 4 : DP == 16 ? 6 : 8;
   }
+  if (recompute) return DP == 64 ? 3 : DP == 32 ? 5 : 8;
   return DP == 64 ? 2 : DP == 32 ? 3 : DP == 16 ? 4 : 8;
 }
 
@@ -2043,7 +2049,6 @@ static void merge_go(const ProblemDev *p, const LaunchShape &sh, int s, int item
 
 hipError_t launch_level_merge(const ProblemDev *p, const LaunchShape &sh, int bits, int s, bool recompute,
                               int items, const ProblemDev *host_one, hipStream_t st) {
-  if (recompute && bits != 32) return hipErrorInvalidValue;
   const int need = sh.max_D - s + 1;  // widest merge of the launch
 #define GO(B, T, X)                                                                       \
   if (bits == B && recompute == X) {                                                      \
@@ -2056,6 +2061,7 @@ hipError_t launch_level_merge(const ProblemDev *p, const LaunchShape &sh, int bi
   GO(32, uint32_t, false)
   GO(32, uint32_t, true)
   GO(64, uint64_t, false)
+  GO(64, uint64_t, true)
 #undef GO
   return hipGetLastError();
 }
@@ -2065,8 +2071,9 @@ int small_max_blocks() { return kSmallMaxN; }
 // reciprocals and the merge do not fit the 128 registers of its sixteen waves): 32-bit values, or
 // 64-bit values where the caller's bound on a search's total time keeps every stage time in the
 // range the double-precision quotient is exact for
+bool can_recompute_times(int bits, int64_t max_total_time) { return bits == 32 || max_total_time <= kDirectWideMaxTime; }
 bool small_can_recompute(int bits, int DP, int64_t max_total_time) {
-  return DP <= 32 && (bits == 32 || max_total_time <= kDirectWideMaxTime);
+  return DP <= 32 && can_recompute_times(bits, max_total_time);
 }
 
 hipError_t launch_solve_small(const ProblemDev *src, ProblemDev *p, int Q, int bits, int DP, bool direct, int64_t *d_opt,
