@@ -607,7 +607,7 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
       merge_items[k] = rannc::merge_grid_items(sh, rannc::merge_rows_per_item(h->tune_spw), slots, recompute_cls[k],
                                                max_rows, &rows_for_list);
     ok = rannc::launch_setup(src + cls_start[k], cp, sh.nprob, rows_for_list, merge_items[k], slots, recompute_cls[k],
-                             max_rows, st) == hipSuccess;
+                             max_rows, sh.nprob == 1 ? &probs[cls_start[k]] : nullptr, st) == hipSuccess;
     ok = ok && staging_read();
     ok = ok && rannc::launch_build(cp, sh, h->bits, kClasses[k], recompute_cls[k] || split_fast ? 1 : 3, st) == hipSuccess;
     if (split) ok = ok && rannc::launch_split_level1(cp, sh, h->bits, st) == hipSuccess;
@@ -617,7 +617,8 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
   for (int k = 0; k < 4; ++k) {
     if (fused[k]) {
       ok = ok && rannc::launch_solve_small(src + cls_start[k], dp + cls_start[k], shape[k].nprob, h->bits, kClasses[k], fused_direct[k], d_opt,
-                                           d_n_stages, d_est_iter_ns, d_status, cs[k]) == hipSuccess;
+                                           d_n_stages, d_est_iter_ns, d_status,
+                                           shape[k].nprob == 1 ? &probs[cls_start[k]] : nullptr, cs[k]) == hipSuccess;
       ok = ok && staging_read();
       h->level_launches++;
     } else {

@@ -137,9 +137,10 @@ hipError_t launch_build(const ProblemDev *probs, const LaunchShape &sh, int bits
 // slots: workgroups of the level kernel that the device holds at a time
 // paired: the list for the level kernel that recomputes the stage times (diagonal blocks as row pairs)
 // src: the descriptors, in device memory (probs itself) or in pinned host memory the device can read;
-// the launch then also stores them to probs
+// the launch then also stores them to probs.  host_one: for a launch over one search, its descriptor in
+// host memory (passed by value instead), or null
 hipError_t launch_setup(const ProblemDev *src, ProblemDev *probs, int Q, int rows_per_item, int max_items, int slots, bool paired,
-                        int max_rows, hipStream_t st);
+                        int max_rows, const ProblemDev *host_one, hipStream_t st);
 int merge_workgroups_per_cu(int bits, int DP, bool recompute);
 int merge_rows_per_item(int rows_per_wave);
 // rows_for_list: what launch_setup is to be given as rows_per_item (the size the host fixed, or -1)
@@ -162,7 +163,7 @@ bool small_can_recompute(int bits, int DP, int64_t max_total_time);
 bool can_recompute_times(int bits, int64_t max_total_time);
 // src: as in launch_setup
 hipError_t launch_solve_small(const ProblemDev *src, ProblemDev *probs, int Q, int bits, int DP, bool direct, int64_t *d_opt,
-                              int32_t *d_n_stages, int64_t *d_est, int32_t *d_status, hipStream_t st);
+                              int32_t *d_n_stages, int64_t *d_est, int32_t *d_status, const ProblemDev *host_one, hipStream_t st);
 hipError_t launch_level_scan(const ProblemDev *probs, const LaunchShape &sh, int bits, int s,
                              int write_v, int32_t *arg_i, int32_t *arg_d, hipStream_t st);
 // Algorithm 1 with forward and backward maxima carried separately (problems with tb != null):

@@ -202,7 +202,7 @@ void build_kernel(const ProblemDev *__restrict__ probs, const int parts, const i
 // Window of the level kernels: wlo[c] = first row i that holds a stage into chunk c that fits for
 // some r <= D (0x7fffffff if none).  Rows below it are never visited.  Memory grows with the stage,
 // so row i <= 64c has such a stage iff the one that ends at the chunk's first column fits, and if row
-// 64c has one then so has every row from the first such row on: a binary search.  (If the chunk's
+// 64c has one then so has every row from the first such row on: a search, sixteen probes at a time.  (If the chunk's
 // first block fits no device by itself, the first later block that does starts the window.)
 //
 // Work list of the level kernels: the rows wlo[c] .. min(64c+63, N-1) of every chunk, cut into
@@ -226,9 +226,10 @@ void build_kernel(const ProblemDev *__restrict__ probs, const int parts, const i
 // of the block form two segments, and no item crosses from one into the other; the last item of a
 // segment carries the number of rows that are left.
 //
-// Bound by latency (a chain of a few memory round trips and barriers).  As four launches, with the
-// windows found by scanning a flag per unit that the table builder had written, this took 15 us on the
-// device at 96 blocks and 24 us at 1024, and every launch costs the host 3 us more.
+// Bound by latency (a chain of a few memory round trips and barriers): 7.4 us at 96 blocks, 8.3 us at
+// 251 with send times, 12 us at 1024.  With saturating sums, binary searches by a thread per chunk and the
+// send times four to a thread it took 10.7, 15.6 and 15 us; as four launches 15 us at 96 blocks and 24 us
+// at 1024, and every launch costs the host 3 us more.
 // ---------------------------------------------------------------------------------------
 constexpr int kSetupThreads = 256;
 
@@ -238,9 +239,16 @@ constexpr int kSetupThreads = 256;
 // later kernels read it (dst; src == dst: it is there already).  A copy in front of the first kernel
 // costs the host 6 us and the stream 4.  The words go through LDS into scalar registers, so that the
 // fields stay wave-uniform.  lds: sizeof(ProblemDev) bytes.
-__device__ __forceinline__ ProblemDev fetch_problem(const ProblemDev *src, ProblemDev *dst, bool keep, uint32_t *lds) {
+// one: the descriptor itself as a kernel argument (launches over one search: no read from the host at
+// all, 1 us), used if use_one.
+__device__ __forceinline__ ProblemDev fetch_problem(const ProblemDev *src, ProblemDev *dst, bool keep, uint32_t *lds,
+                                                    const ProblemDev &one, int use_one) {
   constexpr int W = (int)sizeof(ProblemDev) / 4;
   static_assert(W <= 64 && sizeof(ProblemDev) % 8 == 0, "a word per lane");
+  if (use_one) {
+    if (keep && threadIdx.x == 0) *dst = one;
+    return one;
+  }
   if (threadIdx.x < W / 2) {
     const uint64_t w = ((const uint64_t *)src)[threadIdx.x];
     ((uint64_t *)lds)[threadIdx.x] = w;
@@ -279,15 +287,18 @@ __device__ __forceinline__ bool fits_at(uint64_t P, uint64_t A, uint64_t M, int 
   return A <= slack * (uint64_t)D || __umul64hi(slack, (uint64_t)D) != 0;  // ceil(A/D) <= slack  <=>  A <= slack D
 }
 
-// inclusive sums over the workgroup, saturating at the limit (associative on [0, limit]), of NW values per thread
-template <int NW> __device__ __forceinline__ void setup_scan(uint64_t (&v)[NW], uint64_t (*part)[NW]) {
+// Inclusive sums over the workgroup of NW values per thread.  Values stay below 2^62; the upper halves
+// of all partial sums are collected in `high`: the total reaches 2^62 iff one of them has bit 30 or 31 set
+// (later sums may then wrap: the search is flagged and its values are not looked at).
+template <int NW> __device__ __forceinline__ void setup_scan(uint64_t (&v)[NW], uint64_t (*part)[4], uint32_t &high) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
       const uint64_t x = __shfl_up(v[w], o);
-      if (lane >= o) v[w] = min(v[w] + x, kSumLimit);
+      if (lane >= o) v[w] += x;
+      high |= (uint32_t)(v[w] >> 32);
     }
   }
   if (lane == 63)
@@ -298,7 +309,7 @@ template <int NW> __device__ __forceinline__ void setup_scan(uint64_t (&v)[NW], 
   for (int k = 0; k < kSetupThreads / 64 - 1; ++k)
     if (k < wave)
 #pragma unroll
-      for (int w = 0; w < NW; ++w) v[w] = min(v[w] + part[k][w], kSumLimit);
+      for (int w = 0; w < NW; ++w) { v[w] += part[k][w]; high |= (uint32_t)(v[w] >> 32); }
 }
 
 __device__ void setup_fill(const ProblemDev &pr, int64_t t0, int64_t stride) {
@@ -328,17 +339,19 @@ __device__ void setup_fill(const ProblemDev &pr, int64_t t0, int64_t stride) {
 
 __global__ __launch_bounds__(kSetupThreads) void setup_kernel(const ProblemDev *src, ProblemDev *probs, int rows,
                                                              int max_items, int batch, int slots, int paired,
-                                                             int max_rows) {
+                                                             int max_rows, const ProblemDev one, int use_one) {
   __shared__ __align__(8) uint32_t desc[sizeof(ProblemDev) / 4];
-  const ProblemDev pr = fetch_problem(src + blockIdx.y, probs + blockIdx.y, blockIdx.x == 0, desc);
+  const ProblemDev pr = fetch_problem(src + blockIdx.y, probs + blockIdx.y, blockIdx.x == 0, desc, one, use_one);
   const int N = pr.N, tid = threadIdx.x;
   if (blockIdx.x > 0) {
     setup_fill(pr, (int64_t)(blockIdx.x - 1) * kSetupThreads + tid, (int64_t)(gridDim.x - 1) * kSetupThreads);
     return;
   }
-  constexpr int U = 4;  // entries per thread and tile
+  // Entries per thread and tile.  Two keep the kernel, and with it the workgroups that fill V, at four
+  // waves per SIMD: over 1024 searches of 128 blocks that takes 40 us instead of 71 with four entries.
+  constexpr int U = 2;
   __shared__ uint64_t part[kSetupThreads / 64][4], last[4];
-  __shared__ uint64_t sP[kSetupLdsN + 1], sA[kSetupLdsN + 1];
+  __shared__ uint64_t sP[kSetupLdsN + 1], sA[kSetupLdsN + 1];  // (reused for the work list)
   __shared__ int flags;
   __shared__ unsigned long long max_cut;
   if (tid == 0) { flags = 0; max_cut = 0ull; sP[0] = 0; sA[0] = 0; }
@@ -354,66 +367,71 @@ __global__ __launch_bounds__(kSetupThreads) void setup_kernel(const ProblemDev *
   }
   uint64_t carry[4] = {0, 0, 0, 0};
   unsigned long long mc = 0ull;
-  for (int base = 0; base < N; base += U * kSetupThreads) {
-    const int k0 = base + U * tid;
-    uint64_t v[4][U], sum[4] = {0, 0, 0, 0};
+  uint32_t high = 0;
+  auto sums = [&](auto nw) {  // NW arrays
+    constexpr int NW = decltype(nw)::value;
+    for (int base = 0; base < N; base += U * kSetupThreads) {
+      const int k0 = base + U * tid;
+      uint64_t v[NW][U], sum[NW];
 #pragma unroll
-    for (int w = 0; w < 4; ++w)
-      if (w < 3 || bwd)
+      for (int w = 0; w < NW; ++w)
 #pragma unroll
         for (int u = 0; u < U; ++u) v[w][u] = (uint64_t)in[w][min(k0 + u, N - 1)];
 #pragma unroll
-    for (int w = 0; w < 4; ++w)
-      if (w < 3 || bwd)
+      for (int w = 0; w < NW; ++w) {
+        sum[w] = 0;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           uint64_t x = k0 + u < N ? v[w][u] : 0;
           if ((int64_t)x < 0) { myflags |= 1; x = 0; }
-          if (x >= kSumLimit) { myflags |= 2; x = kSumLimit; }
+          if (x >= kSumLimit) { myflags |= 2; x = 0; }
           v[w][u] = x;
-          sum[w] = min(sum[w] + x, kSumLimit);
+          sum[w] += x;
+          high |= (uint32_t)(sum[w] >> 32);
         }
-    uint64_t run[4] = {sum[0], sum[1], sum[2], sum[3]};
-    __syncthreads();  // (part and last are free again)
-    setup_scan<4>(run, part);
-    if (tid == kSetupThreads - 1)
+      }
+      uint64_t run[NW];
 #pragma unroll
-      for (int w = 0; w < 4; ++w) last[w] = run[w];
-    // back to the sum in front of this thread's entries: from the neighbour's inclusive sum
+      for (int w = 0; w < NW; ++w) run[w] = sum[w];
+      __syncthreads();  // (part and last are free again)
+      setup_scan<NW>(run, part, high);
+      if (tid == kSetupThreads - 1)
 #pragma unroll
-    for (int w = 0; w < 4; ++w)
-      if (w < 3 || bwd) {
-        uint64_t at = __shfl_up(run[w], 1);
-        if ((tid & 63) == 0) {
-          at = 0;
-          for (int k = 0; k < (tid >> 6); ++k) at = min(at + part[k][w], kSumLimit);
-        }
-        at = min(at + carry[w], kSumLimit);
+        for (int w = 0; w < NW; ++w) last[w] = run[w];
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        uint64_t at = carry[w] + run[w] - sum[w];  // in front of this thread's entries
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-          at = min(at + v[w][u], kSumLimit);
+          at += v[w][u];
+          high |= (uint32_t)(at >> 32);
           if (k0 + u < N) {
-            if (at >= kSumLimit) myflags |= 2;
             out[w][k0 + u + 1] = (int64_t)at;
             if (in_lds && w == 1) sP[k0 + u + 1] = at;
             if (in_lds && w == 2) sA[k0 + u + 1] = at;
           }
         }
       }
-    if (pr.o) {  // per-cut send time; the last block has no follower
-      for (int u = 0; u < U; ++u) {
-        const int k = k0 + u;
-        if (k >= N) break;
-        const uint64_t c = cut_time(pr.o[k], pr.bw, myflags);
-        pr.C[k + 1] = (k + 1 < N) ? (int64_t)c : 0;
-        if (k + 1 < N && c > mc) mc = c;
-      }
-    }
-    __syncthreads();
+      __syncthreads();
 #pragma unroll
-    for (int w = 0; w < 4; ++w) carry[w] = min(carry[w] + last[w], kSumLimit);
+      for (int w = 0; w < NW; ++w) carry[w] += last[w];
+    }
+  };
+  if (bwd) sums(std::integral_constant<int, 4>());
+  else sums(std::integral_constant<int, 3>());
+  if (high >> 30) myflags |= 2;
+  if (pr.o)  // per-cut send time; the last block has no follower
+#pragma unroll 1
+    for (int k = tid; k < N; k += kSetupThreads) {
+      const uint64_t c = cut_time(pr.o[k], pr.bw, myflags);
+      pr.C[k + 1] = (k + 1 < N) ? (int64_t)c : 0;
+      if (k + 1 < N && c > mc) mc = c;
+    }
+  if (pr.o) {
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) mc = max(mc, (unsigned long long)__shfl_xor(mc, o));
+    if (mc && (tid & 63) == 0) atomicMax(&max_cut, mc);
   }
-  if (mc) atomicMax(&max_cut, mc);
   if (myflags) atomicOr(&flags, myflags);
   __syncthreads();  // the sums in memory are visible to the whole workgroup as well
   if (tid == 0) {
@@ -434,25 +452,36 @@ __global__ __launch_bounds__(kSetupThreads) void setup_kernel(const ProblemDev *
   const int nch = pr.nch, D = pr.D;
   const uint64_t M = (uint64_t)pr.M;
   auto window = [&](auto P, auto A) {
-    for (int c = tid; c < nch; c += kSetupThreads) {
-      const int j = 64 * c + 1;  // the chunk's first column, for the rows up to 64c
+    // sixteen lanes per chunk: sixteen probes at a time
+    const int sub = tid & 15;
+    for (int c = tid >> 4; c < ((nch + 15) & ~15); c += kSetupThreads / 16) {
+      const int cc = min(c, nch - 1);
+      const int j = 64 * cc + 1;  // the chunk's first column, for the rows up to 64c
       const uint64_t Pj = P[j], Aj = A[j];
-      int lo = 64 * c;
-      if (fits_at(Pj - P[lo], Aj - A[lo], M, D)) {
-        int below = -1;  // the largest row known not to fit
-        while (lo - below > 1) {
-          const int mid = (lo + below) >> 1;
-          if (fits_at(Pj - P[mid], Aj - A[mid], M, D)) lo = mid;
-          else below = mid;
+      int lo = 64 * cc, below = -1;  // the smallest row known to fit (if 64c does), the largest known not to
+      const bool some = fits_at(Pj - P[lo], Aj - A[lo], M, D);
+      while (__ballot(some && lo - below > 1) != 0ull) {
+        const int width = max((lo - below + 15) >> 4, 1);
+        const int at = min(below + (sub + 1) * width, lo);
+        const bool fits = fits_at(Pj - P[max(at, 0)], Aj - A[max(at, 0)], M, D);
+        const unsigned m = (unsigned)(__ballot(fits) >> (tid & 48)) & 0xFFFFu;
+        const int f = m ? __ffs((int)m) - 1 : 15;  // (the last probe is lo, which fits)
+        if (some && lo - below > 1) {
+          const int next = min(below + (f + 1) * width, lo);
+          below += f * width;
+          lo = next;
         }
-      } else {
-        const int hi = min(64 * c + 63, N - 1);
+      }
+      if (!some) {  // the chunk's first block fits no device by itself: the first later one that does
+        const int hi = min(64 * cc + 63, N - 1);
         for (++lo; lo <= hi; ++lo)
           if (fits_at(P[lo + 1] - P[lo], A[lo + 1] - A[lo], M, D)) break;
         if (lo > hi) lo = kNoRow;
       }
-      pr.wlo[c] = lo;
-      seg[c] = run_segments(pr, c, lo, paired);
+      if (c < nch && sub == 0) {
+        pr.wlo[c] = lo;
+        seg[c] = run_segments(pr, c, lo, paired);
+      }
     }
   };
   if (in_lds) window((const uint64_t *)sP, (const uint64_t *)sA);
@@ -500,7 +529,8 @@ __global__ __launch_bounds__(kSetupThreads) void setup_kernel(const ProblemDev *
   }
   // per chunk: items of the two segments, and their rows dealt evenly over them (33 rows in items
   // of up to 16: three items of 11, not 16 + 16 + 1); seg[c] is reused for {items0, per0, lo1, per1}
-  __shared__ int n0_of[1024], n1_of[1024];
+  static_assert(kSetupLdsN >= 1024 / 2, "a chunk per word");
+  int *const n0_of = (int *)sP, *const n1_of = (int *)sA;
   for (int c = tid; c < nch; c += kSetupThreads) {
     const RunSegments g = seg[c];
     const int items0 = (g.n0 + rows - 1) / rows, items1 = (g.n1 + rows - 1) / rows;
@@ -1065,9 +1095,9 @@ template <typename VT, int DP, bool DIRECT>
 __global__ __launch_bounds__((64 * small_waves<VT, DP>())) __attribute__((amdgpu_waves_per_eu((small_waves_per_simd<VT, DP, DIRECT>()))))
 void solve_small_kernel(
     const ProblemDev *src, ProblemDev *probs, int64_t *d_opt, int32_t *d_n_stages, int64_t *d_est,
-    int32_t *d_status) {
+    int32_t *d_status, const ProblemDev one, int use_one) {
   __shared__ __align__(8) uint32_t desc[sizeof(ProblemDev) / 4];
-  const ProblemDev pr = fetch_problem(src + blockIdx.x, probs + blockIdx.x, true, desc);
+  const ProblemDev pr = fetch_problem(src + blockIdx.x, probs + blockIdx.x, true, desc, one, use_one);
   constexpr VT INF = Lim<VT>::inf;
   constexpr int LS = DP + 1;  // row stride of a level in LDS: lanes (= columns) hit different banks
   constexpr int kSmallWaves = small_waves<VT, DP>();
@@ -1474,11 +1504,15 @@ __global__ __launch_bounds__(64) void select_kernel(const ProblemDev *__restrict
 // One workgroup per problem walks from (s*, N, D) down to level 1.  At each cell it finds the
 // lexicographically smallest (i, d') with max(V[s-1][i][d'], h(i,j,d-d')) equal to the cell's
 // value: the candidate that the ascending scan with strict "<" of Algorithm 1 would have kept.
-// A wave owns a split point i and reads the row V[s-1][i][.] with one coalesced request (lane =
-// d'-1).  Both that row and h(i,j,.) are non-increasing (the property the merge kernel rests on),
-// so in row i the only candidate is the smallest d' whose earlier-stages value is <= the cell's
-// value: one row read and one comparison of the stage's time per split point, and the reads of one
-// pass (192 rows) do not depend on each other.
+// A lane owns a split point i.  Both the row V[s-1][i][.] and h(i,j,.) are non-increasing (the property
+// the merge kernel rests on), so in row i the only candidate is the smallest d' whose earlier-stages
+// value is <= the cell's value: found with eight probes and then eight reads of the eighth it lies in,
+// checked against the stage's time.  Value and prefix sum of the chosen row travel to the next step
+// through LDS.
+// Bound by latency: two dependent round trips (the second mostly to lines of the first) and one barrier
+// per stage.  With a wave per row, twelve rows at a time and three barriers a stage took 3.2 us out of
+// memory (1024 blocks, 64 devices) and 1.4 us out of LDS.  Whole kernel, with the results' way to the host:
+// 40 -> 32 us there, 25 -> 17 us at 251 blocks with send times, 16.5 -> 10.3 us at 96 blocks out of LDS.
 // ---------------------------------------------------------------------------------------
 // Whether max(a, h) == v for the stage time h = ceil(x/r) + ceil(C/r) of Sec. III-C, given a <= v.
 // The stage's time comes from the prefix sums (the table may not have been built); x is compared
@@ -1498,140 +1532,145 @@ __device__ __forceinline__ bool stage_time_completes(uint64_t x, uint64_t C, int
   return __umul64hi(w - 1, (uint64_t)r) == 0 && x > (w - 1) * (uint64_t)r;
 }
 
+constexpr int kTracebackThreads = 1024;
+
+// What the waves of a plan recovery exchange: per step the smallest key ((i << 8) | d') found, in three
+// words of which one is cleared while another is in use (one barrier per step), and the value and prefix
+// sum of each wave's first match.
+struct TracebackLds {
+  unsigned int key[3];
+  uint64_t value[2][kTracebackThreads / 64];
+  int64_t T[2][kTracebackThreads / 64];
+};
+
 // STAGED: everything the walk reads (the levels of V below the plan's, T, C, the window bounds, the
 // fits-in-memory bytes) is first copied into the workgroup's LDS with one round of independent reads,
-// and the walk then runs out of LDS.  For a search that small the walk is otherwise a chain of one
-// memory round trip per stage out of a cold cache (about 1 us each).  lds: traceback_lds_bytes() bytes.
-template <typename VT, int DP, bool STAGED>
+// and the walk then runs out of LDS.  lds: traceback_lds_bytes() bytes (not STAGED: nch words).
+// choose: the stage count is chosen here (select_body, by the first wave, while the others copy).
+template <typename VT, bool STAGED>
 __device__ void traceback_body(const ProblemDev &pr, int plan_stride, int32_t *se, int32_t *rp,
-                               unsigned int *best_key, int forced, char *lds) {
+                               TracebackLds &sh, int forced, char *lds, const PlanResults &results, bool choose) {
   constexpr VT INF = Lim<VT>::inf;
-  constexpr int KB = 12;  // rows per wave and pass; their reads are independent
-  const int N = pr.N, D = pr.D, nch = pr.nch;
+  const int N = pr.N, D = pr.D, DP = pr.DP, nch = pr.nch;
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nt = blockDim.x;
   const int64_t lvl = (int64_t)(N + 1) * DP;
   const VT RANNC_GLOBAL *Vg = gptr((const VT *)pr.V);
-  // forced > 0: the plan of exactly `forced` stages (Algorithm 1's own answer V[S][|B|][D]), if
-  // that level holds one; forced = 0: the best level chosen by the solve; forced < 0: no plan wanted
-  int ns = (*pr.status == 0 && forced >= 0) ? (int)pr.res[1] : 0;
-  if (forced > 0 && *pr.status == 0)
-    ns = (forced <= pr.S_eff && Vg[(int64_t)(forced - 1) * lvl + (int64_t)N * DP + D - 1] != INF) ? forced : 0;
-  for (int u = ns + tid; u < plan_stride; u += blockDim.x) { se[u] = -1; rp[u] = -1; }
-  if (ns == 0) return;
+  if (tid < 3) sh.key[tid] = 0xFFFFFFFFu;
   using VP = std::conditional_t<STAGED, const VT *, const VT RANNC_GLOBAL *>;
   using TP = std::conditional_t<STAGED, const int64_t *, const int64_t RANNC_GLOBAL *>;
   using RP = std::conditional_t<STAGED, const uint8_t *, const uint8_t RANNC_GLOBAL *>;
-  using WP = std::conditional_t<STAGED, const int32_t *, const int32_t RANNC_GLOBAL *>;
   VP V;
   TP T, C = nullptr;
   RP rmin;
-  WP wlo;
+  const int32_t *wlo;
+  typedef uint32_t Quad __attribute__((ext_vector_type(4)));
+  [[maybe_unused]] VT *Vl = (VT *)lds;
+  if (choose && wave == 0) select_body(pr, results.d_opt, results.d_n_stages, results.d_est, results.d_status);
   if constexpr (STAGED) {
     const int64_t nT = (((int64_t)(N + 1) * 8 + 31) / 32) * 32;
-    char *w = lds;
-    VT *Vl = (VT *)w; w += (int64_t)pr.S_eff * lvl * (int64_t)sizeof(VT);  // room for every level
+    char *w = lds + (int64_t)pr.S_eff * lvl * (int64_t)sizeof(VT);  // room for every level
     int64_t *Tl = (int64_t *)w; w += nT;
     int64_t *Cl = (int64_t *)w; w += nT;
     int32_t *Wl = (int32_t *)w; w += (((int64_t)nch * 4 + 31) / 32) * 32;
     uint8_t *Rl = (uint8_t *)w;
-    // 16-byte copies (every array starts on a 256-byte boundary of the workspace; a level of V is
-    // a multiple of 32 bytes)
-    typedef uint32_t Quad __attribute__((ext_vector_type(4)));
-    const Quad RANNC_GLOBAL *src = (const Quad RANNC_GLOBAL *)Vg;
-    // eight reads in flight per lane (index clamped instead of tested, so that no branch separates them)
-    const int64_t nquad = (int64_t)ns * lvl * (int64_t)sizeof(VT) / 16;
-    for (int64_t e0 = tid; e0 < nquad; e0 += 8 * (int64_t)blockDim.x) {
-      Quad r[8];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) r[k] = src[min(e0 + k * (int64_t)blockDim.x, nquad - 1)];
-#pragma unroll
-      for (int k = 0; k < 8; ++k)
-        if (e0 + k * (int64_t)blockDim.x < nquad) ((Quad *)Vl)[e0 + k * (int64_t)blockDim.x] = r[k];
+    // (every array starts on a 256-byte boundary of the workspace); the first wave, if it chooses, joins for V
+    const int first = choose ? 64 : 0;
+    if (tid >= first) {
+      for (int e = tid - first; e <= N; e += nt - first) {
+        Tl[e] = pr.T[e];
+        if (pr.C) Cl[e] = pr.C[e];
+      }
+      for (int e = tid - first; e < nch; e += nt - first) Wl[e] = pr.wlo[e];
+      const Quad RANNC_GLOBAL *rsrc = (const Quad RANNC_GLOBAL *)gptr((const uint8_t *)pr.rmin);
+      for (int64_t e = tid - first; e < units_before(nch, N) * 4; e += nt - first) ((Quad *)Rl)[e] = rsrc[e];
     }
-    for (int e = tid; e <= N; e += blockDim.x) {
-      Tl[e] = pr.T[e];
-      if (pr.C) Cl[e] = pr.C[e];
-    }
-    for (int e = tid; e < nch; e += blockDim.x) Wl[e] = pr.wlo[e];
-    const Quad RANNC_GLOBAL *rsrc = (const Quad RANNC_GLOBAL *)gptr((const uint8_t *)pr.rmin);
-    for (int64_t e = tid; e < units_before(nch, N) * 4; e += blockDim.x) ((Quad *)Rl)[e] = rsrc[e];
-    __syncthreads();
     V = Vl; T = Tl; rmin = Rl; wlo = Wl;
     if (pr.C) C = Cl;
   } else {
     V = Vg;
     T = gptr((const int64_t *)pr.T);
     rmin = gptr((const uint8_t *)pr.rmin);
-    wlo = gptr((const int32_t *)pr.wlo);
+    // (the window bounds decide which rows a step reads: out of memory they would be a third round trip)
+    int32_t *Wl = (int32_t *)lds;
+    for (int e = tid; e < nch; e += nt) Wl[e] = pr.wlo[e];
+    wlo = Wl;
     if (pr.C) C = gptr((const int64_t *)pr.C);
   }
+  if (choose) __syncthreads();  // the choice is in pr.res
+  // forced > 0: the plan of exactly `forced` stages (Algorithm 1's own answer V[S][|B|][D]), if
+  // that level holds one; forced = 0: the best level chosen by the solve; forced < 0: no plan wanted
+  int ns = (*pr.status == 0 && forced >= 0) ? (int)pr.res[1] : 0;
+  if (forced > 0 && *pr.status == 0)
+    ns = (forced <= pr.S_eff && Vg[(int64_t)(forced - 1) * lvl + (int64_t)N * DP + D - 1] != INF) ? forced : 0;
+  for (int u = ns + tid; u < plan_stride; u += nt) { se[u] = -1; rp[u] = -1; }
+  if (ns == 0) return;
+  if constexpr (STAGED) {
+    // 16-byte copies (a level of V is a multiple of 32 bytes), eight reads in flight per lane (index
+    // clamped instead of tested, so that no branch separates them)
+    const Quad RANNC_GLOBAL *src = (const Quad RANNC_GLOBAL *)Vg;
+    const int64_t nquad = (int64_t)ns * lvl * (int64_t)sizeof(VT) / 16;
+    for (int64_t e0 = tid; e0 < nquad; e0 += 8 * (int64_t)nt) {
+      Quad r[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) r[k] = src[min(e0 + k * (int64_t)nt, nquad - 1)];
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        if (e0 + k * (int64_t)nt < nquad) ((Quad *)Vl)[e0 + k * (int64_t)nt] = r[k];
+    }
+  }
+  __syncthreads();  // the copies, and the key words
   int j = N, d = D;
+  VT v = V[(int64_t)(ns - 1) * lvl + (int64_t)N * DP + D - 1];
+  int64_t Tj = T[N];
+  int step = 0;
   for (int s = ns; s >= 2; --s) {
     VP Vp = V + (int64_t)(s - 2) * lvl;
     const int jj = j - 1, c = jj >> 6;
-    const int64_t Tj = T[j];
     const uint64_t Cj = C ? (uint64_t)C[j] : 0ull;  // send time of the cut after block j (0 for j = N)
-    if (tid == 0) *best_key = 0xFFFFFFFFu;
-    lds_barrier();  // the waves meet through LDS only: the reads above and the plan stores stay in flight
-    // the cell's value, the window bound and the first pass of rows are read together
-    const VT v = V[(int64_t)(s - 1) * lvl + (int64_t)j * DP + d - 1];
-    const int first = max(s - 1, min(wlo[c], j));  // earlier rows hold no stage that fits
-    unsigned mine = 0xFFFFFFFFu;
-    for (int top = j - 1; top >= s - 1; top -= nw * KB) {  // rows top, top-1, ... downwards
-      VT a[KB];
+    const int first = max(s - 1, min(wlo[c], j));   // earlier rows hold no stage that fits
+    const int lo = s - 1, hi = d - 1, width = (hi - lo + 8) >> 3;  // d' = lo..hi in eighths of this width
+    unsigned key = 0xFFFFFFFFu;
+    for (int i0 = first; i0 < j && key == 0xFFFFFFFFu; i0 += nt) {  // rows ascend: the first match is the smallest
+      const int i = min(i0 + tid, j - 1);
+      VP row = Vp + (int64_t)i * DP - 1;  // row[d']
+      VT a[8];
 #pragma unroll
-      for (int k = 0; k < KB; ++k) {
-        const int i = top - (wave + nw * k);
-        a[k] = (i >= s - 1 && lane < DP) ? Vp[(int64_t)i * DP + lane] : INF;  // lane = d'-1
-      }
-      // the row lane < KB is responsible for: its fits-in-memory byte and prefix sum are read in the
-      // same round trip as the rows (their addresses depend on nothing that is loaded; a row
-      // outside the range is clamped into it and ignored below)
-      const int i = top - (wave + nw * lane);
-      const int ic = min(max(i, s - 1), j - 1);
-      int rmn = 0;
-      int64_t Ti = 0;
-      if (lane < KB) {  // the other lanes would only fetch lines nobody needs
-        rmn = (int)rmin[unit_index(nch, ic, c) * 64 + (jj & 63)];
-        Ti = T[ic];
-      }
-      // per row: smallest d' in [s-1, d-1] with a[d'] <= v (smaller d' cannot match, and if this
-      // one does not match no larger one does: c only grows as r = d - d' shrinks); lane k then
-      // checks row k against the stage time
-      int my_d = 0;
+      for (int k = 0; k < 8; ++k) a[k] = row[min(lo + (k + 1) * width - 1, hi)];
+      const int rmn = (int)rmin[unit_index(nch, i, c) * 64 + (jj & 63)];
+      const int64_t Ti = T[i];
+      int at = lo;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) at += a[k] > v ? width : 0;  // (a prefix of the probes lies above v)
+      bool ok = a[7] <= v && i0 + tid < j;
+      int dp = at;
       VT my_a = INF;
-      // rows of this wave inside the window (they descend with k): the others cost nothing
-      const int low = max(first, s - 1);
-      const int kb = top - wave >= low ? (top - wave - low) / nw + 1 : 0;
 #pragma unroll
-      for (int k = 0; k < KB; ++k) {
-        // out of memory a test, not an exit: behind an exit the compiler moves each row's read to
-        // its use, and the reads of a pass no longer overlap; out of LDS the exit is what is cheaper
-        if constexpr (STAGED) {
-          if (k >= kb) break;
-        }
-        const bool ok = k < kb && lane + 1 >= s - 1 && lane + 1 <= d - 1 && a[k] <= v;
-        const unsigned long long m = __ballot(ok);
-        if (m != 0ull) {
-          const int q = __ffsll((long long)m) - 1;
-          const VT aq = lane_bcast(a[k], q);
-          if (lane == k) { my_d = q + 1; my_a = aq; }
-        }
+      for (int k = 0; k < 8; ++k) a[k] = row[min(at + min(k, width - 1), hi)];
+#pragma unroll
+      for (int k = 7; k >= 0; --k)
+        if (a[k] <= v) { dp = min(at + min(k, width - 1), hi); my_a = a[k]; }
+      const int r = d - dp;
+      ok = ok && r >= rmn && stage_time_completes((uint64_t)(Tj - Ti), Cj, max(r, 1), (uint64_t)my_a, (uint64_t)v);
+      const unsigned long long m = __ballot(ok);
+      const int b = step % 3, p = step & 1;
+      if (m != 0ull && lane == __ffsll((long long)m) - 1) {
+        atomicMin(&sh.key[b], ((unsigned)i << 8) | (unsigned)dp);
+        sh.value[p][wave] = (uint64_t)my_a;
+        sh.T[p][wave] = Ti;
       }
-      if (lane < KB && my_d != 0 && i >= first && v != INF) {
-        const int r = d - my_d;
-        if (r >= rmn && stage_time_completes((uint64_t)(Tj - Ti), Cj, r, (uint64_t)my_a, (uint64_t)v))
-          mine = min(mine, ((unsigned)i << 8) | (unsigned)my_d);
+      lds_barrier();
+      key = sh.key[b];
+      if (tid == 0) sh.key[(step + 2) % 3] = 0xFFFFFFFFu;  // the word of the step before: everybody has read it
+      ++step;
+      if (key != 0xFFFFFFFFu) {
+        const int from = ((int)(key >> 8) - i0) >> 6;  // the wave whose first match it was
+        v = (VT)sh.value[p][from];
+        Tj = sh.T[p][from];
       }
-      if (top - nw * KB < first) break;  // the remaining rows lie below the window
     }
-    if (mine != 0xFFFFFFFFu) atomicMin(best_key, mine);
-    lds_barrier();
-    const unsigned key = *best_key;
-    lds_barrier();
     if (key == 0xFFFFFFFFu) {  // tables inconsistent: report no plan rather than walk on
-      for (int u = tid; u < plan_stride; u += blockDim.x) { se[u] = -1; rp[u] = -1; }
+      for (int u = tid; u < plan_stride; u += nt) { se[u] = -1; rp[u] = -1; }
       return;
     }
     const int i_sel = (int)(key >> 8), d_sel = (int)(key & 255u);
@@ -1642,7 +1681,7 @@ __device__ void traceback_body(const ProblemDev &pr, int plan_stride, int32_t *s
   if (tid == 0) { se[0] = j; rp[0] = d; }
 }
 
-constexpr int kTracebackThreads = 1024;
+
 
 // Outer driver (Algorithm 2 "form_stage" of Sec. III-C), the loops over the solved batch: node
 // counts n = 1, 2, 4, ... in turn, for each the stage counts S ascending over
@@ -1738,16 +1777,16 @@ __device__ __forceinline__ FormStageChoice form_stage_choose(const ProblemDev *_
 // written here), and the flag word that tells the host.
 __device__ __forceinline__ void plan_to_record(int plan_stride, const int32_t *se, const int32_t *rp, const FormStageIn &f) {
   __syncthreads();  // the walk's stores, by this workgroup's first thread, are visible to all of it
+  if (threadIdx.x >= 64) return;  // (the wave that wrote the record: see results_to_host)
   int32_t *plan = (int32_t *)(f.rec + 6);
   if (se)
-    for (int u = threadIdx.x; u < plan_stride; u += blockDim.x) {
+    for (int u = threadIdx.x; u < plan_stride; u += 64) {
       plan[u] = se[u];
       plan[plan_stride + u] = rp[u];
     }
   if (!f.flag) return;
-  __threadfence_system();
-  __syncthreads();
-  if (threadIdx.x == 0) __hip_atomic_store(f.flag, f.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
+  if (threadIdx.x == 0) __hip_atomic_store(f.flag, f.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // The whole workgroup: the first wave makes the choice; false (and the record is complete) if there is none.
@@ -1764,55 +1803,50 @@ __device__ __forceinline__ bool form_stage_picked(const ProblemDev *__restrict__
 }
 
 // The results of one search, copied to the host's mirror of the result buffer; behind them the
-// search's flag word tells the host, which polls it, that they are there.
-__device__ __forceinline__ void results_to_host(const ProblemDev &pr, int Q, int plan_stride, const PlanResults &r) {
+// search's flag word tells the host, which polls it, that they are there.  One wave writes all of it:
+// the release of the flag word then waits for its own stores (with every wave of the workgroup fencing
+// the system this took 4.8 us instead of 1.8).
+__device__ __forceinline__ void results_to_host(const ProblemDev &pr, int plan_stride, const PlanResults &r) {
   __syncthreads();  // this workgroup's stores to the device's buffer are visible to all of it
-  const int q = pr.q, tid = threadIdx.x;
-  if (tid == 0) r.h_opt[q] = r.d_opt[q];
-  if (tid == 1) r.h_est[q] = r.d_est[q];
-  if (tid == 2) r.h_n_stages[q] = r.d_n_stages[q];
-  if (tid == 3) r.h_status[q] = r.d_status[q];
-  for (int u = tid; u < plan_stride; u += blockDim.x) {
+  const int q = pr.q, lane = threadIdx.x;
+  if (lane >= 64) return;
+  if (lane == 0) r.h_opt[q] = r.d_opt[q];
+  if (lane == 1) r.h_est[q] = r.d_est[q];
+  if (lane == 2) r.h_n_stages[q] = r.d_n_stages[q];
+  if (lane == 3) r.h_status[q] = r.d_status[q];
+  for (int u = lane; u < plan_stride; u += 64) {
     r.h_stage_end[(int64_t)q * plan_stride + u] = r.d_stage_end[(int64_t)q * plan_stride + u];
     r.h_replicas[(int64_t)q * plan_stride + u] = r.d_replicas[(int64_t)q * plan_stride + u];
   }
-  __threadfence_system();
-  __syncthreads();
-  if (tid == 0) __hip_atomic_store(&r.h_flag[q], r.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
-// choose: the choice of the stage count (select_kernel) is made here, by the first wave, instead of in
-// a launch of its own.
-__device__ __forceinline__ void traceback_choose(const ProblemDev &pr, const PlanResults &r) {
-  if (threadIdx.x < 64) select_body(pr, r.d_opt, r.d_n_stages, r.d_est, r.d_status);
-  __syncthreads();
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");  // (of the whole wave, for the system)
+  if (lane == 0) __hip_atomic_store(&r.h_flag[q], r.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 __global__ __launch_bounds__(kTracebackThreads) void traceback_kernel(
     const ProblemDev *__restrict__ probs, int plan_stride, int32_t *d_stage_end, int32_t *d_replicas,
     const int32_t *__restrict__ d_levels, const FormStageIn fs, const PlanResults results, int choose) {
-  __shared__ unsigned int best_key;
+  __shared__ TracebackLds sh;
   __shared__ FormStageChoice pick;
+  __shared__ __align__(16) char windows[4096];  // nch <= 1024 words
   if (fs.rec && !form_stage_picked(probs, fs, plan_stride, pick)) return;
   const ProblemDev pr = probs[fs.rec ? pick.at : (int)blockIdx.x];  // by value: no reloads after the plan stores
-  if (choose) traceback_choose(pr, results);
   const int forced = fs.rec ? pick.S : d_levels ? d_levels[pr.q] : 0;
   int32_t *se = d_stage_end + (int64_t)pr.q * plan_stride;
   int32_t *rp = d_replicas + (int64_t)pr.q * plan_stride;
-#define GO(T)                                                                                    \
-  switch (pr.DP) {                                                                               \
-    case 8: traceback_body<T, 8, false>(pr, plan_stride, se, rp, &best_key, forced, nullptr); break;   \
-    case 16: traceback_body<T, 16, false>(pr, plan_stride, se, rp, &best_key, forced, nullptr); break; \
-    case 32: traceback_body<T, 32, false>(pr, plan_stride, se, rp, &best_key, forced, nullptr); break; \
-    default: traceback_body<T, 64, false>(pr, plan_stride, se, rp, &best_key, forced, nullptr); break; \
-  }
   if (pr.VF) {  // split objective: first-match over all candidates
-    if (pr.bits == 32) traceback_split_body<uint32_t>(pr, plan_stride, se, rp, &best_key, forced);
-    else traceback_split_body<uint64_t>(pr, plan_stride, se, rp, &best_key, forced);
-  } else if (pr.bits == 32) { GO(uint32_t) } else { GO(uint64_t) }
-#undef GO
+    if (choose) {
+      if (threadIdx.x < 64) select_body(pr, results.d_opt, results.d_n_stages, results.d_est, results.d_status);
+      __syncthreads();
+    }
+    if (pr.bits == 32) traceback_split_body<uint32_t>(pr, plan_stride, se, rp, &sh.key[0], forced);
+    else traceback_split_body<uint64_t>(pr, plan_stride, se, rp, &sh.key[0], forced);
+  } else if (pr.bits == 32) {
+    traceback_body<uint32_t, false>(pr, plan_stride, se, rp, sh, forced, windows, results, choose != 0);
+  } else {
+    traceback_body<uint64_t, false>(pr, plan_stride, se, rp, sh, forced, windows, results, choose != 0);
+  }
   if (fs.rec) plan_to_record(plan_stride, se, rp, fs);
-  if (results.h_flag) results_to_host(pr, gridDim.x, plan_stride, results);
+  if (results.h_flag) results_to_host(pr, plan_stride, results);
 }
 
 // Plan recovery out of LDS, for launches of few, small min-max searches (the host checks that every
@@ -1820,26 +1854,18 @@ __global__ __launch_bounds__(kTracebackThreads) void traceback_kernel(
 __global__ __launch_bounds__(kTracebackThreads) void traceback_lds_kernel(
     const ProblemDev *__restrict__ probs, int plan_stride, int32_t *d_stage_end, int32_t *d_replicas,
     const int32_t *__restrict__ d_levels, const FormStageIn fs, const PlanResults results, int choose) {
-  __shared__ unsigned int best_key;
+  __shared__ TracebackLds sh;
   __shared__ FormStageChoice pick;
   extern __shared__ __align__(16) char staged[];
   if (fs.rec && !form_stage_picked(probs, fs, plan_stride, pick)) return;
   const ProblemDev pr = probs[fs.rec ? pick.at : (int)blockIdx.x];
-  if (choose) traceback_choose(pr, results);
   const int forced = fs.rec ? pick.S : d_levels ? d_levels[pr.q] : 0;
   int32_t *se = d_stage_end + (int64_t)pr.q * plan_stride;
   int32_t *rp = d_replicas + (int64_t)pr.q * plan_stride;
-#define GO(T)                                                                                   \
-  switch (pr.DP) {                                                                              \
-    case 8: traceback_body<T, 8, true>(pr, plan_stride, se, rp, &best_key, forced, staged); break;    \
-    case 16: traceback_body<T, 16, true>(pr, plan_stride, se, rp, &best_key, forced, staged); break;  \
-    case 32: traceback_body<T, 32, true>(pr, plan_stride, se, rp, &best_key, forced, staged); break;  \
-    default: traceback_body<T, 64, true>(pr, plan_stride, se, rp, &best_key, forced, staged); break;  \
-  }
-  if (pr.bits == 32) { GO(uint32_t) } else { GO(uint64_t) }
-#undef GO
+  if (pr.bits == 32) traceback_body<uint32_t, true>(pr, plan_stride, se, rp, sh, forced, staged, results, choose != 0);
+  else traceback_body<uint64_t, true>(pr, plan_stride, se, rp, sh, forced, staged, results, choose != 0);
   if (fs.rec) plan_to_record(plan_stride, se, rp, fs);
-  if (results.h_flag) results_to_host(pr, gridDim.x, plan_stride, results);
+  if (results.h_flag) results_to_host(pr, plan_stride, results);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1921,12 +1947,12 @@ __global__ __launch_bounds__(256) void arg_init_kernel(const ProblemDev *__restr
 // Launchers
 // ---------------------------------------------------------------------------------------
 hipError_t launch_setup(const ProblemDev *src, ProblemDev *probs, int Q, int rows_per_item, int max_items, int slots,
-                        bool paired, int max_rows, hipStream_t st) {
+                        bool paired, int max_rows, const ProblemDev *host_one, hipStream_t st) {
   const int fill = Q >= 256 ? 4 : Q >= 16 ? 16 : 128;  // workgroups that fill a search's V
   for (int q0 = 0; q0 < Q; q0 += 65535) {
     const int nq = min(65535, Q - q0);
     hipLaunchKernelGGL(setup_kernel, dim3(1 + fill, nq), dim3(kSetupThreads), 0, st, src + q0, probs + q0, rows_per_item,
-                       max_items, Q, slots, paired ? 1 : 0, max_rows);
+                       max_items, Q, slots, paired ? 1 : 0, max_rows, host_one ? *host_one : ProblemDev{}, host_one ? 1 : 0);
   }
   return hipGetLastError();
 }
@@ -2077,12 +2103,14 @@ bool small_can_recompute(int bits, int DP, int64_t max_total_time) {
 }
 
 hipError_t launch_solve_small(const ProblemDev *src, ProblemDev *p, int Q, int bits, int DP, bool direct, int64_t *d_opt,
-                              int32_t *d_n_stages, int64_t *d_est, int32_t *d_status, hipStream_t st) {
+                              int32_t *d_n_stages, int64_t *d_est, int32_t *d_status, const ProblemDev *host_one,
+                              hipStream_t st) {
+  const ProblemDev one = host_one ? *host_one : ProblemDev{};
   if (direct && DP > 32) return hipErrorInvalidValue;
 #define GO(B, T, W, X)                                                                                 \
   if (bits == B && DP == W && direct == X)                                                             \
     hipLaunchKernelGGL((solve_small_kernel<T, W, X>), dim3(Q), dim3(64 * small_waves<T, W>()), 0, st, src, p, d_opt, \
-                       d_n_stages, d_est, d_status);
+                       d_n_stages, d_est, d_status, one, host_one ? 1 : 0);
   GO(32, uint32_t, 8, false) GO(32, uint32_t, 16, false) GO(32, uint32_t, 32, false) GO(32, uint32_t, 64, false)
   GO(64, uint64_t, 8, false) GO(64, uint64_t, 16, false) GO(64, uint64_t, 32, false) GO(64, uint64_t, 64, false)
   GO(32, uint32_t, 8, true) GO(32, uint32_t, 16, true) GO(32, uint32_t, 32, true)
