@@ -350,7 +350,19 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
   }
   // (a handle told to run every small search as one launch keeps the classes apart: the form of that
   // kernel depends on the class)
-  const int all = h->fused_small == 2 ? 0 : group_dp(b);
+  int all = h->fused_small == 2 ? 0 : group_dp(b);
+  if (all) {
+    // a workspace sized for another batch can hold these searches only at their own classes' widths
+    size_t need = header_bytes(h->lim.max_problems);
+    for (int q = 0; q < Q && all; ++q) {
+      Sizes sz;
+      const int S_eff = std::min(b->max_stages[q], std::min(b->n_blocks[q], b->n_devices[q]));
+      if (!problem_sizes(b->n_blocks[q], b->n_devices[q], all, S_eff, h->bits, split, packed_of(&h->lim), &sz) ||
+          need + sz.total() > h->ws_bytes)
+        all = 0;
+      else need += sz.total();
+    }
+  }
   auto dp_of = [&](int q) { return all ? all : rannc::dp_class(b->n_devices[q]); };
   int cls_start[5] = {0, 0, 0, 0, 0};
   for (int q = 0; q < Q; ++q)

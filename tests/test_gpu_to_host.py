@@ -59,3 +59,21 @@ def test_rejections():
         assert call(d=None) == B.INVALID_ARG and call(h=None) == B.INVALID_ARG
         assert call(d=s._out_dev.data_ptr() + 4) == B.INVALID_ARG
         assert B.rannc_dp_solve_to_host(None, s.hb, s.stream(), 4, s._out_dev, s._out_host, n) == B.INVALID_ARG
+
+
+def test_few_searches_in_a_workspace_sized_for_many():
+    """A workspace sized for 65 searches at their own device-count classes holds 61 of them although one
+    group of them, padded to the widest class, would not fit: the classes then run apart."""
+    narrow = [synth.random_small(700 + q, 100, 8, 8, tight=3.0) for q in range(64)]
+    probs = narrow + [synth.random_small(790, 20, 64, 8, tight=3.0)]
+    few = probs[4:]
+    with B.Session(synth.concat_batch(probs)) as big, B.Session(synth.concat_batch(few)) as own:
+        assert own.ws_bytes > big.ws_bytes      # the padded layout
+        want = own.run()
+        n = own._out_host.numel()
+        rc = B.rannc_dp_solve_to_host(big.h, own.hb, big.stream(), own.plan_stride, own._out_dev, own._out_host, n)
+        assert rc == B.OK
+        got = dict(zip(("opt", "est_iter_ns", "n_stages", "status", "stage_end", "replicas"), own._h_views))
+        for key, v in got.items():
+            assert np.array_equal(v, want[key]), key
+        assert_results_match(few, want)
