@@ -850,6 +850,8 @@ int rannc_dp_solve_to_host(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_s
     r.h_flag = (uint64_t *)(m + at.total);
     r.seq = ++h->seq;
     flags = (uint64_t *)(h->res_pin + at.total);
+    // (a call of another layout may have left a result here that equals seq, which starts at 1)
+    std::memset(flags, 0, 8 * (size_t)Q);
   }
   bool chosen = false;
   rc = solve_impl(h, b, hip_stream, r.d_opt, r.d_n_stages, r.d_est, r.d_status, &chosen);
@@ -1092,6 +1094,7 @@ int rannc_dp_form_stage(rannc_dp_t *h, const rannc_dp_form_stage_in_t *in, void 
   if (pin_dev) {
     f.flag = (uint64_t *)(pin_dev + need);
     f.seq = ++h->seq;
+    std::memset(pin + need, 0, 8);  // an earlier call's inputs may have stood here
   }
   bool chosen = false;
   h->call_total_bound = max_total < lim ? (int64_t)max_total : 0;

@@ -77,3 +77,20 @@ def test_few_searches_in_a_workspace_sized_for_many():
         for key, v in got.items():
             assert np.array_equal(v, want[key]), key
         assert_results_match(few, want)
+
+
+def test_results_of_another_layout_are_no_completion():
+    """The word that says a call of one search is done lies where a call of seven searches left its last
+    optimum; an optimum equal to the call's number must not end the wait."""
+    seven = [synth.random_small(800 + q, 1, 1, 1) for q in range(7)]
+    one = [synth.random_small(810, 1, 1, 1)]
+    for p in seven + one:
+        p["mem_capacity"] = 1 << 50
+    seven[6]["time_ns"] = np.array([2], np.int64)    # its optimum: the number of the second call
+    one[0]["time_ns"] = np.array([77], np.int64)
+    with B.Session(synth.concat_batch(seven)) as s, B.Session(synth.concat_batch(one)) as o:
+        assert s.run()["opt"][6] == 2
+        rc = B.rannc_dp_solve_to_host(s.h, o.hb, s.stream(), 1, o._out_dev, o._out_host, o._out_host.numel())
+        assert rc == B.OK
+        assert_results_match(one, dict(zip(("opt", "est_iter_ns", "n_stages", "status", "stage_end", "replicas"),
+                                           o._h_views)))
