@@ -1513,6 +1513,9 @@ __global__ __launch_bounds__(64) void select_kernel(const ProblemDev *__restrict
 // per stage.  With a wave per row, twelve rows at a time and three barriers a stage took 3.2 us out of
 // memory (1024 blocks, 64 devices) and 1.4 us out of LDS.  Whole kernel, with the results' way to the host:
 // 40 -> 32 us there, 25 -> 17 us at 251 blocks with send times, 16.5 -> 10.3 us at 96 blocks out of LDS.
+// Waves without a row of the window skip the evaluation: sixteen waves share four SIMDs, and the idle ones'
+// instructions took longer than the step's own latency (with Algorithm 2's loops over 24 searches of 32
+// blocks 30.0 -> 24.1 us; solve and recovery apart, 1024 blocks: 30.6 -> 26.6 us).
 // ---------------------------------------------------------------------------------------
 // Whether max(a, h) == v for the stage time h = ceil(x/r) + ceil(C/r) of Sec. III-C, given a <= v.
 // The stage's time comes from the prefix sums (the table may not have been built); x is compared
@@ -1632,32 +1635,34 @@ __device__ void traceback_body(const ProblemDev &pr, int plan_stride, int32_t *s
     const int lo = s - 1, hi = d - 1, width = (hi - lo + 8) >> 3;  // d' = lo..hi in eighths of this width
     unsigned key = 0xFFFFFFFFu;
     for (int i0 = first; i0 < j && key == 0xFFFFFFFFu; i0 += nt) {  // rows ascend: the first match is the smallest
-      const int i = min(i0 + tid, j - 1);
-      VP row = Vp + (int64_t)i * DP - 1;  // row[d']
-      VT a[8];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) a[k] = row[min(lo + (k + 1) * width - 1, hi)];
-      const int rmn = (int)rmin[unit_index(nch, i, c) * 64 + (jj & 63)];
-      const int64_t Ti = T[i];
-      int at = lo;
-#pragma unroll
-      for (int k = 0; k < 8; ++k) at += a[k] > v ? width : 0;  // (a prefix of the probes lies above v)
-      bool ok = a[7] <= v && i0 + tid < j;
-      int dp = at;
-      VT my_a = INF;
-#pragma unroll
-      for (int k = 0; k < 8; ++k) a[k] = row[min(at + min(k, width - 1), hi)];
-#pragma unroll
-      for (int k = 7; k >= 0; --k)
-        if (a[k] <= v) { dp = min(at + min(k, width - 1), hi); my_a = a[k]; }
-      const int r = d - dp;
-      ok = ok && r >= rmn && stage_time_completes((uint64_t)(Tj - Ti), Cj, max(r, 1), (uint64_t)my_a, (uint64_t)v);
-      const unsigned long long m = __ballot(ok);
       const int b = step % 3, p = step & 1;
-      if (m != 0ull && lane == __ffsll((long long)m) - 1) {
-        atomicMin(&sh.key[b], ((unsigned)i << 8) | (unsigned)dp);
-        sh.value[p][wave] = (uint64_t)my_a;
-        sh.T[p][wave] = Ti;
+      if (i0 + 64 * wave < j) {  // (the window rarely fills the workgroup; the other waves would only take issue slots)
+        const int i = min(i0 + tid, j - 1);
+        VP row = Vp + (int64_t)i * DP - 1;  // row[d']
+        VT a[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) a[k] = row[min(lo + (k + 1) * width - 1, hi)];
+        const int rmn = (int)rmin[unit_index(nch, i, c) * 64 + (jj & 63)];
+        const int64_t Ti = T[i];
+        int at = lo;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) at += a[k] > v ? width : 0;  // (a prefix of the probes lies above v)
+        bool ok = a[7] <= v && i0 + tid < j;
+        int dp = at;
+        VT my_a = INF;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) a[k] = row[min(at + min(k, width - 1), hi)];
+#pragma unroll
+        for (int k = 7; k >= 0; --k)
+          if (a[k] <= v) { dp = min(at + min(k, width - 1), hi); my_a = a[k]; }
+        const int r = d - dp;
+        ok = ok && r >= rmn && stage_time_completes((uint64_t)(Tj - Ti), Cj, max(r, 1), (uint64_t)my_a, (uint64_t)v);
+        const unsigned long long m = __ballot(ok);
+        if (m != 0ull && lane == __ffsll((long long)m) - 1) {
+          atomicMin(&sh.key[b], ((unsigned)i << 8) | (unsigned)dp);
+          sh.value[p][wave] = (uint64_t)my_a;
+          sh.T[p][wave] = Ti;
+        }
       }
       lds_barrier();
       key = sh.key[b];
