@@ -4,6 +4,7 @@
 // recurrence; that is all in the kernel files (rannc_dp_kernels.hip, rannc_dp_split.hip, rannc_dp_compact.hip).
 #include "../../include/rannc_dp.h"
 #include "rannc_dp_internal.h"
+#include "rannc_dp_worklist.h"
 
 #include <algorithm>
 #include <atomic>

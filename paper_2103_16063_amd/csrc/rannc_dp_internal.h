@@ -55,6 +55,7 @@ constexpr int kMergeWaves = 4;
 constexpr int kMergeMinRows = 4;
 // largest work item (rows): the recomputing form holds the item's rows in LDS
 __host__ __device__ constexpr int merge_max_rows(int bits) { return bits == 64 ? 32 : 64; }
+// (and, with two rows to an entry of a diagonal block's segment, cuts those shorter: rannc_dp_worklist.h)
 constexpr int kMergeRows8From = 6144;
 constexpr int kMergeRows16From = 16384;
 // From this many rows (unpruned) in a launch on, a search without a communication term has its
@@ -141,12 +142,7 @@ hipError_t launch_build(const ProblemDev *probs, const LaunchShape &sh, int bits
 // host memory (passed by value instead), or null
 hipError_t launch_setup(const ProblemDev *src, ProblemDev *probs, int Q, int rows_per_item, int max_items, int slots, bool paired,
                         int max_rows, const ProblemDev *host_one, hipStream_t st);
-int merge_workgroups_per_cu(int bits, int DP, bool recompute);
 int merge_rows_per_item(int rows_per_wave);
-// rows_for_list: what launch_setup is to be given as rows_per_item (the size the host fixed, or -1)
-int merge_grid_items(const LaunchShape &sh, int rows_per_item, int slots, bool paired, int max_rows, int *rows_for_list);
-// rows of the searches of a launch if nothing is pruned (every chunk c holds rows 0 .. 64c+63)
-int64_t merge_launch_rows(const LaunchShape &sh);
 // recompute: the level kernel computes the stage times from the prefix sums instead of reading
 // their table (where can_recompute_times says so)
 // items: merge_grid_items of the launch, the value launch_setup was given

@@ -8,6 +8,7 @@
 // level kernels: every access stays inside the problem's own regions, and its values are never
 // reported (the final selection, the plan recovery and the exports check the status word).
 #include "rannc_dp_device.h"
+#include "rannc_dp_worklist.h"
 
 #include <type_traits>
 
@@ -263,23 +264,6 @@ __device__ __forceinline__ ProblemDev fetch_problem(const ProblemDev *src, Probl
 }
 constexpr int kSetupLdsN = 1024;  // up to this many blocks the windows are searched in LDS
 
-struct RunSegments { int lo0, n0, lo1, n1; };
-__device__ __forceinline__ RunSegments run_segments(const ProblemDev &pr, int c, int lo, int paired) {
-  RunSegments g;
-  const int hi = min(64 * c + 63, pr.N - 1);
-  g.lo0 = lo; g.n0 = lo <= hi ? hi - lo + 1 : 0; g.lo1 = 0; g.n1 = 0;
-  if (paired && lo <= hi && hi >= 64 * c) {
-    const int w = max(lo, 64 * c) - 64 * c, hmax = hi - 64 * c;  // window start and last row inside the block
-    g.n0 = max(64 * c - lo, 0);
-    // pairs p_lo .. p_top: every pair that holds a row of the window (a few more when the window
-    // starts inside the block; their rows have no stage that fits and cost a skipped pass)
-    const int p_lo = w == 0 ? 0 : 1, p_top = w <= 32 ? min(32, hmax) : min(31, 64 - w);
-    g.lo1 = 64 * c + p_lo;
-    g.n1 = max(p_top - p_lo + 1, 0);
-  }
-  return g;
-}
-
 // whether bytes P (not divided) + ceil(A / D) fit M
 __device__ __forceinline__ bool fits_at(uint64_t P, uint64_t A, uint64_t M, int D) {
   if (P > M) return false;
@@ -480,7 +464,7 @@ __global__ __launch_bounds__(kSetupThreads) void setup_kernel(const ProblemDev *
       }
       if (c < nch && sub == 0) {
         pr.wlo[c] = lo;
-        seg[c] = run_segments(pr, c, lo, paired);
+        seg[c] = run_segments(N, c, lo, paired != 0);
       }
     }
   };
@@ -499,7 +483,7 @@ __global__ __launch_bounds__(kSetupThreads) void setup_kernel(const ProblemDev *
       int cnt = 0;
       for (int c = tid / NC; c < nch; c += kSetupThreads / NC) {
         const RunSegments g = seg[c];
-        cnt += (g.n0 + r - 1) / r + (g.n1 + r - 1) / r;
+        cnt += items_of_rows(g, r) + items_of_pairs(g, r, max_rows);
       }
       if (cnt) atomicAdd(&count[k], cnt);
     }
@@ -533,7 +517,7 @@ __global__ __launch_bounds__(kSetupThreads) void setup_kernel(const ProblemDev *
   int *const n0_of = (int *)sP, *const n1_of = (int *)sA;
   for (int c = tid; c < nch; c += kSetupThreads) {
     const RunSegments g = seg[c];
-    const int items0 = (g.n0 + rows - 1) / rows, items1 = (g.n1 + rows - 1) / rows;
+    const int items0 = items_of_rows(g, rows), items1 = items_of_pairs(g, rows, max_rows);
     start[c + 1] = items0 + items1;  // items of chunk c
     n0_of[c] = g.n0;
     n1_of[c] = g.n1;
@@ -796,8 +780,12 @@ __device__ __forceinline__ void row_merge_direct(VT (&x)[H], AP arow, VT tij, in
 // memory binds, 506 -> 474 us where it does not; 512 searches of 128 blocks at 64 devices 92 -> 82 us).
 // H: width of the merge (multiple of eight, at least rl); LS: row stride of the tile, whose entry t is
 // output t of the merge.  Returns whether any row of this wave had work.
-// Most rows of V[s-1] an item reads: those of the largest item, or twice the pairs of half a diagonal block.
-template <typename VT> constexpr int item_rows() { return merge_max_rows(8 * sizeof(VT)) + 2; }
+// Most rows of V[s-1] an item reads: those of the largest item, or both rows of a diagonal item's pairs.
+template <typename VT> constexpr int item_rows() {
+  constexpr int bits = 8 * sizeof(VT);
+  static_assert(2 * merge_max_pairs(merge_max_rows(bits)) <= merge_item_rows(bits), "the rows of an item fit");
+  return merge_item_rows(bits);
+}
 template <typename VT, int HMAX> struct ItemRows {
   static constexpr int E = 16 / (int)sizeof(VT);  // values per 16 bytes
   static constexpr int AS = HMAX + E;             // row stride of the copied rows: 16-byte aligned, rows on different banks
@@ -1965,60 +1953,6 @@ hipError_t launch_setup(const ProblemDev *src, ProblemDev *probs, int Q, int row
 int merge_rows_per_item(int rows_per_wave) {
   if (rows_per_wave <= 0) return -1;  // chosen on the device
   return kMergeWaves * (rows_per_wave <= 1 ? 1 : rows_per_wave <= 2 ? 2 : rows_per_wave <= 4 ? 4 : rows_per_wave <= 8 ? 8 : rows_per_wave <= 12 ? 12 : 16);
-}
-
-// Grid of the sorted-merge level kernel = items of the largest search of the launch if nothing is
-// pruned.  rows_per_item > 0: in items of that size.  Otherwise in the size that suits the launch
-// as a whole: 4-row items (most workgroups) while that leaves the device short of work, larger ones
-// (fewer folds and atomics per row) when the launch is full anyway.  The work list then takes the
-// smallest item size that fits this grid.
-int64_t merge_launch_rows(const LaunchShape &sh) {
-  int64_t all_rows = 0;
-  for (int c = 0; c < sh.max_nch; ++c) all_rows += min(64 * c + 64, sh.max_N);
-  return all_rows * sh.nprob;
-}
-
-int merge_grid_items(const LaunchShape &sh, int rows_per_item, int slots, bool paired, int max_rows, int *rows_for_list) {
-  // items of the largest search of the launch if nothing is pruned, in items of `rows` rows: the
-  // segments of run_segments for windows that start at row 0 (a pruned window has no more rows in
-  // either segment, so no more items at any size)
-  auto items_at = [&](int rows) {
-    int64_t items = 0;
-    for (int c = 0; c < sh.max_nch; ++c) {
-      const int hi = min(64 * c + 63, sh.max_N - 1);
-      int n0 = hi + 1, n1 = 0;
-      if (paired && hi >= 64 * c) { n0 = 64 * c; n1 = min(32, hi - 64 * c) + 1; }
-      items += (n0 + rows - 1) / rows + (n1 + rows - 1) / rows;
-    }
-    return std::max<int64_t>(1, items);
-  };
-  int rows = std::min(rows_per_item, max_rows);
-  *rows_for_list = rows;
-  if (rows <= 0) {
-    const int64_t launch_rows = merge_launch_rows(sh);
-    rows = launch_rows >= kMergeRows16From ? 16 : launch_rows >= kMergeRows8From ? 8 : kMergeMinRows;
-    // A launch of the recomputing form over several searches with many rounds of workgroups: the
-    // largest items that still fill the device one and a quarter times if nothing is pruned, the same
-    // size for every search of the launch.  Copying the rows in, clearing the tile and the atomics are
-    // paid per item (config 5: 16 -> 64 rows, 157 -> 115 us per level when an item held its minimum in
-    // registers; six workgroups per compute unit at 32 devices since: one and a quarter rounds 2.13 ms
-    // for all levels, two 2.13, three 2.25; over ragged batches of 100 to 1 500 searches within 5 %).
-    if (paired && sh.nprob > 1 && items_at(rows) * sh.nprob > slots)
-      for (int r = max_rows; r > rows; r -= 4)
-        if (4 * items_at(r) * sh.nprob >= 5ll * slots) { rows = r; *rows_for_list = r; break; }
-  }
-  return (int)items_at(rows);
-}
-
-// Workgroups of the sorted-merge level kernel that one compute unit holds at a time (by the
-// registers of its four waves, one per SIMD; see the kernel's resource usage).
-int merge_workgroups_per_cu(int bits, int DP, bool recompute) {
-  if (bits == 32) {
-    if (recompute) return DP == 64 ? 4 : DP == 32 ? 6 : 8;
-    return DP == 64 ? 3 : DP == 32 ? 4 : DP == 16 ? 6 : 8;
-  }
-  if (recompute) return DP == 64 ? 3 : DP == 32 ? 5 : 8;
-  return DP == 64 ? 2 : DP == 32 ? 3 : DP == 16 ? 4 : 8;
 }
 
 constexpr int kBuildRowsFitOnly = 8;  // rows per wave when only the fits-in-memory part is built ...

@@ -1,0 +1,98 @@
+// Rules that cut the rows of a launch of the sorted-merge level kernel into work items: used by the
+// kernel that writes the list (setup_kernel), by the host that sizes the grid, and by their model on the
+// CPU.
+#pragma once
+
+#include "rannc_dp_internal.h"
+
+#include <algorithm>
+
+namespace rannc {
+
+// The recomputing form holds the rows of an item in an LDS array of this many rows.  An entry of a
+// diagonal block's segment (RunSegments) is a PAIR of rows, both of them held, so that an item has at
+// most half as many entries there: 33 of 32-bit values (a full segment), 17 of 64-bit ones (a larger
+// array would cost the third workgroup of a compute unit at 64 devices).
+__host__ __device__ constexpr int merge_item_rows(int bits) { return merge_max_rows(bits) + 2; }
+__host__ __device__ constexpr int merge_max_pairs(int max_rows) { return max_rows / 2 + 1; }
+
+// The rows of one chunk's window as the work list cuts them (see setup_kernel): n0 rows from lo0 on, then,
+// for the recomputing form, n1 entries from lo1 on that stand for the rows of the diagonal block.
+struct RunSegments { int lo0, n0, lo1, n1; };
+__host__ __device__ inline RunSegments run_segments(int N, int c, int lo, bool paired) {
+  RunSegments g;
+  const int last = 64 * c + 63, hi = last < N - 1 ? last : N - 1;
+  g.lo0 = lo; g.n0 = lo <= hi ? hi - lo + 1 : 0; g.lo1 = 0; g.n1 = 0;
+  if (paired && lo <= hi && hi >= 64 * c) {
+    const int w = lo > 64 * c ? lo - 64 * c : 0, hmax = hi - 64 * c;  // window start and last row inside the block
+    g.n0 = lo < 64 * c ? 64 * c - lo : 0;
+    // pairs p_lo .. p_top: every pair that holds a row of the window (a few more when the window
+    // starts inside the block; their rows have no stage that fits and cost a skipped pass)
+    const int p_lo = w == 0 ? 0 : 1, p_top = w <= 32 ? (hmax < 32 ? hmax : 32) : (64 - w < 31 ? 64 - w : 31);
+    g.lo1 = 64 * c + p_lo;
+    g.n1 = p_top >= p_lo ? p_top - p_lo + 1 : 0;
+  }
+  return g;
+}
+// items of the two segments (items of at most `rows` rows, in launches whose items have at most max_rows)
+__host__ __device__ inline int items_of_rows(const RunSegments &g, int rows) { return (g.n0 + rows - 1) / rows; }
+__host__ __device__ inline int items_of_pairs(const RunSegments &g, int rows, int max_rows) {
+  const int most = rows < merge_max_pairs(max_rows) ? rows : merge_max_pairs(max_rows);
+  return (g.n1 + most - 1) / most;
+}
+
+// rows of the searches of a launch if nothing is pruned (every chunk c holds rows 0 .. 64c+63)
+inline int64_t merge_launch_rows(const LaunchShape &sh) {
+  int64_t all_rows = 0;
+  for (int c = 0; c < sh.max_nch; ++c) all_rows += std::min(64 * c + 64, sh.max_N);
+  return all_rows * sh.nprob;
+}
+
+// Grid of the sorted-merge level kernel = items of the largest search of the launch if nothing is
+// pruned.  rows_per_item > 0: in items of that size.  Otherwise in the size that suits the launch
+// as a whole: 4-row items (most workgroups) while that leaves the device short of work, larger ones
+// (fewer folds and atomics per row) when the launch is full anyway.  The work list then takes the
+// smallest item size that fits this grid.
+// rows_for_list: what launch_setup is to be given as rows_per_item (the size the host fixed, or -1)
+inline int merge_grid_items(const LaunchShape &sh, int rows_per_item, int slots, bool paired, int max_rows, int *rows_for_list) {
+  // items of the largest search of the launch if nothing is pruned, in items of `rows` rows: the
+  // segments of run_segments for windows that start at row 0 (a pruned window has no more rows in
+  // either segment, so no more items at any size)
+  auto items_at = [&](int rows) {
+    int64_t items = 0;
+    for (int c = 0; c < sh.max_nch; ++c) {
+      const RunSegments g = run_segments(sh.max_N, c, 0, paired);
+      items += items_of_rows(g, rows) + items_of_pairs(g, rows, max_rows);
+    }
+    return std::max<int64_t>(1, items);
+  };
+  int rows = std::min(rows_per_item, max_rows);
+  *rows_for_list = rows;
+  if (rows <= 0) {
+    const int64_t launch_rows = merge_launch_rows(sh);
+    rows = launch_rows >= kMergeRows16From ? 16 : launch_rows >= kMergeRows8From ? 8 : kMergeMinRows;
+    // A launch of the recomputing form over several searches with many rounds of workgroups: the
+    // largest items that still fill the device one and a quarter times if nothing is pruned, the same
+    // size for every search of the launch.  Copying the rows in, clearing the tile and the atomics are
+    // paid per item (config 5: 16 -> 64 rows, 157 -> 115 us per level when an item held its minimum in
+    // registers; six workgroups per compute unit at 32 devices since: one and a quarter rounds 2.13 ms
+    // for all levels, two 2.13, three 2.25; over ragged batches of 100 to 1 500 searches within 5 %).
+    if (paired && sh.nprob > 1 && items_at(rows) * sh.nprob > slots)
+      for (int r = max_rows; r > rows; r -= 4)
+        if (4 * items_at(r) * sh.nprob >= 5ll * slots) { rows = r; *rows_for_list = r; break; }
+  }
+  return (int)items_at(rows);
+}
+
+// Workgroups of the sorted-merge level kernel that one compute unit holds at a time (by the
+// registers of its four waves, one per SIMD; see the kernel's resource usage).
+inline int merge_workgroups_per_cu(int bits, int DP, bool recompute) {
+  if (bits == 32) {
+    if (recompute) return DP == 64 ? 4 : DP == 32 ? 6 : 8;
+    return DP == 64 ? 3 : DP == 32 ? 4 : DP == 16 ? 6 : 8;
+  }
+  if (recompute) return DP == 64 ? 3 : DP == 32 ? 5 : 8;
+  return DP == 64 ? 2 : DP == 32 ? 3 : DP == 16 ? 4 : 8;
+}
+
+}  // namespace rannc
