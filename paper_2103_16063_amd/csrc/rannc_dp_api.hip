@@ -122,6 +122,7 @@ struct rannc_dp {
   int next_slot;
   // state of the last successful solve
   bool solved;
+  bool unchosen;  // its stage counts have not been chosen: plan recovery has that done first
   int Q;
   std::vector<ProblemDev> host_probs;  // in device order: grouped by DP class
   std::vector<int32_t> pos_of;         // position of the caller's problem q in that order
@@ -214,6 +215,7 @@ int rannc_dp_create(const rannc_dp_limits_t *l, void *d_workspace, size_t worksp
   h->staging_bytes = header_bytes(l->max_problems);
   h->next_slot = 0;
   h->solved = false;
+  h->unchosen = false;
   h->Q = 0;
   h->timing = false;
   h->ev_valid = false;
@@ -702,6 +704,7 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
   h->pos_of.swap(pos_of);
   h->Q = Q;
   h->solved = true;
+  h->unchosen = choose_later;
   return RANNC_DP_OK;
 }
 
@@ -740,11 +743,16 @@ static int traceback_impl(rannc_dp_t *h, void *hip_stream, const int32_t *d_leve
     lds_bytes = std::max(lds_bytes, need);
   }
   if (!staged) lds_bytes = 0;
-  if (rannc::launch_traceback(h->d_probs, h->Q, plan_stride, d_stage_end, d_replicas, d_levels, lds_bytes, form_stage,
+  // The outer driver chooses one search and stage count itself and leaves those of the other searches
+  // open.  (Done again by every recovery until the next solve: a call may be recorded and never run.)
+  if ((h->unchosen && !form_stage && !choose &&
+       rannc::launch_select(h->d_probs, h->Q, nullptr, nullptr, nullptr, nullptr, (hipStream_t)hip_stream) != hipSuccess) ||
+      rannc::launch_traceback(h->d_probs, h->Q, plan_stride, d_stage_end, d_replicas, d_levels, lds_bytes, form_stage,
                               results, choose, (hipStream_t)hip_stream) != hipSuccess) {
     (void)hipGetLastError();
     return RANNC_DP_HIP_ERROR;
   }
+  if (choose) h->unchosen = false;
   return RANNC_DP_OK;
 }
 

@@ -175,6 +175,7 @@ constexpr int64_t kSplitPackedMax = (1LL << 42) - 2;
 int split_rows_per_item(const LaunchShape &sh, int DP);
 hipError_t launch_level_split_fast(const ProblemDev *probs, const LaunchShape &sh, int bits, int DP, int s,
                                    int rows_per_item, hipStream_t st);
+// (any of the outputs may be null: the choice itself is kept with the search)
 hipError_t launch_select(const ProblemDev *probs, int Q, int64_t *d_opt, int32_t *d_n_stages,
                          int64_t *d_est, int32_t *d_status, hipStream_t st);
 // d_levels: per problem (caller's order) the exact stage count to recover, 0 = the best one; or null

@@ -1447,8 +1447,8 @@ __device__ __forceinline__ void select_finish(const ProblemDev &pr, int64_t v, i
   if (best == INT64_MAX) bs = 0;
   pr.res[0] = best;
   pr.res[1] = bs;
-  d_opt[q] = best;
-  d_n_stages[q] = bs;
+  if (d_opt) d_opt[q] = best;
+  if (d_n_stages) d_n_stages[q] = bs;
   if (d_est) {
     int64_t e = INT64_MAX;
     if (bs > 0) {

@@ -233,3 +233,43 @@ def test_one_handle_serves_inputs_of_growing_size():
             _assert_same(c, got, _oracle_form_stage(c), big.plan_stride)
     finally:
         big.close()
+
+
+@pytest.mark.parametrize("N", [20, 150])
+def test_plans_of_all_searches_behind_the_driver(N):
+    """The driver leaves its searches on the handle as a solved batch: plan recovery behind it gives the best
+    plan of every one of them, with no word of an earlier use of the workspace in between (at 150 blocks
+    the searches run level by level and the driver itself asks for one plan only)."""
+    nodes, per_node, batch = 2, 4, 8
+    c = synth.form_stage_case(11, N, nodes, per_node, batch, tight=3.0, tmax=60)
+    fs = B.FormStageSession(N, nodes, per_node, batch)
+    try:
+        fs.ws.fill_(0x5A)
+        rc, out, *_ = fs.run(c["time_per_sample_ns"], c["act_bytes_per_sample"], c["param_bytes"], c["mem_capacity"])
+        assert rc == B.OK and out.feasible
+        stream = torch.cuda.current_stream().cuda_stream
+        probs = []
+        for n in (1, 2):
+            MB = 1
+            while MB <= batch // (nodes // n):
+                b = batch // (nodes // n) // MB
+                probs.append({"name": f"n{n}_MB{MB}", "time_ns": c["time_per_sample_ns"] * b, "param_bytes": c["param_bytes"],
+                              "act_bytes": c["act_bytes_per_sample"] * b, "n_devices": n * per_node,
+                              "max_stages": n * per_node, "n_microbatches": MB, "mem_capacity": c["mem_capacity"]})
+                MB *= 2
+        assert len(probs) == fs.Q
+        levels = torch.zeros(fs.Q, dtype=torch.int32, device="cuda:0")
+        for lev in (None, levels):
+            se, rp = (torch.full((fs.Q, fs.plan_stride), -7, dtype=torch.int32, device="cuda:0") for _ in range(2))
+            rc = (B.rannc_dp_traceback(fs.h, stream, fs.plan_stride, se, rp) if lev is None else
+                  B.rannc_dp_traceback_at(fs.h, stream, lev, fs.plan_stride, se, rp))
+            assert rc == B.OK
+            torch.cuda.synchronize()
+            for q, pr in enumerate(probs):
+                o = oracle.solve(pr)
+                k = o["n_levels"]
+                assert np.array_equal(se[q, :k].cpu().numpy(), o["stage_end"][:k]), pr["name"]
+                assert np.array_equal(rp[q, :k].cpu().numpy(), o["replicas"][:k]), pr["name"]
+                assert (se[q, k:] == -1).all() and (rp[q, k:] == -1).all()
+    finally:
+        fs.close()
