@@ -176,9 +176,11 @@ RANNC_DP_API int rannc_dp_create(const rannc_dp_limits_t *limits, void *d_worksp
  *   d_est_iter_ns DEVICE int64[Q] or NULL: (MB + s* - 1) * opt, the fill-and-drain time of one
  *                synchronous pipeline iteration (Fig. 1), saturating at INT64_MAX
  *   d_status     DEVICE int32[Q] or NULL: RANNC_DP_PROBLEM_* per problem
- * Searches of different device-count classes (D <= 8, 16, 32, 64) of one batch of more than 64 searches
- * may run on streams of the handle (smaller batches run as one group); they start after the work already on hip_stream and hip_stream is made to wait
- * for them, so for the caller everything is ordered on hip_stream as if it ran there.
+ * Searches of different device-count classes (D <= 8, 16, 32, 64) of one batch may run on streams of the
+ * handle; they start after the work already on hip_stream and hip_stream is made to wait for them, so
+ * for the caller everything is ordered on hip_stream as if it ran there.  (A batch of up to 64 searches
+ * normally runs as one group on hip_stream; class by class where the searches of the narrower classes are
+ * large, where the workspace does not hold them at the widest one's width, and with one_launch_small = 2.)
  * Host-side argument errors are returned before anything is enqueued. */
 RANNC_DP_API int rannc_dp_solve(rannc_dp_t *h, const rannc_dp_batch_t *batch, void *hip_stream,
                    int64_t *d_opt, int32_t *d_n_stages, int64_t *d_est_iter_ns,

@@ -33,17 +33,53 @@ struct Sizes {  // bytes of one problem's regions inside the workspace
   }
 };
 
-// A batch of at most this many searches runs as ONE group: its V rows are padded to the widest
-// device-count class of the batch, so that every launch covers all of its searches.  Few searches do
-// not fill the device, a level costs what a launch costs, and a launch per class and level costs the
-// host 3 us each (outer driver at 512 blocks, three classes: 75 launches for 31 levels).  The merges are
-// as wide as each search's level needs anyway.
-constexpr int kOneGroupMax = 64;
-int group_dp(const rannc_dp_batch_t *b) {
+// A batch of few searches can run as ONE group: its V rows are padded to the widest device-count class of
+// the batch, so that every launch covers all of its searches.  A level then costs one launch instead of
+// one per class (3 us of the host each) and no stream is forked and joined (20 us a class).  The price is
+// paid by the narrower searches: their merges are as wide as their own level needs anyway, but they run
+// in the wide kernel, with fewer workgroups per compute unit and longer rows to copy and clear.  It
+// grows with their rows, the saving with the number of classes.  So a batch is a group while the narrower
+// searches have at most this many rows (unpruned): the first number for a batch of two classes, the second
+// more for every further class.  Measured over 550 batches of 2 to 64 searches of 16 to 1024 blocks, one
+// group / class by class: 4 x 160 blocks at 8 and 4 at 64 devices 154 / 187 us, 24 searches of the
+// outer driver at 384 blocks 334 / 372, 16 x 256 at each of 8, 16 and 32 221 / 277, 2 x 96 at each class
+// 141 / 269; beyond the lines 15 x 400 at 8 and one at 32 261 / 180, 2 x 1024 at each class 1230 / 753, 63 x
+// 1024 at 8 and one at 64 7350 / 1085.  With 64-bit values or the split objective the wide kernels
+// are slower still: 4 x 200 at 8 and 4 at 64, 64-bit, 290 / 246; 15 x 128 at 16 and one at 32, split, 412 / 295.
+constexpr int kOneGroupMax = 64;  // searches
+struct GroupRows { int two, more; };
+constexpr GroupRows kGroupRows[3][3] = {  // widest class: 16, 32, 64 devices
+    {{20480, 0}, {10240, 25600}, {5632, 1792}},  // 32-bit values
+    {{10240, 0}, {7168, 7168}, {1408, 1408}},    // 64-bit values
+    {{3584, 0}, {1792, 1792}, {768, 768}},       // split objective
+};
+
+int64_t search_rows(int N) {  // chunk c holds rows 0 .. 64c+63
+  const int64_t full = N / 64;
+  return 32 * full * (full + 1) + (N % 64 ? N : 0);
+}
+
+// the class whose width all searches of the batch would run at as a group, or 0: too many searches
+int widest_class(const rannc_dp_batch_t *b) {
   if (b->n_problems > kOneGroupMax) return 0;
   int D = 1;
   for (int q = 0; q < b->n_problems; ++q) D = std::max(D, b->n_devices[q]);
   return rannc::dp_class(D);
+}
+
+// the class whose width all searches of the batch run at, or 0: each at that of its own class
+int group_dp(const rannc_dp_batch_t *b, int bits, bool split) {
+  const int widest = widest_class(b);
+  int64_t narrower = 0;
+  int classes = 0;  // as a mask, 8 | 16 | 32 | 64
+  for (int q = 0; q < b->n_problems && widest; ++q) {
+    const int own = rannc::dp_class(b->n_devices[q]);
+    classes |= own;
+    if (own < widest) narrower += search_rows(b->n_blocks[q]);
+  }
+  if (classes == widest) return widest;
+  const GroupRows &most = kGroupRows[split ? 2 : bits == 64 ? 1 : 0][widest == 16 ? 0 : widest == 32 ? 1 : 2];
+  return narrower <= most.two + (int64_t)(__builtin_popcount(classes) - 2) * most.more ? widest : 0;
 }
 
 // false on arithmetic overflow
@@ -187,7 +223,7 @@ size_t rannc_dp_workspace_bytes(const rannc_dp_limits_t *l) {
 size_t rannc_dp_workspace_bytes_for(const rannc_dp_limits_t *l, const rannc_dp_batch_t *b) {
   if (!limits_ok(l) || check_batch(l, b) != RANNC_DP_OK) return 0;
   size_t tot = header_bytes(l->max_problems);
-  const int all = group_dp(b);
+  const int all = widest_class(b);  // (room for the group, whichever way the batch then runs)
   for (int q = 0; q < b->n_problems; ++q) {
     Sizes sz;
     const int S_eff = std::min(b->max_stages[q], std::min(b->n_blocks[q], b->n_devices[q]));
@@ -353,7 +389,7 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
   }
   // (a handle told to run every small search as one launch keeps the classes apart: the form of that
   // kernel depends on the class)
-  int all = h->fused_small == 2 ? 0 : group_dp(b);
+  int all = h->fused_small == 2 ? 0 : group_dp(b, h->bits, split);
   if (all) {
     // a workspace sized for another batch can hold these searches only at their own classes' widths
     size_t need = header_bytes(h->lim.max_problems);
