@@ -202,8 +202,9 @@ RANNC_DP_API int rannc_dp_traceback(rannc_dp_t *h, void *hip_stream, int32_t pla
  * with the meaning they have above.
  *   d_results  DEVICE, h_results HOST (pinned memory is copied to faster in large batches), 8-byte aligned,
  *              results_bytes bytes each
- * Synchronous: everything before it on hip_stream has completed when it returns.  Its first use on a
- * handle (and any later use with a larger batch) allocates pinned host memory, freed by destroy.
+ * Synchronous: everything before it on hip_stream has completed when it returns.  Allocates nothing,
+ * except where plan_stride is beyond the handle's longest plan (max_stages, at most 64): then pinned
+ * host memory, at the first such call and at any later one that needs more, freed by destroy.
  * Errors as rannc_dp_solve and rannc_dp_traceback; INVALID_ARG if results_bytes is too small. */
 RANNC_DP_API int rannc_dp_solve_to_host(rannc_dp_t *h, const rannc_dp_batch_t *batch, void *hip_stream,
                                         int32_t plan_stride, void *d_results, void *h_results,

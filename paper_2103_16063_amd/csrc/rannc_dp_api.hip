@@ -142,6 +142,23 @@ int check_batch(const rannc_dp_limits_t *l, const rannc_dp_batch_t *b) {
   return RANNC_DP_OK;
 }
 
+struct ResultLayout {  // offsets of the arrays of one result buffer
+  size_t opt, est, n_stages, status, stage_end, replicas, total;
+  ResultLayout(size_t Q, size_t stride) {
+    auto a8 = [](size_t x) { return (x + 7) / 8 * 8; };
+    opt = 0;
+    est = opt + 8 * Q;
+    n_stages = est + 8 * Q;
+    status = n_stages + a8(4 * Q);
+    stage_end = status + a8(4 * Q);
+    replicas = stage_end + a8(4 * Q * stride);
+    total = replicas + a8(4 * Q * stride);
+  }
+};
+
+// batches of up to this many searches write their results to host memory themselves
+constexpr int kPollMaxProblems = 64;
+
 }  // namespace
 
 struct rannc_dp {
@@ -149,9 +166,13 @@ struct rannc_dp {
   int bits;
   char *ws;
   size_t ws_bytes;
-  // pinned staging for the per-problem descriptors and problem lists, reused round-robin
+  // Pinned host memory, one allocation: staging for the per-problem descriptors, reused round-robin, and
+  // behind it the mirror the kernels write a small batch's results into.  (A mirror allocated by the first
+  // call that wants one made that call wait for it: first call of a
+  // handle at 16 / 96 / 251 blocks 50 / 82 / 134 us, here 27 / 59 / 109.)
+  char *pin, *pin_dev;               // pin_dev: the address the device uses, or null
   char *staging[kStagingSlots];
-  char *staging_dev[kStagingSlots];  // the address the device reads it through, or null
+  char *staging_dev[kStagingSlots];  // or null
   hipEvent_t staging_free[kStagingSlots];
   bool staging_used[kStagingSlots];
   size_t staging_bytes;
@@ -172,9 +193,10 @@ struct rannc_dp {
   // the others run on streams of the handle (default priority), forked from and joined to the
   // caller's stream with events.  Off while per-phase timing is on (the phases are timed on the
   // caller's stream) and with RANNC_DP_STREAMS=0.
-  char *res_pin;         // pinned host mirror of a batch's results, written by the kernels (grown on demand)
-  char *res_pin_dev;     // its device address
+  char *res_pin;         // the mirror: inside pin, or (a longer plan stride) an allocation of its own
+  char *res_pin_dev;     // its device address, or null
   size_t res_pin_bytes;
+  bool res_pin_own;
   uint64_t seq;          // of the calls that poll for their results
   char *fs_pin;          // pinned host mirror of the outer driver's device scratch (grown on demand)
   char *fs_pin_dev;      // the address the device reads and writes the mirror through, or null
@@ -272,25 +294,36 @@ int rannc_dp_create(const rannc_dp_limits_t *l, void *d_workspace, size_t worksp
   h->fused_small = l->one_launch_small == 1 ? 0 : l->one_launch_small == 2 ? 2 : 1;
   if (const char *e = std::getenv("RANNC_DP_FUSED_SMALL")) h->fused_small = std::atoi(e);
   h->d_probs = (ProblemDev *)h->ws;
-  h->res_pin = nullptr;
-  h->res_pin_dev = nullptr;
-  h->res_pin_bytes = 0;
+  h->res_pin_own = false;
   h->seq = 0;
   h->fs_pin = nullptr;
   h->fs_pin_dev = nullptr;
   h->fs_pin_bytes = 0;
   h->multi_stream = l->single_stream == 0;
   if (const char *e = std::getenv("RANNC_DP_STREAMS")) h->multi_stream = std::atoi(e) != 0;
-  int made_staging = 0, made_ev_s = 0, made_ev = 0, made_aux = 0, made_join = 0;
+  int made_ev_s = 0, made_ev = 0, made_aux = 0, made_join = 0;
   bool made_fork = false;
   bool ok = true;
-  for (int k = 0; k < kStagingSlots && ok; ++k) {
-    h->staging_used[k] = false;
-    ok = hipHostMalloc((void **)&h->staging[k], h->staging_bytes, hipHostMallocMapped | hipHostMallocPortable) == hipSuccess;
-    if (ok) ++made_staging;
-    if (ok && hipHostGetDevicePointer((void **)&h->staging_dev[k], h->staging[k], 0) != hipSuccess) {
+  {
+    const size_t polled = (size_t)std::min(l->max_problems, kPollMaxProblems);
+    h->res_pin_bytes = ResultLayout(polled, (size_t)std::min(l->max_stages, RANNC_DP_MAX_DEVICES)).total + 8 * polled;
+    const size_t res_at = kStagingSlots * h->staging_bytes;
+    ok = hipHostMalloc((void **)&h->pin, res_at + h->res_pin_bytes, hipHostMallocMapped | hipHostMallocPortable) == hipSuccess;
+    if (!ok) {
+      h->pin = nullptr;
+    } else if (hipHostGetDevicePointer((void **)&h->pin_dev, h->pin, 0) != hipSuccess) {
       (void)hipGetLastError();
-      h->staging_dev[k] = nullptr;
+      h->pin_dev = nullptr;
+    }
+    for (int k = 0; k < kStagingSlots && ok; ++k) {
+      h->staging_used[k] = false;
+      h->staging[k] = h->pin + k * h->staging_bytes;
+      h->staging_dev[k] = h->pin_dev ? h->pin_dev + k * h->staging_bytes : nullptr;
+    }
+    if (ok) {
+      h->res_pin = h->pin + res_at;
+      h->res_pin_dev = h->pin_dev ? h->pin_dev + res_at : nullptr;
+      std::memset(h->res_pin, 0, h->res_pin_bytes);
     }
   }
   for (int k = 0; k < kStagingSlots && ok; ++k) {
@@ -317,7 +350,7 @@ int rannc_dp_create(const rannc_dp_limits_t *l, void *d_workspace, size_t worksp
     for (int k = 0; k < made_aux; ++k) (void)hipStreamDestroy(h->aux[k]);
     for (int k = 0; k < made_join; ++k) (void)hipEventDestroy(h->join_ev[k]);
     if (made_fork) (void)hipEventDestroy(h->fork_ev);
-    for (int k = 0; k < made_staging; ++k) (void)hipHostFree(h->staging[k]);
+    if (h->pin) (void)hipHostFree(h->pin);
     for (int k = 0; k < made_ev_s; ++k) (void)hipEventDestroy(h->staging_free[k]);
     for (int k = 0; k < made_ev; ++k) (void)hipEventDestroy(h->ev[k]);
     delete h;
@@ -332,7 +365,6 @@ void rannc_dp_destroy(rannc_dp_t *h) {
   if (!h) return;
   for (int k = 0; k < kStagingSlots; ++k) {
     if (h->staging_used[k]) (void)hipEventSynchronize(h->staging_free[k]);
-    (void)hipHostFree(h->staging[k]);
     (void)hipEventDestroy(h->staging_free[k]);
   }
   for (int k = 0; k < 4; ++k) (void)hipEventDestroy(h->ev[k]);
@@ -343,7 +375,8 @@ void rannc_dp_destroy(rannc_dp_t *h) {
   }
   (void)hipEventDestroy(h->fork_ev);
   if (h->fs_pin) (void)hipHostFree(h->fs_pin);
-  if (h->res_pin) (void)hipHostFree(h->res_pin);
+  if (h->res_pin_own) (void)hipHostFree(h->res_pin);
+  (void)hipHostFree(h->pin);
   delete h;
 }
 
@@ -829,23 +862,6 @@ int wait_flags(hipStream_t st, const uint64_t *flags, int n, uint64_t seq) {
   return RANNC_DP_OK;
 }
 
-struct ResultLayout {  // offsets of the arrays of one result buffer
-  size_t opt, est, n_stages, status, stage_end, replicas, total;
-  ResultLayout(size_t Q, size_t stride) {
-    auto a8 = [](size_t x) { return (x + 7) / 8 * 8; };
-    opt = 0;
-    est = opt + 8 * Q;
-    n_stages = est + 8 * Q;
-    status = n_stages + a8(4 * Q);
-    stage_end = status + a8(4 * Q);
-    replicas = stage_end + a8(4 * Q * stride);
-    total = replicas + a8(4 * Q * stride);
-  }
-};
-
-// batches of up to this many searches write their results to host memory themselves
-constexpr int kPollMaxProblems = 64;
-
 }  // namespace
 
 int rannc_dp_solve_to_host(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream, int32_t plan_stride,
@@ -867,17 +883,15 @@ int rannc_dp_solve_to_host(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_s
   r.d_stage_end = (int32_t *)(d + at.stage_end); r.d_replicas = (int32_t *)(d + at.replicas);
   bool poll = Q <= kPollMaxProblems;
   const size_t need = at.total + 8 * (size_t)Q;
-  if (poll && h->res_pin_bytes < need) {
-    if (h->res_pin) {  // (no earlier call is under way: they all waited)
-      (void)hipHostFree(h->res_pin);
-      h->res_pin = nullptr;
-      h->res_pin_bytes = 0;
-    }
-    if (hipHostMalloc((void **)&h->res_pin, need, hipHostMallocMapped | hipHostMallocPortable) != hipSuccess) {
+  if (poll && h->res_pin_bytes < need) {  // a longer stride than any plan of the handle
+    char *grown = nullptr;
+    if (hipHostMalloc((void **)&grown, need, hipHostMallocMapped | hipHostMallocPortable) != hipSuccess) {
       (void)hipGetLastError();
-      h->res_pin = nullptr;
       return RANNC_DP_NO_HOST_MEMORY;
     }
+    if (h->res_pin_own) (void)hipHostFree(h->res_pin);  // (no earlier call is under way: they all waited)
+    h->res_pin_own = true;
+    h->res_pin = grown;
     h->res_pin_bytes = need;
     std::memset(h->res_pin, 0, need);
     if (hipHostGetDevicePointer((void **)&h->res_pin_dev, h->res_pin, 0) != hipSuccess) {

@@ -94,3 +94,37 @@ def test_results_of_another_layout_are_no_completion():
         assert rc == B.OK
         assert_results_match(one, dict(zip(("opt", "est_iter_ns", "n_stages", "status", "stage_end", "replicas"),
                                            o._h_views)))
+
+
+def _device_mappings():
+    with open("/proc/self/maps") as f:
+        return sum("/dev/dri/" in line for line in f)
+
+
+@pytest.mark.parametrize("Q", [1, 64])
+def test_first_call_of_a_handle_allocates_no_pinned_memory(Q):
+    """What hipHostMalloc hands out is a mapping of the device file; a first call that makes one waits for it."""
+    probs = [synth.random_small(820 + q, 40, 16, 6, tight=2.0) for q in range(Q)]
+    with B.Session(synth.concat_batch(probs)) as s:
+        s.run()                    # (whatever the process does once is behind us)
+    with B.Session(synth.concat_batch(probs)) as s:
+        before = _device_mappings()
+        res = s.run()
+        assert before > 0 and _device_mappings() == before
+        assert_results_match(probs, res)
+
+
+def test_plan_strides_beyond_the_longest_plan():
+    probs = [synth.random_small(830 + q, 40, 16, 6, tight=2.0) for q in range(3)]
+    with B.Session(synth.concat_batch(probs)) as s:
+        want = s.run()
+        for stride in (6, 70, 300, 100, 6):      # the mirror grows twice, and serves smaller strides after
+            n = 3 * 16 + 16 + 16 + 2 * 3 * 4 * stride
+            d = torch.empty(n // 8, dtype=torch.int64, device="cuda:0")
+            h = torch.zeros(n // 8, dtype=torch.int64)
+            assert B.rannc_dp_solve_to_host(s.h, s.hb, s.stream(), stride, d, h, n) == B.OK
+            w = h.numpy()
+            assert np.array_equal(w[:3], want["opt"]) and np.array_equal(w[3:6], want["est_iter_ns"])
+            plans = w[10:].view(np.int32).reshape(2, 3, stride)
+            for key, plan in zip(("stage_end", "replicas"), plans):
+                assert np.array_equal(plan[:, :6], want[key]) and (plan[:, 6:] == -1).all(), (stride, key)
