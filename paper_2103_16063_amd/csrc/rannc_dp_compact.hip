@@ -1,6 +1,7 @@
 // gfx950 kernel of the compaction step of RaNNC's block-level phase (Sec. III-B) on a chain, and
 // its launcher.
 #include "rannc_dp_device.h"
+#include "rannc_dp_once.h"
 
 namespace rannc {
 
@@ -537,12 +538,12 @@ template <int MODE>
 static hipError_t compact_go(size_t lds, int G, int k, int64_t M, int max_walks, const int64_t *t, const int64_t *p,
                              const int64_t *a, void *ws, int32_t *n_out, int32_t *block_end, int64_t *t_out,
                              int64_t *p_out, int64_t *a_out, int32_t *status, hipStream_t st) {
-  // more than the default 64 KiB of dynamic LDS has to be asked for once
+  // more than the default 64 KiB of dynamic LDS has to be asked for
   constexpr size_t most = MODE == 0 ? 3 * compact_array_bytes(kCompactSmall, 8) + 2 * compact_array_bytes(kCompactSmall, 4)
                           : MODE == 1 ? compact_array_bytes(kCompactTimesLds, 8) : 0;
   if constexpr (most > 64 * 1024) {
-    static const hipError_t attr =
-        hipFuncSetAttribute((const void *)compact_kernel<MODE>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
+    static std::atomic<uint64_t> asked{0};
+    const hipError_t attr = allow_lds(asked, (const void *)compact_kernel<MODE>, (int)most);
     if (attr != hipSuccess) return attr;
   }
   if (lds > most) return hipErrorInvalidValue;

@@ -8,6 +8,7 @@
 // level kernels: every access stays inside the problem's own regions, and its values are never
 // reported (the final selection, the plan recovery and the exports check the status word).
 #include "rannc_dp_device.h"
+#include "rannc_dp_once.h"
 #include "rannc_dp_worklist.h"
 
 #include <type_traits>
@@ -2095,9 +2096,9 @@ hipError_t launch_traceback(const ProblemDev *p, int Q, int plan_stride, int32_t
   const FormStageIn &f = form_stage ? *form_stage : no_choice;
   if (form_stage) Q = 1;
   if (lds_bytes > 0) {
-    // more than the default 64 KiB of dynamic LDS has to be asked for once
-    static const hipError_t attr = hipFuncSetAttribute((const void *)traceback_lds_kernel,
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, kTracebackLdsMax);
+    // more than the default 64 KiB of dynamic LDS has to be asked for
+    static std::atomic<uint64_t> asked{0};
+    const hipError_t attr = allow_lds(asked, (const void *)traceback_lds_kernel, kTracebackLdsMax);
     if (attr != hipSuccess) return attr;
     if (lds_bytes > kTracebackLdsMax) return hipErrorInvalidValue;
     hipLaunchKernelGGL(traceback_lds_kernel, dim3(Q), dim3(kTracebackThreads), (size_t)lds_bytes, st, p, plan_stride,
