@@ -975,8 +975,6 @@ size_t fs_scratch(int Q, int N, int stride) {
   b += 5 * align_up((size_t)Q * N * 8);       // scaled time, param, act, cut bytes, backward time
   b += align_up((size_t)Q * 8);               // n and MB of every search (int32 each; travels up with the inputs)
   b += 2 * align_up((size_t)Q * 8);           // opt, (n_stages + status as int32 pairs)
-  b += align_up((size_t)Q * stride * 8);      // per-level values
-  b += align_up((size_t)Q * 4);               // forced levels
   b += 2 * align_up((size_t)Q * stride * 4);  // plans of the batch
   b += align_up(6 * 8 + (size_t)stride * 8);  // result record and the chosen plan (travels down)
   return b;
@@ -1069,9 +1067,7 @@ int rannc_dp_form_stage(rannc_dp_t *h, const rannc_dp_form_stage_in_t *in, void 
   const size_t o_p = o_t + a_in, o_a = o_t + 2 * a_in, o_o = o_t + 3 * a_in, o_b = o_t + 4 * a_in;
   const size_t o_opt = o_t + 5 * a_in;
   const size_t o_ns = o_opt + align_up((size_t)Q * 8);
-  const size_t o_vals = o_ns + align_up((size_t)Q * 8);  // (room of an earlier layout; rannc_dp_form_stage_scratch_bytes counts it)
-  const size_t o_lev = o_vals + align_up((size_t)Q * stride * 8);
-  const size_t o_se = o_lev + align_up((size_t)Q * 4);
+  const size_t o_se = o_ns + align_up((size_t)Q * 8);
   const size_t o_rp = o_se + align_up((size_t)Q * stride * 4);
   const size_t o_rec = o_rp + align_up((size_t)Q * stride * 4);
   char *dev = (char *)d_scratch, *pin = h->fs_pin;
