@@ -277,11 +277,11 @@ def test_rows_per_wave_variants(rows, algo):
     probs = [synth.enlarged_transformer_chain(seed=21, N=333, D=64, S=12, M=24 * synth.GiB),
              synth.random_small(77, 150, 40, 9, tight=1.3, tmax=5000),
              synth.random_small(78, 65, 7, 7, tight=1.1, tmax=50)]
-    for width in WIDTHS:
+    for width in WIDTHS + [B.WIDE_RECOMPUTE_MAX_TOTAL_TIME]:
         res, sess = gpu_run(probs, max_total_time_ns=width, rows_per_wave=rows, algo=algo, one_launch_small=1)
         with sess:
             rc, info = B.rannc_dp_solve_info(sess.h)
-            want = B.KERNEL_MERGE_RECOMPUTE if (algo == B.ALGO_RECOMPUTE and width == B.NARROW_MAX_TOTAL_TIME) \
+            want = B.KERNEL_MERGE_RECOMPUTE if (algo == B.ALGO_RECOMPUTE and width <= B.WIDE_RECOMPUTE_MAX_TOTAL_TIME) \
                 else B.KERNEL_MERGE_TABLE
             assert rc == B.OK and list(info.n_problems) == [1, 0, 0, 2]
             assert [info.level_kernel[k] for k in (0, 3)] == [want, want]
@@ -522,8 +522,9 @@ def test_more_searches_than_one_grid_dimension_holds(fused):
 
 def test_environment_overrides_and_automatic_choice_of_the_level_kernel(monkeypatch):
     """What rannc_dp_solve_info reports: a large class of a 32-bit batch has its stage times
-    recomputed, a small one reads the table, 64-bit handles and batches with a communication term
-    always read the table; the documented environment variables override the limits' tuning."""
+    recomputed, a small one reads the table, 64-bit handles with a bound above 2^40 ns and batches with a
+    communication term always read the table; the documented environment variables override the limits'
+    tuning."""
     big = synth.batched_sweep(Q=1000)
     big = [p for p in big if p["n_devices"] == 64][:200] + [p for p in big if p["n_devices"] == 32][:2]
     res, sess = gpu_run(big)

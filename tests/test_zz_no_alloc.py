@@ -32,8 +32,8 @@ def run(static, t, p, a, k, M, walks):
 
 def test_static_workspace_entry_point_matches_on_two_calls_in_a_row():
     g = np.random.default_rng(77)
-    # first a chain whose state lives in the workspace (beyond the LDS size) and whose listing is
-    # the bitonic sort, then a much smaller one whose workspace still holds the first call's data
+    # first a chain whose state lives in the workspace (beyond the LDS size), then much smaller ones while
+    # the workspace still holds the first call's data
     for G, k, M, walks in ((6000, 50, 5000, 0), (700, 9, 900, 0), (1601, 3, 10**9, 2), (40, 4, 150, 1)):
         t = g.integers(0, 1000, G)
         p, a = g.integers(0, 50, G), g.integers(0, 50, G)
