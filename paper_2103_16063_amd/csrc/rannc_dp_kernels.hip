@@ -677,9 +677,10 @@ __device__ __forceinline__ void row_merge(VT (&x)[H], const VT RANNC_GLOBAL *__r
   bitonic_sort(x);
 }
 
-// The same for a level kernel that recomputes the stage times instead of reading their table (32-bit
-// values, no communication term): the lane's stage has total time tij, fits from rmn replicas on
-// (255: never, or a lane without work), and c[r] = ceil(tij / r), INF for r < rmn.
+// The same for a level kernel that recomputes the stage times instead of reading their table (no
+// communication term; 32-bit values here, 64-bit ones at DirectArith<uint64_t>): the lane's stage has total
+// time tij, fits from rmn replicas on (255: never, or a lane without work), and c[r] = ceil(tij / r),
+// INF for r < rmn.
 //
 // ceil(x / r) for 0 <= x < 2^32 and odd r <= 63 without an integer division, in double precision:
 //     t = x + (r/2 - 1 + r * 2^-18)            exact (a multiple of 2^-18 below 2^33)
