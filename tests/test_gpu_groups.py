@@ -76,3 +76,29 @@ def test_a_group_that_does_not_fit_the_workspace_runs_class_by_class():
         finally:
             torch.cuda.synchronize()
             B.rannc_dp_destroy(other)
+
+
+@pytest.mark.parametrize("narrow", [3, 20])      # one group; class by class on streams of the handle
+def test_recorded_into_a_graph_and_replayed(narrow):
+    probs = _batch([(160, 8)] * narrow + [(160, 64)], False)
+    with B.Session(synth.concat_batch(probs)) as s:
+        want = s.run()
+        side = torch.cuda.Stream()
+        with torch.cuda.stream(side):
+            s.solve()
+            s.traceback()
+        side.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            s.solve()
+            s.traceback()
+        for _ in range(4):
+            s.d_opt.fill_(-7)
+            s.d_se.fill_(-7)
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert np.array_equal(s.d_opt.cpu().numpy(), want["opt"])
+            assert np.array_equal(s.d_se.cpu().numpy(), want["stage_end"])
+        for _ in range(3):
+            assert_results_match(probs, s.run())
