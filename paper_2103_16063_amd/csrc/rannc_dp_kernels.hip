@@ -682,51 +682,51 @@ __device__ __forceinline__ void row_merge(VT (&x)[H], const VT RANNC_GLOBAL *__r
 // time tij, fits from rmn replicas on (255: never, or a lane without work), and c[r] = ceil(tij / r),
 // INF for r < rmn.
 //
-// ceil(x / r) for 0 <= x < 2^32 and odd r <= 63 without an integer division, in double precision:
-//     t = x + (r/2 - 1 + r * 2^-18)            exact (a multiple of 2^-18 below 2^33)
-//     y = t * (1/r) + 1.5 * 2^52               one fused multiply-add
-// t / r = (x + r - 1)/r - 1/2 + 2^-18; the fraction of (x + r - 1)/r is a multiple of 1/r, at most
-// 62/63, and the rounded 1/r puts the product off by less than 2^-21, so t * (1/r) lies strictly
-// between k - 1/2 and k + 1/2 for k = floor((x + r - 1) / r): the addition of 1.5 * 2^52 rounds it to
-// that integer and leaves k in the low word of the sum.  Even replica counts follow from
-// ceil(x / 2r) = ceil(ceil(x / r) / 2): an add and a shift.  Two full-rate instructions per entry.
-// The reciprocals live in scalar register pairs for the whole kernel and 1.5 * 2^52 in a vector
-// register pair (an instruction takes one scalar operand): the rows of V[s-1] come out of LDS, so the
-// scalar registers are free for them.
-// The INF below rmn comes from a per-lane bit mask (bit r-1 set for r < rmn), one bit-field extract
-// per entry, folded into the first maximum of the merge together with a[].
-struct DirectConsts {
-  double inv[32];  // 1 / (2k + 1)
-  double magic;    // 1.5 * 2^52
+// ceil(x / r) for r = odd * 2^k, k <= 3, is ONE double-precision instruction, run with the rounding mode set
+// to "towards +infinity":
+//     y = x * (inv * 2^-53) + 2^(k - 1)      a fused multiply-add, inv just below 1/odd
+// The sum lies in [2^(k-1), 2^k), where doubles are multiples of 2^(k-53): the rounding takes x * inv / 2^k up
+// to the next whole number and leaves that in the mantissa field of y.  inv lies below 1/odd by less than
+// 2^-50 of it (and is exact for odd = 1), so x * inv / 2^k falls short of x / r by less than x / r * 2^-50:
+// less than 2^-18 for x < 2^32, 2^-10 for x <= 2^40.  If x / r is a whole number the ceiling takes it back up to
+// that number; if not, its fraction is at least 1/64 and stays positive.  Four counts up to 64 have k > 3:
+// ceil(x / 2r) = ceil(ceil(x / r) / 2), an add and a shift.  (With the default rounding, odd counts took an
+// addition and a fused multiply-add and even ones an addition and a shift of the odd quotient: twice the
+// instructions.  That form is still the table builder's, which is bound by its stores.  1024 blocks at 64
+// devices: 514 -> 479 us a call where memory never binds, 346 -> 334 where it does.)
+// The reciprocals live in scalar register pairs for the whole kernel (an instruction takes one scalar
+// operand; 1/2, 1, 2 and 4 need no register): the rows of V[s-1] come out of LDS, so the scalar registers
+// are free for them.
+// INF below rmn: a per-lane bit mask (bit r-1 set for r < rmn), folded into the entries.  Lanes without
+// work are not looked at afterwards, and in almost every pass the others fit on one replica already
+// (persistent bytes, which no replica shares, are the larger part): such a pass skips the mask.
+template <int HMAX> struct DirectConsts {
+  double inv[HMAX / 2];  // 2^-53 times a number just below 1 / (2k + 1)
 };
-__device__ __forceinline__ void direct_consts_init(DirectConsts &k) {
+// Also sets the rounding mode of the wave's double-precision instructions, for the rest of the kernel: no
+// other one in the kernels that call this rounds.  (In assembly, so that the compiler does not set the
+// mode back in front of them; every quotient depends on the registers written behind it.)
+template <int HMAX> __device__ __forceinline__ void direct_consts_init(DirectConsts<HMAX> &k) {
+  asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 2, 2), 1" ::);  // towards +infinity
 #pragma unroll
-  for (int q = 0; q < 32; ++q) {
-    k.inv[q] = 1.0 / (double)(2 * q + 1);
-    asm("" : "+s"(k.inv[q]));  // a register, not an immediate (not volatile: no memory effects)
+  for (int q = 0; q < HMAX / 2; ++q) {
+    k.inv[q] = 0x1p-53 * (q == 0 ? 1.0 : 1.0 / (double)(2 * q + 1) * (1.0 - 0x1p-51));
+    asm volatile("" : "+s"(k.inv[q]));  // a register, not an immediate
   }
-  k.magic = 0x1.8p52;
-  asm("" : "+v"(k.magic));
 }
 
-// The same with 64-bit values, for stage times below 2^40 (the caller's bound on a search's total
-// time guarantees it): the offset is 2^-8 instead of 2^-18, so that t stays exact (a multiple of 2^-8
-// below 2^41: 49 bits) while the rounded reciprocal moves the product by less than 2^41 * 2^-53 =
-// 2^-12, far inside both margins (2^-8 below, 1/63 - 2^-8 above).  The quotient, below 2^40, sits in
-// the low 51 bits of the sum; the even counts are a 64-bit add and shift.
 template <typename VT> struct DirectArith;
 template <> struct DirectArith<uint32_t> {
-  static constexpr double kOffset = 0x1p-18;
   static __device__ __forceinline__ uint32_t quotient(double y) { return (uint32_t)__double_as_longlong(y); }
   // 0 or INF from bit (m & 31) of the mask word
   static __device__ __forceinline__ uint32_t inf_if(int word, int m) {
     return (uint32_t)__builtin_amdgcn_sbfe(word, m & 31, 1);
   }
 };
+// 64-bit values: for stage times up to 2^40 (the caller's bound on a search's total time guarantees it)
 template <> struct DirectArith<uint64_t> {
-  static constexpr double kOffset = 0x1p-8;
   static __device__ __forceinline__ uint64_t quotient(double y) {
-    return (uint64_t)__double_as_longlong(y) & ((1ull << 51) - 1ull);
+    return (uint64_t)__double_as_longlong(y) & ((1ull << 52) - 1ull);
   }
   static __device__ __forceinline__ uint64_t inf_if(int word, int m) {
     return (uint64_t)((uint32_t)__builtin_amdgcn_sbfe(word, m & 31, 1) & (uint32_t)(Lim<uint64_t>::inf >> 32)) << 32;
@@ -735,40 +735,34 @@ template <> struct DirectArith<uint64_t> {
 // largest stage time the 64-bit form is exact for
 constexpr int64_t kDirectWideMaxTime = (int64_t)1 << 40;
 
-// AP of the helpers below: x[] already holds the lane's own a[] row (read per lane, not wave-uniform)
-struct InPlaceRow {};
-
-// entry r = ODD << SH and the ones it is the parent of
-template <typename VT, int H, int ODD, int SH, typename AP>
-__device__ __forceinline__ void direct_chain(VT (&x)[H], AP arow, VT q_odd, int mlo, int mhi) {
-  constexpr int R = ODD << SH, M = R - 1;
-  if constexpr (R <= H) {
-    const VT h = SH == 0 ? q_odd : (q_odd + (VT)((1u << SH) - 1u)) >> SH;
-    const VT inf = DirectArith<VT>::inf_if(M < 32 ? mlo : mhi, M);
-    if constexpr (std::is_same<AP, InPlaceRow>::value) x[H - 1 - M] = vmax(vmax(x[H - 1 - M], h), inf);
-    else x[H - 1 - M] = vmax(vmax((VT)arow[H - 1 - M], h), inf);
-    direct_chain<VT, H, ODD, SH + 1, AP>(x, arow, q_odd, mlo, mhi);
+// x[H-1-M] := max(x[H-1-M], c[M+1]) for every entry: x[] holds the lane's row a[sig ..] and becomes the
+// bitonic sequence of the merge.  q8[n - 1]: the quotient of 8n, n odd.
+template <typename VT, int H, int HMAX, int M = 0>
+__device__ __forceinline__ void direct_entries(VT (&x)[H], double tij, const DirectConsts<HMAX> &k, VT (&q8)[H / 8]) {
+  if constexpr (M < H) {
+    constexpr int R = M + 1, CTZ = __builtin_ctz(R), SH = CTZ < 3 ? CTZ : 3, ODD = R >> CTZ;
+    VT h;
+    if constexpr (CTZ <= 3) h = DirectArith<VT>::quotient(__builtin_fma(tij, k.inv[ODD / 2], 0.5 * (1 << SH)));
+    else h = (q8[ODD - 1] + (VT)((1 << (CTZ - 3)) - 1)) >> (CTZ - 3);
+    if constexpr (CTZ == 3) q8[ODD - 1] = h;
+    x[H - 1 - M] = vmax(x[H - 1 - M], h);
+    if constexpr (M % 8 == 7) __builtin_amdgcn_sched_barrier(0);  // (all quotients at once would take twice the registers)
+    direct_entries<VT, H, HMAX, M + 1>(x, tij, k, q8);
   }
 }
 
-// t = x + (r/2 - 1 + r * offset) for the odd r = 2K + 1; the next odd r adds 1 + 2 * offset (exact:
-// every t is a multiple of the offset inside the 53 bits), so one constant serves all entries
-template <typename VT, int H, typename AP, int K = 0>
-__device__ __forceinline__ void direct_entries(VT (&x)[H], AP arow, double t, const DirectConsts &k, int mlo, int mhi) {
-  constexpr int ODD = 2 * K + 1;
-  if constexpr (ODD <= H) {
-    const double y = __builtin_fma(t, k.inv[K], k.magic);
-    direct_chain<VT, H, ODD, 0, AP>(x, arow, DirectArith<VT>::quotient(y), mlo, mhi);
-    direct_entries<VT, H, AP, K + 1>(x, arow, t + (1.0 + 2.0 * DirectArith<VT>::kOffset), k, mlo, mhi);
+// act: the lane has work (x of the others is not looked at)
+template <typename VT, int H, int HMAX>
+__device__ __forceinline__ void row_merge_direct(VT (&x)[H], VT tij, int rmn, bool act, const DirectConsts<HMAX> &k) {
+  VT q8[H / 8];
+  direct_entries<VT, H, HMAX>(x, (double)tij, k, q8);
+  if (__ballot(act && rmn > 1) != 0ull) {
+    // bit r-1 set for r < rmn: these replica counts do not fit
+    const unsigned long long below = rmn > 64 ? ~0ull : ((1ull << (rmn - 1)) - 1ull);
+    const int mlo = (int)(uint32_t)below, mhi = (int)(uint32_t)(below >> 32);
+#pragma unroll
+    for (int m = 0; m < H; ++m) x[H - 1 - m] = vmax(x[H - 1 - m], DirectArith<VT>::inf_if(m < 32 ? mlo : mhi, m));
   }
-}
-
-template <typename VT, int H, typename AP>
-__device__ __forceinline__ void row_merge_direct(VT (&x)[H], AP arow, VT tij, int rmn, const DirectConsts &k) {
-  // bit r-1 set for r < rmn: these replica counts do not fit (all of them for rmn = 255)
-  const unsigned long long below = rmn > 64 ? ~0ull : ((1ull << (rmn - 1)) - 1ull);
-  direct_entries<VT, H, AP>(x, arow, (double)tij + (DirectArith<VT>::kOffset - 0.5), k, (int)(uint32_t)below,
-                            (int)(uint32_t)(below >> 32));
   bitonic_sort(x);
 }
 
@@ -799,7 +793,7 @@ template <typename VT, int HMAX> struct ItemRows {
 template <typename VT, int H, int LS, int HMAX>
 __device__ __forceinline__ bool merge_rows_direct(VT *tile, ItemRows<VT, HMAX> &it, const ProblemDev &pr, const int s,
                                                   const int c, const int i0, const int i_hi, const int lane,
-                                                  const int wave, const DirectConsts &k) {
+                                                  const int wave, const DirectConsts<HMAX> &k) {
   constexpr VT INF = Lim<VT>::inf;
   constexpr int E = ItemRows<VT, HMAX>::E, AS = ItemRows<VT, HMAX>::AS, NT = 64 * kMergeWaves;
   typedef uint32_t Quad __attribute__((ext_vector_type(4)));
@@ -866,7 +860,7 @@ __device__ __forceinline__ bool merge_rows_direct(VT *tile, ItemRows<VT, HMAX> &
 #pragma unroll
       for (int u = 0; u < E; ++u) w[E * g + u] = v[u];
     }
-    row_merge_direct<VT, H, InPlaceRow>(w, InPlaceRow(), tij, r.rmn, k);
+    row_merge_direct<VT, H>(w, tij, r.rmn, act, k);
     if (act) {
 #pragma unroll
       for (int t = 0; t < H; ++t) atomicMin(&tile[r.col * LS + t], w[t]);
@@ -876,9 +870,11 @@ __device__ __forceinline__ bool merge_rows_direct(VT *tile, ItemRows<VT, HMAX> &
 }
 
 // Waves per SIMD the level kernel is compiled for: the two value arrays of the widest 32-bit case
-// fit the 168 registers of three waves per SIMD (the compiler left alone takes one more).
+// fit the 168 registers of three waves per SIMD (the compiler left alone takes one more).  The
+// recomputing form on 32-bit values holds one array: as many as its workgroups per compute unit.
 template <typename VT, int HMAX, bool DIRECT> constexpr int merge_waves_per_simd() {
-  return HMAX == 64 && (!DIRECT || sizeof(VT) == 8) ? 3 : 1;
+  if (DIRECT && sizeof(VT) == 4) return HMAX == 64 ? 4 : HMAX == 48 ? 5 : 6;
+  return HMAX == 64 ? 3 : 1;
 }
 
 // The rows i0+wave, i0+wave+4, ... <= i_hi of one work item, folded into acc (running minimum of the
@@ -979,7 +975,7 @@ __device__ __forceinline__ void level_merge_body(const ProblemDev &pr, const int
   bool any = false;
   const int ng = (D - s + 1 + 7) >> 3;  // width of the merge in groups of eight
   if constexpr (DIRECT) {
-    DirectConsts k;
+    DirectConsts<HMAX> k;
     direct_consts_init(k);
     __shared__ __align__(16) ItemRows<VT, HMAX> rows_in;
 #define RANNC_ROWS(K)                                                                            \
@@ -1183,7 +1179,7 @@ void solve_small_kernel(
   if (tid == 0) s_top[0] = lv[0][N * LS + D - 1];
 
   // ---- levels 2..S_eff ----
-  [[maybe_unused]] DirectConsts kc;
+  [[maybe_unused]] DirectConsts<DP> kc;
   if constexpr (DIRECT) direct_consts_init(kc);
   // passes of the recomputing form (see the level loop): P0 for the triangle of chunk 0, then F1 for
   // the rectangle and P1 for the triangle of chunk 1
@@ -1241,7 +1237,8 @@ void solve_small_kernel(
     constexpr int H = (HH) <= DP ? (HH) : DP;                                                        \
     const int sig = merge_shift(s, DP, H);                                                           \
     VT x[H];                                                                                         \
-    row_merge_direct<VT, H, const VT *>(x, prev + row * LS + sig, tij, act ? rmn : 255, kc); \
+    _Pragma("unroll") for (int t = 0; t < H; ++t) x[t] = prev[row * LS + sig + t];                   \
+    row_merge_direct<VT, H>(x, tij, rmn, act, kc);                                                   \
     if (act && jj + 1 >= s) {                                                                        \
       /* no test per entry: columns D.. hold 0 and keep it, column DP (t + 1 + sig <= DP) is padding */ \
       VT *dst = cur + (jj + 1) * LS + 1 + sig;                                                       \
