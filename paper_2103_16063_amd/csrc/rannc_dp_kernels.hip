@@ -766,104 +766,93 @@ __device__ __forceinline__ void row_merge_direct(VT (&x)[H], VT tij, int rmn, bo
   bitonic_sort(x);
 }
 
-// The rows of one work item of the recomputing level kernel.  Everything the item reads is copied
-// into LDS first, with one round of independent loads (the rows of V[s-1], the rmin bytes and the
-// prefix sums of its rows); the row loop then waits for nothing outside the compute unit.  (With each
-// row's V[s-1] fetched by scalar loads where it was needed, the loop of a search of 1024 blocks at 64
-// devices took 12.4 us of a launch whose instructions account for 6.)  Every row's merge goes straight
-// into the item's LDS tile: a running minimum in registers costs as many instructions per row as the
-// LDS does, and as many registers as the merge itself (1024 blocks: 306 -> 279 us for 31 levels where
-// memory binds, 506 -> 474 us where it does not; 512 searches of 128 blocks at 64 devices 92 -> 82 us).
+// The rows of one work item of the recomputing level kernel.  A wave fetches what a row needs (its row of
+// V[s-1], a value per lane; the rmin bytes; the prefix sums) while it works on the row before, puts the
+// row into LDS when its turn comes and reads it back four values at a time; the waves of the item share
+// nothing but the tile, so a row loop starts one round of loads after the item is known.  (With everything
+// an item reads copied to LDS by the whole workgroup first, a launch without any row to work on took 5.5
+// us at 1024 blocks, where an empty one takes 1.8, and 15 us over 512 searches of 128 blocks.)
+// Every row's merge goes straight into the item's LDS tile: a running minimum in registers costs as many
+// instructions per row as the LDS does, and as many registers as the merge itself.
 // H: width of the merge (multiple of eight, at least rl); LS: row stride of the tile, whose entry t is
-// output t of the merge.  Returns whether any row of this wave had work.
-// Most rows of V[s-1] an item reads: those of the largest item, or both rows of a diagonal item's pairs.
-template <typename VT> constexpr int item_rows() {
-  constexpr int bits = 8 * sizeof(VT);
-  static_assert(2 * merge_max_pairs(merge_max_rows(bits)) <= merge_item_rows(bits), "the rows of an item fit");
-  return merge_item_rows(bits);
-}
-template <typename VT, int HMAX> struct ItemRows {
-  static constexpr int E = 16 / (int)sizeof(VT);  // values per 16 bytes
-  static constexpr int AS = HMAX + E;             // row stride of the copied rows: 16-byte aligned, rows on different banks
-  VT a[item_rows<VT>() * AS];
-  uint8_t rmin[item_rows<VT>() * 64];
-  int64_t T[item_rows<VT>()], Tcol[64];  // prefix sums of the rows and of the chunk's columns
-};
+// output t of the merge.  mine: two rows of this wave.  DIAG: the diagonal block, whose listed row 64c+p
+// stands for the pair of rows 64c+p (lanes p.. with their own columns) and 64c+64-p (the p columns from 64-p
+// on, on the lanes below p): one pass of a full wave instead of two half-empty ones.
+// Returns whether any row of this wave had work.
+template <typename VT, int HMAX> constexpr int direct_row_stride() { return HMAX + 16 / (int)sizeof(VT); }
 
-template <typename VT, int H, int LS, int HMAX>
-__device__ __forceinline__ bool merge_rows_direct(VT *tile, ItemRows<VT, HMAX> &it, const ProblemDev &pr, const int s,
-                                                  const int c, const int i0, const int i_hi, const int lane,
-                                                  const int wave, const DirectConsts<HMAX> &k) {
+template <typename VT, int H, int LS, int HMAX, bool DIAG>
+__device__ __forceinline__ bool merge_rows_direct(VT *tile, VT *mine, const ProblemDev &pr, const int s, const int c,
+                                                  const int i0, const int i_hi, const int lane, const int wave,
+                                                  const DirectConsts<HMAX> &k) {
   constexpr VT INF = Lim<VT>::inf;
-  constexpr int E = ItemRows<VT, HMAX>::E, AS = ItemRows<VT, HMAX>::AS, NT = 64 * kMergeWaves;
-  typedef uint32_t Quad __attribute__((ext_vector_type(4)));
+  constexpr int E = 16 / (int)sizeof(VT);  // values per 16 bytes
+  constexpr int AS = direct_row_stride<VT, HMAX>(), NT = 64 * kMergeWaves;
+  constexpr int TW = 8 / (int)sizeof(VT);  // of a prefix sum only the low bits of a value are looked at
   typedef VT Values __attribute__((ext_vector_type(E)));
-  typedef VT ValuesAny __attribute__((ext_vector_type(E), aligned(sizeof(VT))));  // (a[sig] is any value of the row)
   const int N = pr.N, D = pr.D, DP = pr.DP, nch = pr.nch;
   const int sig = merge_shift(s, DP, H);
   const int64_t lvl = (int64_t)(N + 1) * DP;
-  const VT RANNC_GLOBAL *__restrict__ Vprev = gptr((const VT *)pr.V) + (int64_t)(s - 2) * lvl + sig;
+  const VT RANNC_GLOBAL *__restrict__ Vprev = gptr((const VT *)pr.V) + (int64_t)(s - 2) * lvl + sig + min(lane, H - 1);
   const uint8_t RANNC_GLOBAL *__restrict__ rmin = gptr((const uint8_t *)pr.rmin);
-  const int64_t RANNC_GLOBAL *__restrict__ T = gptr((const int64_t *)pr.T);
+  const VT RANNC_GLOBAL *__restrict__ T = gptr((const VT *)pr.T);
   const int rl = D - s + 1;
-  // Diagonal block: the listed row 64c+p stands for the pair of rows 64c+p (lanes p.. with their own
-  // columns) and 64c+64-p (the p columns from 64-p on, on the lanes below p): one pass of a full wave
-  // instead of two half-empty ones.
-  const bool diag = i0 >= 64 * c;
-  const int n = i_hi - i0 + 1, p0 = i0 - 64 * c, p1 = i_hi - 64 * c;
-  const int staged = diag ? 2 * n : n;  // the second rows 64-p1 .. 64-p0 of the pairs behind the first ones
-  auto row_of = [&](int e) {
-    const int row = e < n ? i0 + e : 64 * c + 64 - p1 + (e - n);
-    return min(min(row, 64 * c + 63), N - 1);  // (p = 0 has no second row; rows beyond the chain have no work)
-  };
-  for (int e = threadIdx.x; e < staged * (H / E); e += NT) {
-    const int row = e / (H / E), q = e % (H / E);
-    const ValuesAny v = *(const ValuesAny RANNC_GLOBAL *)(Vprev + (int64_t)row_of(row) * DP + E * q);
-    *(Values *)&it.a[row * AS + E * q] = (Values)v;
-  }
-  for (int e = threadIdx.x; e < staged * 4; e += NT)
-    *(Quad *)&it.rmin[e * 16] = *(const Quad RANNC_GLOBAL *)(rmin + unit_index(nch, row_of(e >> 2), c) * 64 + (e & 3) * 16);
-  for (int e = threadIdx.x; e < staged; e += NT) it.T[e] = T[row_of(e)];
-  if (threadIdx.x < 64) it.Tcol[threadIdx.x] = T[min(64 * c + lane + 1, N)];  // (clamped: columns beyond N have no work)
-  __syncthreads();
-  bool any = false;
-  // what decides whether a row has work is read one row ahead
-  struct Row { VT alast; int rmn; int64_t Ti; int e, row, col; };
-  auto look = [&](int x) -> Row {
+  const int n = i_hi - i0 + 1, p0 = i0 - 64 * c;
+  struct Row { VT a, b, Ti; int rmn; };
+  auto partner = [&](int p) { return min(min(64 * c + 64 - p, 64 * c + 63), N - 1); };  // (p = 0 has none; rows beyond the chain have no work)
+  auto fetch = [&](int x) -> Row {
     Row r;
-    const int xc = min(x, n - 1);
-    r.e = xc; r.row = i0 + xc; r.col = lane;
-    if (diag) {
-      const int p = p0 + xc;
-      if (lane < p) { r.e = n + p1 - p; r.row = p < 32 ? 64 * c + 64 - p : N; r.col = lane + 64 - p; }  // rows 64c and 64c+32 have no partner
-    }
-    // an (s-1)-stage plan on at most D-1 devices covers blocks 1..row iff the last of them is finite
-    r.alast = it.a[r.e * AS + D - 2 - sig];
-    r.rmn = it.rmin[r.e * 64 + r.col];
-    r.Ti = it.T[r.e];
+    const int xc = min(x, n - 1), p = p0 + xc;
+    r.a = Vprev[(int64_t)(i0 + xc) * DP];
+    r.b = DIAG ? Vprev[(int64_t)partner(p) * DP] : (VT)0;
+    const int row = DIAG && lane < p ? partner(p) : i0 + xc, col = DIAG && lane < p ? lane + 64 - p : lane;
+    r.rmn = rmin[unit_index(nch, row, c) * 64 + col];
+    r.Ti = T[row * TW];
     return r;
   };
-  int x = wave;
-  Row cur = look(x);
-  while (x < n) {  // wave-uniform
-    const Row r = cur;
-    const bool act = r.row >= s - 1 && r.row < N && 64 * c + r.col < N && r.alast != INF && r.rmn <= rl;
-    cur = look(x + kMergeWaves);
-    x += kMergeWaves;
+  Row next = fetch(wave);
+  const VT Tcol = T[min(64 * c + lane + 1, N) * TW];  // (clamped: columns beyond N have no work)
+  typedef uint32_t Quad __attribute__((ext_vector_type(4)));
+  static_assert(64 * LS * sizeof(VT) % 16 == 0, "the tile is cleared 16 bytes at a time");
+  constexpr uint32_t inf_lo = (uint32_t)INF, inf_hi = (uint32_t)((uint64_t)INF >> (sizeof(VT) == 8 ? 32 : 0));
+  for (int e = threadIdx.x; e < 64 * LS / E; e += NT) ((Quad *)tile)[e] = Quad{inf_lo, inf_hi, inf_lo, inf_hi};
+  lds_barrier();  // (the loads stay in flight)
+  bool any = false;
+#pragma unroll 1
+  for (int x = wave; x < n; x += kMergeWaves) {
+    const Row r = next;
+    next = fetch(x + kMergeWaves);
+    const int p = p0 + x;
+    int row = i0 + x, col = lane;
+    // an (s-1)-stage plan on at most D-1 devices covers blocks 1..row iff the last of them is finite
+    VT alast = lane_bcast(r.a, D - 2 - sig);
+    if (DIAG && lane < p) {
+      row = p < 32 ? 64 * c + 64 - p : N;  // rows 64c and 64c+32 have no partner
+      col = lane + 64 - p;
+      alast = lane_bcast(r.b, D - 2 - sig);
+    }
+    const bool act = row >= s - 1 && row < N && 64 * c + col < N && alast != INF && r.rmn <= rl;
     if (__ballot(act) == 0ull) continue;
     any = true;
-    const VT tij = (VT)(it.Tcol[r.col] - r.Ti);
+    if (lane < H) {
+      mine[lane] = r.a;
+      if (DIAG) mine[AS + lane] = r.b;
+    }
+    const VT tij = (DIAG ? __shfl(Tcol, col) : Tcol) - r.Ti;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const VT *from = mine + (DIAG && lane < p ? AS : 0);
     VT w[H];
 #pragma unroll
     for (int g = 0; g < H / E; ++g) {
-      const Values v = *(const Values *)&it.a[r.e * AS + E * g];
+      const Values v = *(const Values *)&from[E * g];
 #pragma unroll
       for (int u = 0; u < E; ++u) w[E * g + u] = v[u];
     }
     row_merge_direct<VT, H>(w, tij, r.rmn, act, k);
     if (act) {
 #pragma unroll
-      for (int t = 0; t < H; ++t) atomicMin(&tile[r.col * LS + t], w[t]);
+      for (int t = 0; t < H; ++t) atomicMin(&tile[col * LS + t], w[t]);
     }
   }
   return any;
@@ -963,11 +952,13 @@ __device__ __forceinline__ void level_merge_body(const ProblemDev &pr, const int
   constexpr bool ROWFOLD = DIRECT || (sizeof(VT) == 8 && HMAX >= 48);  // rows fold into the tile while the row loop runs
   constexpr int NT = 64 * kMergeWaves;
   constexpr int LS = HMAX + 1;
-  __shared__ VT tile[64 * LS];
+  __shared__ __align__(16) VT tile[64 * LS];
   [[maybe_unused]] VT acc[HMAX];
   if constexpr (ROWFOLD) {
-    for (int e = threadIdx.x; e < 64 * LS; e += NT) tile[e] = INF;
-    if constexpr (!DIRECT) __syncthreads();  // (the recomputing form meets at a barrier before its row loop)
+    if constexpr (!DIRECT) {  // (the recomputing form clears the tile behind its first loads)
+      for (int e = threadIdx.x; e < 64 * LS; e += NT) tile[e] = INF;
+      __syncthreads();
+    }
   } else {
 #pragma unroll
     for (int t = 0; t < HMAX; ++t) acc[t] = INF;
@@ -977,11 +968,15 @@ __device__ __forceinline__ void level_merge_body(const ProblemDev &pr, const int
   if constexpr (DIRECT) {
     DirectConsts<HMAX> k;
     direct_consts_init(k);
-    __shared__ __align__(16) ItemRows<VT, HMAX> rows_in;
-#define RANNC_ROWS(K)                                                                            \
-  case K:                                                                                      \
-    if constexpr (8 * K <= HMAX)                                                               \
-      any = merge_rows_direct<VT, 8 * K, LS>(tile, rows_in, pr, s, c, i0, i_hi, lane, wave, k);  \
+    constexpr int AS = direct_row_stride<VT, HMAX>();
+    __shared__ __align__(16) VT rows_in[kMergeWaves * 2 * AS];
+    VT *const mine = rows_in + wave * 2 * AS;
+    const bool diag = i0 >= 64 * c;
+#define RANNC_ROWS(K)                                                                                           \
+  case K:                                                                                                       \
+    if constexpr (8 * K <= HMAX)                                                                                \
+      any = diag ? merge_rows_direct<VT, 8 * K, LS, HMAX, true>(tile, mine, pr, s, c, i0, i_hi, lane, wave, k)  \
+                 : merge_rows_direct<VT, 8 * K, LS, HMAX, false>(tile, mine, pr, s, c, i0, i_hi, lane, wave, k); \
     break;
     switch (ng) {
       RANNC_ROWS(1) RANNC_ROWS(2) RANNC_ROWS(3) RANNC_ROWS(4)
