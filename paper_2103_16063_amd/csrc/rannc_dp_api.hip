@@ -91,8 +91,8 @@ bool problem_sizes(int N, int D, int DP, int S_eff, int bits, bool split, bool p
   const unsigned __int128 V = (unsigned __int128)S_eff * (unsigned)(N + 1) * (unsigned)DP * esz;
   if (cost > ((unsigned __int128)1 << 46) || V > ((unsigned __int128)1 << 46)) return false;
   o->prefix = align_up((size_t)(N + 1) * 8);
-  o->wlo = align_up((size_t)nch * 4);
-  o->runs = align_up((size_t)(rannc::max_runs(nch) + 1) * 4);
+  o->wlo = align_up((size_t)nch * 20);  // the windows, and four words per chunk for the recomputing level kernel
+  o->runs = align_up((size_t)rannc::max_run_words(nch) * 4);
   o->ufit = align_up((size_t)rannc::units_before(nch, N));
   o->misc = align_up(64);  // status word, result pair
   o->rmin = align_up((size_t)rows);
@@ -476,7 +476,9 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
     p.T = (int64_t *)base; base += sz.prefix;
     p.P = (int64_t *)base; base += sz.prefix;
     p.A = (int64_t *)base; base += sz.prefix;
-    p.C = b->cut_bytes ? (int64_t *)base : nullptr; base += sz.prefix;
+    p.C = b->cut_bytes ? (int64_t *)base : nullptr;
+    p.ends = (uint32_t *)base;  // (where the level kernel recomputes the stage times: set below)
+    base += sz.prefix;
     if (split) {
       p.tb = b->time_bwd_ns + b->block_offset[q];
       p.TB = (int64_t *)base; base += sz.prefix;
@@ -509,6 +511,28 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
       }
   }
 
+  const bool scan = h->lim.algo == RANNC_DP_ALGO_SCAN;
+  // split objective: packed-key kernel wherever a cell's winner fits a 64-bit word (all 32-bit
+  // handles, 64-bit ones up to 2^42 - 2 ns); RANNC_DP_ALGO_SCAN and larger time bounds take the
+  // literal one
+  const bool split_fast = split && !scan && packed_of(&h->lim);
+  // what the host knows about the total time of a search of this batch: the handle's bound, or the
+  // outer driver's own sum over the inputs it has just scaled
+  const int64_t total_bound = h->call_total_bound > 0 ? std::min(h->call_total_bound, h->lim.max_total_time_ns)
+                                                      : h->lim.max_total_time_ns;
+  // stage times recomputed inside the level kernel instead of read from their table: where it
+  // applies, on request, or (AUTO) for the classes whose launches are large enough to be bound by
+  // throughput
+  const bool can_recompute = !scan && !split && !b->cut_bytes && rannc::can_recompute_times(h->bits, total_bound);
+  bool recompute_cls[4];
+  for (int k = 0; k < 4; ++k)
+    recompute_cls[k] = can_recompute && (h->lim.algo == RANNC_DP_ALGO_RECOMPUTE ||
+                                         (h->lim.algo == RANNC_DP_ALGO_AUTO &&
+                                          rannc::merge_launch_rows(shape[k]) >= rannc::kRecomputeRowsFrom));
+  for (int q = 0; q < Q; ++q)
+    for (int k = 0; k < 4; ++k)
+      if (probs[q].DP == kClasses[k] && !recompute_cls[k]) probs[q].ends = nullptr;
+
   // ---- descriptors to the device ---------------------------------------------------
   const int slot = h->next_slot;
   h->next_slot = (slot + 1) % kStagingSlots;
@@ -537,24 +561,6 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
   // ---- kernels ---------------------------------------------------------------------------
   ProblemDev *const dp = h->d_probs;
   const ProblemDev *const src = in_place ? (const ProblemDev *)h->staging_dev[slot] : dp;
-  const bool scan = h->lim.algo == RANNC_DP_ALGO_SCAN;
-  // split objective: packed-key kernel wherever a cell's winner fits a 64-bit word (all 32-bit
-  // handles, 64-bit ones up to 2^42 - 2 ns); RANNC_DP_ALGO_SCAN and larger time bounds take the
-  // literal one
-  const bool split_fast = split && !scan && packed_of(&h->lim);
-  // what the host knows about the total time of a search of this batch: the handle's bound, or the
-  // outer driver's own sum over the inputs it has just scaled
-  const int64_t total_bound = h->call_total_bound > 0 ? std::min(h->call_total_bound, h->lim.max_total_time_ns)
-                                                      : h->lim.max_total_time_ns;
-  // stage times recomputed inside the level kernel instead of read from their table: where it
-  // applies, on request, or (AUTO) for the classes whose launches are large enough to be bound by
-  // throughput
-  const bool can_recompute = !scan && !split && !b->cut_bytes && rannc::can_recompute_times(h->bits, total_bound);
-  bool recompute_cls[4];
-  for (int k = 0; k < 4; ++k)
-    recompute_cls[k] = can_recompute && (h->lim.algo == RANNC_DP_ALGO_RECOMPUTE ||
-                                         (h->lim.algo == RANNC_DP_ALGO_AUTO &&
-                                          rannc::merge_launch_rows(shape[k]) >= rannc::kRecomputeRowsFrom));
   bool ok = true;
   const bool timing = h->timing;
   h->ev_valid = false;

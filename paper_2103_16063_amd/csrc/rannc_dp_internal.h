@@ -47,6 +47,14 @@ __host__ __device__ inline int64_t max_runs(int nch) {
   const int64_t small = rows < kSplitSmallRows + nch ? rows : kSplitSmallRows + nch;
   return by4 > small ? by4 : small;
 }
+// words of the list: one per item and the count, or kPassItemWords per item of at least four passes (a
+// chunk has at most 64c + 33)
+constexpr int kPassItemWords = 8;
+__host__ __device__ inline int max_pass_items(int nch) { return 8 * nch * (nch - 1) + 9 * nch; }
+__host__ __device__ inline int64_t max_run_words(int nch) {
+  const int64_t passes = kPassItemWords * (1 + (int64_t)max_pass_items(nch));
+  return passes > max_runs(nch) + 1 ? passes : max_runs(nch) + 1;
+}
 
 // Sorted-merge level kernel: waves per work item; a wave takes 1, 2, 4, ... of the item's rows.  The
 // host sizes the grid for items of 16 rows when the searches of a launch together hold at least
@@ -92,9 +100,13 @@ struct ProblemDev {
   void *cost;
   void *V;
   uint8_t *ufit;               // per unit: 1 if any of its stages fits for some r <= D
+  uint32_t *ends;              // recomputing level kernel (else null): N entries ends[], then N + 1 running sums of
+                               // them (pass_entries; they use the words that C would)
   int32_t *wlo;                // [nch] smallest row i with a stage (i, j in chunk) that fits for some
-                               // r <= D; 0x7fffffff if none
-  int32_t *runs;               // runs[0] = count, then ((rows - 1) << 26 | c << 16 | first row) per work item
+                               // r <= D; 0x7fffffff if none; behind it, with ends, four words per chunk (PassChunk)
+  int32_t *runs;               // runs[0] = count, then ((rows - 1) << 26 | c << 16 | first row) per work item;
+                               // with ends, from word kPassItemWords on, kPassItemWords words per work item: first
+                               // pass, c | (passes - 1) << 16, first and last row << 16 of its first four passes
   int32_t *status;             // RANNC_DP_PROBLEM_*
   int64_t *res;                // res[0] = opt (int64, INT64_MAX if none), res[1] = n_stages
 };

@@ -89,6 +89,70 @@ __device__ __forceinline__ void build_rows(VT tij, VT cj, int rmin, int D, VT RA
   }
 }
 
+// ---------------------------------------------------------------------------------------
+// Passes of the recomputing level kernel.
+//
+// ends[i] is the last block a stage that starts behind block i can take and still fit (for some r <= D;
+// i itself if not even one block fits).  Memory grows with the stage, so the stages (i, j) of row i
+// that fit are exactly j = i+1 .. ends[i], and ends[] never decreases.  The level kernel works on the stages
+// that fit and on nothing else: those of chunk c, row by row from the window's first row on, are numbered
+// through, and a PASS is sixty-four of them in a row, a lane each, whatever rows they come from.  (With a
+// pass per row, two rows to a pass in the diagonal block, 20 % of the lanes idled at 1024 blocks where a
+// stage spans 115 of them, 26 % over the searches of 128 blocks that span 46, half where the last
+// chunk is a third full.)
+//
+// Stages of the chunk in rows w .. i-1, with X = min(64c+64, N) and the first row `full` whose stages reach X:
+//     sum over those rows of min(ends, X) - max(row, 64c)
+// in closed form from the running sums of ends[] (stages_before).
+//
+// Per pass 64 words { row, column in the chunk << 16, smallest r that fits << 22 }, all ones behind the
+// chunk's last stage, then the 64 stages' times at one replica.  They live in the region of the
+// stage-time table, which a search that recomputes the times does not build (a table that is asked for
+// later replaces them, and the next solve writes them again).
+// ---------------------------------------------------------------------------------------
+template <typename VT> constexpr int pass_bytes() { return 64 * (4 + (int)sizeof(VT)); }
+
+__device__ __forceinline__ uint32_t *pass_chunks(const ProblemDev &pr) { return (uint32_t *)pr.wlo + pr.nch; }
+
+// The entries of row i in chunk c, by one wave; fits: the lane's stage fits, from rmin replicas on.
+template <typename VT>
+__device__ __forceinline__ void pass_entries(const ProblemDev &pr, int i, int c, int lane, bool fits, int rmin, VT tij) {
+  const int N = pr.N, b = 64 * c, hi = min(b + 63, N - 1);
+  const int w = pr.wlo[c];
+  if (i < w) return;
+  const uint32_t *const esum = pr.ends + N;
+  const uint32_t *const rec = pass_chunks(pr) + 4 * c;
+  const uint32_t full = rec[0], base = rec[1], start = rec[2], per = rec[3];
+  const uint32_t first = stages_before(esum, N, c, (uint32_t)w, full, (uint32_t)i);
+  const uint32_t all = stages_before(esum, N, c, (uint32_t)w, full, (uint32_t)hi + 1u);
+  char *const passes = (char *)pr.cost + (int64_t)base * pass_bytes<VT>();
+  auto word_at = [&](uint32_t at) { return (uint32_t *)(passes + (int64_t)(at >> 6) * pass_bytes<VT>()) + (at & 63u); };
+  if (fits) {
+    const uint32_t at = first + (uint32_t)(b + lane - max(i, b)), q = at >> 6;
+    *word_at(at) = (uint32_t)i | (uint32_t)lane << 16 | (uint32_t)rmin << 22;
+    ((VT *)(passes + (int64_t)q * pass_bytes<VT>() + 256))[at & 63u] = tij;
+    // the work list: the rows of an item's first passes, one for each wave, and the item itself
+    const bool begins = (at & 63u) == 0u, ends = (at & 63u) == 63u || at == all - 1u;
+    if (begins || ends) {
+      const uint32_t item = q / per, slot = q - item * per;
+      uint32_t *const list = (uint32_t *)pr.runs + kPassItemWords * (1 + start + item);
+      if (begins && slot == 0) {
+        const uint32_t n = min(per, ((all + 63u) >> 6) - q);
+        list[0] = base + q;
+        list[1] = (uint32_t)c | (n - 1u) << 16;
+      }
+      if (slot < (uint32_t)kMergeWaves) {
+        if (begins) ((uint16_t *)(list + 2 + slot))[0] = (uint16_t)i;
+        if (ends) ((uint16_t *)(list + 2 + slot))[1] = (uint16_t)i;
+      }
+    }
+  }
+  if (i == hi) {
+    const uint32_t at = all + (uint32_t)lane;
+    if ((at >> 6) == ((all - 1u) >> 6)) *word_at(at) = ~0u;
+  }
+}
+
 // One unit (row i, chunk c) of the tables, by one wave.  T, P, A, Cc may live in global memory or in
 // LDS; Cc (per-cut send time at one replica, Cc[N] = 0) is null when there is no communication
 // term.  Returns whether any stage of the unit fits.  Row 0's entries are level 1 of V: with
@@ -96,12 +160,14 @@ __device__ __forceinline__ void build_rows(VT tij, VT cj, int rmin, int D, VT RA
 // the value table (a lane's D values are a row of V, so writing them from here would scatter every
 // store instruction over 64 cache lines).  with_times = false: only the fits-in-memory part (rmin,
 // ufit) and level 1 are produced, for searches whose level kernel recomputes the stage times.
-// lds_rmin: the unit's 64 rmin bytes also go there (255 for a lane without a stage).
+// lds_rmin: the unit's 64 rmin bytes also go there (255 for a lane without a stage).  with_passes: the
+// unit's entries of the recomputing level kernel's passes as well.
 template <typename VT, int DP, bool NODIV = false>
 __device__ __forceinline__ bool build_unit(const ProblemDev &pr, const int64_t *T, const int64_t *P,
                                            const int64_t *A, const int64_t *Cc, int i, int c, int lane,
                                            VT *lds_level1, int ls, int row0, const int64_t *TBp = nullptr,
-                                           const bool with_times = true, uint8_t *lds_rmin = nullptr) {
+                                           const bool with_times = true, uint8_t *lds_rmin = nullptr,
+                                           const bool with_passes = false) {
   const int N = pr.N, D = pr.D, nch = pr.nch;
   const int jj = 64 * c + lane;
   const bool valid = (jj >= i) && (jj < N);
@@ -123,6 +189,7 @@ __device__ __forceinline__ bool build_unit(const ProblemDev &pr, const int64_t *
   const bool unit_fits = __ballot(fits) != 0ull;
   const int64_t u = unit_index(nch, i, c);
   if (lane == 0) pr.ufit[u] = (uint8_t)unit_fits;
+  if (with_passes) pass_entries<VT>(pr, i, c, lane, fits, rmin, (VT)Tij);
   if (lds_rmin) lds_rmin[lane] = (uint8_t)(valid ? rmin : 255);  // the caller's copy: every lane, 255 = no stage
   if (!valid) return unit_fits;
   pr.rmin[u * 64 + lane] = (uint8_t)rmin;
@@ -169,7 +236,7 @@ void build_kernel(const ProblemDev *__restrict__ probs, const int parts, const i
   auto one_row = [&](const int i) {
     const bool level1 = i == 0 && (parts & 1);
     (void)build_unit<VT, DP, true>(pr, pr.T, pr.P, pr.A, pr.C, i, c, lane, level1 ? tile : nullptr, DP + 1, 64 * c + 1,
-                                   pr.TB, (parts & 2) != 0);
+                                   pr.TB, (parts & 2) != 0, nullptr, (parts & 1) && pr.ends && pr.S_eff > 1);
     if (level1) {
       // rows j = 64c+1 .. of level 1 are contiguous in V: written with consecutive lanes on
       // consecutive words (columns d > D keep the zeros of the fill)
@@ -221,12 +288,9 @@ void build_kernel(const ProblemDev *__restrict__ probs, const int parts, const i
 // the round is then as full as it can be, and no compute unit is left with one workgroup more
 // than its neighbours.  (For a launch of many rounds, hundreds of searches, the host fixes the item
 // size for all of them: merge_grid_items.)
-// paired (the level kernel that recomputes the stage times): inside the diagonal block of a chunk
-// (rows 64c .. 64c+63, where row 64c+p has work only in the lanes from p on) the list holds the
-// rows p = 0 .. 32 only; the kernel treats row 64c+p as the PAIR of rows 64c+p and 64c+64-p, whose
-// lanes with work add up to exactly one wave.  The rows in front of the block and the listed rows
-// of the block form two segments, and no item crosses from one into the other; the last item of a
-// segment carries the number of rows that are left.
+// paired (the level kernel that recomputes the stage times): the list is of passes instead of rows
+// (pass_entries), an item of at most that many passes of one chunk; workgroup 0 finds ends[], its
+// running sums and every chunk's share of the list, the table builder writes the entries.
 //
 // Bound by latency (a chain of a few memory round trips and barriers): 7.4 us at 96 blocks, 8.3 us at
 // 251 with send times, 12 us at 1024.  With saturating sums, binary searches by a thread per chunk and the
@@ -319,6 +383,162 @@ __device__ void setup_fill(const ProblemDev &pr, int64_t t0, int64_t stride) {
       }
       V[e] = q;
     }
+  }
+}
+
+// The item size, in fours, for items whose number at size 4 (k + 1) is count[k] (see above).
+__device__ __forceinline__ int setup_item_size(const int *count, int most, int max_items, int batch, int slots, bool passes) {
+  int pick = most - 1;
+  for (int k = most - 1; k >= 0; --k)
+    if (count[k] <= max_items) pick = k;
+  if ((long long)count[pick] * batch <= slots) return pick;
+  for (int k = pick + 1; k < most; ++k) {
+    const long long then = (long long)count[k] * batch;
+    if (then <= slots) {
+      if (2 * then >= slots) return k;
+      break;
+    }
+  }
+  // one large search of the recomputing form with many rounds: the largest items that still leave one and a
+  // half rounds, by the passes that are really there (the host, which fixes the size for a launch over
+  // many searches, cannot see the pruning of a single one)
+  if (passes && batch == 1)
+    for (int k = most - 1; k > pick; --k)
+      if (2 * count[k] >= 3 * slots) return k;
+  return pick;
+}
+
+// ends[], its running sums, the windows and every chunk's share of the pass list (see pass_entries), by
+// one workgroup.  E: where this function reads ends (N entries) and the sums (N + 1) back; the workspace
+// gets them as well.  cpass: LDS, 1024 words.  bad: the sums P, A may have wrapped.
+template <typename SP, typename EP>
+__device__ __forceinline__ void setup_passes(const ProblemDev &pr, SP P, SP A, EP E, int *cpass, bool bad, int rows, int max_items,
+                                             int batch, int slots, int most) {
+  constexpr int U = 2;  // consecutive rows of a thread
+  __shared__ uint32_t part[kSetupThreads / 64];
+  __shared__ int count[16];
+  const int N = pr.N, D = pr.D, nch = pr.nch, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const uint64_t M = (uint64_t)pr.M;
+  uint32_t *const ends = pr.ends, *const esum = ends + N;
+  uint32_t carry = 0;
+  for (int base = 0; base < N; base += U * kSetupThreads) {
+    const int i0 = base + U * tid;
+    int lo[U], hi[U];  // the last block known to fit (the empty stage does), the last that may
+    uint64_t Pi[U], Ai[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = min(i0 + u, N - 1);
+      lo[u] = i; hi[u] = bad || i0 + u >= N ? i : N;
+      Pi[u] = P[i]; Ai[u] = A[i];
+    }
+    bool more = true;
+    while (__any(more)) {
+      more = false;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int mid = (lo[u] + hi[u] + 1) >> 1;  // lo itself once they meet
+        if (fits_at(P[mid] - Pi[u], A[mid] - Ai[u], M, D)) lo[u] = mid;
+        else hi[u] = mid - 1;
+        hi[u] = max(hi[u], lo[u]);
+        more = more || lo[u] < hi[u];
+      }
+    }
+    uint32_t sum = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) sum += i0 + u < N ? (uint32_t)lo[u] : 0u;
+    uint32_t run = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t x = __shfl_up(run, o);
+      if (lane >= o) run += x;
+    }
+    if (lane == 63) part[wave] = run;
+    __syncthreads();
+    uint32_t at = carry + run - sum;
+#pragma unroll
+    for (int k = 0; k < kSetupThreads / 64; ++k) {
+      if (k < wave) at += part[k];
+      carry += part[k];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = i0 + u;
+      if (i < N) {
+        ends[i] = (uint32_t)lo[u];
+        esum[i] = at;
+        E[i] = (uint32_t)lo[u];
+        E[N + i] = at;
+        at += (uint32_t)lo[u];
+      }
+    }
+    __syncthreads();
+  }
+  if (tid == 0) { esum[N] = carry; E[2 * N] = carry; }
+  if (tid < 16) count[tid] = 0;
+  __syncthreads();
+  for (int c = tid; c < nch; c += kSetupThreads) {
+    const int b = 64 * c, last = min(b + 63, N - 1);
+    const uint32_t X = (uint32_t)min(b + 64, N);
+    int w = kNoRow, full = 0;
+    uint32_t all = 0;
+    if (E[b] > (uint32_t)b) {  // the first row whose stages reach into the chunk
+      int lo = 0, hi = b;
+      while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (E[mid] > (uint32_t)b) hi = mid;
+        else lo = mid + 1;
+      }
+      w = lo;
+    } else {  // the chunk's first block fits no device by itself: the first later one that does
+      for (int i = b + 1; i <= last; ++i)
+        if (E[i] > (uint32_t)i) { w = i; break; }
+    }
+    if (w != kNoRow) {
+      int lo = w, hi = last + 1;
+      while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (E[mid] >= X) hi = mid;
+        else lo = mid + 1;
+      }
+      full = lo;
+      all = stages_before(E + N, N, c, (uint32_t)w, (uint32_t)full, (uint32_t)last + 1u);
+    }
+    pr.wlo[c] = w;
+    pass_chunks(pr)[4 * c] = (uint32_t)full;
+    cpass[c] = (int)((all + 63u) >> 6);  // nch <= 1024 (N <= 65535)
+  }
+  __syncthreads();
+  if (rows <= 0) {
+    // thread t counts the items of candidate size 4 (t % 16 + 1) over the chunks t / 16, t / 16 + 16, ...
+    const int k = tid % 16, r = 4 * (k + 1);
+    int cnt = 0;
+    for (int c = tid / 16; c < nch; c += kSetupThreads / 16) cnt += (cpass[c] + r - 1) / r;
+    if (cnt) atomicAdd(&count[k], cnt);
+    __syncthreads();
+    rows = 4 * (setup_item_size(count, most, max_items, batch, slots, true) + 1);
+  }
+  // passes and items in front of every chunk; the passes of a chunk dealt evenly over its items
+  if (wave == 0) {
+    uint32_t passes = 0, items = 0;
+    for (int c0 = 0; c0 < nch; c0 += 64) {
+      const int c = c0 + lane;
+      const uint32_t np = c < nch ? (uint32_t)cpass[c] : 0u, ni = (np + (uint32_t)rows - 1u) / (uint32_t)rows;
+      uint32_t p = np, t = ni;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t x = __shfl_up(p, o), y = __shfl_up(t, o);
+        if (lane >= o) { p += x; t += y; }
+      }
+      if (c < nch) {
+        uint32_t *const rec = pass_chunks(pr) + 4 * c;
+        rec[1] = passes + p - np;
+        rec[2] = items + t - ni;
+        rec[3] = ni ? (np + ni - 1u) / ni : 1u;
+      }
+      passes += (uint32_t)__shfl(p, 63);
+      items += (uint32_t)__shfl(t, 63);
+    }
+    if (lane == 0) pr.runs[0] = (int32_t)items;
   }
 }
 
@@ -431,6 +651,14 @@ __global__ __launch_bounds__(kSetupThreads) void setup_kernel(const ProblemDev *
   // ---- windows ----
   __shared__ int start[1025];  // nch <= 1024 (N <= 65535)
   __shared__ RunSegments seg[1024];  // every chunk's segments
+  if (paired) {
+    const bool bad = flags != 0;  // (sums that may have wrapped: no stage fits)
+    static_assert(sizeof(seg) >= 4 * (2 * kSetupLdsN + 1), "ends and their sums");
+    if (in_lds) setup_passes(pr, (const uint64_t *)sP, (const uint64_t *)sA, (uint32_t *)seg, start, bad, rows, max_items, batch, slots, max_rows / 4);
+    else setup_passes(pr, (const uint64_t RANNC_GLOBAL *)out[1], (const uint64_t RANNC_GLOBAL *)out[2], pr.ends, start, bad, rows,
+                      max_items, batch, slots, max_rows / 4);
+    return;
+  }
   constexpr int NC = 16;  // candidate item sizes 4, 8, ..., 64 rows, up to max_rows
   const int most = max_rows / 4;
   __shared__ int count[NC];
@@ -465,7 +693,7 @@ __global__ __launch_bounds__(kSetupThreads) void setup_kernel(const ProblemDev *
       }
       if (c < nch && sub == 0) {
         pr.wlo[c] = lo;
-        seg[c] = run_segments(N, c, lo, paired != 0);
+        seg[c] = run_segments(N, c, lo, false);
       }
     }
   };
@@ -489,28 +717,7 @@ __global__ __launch_bounds__(kSetupThreads) void setup_kernel(const ProblemDev *
       if (cnt) atomicAdd(&count[k], cnt);
     }
     __syncthreads();
-    {
-      int pick = most - 1;
-      for (int k = most - 1; k >= 0; --k)
-        if (count[k] <= max_items) pick = k;
-      if ((long long)count[pick] * batch > slots) {
-        bool one_round = false;
-        for (int k = pick + 1; k < most; ++k) {
-          const long long then = (long long)count[k] * batch;
-          if (then <= slots) {
-            if (2 * then >= slots) { pick = k; one_round = true; }
-            break;
-          }
-        }
-        // one large search of the recomputing form with many rounds: the largest items that still
-        // leave one and a half rounds, by the rows that are really there (the host, which fixes the size for
-        // a launch over many searches, cannot see the pruning of a single one)
-        if (!one_round && paired && batch == 1)
-          for (int k = most - 1; k > pick; --k)
-            if (2 * count[k] >= 3 * slots) { pick = k; break; }
-      }
-      rows = 4 * (pick + 1);
-    }
+    rows = 4 * (setup_item_size(count, most, max_items, batch, slots, false) + 1);
   }
   // per chunk: items of the two segments, and their rows dealt evenly over them (33 rows in items
   // of up to 16: three items of 11, not 16 + 16 + 1); seg[c] is reused for {items0, per0, lo1, per1}
@@ -766,52 +973,51 @@ __device__ __forceinline__ void row_merge_direct(VT (&x)[H], VT tij, int rmn, bo
   bitonic_sort(x);
 }
 
-// The rows of one work item of the recomputing level kernel.  A wave fetches what a row needs (its row of
-// V[s-1], a value per lane; the rmin bytes; the prefix sums) while it works on the row before, puts the
-// row into LDS when its turn comes and reads it back four values at a time; the waves of the item share
-// nothing but the tile, so a row loop starts one round of loads after the item is known.  (With everything
-// an item reads copied to LDS by the whole workgroup first, a launch without any row to work on took 5.5
-// us at 1024 blocks, where an empty one takes 1.8, and 15 us over 512 searches of 128 blocks.)
-// Every row's merge goes straight into the item's LDS tile: a running minimum in registers costs as many
-// instructions per row as the LDS does, and as many registers as the merge itself.
+// The passes of one work item of the recomputing level kernel (see pass_entries), wave w the passes w, w+4, ...
+// A wave fetches what a pass needs while it works on the one before: the entries two passes ahead, the few
+// rows of V[s-1] they name one pass ahead, a value per lane.  When its turn comes the rows are put into LDS
+// and every lane reads its own back, four values at a time.  A pass with more rows than that (the end of a
+// diagonal block, stages of few blocks) has each lane read its row from memory.  The waves of the item
+// share nothing but the tile, so that the loop starts one round of loads after the item is known.  (With
+// everything an item reads copied to LDS by the whole workgroup first, a launch without any row to work
+// on took 5.5 us at 1024 blocks, where an empty one takes 1.8, and 15 us over 512 searches of 128 blocks.)
+// Every pass's merge goes straight into the item's LDS tile: a running minimum in registers costs as many
+// instructions per pass as the LDS does, and as many registers as the merge itself.
 // H: width of the merge (multiple of eight, at least rl); LS: row stride of the tile, whose entry t is
-// output t of the merge.  mine: two rows of this wave.  DIAG: the diagonal block, whose listed row 64c+p
-// stands for the pair of rows 64c+p (lanes p.. with their own columns) and 64c+64-p (the p columns from 64-p
-// on, on the lanes below p): one pass of a full wave instead of two half-empty ones.
-// Returns whether any row of this wave had work.
-template <typename VT, int HMAX> constexpr int direct_row_stride() { return HMAX + 16 / (int)sizeof(VT); }
+// output t of the merge.  near: first and last row of this wave's first pass.  mine: kNearWords values.
+// Returns whether any pass of this wave had work.
+constexpr int kNearWords = 4 * (64 + 4);
 
-template <typename VT, int H, int LS, int HMAX, bool DIAG>
-__device__ __forceinline__ bool merge_rows_direct(VT *tile, VT *mine, const ProblemDev &pr, const int s, const int c,
-                                                  const int i0, const int i_hi, const int lane, const int wave,
-                                                  const DirectConsts<HMAX> &k) {
+template <typename VT, int H, int LS, int HMAX>
+__device__ __forceinline__ bool merge_passes(VT *tile, VT *mine, const VT RANNC_GLOBAL *__restrict__ V, const char RANNC_GLOBAL *__restrict__ passes,
+                                             const int N, const int D, const int DP, const int s, const int n,
+                                             const uint32_t near, const int lane, const int wave, const DirectConsts<HMAX> &k) {
   constexpr VT INF = Lim<VT>::inf;
   constexpr int E = 16 / (int)sizeof(VT);  // values per 16 bytes
-  constexpr int AS = direct_row_stride<VT, HMAX>(), NT = 64 * kMergeWaves;
-  constexpr int TW = 8 / (int)sizeof(VT);  // of a prefix sum only the low bits of a value are looked at
+  constexpr int AS = H + E, NT = 64 * kMergeWaves;  // row stride in LDS: 16-byte aligned, rows on different banks
+  constexpr int HP = H <= 8 ? 8 : H <= 16 ? 16 : H <= 32 ? 32 : 64, PER = 64 / HP;  // rows a load covers
+  constexpr int LOADS = HP == 64 ? 4 : 2, NEAR = LOADS * PER;
+  static_assert(NEAR * AS <= kNearWords, "the near rows fit their LDS");
   typedef VT Values __attribute__((ext_vector_type(E)));
-  const int N = pr.N, D = pr.D, DP = pr.DP, nch = pr.nch;
-  const int sig = merge_shift(s, DP, H);
-  const int64_t lvl = (int64_t)(N + 1) * DP;
-  const VT RANNC_GLOBAL *__restrict__ Vprev = gptr((const VT *)pr.V) + (int64_t)(s - 2) * lvl + sig + min(lane, H - 1);
-  const uint8_t RANNC_GLOBAL *__restrict__ rmin = gptr((const uint8_t *)pr.rmin);
-  const VT RANNC_GLOBAL *__restrict__ T = gptr((const VT *)pr.T);
-  const int rl = D - s + 1;
-  const int n = i_hi - i0 + 1, p0 = i0 - 64 * c;
-  struct Row { VT a, b, Ti; int rmn; };
-  auto partner = [&](int p) { return min(min(64 * c + 64 - p, 64 * c + 63), N - 1); };  // (p = 0 has none; rows beyond the chain have no work)
-  auto fetch = [&](int x) -> Row {
-    Row r;
-    const int xc = min(x, n - 1), p = p0 + xc;
-    r.a = Vprev[(int64_t)(i0 + xc) * DP];
-    r.b = DIAG ? Vprev[(int64_t)partner(p) * DP] : (VT)0;
-    const int row = DIAG && lane < p ? partner(p) : i0 + xc, col = DIAG && lane < p ? lane + 64 - p : lane;
-    r.rmn = rmin[unit_index(nch, row, c) * 64 + col];
-    r.Ti = T[row * TW];
+  typedef VT ValuesAny __attribute__((ext_vector_type(E), aligned(sizeof(VT))));  // (a[sig] is any value of the row)
+  const int sig = merge_shift(s, DP, H), rl = D - s + 1, top = D - 2 - sig;
+  const VT RANNC_GLOBAL *__restrict__ Vprev = V + (int64_t)(s - 2) * (int64_t)(N + 1) * DP + sig;
+  const int sub = lane / HP, t_of = lane % HP;
+  struct Entry { uint32_t word; VT tij; };
+  struct Rows { int lo, hi; VT a[LOADS]; };
+  auto fetch = [&](int x) -> Entry {
+    const char RANNC_GLOBAL *p = passes + min(x, n - 1) * pass_bytes<VT>();
+    return {((const uint32_t RANNC_GLOBAL *)p)[lane], ((const VT RANNC_GLOBAL *)(p + 256))[lane]};
+  };
+  auto fetch_rows = [&](int lo, int hi) -> Rows {
+    Rows r;
+    r.lo = lo; r.hi = hi;
+#pragma unroll
+    for (int q = 0; q < LOADS; ++q) r.a[q] = Vprev[(int64_t)min(lo + q * PER + sub, hi) * DP + min(t_of, H - 1)];
     return r;
   };
-  Row next = fetch(wave);
-  const VT Tcol = T[min(64 * c + lane + 1, N) * TW];  // (clamped: columns beyond N have no work)
+  Entry next = fetch(wave), after = fetch(wave + kMergeWaves);
+  Rows next_rows = fetch_rows((int)(near & 0xffffu), (int)(near >> 16));
   typedef uint32_t Quad __attribute__((ext_vector_type(4)));
   static_assert(64 * LS * sizeof(VT) % 16 == 0, "the tile is cleared 16 bytes at a time");
   constexpr uint32_t inf_lo = (uint32_t)INF, inf_hi = (uint32_t)((uint64_t)INF >> (sizeof(VT) == 8 ? 32 : 0));
@@ -820,36 +1026,48 @@ __device__ __forceinline__ bool merge_rows_direct(VT *tile, VT *mine, const Prob
   bool any = false;
 #pragma unroll 1
   for (int x = wave; x < n; x += kMergeWaves) {
-    const Row r = next;
-    next = fetch(x + kMergeWaves);
-    const int p = p0 + x;
-    int row = i0 + x, col = lane;
-    // an (s-1)-stage plan on at most D-1 devices covers blocks 1..row iff the last of them is finite
-    VT alast = lane_bcast(r.a, D - 2 - sig);
-    if (DIAG && lane < p) {
-      row = p < 32 ? 64 * c + 64 - p : N;  // rows 64c and 64c+32 have no partner
-      col = lane + 64 - p;
-      alast = lane_bcast(r.b, D - 2 - sig);
+    const Entry e = next;
+    const Rows r = next_rows;
+    next = after;
+    after = fetch(x + 2 * kMergeWaves);
+    {
+      const int last = 63 - __clzll((long long)__ballot(next.word != ~0u));  // (lane 0 has a stage)
+      next_rows = fetch_rows((int)(lane_bcast(next.word, 0) & 0xffffu), (int)(lane_bcast(next.word, last) & 0xffffu));
     }
-    const bool act = row >= s - 1 && row < N && 64 * c + col < N && alast != INF && r.rmn <= rl;
+    const int row = min((int)(e.word & 0xffffu), r.hi), col = (int)(e.word >> 16) & 63, rmn = (int)(e.word >> 22);
+    VT alast, w[H];
+    if (r.hi - r.lo < NEAR) {
+      if (t_of < H) {
+#pragma unroll
+        for (int q = 0; q < LOADS; ++q) mine[(q * PER + sub) * AS + t_of] = r.a[q];
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      const VT *from = mine + (row - r.lo) * AS;
+      alast = from[top];
+#pragma unroll
+      for (int g = 0; g < H / E; ++g) {
+        const Values v = *(const Values *)&from[E * g];
+#pragma unroll
+        for (int u = 0; u < E; ++u) w[E * g + u] = v[u];
+      }
+    } else {
+      const VT RANNC_GLOBAL *from = Vprev + (int64_t)row * DP;
+      alast = from[top];
+#pragma unroll
+      for (int g = 0; g < H / E; ++g) {
+        const ValuesAny v = *(const ValuesAny RANNC_GLOBAL *)(from + E * g);
+#pragma unroll
+        for (int u = 0; u < E; ++u) w[E * g + u] = v[u];
+      }
+      __builtin_amdgcn_s_waitcnt(0x0f70);  // (vmcnt(0) here, or the compiler waits where the two branches meet)
+    }
+    // an (s-1)-stage plan on at most D-1 devices covers blocks 1..row iff the last of them is finite
+    // (behind the chunk's last stage rmn is above any rl)
+    const bool act = rmn <= rl && row >= s - 1 && alast != INF;
     if (__ballot(act) == 0ull) continue;
     any = true;
-    if (lane < H) {
-      mine[lane] = r.a;
-      if (DIAG) mine[AS + lane] = r.b;
-    }
-    const VT tij = (DIAG ? __shfl(Tcol, col) : Tcol) - r.Ti;
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    const VT *from = mine + (DIAG && lane < p ? AS : 0);
-    VT w[H];
-#pragma unroll
-    for (int g = 0; g < H / E; ++g) {
-      const Values v = *(const Values *)&from[E * g];
-#pragma unroll
-      for (int u = 0; u < E; ++u) w[E * g + u] = v[u];
-    }
-    row_merge_direct<VT, H>(w, tij, r.rmn, act, k);
+    row_merge_direct<VT, H>(w, e.tij, rmn, act, k);
     if (act) {
 #pragma unroll
       for (int t = 0; t < H; ++t) atomicMin(&tile[col * LS + t], w[t]);
@@ -932,21 +1150,42 @@ __device__ __forceinline__ bool merge_rows(VT (&acc)[HMAX], VT *tile_lane, const
 // the launch: narrow levels run with more waves per SIMD); each search takes the width it needs.
 template <typename VT, int HMAX, bool DIRECT>
 __device__ __forceinline__ void level_merge_body(const ProblemDev &pr, const int s, const int item) {
-  if (s > pr.S_eff) return;
-  const int N = pr.N, D = pr.D, DP = pr.DP;
+  // What the workgroup needs of the descriptor, and then of the list, is asked for at once and waited for
+  // once: left alone, the compiler reads each field where it is first used, behind the exits in front of
+  // it, and a launch starts with a chain of six scalar reads.
+  const int S_eff = pr.S_eff, N = pr.N, D = pr.D, DP = pr.DP, nch = pr.nch;
   const int32_t RANNC_GLOBAL *__restrict__ runs = gptr((const int32_t *)pr.runs);
-  if (item >= runs[0]) return;
-  const unsigned desc = (unsigned)runs[1 + item];
-  const int c = (int)((desc >> 16) & 0x3ffu), i0 = (int)(desc & 0xffffu), rows = (int)(desc >> 26) + 1;
-  if (64 * c + 64 < s) return;  // no column j >= s in this chunk
-  const int i_hi = min(min(i0 + rows - 1, 64 * c + 63), N - 1);
-  // (an item of the diagonal block of the recomputing kernel also stands for the partner rows
-  // 64c+64-p of its rows 64c+p, which lie above them)
-  if (i_hi < s - 1 && !(DIRECT && i0 >= 64 * c)) return;
-  const int lane = threadIdx.x & 63;
+  VT RANNC_GLOBAL *const V = gptr((VT *)pr.V);
+  const char RANNC_GLOBAL *__restrict__ passes = gptr((const char *)pr.cost);
+  asm volatile("" :: "s"(S_eff), "s"(N), "s"(D), "s"(DP), "s"(nch), "s"(runs), "s"(V), "s"(passes));
+  if (s > S_eff) return;
+  int c, i0 = 0, i_hi = 0, n = 0;
+  [[maybe_unused]] uint32_t near = 0;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int count = runs[0];
+  if constexpr (DIRECT) {
+    typedef uint32_t Item __attribute__((ext_vector_type(8)));
+    const Item it = *(const Item RANNC_GLOBAL *)((const uint32_t RANNC_GLOBAL *)runs +
+                                                 kPassItemWords * (1 + min(item, max_pass_items(nch) - 1)));  // (a place that every list has)
+    asm volatile("" :: "s"(count), "s"(it));
+    if (item >= count) return;
+    c = (int)(it[1] & 0xffffu);
+    n = (int)(it[1] >> 16) + 1;
+    near = wave == 0 || n < 2 ? it[2] : wave == 1 || n < 3 ? it[3] : wave == 2 || n < 4 ? it[4] : it[5];
+    passes += (int64_t)it[0] * pass_bytes<VT>();
+  } else {
+    const unsigned desc = ((const uint32_t RANNC_GLOBAL *)runs)[1 + min(item, 8 * nch * (nch + 1) - 1)];
+    asm volatile("" :: "s"(count), "s"(desc));
+    if (item >= count) return;
+    c = (int)((desc >> 16) & 0x3ffu);
+    i0 = (int)(desc & 0xffffu);
+    i_hi = min(min(i0 + (int)(desc >> 26), 64 * c + 63), N - 1);
+    if (i_hi < s - 1) return;
+  }
+  if (64 * c + 64 < s) return;  // no column j >= s in this chunk
+  const int lane = threadIdx.x & 63;
   constexpr VT INF = Lim<VT>::inf;
-  VT RANNC_GLOBAL *Vcur = gptr((VT *)pr.V) + (int64_t)(s - 1) * (int64_t)(N + 1) * DP;
+  VT RANNC_GLOBAL *Vcur = V + (int64_t)(s - 1) * (int64_t)(N + 1) * DP;
 
   // acc[t] = running minimum over this wave's rows of the sorted merge
   constexpr bool ROWFOLD = DIRECT || (sizeof(VT) == 8 && HMAX >= 48);  // rows fold into the tile while the row loop runs
@@ -968,15 +1207,12 @@ __device__ __forceinline__ void level_merge_body(const ProblemDev &pr, const int
   if constexpr (DIRECT) {
     DirectConsts<HMAX> k;
     direct_consts_init(k);
-    constexpr int AS = direct_row_stride<VT, HMAX>();
-    __shared__ __align__(16) VT rows_in[kMergeWaves * 2 * AS];
-    VT *const mine = rows_in + wave * 2 * AS;
-    const bool diag = i0 >= 64 * c;
-#define RANNC_ROWS(K)                                                                                           \
-  case K:                                                                                                       \
-    if constexpr (8 * K <= HMAX)                                                                                \
-      any = diag ? merge_rows_direct<VT, 8 * K, LS, HMAX, true>(tile, mine, pr, s, c, i0, i_hi, lane, wave, k)  \
-                 : merge_rows_direct<VT, 8 * K, LS, HMAX, false>(tile, mine, pr, s, c, i0, i_hi, lane, wave, k); \
+    __shared__ __align__(16) VT rows_in[kMergeWaves * kNearWords];
+    VT *const mine = rows_in + wave * kNearWords;
+#define RANNC_ROWS(K)                                                                          \
+  case K:                                                                                      \
+    if constexpr (8 * K <= HMAX)                                                               \
+      any = merge_passes<VT, 8 * K, LS, HMAX>(tile, mine, V, passes, N, D, DP, s, n, near, lane, wave, k); \
     break;
     switch (ng) {
       RANNC_ROWS(1) RANNC_ROWS(2) RANNC_ROWS(3) RANNC_ROWS(4)

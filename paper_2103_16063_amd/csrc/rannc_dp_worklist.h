@@ -41,6 +41,21 @@ __host__ __device__ inline int items_of_pairs(const RunSegments &g, int rows, in
   return (g.n1 + most - 1) / most;
 }
 
+// What the recomputing form's list knows of a chunk (rannc_dp_kernels.hip, pass_entries): its first row whose
+// stages reach the chunk's end, the passes and the items in front of it, and the passes of an item.
+struct PassChunk { uint32_t full, base, start, per; };
+
+// Stages that fit in rows w .. i-1 of chunk c, for i up to the chunk's last row + 1; w: the first row with one,
+// full: the first row from w on whose stages reach the chunk's end.  esum[i] is the sum of ends[0 .. i-1]
+// (below 2^32: N <= 65535; the differences are taken modulo 2^32).
+template <typename EP>
+__host__ __device__ inline uint32_t stages_before(EP esum, int N, int c, uint32_t w, uint32_t full, uint32_t i) {
+  const uint32_t b = 64u * (uint32_t)c, X = b + 64u < (uint32_t)N ? b + 64u : (uint32_t)N;
+  const uint32_t up = b > w ? b : w, m = up < i ? up : i;  // rows w .. m-1 begin at b, the others at themselves
+  const uint32_t starts = (m - w) * b + (i * (i - 1u)) / 2u - (m * (m - 1u)) / 2u;
+  return esum[i < full ? i : full] - esum[w] + (i > full ? (i - full) * X : 0u) - starts;
+}
+
 // rows of the searches of a launch if nothing is pruned (every chunk c holds rows 0 .. 64c+63)
 inline int64_t merge_launch_rows(const LaunchShape &sh) {
   int64_t all_rows = 0;
