@@ -696,11 +696,19 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
     else
       merge_items[k] = rannc::merge_grid_items(sh, rannc::merge_rows_per_item(h->tune_spw), slots, recompute_cls[k],
                                                max_rows, &rows_for_list);
-    ok = rannc::launch_setup(src + cls_start[k], cp, sh.nprob, rows_for_list, merge_items[k], slots, recompute_cls[k],
-                             max_rows, sh.nprob == 1 ? &probs[cls_start[k]] : nullptr, st) == hipSuccess;
-    ok = ok && staging_read();
-    ok = ok && rannc::launch_build(cp, sh, h->bits, kClasses[k], recompute_cls[k] || split_fast ? 1 : 3, st) == hipSuccess;
-    if (split) ok = ok && rannc::launch_split_level1(cp, sh, h->bits, st) == hipSuccess;
+    const ProblemDev *host_one = sh.nprob == 1 ? &probs[cls_start[k]] : nullptr;
+    const int parts = recompute_cls[k] || split_fast ? 1 : 3;
+    if (rannc::can_prepare(sh)) {
+      ok = rannc::launch_prepare(src + cls_start[k], cp, sh, h->bits, kClasses[k], parts, rows_for_list, merge_items[k], slots,
+                                 recompute_cls[k], max_rows, split, b->cut_bytes != nullptr, host_one, st) == hipSuccess;
+      ok = ok && staging_read();
+    } else {
+      ok = rannc::launch_setup(src + cls_start[k], cp, sh.nprob, rows_for_list, merge_items[k], slots, recompute_cls[k],
+                               max_rows, host_one, st) == hipSuccess;
+      ok = ok && staging_read();
+      ok = ok && rannc::launch_build(cp, sh, h->bits, kClasses[k], parts, st) == hipSuccess;
+      if (split) ok = ok && rannc::launch_split_level1(cp, sh, h->bits, st) == hipSuccess;
+    }
   }
   if (timing) ok = ok && hipEventRecord(h->ev[1], st) == hipSuccess;
   int max_levels = 0;

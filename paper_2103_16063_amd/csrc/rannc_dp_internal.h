@@ -154,6 +154,12 @@ hipError_t launch_build(const ProblemDev *probs, const LaunchShape &sh, int bits
 // host memory (passed by value instead), or null
 hipError_t launch_setup(const ProblemDev *src, ProblemDev *probs, int Q, int rows_per_item, int max_items, int slots, bool paired,
                         int max_rows, const ProblemDev *host_one, hipStream_t st);
+// launch_setup and launch_build (parts 1 or 3), and with the split objective launch_split_level1, as one launch
+// (where can_prepare says so)
+bool can_prepare(const LaunchShape &sh);
+hipError_t launch_prepare(const ProblemDev *src, ProblemDev *probs, const LaunchShape &sh, int bits, int DP, int parts,
+                          int rows_per_item, int max_items, int slots, bool paired, int max_rows, bool split, bool comm,
+                          const ProblemDev *host_one, hipStream_t st);
 int merge_rows_per_item(int rows_per_wave);
 // recompute: the level kernel computes the stage times from the prefix sums instead of reading
 // their table (where can_recompute_times says so)

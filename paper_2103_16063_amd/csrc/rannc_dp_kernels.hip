@@ -115,14 +115,13 @@ template <typename VT> constexpr int pass_bytes() { return 64 * (4 + (int)sizeof
 __device__ __forceinline__ uint32_t *pass_chunks(const ProblemDev &pr) { return (uint32_t *)pr.wlo + pr.nch; }
 
 // The entries of row i in chunk c, by one wave; fits: the lane's stage fits, from rmin replicas on.
-template <typename VT>
-__device__ __forceinline__ void pass_entries(const ProblemDev &pr, int i, int c, int lane, bool fits, int rmin, VT tij) {
+// w, rec, esum: the chunk's window, its share of the list and the running sums of ends[].
+template <typename VT, typename EP>
+__device__ __forceinline__ void pass_entries(const ProblemDev &pr, int i, int c, int lane, bool fits, int rmin, VT tij, int w,
+                                             const PassChunk &rec, EP esum) {
   const int N = pr.N, b = 64 * c, hi = min(b + 63, N - 1);
-  const int w = pr.wlo[c];
   if (i < w) return;
-  const uint32_t *const esum = pr.ends + N;
-  const uint32_t *const rec = pass_chunks(pr) + 4 * c;
-  const uint32_t full = rec[0], base = rec[1], start = rec[2], per = rec[3];
+  const uint32_t full = rec.full, base = rec.base, start = rec.start, per = rec.per;
   const uint32_t first = stages_before(esum, N, c, (uint32_t)w, full, (uint32_t)i);
   const uint32_t all = stages_before(esum, N, c, (uint32_t)w, full, (uint32_t)hi + 1u);
   char *const passes = (char *)pr.cost + (int64_t)base * pass_bytes<VT>();
@@ -160,14 +159,15 @@ __device__ __forceinline__ void pass_entries(const ProblemDev &pr, int i, int c,
 // the value table (a lane's D values are a row of V, so writing them from here would scatter every
 // store instruction over 64 cache lines).  with_times = false: only the fits-in-memory part (rmin,
 // ufit) and level 1 are produced, for searches whose level kernel recomputes the stage times.
-// lds_rmin: the unit's 64 rmin bytes also go there (255 for a lane without a stage).  with_passes: the
-// unit's entries of the recomputing level kernel's passes as well.
+// lds_rmin: the unit's 64 rmin bytes also go there (255 for a lane without a stage).  stages: what
+// pass_entries wants to know of the lane's stage.
+template <typename VT> struct UnitStages { bool fits; int rmin; VT tij; };
 template <typename VT, int DP, bool NODIV = false>
 __device__ __forceinline__ bool build_unit(const ProblemDev &pr, const int64_t *T, const int64_t *P,
                                            const int64_t *A, const int64_t *Cc, int i, int c, int lane,
                                            VT *lds_level1, int ls, int row0, const int64_t *TBp = nullptr,
                                            const bool with_times = true, uint8_t *lds_rmin = nullptr,
-                                           const bool with_passes = false) {
+                                           UnitStages<VT> *stages = nullptr) {
   const int N = pr.N, D = pr.D, nch = pr.nch;
   const int jj = 64 * c + lane;
   const bool valid = (jj >= i) && (jj < N);
@@ -189,7 +189,7 @@ __device__ __forceinline__ bool build_unit(const ProblemDev &pr, const int64_t *
   const bool unit_fits = __ballot(fits) != 0ull;
   const int64_t u = unit_index(nch, i, c);
   if (lane == 0) pr.ufit[u] = (uint8_t)unit_fits;
-  if (with_passes) pass_entries<VT>(pr, i, c, lane, fits, rmin, (VT)Tij);
+  if (stages) *stages = {fits, rmin, (VT)Tij};
   if (lds_rmin) lds_rmin[lane] = (uint8_t)(valid ? rmin : 255);  // the caller's copy: every lane, 255 = no stage
   if (!valid) return unit_fits;
   pr.rmin[u * 64 + lane] = (uint8_t)rmin;
@@ -235,8 +235,13 @@ void build_kernel(const ProblemDev *__restrict__ probs, const int parts, const i
   if (c >= pr.nch) return;
   auto one_row = [&](const int i) {
     const bool level1 = i == 0 && (parts & 1);
+    UnitStages<VT> st;
     (void)build_unit<VT, DP, true>(pr, pr.T, pr.P, pr.A, pr.C, i, c, lane, level1 ? tile : nullptr, DP + 1, 64 * c + 1,
-                                   pr.TB, (parts & 2) != 0, nullptr, (parts & 1) && pr.ends && pr.S_eff > 1);
+                                   pr.TB, (parts & 2) != 0, nullptr, &st);
+    if ((parts & 1) && pr.ends && pr.S_eff > 1) {
+      const uint32_t *const rec = pass_chunks(pr) + 4 * c;
+      pass_entries<VT>(pr, i, c, lane, st.fits, st.rmin, st.tij, pr.wlo[c], PassChunk{rec[0], rec[1], rec[2], rec[3]}, pr.ends + pr.N);
+    }
     if (level1) {
       // rows j = 64c+1 .. of level 1 are contiguous in V: written with consecutive lanes on
       // consecutive words (columns d > D keep the zeros of the fill)
@@ -361,8 +366,8 @@ template <int NW> __device__ __forceinline__ void setup_scan(uint64_t (&v)[NW], 
       for (int w = 0; w < NW; ++w) { v[w] += part[k][w]; high |= (uint32_t)(v[w] >> 32); }
 }
 
-__device__ void setup_fill(const ProblemDev &pr, int64_t t0, int64_t stride) {
-  // every V entry "no plan" (padding columns d > D hold 0 so that padded rows stay sorted)
+__device__ void setup_fill(const ProblemDev &pr, int levels_done, int64_t t0, int64_t stride) {
+  // every V entry behind the first levels_done levels "no plan" (padding columns d > D hold 0 so that padded rows stay sorted)
   typedef uint32_t Quad __attribute__((ext_vector_type(4)));
   if (pr.keys) {  // packed winners of the split level kernel: "none"
     const int64_t nk = (int64_t)(pr.N + 1) * pr.DP;
@@ -373,7 +378,7 @@ __device__ void setup_fill(const ProblemDev &pr, int64_t t0, int64_t stride) {
   const int64_t quads = (int64_t)pr.S_eff * (pr.N + 1) * words / 4;
   for (int w = 0; w < (pr.VF ? 3 : 1); ++w) {
     Quad RANNC_GLOBAL *V = (Quad RANNC_GLOBAL *)gptr((uint32_t *)tabs[w]);
-    for (int64_t e = t0; e < quads; e += stride) {
+    for (int64_t e = t0 + levels_done * ((int64_t)(pr.N + 1) * words / 4); e < quads; e += stride) {
       const int at = (int)((4 * e) & (words - 1));
       Quad q;
 #pragma unroll
@@ -549,7 +554,7 @@ __global__ __launch_bounds__(kSetupThreads) void setup_kernel(const ProblemDev *
   const ProblemDev pr = fetch_problem(src + blockIdx.y, probs + blockIdx.y, blockIdx.x == 0, desc, one, use_one);
   const int N = pr.N, tid = threadIdx.x;
   if (blockIdx.x > 0) {
-    setup_fill(pr, (int64_t)(blockIdx.x - 1) * kSetupThreads + tid, (int64_t)(gridDim.x - 1) * kSetupThreads);
+    setup_fill(pr, 0, (int64_t)(blockIdx.x - 1) * kSetupThreads + tid, (int64_t)(gridDim.x - 1) * kSetupThreads);
     return;
   }
   // Entries per thread and tile.  Two keep the kernel, and with it the workgroups that fill V, at four
@@ -757,6 +762,336 @@ __global__ __launch_bounds__(kSetupThreads) void setup_kernel(const ProblemDev *
     const int left = k < items0 ? n0_of[c] - k * per0 : n1_of[c] - (k - items0) * per1;
     const int take = max(min(k < items0 ? per0 : per1, left), 1);  // (never below one row: the word stays well-formed)
     runs[1 + e] = ((take - 1) << 26) | (c << 16) | first;
+  }
+}
+
+// ---------------------------------------------------------------------------------------
+// setup_kernel and build_kernel as ONE launch, for searches of up to kSetupLdsN blocks (and, with the split
+// objective, its level 1): the first `groups` workgroups of a search each form the prefix sums, the ends
+// and the chunks' shares of the pass list for themselves, in LDS, and then build their share of the tables;
+// the first of them also writes what later launches read.  The other workgroups fill V.  Nothing is
+// exchanged between workgroups.  Bound by latency: one round of reads, the sums, ten steps of the search
+// for the ends, a few barriers, the tables.  The two launches took 7 + 5 us at 96 blocks, 8 + 7 at 251 and 14 +
+// 28 at 1024 (where the second one reads the sums back from memory).
+// ---------------------------------------------------------------------------------------
+constexpr int kPrepareChunks = kSetupLdsN / 64;
+struct PrepareIn { int groups, parts, rows, max_items, batch, slots, paired, max_rows; };
+
+// Inclusive prefix sums of one array by one wave, PER (odd: no bank conflicts) consecutive entries per
+// lane, into s[1 .. N]; flags and high as in setup_kernel.
+template <int PER>
+__device__ __forceinline__ void prepare_sums(const int64_t RANNC_GLOBAL *in, int64_t *s, int N, int &flags, uint32_t &high) {
+  const int lane = threadIdx.x & 63, i0 = lane * PER;
+  uint64_t v[PER], sum = 0;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) v[k] = (uint64_t)in[min(i0 + k, N - 1)];
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    uint64_t x = i0 + k < N ? v[k] : 0;
+    if ((int64_t)x < 0) { flags |= 1; x = 0; }
+    if (x >= kSumLimit) { flags |= 2; x = 0; }
+    sum += x;
+    v[k] = sum;
+    high |= (uint32_t)(sum >> 32);
+  }
+  uint64_t run = sum;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint64_t x = __shfl_up(run, o);
+    if (lane >= o) run += x;
+    high |= (uint32_t)(run >> 32);
+  }
+  run -= sum;  // in front of this lane's entries
+#pragma unroll
+  for (int k = 0; k < PER; ++k)
+    if (i0 + k < N) {
+      s[i0 + k + 1] = (int64_t)(run + v[k]);
+      high |= (uint32_t)((run + v[k]) >> 32);
+    }
+  if (lane == 0) s[0] = 0;
+}
+
+// The last block of the largest stage behind block i for which fits(j) holds (i if there is none; the empty
+// stage fits).
+template <typename F> __device__ __forceinline__ int prepare_end(int i, int N, F fits) {
+  int lo = i, hi = N;
+  while (__any(lo < hi)) {
+    const int mid = (lo + hi + 1) >> 1;  // lo itself once they meet
+    if (fits(mid)) lo = mid;
+    else hi = mid - 1;
+  }
+  return lo;
+}
+
+// setup_item_size by one wave: lane k < 16 holds the number of items of size 4 (k + 1).
+__device__ __forceinline__ int prepare_item_size(int cnt, int most, int max_items, int batch, int slots, bool passes) {
+  const int lane = threadIdx.x & 63;
+  const uint32_t listed = (uint32_t)__ballot(lane < most && cnt <= max_items);
+  const int pick = listed ? __ffs((int)listed) - 1 : most - 1;
+  const long long then = (long long)cnt * batch;
+  if ((long long)__builtin_amdgcn_readlane(cnt, pick) * batch <= slots) return pick;
+  const uint32_t round = (uint32_t)__ballot(lane > pick && lane < most && then <= slots);
+  const uint32_t full = (uint32_t)__ballot(2 * then >= slots);
+  if (round && ((full >> (__ffs((int)round) - 1)) & 1u)) return __ffs((int)round) - 1;
+  const uint32_t many = (uint32_t)__ballot(lane > pick && lane < most && 2 * cnt >= 3 * slots);
+  if (passes && batch == 1 && many) return 31 - __clz((int)many);
+  return pick;
+}
+// ceil(x / r) for x, r < 2^16 (the sum's half keeps the product off the whole numbers by more than its error)
+__device__ __forceinline__ int prepare_ceil(int x, int r, float inv) { return (int)(((float)(x + r - 1) + 0.5f) * inv); }
+
+// TIMES: the stage-time tables as well (DP then is the class they are unrolled for; otherwise any).
+// NT: threads of a workgroup, 1024 for few searches (a thread per row, a unit or two per wave: 24 -> 19 us at
+// 1024 blocks), 256 for many (five workgroups to a compute unit instead of one: the sweep of 2048 searches of 128
+// blocks 1854 -> 1741 us a call).
+template <typename VT, int DP, bool TIMES, int NT>
+__global__ __launch_bounds__(NT) void prepare_kernel(const ProblemDev *src, ProblemDev *probs, const PrepareIn in,
+                                                               const ProblemDev one, int use_one) {
+  constexpr VT INF = Lim<VT>::inf;
+  constexpr int WAVES = NT / 64;
+  __shared__ __align__(8) uint32_t desc[sizeof(ProblemDev) / 4];
+  __shared__ int s_flags, s_w[kPrepareChunks], s_full[kPrepareChunks];
+  __shared__ PassChunk s_rec[kPrepareChunks];
+  __shared__ unsigned long long s_max_cut;
+  __shared__ uint32_t s_part[WAVES];
+  extern __shared__ __align__(16) char lds[];
+  const ProblemDev pr = fetch_problem(src + blockIdx.y, probs + blockIdx.y, blockIdx.x == 0, desc, one, use_one);
+  const int N = pr.N, D = pr.D, nch = pr.nch, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if ((int)blockIdx.x >= in.groups) {
+    setup_fill(pr, 1, (int64_t)(blockIdx.x - in.groups) * NT + tid, (int64_t)(gridDim.x - in.groups) * NT);
+    return;
+  }
+  const bool bwd = pr.tb != nullptr, comm = pr.o != nullptr, writes = blockIdx.x == 0;
+  int64_t *const sT = (int64_t *)lds, *const sP = sT + (N + 1), *const sA = sP + (N + 1);
+  int64_t *const sTB = sA + (N + 1), *const sC = sTB + (bwd ? N + 1 : 0);
+  uint64_t *const sZ = (uint64_t *)(sC + (comm ? N + 1 : 0));
+  uint32_t *const sE = (uint32_t *)(sZ + (N + 1)), *const esum = sE + N;
+  if (tid == 0) { s_flags = 0; s_max_cut = 0ull; }
+  if (tid < kPrepareChunks) { s_w[tid] = kNoRow; s_full[tid] = min(64 * tid + 64, N); }  // (the row behind the chunk's last)
+  int flags = 0;
+  uint32_t high = 0;
+  if (wave < 3 || bwd) {  // a wave per array
+    const int64_t *from = wave == 0 ? pr.t : wave == 1 ? pr.p : wave == 2 ? pr.a : pr.tb;
+    int64_t *to = wave == 0 ? sT : wave == 1 ? sP : wave == 2 ? sA : sTB;
+    if (N <= 64) prepare_sums<1>(gptr(from), to, N, flags, high);
+    else if (N <= 192) prepare_sums<3>(gptr(from), to, N, flags, high);
+    else if (N <= 320) prepare_sums<5>(gptr(from), to, N, flags, high);
+    else if (N <= 576) prepare_sums<9>(gptr(from), to, N, flags, high);
+    else prepare_sums<17>(gptr(from), to, N, flags, high);
+  }
+  static_assert(kSetupLdsN <= 17 * 64, "entries of a lane");
+  if (high >> 30) flags |= 2;
+  __syncthreads();  // (s_flags is set)
+  if (comm) {  // per-cut send time; the last block has no follower
+    unsigned long long mc = 0ull;
+#pragma unroll 1
+    for (int k = tid; k < N; k += NT) {
+      const uint64_t c = cut_time(pr.o[k], pr.bw, flags);
+      sC[k + 1] = k + 1 < N ? (int64_t)c : 0;
+      if (k + 1 < N && c > mc) mc = c;
+    }
+    if (tid == 0) sC[0] = 0;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) mc = max(mc, (unsigned long long)__shfl_xor(mc, o));
+    if (mc && lane == 0) atomicMax(&s_max_cut, mc);
+  }
+  if (flags) atomicOr(&s_flags, flags);
+  __syncthreads();
+  flags = s_flags;
+  if (writes) {
+    if (tid == 0) {
+      int st = RANNC_DP_PROBLEM_OK;
+      if (flags & 1) st = RANNC_DP_PROBLEM_NEGATIVE_INPUT;
+      else if (flags & 2) st = RANNC_DP_PROBLEM_SUM_OVERFLOW;
+      else if ((uint64_t)sT[N] + (bwd ? (uint64_t)sTB[N] : 0ull) + s_max_cut > (uint64_t)pr.time_limit)
+        st = RANNC_DP_PROBLEM_TIME_TOO_LARGE;  // a value is at most forward + send + backward time of all blocks
+      *pr.status = st;
+    }
+    for (int e = tid; e <= N; e += NT) {
+      pr.T[e] = sT[e]; pr.P[e] = sP[e]; pr.A[e] = sA[e];
+      if (bwd) pr.TB[e] = sTB[e];
+      if (comm) pr.C[e] = sC[e];
+    }
+  }
+
+  // ---- ends, windows, the chunks' shares of the list ----
+  {
+    // A stage fits on D devices iff D bytes_not_divided + divided ones <= D M: one difference of the sums Z =
+    // D P + A, where neither they nor D M wrap.
+    const uint64_t M = (uint64_t)pr.M;
+    const bool bad = flags != 0;  // (the sums may have wrapped: no stage fits)
+    const bool small = (uint64_t)sP[N] < (1ull << 55) && (uint64_t)sA[N] < (1ull << 60);
+    const uint64_t DM = __umul64hi(M, (uint64_t)D) ? ~0ull : M * (uint64_t)D;
+    if (small) {
+      for (int i = tid; i <= N; i += NT) sZ[i] = (uint64_t)D * (uint64_t)sP[i] + (uint64_t)sA[i];
+      __syncthreads();
+    }
+    for (int i0 = 0; i0 < N; i0 += NT) {
+      if (i0 + 64 * wave >= N) break;
+      const int i = min(i0 + tid, N - 1);
+      int e = i;
+      if (!bad && small) {
+        const uint64_t Zi = sZ[i];
+        e = prepare_end(i, N, [&](int j) { return sZ[j] - Zi <= DM; });
+      } else if (!bad) {
+        const uint64_t Pi = (uint64_t)sP[i], Ai = (uint64_t)sA[i];
+        e = prepare_end(i, N, [&](int j) { return fits_at((uint64_t)sP[j] - Pi, (uint64_t)sA[j] - Ai, M, D); });
+      }
+      if (i0 + tid < N) sE[i] = (uint32_t)e;
+    }
+    __syncthreads();
+    const int Q = (N + NT - 1) / NT;  // consecutive rows of a thread
+    uint32_t sum = 0;
+    for (int i = Q * tid; i < min(Q * tid + Q, N); ++i) {
+      const uint32_t end = sE[i], before = i ? sE[i - 1] : 0u;
+      sum += end;
+      // the chunks whose begin, and whose end, this row is the first to pass
+      for (int c = i ? (int)(before + 63u) >> 6 : 0; c < nch && 64u * (uint32_t)c < end; ++c) s_w[c] = i;
+      for (int c = i ? (int)(before >> 6) : 0; c < nch; ++c) {
+        const uint32_t X = (uint32_t)min(64 * c + 64, N);
+        if (X > end) break;
+        if (i == 0 || X > before) s_full[c] = min(s_full[c], i);
+      }
+    }
+    uint32_t run = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t x = __shfl_up(run, o);
+      if (lane >= o) run += x;
+    }
+    if (lane == 63) s_part[wave] = run;
+    __syncthreads();
+    uint32_t at = run - sum;
+    for (int q = 0; q < wave; ++q) at += s_part[q];
+    for (int i = Q * tid; i < min(Q * tid + Q, N); ++i) {
+      esum[i] = at;
+      at += sE[i];
+      if (i == N - 1) esum[N] = at;
+    }
+    if (tid < nch) {
+      const int c = tid;
+      int w = s_w[c];
+      if (w > 64 * c) {  // the chunk's first block fits no device by itself: the first later one that does
+        w = kNoRow;
+        for (int i = 64 * c + 1; i <= min(64 * c + 63, N - 1); ++i)
+          if (sE[i] > (uint32_t)i) { w = i; break; }
+      }
+      s_w[c] = w;
+      if (w != kNoRow) s_full[c] = max(s_full[c], w);
+      if (writes) pr.wlo[c] = w;
+    }
+    __syncthreads();
+  }
+  int rows = in.rows;
+  if (in.paired) {
+    if (wave == 0) {
+      uint32_t np = 0;
+      if (lane < nch && s_w[lane] != kNoRow)
+        np = (stages_before(esum, N, lane, (uint32_t)s_w[lane], (uint32_t)s_full[lane], (uint32_t)min(64 * lane + 64, N)) + 63u) >> 6;
+      if (rows <= 0) {  // lane k counts the items of size 4 (k + 1)
+        const int r = 4 * (lane & 15) + 4;
+        const float inv = 1.0f / (float)r;
+        int cnt = 0;
+        for (int c = 0; c < nch; ++c) cnt += prepare_ceil((int)lane_bcast(np, c), r, inv);
+        rows = 4 * (prepare_item_size(cnt, in.max_rows / 4, in.max_items, in.batch, in.slots, true) + 1);
+      }
+      const uint32_t ni = (np + (uint32_t)rows - 1u) / (uint32_t)rows;
+      uint32_t p = np, t = ni;
+#pragma unroll
+      for (int o = 1; o < kPrepareChunks; o <<= 1) {
+        const uint32_t x = __shfl_up(p, o), y = __shfl_up(t, o);
+        if (lane >= o) { p += x; t += y; }
+      }
+      if (lane < nch) s_rec[lane] = {(uint32_t)s_full[lane], p - np, t - ni, ni ? (np + ni - 1u) / ni : 1u};
+      if (writes && lane == kPrepareChunks - 1) pr.runs[0] = (int32_t)t;
+    }
+    __syncthreads();
+  }
+
+  // ---- tables: of a row the units that hold a stage that fits, `parts` waves to a row; the others hold only
+  // "fits nowhere" ----
+  const bool passes = in.paired && pr.S_eff > 1;
+  for (int id = (int)blockIdx.x * WAVES + wave; id < N * in.parts; id += in.groups * WAVES) {  // wave-uniform
+    const int i = id / in.parts, part = id - i * in.parts;
+    const int own = i >> 6, last = min(i | 63, N - 1);
+    // the first chunk without such a stage (row 0 has its units written in any case, and a chunk's last row closes
+    // the chunk's passes)
+    const int behind = max((int)(sE[i] + 63u) >> 6, own + (i == 0 || i == last ? 1 : 0));
+    for (int c = own + part; c < behind; c += in.parts) {
+      UnitStages<VT> st;
+      (void)build_unit<VT, DP, true>(pr, sT, sP, sA, comm ? sC : nullptr, i, c, lane, nullptr, 0, 0, bwd ? sTB : nullptr, TIMES,
+                                     nullptr, &st);
+      if (passes) pass_entries<VT>(pr, i, c, lane, st.fits, st.rmin, st.tij, s_w[c], s_rec[c], esum);
+    }
+    if (part != 0) continue;
+    const int from = max(behind, own), rest = nch - from;
+    if (rest <= 0) continue;
+    const int64_t u = unit_index(nch, i, from);
+    typedef uint32_t Quad __attribute__((ext_vector_type(4)));
+    Quad RANNC_GLOBAL *const rm = (Quad RANNC_GLOBAL *)(gptr(pr.rmin) + u * 64);
+    if (lane < 4 * rest) rm[lane] = Quad{~0u, ~0u, ~0u, ~0u};  // (at most sixteen chunks)
+    if (lane < rest) pr.ufit[u + lane] = 0;
+  }
+  // ---- level 1: one stage on d devices, an entry per thread and turn (a thread keeps its d) ----
+  {
+    const int VD = pr.DP, d = (tid & (VD - 1)) + 1;
+    const double inv = 1.0 / (double)d;
+    auto share = [&](int64_t x) -> VT {
+      if constexpr (sizeof(VT) == 4) return ceil_div<VT>((VT)x, d, inv);
+      else return (VT)(((uint64_t)x + (uint64_t)(d - 1)) / (uint64_t)d);
+    };
+    auto *const V = gptr((VT *)pr.V), *const VF = gptr((VT *)pr.VF), *const VB = gptr((VT *)pr.VB);
+    const int per = NT / VD;  // rows of a turn
+    for (int j = (int)blockIdx.x * per + tid / VD; j <= N; j += in.groups * per) {
+      const int64_t e = (int64_t)j * VD + d - 1;
+      const bool fit = j > 0 && d <= D && fits_at((uint64_t)sP[j], (uint64_t)sA[j], (uint64_t)pr.M, d);
+      const VT none = d <= D ? INF : (VT)0;  // (padding columns hold 0, so that padded rows stay sorted)
+      VT f = 0, b = 0;
+      if (fit) {
+        f = share(sT[j]);
+        if (comm) f += share(sC[j]);
+        if (bwd) b = share(sTB[j]);
+      }
+      V[e] = fit ? f + b : none;
+      if (bwd) {
+        VF[e] = fit ? f : none;
+        VB[e] = fit ? b : none;
+      }
+    }
+  }
+  if (in.paired || !writes) return;
+
+  // ---- work list of rows (of the first workgroup; nch <= 16) ----
+  int32_t *const runs = pr.runs;
+  __shared__ int start[kPrepareChunks + 1];
+  if (wave == 0) {
+    const int n0 = lane < nch ? run_segments(N, lane, s_w[lane], false).n0 : 0;
+    if (rows <= 0) {
+      const int r = 4 * (lane & 15) + 4;
+      const float inv = 1.0f / (float)r;
+      int cnt = 0;
+      for (int c = 0; c < nch; ++c) cnt += prepare_ceil((int)lane_bcast((uint32_t)n0, c), r, inv);
+      rows = 4 * (prepare_item_size(cnt, in.max_rows / 4, in.max_items, in.batch, in.slots, false) + 1);
+    }
+    int run = (n0 + rows - 1) / rows;
+    const int mine = run;
+#pragma unroll
+    for (int o = 1; o < kPrepareChunks; o <<= 1) {
+      const int x = __shfl_up(run, o);
+      if (lane >= o) run += x;
+    }
+    if (lane < nch) start[lane] = run - mine;
+    if (lane == kPrepareChunks - 1) { start[nch] = run; runs[0] = run; }
+  }
+  __syncthreads();
+  for (int c = 0; c < nch; ++c) {
+    const RunSegments g = run_segments(N, c, s_w[c], false);
+    const int items = start[c + 1] - start[c], per = items ? (g.n0 + items - 1) / items : 0;
+    for (int k = tid; k < items; k += NT) {
+      const int take = max(min(per, g.n0 - k * per), 1);  // (never below one row: the word stays well-formed)
+      runs[1 + start[c] + k] = ((take - 1) << 26) | (c << 16) | (g.lo0 + k * per);
+    }
   }
 }
 
@@ -2216,6 +2551,53 @@ hipError_t launch_build(const ProblemDev *p, const LaunchShape &sh, int bits, in
   GO(64, uint64_t)
 #undef GO
   return hipGetLastError();
+}
+
+bool can_prepare(const LaunchShape &sh) { return sh.max_N <= kSetupLdsN; }
+
+constexpr int kPrepareMany = 8;  // searches of a launch
+
+template <typename VT, int DP, bool TIMES>
+static hipError_t prepare_go(const ProblemDev *src, ProblemDev *probs, const LaunchShape &sh, PrepareIn in, size_t lds, int fill,
+                             const ProblemDev *host_one, hipStream_t st) {
+  const ProblemDev one = host_one ? *host_one : ProblemDev{};
+  for (int q0 = 0; q0 < sh.nprob; q0 += 65535) {
+    const dim3 grid(in.groups + fill, min(65535, sh.nprob - q0));
+    if (sh.nprob < kPrepareMany)
+      hipLaunchKernelGGL((prepare_kernel<VT, DP, TIMES, 1024>), grid, dim3(1024), lds, st, src + q0, probs + q0, in, one, host_one ? 1 : 0);
+    else
+      hipLaunchKernelGGL((prepare_kernel<VT, DP, TIMES, 256>), grid, dim3(256), lds, st, src + q0, probs + q0, in, one, host_one ? 1 : 0);
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_prepare(const ProblemDev *src, ProblemDev *probs, const LaunchShape &sh, int bits, int DP, int parts,
+                          int rows_per_item, int max_items, int slots, bool paired, int max_rows, bool split, bool comm,
+                          const ProblemDev *host_one, hipStream_t st) {
+  if (!can_prepare(sh)) return hipErrorInvalidValue;
+  PrepareIn in;
+  in.rows = rows_per_item; in.max_items = max_items; in.batch = sh.nprob; in.slots = slots;
+  in.paired = paired ? 1 : 0; in.max_rows = max_rows;
+  // Workgroups that build: four waves to a row of a lone search, whole rows where there are many searches and
+  // every further workgroup would only form the sums once more.
+  const bool many = sh.nprob >= kPrepareMany;
+  in.parts = many ? 1 : 4;
+  in.groups = many ? max(1, min((sh.max_N + 3) / 4, 1280 / sh.nprob)) : max(1, min((sh.max_N * in.parts + 15) / 16, 512 / sh.nprob));
+  const int fill = many ? (sh.nprob >= 256 ? 4 : 16) : 32;  // workgroups that fill a search's V
+  static_assert((kSetupLdsN + 1) * 8 * 6 + (2 * kSetupLdsN + 1) * 4 <= 60 * 1024, "dynamic LDS that need not be asked for");
+  const size_t lds = (size_t)(sh.max_N + 1) * 8 * (4 + (split ? 1 : 0) + (comm ? 1 : 0)) + (size_t)(2 * sh.max_N + 1) * 4;
+#define GO(B, T)                                                                                            \
+  if (bits == B) {                                                                                          \
+    if (!(parts & 2)) return prepare_go<T, 8, false>(src, probs, sh, in, lds, fill, host_one, st);          \
+    if (DP == 8) return prepare_go<T, 8, true>(src, probs, sh, in, lds, fill, host_one, st);                \
+    if (DP == 16) return prepare_go<T, 16, true>(src, probs, sh, in, lds, fill, host_one, st);              \
+    if (DP == 32) return prepare_go<T, 32, true>(src, probs, sh, in, lds, fill, host_one, st);              \
+    return prepare_go<T, 64, true>(src, probs, sh, in, lds, fill, host_one, st);                            \
+  }
+  GO(32, uint32_t)
+  GO(64, uint64_t)
+#undef GO
+  return hipErrorInvalidValue;
 }
 
 template <typename VT, int HMAX, bool DIRECT>
