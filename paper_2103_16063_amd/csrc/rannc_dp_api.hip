@@ -987,7 +987,6 @@ bool fs_pairs(const rannc_dp_form_stage_in_t *in, std::vector<FsPair> *out, int 
 size_t fs_scratch(int Q, int N, int stride) {
   size_t b = 0;
   b += 5 * align_up((size_t)Q * N * 8);       // scaled time, param, act, cut bytes, backward time
-  b += align_up((size_t)Q * 8);               // n and MB of every search (int32 each; travels up with the inputs)
   b += 2 * align_up((size_t)Q * 8);           // opt, (n_stages + status as int32 pairs)
   b += 2 * align_up((size_t)Q * stride * 4);  // plans of the batch
   b += align_up(6 * 8 + (size_t)stride * 8);  // result record and the chosen plan (travels down)
@@ -1077,7 +1076,7 @@ int rannc_dp_form_stage(rannc_dp_t *h, const rannc_dp_form_stage_in_t *in, void 
   }
   // layout of the scratch (device) and of its mirror (host)
   const size_t a_in = align_up((size_t)Q * N * 8);
-  const size_t o_pair = 0, o_t = align_up((size_t)Q * 8);
+  const size_t o_t = 0;
   const size_t o_p = o_t + a_in, o_a = o_t + 2 * a_in, o_o = o_t + 3 * a_in, o_b = o_t + 4 * a_in;
   const size_t o_opt = o_t + 5 * a_in;
   const size_t o_ns = o_opt + align_up((size_t)Q * 8);
@@ -1087,7 +1086,6 @@ int rannc_dp_form_stage(rannc_dp_t *h, const rannc_dp_form_stage_in_t *in, void 
   char *dev = (char *)d_scratch, *pin = h->fs_pin;
   int64_t *ht = (int64_t *)(pin + o_t), *hp = (int64_t *)(pin + o_p), *ha = (int64_t *)(pin + o_a);
   int64_t *ho = (int64_t *)(pin + o_o), *hb = (int64_t *)(pin + o_b);
-  int32_t *hpn = (int32_t *)(pin + o_pair), *hpm = hpn + Q;
   // per-microbatch inputs of every (n, MB): b samples on one pipeline replica
   const __int128 lim = (__int128)1 << 62;
   __int128 max_total = 0;  // largest total time of a search (forward, no communication term: what the
@@ -1097,8 +1095,6 @@ int rannc_dp_form_stage(rannc_dp_t *h, const rannc_dp_form_stage_in_t *in, void 
     hD[q] = in->devices_per_node * pairs[q].n;
     hS[q] = hD[q];
     hMB[q] = pairs[q].MB;
-    hpn[q] = pairs[q].n;
-    hpm[q] = pairs[q].MB;
     hoff[q] = (int64_t)q * N;
     for (int k = 0; k < N; ++k) {
       const int64_t ts = in->time_per_sample_ns[k], as = in->act_bytes_per_sample[k];
@@ -1124,10 +1120,9 @@ int rannc_dp_form_stage(rannc_dp_t *h, const rannc_dp_form_stage_in_t *in, void 
     max_total = std::max(max_total, total);
   }
   hoff[Q] = (int64_t)Q * N;
-  // The (n, MB) of every search and the block arrays in use are contiguous: one copy up.  Small
-  // inputs (the paper's 32 blocks: 18 KB) are not copied at all: the mirror is pinned host memory
-  // that the device reads through the same address, every word once, which costs the kernels a
-  // bus round trip and saves the call a copy in front of its first kernel.
+  // The block arrays in use are contiguous: one copy up.  Small inputs (the paper's 32 blocks: 18 KB) are
+  // not copied at all: the mirror is pinned host memory that the device reads through the same address,
+  // which costs the kernels a bus round trip and saves the call a copy in front of its first kernel.
   const size_t in_bytes = o_t + (split ? 5 : comm ? 4 : 3) * a_in;
   char *pin_dev = h->fs_pin_dev;
   const bool in_place = pin_dev && in_bytes <= kFsReadInPlaceMax;
@@ -1139,7 +1134,6 @@ int rannc_dp_form_stage(rannc_dp_t *h, const rannc_dp_form_stage_in_t *in, void 
   int64_t *d_opt = (int64_t *)(dev + o_opt);
   int32_t *d_ns = (int32_t *)(dev + o_ns), *d_st = d_ns + Q;
   int32_t *d_se = (int32_t *)(dev + o_se), *d_rp = (int32_t *)(dev + o_rp);
-  const int32_t *d_pn = (const int32_t *)(src + o_pair), *d_pm = d_pn + Q;
   // the result record and the chosen plan behind it are written by the kernels straight into the
   // mirror (they only write it): no copy down, the wait for the stream is all that is left
   int64_t *d_rec = (int64_t *)((pin_dev ? pin_dev : dev) + o_rec);
@@ -1158,7 +1152,6 @@ int rannc_dp_form_stage(rannc_dp_t *h, const rannc_dp_form_stage_in_t *in, void 
   // the chosen (n, MB, S) and writes record, plan and flag word into the mirror.
   rannc::FormStageIn f = {};
   f.Q = Q; f.N = N; f.devices_per_node = in->devices_per_node;
-  f.pair_n = d_pn; f.pair_mb = d_pm;
   f.rec = d_rec;
   if (pin_dev) {
     f.flag = (uint64_t *)(pin_dev + need);

@@ -126,7 +126,6 @@ struct PlanResults {
 // memory; flag (or null) = seq is stored behind it).
 struct FormStageIn {
   int Q, N, devices_per_node;
-  const int32_t *pair_n, *pair_mb;  // node count and microbatch count of every search
   int64_t *rec;
   uint64_t *flag, seq;
 };

@@ -1633,8 +1633,9 @@ constexpr int kSmallMaxN = 128;
 constexpr int kSmallWavesMax = 16;
 template <typename VT, int DP> constexpr int small_waves() { return sizeof(VT) * DP >= 256 ? 8 : kSmallWavesMax; }
 
-__device__ __forceinline__ void select_finish(const ProblemDev &pr, int64_t v, int st, int64_t *d_opt,
-                                              int32_t *d_n_stages, int64_t *d_est, int32_t *d_status);
+struct Chosen { int64_t opt, est; int n_stages, status; };
+__device__ __forceinline__ Chosen select_finish(const ProblemDev &pr, int64_t v, int st, int64_t *d_opt,
+                                                int32_t *d_n_stages, int64_t *d_est, int32_t *d_status);
 
 // Waves per SIMD the one-launch kernel is compiled for.  The recomputing form on 32-bit values at 16
 // devices needs 70 registers left alone, one wave per SIMD short of TWO workgroups per compute unit
@@ -1928,110 +1929,46 @@ __global__ __launch_bounds__(64) void level_scan_kernel(const ProblemDev *__rest
   if (arg_d) arg_d[e] = bd;
 }
 
-// Plan recovery for the split objective: the candidate kept by a cell is the first one, in scan
-// order, whose sum equals the cell's value.  All threads of the workgroup evaluate the candidates
-// of one cell, numbered in scan order, and the smallest matching number wins.
-template <typename VT>
-__device__ void traceback_split_body(const ProblemDev &pr, int plan_stride, int32_t *se, int32_t *rp,
-                                     unsigned int *best_key, int forced) {
-  constexpr VT INF = Lim<VT>::inf;
-  const int N = pr.N, D = pr.D, DP = pr.DP, nch = pr.nch;
-  const int tid = threadIdx.x;
-  const int64_t lvl = (int64_t)(N + 1) * DP;
-  const VT *V = (const VT *)pr.V, *VF = (const VT *)pr.VF, *VB = (const VT *)pr.VB;
-  // the stage times are valued from the prefix sums (the level kernel has not built their tables)
-  __shared__ double inv[64];
-  if (tid < 64) inv[tid] = 1.0 / (double)(tid + 1);
-  const bool quick = pr.time_limit <= kCeilDivMax;
-  __syncthreads();
-  auto share = [&](int64_t x, int r) -> VT {
-    if (quick) return ceil_div<VT>((VT)x, r, inv[r - 1]);
-    return (VT)(((uint64_t)x + (uint64_t)(r - 1)) / (uint64_t)r);
-  };
-  int ns = (*pr.status == 0 && forced >= 0) ? (int)pr.res[1] : 0;  // forced < 0: no plan wanted
-  if (forced > 0 && *pr.status == 0)
-    ns = (forced <= pr.S_eff && V[(int64_t)(forced - 1) * lvl + (int64_t)N * DP + D - 1] != INF) ? forced : 0;
-  for (int u = ns + tid; u < plan_stride; u += blockDim.x) { se[u] = -1; rp[u] = -1; }
-  if (ns == 0) return;
-  int j = N, d = D;
-  for (int s = ns; s >= 2; --s) {
-    if (tid == 0) *best_key = 0xFFFFFFFFu;
-    __syncthreads();
-    const VT v = V[(int64_t)(s - 1) * lvl + (int64_t)j * DP + d - 1];
-    const int jj = j - 1, c = jj >> 6;
-    const int64_t Tj = pr.T[j], TBj = pr.TB[j], Cj = pr.C ? pr.C[j] : 0;
-    const int nd = d - (s - 1);                       // d' = s-1 .. d-1
-    const int total = (j - (s - 1)) * nd;             // i = s-1 .. j-1
-    unsigned mine = 0xFFFFFFFFu;
-    for (int e = tid; e < total && mine == 0xFFFFFFFFu; e += blockDim.x) {
-      const int i = s - 1 + e / nd, dp = s - 1 + e % nd;
-      const int64_t pc = (int64_t)(s - 2) * lvl + (int64_t)i * DP + dp - 1;
-      if (V[pc] == INF) continue;
-      const int64_t u = unit_index(nch, i, c);
-      const int r = d - dp;
-      if (r < (int)pr.rmin[u * 64 + (jj & 63)]) continue;
-      const VT hf = share(Tj - pr.T[i], r) + (Cj ? share(Cj, r) : (VT)0), hb = share(TBj - pr.TB[i], r);
-      const VT f = vmax(VF[pc], hf), b = vmax(VB[pc], hb);
-      if ((VT)(f + b) == v) mine = ((unsigned)i << 8) | (unsigned)dp;  // (i, d') ascends with e
-    }
-    if (mine != 0xFFFFFFFFu) atomicMin(best_key, mine);
-    __syncthreads();
-    const unsigned key = *best_key;
-    __syncthreads();
-    if (key == 0xFFFFFFFFu) {  // tables inconsistent: report no plan rather than walk on
-      for (int u = tid; u < plan_stride; u += blockDim.x) { se[u] = -1; rp[u] = -1; }
-      return;
-    }
-    const int i_sel = (int)(key >> 8), d_sel = (int)(key & 255u);
-    if (tid == 0) { se[s - 1] = j; rp[s - 1] = d - d_sel; }
-    j = i_sel;
-    d = d_sel;
-  }
-  if (tid == 0) { se[0] = j; rp[0] = d; }
-}
-
 // ---------------------------------------------------------------------------------------
 // Final choice of the stage count: opt = min over s of V[s][N][D], smallest s among equals.
 // One wave per problem, lane s-1 reads V[s][N][D] (S_eff <= D <= 64).
 // ---------------------------------------------------------------------------------------
 // one wave: lane s-1 brings V[s][N][D] (INT64_MAX beyond S_eff or if the status is bad)
-__device__ __forceinline__ void select_finish(const ProblemDev &pr, int64_t v, int st, int64_t *d_opt,
-                                              int32_t *d_n_stages, int64_t *d_est, int32_t *d_status) {
+__device__ __forceinline__ Chosen select_finish(const ProblemDev &pr, int64_t v, int st, int64_t *d_opt,
+                                                int32_t *d_n_stages, int64_t *d_est, int32_t *d_status) {
   const int lane = threadIdx.x & 63;
   const int q = pr.q;
-  // lexicographic minimum of (value, s): fewest stages among equal values
-  int bs = lane + 1;
+  // the minimum; the first lane that holds it has the fewest stages
+  int64_t best = v;
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) {
-    const int64_t ov = __shfl_xor(v, o);
-    const int os = __shfl_xor(bs, o);
-    if (ov < v || (ov == v && os < bs)) { v = ov; bs = os; }
+    const int64_t ov = __shfl_xor(best, o);
+    if (ov < best) best = ov;
   }
-  if (lane != 0) return;
-  const int64_t best = v;
-  if (best == INT64_MAX) bs = 0;
-  pr.res[0] = best;
-  pr.res[1] = bs;
-  if (d_opt) d_opt[q] = best;
-  if (d_n_stages) d_n_stages[q] = bs;
-  if (d_est) {
-    int64_t e = INT64_MAX;
-    if (bs > 0) {
-      const int64_t f = (int64_t)pr.MB + bs - 1;
-      e = (best != 0 && f > INT64_MAX / best) ? INT64_MAX : f * best;
-    }
-    d_est[q] = e;
+  const int bs = best == INT64_MAX ? 0 : __ffsll((long long)__ballot(v == best));
+  Chosen c = {best, INT64_MAX, bs, st};
+  if (bs > 0) {
+    const int64_t f = (int64_t)pr.MB + bs - 1;
+    c.est = (best != 0 && f > INT64_MAX / best) ? INT64_MAX : f * best;
   }
-  if (d_status) d_status[q] = st;
+  if (lane == 0) {
+    pr.res[0] = best;
+    pr.res[1] = bs;
+    if (d_opt) d_opt[q] = best;
+    if (d_n_stages) d_n_stages[q] = bs;
+    if (d_est) d_est[q] = c.est;
+    if (d_status) d_status[q] = st;
+  }
+  return c;
 }
 
 // one wave
-__device__ __forceinline__ void select_body(const ProblemDev &pr, int64_t *d_opt, int32_t *d_n_stages, int64_t *d_est,
-                                            int32_t *d_status) {
+__device__ __forceinline__ Chosen select_body(const ProblemDev &pr, int64_t *d_opt, int32_t *d_n_stages, int64_t *d_est,
+                                              int32_t *d_status) {
   const int lane = threadIdx.x & 63;
-  const int st = *pr.status;
+  const int st = *pr.status;  // (asked for together with the values)
   int64_t v = INT64_MAX;
-  if (st == 0 && lane < pr.S_eff) {
+  if (lane < pr.S_eff) {
     const int64_t lvl = (int64_t)(pr.N + 1) * pr.DP;
     const int64_t cell = (int64_t)pr.N * pr.DP + pr.D - 1;
     if (pr.bits == 32) {
@@ -2042,7 +1979,8 @@ __device__ __forceinline__ void select_body(const ProblemDev &pr, int64_t *d_opt
       v = (u == Lim<uint64_t>::inf) ? INT64_MAX : (int64_t)u;
     }
   }
-  select_finish(pr, v, st, d_opt, d_n_stages, d_est, d_status);
+  if (st != 0) v = INT64_MAX;
+  return select_finish(pr, v, st, d_opt, d_n_stages, d_est, d_status);
 }
 
 __global__ __launch_bounds__(64) void select_kernel(const ProblemDev *__restrict__ probs,
@@ -2056,73 +1994,112 @@ __global__ __launch_bounds__(64) void select_kernel(const ProblemDev *__restrict
 // optimal table value).
 // One workgroup per problem walks from (s*, N, D) down to level 1.  At each cell it finds the
 // lexicographically smallest (i, d') with max(V[s-1][i][d'], h(i,j,d-d')) equal to the cell's
-// value: the candidate that the ascending scan with strict "<" of Algorithm 1 would have kept.
-// A lane owns a split point i.  Both the row V[s-1][i][.] and h(i,j,.) are non-increasing (the property
-// the merge kernel rests on), so in row i the only candidate is the smallest d' whose earlier-stages
-// value is <= the cell's value: found with eight probes and then eight reads of the eighth it lies in,
-// checked against the stage's time.  Value and prefix sum of the chosen row travel to the next step
-// through LDS.
-// Bound by latency: two dependent round trips (the second mostly to lines of the first) and one barrier
-// per stage.  With a wave per row, twelve rows at a time and three barriers a stage took 3.2 us out of
-// memory (1024 blocks, 64 devices) and 1.4 us out of LDS.  Whole kernel, with the results' way to the host:
-// 40 -> 32 us there, 25 -> 17 us at 251 blocks with send times, 16.5 -> 10.3 us at 96 blocks out of LDS.
-// Waves without a row of the window skip the evaluation: sixteen waves share four SIMDs, and the idle ones'
-// instructions took longer than the step's own latency (with Algorithm 2's loops over 24 searches of 32
-// blocks 30.0 -> 24.1 us; solve and recovery apart, 1024 blocks: 30.6 -> 26.6 us).
+// value v: the candidate that the ascending scan with strict "<" of Algorithm 1 would have kept.
+// v is the minimum over all candidates, so "equal" is "at most".  A lane owns a split point i.  The stage
+// (i, j) takes at most v from some replica count r on (its time and its bytes fall with r), and V[s-1][i][.]
+// falls with d': row i holds a candidate iff V[s-1][i][d - r] <= v, and its first one is the smallest d' with
+// V[s-1][i][d'] <= v.  r follows from the time alone where one replica holds the bytes, so a lane asks for the
+// rmin byte and for the eight values up to V[s-1][i][d - r] at once; the first candidate lies among them
+// unless the row is flat for longer, and then only the first row with a candidate is looked at further.
+// Value and prefix sum of the chosen row travel to the next step through LDS.
+// Bound by latency: one round trip and one barrier per stage.  (Eight probes of the whole row and then
+// eight reads of the eighth it lies in were two: 1.9 us a stage out of memory at 64 devices, now 1.6; what stands in
+// front of the walk and behind it 8.0 us, now 5.3, 1024 blocks in one stage.)
+// The plan and what else the host is told stay in LDS until one wave writes all of it.
 // ---------------------------------------------------------------------------------------
-// Whether max(a, h) == v for the stage time h = ceil(x/r) + ceil(C/r) of Sec. III-C, given a <= v.
-// The stage's time comes from the prefix sums (the table may not have been built); x is compared
-// with multiples of r instead of being divided by it (a 64-bit division costs far more than the
-// rest of a pass).  C is the same for every lane, so its branch does not diverge.
-__device__ __forceinline__ bool stage_time_completes(uint64_t x, uint64_t C, int r, uint64_t a, uint64_t v) {
-  uint64_t w = v;  // what ceil(x/r) may reach at most, and has to reach when a < v
-  if (C) {
-    const uint64_t hc = (C + (uint64_t)(r - 1)) / (uint64_t)r;
-    if (hc > v) return false;
-    w = v - hc;
-  }
-  // ceil(x/r) <= w  <=>  x <= w r
-  if (__umul64hi(w, (uint64_t)r) == 0 && x > w * (uint64_t)r) return false;
-  if (a == v || w == 0) return true;
-  // ceil(x/r) >= w  <=>  x > (w-1) r
-  return __umul64hi(w - 1, (uint64_t)r) == 0 && x > (w - 1) * (uint64_t)r;
-}
-
 constexpr int kTracebackThreads = 1024;
 
 // What the waves of a plan recovery exchange: per step the smallest key ((i << 8) | d') found, in three
 // words of which one is cleared while another is in use (one barrier per step), and the value and prefix
-// sum of each wave's first match.
+// sum of each wave's first match; then the plan.
 struct TracebackLds {
   unsigned int key[3];
   uint64_t value[2][kTracebackThreads / 64];
   int64_t T[2][kTracebackThreads / 64];
+  Chosen chosen;
+  int ns;  // stages of the plan, 0: none
+  int32_t end[RANNC_DP_MAX_DEVICES], replicas[RANNC_DP_MAX_DEVICES];
 };
+
+// x <= v r for v < 2^62, r < 2^32
+__device__ __forceinline__ bool at_most_times(uint64_t x, uint64_t v, uint32_t r) {
+  return __umul64hi(v, (uint64_t)r) != 0 || x <= v * (uint64_t)r;
+}
+
+// The smallest r with ceil(x / r) + ceil(C / r) <= v, or more than `most`; inv_v = 1 / v in double precision,
+// hc: lane r - 1 of the wave holds ceil(C / r) (only with C).
+__device__ __forceinline__ int least_replicas(uint64_t x, uint64_t C, uint64_t v, double inv_v, uint64_t hc, int most) {
+  if (v == 0) return x == 0 && C == 0 ? 1 : most + 1;
+  const double q = (double)(x + C) * inv_v;  // (off by far less than one below 2^7)
+  int r = max((int)min(q, 100.0), 1);
+  if (r > 1 && at_most_times(x + C, v, (uint32_t)r - 1u)) --r;
+  if (!at_most_times(x + C, v, (uint32_t)r)) ++r;  // ceil((x + C) / v), or above 64
+  if (C) {  // two ceilings may need some more
+    for (int more = 0; __any(more == 0); ) {
+      const uint64_t c = __shfl(hc, min(r, 64) - 1);
+      const bool ok = more || r > most || (c <= v && (v == c ? x == 0 : at_most_times(x, v - c, (uint32_t)r)));
+      if (ok) more = 1;
+      else ++r;
+    }
+  }
+  return r;
+}
+
+// forced > 0: the plan of exactly `forced` stages (Algorithm 1's own answer V[S][|B|][D]), if that level
+// holds one; forced = 0: the best level chosen by the solve, or here (choose: select_body, by the first
+// wave); forced < 0: no plan wanted.  The first wave leaves ns and, chosen here or read (results), what
+// else the host is told in sh; every wave learns ns behind a barrier.  v_of(s): V[s][N][D].
+template <typename VT>
+__device__ __forceinline__ int traceback_stages(const ProblemDev &pr, TracebackLds &sh, int forced, const PlanResults &results,
+                                                bool choose) {
+  if (threadIdx.x < 64) {
+    const int64_t lvl = (int64_t)(pr.N + 1) * pr.DP, cell = (int64_t)pr.N * pr.DP + pr.D - 1;
+    Chosen c;
+    if (choose) {
+      c = select_body(pr, results.d_opt, results.d_n_stages, results.d_est, results.d_status);
+    } else {
+      c = {INT64_MAX, INT64_MAX, (int)pr.res[1], *pr.status};
+      if (results.h_flag) {
+        c.opt = results.d_opt[pr.q];
+        c.est = results.d_est[pr.q];
+      }
+    }
+    int ns = forced < 0 || c.status != 0 ? 0 : c.n_stages;
+    if (forced > 0 && c.status == 0)
+      ns = forced <= pr.S_eff && gptr((const VT *)pr.V)[(int64_t)(forced - 1) * lvl + cell] != Lim<VT>::inf ? forced : 0;
+    if (threadIdx.x == 0) { sh.chosen = c; sh.ns = ns; }
+  }
+  if (threadIdx.x < 3) sh.key[threadIdx.x] = 0xFFFFFFFFu;
+  __syncthreads();
+  return sh.ns;
+}
 
 // STAGED: everything the walk reads (the levels of V below the plan's, T, C, the window bounds, the
 // fits-in-memory bytes) is first copied into the workgroup's LDS with one round of independent reads,
-// and the walk then runs out of LDS.  lds: traceback_lds_bytes() bytes (not STAGED: nch words).
-// choose: the stage count is chosen here (select_body, by the first wave, while the others copy).
+// and the walk then runs out of LDS.  Otherwise the window bounds and, up to kTracebackSums of them, the
+// prefix sums are (out of memory they would be another round trip).
+// lds: traceback_lds_bytes() bytes (not STAGED: kTracebackSums + 1 sums and nch words).
+constexpr int kTracebackSums = 2048;
+
 template <typename VT, bool STAGED>
-__device__ void traceback_body(const ProblemDev &pr, int plan_stride, int32_t *se, int32_t *rp,
-                               TracebackLds &sh, int forced, char *lds, const PlanResults &results, bool choose) {
-  constexpr VT INF = Lim<VT>::inf;
+__device__ void traceback_body(const ProblemDev &pr, TracebackLds &sh, int forced, char *lds, const PlanResults &results, bool choose) {
   const int N = pr.N, D = pr.D, DP = pr.DP, nch = pr.nch;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nt = blockDim.x;
   const int64_t lvl = (int64_t)(N + 1) * DP;
   const VT RANNC_GLOBAL *Vg = gptr((const VT *)pr.V);
-  if (tid < 3) sh.key[tid] = 0xFFFFFFFFu;
   using VP = std::conditional_t<STAGED, const VT *, const VT RANNC_GLOBAL *>;
-  using TP = std::conditional_t<STAGED, const int64_t *, const int64_t RANNC_GLOBAL *>;
+  using CP = std::conditional_t<STAGED, const int64_t *, const int64_t RANNC_GLOBAL *>;
   using RP = std::conditional_t<STAGED, const uint8_t *, const uint8_t RANNC_GLOBAL *>;
-  VP V;
-  TP T, C = nullptr;
-  RP rmin;
-  const int32_t *wlo;
   typedef uint32_t Quad __attribute__((ext_vector_type(4)));
+  VP V;
+  CP C = nullptr;
+  RP rmin;
+  const int64_t *T;
+  const int32_t *wlo;
   [[maybe_unused]] VT *Vl = (VT *)lds;
-  if (choose && wave == 0) select_body(pr, results.d_opt, results.d_n_stages, results.d_est, results.d_status);
+  const bool sums = STAGED || N <= kTracebackSums;
+  // (the first wave looks for the stage count meanwhile)
   if constexpr (STAGED) {
     const int64_t nT = (((int64_t)(N + 1) * 8 + 31) / 32) * 32;
     char *w = lds + (int64_t)pr.S_eff * lvl * (int64_t)sizeof(VT);  // room for every level
@@ -2130,36 +2107,33 @@ __device__ void traceback_body(const ProblemDev &pr, int plan_stride, int32_t *s
     int64_t *Cl = (int64_t *)w; w += nT;
     int32_t *Wl = (int32_t *)w; w += (((int64_t)nch * 4 + 31) / 32) * 32;
     uint8_t *Rl = (uint8_t *)w;
-    // (every array starts on a 256-byte boundary of the workspace); the first wave, if it chooses, joins for V
-    const int first = choose ? 64 : 0;
-    if (tid >= first) {
-      for (int e = tid - first; e <= N; e += nt - first) {
+    // (every array starts on a 256-byte boundary of the workspace)
+    if (tid >= 64) {
+      for (int e = tid - 64; e <= N; e += nt - 64) {
         Tl[e] = pr.T[e];
         if (pr.C) Cl[e] = pr.C[e];
       }
-      for (int e = tid - first; e < nch; e += nt - first) Wl[e] = pr.wlo[e];
+      for (int e = tid - 64; e < nch; e += nt - 64) Wl[e] = pr.wlo[e];
       const Quad RANNC_GLOBAL *rsrc = (const Quad RANNC_GLOBAL *)gptr((const uint8_t *)pr.rmin);
-      for (int64_t e = tid - first; e < units_before(nch, N) * 4; e += nt - first) ((Quad *)Rl)[e] = rsrc[e];
+      for (int64_t e = tid - 64; e < units_before(nch, N) * 4; e += nt - 64) ((Quad *)Rl)[e] = rsrc[e];
     }
     V = Vl; T = Tl; rmin = Rl; wlo = Wl;
     if (pr.C) C = Cl;
   } else {
     V = Vg;
-    T = gptr((const int64_t *)pr.T);
     rmin = gptr((const uint8_t *)pr.rmin);
-    // (the window bounds decide which rows a step reads: out of memory they would be a third round trip)
-    int32_t *Wl = (int32_t *)lds;
-    for (int e = tid; e < nch; e += nt) Wl[e] = pr.wlo[e];
+    int64_t *Tl = (int64_t *)lds;
+    int32_t *Wl = (int32_t *)(Tl + kTracebackSums + 1);
+    if (tid >= 64) {
+      if (sums)
+        for (int e = tid - 64; e <= N; e += nt - 64) Tl[e] = pr.T[e];
+      for (int e = tid - 64; e < nch; e += nt - 64) Wl[e] = pr.wlo[e];
+    }
+    T = Tl;
     wlo = Wl;
     if (pr.C) C = gptr((const int64_t *)pr.C);
   }
-  if (choose) __syncthreads();  // the choice is in pr.res
-  // forced > 0: the plan of exactly `forced` stages (Algorithm 1's own answer V[S][|B|][D]), if
-  // that level holds one; forced = 0: the best level chosen by the solve; forced < 0: no plan wanted
-  int ns = (*pr.status == 0 && forced >= 0) ? (int)pr.res[1] : 0;
-  if (forced > 0 && *pr.status == 0)
-    ns = (forced <= pr.S_eff && Vg[(int64_t)(forced - 1) * lvl + (int64_t)N * DP + D - 1] != INF) ? forced : 0;
-  for (int u = ns + tid; u < plan_stride; u += nt) { se[u] = -1; rp[u] = -1; }
+  const int ns = traceback_stages<VT>(pr, sh, forced, results, choose);
   if (ns == 0) return;
   if constexpr (STAGED) {
     // 16-byte copies (a level of V is a multiple of 32 bytes), eight reads in flight per lane (index
@@ -2174,46 +2148,66 @@ __device__ void traceback_body(const ProblemDev &pr, int plan_stride, int32_t *s
       for (int k = 0; k < 8; ++k)
         if (e0 + k * (int64_t)nt < nquad) ((Quad *)Vl)[e0 + k * (int64_t)nt] = r[k];
     }
+    __syncthreads();
   }
-  __syncthreads();  // the copies, and the key words
+  auto sum_at = [&](int i) -> int64_t { return sums ? T[i] : pr.T[i]; };
   int j = N, d = D;
   VT v = V[(int64_t)(ns - 1) * lvl + (int64_t)N * DP + D - 1];
-  int64_t Tj = T[N];
+  int64_t Tj = sum_at(N);
   int step = 0;
   for (int s = ns; s >= 2; --s) {
     VP Vp = V + (int64_t)(s - 2) * lvl;
     const int jj = j - 1, c = jj >> 6;
     const uint64_t Cj = C ? (uint64_t)C[j] : 0ull;  // send time of the cut after block j (0 for j = N)
     const int first = max(s - 1, min(wlo[c], j));   // earlier rows hold no stage that fits
-    const int lo = s - 1, hi = d - 1, width = (hi - lo + 8) >> 3;  // d' = lo..hi in eighths of this width
+    const int low = s - 2, most = d - (s - 1);      // V[..][low] is d' = s-1; replicas left for this stage
+    const double inv_v = 1.0 / (double)v;
+    uint64_t hc = 0;
+    if (Cj) hc = (Cj + (uint64_t)lane) / (uint64_t)(lane + 1);
     unsigned key = 0xFFFFFFFFu;
     for (int i0 = first; i0 < j && key == 0xFFFFFFFFu; i0 += nt) {  // rows ascend: the first match is the smallest
       const int b = step % 3, p = step & 1;
       if (i0 + 64 * wave < j) {  // (the window rarely fills the workgroup; the other waves would only take issue slots)
         const int i = min(i0 + tid, j - 1);
-        VP row = Vp + (int64_t)i * DP - 1;  // row[d']
+        VP row = Vp + (int64_t)i * DP;  // row[d' - 1]
+        const int rmn = (int)rmin[unit_index(nch, i, c) * 64 + (jj & 63)];
+        const int64_t Ti = sum_at(i);
+        const int rt = least_replicas((uint64_t)(Tj - Ti), Cj, (uint64_t)v, inv_v, hc, most);
+        int base = max(d - min(rt, d) - 8, 0);  // eight values, up to V[..][d - rt] if that exists
         VT a[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) a[k] = row[min(lo + (k + 1) * width - 1, hi)];
-        const int rmn = (int)rmin[unit_index(nch, i, c) * 64 + (jj & 63)];
-        const int64_t Ti = T[i];
-        int at = lo;
+        for (int k = 0; k < 8; ++k) a[k] = row[base + k];
+        const int top = d - max(rt, rmn) - 1;
+        bool ok = top >= low && i0 + tid < j;
+        if (__any(ok && top < base)) {  // the bytes need more replicas than the time
+          if (ok && top < base) {
+            base = max(top - 7, 0);
 #pragma unroll
-        for (int k = 0; k < 8; ++k) at += a[k] > v ? width : 0;  // (a prefix of the probes lies above v)
-        bool ok = a[7] <= v && i0 + tid < j;
-        int dp = at;
-        VT my_a = INF;
+            for (int k = 0; k < 8; ++k) a[k] = row[base + k];
+          }
+        }
+        unsigned within = 0;  // (non-increasing: the upper ones)
 #pragma unroll
-        for (int k = 0; k < 8; ++k) a[k] = row[min(at + min(k, width - 1), hi)];
-#pragma unroll
-        for (int k = 7; k >= 0; --k)
-          if (a[k] <= v) { dp = min(at + min(k, width - 1), hi); my_a = a[k]; }
-        const int r = d - dp;
-        ok = ok && r >= rmn && stage_time_completes((uint64_t)(Tj - Ti), Cj, max(r, 1), (uint64_t)my_a, (uint64_t)v);
+        for (int k = 0; k < 8; ++k) within |= a[k] <= v ? 1u << k : 0u;
+        ok = ok && ((within >> ((top - base) & 31)) & 1u);
         const unsigned long long m = __ballot(ok);
         if (m != 0ull && lane == __ffsll((long long)m) - 1) {
-          atomicMin(&sh.key[b], ((unsigned)i << 8) | (unsigned)dp);
-          sh.value[p][wave] = (uint64_t)my_a;
+          while ((within & 1u) && base > 0) {  // the row is flat here: further down
+            base = max(base - 8, 0);
+            within = 0;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) a[k] = row[base + k];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) within |= a[k] <= v ? 1u << k : 0u;
+          }
+          // (the first place that holds a value of at most v; below a window without one, the window above's first)
+          const int k = within ? __ffs((int)within) - 1 : 8;
+          VT mine = a[0];
+#pragma unroll
+          for (int u = 1; u < 8; ++u) mine = k == u ? a[u] : mine;
+          if (k == 8) mine = row[base + 8];
+          atomicMin(&sh.key[b], ((unsigned)i << 8) | (unsigned)(base + k + 1));
+          sh.value[p][wave] = (uint64_t)mine;
           sh.T[p][wave] = Ti;
         }
       }
@@ -2228,18 +2222,112 @@ __device__ void traceback_body(const ProblemDev &pr, int plan_stride, int32_t *s
       }
     }
     if (key == 0xFFFFFFFFu) {  // tables inconsistent: report no plan rather than walk on
-      for (int u = tid; u < plan_stride; u += nt) { se[u] = -1; rp[u] = -1; }
+      if (tid == 0) sh.ns = 0;
       return;
     }
     const int i_sel = (int)(key >> 8), d_sel = (int)(key & 255u);
-    if (tid == 0) { se[s - 1] = j; rp[s - 1] = d - d_sel; }
+    if (tid == 0) { sh.end[s - 1] = j; sh.replicas[s - 1] = d - d_sel; }
     j = i_sel;
     d = d_sel;
   }
-  if (tid == 0) { se[0] = j; rp[0] = d; }
+  if (tid == 0) { sh.end[0] = j; sh.replicas[0] = d; }
 }
 
-
+// Plan recovery for the split objective: the candidate kept by a cell is the first one, in scan
+// order, whose sum equals the cell's value.  All threads of the workgroup evaluate the candidates
+// of one cell, numbered in scan order and several per thread with their reads in flight together; the
+// smallest matching number wins.
+template <typename VT>
+__device__ void traceback_split_body(const ProblemDev &pr, TracebackLds &sh, int forced, const PlanResults &results, bool choose) {
+  constexpr VT INF = Lim<VT>::inf;
+  const int N = pr.N, D = pr.D, DP = pr.DP, nch = pr.nch;
+  const int tid = threadIdx.x, nt = blockDim.x;
+  const int64_t lvl = (int64_t)(N + 1) * DP;
+  const VT RANNC_GLOBAL *V = gptr((const VT *)pr.V), *VF = gptr((const VT *)pr.VF), *VB = gptr((const VT *)pr.VB);
+  const int64_t RANNC_GLOBAL *T = gptr((const int64_t *)pr.T), *TB = gptr((const int64_t *)pr.TB);
+  const uint8_t RANNC_GLOBAL *rmin = gptr((const uint8_t *)pr.rmin);
+  // the stage times are valued from the prefix sums (the level kernel has not built their tables)
+  __shared__ double inv[64];
+  if (tid < 64) inv[tid] = 1.0 / (double)(tid + 1);
+  const bool quick = pr.time_limit <= kCeilDivMax;
+  const int ns = traceback_stages<VT>(pr, sh, forced, results, choose);
+  if (ns == 0) return;
+  auto share = [&](int64_t x, int r) -> VT {
+    if (quick) return ceil_div<VT>((VT)x, r, inv[r - 1]);
+    return (VT)(((uint64_t)x + (uint64_t)(r - 1)) / (uint64_t)r);
+  };
+  int j = N, d = D, step = 0;
+  VT v = V[(int64_t)(ns - 1) * lvl + (int64_t)N * DP + D - 1];
+  for (int s = ns; s >= 2; --s, ++step) {
+    const int b = step % 3, p = step & 1;
+    const int jj = j - 1, c = jj >> 6;
+    const int64_t Tj = T[j], TBj = TB[j], Cj = pr.C ? pr.C[j] : 0;
+    const int nd = d - (s - 1);                       // d' = s-1 .. d-1
+    const int from = max(s - 1, min(pr.wlo[c], j));   // earlier rows hold no stage that fits
+    const int total = (j - from) * nd;                // i = from .. j-1
+    const float inv_nd = 1.0f / (float)nd;
+    unsigned mine = 0xFFFFFFFFu;
+    VT sum_v = 0;
+    constexpr int U = 2;
+    for (int e0 = tid; e0 < total && mine == 0xFFFFFFFFu; e0 += U * nt) {
+      VT f[U], g[U];
+      int64_t Ti[U], TBi[U];
+      int rm[U], row[U], dd[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int e = min(e0 + u * nt, total - 1);
+        int q = (int)((float)e * inv_nd);  // e / nd, corrected
+        q -= q * nd > e ? 1 : 0;
+        q += (q + 1) * nd <= e ? 1 : 0;
+        row[u] = from + q;
+        dd[u] = s - 1 + e - q * nd;
+        const int64_t pc = (int64_t)(s - 2) * lvl + (int64_t)row[u] * DP + dd[u] - 1;
+        f[u] = VF[pc];
+        g[u] = VB[pc];
+        rm[u] = (int)rmin[unit_index(nch, row[u], c) * 64 + (jj & 63)];
+        Ti[u] = T[row[u]];
+        TBi[u] = TB[row[u]];
+      }
+#pragma unroll
+      for (int u = U - 1; u >= 0; --u) {
+        // (few candidates get past what their parts alone allow: neither the earlier stages nor this one may take
+        // more than v)
+        const int r = d - dd[u];
+        const uint64_t x = (uint64_t)(Tj - Ti[u]) + (uint64_t)(TBj - TBi[u]) + (uint64_t)Cj;
+        if (f[u] == INF || f[u] + g[u] > v || r < rm[u] || !at_most_times(x, (uint64_t)v, (uint32_t)r)) continue;
+        const VT hf = share(Tj - Ti[u], r) + (Cj ? share(Cj, r) : (VT)0), hb = share(TBj - TBi[u], r);
+        if ((VT)(vmax(f[u], hf) + vmax(g[u], hb)) == v) {  // (i, d') ascends with e
+          mine = ((unsigned)row[u] << 8) | (unsigned)dd[u];
+          sum_v = f[u] + g[u];
+        }
+      }
+    }
+    const unsigned key_mine = mine;
+    unsigned best = mine;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) best = min(best, (unsigned)__shfl_xor(best, o));
+    if (best != 0xFFFFFFFFu && key_mine == best) {  // (candidates are distinct: one lane)
+      atomicMin(&sh.key[b], best);
+      sh.value[p][tid >> 6] = (uint64_t)sum_v;
+      sh.T[p][tid >> 6] = (int64_t)best;
+    }
+    if (best == 0xFFFFFFFFu && (tid & 63) == 0) sh.T[p][tid >> 6] = -1;
+    __syncthreads();
+    const unsigned key = sh.key[b];
+    if (tid == 0) sh.key[(step + 2) % 3] = 0xFFFFFFFFu;
+    if (key == 0xFFFFFFFFu) {  // tables inconsistent: report no plan rather than walk on
+      if (tid == 0) sh.ns = 0;
+      return;
+    }
+    for (int w = 0; w < nt / 64; ++w)
+      if (sh.T[p][w] == (int64_t)key) v = (VT)sh.value[p][w];
+    const int i_sel = (int)(key >> 8), d_sel = (int)(key & 255u);
+    if (tid == 0) { sh.end[s - 1] = j; sh.replicas[s - 1] = d - d_sel; }
+    j = i_sel;
+    d = d_sel;
+  }
+  if (tid == 0) { sh.end[0] = j; sh.replicas[0] = d; }
+}
 
 // Outer driver (Algorithm 2 "form_stage" of Sec. III-C), the loops over the solved batch: node
 // counts n = 1, 2, 4, ... in turn, for each the stage counts S ascending over
@@ -2271,8 +2359,8 @@ __device__ __forceinline__ FormStageChoice form_stage_choose(const ProblemDev *_
       if (q < bad_q) { bad_q = q; bad_st = st; }
       continue;
     }
-    const int n = f.pair_n[q];
-    const int64_t mb = f.pair_mb[q];
+    const int n = pr.D / f.devices_per_node;
+    const int64_t mb = pr.MB;
     const int lo = f.devices_per_node * (n - 1) + 1;
     const int hi = min(min(f.devices_per_node * n, f.N), pr.S_eff);
     const int64_t lvl = (int64_t)(pr.N + 1) * pr.DP, cell = (int64_t)pr.N * pr.DP + pr.D - 1;
@@ -2306,16 +2394,25 @@ __device__ __forceinline__ FormStageChoice form_stage_choose(const ProblemDev *_
       break;
     }
   }
+  // the smallest n and S, then the smallest estimate, then the first search of the batch
+  auto least = [](auto v) {
 #pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    const int ok = __shfl_xor(best_k, o), oq = __shfl_xor(best_q, o), op = __shfl_xor(best_p, o);
-    const int64_t oe = __shfl_xor(best_e, o), ov = __shfl_xor(best_v, o);
-    if (ok < best_k || (ok == best_k && (oe < best_e || (oe == best_e && oq < best_q)))) {
-      best_k = ok; best_e = oe; best_v = ov; best_q = oq; best_p = op;
-    }
-    const int obq = __shfl_xor(bad_q, o), obs = __shfl_xor(bad_st, o);
-    if (obq < bad_q) { bad_q = obq; bad_st = obs; }
+    for (int o = 32; o >= 1; o >>= 1) v = min(v, __shfl_xor(v, o));
+    return v;
+  };
+  const int k_min = least(best_k);
+  const int64_t e_min = least(best_k == k_min ? best_e : INT64_MAX);
+  const int q_min = least(best_k == k_min && best_e == e_min ? best_q : NONE);
+  if (__any(bad_q != NONE)) {
+    const int first = least(bad_q);
+    const unsigned long long m = __ballot(bad_q == first);
+    bad_st = __shfl(bad_st, __ffsll((long long)m) - 1);
+    bad_q = first;
   }
+  const int winner = __ffsll((long long)__ballot(best_q == q_min)) - 1;
+  best_k = k_min; best_e = e_min; best_q = q_min;
+  best_p = __shfl(best_p, winner);
+  best_v = __shfl(best_v, winner);
   const bool found = bad_q == NONE && best_q != NONE;
   if (lane == 0) {
     f.rec[0] = found ? best_q : -1;
@@ -2331,20 +2428,37 @@ __device__ __forceinline__ FormStageChoice form_stage_choose(const ProblemDev *_
   return c;
 }
 
-// The chosen search's plan, copied behind the record (which may live in host memory: it is only
-// written here), and the flag word that tells the host.
-__device__ __forceinline__ void plan_to_record(int plan_stride, const int32_t *se, const int32_t *rp, const FormStageIn &f) {
-  __syncthreads();  // the walk's stores, by this workgroup's first thread, are visible to all of it
-  if (threadIdx.x >= 64) return;  // (the wave that wrote the record: see results_to_host)
-  int32_t *plan = (int32_t *)(f.rec + 6);
-  if (se)
-    for (int u = threadIdx.x; u < plan_stride; u += 64) {
-      plan[u] = se[u];
-      plan[plan_stride + u] = rp[u];
+// The plan to the caller's arrays, and behind the outer driver's record or to the host's mirror of the
+// results (both may live in host memory: they are only written here), then the flag word that tells the host,
+// which polls it.  One wave writes all of it: the release of the flag word then waits for its own stores
+// (with every wave of the workgroup fencing the system this took 4.8 us instead of 1.8).
+__device__ __forceinline__ void plan_out(const ProblemDev &pr, int plan_stride, int32_t *se, int32_t *rp, const TracebackLds &sh,
+                                         const FormStageIn &f, const PlanResults &r) {
+  __syncthreads();
+  const int lane = threadIdx.x, q = pr.q;
+  if (lane >= 64) return;
+  int32_t *const plan = f.rec ? (int32_t *)(f.rec + 6) : nullptr;
+  const bool host = r.h_flag != nullptr;
+  if (host && lane == 0) {
+    r.h_opt[q] = sh.chosen.opt;
+    r.h_est[q] = sh.chosen.est;
+    r.h_n_stages[q] = sh.chosen.n_stages;
+    r.h_status[q] = sh.chosen.status;
+  }
+  for (int u = lane; u < plan_stride; u += 64) {
+    const int32_t end = u < sh.ns ? sh.end[u] : -1, reps = u < sh.ns ? sh.replicas[u] : -1;
+    se[u] = end;
+    rp[u] = reps;
+    if (plan) { plan[u] = end; plan[plan_stride + u] = reps; }
+    if (host) {
+      r.h_stage_end[(int64_t)q * plan_stride + u] = end;
+      r.h_replicas[(int64_t)q * plan_stride + u] = reps;
     }
-  if (!f.flag) return;
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
-  if (threadIdx.x == 0) __hip_atomic_store(f.flag, f.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+  uint64_t *const flag = f.rec ? f.flag : host ? &r.h_flag[q] : nullptr;
+  if (!flag) return;
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");  // (of the whole wave, for the system)
+  if (lane == 0) __hip_atomic_store(flag, f.rec ? f.seq : r.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // The whole workgroup: the first wave makes the choice; false (and the record is complete) if there is none.
@@ -2356,28 +2470,11 @@ __device__ __forceinline__ bool form_stage_picked(const ProblemDev *__restrict__
   }
   __syncthreads();
   if (pick.at >= 0) return true;
-  plan_to_record(stride, nullptr, nullptr, f);
-  return false;
-}
-
-// The results of one search, copied to the host's mirror of the result buffer; behind them the
-// search's flag word tells the host, which polls it, that they are there.  One wave writes all of it:
-// the release of the flag word then waits for its own stores (with every wave of the workgroup fencing
-// the system this took 4.8 us instead of 1.8).
-__device__ __forceinline__ void results_to_host(const ProblemDev &pr, int plan_stride, const PlanResults &r) {
-  __syncthreads();  // this workgroup's stores to the device's buffer are visible to all of it
-  const int q = pr.q, lane = threadIdx.x;
-  if (lane >= 64) return;
-  if (lane == 0) r.h_opt[q] = r.d_opt[q];
-  if (lane == 1) r.h_est[q] = r.d_est[q];
-  if (lane == 2) r.h_n_stages[q] = r.d_n_stages[q];
-  if (lane == 3) r.h_status[q] = r.d_status[q];
-  for (int u = lane; u < plan_stride; u += 64) {
-    r.h_stage_end[(int64_t)q * plan_stride + u] = r.d_stage_end[(int64_t)q * plan_stride + u];
-    r.h_replicas[(int64_t)q * plan_stride + u] = r.d_replicas[(int64_t)q * plan_stride + u];
+  if (threadIdx.x == 0 && f.flag) {  // (the first wave has written the record and an empty plan)
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
+    __hip_atomic_store(f.flag, f.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");  // (of the whole wave, for the system)
-  if (lane == 0) __hip_atomic_store(&r.h_flag[q], r.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  return false;
 }
 
 __global__ __launch_bounds__(kTracebackThreads) void traceback_kernel(
@@ -2385,26 +2482,19 @@ __global__ __launch_bounds__(kTracebackThreads) void traceback_kernel(
     const int32_t *__restrict__ d_levels, const FormStageIn fs, const PlanResults results, int choose) {
   __shared__ TracebackLds sh;
   __shared__ FormStageChoice pick;
-  __shared__ __align__(16) char windows[4096];  // nch <= 1024 words
+  __shared__ __align__(16) char sums[8 * (kTracebackSums + 1) + 4096];  // and the window bounds: nch <= 1024 words
   if (fs.rec && !form_stage_picked(probs, fs, plan_stride, pick)) return;
   const ProblemDev pr = probs[fs.rec ? pick.at : (int)blockIdx.x];  // by value: no reloads after the plan stores
   const int forced = fs.rec ? pick.S : d_levels ? d_levels[pr.q] : 0;
-  int32_t *se = d_stage_end + (int64_t)pr.q * plan_stride;
-  int32_t *rp = d_replicas + (int64_t)pr.q * plan_stride;
   if (pr.VF) {  // split objective: first-match over all candidates
-    if (choose) {
-      if (threadIdx.x < 64) select_body(pr, results.d_opt, results.d_n_stages, results.d_est, results.d_status);
-      __syncthreads();
-    }
-    if (pr.bits == 32) traceback_split_body<uint32_t>(pr, plan_stride, se, rp, &sh.key[0], forced);
-    else traceback_split_body<uint64_t>(pr, plan_stride, se, rp, &sh.key[0], forced);
+    if (pr.bits == 32) traceback_split_body<uint32_t>(pr, sh, forced, results, choose != 0);
+    else traceback_split_body<uint64_t>(pr, sh, forced, results, choose != 0);
   } else if (pr.bits == 32) {
-    traceback_body<uint32_t, false>(pr, plan_stride, se, rp, sh, forced, windows, results, choose != 0);
+    traceback_body<uint32_t, false>(pr, sh, forced, sums, results, choose != 0);
   } else {
-    traceback_body<uint64_t, false>(pr, plan_stride, se, rp, sh, forced, windows, results, choose != 0);
+    traceback_body<uint64_t, false>(pr, sh, forced, sums, results, choose != 0);
   }
-  if (fs.rec) plan_to_record(plan_stride, se, rp, fs);
-  if (results.h_flag) results_to_host(pr, plan_stride, results);
+  plan_out(pr, plan_stride, d_stage_end + (int64_t)pr.q * plan_stride, d_replicas + (int64_t)pr.q * plan_stride, sh, fs, results);
 }
 
 // Plan recovery out of LDS, for launches of few, small min-max searches (the host checks that every
@@ -2418,12 +2508,9 @@ __global__ __launch_bounds__(kTracebackThreads) void traceback_lds_kernel(
   if (fs.rec && !form_stage_picked(probs, fs, plan_stride, pick)) return;
   const ProblemDev pr = probs[fs.rec ? pick.at : (int)blockIdx.x];
   const int forced = fs.rec ? pick.S : d_levels ? d_levels[pr.q] : 0;
-  int32_t *se = d_stage_end + (int64_t)pr.q * plan_stride;
-  int32_t *rp = d_replicas + (int64_t)pr.q * plan_stride;
-  if (pr.bits == 32) traceback_body<uint32_t, true>(pr, plan_stride, se, rp, sh, forced, staged, results, choose != 0);
-  else traceback_body<uint64_t, true>(pr, plan_stride, se, rp, sh, forced, staged, results, choose != 0);
-  if (fs.rec) plan_to_record(plan_stride, se, rp, fs);
-  if (results.h_flag) results_to_host(pr, plan_stride, results);
+  if (pr.bits == 32) traceback_body<uint32_t, true>(pr, sh, forced, staged, results, choose != 0);
+  else traceback_body<uint64_t, true>(pr, sh, forced, staged, results, choose != 0);
+  plan_out(pr, plan_stride, d_stage_end + (int64_t)pr.q * plan_stride, d_replicas + (int64_t)pr.q * plan_stride, sh, fs, results);
 }
 
 // ---------------------------------------------------------------------------------------
