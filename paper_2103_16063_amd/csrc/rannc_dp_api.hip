@@ -99,7 +99,7 @@ bool problem_sizes(int N, int D, int DP, int S_eff, int bits, bool split, bool p
   o->cost = align_up((size_t)cost);
   o->V = align_up((size_t)V);
   o->split = split;
-  o->keys = (split && packed) ? align_up((size_t)(N + 1) * (size_t)DP * 8) : 0;
+  o->keys = (split && packed) ? align_up((size_t)(N + 1) * (size_t)DP * 8 * rannc::kSplitKeyTables) : 0;
   return true;
 }
 

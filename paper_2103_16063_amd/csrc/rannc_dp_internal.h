@@ -89,7 +89,7 @@ struct ProblemDev {
   void *costb;                 // backward stage-time table, layout of cost; null when tb is null
   void *VF, *VB;               // largest forward / backward stage time of the plan behind each V entry
                                // (layout of V); null when tb is null
-  void *keys;                  // [DP][N+1] uint64: packed (value, i, d') winners of the level in flight;
+  void *keys;                  // kSplitKeyTables x [DP][N+1] uint64: packed (value, i) winners of a level;
                                // only with tb and a time bound the packing can hold, else null
   const int64_t *o;            // caller's bytes per cut (DEVICE), N entries, or null: no communication term
   int64_t bw;                  // bandwidth in bytes per microsecond (>= 1 when o is given)
@@ -190,6 +190,9 @@ hipError_t launch_level_split(const ProblemDev *probs, const LaunchShape &sh, in
 constexpr int64_t kSplitPackedMax = (1LL << 42) - 2;
 // rows per work item of a launch; the level launcher is given the same value
 int split_rows_per_item(const LaunchShape &sh, int DP);
+constexpr int kSplitMaxRows = 16;
+// key tables of a search: of the level in flight, of the one before, and one that is cleared for the next
+constexpr int kSplitKeyTables = 3;
 hipError_t launch_level_split_fast(const ProblemDev *probs, const LaunchShape &sh, int bits, int DP, int s,
                                    int rows_per_item, hipStream_t st);
 // (any of the outputs may be null: the choice itself is kept with the search)

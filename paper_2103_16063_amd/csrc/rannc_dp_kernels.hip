@@ -370,7 +370,7 @@ __device__ void setup_fill(const ProblemDev &pr, int levels_done, int64_t t0, in
   // every V entry behind the first levels_done levels "no plan" (padding columns d > D hold 0 so that padded rows stay sorted)
   typedef uint32_t Quad __attribute__((ext_vector_type(4)));
   if (pr.keys) {  // packed winners of the split level kernel: "none"
-    const int64_t nk = (int64_t)(pr.N + 1) * pr.DP;
+    const int64_t nk = (int64_t)(pr.N + 1) * pr.DP * kSplitKeyTables;
     for (int64_t e = t0; e < nk; e += stride) ((unsigned long long *)pr.keys)[e] = ~0ull;
   }
   void *tabs[3] = {pr.V, pr.VF, pr.VB};

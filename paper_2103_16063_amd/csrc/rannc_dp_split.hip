@@ -128,20 +128,105 @@ template <typename VT> constexpr VT split_nofit() { return sizeof(VT) == 8 ? (VT
 __device__ __forceinline__ uint32_t split_sum(uint32_t f, uint32_t b) { return __builtin_elementwise_add_sat(f, b); }
 __device__ __forceinline__ uint64_t split_sum(uint64_t f, uint64_t b) { return f + b; }
 
+// The key table of level s.
+__device__ __forceinline__ unsigned long long RANNC_GLOBAL *split_keys(const ProblemDev &pr, int s) {
+  return gptr((unsigned long long *)pr.keys) + (int64_t)(s % kSplitKeyTables) * (pr.N + 1) * pr.DP;
+}
+
+// Cell (j, d) of level s >= 2 whose packed winner is key: eight lanes look for the first d' of the winner's row
+// i whose sum is the cell's value (there is one), each at every eighth d'; the lane that finds it calls
+// out(value, forward, backward maximum).  inv[r] = 1 / r.  Bound by latency: one round of reads.
+constexpr int kFinalizeLanes = 8;
+template <typename VT, typename Out>
+__device__ __forceinline__ void split_winner(const ProblemDev &pr, const int s, const int j, const int d,
+                                             const unsigned long long key, const double *inv, Out out) {
+  const int N = pr.N, DP = pr.DP, sub = threadIdx.x & (kFinalizeLanes - 1);
+  const int i = split_key_i<VT>(key);
+  const VT v = split_key_v<VT>(key);
+  const int64_t lvl = (int64_t)(N + 1) * DP;
+  const VT RANNC_GLOBAL *F = gptr((const VT *)pr.VF) + (int64_t)(s - 2) * lvl + (int64_t)i * DP - 1;
+  const VT RANNC_GLOBAL *B = gptr((const VT *)pr.VB) + (int64_t)(s - 2) * lvl + (int64_t)i * DP - 1;
+  const int rmn = (int)pr.rmin[unit_index(pr.nch, i, (j - 1) >> 6) * 64 + ((j - 1) & 63)];
+  const VT xf = (VT)(pr.T[j] - pr.T[i]), xb = (VT)(pr.TB[j] - pr.TB[i]), xc = pr.C ? (VT)pr.C[j] : (VT)0;
+#pragma unroll 1
+  for (int d1 = s - 1 + sub; d1 - sub <= d - 1; d1 += 2 * kFinalizeLanes) {
+    VT f[2], b[2];
+    unsigned mine = 0;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int dp = min(d1 + u * kFinalizeLanes, d - 1);
+      f[u] = F[dp];
+      b[u] = B[dp];
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int dp = d1 + u * kFinalizeLanes, r = max(d - dp, 1);
+      const double in = inv[r];
+      f[u] = vmax(f[u], (VT)(ceil_div<VT>(xf, r, in) + (xc ? ceil_div<VT>(xc, r, in) : (VT)0)));
+      b[u] = vmax(b[u], ceil_div<VT>(xb, r, in));
+      if (dp <= d - 1 && r >= rmn && split_sum(f[u], b[u]) == v) mine |= 1u << u;
+    }
+    // the smallest d' of the two rounds of eight
+    const int base = (threadIdx.x & 63) & ~(kFinalizeLanes - 1);
+    const unsigned m0 = (unsigned)(__ballot(mine & 1u) >> base) & ((1u << kFinalizeLanes) - 1u);
+    const unsigned m1 = (unsigned)(__ballot(mine & 2u) >> base) & ((1u << kFinalizeLanes) - 1u);
+    if (m0 | m1) {
+      const int u = m0 ? 0 : 1;
+      if (sub == __ffs((int)(m0 ? m0 : m1)) - 1) out(v, u ? f[1] : f[0], u ? b[1] : b[0]);
+      break;
+    }
+  }
+}
+
+// Sixty-four cells (j = 64 block .., d) of level s, by one workgroup of the level kernel's size: V and the two
+// maxima in memory.  Level s - 1's key table, which nothing reads any more, is cleared for level s + 2.
+constexpr int kSplitThreads = 64 * kSplitWaves;
+template <typename VT>
+__device__ __forceinline__ void split_winners(const ProblemDev &pr, const int s, const int block, const int d, const double *inv) {
+  const int N = pr.N, DP = pr.DP;
+  const int j = block * (kSplitThreads / kFinalizeLanes) + (int)(threadIdx.x / kFinalizeLanes);
+  if (j > N || d > pr.D) return;
+  const int64_t at = (int64_t)(d - 1) * (N + 1) + j;
+  if (s > 2 && (threadIdx.x & (kFinalizeLanes - 1)) == 0) split_keys(pr, s - 1)[at] = ~0ull;
+  const unsigned long long key = d >= s ? split_keys(pr, s)[at] : ~0ull;
+  if (key == ~0ull) return;  // no candidate: the cell keeps "no plan" (the eight lanes of a cell agree)
+  const int64_t e = (int64_t)(s - 1) * (int64_t)(N + 1) * DP + (int64_t)j * DP + d - 1;
+  split_winner<VT>(pr, s, j, d, key, inv, [&](VT v, VT f, VT b) {
+    ((VT *)pr.V)[e] = v;
+    ((VT *)pr.VF)[e] = f;
+    ((VT *)pr.VB)[e] = b;
+  });
+}
+
 // Candidates d' = lo..hi of one staged row against the device totals d_k, k >= K0, of this wave
-// (all of them lie above hi, so every (d', k) pair is a candidate).
+// (all of them lie above hi, so every (d', k) pair is a candidate).  Two d' at a time, written out: the lane
+// reads keep the compiler from unrolling the loop itself.  (Outer driver at 96 blocks / 256 blocks alone, whole
+// call: one at a time 535 / 209 us, two 521 / 203, four, which take a workgroup's registers off each compute
+// unit, 552 / 219.  Totals next to each other instead of eight apart, with a sliding window of times in
+// registers instead of two LDS reads per candidate: 207 us alone, but 588 for the driver, whose waves then
+// wait for the one with the most candidates at every row.)
+template <typename VT, int KP, int K0, int U>
+__device__ __forceinline__ void split_candidates(int dp, int d0, int lane, VT F, VT B, const VT *sf, const VT *sb, VT (&row_v)[KP]) {
+  VT af[U], ab[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) { af[u] = lane_bcast(F, dp + u - 1); ab[u] = lane_bcast(B, dp + u - 1); }
+  // the times of r = d_k - d' (>= 1; beyond the staged ones only for totals above D)
+  const VT *const f = sf + (d0 - dp - 1) * 64 + lane, *const b = sb + (d0 - dp - 1) * 64 + lane;
+#pragma unroll
+  for (int k = K0; k < KP; ++k) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      row_v[k] = vmin(row_v[k], split_sum(vmax(af[u], f[(kSplitWaves * k - u) * 64]), vmax(ab[u], b[(kSplitWaves * k - u) * 64])));
+  }
+}
 template <typename VT, int KP, int K0>
 __device__ __forceinline__ void split_segment(int lo, int hi, int d0, int lane, VT F, VT B, const VT *sf, const VT *sb,
                                               VT (&row_v)[KP]) {
-#pragma unroll 4
-  for (int dp = lo; dp <= hi; ++dp) {
-    const VT af = lane_bcast(F, dp - 1), ab = lane_bcast(B, dp - 1);
-#pragma unroll
-    for (int k = K0; k < KP; ++k) {
-      const int r = d0 + kSplitWaves * k - dp;  // >= 1; beyond the staged ones only for totals above D
-      row_v[k] = vmin(row_v[k], split_sum(vmax(af, sf[(r - 1) * 64 + lane]), vmax(ab, sb[(r - 1) * 64 + lane])));
-    }
-  }
+  int dp = lo;
+#pragma unroll 1
+  for (; dp + 1 <= hi; dp += 2) split_candidates<VT, KP, K0, 2>(dp, d0, lane, F, B, sf, sb, row_v);
+#pragma unroll 1
+  for (; dp <= hi; ++dp) split_candidates<VT, KP, K0, 1>(dp, d0, lane, F, B, sf, sb, row_v);
 }
 
 template <typename VT, int KP, int K0>
@@ -160,15 +245,12 @@ __device__ __forceinline__ void split_row(int dlo, int D, int d0, int lane, VT F
 // the D-s+1 totals (and counts) that are left at level s, over eight waves.
 template <typename VT, int DP, int KP>
 __device__ __forceinline__ void split_rows(const ProblemDev &pr, const int s, const int c, const int i_lo, const int i_hi,
-                                           VT (*sf)[DP * 64], VT (*sb)[DP * 64], const int n_buf) {
+                                           VT (*sf)[DP * 64], VT (*sb)[DP * 64], const int n_buf, const VT *rowF, const VT *rowB) {
   constexpr VT INF = Lim<VT>::inf;
   const int N = pr.N, D = pr.D, nch = pr.nch;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int jj = 64 * c + lane;
-  const int64_t lvl = (int64_t)(N + 1) * pr.DP;
-  const VT RANNC_GLOBAL *__restrict__ Fprev = gptr((const VT *)pr.VF) + (int64_t)(s - 2) * lvl;
-  const VT RANNC_GLOBAL *__restrict__ Bprev = gptr((const VT *)pr.VB) + (int64_t)(s - 2) * lvl;
   const uint8_t RANNC_GLOBAL *__restrict__ rmin = gptr((const uint8_t *)pr.rmin);
   const int64_t RANNC_GLOBAL *__restrict__ T = gptr((const int64_t *)pr.T);
   const int64_t RANNC_GLOBAL *__restrict__ TB = gptr((const int64_t *)pr.TB);
@@ -178,8 +260,8 @@ __device__ __forceinline__ void split_rows(const ProblemDev &pr, const int s, co
   auto load = [&](int i) -> Row {  // the next row's, while one is worked on (clamped into the item)
     const int ic = min(i, i_hi);
     Row r;
-    r.F = Fprev[(int64_t)ic * pr.DP + min(lane, D - 1)];  // lane q holds d' = q + 1
-    r.B = Bprev[(int64_t)ic * pr.DP + min(lane, D - 1)];
+    r.F = rowF[(ic - i_lo) * DP + min(lane, D - 1)];  // lane q holds d' = q + 1
+    r.B = rowB[(ic - i_lo) * DP + min(lane, D - 1)];
     r.rmn = rmin[unit_index(nch, ic, c) * 64 + lane];
     return r;
   };
@@ -241,7 +323,7 @@ __device__ __forceinline__ void split_rows(const ProblemDev &pr, const int s, co
     else lds_barrier();
   }
   if (jj >= N || jj + 1 < s) return;
-  unsigned long long RANNC_GLOBAL *K = gptr((unsigned long long *)pr.keys);
+  unsigned long long RANNC_GLOBAL *K = split_keys(pr, s);
 #pragma unroll
   for (int k = 0; k < KP; ++k) {
     const int dk = d0 + kSplitWaves * k;
@@ -251,15 +333,29 @@ __device__ __forceinline__ void split_rows(const ProblemDev &pr, const int s, co
   }
 }
 
+// items: workgroups of the grid that work on the level's items; the others, `blocks` to a device total from
+// s - 2 on, finish level s - 1.  Most rows of an item: kSplitMaxRows.
 template <typename VT, int DP>
-__global__ __launch_bounds__(64 * kSplitWaves) void level_split_fast_kernel(
-    const ProblemDev *__restrict__ probs, const int s) {
+__global__ __launch_bounds__(kSplitThreads) void level_split_fast_kernel(
+    const ProblemDev *__restrict__ probs, const int s, const int items, const int blocks) {
   const ProblemDev &pr = probs[blockIdx.z];
+  __shared__ double inv[65];
+  if (threadIdx.x < 64) inv[threadIdx.x + 1] = 1.0 / (double)(threadIdx.x + 1);
+  if ((int)blockIdx.x >= items) {
+    if (s - 1 > pr.S_eff || s == 2) return;  // (level 1 has no keys)
+    __syncthreads();
+    const int at = (int)blockIdx.x - items;
+    split_winners<VT>(pr, s - 1, at % blocks, s - 2 + at / blocks, inv);
+    return;
+  }
   if (s > pr.S_eff) return;
-  const int N = pr.N;
+  const int N = pr.N, D = pr.D;
   const int32_t RANNC_GLOBAL *__restrict__ runs = gptr((const int32_t *)pr.runs);
-  if ((int)blockIdx.x >= runs[0]) return;
-  const unsigned desc = (unsigned)runs[1 + blockIdx.x];
+  // (the item is read together with their number, at a place that every list has)
+  const int count = runs[0];
+  const unsigned desc = (unsigned)runs[1 + min((int)blockIdx.x, (int)max_runs(pr.nch) - 1)];
+  asm volatile("" :: "s"(count), "s"(desc));
+  if ((int)blockIdx.x >= count) return;
   const int c = (int)((desc >> 16) & 0x3ffu), i0 = (int)(desc & 0xffffu), rows = (int)(desc >> 26) + 1;
   if (64 * c + 64 < s) return;  // no column j >= s in this chunk
   const int i_hi = min(min(i0 + rows - 1, 64 * c + 63), N - 1);
@@ -267,11 +363,37 @@ __global__ __launch_bounds__(64 * kSplitWaves) void level_split_fast_kernel(
   if (i_hi < i_lo) return;
   constexpr int BUF = 4 * DP * 64 * (int)sizeof(VT) <= 64 * 1024 ? 2 : 1;
   __shared__ VT sf[BUF][DP * 64], sb[BUF][DP * 64];
-#define RANNC_ROWS(K)                                                                              \
-  case K:                                                                                          \
-    if constexpr (kSplitWaves * K <= DP) split_rows<VT, DP, K>(pr, s, c, i_lo, i_hi, sf, sb, BUF); \
+  // the two maxima of the item's rows at level s - 1
+  __shared__ VT rowF[kSplitMaxRows * DP], rowB[kSplitMaxRows * DP];
+  const int n = i_hi - i_lo + 1;
+  if (s == 2) {
+    const VT RANNC_GLOBAL *F = gptr((const VT *)pr.VF) + (int64_t)i_lo * pr.DP, *B = gptr((const VT *)pr.VB) + (int64_t)i_lo * pr.DP;
+    for (int e = threadIdx.x; e < n * DP; e += kSplitThreads) {
+      const int64_t at = (int64_t)(e / DP) * pr.DP + min(e % DP, pr.DP - 1);
+      rowF[e] = F[at];
+      rowB[e] = B[at];
+    }
+  } else {
+    for (int e = threadIdx.x; e < n * DP; e += kSplitThreads) rowF[e] = rowB[e] = Lim<VT>::inf;
+    __syncthreads();
+    const unsigned long long RANNC_GLOBAL *K = split_keys(pr, s - 1);
+    const int nd = D - s + 1;  // d' = s-1 .. D-1
+    for (int e = (int)(threadIdx.x / kFinalizeLanes); e < n * nd; e += kSplitThreads / kFinalizeLanes) {
+      const int q = e / nd, d = s - 1 + e - q * nd;
+      const unsigned long long key = K[(int64_t)(d - 1) * (N + 1) + i_lo + q];
+      if (key != ~0ull)
+        split_winner<VT>(pr, s - 1, i_lo + q, d, key, inv, [&](VT, VT f, VT b) {
+          rowF[q * DP + d - 1] = f;
+          rowB[q * DP + d - 1] = b;
+        });
+    }
+  }
+  __syncthreads();
+#define RANNC_ROWS(K)                                                                                          \
+  case K:                                                                                                      \
+    if constexpr (kSplitWaves * K <= DP) split_rows<VT, DP, K>(pr, s, c, i_lo, i_hi, sf, sb, BUF, rowF, rowB); \
     break;
-  switch ((pr.D - s + kSplitWaves) / kSplitWaves) {
+  switch ((D - s + kSplitWaves) / kSplitWaves) {
     RANNC_ROWS(1) RANNC_ROWS(2) RANNC_ROWS(3) RANNC_ROWS(4)
     RANNC_ROWS(5) RANNC_ROWS(6) RANNC_ROWS(7) RANNC_ROWS(8)
     default: break;
@@ -279,64 +401,15 @@ __global__ __launch_bounds__(64 * kSplitWaves) void level_split_fast_kernel(
 #undef RANNC_ROWS
 }
 
-// Packed winners of level s into V and the two carried maxima; clears the key table for the next level.
-// Eight lanes per cell look for the first d' of the winner's row i whose sum is the cell's value (there is
-// one), each at every eighth d'.  Bound by latency: the key, then one round of reads.
-constexpr int kFinalizeLanes = 8;
+// The winners of a launch's last level.
 template <typename VT>
-__global__ __launch_bounds__(256) void split_finalize_kernel(const ProblemDev *__restrict__ probs, const int s) {
+__global__ __launch_bounds__(kSplitThreads) void split_finalize_kernel(const ProblemDev *__restrict__ probs, const int s) {
   const ProblemDev &pr = probs[blockIdx.z];
-  if (s > pr.S_eff) return;
+  if (s != pr.S_eff) return;  // (those of shorter searches are done)
   __shared__ double inv[65];
-  const int N = pr.N, D = pr.D, DP = pr.DP;
-  const int sub = threadIdx.x & (kFinalizeLanes - 1);
-  const int j = blockIdx.x * (256 / kFinalizeLanes) + (int)(threadIdx.x / kFinalizeLanes), d = blockIdx.y + 1;
-  unsigned long long *K = (unsigned long long *)pr.keys + (int64_t)(d - 1) * (N + 1) + j;
-  const unsigned long long key = j <= N && d <= D ? *K : ~0ull;
   if (threadIdx.x < 64) inv[threadIdx.x + 1] = 1.0 / (double)(threadIdx.x + 1);
   __syncthreads();
-  if (key == ~0ull) return;  // no candidate: the cell keeps "no plan" (the eight lanes of a cell agree)
-  const int i = split_key_i<VT>(key);
-  const VT v = split_key_v<VT>(key);
-  const int64_t lvl = (int64_t)(N + 1) * DP;
-  const VT RANNC_GLOBAL *F = gptr((const VT *)pr.VF) + (int64_t)(s - 2) * lvl + (int64_t)i * DP - 1;
-  const VT RANNC_GLOBAL *B = gptr((const VT *)pr.VB) + (int64_t)(s - 2) * lvl + (int64_t)i * DP - 1;
-  const int rmn = (int)pr.rmin[unit_index(pr.nch, i, (j - 1) >> 6) * 64 + ((j - 1) & 63)];
-  const VT xf = (VT)(pr.T[j] - pr.T[i]), xb = (VT)(pr.TB[j] - pr.TB[i]), xc = pr.C ? (VT)pr.C[j] : (VT)0;
-#pragma unroll 1
-  for (int d1 = s - 1 + sub; d1 - sub <= d - 1; d1 += 2 * kFinalizeLanes) {
-    VT f[2], b[2];
-    unsigned mine = 0;
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int dp = min(d1 + u * kFinalizeLanes, d - 1);
-      f[u] = F[dp];
-      b[u] = B[dp];
-    }
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int dp = d1 + u * kFinalizeLanes, r = max(d - dp, 1);
-      const double in = inv[r];
-      f[u] = vmax(f[u], (VT)(ceil_div<VT>(xf, r, in) + (xc ? ceil_div<VT>(xc, r, in) : (VT)0)));
-      b[u] = vmax(b[u], ceil_div<VT>(xb, r, in));
-      if (dp <= d - 1 && r >= rmn && split_sum(f[u], b[u]) == v) mine |= 1u << u;
-    }
-    // the smallest d' of the two rounds of eight
-    const int base = (threadIdx.x & 63) & ~(kFinalizeLanes - 1);
-    const unsigned m0 = (unsigned)(__ballot(mine & 1u) >> base) & ((1u << kFinalizeLanes) - 1u);
-    const unsigned m1 = (unsigned)(__ballot(mine & 2u) >> base) & ((1u << kFinalizeLanes) - 1u);
-    if (m0 | m1) {
-      const int u = m0 ? 0 : 1;
-      if (sub == __ffs((int)(m0 ? m0 : m1)) - 1) {
-        const int64_t e = (int64_t)(s - 1) * lvl + (int64_t)j * DP + d - 1;
-        ((VT *)pr.V)[e] = v;
-        ((VT *)pr.VF)[e] = u ? f[1] : f[0];
-        ((VT *)pr.VB)[e] = u ? b[1] : b[0];
-        *K = ~0ull;  // ready for the next level
-      }
-      break;
-    }
-  }
+  split_winners<VT>(pr, s, blockIdx.x, blockIdx.y + 1, inv);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -376,23 +449,25 @@ hipError_t launch_level_split(const ProblemDev *p, const LaunchShape &sh, int bi
 // 166 / 137 / 133 / 135 / 146.
 int split_rows_per_item(const LaunchShape &sh, int DP) {
   const int64_t groups = DP == 8 ? 256 : DP == 64 ? 2560 : 1024;
-  const int64_t rows = std::min<int64_t>(16, (sh.wide_rows + groups - 1) / groups);
+  const int64_t rows = std::min<int64_t>(kSplitMaxRows, (sh.wide_rows + groups - 1) / groups);
   int64_t most = 0;  // rows of the largest search: its list has room for single-row items up to a size
   for (int c = 0; c < sh.max_nch; ++c) most += std::min(64 * c + 64, sh.max_N);
   return (int)std::max<int64_t>(most > kSplitSmallRows ? 4 : 1, rows);
 }
 
 template <typename VT>
-static void split_fast_go(const ProblemDev *p, const LaunchShape &sh, int DP, int s, int64_t items, hipStream_t st) {
+static void split_fast_go(const ProblemDev *p, const LaunchShape &sh, int DP, int s, int items, hipStream_t st) {
+  constexpr int cells = kSplitThreads / kFinalizeLanes;
+  const int blocks = (sh.max_N + cells) / cells;
   for (int q0 = 0; q0 < sh.nprob; q0 += 65535) {
     const int nq = min(65535, sh.nprob - q0);
-    const dim3 grid((unsigned)items, 1, nq), block(64 * kSplitWaves);
-    if (DP == 8) hipLaunchKernelGGL((level_split_fast_kernel<VT, 8>), grid, block, 0, st, p + q0, s);
-    else if (DP == 16) hipLaunchKernelGGL((level_split_fast_kernel<VT, 16>), grid, block, 0, st, p + q0, s);
-    else if (DP == 32) hipLaunchKernelGGL((level_split_fast_kernel<VT, 32>), grid, block, 0, st, p + q0, s);
-    else hipLaunchKernelGGL((level_split_fast_kernel<VT, 64>), grid, block, 0, st, p + q0, s);
-    hipLaunchKernelGGL((split_finalize_kernel<VT>), dim3((sh.max_N + 256 / kFinalizeLanes) / (256 / kFinalizeLanes), sh.max_D, nq), dim3(256), 0, st,
-                       p + q0, s);
+    const dim3 grid((unsigned)(items + (s > 2 ? blocks * (sh.max_D - s + 3) : 0)), 1, nq), block(kSplitThreads);
+    if (DP == 8) hipLaunchKernelGGL((level_split_fast_kernel<VT, 8>), grid, block, 0, st, p + q0, s, items, blocks);
+    else if (DP == 16) hipLaunchKernelGGL((level_split_fast_kernel<VT, 16>), grid, block, 0, st, p + q0, s, items, blocks);
+    else if (DP == 32) hipLaunchKernelGGL((level_split_fast_kernel<VT, 32>), grid, block, 0, st, p + q0, s, items, blocks);
+    else hipLaunchKernelGGL((level_split_fast_kernel<VT, 64>), grid, block, 0, st, p + q0, s, items, blocks);
+    if (s == sh.max_S_eff)
+      hipLaunchKernelGGL((split_finalize_kernel<VT>), dim3(blocks, sh.max_D, nq), block, 0, st, p + q0, s);
   }
 }
 
@@ -401,8 +476,9 @@ hipError_t launch_level_split_fast(const ProblemDev *p, const LaunchShape &sh, i
   const int per = rows_per_item;
   int64_t items = 0;  // upper bound on the items of any problem of the launch
   for (int c = 0; c < sh.max_nch; ++c) items += (min(64 * c + 64, sh.max_N) + per - 1) / per;
-  if (bits == 32) split_fast_go<uint32_t>(p, sh, DP, s, items, st);
-  else split_fast_go<uint64_t>(p, sh, DP, s, items, st);
+  if (per > kSplitMaxRows) return hipErrorInvalidValue;
+  if (bits == 32) split_fast_go<uint32_t>(p, sh, DP, s, (int)items, st);
+  else split_fast_go<uint64_t>(p, sh, DP, s, (int)items, st);
   return hipGetLastError();
 }
 
