@@ -398,8 +398,11 @@ int rannc_dp_get_timing(rannc_dp_t *h, float *out_ms, int32_t *out_level_launche
 
 // chosen != null: the caller waits for the batch before the handle is used again, and the plan recovery
 // behind it can choose the stage counts; *chosen = whether that has been done here already.
+// results != null: a solve that is one launch over few searches recovers their plans there as well;
+// *recovered = whether it has.
 static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream, int64_t *d_opt, int32_t *d_n_stages,
-                      int64_t *d_est_iter_ns, int32_t *d_status, bool *chosen) {
+                      int64_t *d_est_iter_ns, int32_t *d_status, bool *chosen, int32_t plan_stride = 0,
+                      const rannc::PlanResults *results = nullptr, bool *recovered = nullptr) {
   if (!h || !d_opt || !d_n_stages) return RANNC_DP_INVALID_ARG;
   int rc = check_batch(&h->lim, b);
   if (rc != RANNC_DP_OK) return rc;
@@ -711,12 +714,16 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
     }
   }
   if (timing) ok = ok && hipEventRecord(h->ev[1], st) == hipSuccess;
-  int max_levels = 0;
+  int max_levels = 0, in_one = 0;
+  for (int k = 0; k < 4; ++k) in_one += fused[k] && shape[k].nprob == Q ? 1 : 0;
+  const bool recover = results && in_one && !timing;
+  if (recovered) *recovered = recover;
   for (int k = 0; k < 4; ++k) {
     if (fused[k]) {
       ok = ok && rannc::launch_solve_small(src + cls_start[k], dp + cls_start[k], shape[k].nprob, h->bits, kClasses[k], fused_direct[k], d_opt,
                                            d_n_stages, d_est_iter_ns, d_status,
-                                           shape[k].nprob == 1 ? &probs[cls_start[k]] : nullptr, cs[k]) == hipSuccess;
+                                           shape[k].nprob == 1 ? &probs[cls_start[k]] : nullptr, plan_stride,
+                                           recover ? results : nullptr, cs[k]) == hipSuccess;
       ok = ok && staging_read();
       h->level_launches++;
     } else {
@@ -926,9 +933,9 @@ int rannc_dp_solve_to_host(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_s
     // (a call of another layout may have left a result here that equals seq, which starts at 1)
     std::memset(flags, 0, 8 * (size_t)Q);
   }
-  bool chosen = false;
-  rc = solve_impl(h, b, hip_stream, r.d_opt, r.d_n_stages, r.d_est, r.d_status, &chosen);
-  if (rc == RANNC_DP_OK)
+  bool chosen = false, recovered = false;
+  rc = solve_impl(h, b, hip_stream, r.d_opt, r.d_n_stages, r.d_est, r.d_status, &chosen, plan_stride, poll ? &r : nullptr, &recovered);
+  if (rc == RANNC_DP_OK && !recovered)
     rc = traceback_impl(h, hip_stream, nullptr, plan_stride, r.d_stage_end, r.d_replicas, nullptr, &r, !chosen);
   if (rc == RANNC_DP_OK && !poll &&
       (hipMemcpyAsync(h_results, d_results, at.total, hipMemcpyDeviceToHost, st) != hipSuccess ||

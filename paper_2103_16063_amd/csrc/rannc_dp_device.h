@@ -65,6 +65,21 @@ __device__ __forceinline__ uint64_t lane_bcast(uint64_t v, int q) {
   return ((uint64_t)hi << 32) | lo;
 }
 
+// Smallest value of the wave (all lanes active), the same in every lane.  Four steps inside the rows of
+// sixteen lanes without the LDS crossbar, then the four rows through scalar registers.
+__device__ __forceinline__ uint32_t wave_min(uint32_t v) {
+  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0xB1, 0xF, 0xF, false));   // quad_perm 1 0 3 2
+  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x4E, 0xF, 0xF, false));   // quad_perm 2 3 0 1
+  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x141, 0xF, 0xF, false));  // row_half_mirror
+  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x140, 0xF, 0xF, false));  // row_mirror
+  return min(min(lane_bcast(v, 0), lane_bcast(v, 16)), min(lane_bcast(v, 32), lane_bcast(v, 48)));
+}
+__device__ __forceinline__ uint64_t wave_min(uint64_t v) {
+  const uint32_t hi = wave_min((uint32_t)(v >> 32));
+  const uint32_t lo = wave_min((uint32_t)(v >> 32) == hi ? (uint32_t)v : ~0u);
+  return (uint64_t)hi << 32 | lo;
+}
+
 // ceil(x / r) for any 1 <= r <= 64 from the correctly rounded reciprocal 1/r, in double precision:
 //     t = x + (r/2 - 1 + r o)     y = t (1/r) + 1.5 2^52     (one fused multiply-add)
 // t / r = (x + r - 1)/r - 1/2 + o, and the fraction of (x + r - 1)/r is at most 63/64, so t (1/r) lies

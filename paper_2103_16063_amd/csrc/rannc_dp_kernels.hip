@@ -159,15 +159,13 @@ __device__ __forceinline__ void pass_entries(const ProblemDev &pr, int i, int c,
 // the value table (a lane's D values are a row of V, so writing them from here would scatter every
 // store instruction over 64 cache lines).  with_times = false: only the fits-in-memory part (rmin,
 // ufit) and level 1 are produced, for searches whose level kernel recomputes the stage times.
-// lds_rmin: the unit's 64 rmin bytes also go there (255 for a lane without a stage).  stages: what
-// pass_entries wants to know of the lane's stage.
+// stages: what the lists of stages that fit want to know of the lane's stage.
 template <typename VT> struct UnitStages { bool fits; int rmin; VT tij; };
 template <typename VT, int DP, bool NODIV = false>
 __device__ __forceinline__ bool build_unit(const ProblemDev &pr, const int64_t *T, const int64_t *P,
                                            const int64_t *A, const int64_t *Cc, int i, int c, int lane,
                                            VT *lds_level1, int ls, int row0, const int64_t *TBp = nullptr,
-                                           const bool with_times = true, uint8_t *lds_rmin = nullptr,
-                                           UnitStages<VT> *stages = nullptr) {
+                                           const bool with_times = true, UnitStages<VT> *stages = nullptr) {
   const int N = pr.N, D = pr.D, nch = pr.nch;
   const int jj = 64 * c + lane;
   const bool valid = (jj >= i) && (jj < N);
@@ -190,7 +188,6 @@ __device__ __forceinline__ bool build_unit(const ProblemDev &pr, const int64_t *
   const int64_t u = unit_index(nch, i, c);
   if (lane == 0) pr.ufit[u] = (uint8_t)unit_fits;
   if (stages) *stages = {fits, rmin, (VT)Tij};
-  if (lds_rmin) lds_rmin[lane] = (uint8_t)(valid ? rmin : 255);  // the caller's copy: every lane, 255 = no stage
   if (!valid) return unit_fits;
   pr.rmin[u * 64 + lane] = (uint8_t)rmin;
   // A unit in which no stage fits for any r is never read (every reader consults ufit or rmin
@@ -237,7 +234,7 @@ void build_kernel(const ProblemDev *__restrict__ probs, const int parts, const i
     const bool level1 = i == 0 && (parts & 1);
     UnitStages<VT> st;
     (void)build_unit<VT, DP, true>(pr, pr.T, pr.P, pr.A, pr.C, i, c, lane, level1 ? tile : nullptr, DP + 1, 64 * c + 1,
-                                   pr.TB, (parts & 2) != 0, nullptr, &st);
+                                   pr.TB, (parts & 2) != 0, &st);
     if ((parts & 1) && pr.ends && pr.S_eff > 1) {
       const uint32_t *const rec = pass_chunks(pr) + 4 * c;
       pass_entries<VT>(pr, i, c, lane, st.fits, st.rmin, st.tij, pr.wlo[c], PassChunk{rec[0], rec[1], rec[2], rec[3]}, pr.ends + pr.N);
@@ -1021,7 +1018,7 @@ __global__ __launch_bounds__(NT) void prepare_kernel(const ProblemDev *src, Prob
     for (int c = own + part; c < behind; c += in.parts) {
       UnitStages<VT> st;
       (void)build_unit<VT, DP, true>(pr, sT, sP, sA, comm ? sC : nullptr, i, c, lane, nullptr, 0, 0, bwd ? sTB : nullptr, TIMES,
-                                     nullptr, &st);
+                                     &st);
       if (passes) pass_entries<VT>(pr, i, c, lane, st.fits, st.rmin, st.tij, s_w[c], s_rec[c], esum);
     }
     if (part != 0) continue;
@@ -1617,271 +1614,6 @@ void level_merge_one_kernel(const ProblemDev pr, const int s) {
 }
 
 // ---------------------------------------------------------------------------------------
-// Whole search of a SMALL problem (N <= 128, i.e. at most two column chunks) in one workgroup and
-// one launch: prefix sums, tables, every level, choice of the stage count.  Same arithmetic as the
-// kernels above (the same build_unit / row_merge), but two consecutive levels of V
-// live in LDS, so the waves of the workgroup fold their merges with LDS atomics and meet at
-// workgroup barriers: no launch per level, no global atomics.  Every level is also copied to the
-// V table in memory (plan recovery and export read it there).  Meant for searches at the
-// paper's own scale (k = 32 blocks, D <= 32, Sec. IV-A) and for batches of them (the many
-// form_stage_dp calls of Algorithm 2): one workgroup per search.
-// ---------------------------------------------------------------------------------------
-constexpr int kSmallMaxN = 128;
-// Sixteen waves per search, eight where a lane's value array alone takes 64 registers or more (64
-// devices, or 64-bit values from 32 devices on): with the 128 registers of sixteen waves those
-// kernels spilled up to 1 600 registers per lane.
-constexpr int kSmallWavesMax = 16;
-template <typename VT, int DP> constexpr int small_waves() { return sizeof(VT) * DP >= 256 ? 8 : kSmallWavesMax; }
-
-struct Chosen { int64_t opt, est; int n_stages, status; };
-__device__ __forceinline__ Chosen select_finish(const ProblemDev &pr, int64_t v, int st, int64_t *d_opt,
-                                                int32_t *d_n_stages, int64_t *d_est, int32_t *d_status);
-
-// Waves per SIMD the one-launch kernel is compiled for.  The recomputing form on 32-bit values at 16
-// devices needs 70 registers left alone, one wave per SIMD short of TWO workgroups per compute unit
-// (16 waves each); held to 64 registers the two rounds of a batch of 512 searches run side by side.
-template <typename VT, int DP, bool DIRECT> constexpr int small_waves_per_simd() {
-  return (DIRECT && sizeof(VT) == 4 && DP == 16) ? 8 : small_waves<VT, DP>() / 4;
-}
-
-template <typename VT, int DP, bool DIRECT>
-__global__ __launch_bounds__((64 * small_waves<VT, DP>())) __attribute__((amdgpu_waves_per_eu((small_waves_per_simd<VT, DP, DIRECT>()))))
-void solve_small_kernel(
-    const ProblemDev *src, ProblemDev *probs, int64_t *d_opt, int32_t *d_n_stages, int64_t *d_est,
-    int32_t *d_status, const ProblemDev one, int use_one) {
-  __shared__ __align__(8) uint32_t desc[sizeof(ProblemDev) / 4];
-  const ProblemDev pr = fetch_problem(src + blockIdx.x, probs + blockIdx.x, true, desc, one, use_one);
-  constexpr VT INF = Lim<VT>::inf;
-  constexpr int LS = DP + 1;  // row stride of a level in LDS: lanes (= columns) hit different banks
-  constexpr int kSmallWaves = small_waves<VT, DP>();
-  constexpr int NT = 64 * kSmallWaves;
-  __shared__ int64_t sT[kSmallMaxN + 1], sP[kSmallMaxN + 1], sA[kSmallMaxN + 1], sC[kSmallMaxN + 1];
-  __shared__ unsigned long long s_max_cut;
-  // levels of V in LDS: the one being read and the one being folded into; the recomputing form keeps
-  // a third, cleared while a level runs, so that a level costs one workgroup barrier instead of two
-  constexpr int kLevelBufs = DIRECT ? 3 : 2;
-  __shared__ VT lv[kLevelBufs][(kSmallMaxN + 1) * LS];
-  __shared__ VT s_top[64];
-  __shared__ int s_flags, s_wlo[2];
-  // DIRECT: the stage times are recomputed from the prefix sums in LDS (as the recomputing level
-  // kernel does), and the fits-in-memory bytes of all units stay in LDS too: no table is written and
-  // the levels read nothing from memory
-  constexpr int kUnits = kSmallMaxN + 64;  // 64 rows of chunk 0, then up to 128 rows of chunk 1
-  __shared__ uint8_t s_rmin[DIRECT ? kUnits * 64 : 64];
-  const int N = pr.N, D = pr.D, nch = pr.nch, S_eff = pr.S_eff;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-
-  // ---- prefix sums and validation (as setup_kernel) ----
-  if (tid == 0) {
-    s_flags = 0; s_wlo[0] = kNoRow; s_wlo[1] = kNoRow; s_max_cut = 0ull; sC[0] = 0;
-    if (pr.o) pr.C[0] = 0;
-  }
-  int myflags = 0;
-  __syncthreads();
-  if (tid < N && pr.o) {  // per-cut send time (as setup_kernel)
-    const uint64_t c = cut_time(pr.o[tid], pr.bw, myflags);
-    sC[tid + 1] = (tid + 1 < N) ? (int64_t)c : 0;
-    pr.C[tid + 1] = sC[tid + 1];  // plan recovery values the stages from the prefix sums in memory
-    if (tid + 1 < N && c) atomicMax(&s_max_cut, (unsigned long long)c);
-  }
-  // A wave per array, two blocks per lane, so that the sums need no barrier (a scan over the workgroup had
-  // fourteen; whole call, 16 blocks: 26.1 -> 24.8 us, the outer driver at 32 blocks: 102.2 -> 98.8 us).
-  if (wave < 3) {
-    const int64_t *in = wave == 0 ? pr.t : wave == 1 ? pr.p : pr.a;
-    int64_t *out = wave == 0 ? pr.T : wave == 1 ? pr.P : pr.A;
-    int64_t *sout = wave == 0 ? sT : wave == 1 ? sP : sA;
-    uint64_t u[2];
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      int64_t v = 2 * lane + k < N ? in[2 * lane + k] : 0;
-      if (v < 0) { myflags |= 1; v = 0; }
-      u[k] = (uint64_t)v;
-      if (u[k] >= kSumLimit) { myflags |= 2; u[k] = kSumLimit; }
-    }
-    uint64_t sum = u[0] + u[1];  // of the lanes up to this one; every sum saturates at kSumLimit
-    sum = sum > kSumLimit ? kSumLimit : sum;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const uint64_t below = (uint64_t)__shfl_up((unsigned long long)sum, off);
-      if (lane >= off) sum += below;
-      sum = sum > kSumLimit ? kSumLimit : sum;
-    }
-    uint64_t before = (uint64_t)__shfl_up((unsigned long long)sum, 1);
-    if (lane == 0) before = 0;
-    const uint64_t mid = before + u[0] > kSumLimit ? kSumLimit : before + u[0];
-    if (sum >= kSumLimit) myflags |= 2;  // (the largest of the lane's sums; beyond block N it stays the last one)
-    if (2 * lane < N) { sout[2 * lane + 1] = (int64_t)mid; out[2 * lane + 1] = (int64_t)mid; }
-    if (2 * lane + 1 < N) { sout[2 * lane + 2] = (int64_t)sum; out[2 * lane + 2] = (int64_t)sum; }
-  }
-  if (tid == 0) { sT[0] = sP[0] = sA[0] = 0; pr.T[0] = pr.P[0] = pr.A[0] = 0; }
-  if (myflags) atomicOr(&s_flags, myflags);
-  // level 1 buffer: "no plan" everywhere, padding columns 0
-  for (int e = tid; e < (N + 1) * LS; e += NT) lv[0][e] = ((e % LS) < D) ? INF : (VT)0;
-  if constexpr (DIRECT)  // level 2's buffer as well
-    for (int e = tid; e < (N + 1) * LS; e += NT) lv[1][e] = ((e % LS) < D) ? INF : (VT)0;
-  __syncthreads();
-  int st = RANNC_DP_PROBLEM_OK;
-  if (s_flags & 1) st = RANNC_DP_PROBLEM_NEGATIVE_INPUT;
-  else if (s_flags & 2) st = RANNC_DP_PROBLEM_SUM_OVERFLOW;
-  else if ((uint64_t)sT[N] + s_max_cut > (uint64_t)pr.time_limit) st = RANNC_DP_PROBLEM_TIME_TOO_LARGE;
-  if (tid == 0) *pr.status = st;
-
-  // ---- tables (as build_kernel): rows 0..min(63,N-1) of chunk 0, then rows 0..N-1 of chunk 1 ----
-  const int R0 = min(64, N), RT = R0 + (nch > 1 ? N : 0);
-  for (int f = wave; f < RT; f += kSmallWaves) {
-    const int c = f >= R0, i = c ? f - R0 : f;
-    const bool fits = build_unit<VT, DP>(pr, sT, sP, sA, pr.o ? sC : nullptr, i, c, lane, lv[0], LS, 0, nullptr,
-                                         !DIRECT, DIRECT ? s_rmin + f * 64 : nullptr);
-    if (fits && lane == 0) atomicMin(&s_wlo[c], i);
-  }
-  __syncthreads();
-  if (tid < nch) pr.wlo[tid] = s_wlo[tid];
-  const int64_t lvl = (int64_t)(N + 1) * DP;
-  VT RANNC_GLOBAL *Vg = gptr((VT *)pr.V);
-  const VT RANNC_GLOBAL *cost = gptr((const VT *)pr.cost);
-  const uint8_t RANNC_GLOBAL *rmin = gptr((const uint8_t *)pr.rmin);
-  // level 1 to memory
-  for (int e = tid; e < (N + 1) * DP; e += NT) Vg[e] = lv[0][(e / DP) * LS + (e % DP)];
-  if (tid == 0) s_top[0] = lv[0][N * LS + D - 1];
-
-  // ---- levels 2..S_eff ----
-  [[maybe_unused]] DirectConsts<DP> kc;
-  if constexpr (DIRECT) direct_consts_init(kc);
-  // passes of the recomputing form (see the level loop): P0 for the triangle of chunk 0, then F1 for
-  // the rectangle and P1 for the triangle of chunk 1
-  const int W0 = R0, W1 = nch > 1 ? N - 64 : 1;
-  const int lg0 = W0 > 1 ? 32 - __builtin_clz(W0 - 1) : 0, lg1 = W1 > 1 ? 32 - __builtin_clz(W1 - 1) : 0;
-  const int P0 = (W0 / 2 + (64 >> lg0)) >> (6 - lg0);
-  const int F1 = nch > 1 ? 64 >> (6 - lg1) : 0;
-  const int P1 = nch > 1 ? (W1 / 2 + (64 >> lg1)) >> (6 - lg1) : 0;
-  [[maybe_unused]] const int RTP = P0 + F1 + P1;
-  for (int s = 2; s <= S_eff; ++s) {
-    // level s lives in buffer (s-1) mod kLevelBufs
-    const VT *prev = lv[(s - 2) % kLevelBufs];  // level s-1
-    VT *cur = lv[(s - 1) % kLevelBufs];         // level s
-    const int rl = D - s + 1;
-    if constexpr (!DIRECT) {
-      for (int e = tid; e < (N + 1) * LS; e += NT) cur[e] = ((e % LS) < D) ? INF : (VT)0;
-      lds_barrier();  // LDS only: the copy of the previous level to memory stays in flight
-    }
-    if constexpr (DIRECT) {
-      // One pass of a wave = 64 (row, column) pairs, one per lane, so that no lane idles on the
-      // triangular blocks.  A diagonal block of W columns (rows base..base+W-1) is cut into groups of
-      // LG = 2^lg >= W lanes, G = 64 / LG groups to a pass; group number p (0..W/2) covers row base+p on
-      // the lanes l >= p (columns l) and, for 0 < p < W-p, row base+W-p on the lanes l < p (columns
-      // l+W-p): W lanes of work where a row alone has W-p.  The rectangular block of chunk 1 (rows
-      // 0..63, W1 columns) runs G1 rows to a pass the same way.  Every lane reads its own a[] row
-      // from LDS and folds its own column in, so a pass may mix rows freely.
-      for (int f = wave; f < RTP; f += kSmallWaves) {
-        const int c = f >= P0;
-        if (64 * c + 64 < s) continue;
-        int row, col;
-        bool valid;
-        if (c && f < P0 + F1) {
-          const int l = lane & ((1 << lg1) - 1);
-          row = ((f - P0) << (6 - lg1)) + (lane >> lg1);
-          col = l;
-          valid = l < W1;
-        } else {
-          const int W = c ? W1 : W0, lg = c ? lg1 : lg0;
-          const int l = lane & ((1 << lg) - 1);
-          const int p = ((c ? f - P0 - F1 : f) << (6 - lg)) + (lane >> lg);
-          const bool second = l < p;
-          valid = l < W && 2 * p <= W && (!second || 2 * p < W);
-          row = 64 * c + (second ? W - p : p);
-          col = second ? l + W - p : l;
-        }
-        if (!valid) { row = 64 * c; col = 0; }
-        const int jj = 64 * c + col;
-        const int rmn = s_rmin[((c ? R0 : 0) + row) * 64 + col];  // 255 outside the stage's range
-        // the row must be able to end s-1 stages: i >= s-1, and some (s-1)-stage plan covers blocks 1..i
-        const bool act = valid && rmn <= rl && row >= s - 1 && row >= s_wlo[c] && prev[row * LS + D - 1] != INF;
-        if (__ballot(act) == 0ull) continue;
-        const VT tij = (VT)(sT[min(jj + 1, N)] - sT[row]);
-#define RANNC_ROW(HH)                                                                                \
-  {                                                                                                  \
-    constexpr int H = (HH) <= DP ? (HH) : DP;                                                        \
-    const int sig = merge_shift(s, DP, H);                                                           \
-    VT x[H];                                                                                         \
-    _Pragma("unroll") for (int t = 0; t < H; ++t) x[t] = prev[row * LS + sig + t];                   \
-    row_merge_direct<VT, H>(x, tij, rmn, act, kc);                                                   \
-    if (act && jj + 1 >= s) {                                                                        \
-      /* no test per entry: columns D.. hold 0 and keep it, column DP (t + 1 + sig <= DP) is padding */ \
-      VT *dst = cur + (jj + 1) * LS + 1 + sig;                                                       \
-      _Pragma("unroll") for (int t = 0; t < H; ++t) atomicMin(&dst[t], x[t]);                        \
-    }                                                                                                \
-  }
-        if (rl <= 8) RANNC_ROW(8)
-        else if (rl <= 16) RANNC_ROW(16)
-        else if (rl <= 24) RANNC_ROW(24)
-        else RANNC_ROW(32)
-#undef RANNC_ROW
-      }
-    } else {
-      for (int f = wave; f < RT; f += kSmallWaves) {
-        const int c = f >= R0, i = c ? f - R0 : f;
-        if (i < s - 1 || i < s_wlo[c] || 64 * c + 64 < s) continue;
-        if (prev[i * LS + D - 1] == INF) continue;  // no (s-1)-stage plan covers blocks 1..i
-        const int jj = 64 * c + lane;
-        const int64_t u = unit_index(nch, i, c);
-        int rmn = 255;
-        if (jj >= i && jj < N) rmn = rmin[u * 64 + lane];
-        const bool act = rmn <= rl;
-        if (__ballot(act) == 0ull) continue;
-        const int col = act ? lane : __ffsll((long long)__ballot(act)) - 1;
-        const VT RANNC_GLOBAL *unit = cost + u * 64 * D + col;
-        const VT off = act ? (VT)0 : INF;
-#define RANNC_ROW(K)                                                                                  \
-  case K:                                                                                             \
-    if constexpr (8 * K <= DP) {                                                                      \
-      constexpr int H = 8 * K;                                                                        \
-      const int sig = merge_shift(s, DP, H);                                                          \
-      VT x[H];                                                                                        \
-      row_merge<VT, H, const VT *>(x, unit, prev + i * LS + sig, off, rl);                            \
-      /* (no test per entry, as above; folding INF in is a no-op) */                                  \
-      if (act && jj + 1 >= s) {                                                                       \
-        VT *dst = cur + (jj + 1) * LS + 1 + sig;                                                      \
-        _Pragma("unroll") for (int t = 0; t < H; ++t) atomicMin(&dst[t], x[t]);                       \
-      }                                                                                               \
-    }                                                                                                 \
-    break;
-        switch ((rl + 7) >> 3) {
-          RANNC_ROW(1) RANNC_ROW(2) RANNC_ROW(3) RANNC_ROW(4)
-          RANNC_ROW(5) RANNC_ROW(6) RANNC_ROW(7) RANNC_ROW(8)
-          default: break;
-        }
-#undef RANNC_ROW
-      }
-    }
-    if constexpr (DIRECT) {
-      // The next level's buffer held level s-2: its last readers were the passes of level s-1, which
-      // the barrier before this level's passes closed, and its copy to memory was issued by these
-      // same threads before their passes of level s-1.
-      if (s < S_eff) {
-        VT *next = lv[s % kLevelBufs];
-        for (int e = tid; e < (N + 1) * LS; e += NT) next[e] = ((e % LS) < D) ? INF : (VT)0;
-      }
-    }
-    lds_barrier();
-    VT RANNC_GLOBAL *Vs = Vg + (int64_t)(s - 1) * lvl;
-    for (int e = tid; e < (N + 1) * DP; e += NT) Vs[e] = cur[(e / DP) * LS + (e % DP)];
-    if (tid == 0) s_top[s - 1] = cur[N * LS + D - 1];
-  }
-  __syncthreads();
-
-  // ---- choice of the stage count (as select_kernel) ----
-  if (wave == 0) {
-    int64_t v = INT64_MAX;
-    if (st == 0 && lane < S_eff) {
-      const VT u = s_top[lane];
-      v = (u == INF) ? INT64_MAX : (int64_t)u;
-    }
-    select_finish(pr, v, st, d_opt, d_n_stages, d_est, d_status);
-  }
-}
-
-// ---------------------------------------------------------------------------------------
 // DP level s >= 2, literal form: one thread per cell (j, d) scans every split point i
 // (ascending) and every device count d' of the earlier stages (ascending), skipping infeasible
 // predecessors and stages that do not fit, and keeps the first strict minimum -- the loops of
@@ -1934,17 +1666,13 @@ __global__ __launch_bounds__(64) void level_scan_kernel(const ProblemDev *__rest
 // One wave per problem, lane s-1 reads V[s][N][D] (S_eff <= D <= 64).
 // ---------------------------------------------------------------------------------------
 // one wave: lane s-1 brings V[s][N][D] (INT64_MAX beyond S_eff or if the status is bad)
+struct Chosen { int64_t opt, est; int n_stages, status; };
 __device__ __forceinline__ Chosen select_finish(const ProblemDev &pr, int64_t v, int st, int64_t *d_opt,
                                                 int32_t *d_n_stages, int64_t *d_est, int32_t *d_status) {
   const int lane = threadIdx.x & 63;
   const int q = pr.q;
   // the minimum; the first lane that holds it has the fewest stages
-  int64_t best = v;
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    const int64_t ov = __shfl_xor(best, o);
-    if (ov < best) best = ov;
-  }
+  const int64_t best = (int64_t)wave_min((uint64_t)v);  // (no value is negative)
   const int bs = best == INT64_MAX ? 0 : __ffsll((long long)__ballot(v == best));
   Chosen c = {best, INT64_MAX, bs, st};
   if (bs > 0) {
@@ -2025,21 +1753,24 @@ struct TracebackLds {
 __device__ __forceinline__ bool at_most_times(uint64_t x, uint64_t v, uint32_t r) {
   return __umul64hi(v, (uint64_t)r) != 0 || x <= v * (uint64_t)r;
 }
+__device__ __forceinline__ bool at_most_times(uint64_t x, uint32_t v, uint32_t r) { return x <= (uint64_t)v * r; }
 
-// The smallest r with ceil(x / r) + ceil(C / r) <= v, or more than `most`; inv_v = 1 / v in double precision,
-// hc: lane r - 1 of the wave holds ceil(C / r) (only with C).
-__device__ __forceinline__ int least_replicas(uint64_t x, uint64_t C, uint64_t v, double inv_v, uint64_t hc, int most) {
+// The smallest r with ceil(x / r) + ceil(C / r) <= v, or more than `most`; inv_v: about 1 / v; hc: lane r - 1 of
+// the wave holds ceil(C / r) (only with C).
+template <typename VT>
+__device__ __forceinline__ int least_replicas(uint64_t x, uint64_t C, VT v, float inv_v, uint64_t hc, int most) {
   if (v == 0) return x == 0 && C == 0 ? 1 : most + 1;
-  const double q = (double)(x + C) * inv_v;  // (off by far less than one below 2^7)
-  int r = max((int)min(q, 100.0), 1);
+  // ceil((x + C) / v), or above 64: below 2^7 the quotient is off by far less than one, so that its whole part is
+  // too small by at most two (n - 1 for a quotient just above n) and never too large by more than one
+  int r = max((int)min((float)(x + C) * inv_v, 100.0f), 1);
   if (r > 1 && at_most_times(x + C, v, (uint32_t)r - 1u)) --r;
-  if (!at_most_times(x + C, v, (uint32_t)r)) ++r;  // ceil((x + C) / v), or above 64
+  if (!at_most_times(x + C, v, (uint32_t)r)) ++r;
+  if (!at_most_times(x + C, v, (uint32_t)r)) ++r;
   if (C) {  // two ceilings may need some more
-    for (int more = 0; __any(more == 0); ) {
+    for (bool done = false; __any(!done);) {
       const uint64_t c = __shfl(hc, min(r, 64) - 1);
-      const bool ok = more || r > most || (c <= v && (v == c ? x == 0 : at_most_times(x, v - c, (uint32_t)r)));
-      if (ok) more = 1;
-      else ++r;
+      done = done || r > most || (c <= (uint64_t)v && at_most_times(x, (VT)(v - (VT)c), (uint32_t)r));
+      if (!done) ++r;
     }
   }
   return r;
@@ -2048,7 +1779,7 @@ __device__ __forceinline__ int least_replicas(uint64_t x, uint64_t C, uint64_t v
 // forced > 0: the plan of exactly `forced` stages (Algorithm 1's own answer V[S][|B|][D]), if that level
 // holds one; forced = 0: the best level chosen by the solve, or here (choose: select_body, by the first
 // wave); forced < 0: no plan wanted.  The first wave leaves ns and, chosen here or read (results), what
-// else the host is told in sh; every wave learns ns behind a barrier.  v_of(s): V[s][N][D].
+// else the host is told in sh; every wave learns ns behind a barrier.
 template <typename VT>
 __device__ __forceinline__ int traceback_stages(const ProblemDev &pr, TracebackLds &sh, int forced, const PlanResults &results,
                                                 bool choose) {
@@ -2074,94 +1805,20 @@ __device__ __forceinline__ int traceback_stages(const ProblemDev &pr, TracebackL
   return sh.ns;
 }
 
-// STAGED: everything the walk reads (the levels of V below the plan's, T, C, the window bounds, the
-// fits-in-memory bytes) is first copied into the workgroup's LDS with one round of independent reads,
-// and the walk then runs out of LDS.  Otherwise the window bounds and, up to kTracebackSums of them, the
-// prefix sums are (out of memory they would be another round trip).
-// lds: traceback_lds_bytes() bytes (not STAGED: kTracebackSums + 1 sums and nch words).
-constexpr int kTracebackSums = 2048;
-
-template <typename VT, bool STAGED>
-__device__ void traceback_body(const ProblemDev &pr, TracebackLds &sh, int forced, char *lds, const PlanResults &results, bool choose) {
-  const int N = pr.N, D = pr.D, DP = pr.DP, nch = pr.nch;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nt = blockDim.x;
-  const int64_t lvl = (int64_t)(N + 1) * DP;
-  const VT RANNC_GLOBAL *Vg = gptr((const VT *)pr.V);
-  using VP = std::conditional_t<STAGED, const VT *, const VT RANNC_GLOBAL *>;
-  using CP = std::conditional_t<STAGED, const int64_t *, const int64_t RANNC_GLOBAL *>;
-  using RP = std::conditional_t<STAGED, const uint8_t *, const uint8_t RANNC_GLOBAL *>;
-  typedef uint32_t Quad __attribute__((ext_vector_type(4)));
-  VP V;
-  CP C = nullptr;
-  RP rmin;
-  const int64_t *T;
-  const int32_t *wlo;
-  [[maybe_unused]] VT *Vl = (VT *)lds;
-  const bool sums = STAGED || N <= kTracebackSums;
-  // (the first wave looks for the stage count meanwhile)
-  if constexpr (STAGED) {
-    const int64_t nT = (((int64_t)(N + 1) * 8 + 31) / 32) * 32;
-    char *w = lds + (int64_t)pr.S_eff * lvl * (int64_t)sizeof(VT);  // room for every level
-    int64_t *Tl = (int64_t *)w; w += nT;
-    int64_t *Cl = (int64_t *)w; w += nT;
-    int32_t *Wl = (int32_t *)w; w += (((int64_t)nch * 4 + 31) / 32) * 32;
-    uint8_t *Rl = (uint8_t *)w;
-    // (every array starts on a 256-byte boundary of the workspace)
-    if (tid >= 64) {
-      for (int e = tid - 64; e <= N; e += nt - 64) {
-        Tl[e] = pr.T[e];
-        if (pr.C) Cl[e] = pr.C[e];
-      }
-      for (int e = tid - 64; e < nch; e += nt - 64) Wl[e] = pr.wlo[e];
-      const Quad RANNC_GLOBAL *rsrc = (const Quad RANNC_GLOBAL *)gptr((const uint8_t *)pr.rmin);
-      for (int64_t e = tid - 64; e < units_before(nch, N) * 4; e += nt - 64) ((Quad *)Rl)[e] = rsrc[e];
-    }
-    V = Vl; T = Tl; rmin = Rl; wlo = Wl;
-    if (pr.C) C = Cl;
-  } else {
-    V = Vg;
-    rmin = gptr((const uint8_t *)pr.rmin);
-    int64_t *Tl = (int64_t *)lds;
-    int32_t *Wl = (int32_t *)(Tl + kTracebackSums + 1);
-    if (tid >= 64) {
-      if (sums)
-        for (int e = tid - 64; e <= N; e += nt - 64) Tl[e] = pr.T[e];
-      for (int e = tid - 64; e < nch; e += nt - 64) Wl[e] = pr.wlo[e];
-    }
-    T = Tl;
-    wlo = Wl;
-    if (pr.C) C = gptr((const int64_t *)pr.C);
-  }
-  const int ns = traceback_stages<VT>(pr, sh, forced, results, choose);
-  if (ns == 0) return;
-  if constexpr (STAGED) {
-    // 16-byte copies (a level of V is a multiple of 32 bytes), eight reads in flight per lane (index
-    // clamped instead of tested, so that no branch separates them)
-    const Quad RANNC_GLOBAL *src = (const Quad RANNC_GLOBAL *)Vg;
-    const int64_t nquad = (int64_t)ns * lvl * (int64_t)sizeof(VT) / 16;
-    for (int64_t e0 = tid; e0 < nquad; e0 += 8 * (int64_t)nt) {
-      Quad r[8];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) r[k] = src[min(e0 + k * (int64_t)nt, nquad - 1)];
-#pragma unroll
-      for (int k = 0; k < 8; ++k)
-        if (e0 + k * (int64_t)nt < nquad) ((Quad *)Vl)[e0 + k * (int64_t)nt] = r[k];
-    }
-    __syncthreads();
-  }
-  auto sum_at = [&](int i) -> int64_t { return sums ? T[i] : pr.T[i]; };
+// The walk over the levels, by the whole workgroup.  at: where the tables are (row(s, i): V[s][i][1 ..]).
+template <typename VT, typename At>
+__device__ __forceinline__ void traceback_walk(const At &at, int N, int D, int ns, TracebackLds &sh) {
+  const int tid = threadIdx.x, lane = tid & 63, nt = blockDim.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int j = N, d = D;
-  VT v = V[(int64_t)(ns - 1) * lvl + (int64_t)N * DP + D - 1];
-  int64_t Tj = sum_at(N);
+  VT v = at.row(ns, N)[D - 1];
+  int64_t Tj = at.sum(N);
   int step = 0;
   for (int s = ns; s >= 2; --s) {
-    VP Vp = V + (int64_t)(s - 2) * lvl;
-    const int jj = j - 1, c = jj >> 6;
-    const uint64_t Cj = C ? (uint64_t)C[j] : 0ull;  // send time of the cut after block j (0 for j = N)
-    const int first = max(s - 1, min(wlo[c], j));   // earlier rows hold no stage that fits
+    const uint64_t Cj = at.send(j);  // send time of the cut after block j (0 for j = N)
+    const int first = max(s - 1, at.first(j));
     const int low = s - 2, most = d - (s - 1);      // V[..][low] is d' = s-1; replicas left for this stage
-    const double inv_v = 1.0 / (double)v;
+    const float inv_v = __builtin_amdgcn_rcpf((float)v);
     uint64_t hc = 0;
     if (Cj) hc = (Cj + (uint64_t)lane) / (uint64_t)(lane + 1);
     unsigned key = 0xFFFFFFFFu;
@@ -2169,10 +1826,10 @@ __device__ void traceback_body(const ProblemDev &pr, TracebackLds &sh, int force
       const int b = step % 3, p = step & 1;
       if (i0 + 64 * wave < j) {  // (the window rarely fills the workgroup; the other waves would only take issue slots)
         const int i = min(i0 + tid, j - 1);
-        VP row = Vp + (int64_t)i * DP;  // row[d' - 1]
-        const int rmn = (int)rmin[unit_index(nch, i, c) * 64 + (jj & 63)];
-        const int64_t Ti = sum_at(i);
-        const int rt = least_replicas((uint64_t)(Tj - Ti), Cj, (uint64_t)v, inv_v, hc, most);
+        const auto row = at.row(s - 1, i);  // row[d' - 1]
+        const int rmn = at.least(i, j);
+        const int64_t Ti = at.sum(i);
+        const int rt = least_replicas<VT>((uint64_t)(Tj - Ti), Cj, v, inv_v, hc, most);
         int base = max(d - min(rt, d) - 8, 0);  // eight values, up to V[..][d - rt] if that exists
         VT a[8];
 #pragma unroll
@@ -2231,6 +1888,101 @@ __device__ void traceback_body(const ProblemDev &pr, TracebackLds &sh, int force
     d = d_sel;
   }
   if (tid == 0) { sh.end[0] = j; sh.replicas[0] = d; }
+}
+
+// STAGED: everything the walk reads (the levels of V below the plan's, T, C, the window bounds, the
+// fits-in-memory bytes) is first copied into the workgroup's LDS with one round of independent reads,
+// and the walk then runs out of LDS.  Otherwise the window bounds and, up to kTracebackSums of them, the
+// prefix sums are (out of memory they would be another round trip).
+// lds: traceback_lds_bytes() bytes (not STAGED: up to kTracebackSums + 1 sums, and nch words).
+constexpr int kTracebackSums = 2048;
+
+template <typename VT, bool STAGED>
+__device__ void traceback_body(const ProblemDev &pr, TracebackLds &sh, int forced, char *lds, const PlanResults &results, bool choose) {
+  const int N = pr.N, D = pr.D, DP = pr.DP, nch = pr.nch;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nt = blockDim.x;
+  const int64_t lvl = (int64_t)(N + 1) * DP;
+  const VT RANNC_GLOBAL *Vg = gptr((const VT *)pr.V);
+  using VP = std::conditional_t<STAGED, const VT *, const VT RANNC_GLOBAL *>;
+  using CP = std::conditional_t<STAGED, const int64_t *, const int64_t RANNC_GLOBAL *>;
+  using RP = std::conditional_t<STAGED, const uint8_t *, const uint8_t RANNC_GLOBAL *>;
+  typedef uint32_t Quad __attribute__((ext_vector_type(4)));
+  VP V;
+  CP C = nullptr;
+  RP rmin;
+  const int64_t *T;
+  const int32_t *wlo;
+  [[maybe_unused]] VT *Vl = (VT *)lds;
+  const bool sums = STAGED || N <= kTracebackSums;
+  // (the first wave looks for the stage count meanwhile)
+  if constexpr (STAGED) {
+    const int64_t nT = (((int64_t)(N + 1) * 8 + 31) / 32) * 32;
+    char *w = lds + (int64_t)pr.S_eff * lvl * (int64_t)sizeof(VT);  // room for every level
+    int64_t *Tl = (int64_t *)w; w += nT;
+    int64_t *Cl = (int64_t *)w; w += nT;
+    int32_t *Wl = (int32_t *)w; w += (((int64_t)nch * 4 + 31) / 32) * 32;
+    uint8_t *Rl = (uint8_t *)w;
+    // (every array starts on a 256-byte boundary of the workspace)
+    if (tid >= 64) {
+      for (int e = tid - 64; e <= N; e += nt - 64) {
+        Tl[e] = pr.T[e];
+        if (pr.C) Cl[e] = pr.C[e];
+      }
+      for (int e = tid - 64; e < nch; e += nt - 64) Wl[e] = pr.wlo[e];
+      const Quad RANNC_GLOBAL *rsrc = (const Quad RANNC_GLOBAL *)gptr((const uint8_t *)pr.rmin);
+      for (int64_t e = tid - 64; e < units_before(nch, N) * 4; e += nt - 64) ((Quad *)Rl)[e] = rsrc[e];
+    }
+    V = Vl; T = Tl; rmin = Rl; wlo = Wl;
+    if (pr.C) C = Cl;
+  } else {
+    V = Vg;
+    rmin = gptr((const uint8_t *)pr.rmin);
+    int64_t *Tl = (int64_t *)lds;
+    int32_t *Wl = (int32_t *)(Tl + (sums ? N + 1 : 0));
+    if (tid >= 64) {
+      if (sums)
+        for (int e = tid - 64; e <= N; e += nt - 64) Tl[e] = pr.T[e];
+      for (int e = tid - 64; e < nch; e += nt - 64) Wl[e] = pr.wlo[e];
+    }
+    T = Tl;
+    wlo = Wl;
+    if (pr.C) C = gptr((const int64_t *)pr.C);
+  }
+  const int ns = traceback_stages<VT>(pr, sh, forced, results, choose);
+  if (ns == 0) return;
+  if constexpr (STAGED) {
+    // 16-byte copies (a level of V is a multiple of 32 bytes), eight reads in flight per lane (index
+    // clamped instead of tested, so that no branch separates them)
+    const Quad RANNC_GLOBAL *src = (const Quad RANNC_GLOBAL *)Vg;
+    const int64_t nquad = (int64_t)ns * lvl * (int64_t)sizeof(VT) / 16;
+    for (int64_t e0 = tid; e0 < nquad; e0 += 8 * (int64_t)nt) {
+      Quad r[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) r[k] = src[min(e0 + k * (int64_t)nt, nquad - 1)];
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        if (e0 + k * (int64_t)nt < nquad) ((Quad *)Vl)[e0 + k * (int64_t)nt] = r[k];
+    }
+    __syncthreads();
+  }
+  struct Tables {
+    VP V;
+    CP C;
+    RP rmin;
+    const int64_t *T, *Tg;
+    const int32_t *wlo;
+    int64_t lvl;
+    int DP, nch;
+    __device__ __forceinline__ VP row(int s, int i) const { return V + (int64_t)(s - 1) * lvl + (int64_t)i * DP; }
+    __device__ __forceinline__ int64_t sum(int i) const { return T ? T[i] : Tg[i]; }
+    __device__ __forceinline__ uint64_t send(int j) const { return C ? (uint64_t)C[j] : 0ull; }
+    __device__ __forceinline__ int first(int j) const { return min(wlo[(j - 1) >> 6], j); }  // earlier rows hold no stage that fits
+    __device__ __forceinline__ int least(int i, int j) const {
+      return (int)rmin[unit_index(nch, i, (j - 1) >> 6) * 64 + ((j - 1) & 63)];
+    }
+  };
+  traceback_walk<VT>(Tables{V, C, rmin, sums ? T : nullptr, pr.T, wlo, lvl, DP, nch}, N, D, ns, sh);
 }
 
 // Plan recovery for the split objective: the candidate kept by a cell is the first one, in scan
@@ -2395,11 +2147,7 @@ __device__ __forceinline__ FormStageChoice form_stage_choose(const ProblemDev *_
     }
   }
   // the smallest n and S, then the smallest estimate, then the first search of the batch
-  auto least = [](auto v) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v = min(v, __shfl_xor(v, o));
-    return v;
-  };
+  auto least = [](auto v) { return (decltype(v))wave_min((std::make_unsigned_t<decltype(v)>)v); };  // (no value is negative)
   const int k_min = least(best_k);
   const int64_t e_min = least(best_k == k_min ? best_e : INT64_MAX);
   const int q_min = least(best_k == k_min && best_e == e_min ? best_q : NONE);
@@ -2411,8 +2159,8 @@ __device__ __forceinline__ FormStageChoice form_stage_choose(const ProblemDev *_
   }
   const int winner = __ffsll((long long)__ballot(best_q == q_min)) - 1;
   best_k = k_min; best_e = e_min; best_q = q_min;
-  best_p = __shfl(best_p, winner);
-  best_v = __shfl(best_v, winner);
+  best_p = (int)lane_bcast((uint32_t)best_p, winner);
+  best_v = (int64_t)lane_bcast((uint64_t)best_v, winner);
   const bool found = bad_q == NONE && best_q != NONE;
   if (lane == 0) {
     f.rec[0] = found ? best_q : -1;
@@ -2511,6 +2259,343 @@ __global__ __launch_bounds__(kTracebackThreads) void traceback_lds_kernel(
   if (pr.bits == 32) traceback_body<uint32_t, true>(pr, sh, forced, staged, results, choose != 0);
   else traceback_body<uint64_t, true>(pr, sh, forced, staged, results, choose != 0);
   plan_out(pr, plan_stride, d_stage_end + (int64_t)pr.q * plan_stride, d_replicas + (int64_t)pr.q * plan_stride, sh, fs, results);
+}
+
+// ---------------------------------------------------------------------------------------
+// Whole search of a SMALL problem (N <= 128, i.e. at most two column chunks) in one workgroup and
+// one launch: prefix sums, tables, every level, choice of the stage count.  Same arithmetic as the
+// kernels above (the same build_unit / row_merge), but two consecutive levels of V
+// live in LDS, so the waves of the workgroup fold their merges with LDS atomics and meet at
+// workgroup barriers: no launch per level, no global atomics.  Every level is also copied to the
+// V table in memory (plan recovery and export read it there).  Meant for searches at the
+// paper's own scale (k = 32 blocks, D <= 32, Sec. IV-A) and for batches of them (the many
+// form_stage_dp calls of Algorithm 2): one workgroup per search.
+// ---------------------------------------------------------------------------------------
+constexpr int kSmallMaxN = 128;
+// Sixteen waves per search, eight where a lane's value array alone takes 64 registers or more (64
+// devices, or 64-bit values from 32 devices on): with the 128 registers of sixteen waves those
+// kernels spilled up to 1 600 registers per lane.
+constexpr int kSmallWavesMax = 16;
+template <typename VT, int DP> constexpr int small_waves() { return sizeof(VT) * DP >= 256 ? 8 : kSmallWavesMax; }
+
+// Waves per SIMD the one-launch kernel is compiled for.  The recomputing form on 32-bit values at 16
+// devices needs 70 registers left alone, one wave per SIMD short of TWO workgroups per compute unit
+// (16 waves each); held to 64 registers the two rounds of a batch of 512 searches run side by side.
+template <typename VT, int DP, bool DIRECT> constexpr int small_waves_per_simd() {
+  return (DIRECT && sizeof(VT) == 4 && DP == 16) ? 8 : small_waves<VT, DP>() / 4;
+}
+
+template <typename VT, int DP, bool DIRECT>
+__global__ __launch_bounds__((64 * small_waves<VT, DP>())) __attribute__((amdgpu_waves_per_eu((small_waves_per_simd<VT, DP, DIRECT>()))))
+void solve_small_kernel(
+    const ProblemDev *src, ProblemDev *probs, int64_t *d_opt, int32_t *d_n_stages, int64_t *d_est,
+    int32_t *d_status, const ProblemDev one, int use_one, int plan_stride, const PlanResults results) {
+  __shared__ __align__(8) uint32_t desc[sizeof(ProblemDev) / 4];
+  const ProblemDev pr = fetch_problem(src + blockIdx.x, probs + blockIdx.x, true, desc, one, use_one);
+  constexpr VT INF = Lim<VT>::inf;
+  constexpr int LS = DP + 1;  // row stride of a level in LDS: lanes (= columns) hit different banks
+  constexpr int kSmallWaves = small_waves<VT, DP>();
+  constexpr int NT = 64 * kSmallWaves;
+  __shared__ int64_t sT[kSmallMaxN + 1], sP[kSmallMaxN + 1], sA[kSmallMaxN + 1], sC[kSmallMaxN + 1];
+  __shared__ unsigned long long s_max_cut;
+  // levels of V in LDS: the one being read and the one being folded into; the recomputing form keeps
+  // a third, cleared while a level runs, so that a level costs one workgroup barrier instead of two
+  constexpr int kLevelBufs = DIRECT ? 3 : 2;
+  __shared__ VT levels[kLevelBufs * (kSmallMaxN + 1) * LS];
+  __shared__ VT s_top[64];
+  __shared__ int s_flags, s_wlo[2];
+  __shared__ Chosen s_chosen;
+  // DIRECT: the stage times are recomputed from the prefix sums in LDS (as the recomputing level
+  // kernel does), and the stages that fit are listed in LDS, row by row: no table is written and the levels
+  // read nothing from memory.  A word is { row, last block << 8, smallest r that fits << 16 }.
+  constexpr int kPairs = kSmallMaxN * (kSmallMaxN + 1) / 2 + 64;
+  __shared__ uint32_t s_word[DIRECT ? kPairs : 1];
+  __shared__ uint32_t s_end[DIRECT ? kSmallMaxN : 1], s_at[DIRECT ? kSmallMaxN + 1 : 1];
+  __shared__ uint64_t s_z[DIRECT ? kSmallMaxN + 1 : 1];
+  __shared__ int s_sum[2];
+  const int N = pr.N, D = pr.D, nch = pr.nch, S_eff = pr.S_eff;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // (a chain shorter than the longest one has room for more levels: for all of them, if it is short enough)
+  const int per_level = (N + 1) * LS;
+  const int bufs = DIRECT ? min(max(S_eff, kLevelBufs), kLevelBufs * (kSmallMaxN + 1) * LS / per_level) : kLevelBufs;
+  auto level = [&](int s) -> VT * { return levels + (s - 1) % bufs * per_level; };
+
+  // ---- prefix sums and validation (as setup_kernel) ----
+  if (tid == 0) {
+    s_flags = 0; s_wlo[0] = kNoRow; s_wlo[1] = kNoRow; s_max_cut = 0ull; sC[0] = 0;
+    if (pr.o) pr.C[0] = 0;
+  }
+  int myflags = 0;
+  __syncthreads();
+  if (tid < N && pr.o) {  // per-cut send time (as setup_kernel)
+    const uint64_t c = cut_time(pr.o[tid], pr.bw, myflags);
+    sC[tid + 1] = (tid + 1 < N) ? (int64_t)c : 0;
+    pr.C[tid + 1] = sC[tid + 1];  // plan recovery values the stages from the prefix sums in memory
+    if (tid + 1 < N && c) atomicMax(&s_max_cut, (unsigned long long)c);
+  }
+  // A wave per array, two blocks per lane, so that the sums need no barrier (a scan over the workgroup had
+  // fourteen; whole call, 16 blocks: 26.1 -> 24.8 us, the outer driver at 32 blocks: 102.2 -> 98.8 us).
+  if (wave < 3) {
+    const int64_t *in = wave == 0 ? pr.t : wave == 1 ? pr.p : pr.a;
+    int64_t *out = wave == 0 ? pr.T : wave == 1 ? pr.P : pr.A;
+    int64_t *sout = wave == 0 ? sT : wave == 1 ? sP : sA;
+    uint64_t u[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      int64_t v = 2 * lane + k < N ? in[2 * lane + k] : 0;
+      if (v < 0) { myflags |= 1; v = 0; }
+      u[k] = (uint64_t)v;
+      if (u[k] >= kSumLimit) { myflags |= 2; u[k] = kSumLimit; }
+    }
+    uint64_t sum = u[0] + u[1];  // of the lanes up to this one; every sum saturates at kSumLimit
+    sum = sum > kSumLimit ? kSumLimit : sum;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint64_t below = (uint64_t)__shfl_up((unsigned long long)sum, off);
+      if (lane >= off) sum += below;
+      sum = sum > kSumLimit ? kSumLimit : sum;
+    }
+    uint64_t before = (uint64_t)__shfl_up((unsigned long long)sum, 1);
+    if (lane == 0) before = 0;
+    const uint64_t mid = before + u[0] > kSumLimit ? kSumLimit : before + u[0];
+    if (sum >= kSumLimit) myflags |= 2;  // (the largest of the lane's sums; beyond block N it stays the last one)
+    if (2 * lane < N) { sout[2 * lane + 1] = (int64_t)mid; out[2 * lane + 1] = (int64_t)mid; }
+    if (2 * lane + 1 < N) { sout[2 * lane + 2] = (int64_t)sum; out[2 * lane + 2] = (int64_t)sum; }
+  }
+  if (tid == 0) { sT[0] = sP[0] = sA[0] = 0; pr.T[0] = pr.P[0] = pr.A[0] = 0; }
+  if (myflags) atomicOr(&s_flags, myflags);
+  // level 1 buffer: "no plan" everywhere, padding columns 0
+  for (int e = tid; e < (N + 1) * LS; e += NT) level(1)[e] = ((e % LS) < D) ? INF : (VT)0;
+  if constexpr (DIRECT)  // level 2's buffer as well
+    for (int e = tid; e < (N + 1) * LS; e += NT) level(2)[e] = ((e % LS) < D) ? INF : (VT)0;
+  __syncthreads();
+  int st = RANNC_DP_PROBLEM_OK;
+  if (s_flags & 1) st = RANNC_DP_PROBLEM_NEGATIVE_INPUT;
+  else if (s_flags & 2) st = RANNC_DP_PROBLEM_SUM_OVERFLOW;
+  else if ((uint64_t)sT[N] + s_max_cut > (uint64_t)pr.time_limit) st = RANNC_DP_PROBLEM_TIME_TOO_LARGE;
+  if (tid == 0) *pr.status = st;
+
+  if constexpr (DIRECT) {
+    // Where every row's stages begin in the list: ends[] (pass_entries; a thread per row, on the sums Z as in
+    // prepare_kernel where they cannot wrap) and their running sum.  In any case at most N (N + 1) / 2 stages: the
+    // ends lie between the row and N.
+    const uint64_t M = (uint64_t)pr.M;
+    const bool small = (uint64_t)sP[N] < (1ull << 55) && (uint64_t)sA[N] < (1ull << 60);
+    if (small && tid <= N) s_z[tid] = (uint64_t)D * (uint64_t)sP[tid] + (uint64_t)sA[tid];
+    lds_barrier();
+    if (64 * wave < N) {
+      const int i = min(tid, N - 1);
+      int end;
+      if (small) {
+        const uint64_t DM = __umul64hi(M, (uint64_t)D) ? ~0ull : M * (uint64_t)D, Zi = s_z[i];
+        end = prepare_end(i, N, [&](int j) { return s_z[j] - Zi <= DM; });
+      } else {
+        const uint64_t Pi = (uint64_t)sP[i], Ai = (uint64_t)sA[i];
+        end = prepare_end(i, N, [&](int j) { return fits_at((uint64_t)sP[j] - Pi, (uint64_t)sA[j] - Ai, M, D); });
+      }
+      if (tid < N) s_end[tid] = (uint32_t)end;
+      int run = tid < N ? end - tid : 0;
+      const int mine = run;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int x = __shfl_up(run, o);
+        if (lane >= o) run += x;
+      }
+      if (tid < N) s_at[tid] = (uint32_t)(run - mine);
+      if (lane == 63) s_sum[wave] = run;
+    }
+    lds_barrier();
+    if (tid >= 64 && tid < N) s_at[tid] += (uint32_t)s_sum[0];
+    if (tid == 0) s_at[N] = (uint32_t)(s_sum[0] + (N > 64 ? s_sum[1] : 0));
+    lds_barrier();
+  }
+
+  // ---- tables (as build_kernel): rows 0..min(63,N-1) of chunk 0, then rows 0..N-1 of chunk 1 ----
+  const int R0 = min(64, N), RT = R0 + (nch > 1 ? N : 0);
+  for (int f = wave; f < RT; f += kSmallWaves) {
+    const int c = f >= R0, i = c ? f - R0 : f;
+    if constexpr (DIRECT) {
+      if ((int)s_end[i] <= max(i, 64 * c) && i != 0) {  // no stage of the unit fits
+        const int64_t u = unit_index(nch, i, c);
+        pr.rmin[u * 64 + lane] = 255;
+        if (lane == 0) pr.ufit[u] = 0;
+        continue;
+      }
+    }
+    UnitStages<VT> stage;
+    const bool fits = build_unit<VT, DP>(pr, sT, sP, sA, pr.o ? sC : nullptr, i, c, lane, level(1), LS, 0, nullptr, !DIRECT, &stage);
+    if (fits && lane == 0) atomicMin(&s_wlo[c], i);
+    if constexpr (DIRECT) {
+      const int jj = 64 * c + lane;
+      if (jj >= i && jj < (int)s_end[i])
+        s_word[s_at[i] + jj - i] = (uint32_t)i | (uint32_t)(jj + 1) << 8 | (uint32_t)(stage.fits ? stage.rmin : 255) << 16;
+    }
+  }
+  [[maybe_unused]] int passes = 0;
+  if constexpr (DIRECT) {
+    const int all = s_at[N];
+    passes = (all + 63) >> 6;
+    if (tid < 64 && all + tid < 64 * passes) s_word[all + tid] = 255u << 16;  // (fits nowhere)
+  }
+  __syncthreads();
+  if (tid < nch) pr.wlo[tid] = s_wlo[tid];
+  const int64_t lvl = (int64_t)(N + 1) * DP;
+  VT RANNC_GLOBAL *Vg = gptr((VT *)pr.V);
+  const VT RANNC_GLOBAL *cost = gptr((const VT *)pr.cost);
+  const uint8_t RANNC_GLOBAL *rmin = gptr((const uint8_t *)pr.rmin);
+  // level 1 to memory
+  for (int e = tid; e < (N + 1) * DP; e += NT) Vg[e] = level(1)[(e / DP) * LS + (e % DP)];
+  if (tid == 0) s_top[0] = level(1)[N * LS + D - 1];
+
+  // ---- levels 2..S_eff ----
+  [[maybe_unused]] DirectConsts<DP> kc;
+  if constexpr (DIRECT) direct_consts_init(kc);
+  for (int s = 2; s <= S_eff; ++s) {
+    const VT *prev = level(s - 1);
+    VT *cur = level(s);
+    const int rl = D - s + 1;
+    if constexpr (!DIRECT) {
+      for (int e = tid; e < (N + 1) * LS; e += NT) cur[e] = ((e % LS) < D) ? INF : (VT)0;
+      lds_barrier();  // LDS only: the copy of the previous level to memory stays in flight
+    }
+    if constexpr (DIRECT) {
+      // One pass of a wave = 64 stages of the list, one per lane, whatever rows they come from: every lane
+      // reads its own a[] row from LDS and folds its own column in.  (With the triangle of a chunk as pairs of
+      // rows, stages that do not fit among them, 32 blocks took nine passes a level; the outer driver's
+      // searches of that size hold two passes of stages that fit.)
+      for (int f = wave; f < passes; f += kSmallWaves) {
+        const uint32_t word = s_word[64 * f + lane];
+        const int row = (int)(word & 255u), j = (int)(word >> 8) & 255, rmn = (int)(word >> 16);
+        // some (s-1)-stage plan covers blocks 1..row
+        const bool act = rmn <= rl && row >= s - 1 && prev[row * LS + D - 1] != INF;
+        if (__ballot(act) == 0ull) continue;
+        const VT tij = (VT)(sT[j] - sT[row]);
+#define RANNC_ROW(HH)                                                                                \
+  {                                                                                                  \
+    constexpr int H = (HH) <= DP ? (HH) : DP;                                                        \
+    const int sig = merge_shift(s, DP, H);                                                           \
+    VT x[H];                                                                                         \
+    _Pragma("unroll") for (int t = 0; t < H; ++t) x[t] = prev[row * LS + sig + t];                   \
+    row_merge_direct<VT, H>(x, tij, rmn, act, kc);                                                   \
+    if (act) {                                                                                       \
+      /* no test per entry: columns D.. hold 0 and keep it, column DP (t + 1 + sig <= DP) is padding */ \
+      VT *dst = cur + j * LS + 1 + sig;                                                              \
+      _Pragma("unroll") for (int t = 0; t < H; ++t) atomicMin(&dst[t], x[t]);                        \
+    }                                                                                                \
+  }
+        if (rl <= 8) RANNC_ROW(8)
+        else if (rl <= 16) RANNC_ROW(16)
+        else if (rl <= 24) RANNC_ROW(24)
+        else RANNC_ROW(32)
+#undef RANNC_ROW
+      }
+    } else {
+      for (int f = wave; f < RT; f += kSmallWaves) {
+        const int c = f >= R0, i = c ? f - R0 : f;
+        if (i < s - 1 || i < s_wlo[c] || 64 * c + 64 < s) continue;
+        if (prev[i * LS + D - 1] == INF) continue;  // no (s-1)-stage plan covers blocks 1..i
+        const int jj = 64 * c + lane;
+        const int64_t u = unit_index(nch, i, c);
+        int rmn = 255;
+        if (jj >= i && jj < N) rmn = rmin[u * 64 + lane];
+        const bool act = rmn <= rl;
+        if (__ballot(act) == 0ull) continue;
+        const int col = act ? lane : __ffsll((long long)__ballot(act)) - 1;
+        const VT RANNC_GLOBAL *unit = cost + u * 64 * D + col;
+        const VT off = act ? (VT)0 : INF;
+#define RANNC_ROW(K)                                                                                  \
+  case K:                                                                                             \
+    if constexpr (8 * K <= DP) {                                                                      \
+      constexpr int H = 8 * K;                                                                        \
+      const int sig = merge_shift(s, DP, H);                                                          \
+      VT x[H];                                                                                        \
+      row_merge<VT, H, const VT *>(x, unit, prev + i * LS + sig, off, rl);                            \
+      /* (no test per entry, as above; folding INF in is a no-op) */                                  \
+      if (act && jj + 1 >= s) {                                                                       \
+        VT *dst = cur + (jj + 1) * LS + 1 + sig;                                                      \
+        _Pragma("unroll") for (int t = 0; t < H; ++t) atomicMin(&dst[t], x[t]);                       \
+      }                                                                                               \
+    }                                                                                                 \
+    break;
+        switch ((rl + 7) >> 3) {
+          RANNC_ROW(1) RANNC_ROW(2) RANNC_ROW(3) RANNC_ROW(4)
+          RANNC_ROW(5) RANNC_ROW(6) RANNC_ROW(7) RANNC_ROW(8)
+          default: break;
+        }
+#undef RANNC_ROW
+      }
+    }
+    if constexpr (DIRECT) {
+      // The next level's buffer held level s-2: its last readers were the passes of level s-1, which
+      // the barrier before this level's passes closed, and its copy to memory was issued by these
+      // same threads before their passes of level s-1.
+      if (s < S_eff) {
+        VT *next = level(s + 1);
+        for (int e = tid; e < (N + 1) * LS; e += NT) next[e] = ((e % LS) < D) ? INF : (VT)0;
+      }
+    }
+    lds_barrier();
+    VT RANNC_GLOBAL *Vs = Vg + (int64_t)(s - 1) * lvl;
+    for (int e = tid; e < (N + 1) * DP; e += NT) Vs[e] = cur[(e / DP) * LS + (e % DP)];
+    if (tid == 0) s_top[s - 1] = cur[N * LS + D - 1];
+  }
+  __syncthreads();
+
+  // ---- choice of the stage count (as select_kernel) ----
+  if (wave == 0) {
+    int64_t v = INT64_MAX;
+    if (st == 0 && lane < S_eff) {
+      const VT u = s_top[lane];
+      v = (u == INF) ? INT64_MAX : (int64_t)u;
+    }
+    const Chosen chosen = select_finish(pr, v, st, d_opt, d_n_stages, d_est, d_status);
+    if (tid == 0) s_chosen = chosen;
+  }
+  if (!results.d_stage_end) return;
+  if constexpr (DIRECT) asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 2, 2), 0" ::);  // (direct_consts_init)
+  // ---- plan recovery, where the caller wants it from this launch: out of LDS, but for levels that had to make room
+  // and the tables' own bytes ----
+  __shared__ TracebackLds sh;
+  if (wave == 0) {
+    if (lane == 0) { sh.chosen = s_chosen; sh.ns = s_chosen.status == 0 ? s_chosen.n_stages : 0; }
+    if (lane < 3) sh.key[lane] = 0xFFFFFFFFu;
+  }
+  __syncthreads();
+  if (sh.ns > 0) {
+    struct Common {
+      const int64_t *T, *C;
+      const int *wlo;
+      const uint8_t *rmin;
+      const uint32_t *word, *at, *end;
+      int nch;
+      __device__ __forceinline__ int64_t sum(int i) const { return T[i]; }
+      __device__ __forceinline__ uint64_t send(int j) const { return C ? (uint64_t)C[j] : 0ull; }
+      __device__ __forceinline__ int first(int j) const { return min(wlo[(j - 1) >> 6], j); }
+      __device__ __forceinline__ int least(int i, int j) const {
+        if constexpr (DIRECT) return j <= (int)end[i] ? (int)(word[at[i] + j - 1 - i] >> 16) : 255;
+        else return (int)rmin[unit_index(nch, i, (j - 1) >> 6) * 64 + ((j - 1) & 63)];
+      }
+    };
+    const Common common = {sT, pr.o ? sC : nullptr, s_wlo, pr.rmin, s_word, s_at, s_end, nch};
+    if (DIRECT && bufs >= S_eff) {
+      struct InLds : Common {
+        const VT *levels;
+        int per_level;
+        __device__ __forceinline__ const VT *row(int s, int i) const { return levels + (s - 1) * per_level + i * LS; }
+      };
+      traceback_walk<VT>(InLds{common, levels, per_level}, N, D, sh.ns, sh);
+    } else {
+      struct InMemory : Common {
+        const VT RANNC_GLOBAL *V;
+        int64_t lvl;
+        __device__ __forceinline__ const VT RANNC_GLOBAL *row(int s, int i) const { return V + (int64_t)(s - 1) * lvl + (int64_t)i * DP; }
+      };
+      traceback_walk<VT>(InMemory{common, Vg, lvl}, N, D, sh.ns, sh);
+    }
+  }
+  const int64_t q = (int64_t)pr.q * plan_stride;
+  plan_out(pr, plan_stride, results.d_stage_end + q, results.d_replicas + q, sh, FormStageIn{}, results);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -2742,13 +2827,14 @@ bool small_can_recompute(int bits, int DP, int64_t max_total_time) {
 
 hipError_t launch_solve_small(const ProblemDev *src, ProblemDev *p, int Q, int bits, int DP, bool direct, int64_t *d_opt,
                               int32_t *d_n_stages, int64_t *d_est, int32_t *d_status, const ProblemDev *host_one,
-                              hipStream_t st) {
+                              int plan_stride, const PlanResults *results, hipStream_t st) {
   const ProblemDev one = host_one ? *host_one : ProblemDev{};
+  const PlanResults plan = results ? *results : PlanResults{};
   if (direct && DP > 32) return hipErrorInvalidValue;
 #define GO(B, T, W, X)                                                                                 \
   if (bits == B && DP == W && direct == X)                                                             \
     hipLaunchKernelGGL((solve_small_kernel<T, W, X>), dim3(Q), dim3(64 * small_waves<T, W>()), 0, st, src, p, d_opt, \
-                       d_n_stages, d_est, d_status, one, host_one ? 1 : 0);
+                       d_n_stages, d_est, d_status, one, host_one ? 1 : 0, plan_stride, plan);
   GO(32, uint32_t, 8, false) GO(32, uint32_t, 16, false) GO(32, uint32_t, 32, false) GO(32, uint32_t, 64, false)
   GO(64, uint64_t, 8, false) GO(64, uint64_t, 16, false) GO(64, uint64_t, 32, false) GO(64, uint64_t, 64, false)
   GO(32, uint32_t, 8, true) GO(32, uint32_t, 16, true) GO(32, uint32_t, 32, true)
