@@ -80,6 +80,23 @@ __device__ __forceinline__ uint64_t wave_min(uint64_t v) {
   return (uint64_t)hi << 32 | lo;
 }
 
+// x <= v r for v < 2^62, r < 2^32
+__device__ __forceinline__ bool at_most_times(uint64_t x, uint64_t v, uint32_t r) {
+  return __umul64hi(v, (uint64_t)r) != 0 || x <= v * (uint64_t)r;
+}
+__device__ __forceinline__ bool at_most_times(uint64_t x, uint32_t v, uint32_t r) { return x <= (uint64_t)v * r; }
+
+// ceil(x / v) where that is at most 64 (at least 1), else something above 64; v >= 1, inv_v: about 1 / v.  Below
+// 2^7 the quotient is off by far less than one, so that its whole part is too small by at most two (n - 1 for a
+// quotient just above n) and never too large by more than one.  (A 64-bit division is 150 instructions.)
+template <typename VT> __device__ __forceinline__ int ceil_ratio(uint64_t x, VT v, float inv_v) {
+  int r = max((int)min((float)x * inv_v, 100.0f), 1);
+  if (r > 1 && at_most_times(x, v, (uint32_t)r - 1u)) --r;
+  if (!at_most_times(x, v, (uint32_t)r)) ++r;
+  if (!at_most_times(x, v, (uint32_t)r)) ++r;
+  return r;
+}
+
 // ceil(x / r) for any 1 <= r <= 64 from the correctly rounded reciprocal 1/r, in double precision:
 //     t = x + (r/2 - 1 + r o)     y = t (1/r) + 1.5 2^52     (one fused multiply-add)
 // t / r = (x + r - 1)/r - 1/2 + o, and the fraction of (x + r - 1)/r is at most 63/64, so t (1/r) lies

@@ -179,8 +179,8 @@ __device__ __forceinline__ bool build_unit(const ProblemDev &pr, const int64_t *
     const int64_t slack = pr.M - Pij;
     if (Aij <= slack) rmin = 1;
     else if (slack > 0) {
-      const uint64_t need = ((uint64_t)Aij + (uint64_t)slack - 1) / (uint64_t)slack;
-      if (need <= (uint64_t)D) rmin = (int)need;
+      const int need = ceil_ratio((uint64_t)Aij, (uint64_t)slack, __builtin_amdgcn_rcpf((float)slack));
+      if (need <= D) rmin = need;
     }
   }
   const bool fits = valid && rmin <= D;
@@ -1749,23 +1749,12 @@ struct TracebackLds {
   int32_t end[RANNC_DP_MAX_DEVICES], replicas[RANNC_DP_MAX_DEVICES];
 };
 
-// x <= v r for v < 2^62, r < 2^32
-__device__ __forceinline__ bool at_most_times(uint64_t x, uint64_t v, uint32_t r) {
-  return __umul64hi(v, (uint64_t)r) != 0 || x <= v * (uint64_t)r;
-}
-__device__ __forceinline__ bool at_most_times(uint64_t x, uint32_t v, uint32_t r) { return x <= (uint64_t)v * r; }
-
 // The smallest r with ceil(x / r) + ceil(C / r) <= v, or more than `most`; inv_v: about 1 / v; hc: lane r - 1 of
 // the wave holds ceil(C / r) (only with C).
 template <typename VT>
 __device__ __forceinline__ int least_replicas(uint64_t x, uint64_t C, VT v, float inv_v, uint64_t hc, int most) {
   if (v == 0) return x == 0 && C == 0 ? 1 : most + 1;
-  // ceil((x + C) / v), or above 64: below 2^7 the quotient is off by far less than one, so that its whole part is
-  // too small by at most two (n - 1 for a quotient just above n) and never too large by more than one
-  int r = max((int)min((float)(x + C) * inv_v, 100.0f), 1);
-  if (r > 1 && at_most_times(x + C, v, (uint32_t)r - 1u)) --r;
-  if (!at_most_times(x + C, v, (uint32_t)r)) ++r;
-  if (!at_most_times(x + C, v, (uint32_t)r)) ++r;
+  int r = ceil_ratio(x + C, v, inv_v);
   if (C) {  // two ceilings may need some more
     for (bool done = false; __any(!done);) {
       const uint64_t c = __shfl(hc, min(r, 64) - 1);
