@@ -574,6 +574,9 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
   // estimated time of a class of few small searches (us): as one launch with recomputed stage times
   // (< 0: that kernel does not apply) and as launches per level
   double est_one[4] = {-1.0, -1.0, -1.0, -1.0}, est_levels[4] = {0.0, 0.0, 0.0, 0.0};
+  auto levels_us = [&](const LaunchShape &sh) {
+    return h->bits == 64 ? 26.9 + 4.7 * (sh.max_S_eff - 1) + 0.023 * sh.max_N : 24.3 + 4.1 * (sh.max_S_eff - 1) + 0.033 * sh.max_N;
+  };
   for (int k = 0; k < 4; ++k) {
     const LaunchShape &sh = shape[k];
     if (!sh.nprob) continue;
@@ -591,12 +594,14 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
       bool tiny;
       if (direct_ok) {
         // Stage times recomputed: the levels read nothing from memory.  The kernel runs a level as
-        // passes of 64 (row, column) pairs packed from the triangular and rectangular blocks, sixteen
-        // waves at a time.  Least-squares fit over a sweep (N = 8..128, D = 8, 16, 32, S = 2..D, 1 and
-        // 8 searches; rms 3.7 us): 12 us + 0.04 us per table row in front, then per level a constant
-        // and a price per pass that follow the width of the merge the level still needs (32 / 16 / 8
-        // inputs), the passes of the first round of sixteen dearer than the later ones.  The launches
-        // per level on the same sweep: 21 us + 4.4 us per level + 0.05 us per block.
+        // passes of 64 stages that fit, sixteen waves at a time; the host counts the passes of the
+        // triangular and rectangular blocks, which the stages that fit cannot exceed by much.  Least-squares
+        // fit over whole calls (N = 16..128, D = 8, 16, 32, S = 3..D, memory for an even share twice, six and
+        // thirty times, 1 and 6 searches; 426 shapes, rms 11 us): 24 us + 0.08 us per table row in front,
+        // then per level a constant and a price per pass that follow the width of the merge the level still
+        // needs (32 / 16 / 8 inputs), the passes of the first round of sixteen dearer than the later ones.  The
+        // launches per level on the same sweep: 24 us + 4.1 us per level + 0.03 us per block.  The choice is
+        // 0.7 % above the better of the two on average (64-bit values 1.9 %).
         auto tri = [](int W) {
           int lg = 0;
           while ((1 << lg) < W) ++lg;
@@ -609,15 +614,15 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
           passes += (64 >> (6 - lg)) + tri(sh.max_N - 64);
         }
         const double work = 0.17 * std::min(passes, 16) + 0.105 * std::max(passes - 16, 0);
-        const bool w64 = h->bits == 64;  // the same fit on 64-bit values (rms 5.7 us; eight waves at 32 devices)
-        double us = w64 ? 13.0 + 0.02 * (double)rows : 12.0 + 0.04 * (double)rows;
+        const bool w64 = h->bits == 64;  // the same fit on 64-bit values (rms 22 us; eight waves at 32 devices)
+        double us = 24.3 + (w64 ? 0.090 : 0.079) * (double)rows;
         for (int s = 2; s <= sh.max_S_eff; ++s) {
           const int rl = sh.max_D - s + 1;
-          if (w64) us += rl <= 8 ? 0.33 + 0.63 * work : rl <= 16 ? 1.1 + 0.9 * work : 1.45 + 1.62 * work;
-          else us += rl <= 8 ? 0.43 + 0.45 * work : rl <= 16 ? 0.68 + 0.61 * work : 1.5 + 0.91 * work;
+          if (w64) us += rl <= 8 ? 0.43 + 0.26 * work : rl <= 16 ? 0.67 + 0.53 * work : 0.73 + 1.19 * work;
+          else us += rl <= 8 ? 0.42 + 0.20 * work : rl <= 16 ? 0.84 + 0.37 * work : 0.76 + 0.65 * work;
         }
         est_one[k] = us;
-        tiny = us <= (w64 ? 22.0 + 5.5 * levels + 0.06 * sh.max_N : 21.0 + 4.4 * levels + 0.05 * sh.max_N);
+        tiny = us <= levels_us(sh);
       } else if (heavy) {
         // 64 devices, or 64-bit values from 32 devices on, stage times from the table: a level costs
         // about 7 us plus 1.7 us per pass of eight rows, more than a launch; only two or three levels
@@ -627,12 +632,24 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
         // stage times from the table, sixteen waves (sweep over N = 8..128, D = 8, 16, S = 2..D)
         tiny = rows <= 64 && rows * levels <= (h->bits == 64 ? 240 : 480);
       }
-      // hundreds of searches: the launches per level are throughput-bound as well
-      const bool batch = sh.nprob >= 256 && (cls <= 16 || sh.max_N <= 64) && !(h->bits == 64 && cls == 64);
+      // Hundreds of searches: the launches per level are throughput-bound as well.  One launch where it
+      // recomputes the stage times (256 searches of 96 blocks and 32 devices 129 us against 187 us of launches
+      // per level, 1024 of them 407 against 437 us), and where neither side does (1024 such searches with send
+      // times 1.25 against 1.96 ms; 64 devices, 32-bit values and more than 64 blocks: 3.5 against 3.3 ms).  Where
+      // only the levels recompute -- 64 devices -- they are the faster ones (1024 searches of 24 blocks: 232 us
+      // against 426 us).  From 32 devices and 65 blocks on only for a class alone: beside the levels of other
+      // classes its workgroups stand in their way (2048 searches of 128 blocks in four classes: 1.79 against
+      // 1.69 ms).  Where it recomputes the times one launch is ahead from fewer searches on (8 stages of 64 blocks
+      // and 32 devices: 64 searches 66 against 82 us; of 128 blocks and 16 devices: 64 searches level, 128 of
+      // them 116 against 133 us).
+      const bool alone = sh.nprob == Q;
+      const int many = !direct_ok ? 256 : sh.max_N <= 64 ? 64 : 128;
+      const bool batch = sh.nprob >= many && (direct_ok || !recompute_cls[k]) &&
+                         (cls <= 16 || sh.max_N <= 64 || (alone && (cls < 64 || h->bits == 64)));
       fused[k] = !scan && !split && sh.max_N <= rannc::small_max_blocks() &&
                  (h->fused_small == 1 ? (batch || tiny) : h->fused_small == 2);
       fused_direct[k] = fused[k] && direct_ok;
-      est_levels[k] = h->bits == 64 ? 22.0 + 5.5 * levels + 0.06 * sh.max_N : 21.0 + 4.4 * levels + 0.05 * sh.max_N;
+      est_levels[k] = levels_us(sh);
     }
   }
   // Classes in the shadow of the longest one.  The classes of a batch run side by side on streams
