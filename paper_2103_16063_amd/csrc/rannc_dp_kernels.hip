@@ -2372,7 +2372,9 @@ void solve_small_kernel(
     const uint64_t M = (uint64_t)pr.M;
     const bool small = (uint64_t)sP[N] < (1ull << 55) && (uint64_t)sA[N] < (1ull << 60);
     if (small && tid <= N) s_z[tid] = (uint64_t)D * (uint64_t)sP[tid] + (uint64_t)sA[tid];
-    lds_barrier();
+    // (below 64 blocks the first wave holds every row and meets no other wave here)
+    if (N < 64) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    else lds_barrier();
     if (64 * wave < N) {
       const int i = min(tid, N - 1);
       int end;
@@ -2392,12 +2394,18 @@ void solve_small_kernel(
         if (lane >= o) run += x;
       }
       if (tid < N) s_at[tid] = (uint32_t)(run - mine);
-      if (lane == 63) s_sum[wave] = run;
+      if (N < 64) {
+        if (tid == 63) s_at[N] = (uint32_t)run;
+      } else if (lane == 63) {
+        s_sum[wave] = run;
+      }
     }
     lds_barrier();
-    if (tid >= 64 && tid < N) s_at[tid] += (uint32_t)s_sum[0];
-    if (tid == 0) s_at[N] = (uint32_t)(s_sum[0] + (N > 64 ? s_sum[1] : 0));
-    lds_barrier();
+    if (N >= 64) {
+      if (tid >= 64 && tid < N) s_at[tid] += (uint32_t)s_sum[0];
+      if (tid == 0) s_at[N] = (uint32_t)(s_sum[0] + (N > 64 ? s_sum[1] : 0));
+      lds_barrier();
+    }
   }
 
   // ---- tables (as build_kernel): rows 0..min(63,N-1) of chunk 0, then rows 0..N-1 of chunk 1 ----
