@@ -61,7 +61,7 @@ __host__ __device__ inline int64_t max_run_words(int nch) {
 // kMergeRows16From rows (unpruned), of 8 from kMergeRows8From, of 4 below.
 constexpr int kMergeWaves = 4;
 constexpr int kMergeMinRows = 4;
-// largest work item (rows): the recomputing form holds the item's rows in LDS
+// largest work item: rows, or passes of the recomputing form
 __host__ __device__ constexpr int merge_max_rows(int bits) { return bits == 64 ? 32 : 64; }
 // (and, with two rows to an entry of a diagonal block's segment, cuts those shorter: rannc_dp_worklist.h)
 constexpr int kMergeRows8From = 6144;
@@ -147,7 +147,7 @@ hipError_t launch_build(const ProblemDev *probs, const LaunchShape &sh, int bits
 // rows_per_item: > 0 fixed, -1 chosen on the device for the sorted-merge kernel (the smallest item size
 // whose item count fits max_items)
 // slots: workgroups of the level kernel that the device holds at a time
-// paired: the list for the level kernel that recomputes the stage times (diagonal blocks as row pairs)
+// paired: the list for the level kernel that recomputes the stage times (passes of stages that fit)
 // src: the descriptors, in device memory (probs itself) or in pinned host memory the device can read;
 // the launch then also stores them to probs.  host_one: for a launch over one search, its descriptor in
 // host memory (passed by value instead), or null

@@ -652,7 +652,7 @@ __global__ __launch_bounds__(kSetupThreads) void setup_kernel(const ProblemDev *
 
   // ---- windows ----
   __shared__ int start[1025];  // nch <= 1024 (N <= 65535)
-  __shared__ RunSegments seg[1024];  // every chunk's segments
+  __shared__ RunSegments seg[1024];  // every chunk's window
   if (paired) {
     const bool bad = flags != 0;  // (sums that may have wrapped: no stage fits)
     static_assert(sizeof(seg) >= 4 * (2 * kSetupLdsN + 1), "ends and their sums");
@@ -713,29 +713,16 @@ __global__ __launch_bounds__(kSetupThreads) void setup_kernel(const ProblemDev *
       const int k = tid % NC, r = 4 * (k + 1);
       int cnt = 0;
       for (int c = tid / NC; c < nch; c += kSetupThreads / NC) {
-        const RunSegments g = seg[c];
-        cnt += items_of_rows(g, r) + items_of_pairs(g, r, max_rows);
+        cnt += items_of_rows(seg[c], r);
       }
       if (cnt) atomicAdd(&count[k], cnt);
     }
     __syncthreads();
     rows = 4 * (setup_item_size(count, most, max_items, batch, slots, false) + 1);
   }
-  // per chunk: items of the two segments, and their rows dealt evenly over them (33 rows in items
-  // of up to 16: three items of 11, not 16 + 16 + 1); seg[c] is reused for {items0, per0, lo1, per1}
-  static_assert(kSetupLdsN >= 1024 / 2, "a chunk per word");
-  int *const n0_of = (int *)sP, *const n1_of = (int *)sA;
-  for (int c = tid; c < nch; c += kSetupThreads) {
-    const RunSegments g = seg[c];
-    const int items0 = items_of_rows(g, rows), items1 = items_of_pairs(g, rows, max_rows);
-    start[c + 1] = items0 + items1;  // items of chunk c
-    n0_of[c] = g.n0;
-    n1_of[c] = g.n1;
-    RunSegments h;
-    h.lo0 = g.lo0; h.n0 = items0; h.lo1 = g.lo1;
-    h.n1 = ((items0 ? (g.n0 + items0 - 1) / items0 : 0) << 8) | (items1 ? (g.n1 + items1 - 1) / items1 : 0);  // per0, per1 <= 64
-    seg[c] = h;
-  }
+  // per chunk: its items, the rows dealt evenly over them (33 rows in items of up to 16: three items of 11,
+  // not 16 + 16 + 1)
+  for (int c = tid; c < nch; c += kSetupThreads) start[c + 1] = items_of_rows(seg[c], rows);
   __syncthreads();
   if (tid == 0) {
     int sum = 0;
@@ -753,12 +740,10 @@ __global__ __launch_bounds__(kSetupThreads) void setup_kernel(const ProblemDev *
       else hi = mid;
     }
     const int c = lo, k = e - start[c];
-    const RunSegments h = seg[c];
-    const int items0 = h.n0, per0 = h.n1 >> 8, per1 = h.n1 & 255;
-    const int first = k < items0 ? h.lo0 + k * per0 : h.lo1 + (k - items0) * per1;
-    const int left = k < items0 ? n0_of[c] - k * per0 : n1_of[c] - (k - items0) * per1;
-    const int take = max(min(k < items0 ? per0 : per1, left), 1);  // (never below one row: the word stays well-formed)
-    runs[1 + e] = ((take - 1) << 26) | (c << 16) | first;
+    const RunSegments g = seg[c];
+    const int items = start[c + 1] - start[c], per = (g.n0 + items - 1) / items;
+    const int take = max(min(per, g.n0 - k * per), 1);  // (never below one row: the word stays well-formed)
+    runs[1 + e] = ((take - 1) << 26) | (c << 16) | (g.lo0 + k * per);
   }
 }
 

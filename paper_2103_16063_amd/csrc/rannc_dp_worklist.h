@@ -9,15 +9,14 @@
 
 namespace rannc {
 
-// The recomputing form holds the rows of an item in an LDS array of this many rows.  An entry of a
-// diagonal block's segment (RunSegments) is a PAIR of rows, both of them held, so that an item has at
-// most half as many entries there: 33 of 32-bit values (a full segment), 17 of 64-bit ones (a larger
-// array would cost the third workgroup of a compute unit at 64 devices).
+// The recomputing form works on passes of 64 stages that fit.  The host does not know which ones fit and sizes
+// its grid as if all did: a row in front of a chunk's diagonal block is one pass, and in the block two rows (p
+// and 64 - p) fill one together.  An item of that bound holds at most this many rows, a pair counting as two.
 __host__ __device__ constexpr int merge_item_rows(int bits) { return merge_max_rows(bits) + 2; }
 __host__ __device__ constexpr int merge_max_pairs(int max_rows) { return max_rows / 2 + 1; }
 
-// The rows of one chunk's window as the work list cuts them (see setup_kernel): n0 rows from lo0 on, then,
-// for the recomputing form, n1 entries from lo1 on that stand for the rows of the diagonal block.
+// The rows of one chunk's window as the work list cuts them (see setup_kernel): n0 rows from lo0 on; paired, for
+// the bound above: n1 entries from lo1 on that stand for the rows of the diagonal block.
 struct RunSegments { int lo0, n0, lo1, n1; };
 __host__ __device__ inline RunSegments run_segments(int N, int c, int lo, bool paired) {
   RunSegments g;
