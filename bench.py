@@ -39,11 +39,11 @@ ESIZE = 4  # bytes per table entry in the 32-bit mode all benchmark configuratio
 # one-launch kernels of the D = 8 and D = 16 classes, tables included): their bytes summed, over 32.
 PMC_TRAFFIC = {
     ("c4", False, False): (29.44e6, "profiles/level_merge_config4.md"),
-    ("c4", False, True): (5.91e6, "profiles/level_merge_config4_recompute.md"),
+    ("c4", False, True): (5.94e6, "profiles/level_merge_config4_recompute.md"),
     ("c4", True, False): (48.32e6, "profiles/level_merge_config4_wide.md"),
     ("c4dense", False, False): (113.63e6, "profiles/level_merge_config4_dense.md"),
-    ("c4dense", False, True): (11.66e6, "profiles/level_merge_config4_dense_recompute.md"),
-    ("c5", False, True): (47.1e6, "profiles/level_merge_config5_batched.md"),
+    ("c4dense", False, True): (14.78e6, "profiles/level_merge_config4_dense_recompute.md"),
+    ("c5", False, True): (55.1e6, "profiles/level_merge_config5_batched.md"),
     ("c5", False, False): (811.8e6, "profiles/level_merge_config5_batched_table.md"),
 }
 # useful vector instructions of the sorted-merge level kernel per (i, j) stage: DP maxima that form
