@@ -1469,12 +1469,14 @@ template <typename VT, int HMAX, bool DIRECT>
 __device__ __forceinline__ void level_merge_body(const ProblemDev &pr, const int s, const int item) {
   // What the workgroup needs of the descriptor, and then of the list, is asked for at once and waited for
   // once: left alone, the compiler reads each field where it is first used, behind the exits in front of
-  // it, and a launch starts with a chain of six scalar reads.
+  // it, and a launch starts with a chain of six scalar reads.  (Not in the table form: behind an asm statement the
+  // compiler no longer reads the rows of V[s-1] into scalar registers, 1024 searches of 128 blocks, 64-bit values,
+  // 32 devices 181 -> 264 us per level.)
   const int S_eff = pr.S_eff, N = pr.N, D = pr.D, DP = pr.DP, nch = pr.nch;
   const int32_t RANNC_GLOBAL *__restrict__ runs = gptr((const int32_t *)pr.runs);
   VT RANNC_GLOBAL *const V = gptr((VT *)pr.V);
   const char RANNC_GLOBAL *__restrict__ passes = gptr((const char *)pr.cost);
-  asm volatile("" :: "s"(S_eff), "s"(N), "s"(D), "s"(DP), "s"(nch), "s"(runs), "s"(V), "s"(passes));
+  if constexpr (DIRECT) asm volatile("" :: "s"(S_eff), "s"(N), "s"(D), "s"(DP), "s"(nch), "s"(runs), "s"(V), "s"(passes));
   if (s > S_eff) return;
   int c, i0 = 0, i_hi = 0, n = 0;
   [[maybe_unused]] uint32_t near = 0;
@@ -1491,9 +1493,8 @@ __device__ __forceinline__ void level_merge_body(const ProblemDev &pr, const int
     near = wave == 0 || n < 2 ? it[2] : wave == 1 || n < 3 ? it[3] : wave == 2 || n < 4 ? it[4] : it[5];
     passes += (int64_t)it[0] * pass_bytes<VT>();
   } else {
-    const unsigned desc = ((const uint32_t RANNC_GLOBAL *)runs)[1 + min(item, 8 * nch * (nch + 1) - 1)];
-    asm volatile("" :: "s"(count), "s"(desc));
     if (item >= count) return;
+    const unsigned desc = (unsigned)runs[1 + item];
     c = (int)((desc >> 16) & 0x3ffu);
     i0 = (int)(desc & 0xffffu);
     i_hi = min(min(i0 + (int)(desc >> 26), 64 * c + 63), N - 1);
