@@ -718,7 +718,11 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
                                                max_rows, &rows_for_list);
     const ProblemDev *host_one = sh.nprob == 1 ? &probs[cls_start[k]] : nullptr;
     const int parts = recompute_cls[k] || split_fast ? 1 : 3;
-    if (rannc::can_prepare(sh)) {
+    // (Hundreds of searches' tables at 64 devices are bound by their stores, and the builder on its own keeps more
+    // waves on them: 512 searches of 128 blocks 546 against 583 us, 64-bit values 878 against 1024; at 32 devices
+    // 243 against 226 and 458 against 437.)
+    const bool apart = parts == 3 && kClasses[k] == 64 && sh.nprob > 64;
+    if (rannc::can_prepare(sh) && !apart) {
       ok = rannc::launch_prepare(src + cls_start[k], cp, sh, h->bits, kClasses[k], parts, rows_for_list, merge_items[k], slots,
                                  recompute_cls[k], max_rows, split, b->cut_bytes != nullptr, host_one, st) == hipSuccess;
       ok = ok && staging_read();
