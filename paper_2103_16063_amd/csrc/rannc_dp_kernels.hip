@@ -1270,7 +1270,8 @@ __device__ __forceinline__ void direct_entries(VT (&x)[H], double tij, const Dir
     else h = (q8[ODD - 1] + (VT)((1 << (CTZ - 3)) - 1)) >> (CTZ - 3);
     if constexpr (CTZ == 3) q8[ODD - 1] = h;
     x[H - 1 - M] = vmax(x[H - 1 - M], h);
-    if constexpr (M % 8 == 7) __builtin_amdgcn_sched_barrier(0);  // (all quotients at once would take twice the registers)
+    // (all quotients at once would take twice the registers)
+    if constexpr (M % (32 / (int)sizeof(VT)) == 32 / (int)sizeof(VT) - 1) __builtin_amdgcn_sched_barrier(0);
     direct_entries<VT, H, HMAX, M + 1>(x, tij, k, q8);
   }
 }
@@ -1291,8 +1292,8 @@ __device__ __forceinline__ void row_merge_direct(VT (&x)[H], VT tij, int rmn, bo
 }
 
 // The passes of one work item of the recomputing level kernel (see pass_entries), wave w the passes w, w+4, ...
-// A wave fetches what a pass needs while it works on the one before: the entries two passes ahead, the few
-// rows of V[s-1] they name one pass ahead, a value per lane.  When its turn comes the rows are put into LDS
+// A wave fetches what a pass needs while it works on the one before: the words two passes ahead, the times and the
+// few rows of V[s-1] that the words name one pass ahead, a value per lane.  When its turn comes the rows are put into LDS
 // and every lane reads its own back, four values at a time.  A pass with more rows than that (the end of a
 // diagonal block, stages of few blocks) has each lane read its row from memory.  The waves of the item
 // share nothing but the tile, so that the loop starts one round of loads after the item is known.  (With
@@ -1320,11 +1321,12 @@ __device__ __forceinline__ bool merge_passes(VT *tile, VT *mine, const VT RANNC_
   const int sig = merge_shift(s, DP, H), rl = D - s + 1, top = D - 2 - sig;
   const VT RANNC_GLOBAL *__restrict__ Vprev = V + (int64_t)(s - 2) * (int64_t)(N + 1) * DP + sig;
   const int sub = lane / HP, t_of = lane % HP;
-  struct Entry { uint32_t word; VT tij; };
   struct Rows { int lo, hi; VT a[LOADS]; };
-  auto fetch = [&](int x) -> Entry {
-    const char RANNC_GLOBAL *p = passes + min(x, n - 1) * pass_bytes<VT>();
-    return {((const uint32_t RANNC_GLOBAL *)p)[lane], ((const VT RANNC_GLOBAL *)(p + 256))[lane]};
+  auto fetch_word = [&](int x) -> uint32_t {
+    return ((const uint32_t RANNC_GLOBAL *)(passes + min(x, n - 1) * pass_bytes<VT>()))[lane];
+  };
+  auto fetch_time = [&](int x) -> VT {
+    return ((const VT RANNC_GLOBAL *)(passes + min(x, n - 1) * pass_bytes<VT>() + 256))[lane];
   };
   auto fetch_rows = [&](int lo, int hi) -> Rows {
     Rows r;
@@ -1333,7 +1335,8 @@ __device__ __forceinline__ bool merge_passes(VT *tile, VT *mine, const VT RANNC_
     for (int q = 0; q < LOADS; ++q) r.a[q] = Vprev[(int64_t)min(lo + q * PER + sub, hi) * DP + min(t_of, H - 1)];
     return r;
   };
-  Entry next = fetch(wave), after = fetch(wave + kMergeWaves);
+  uint32_t next_word = fetch_word(wave), after = fetch_word(wave + kMergeWaves);
+  VT next_time = fetch_time(wave);
   Rows next_rows = fetch_rows((int)(near & 0xffffu), (int)(near >> 16));
   typedef uint32_t Quad __attribute__((ext_vector_type(4)));
   static_assert(64 * LS * sizeof(VT) % 16 == 0, "the tile is cleared 16 bytes at a time");
@@ -1343,15 +1346,17 @@ __device__ __forceinline__ bool merge_passes(VT *tile, VT *mine, const VT RANNC_
   bool any = false;
 #pragma unroll 1
   for (int x = wave; x < n; x += kMergeWaves) {
-    const Entry e = next;
+    const uint32_t word = next_word;
+    const VT tij = next_time;
     const Rows r = next_rows;
-    next = after;
-    after = fetch(x + 2 * kMergeWaves);
+    next_word = after;
+    next_time = fetch_time(x + kMergeWaves);
+    after = fetch_word(x + 2 * kMergeWaves);
     {
-      const int last = 63 - __clzll((long long)__ballot(next.word != ~0u));  // (lane 0 has a stage)
-      next_rows = fetch_rows((int)(lane_bcast(next.word, 0) & 0xffffu), (int)(lane_bcast(next.word, last) & 0xffffu));
+      const int last = 63 - __clzll((long long)__ballot(next_word != ~0u));  // (lane 0 has a stage)
+      next_rows = fetch_rows((int)(lane_bcast(next_word, 0) & 0xffffu), (int)(lane_bcast(next_word, last) & 0xffffu));
     }
-    const int row = min((int)(e.word & 0xffffu), r.hi), col = (int)(e.word >> 16) & 63, rmn = (int)(e.word >> 22);
+    const int row = min((int)(word & 0xffffu), r.hi), col = (int)(word >> 16) & 63, rmn = (int)(word >> 22);
     VT alast, w[H];
     if (r.hi - r.lo < NEAR) {
       if (t_of < H) {
@@ -1384,7 +1389,7 @@ __device__ __forceinline__ bool merge_passes(VT *tile, VT *mine, const VT RANNC_
     const bool act = rmn <= rl && row >= s - 1 && alast != INF;
     if (__ballot(act) == 0ull) continue;
     any = true;
-    row_merge_direct<VT, H>(w, e.tij, rmn, act, k);
+    row_merge_direct<VT, H>(w, tij, rmn, act, k);
     if (act) {
 #pragma unroll
       for (int t = 0; t < H; ++t) atomicMin(&tile[col * LS + t], w[t]);
@@ -1395,9 +1400,14 @@ __device__ __forceinline__ bool merge_passes(VT *tile, VT *mine, const VT RANNC_
 
 // Waves per SIMD the level kernel is compiled for: the two value arrays of the widest 32-bit case
 // fit the 168 registers of three waves per SIMD (the compiler left alone takes one more).  The
-// recomputing form on 32-bit values holds one array: as many as its workgroups per compute unit.
+// recomputing form holds one array: as many as its workgroups per compute unit (merge_workgroups_per_cu).  Left
+// alone, the 64-bit forms for up to 32 and 16 values took 98 and 66 registers, one workgroup per compute unit fewer
+// than the size of the items counts on (1024 blocks at 32 devices where memory never binds 300 -> 271 us a call).
+// (64-bit values at 64 devices: loop-invariant addresses and one time, 20 bytes, go to scratch.  With addresses formed
+// for every load and the times asked for behind the merge nothing does, and the call takes 741 us instead of 726.)
 template <typename VT, int HMAX, bool DIRECT> constexpr int merge_waves_per_simd() {
   if (DIRECT && sizeof(VT) == 4) return HMAX == 64 ? 4 : HMAX == 48 ? 5 : 6;
+  if (DIRECT) return HMAX >= 48 ? 3 : HMAX == 32 ? 5 : 8;
   return HMAX == 64 ? 3 : 1;
 }
 

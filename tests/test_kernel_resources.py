@@ -1,0 +1,75 @@
+"""What the built kernels take of a compute unit, from the metadata that the compiler put beside their code: the
+occupancy that the rules for launches count on is the one that the kernels have."""
+import os
+import re
+import struct
+import subprocess
+
+import pytest
+
+from paper_2103_16063_amd import binding
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+LLVM = "/opt/rocm/llvm/bin"
+SIMDS, REGISTERS, LDS = 4, 512, 160 * 1024  # of a compute unit; vector registers of a lane on a SIMD
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    """name -> metadata of every kernel in the library's own gfx950 code objects."""
+    tmp = tmp_path_factory.mktemp("code")
+    data = open(binding.LIB_PATH, "rb").read()
+    out, at = {}, data.find(b"__CLANG_OFFLOAD_BUNDLE__")
+    while at >= 0:
+        (n,) = struct.unpack_from("<Q", data, at + 24)
+        p = at + 32
+        for _ in range(n):
+            off, size, length = struct.unpack_from("<QQQ", data, p)
+            target = data[p + 24:p + 24 + length].decode()
+            p += 24 + length
+            if "gfx950" not in target or size == 0:
+                continue
+            path = str(tmp / f"{at}.co")
+            with open(path, "wb") as f:
+                f.write(data[at + off:at + off + size])
+            notes = subprocess.run([f"{LLVM}/llvm-readelf", "--notes", path], capture_output=True, text=True, check=True).stdout
+            for block in re.split(r"\n  - (?=\.)", notes):
+                name = re.search(r"^\s+\.name:\s+(_Z\S+)", block, re.M)
+                if name:
+                    out[name.group(1)] = {k: int(v) for k, v in re.findall(r"\.(\w+):\s+(\d+)\s*$", block, re.M)}
+        at = data.find(b"__CLANG_OFFLOAD_BUNDLE__", at + 24)
+    assert len(out) > 50, "no kernels found in the library"
+    return out
+
+
+def waves_per_simd(k):
+    vector = max(8, (k["vgpr_count"] + 7) // 8 * 8)
+    return min(8, REGISTERS // vector, 8 if k["sgpr_count"] <= 100 else 7)
+
+
+def workgroups_per_cu(k, threads):
+    by_waves = waves_per_simd(k) * SIMDS // (threads // 64)
+    lds = k["group_segment_fixed_size"]
+    return min(by_waves, LDS // lds if lds else by_waves)
+
+
+def test_level_kernels_fit_the_workgroups_that_size_their_items(kernels, tmp_path):
+    exe = str(tmp_path / "occupancy_model")
+    subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "-x", "hip", "--offload-host-only", "-O1", "-std=c++17",
+                    "-o", exe, os.path.join(HERE, "occupancy_model.hip")], check=True)
+    table = {}
+    for line in subprocess.run([exe], capture_output=True, text=True, check=True).stdout.split("\n"):
+        if line:
+            bits, cls, recompute, groups = map(int, line.split())
+            table[bits, cls, recompute] = groups
+    seen, wrong = 0, []
+    for name, k in kernels.items():
+        m = re.search(r"level_merge(?:_one)?_kernelI([jm])Li(\d+)ELb([01])E", name)
+        if not m:
+            continue
+        seen += 1
+        cls = int(m.group(2))  # (the kernel of 48 values takes the narrower levels of 64 devices)
+        expected = table[32 if m.group(1) == "j" else 64, 64 if cls == 48 else cls, int(m.group(3))]
+        if workgroups_per_cu(k, 256) < expected:
+            wrong.append((name, k["vgpr_count"], k["sgpr_count"], workgroups_per_cu(k, 256), expected))
+    assert seen == 2 * 2 * (5 + 3) and not wrong, wrong
