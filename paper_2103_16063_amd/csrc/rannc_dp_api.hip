@@ -635,17 +635,23 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
       // Hundreds of searches: the launches per level are throughput-bound as well.  One launch where it
       // recomputes the stage times (256 searches of 96 blocks and 32 devices 129 us against 187 us of launches
       // per level, 1024 of them 407 against 437 us), and where neither side does (1024 such searches with send
-      // times 1.25 against 1.96 ms; 64 devices, 32-bit values and more than 64 blocks: 3.5 against 3.3 ms).  Where
+      // times 1.25 against 1.96 ms; not 64 devices, 32-bit values and more than 64 blocks: 3.5 against 3.3 ms).  Where
       // only the levels recompute -- 64 devices -- they are the faster ones (1024 searches of 24 blocks: 232 us
-      // against 426 us).  From 32 devices and 65 blocks on only for a class alone: beside the levels of other
+      // against 426 us).  A workgroup that has a compute unit to itself and more than 64 blocks leaves much of the
+      // device idle in a last round that is not full (one_launch_rounds_full: 100 blocks, 64-bit values, 64 devices,
+      // send times, one launch / levels: 256 searches 1.60 / 1.74 ms, 300 2.50 / 1.99, 400 2.79 / 2.59, 768 4.67 /
+      // 4.80, 1100 7.17 / 6.80; 32 devices, times recomputed: 200 198 / 218 us, 256 202 / 228, 300 331 / 309, 520
+      // 471 / 392, 768 506 / 514).  From 32 devices and 65 blocks on only for a class alone: beside the levels of other
       // classes its workgroups stand in their way (2048 searches of 128 blocks in four classes: 1.79 against
       // 1.69 ms).  Where it recomputes the times one launch is ahead from fewer searches on (8 stages of 64 blocks
       // and 32 devices: 64 searches 66 against 82 us; of 128 blocks and 16 devices: 64 searches level, 128 of
       // them 116 against 133 us).
       const bool alone = sh.nprob == Q;
       const int many = !direct_ok ? 256 : sh.max_N <= 64 ? 64 : 128;
+      const bool one_per_cu = h->bits == 64 && (cls == 64 || (cls == 32 && direct_ok));
       const bool batch = sh.nprob >= many && (direct_ok || !recompute_cls[k]) &&
-                         (cls <= 16 || sh.max_N <= 64 || (alone && (cls < 64 || h->bits == 64)));
+                         (cls <= 16 || sh.max_N <= 64 ||
+                          (alone && (one_per_cu ? rannc::one_launch_rounds_full(sh.nprob, h->n_cus) : cls < 64)));
       fused[k] = !scan && !split && sh.max_N <= rannc::small_max_blocks() &&
                  (h->fused_small == 1 ? (batch || tiny) : h->fused_small == 2);
       fused_direct[k] = fused[k] && direct_ok;

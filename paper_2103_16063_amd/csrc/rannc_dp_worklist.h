@@ -109,4 +109,11 @@ inline int merge_workgroups_per_cu(int bits, int DP, bool recompute) {
   return DP == 64 ? 2 : DP == 32 ? 3 : DP == 16 ? 4 : 6;
 }
 
+// One-launch kernel, a workgroup per search and per compute unit: whether its rounds leave little of the device
+// idle, a lone round a quarter of it, several a sixteenth of the whole.
+inline bool one_launch_rounds_full(int searches, int cus) {
+  const int64_t places = ((int64_t)searches + cus - 1) / cus * cus;
+  return places == cus ? 4ll * searches >= 3ll * cus : 16ll * searches >= 15 * places;
+}
+
 }  // namespace rannc
