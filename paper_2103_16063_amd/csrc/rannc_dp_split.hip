@@ -98,17 +98,18 @@ __global__ __launch_bounds__(64) void level_split_kernel(const ProblemDev *__res
 // stage does not fit; two buffers, so that a row costs one barrier), and the eight waves split the device
 // totals d between them (d = s + wave, s + wave + 8, ...): a lane keeps the running best of its column
 // for each of its wave's d in registers.  The carried maxima of the row of the previous level are held
-// one d' per lane and broadcast by lane reads.  split_finalize_kernel then turns the packed winners
-// of the level into V and the two carried maxima, and clears the key table for the next level.
+// one d' per lane and broadcast by lane reads.  The packed winners of the level become V
+// and the two carried maxima in the next level's launch, or in a launch of their own (split_apart); the key table
+// of the level before is cleared there for the level after next.
 //
 // Bound by vector instructions (four per candidate) and, for few rows, by latency.  With the stage times
 // read from their two tables (built in front), items of four rows, d' in the key and every wave holding
 // the totals of the whole class, a level of the outer driver at 96 blocks (24 searches, 31 levels) read
-// 63 MB and took 22.5 us on average (call 906 -> 575 us), and 1024 blocks at 64 devices 9.6 ms (now 5.5).
+// 63 MB and took 22.5 us on average (call 906 us), and 1024 blocks at 64 devices 9.6 ms (now 534 us and 4.9 ms).
 // Packed winner of a cell: (sum, i) in one 64-bit word whose unsigned order is the lexicographic order
 // of the pair.  32-bit tables: 32 + 32 bits.  64-bit tables: 48 + 16 bits, the sums stay below 2^42 - 1
 // (kSplitPackedMax, a bound of the quotient as well).  d' is not carried: the level's inner loop is four
-// operations per candidate without it and six with it, and the finalize step finds the first d' of row
+// operations per candidate without it and six with it, and split_winner finds the first d' of row
 // i whose sum is the cell's value.
 template <typename VT> __device__ __forceinline__ unsigned long long split_pack(VT v, uint32_t i);
 template <> __device__ __forceinline__ unsigned long long split_pack<uint32_t>(uint32_t v, uint32_t i) {
@@ -204,7 +205,10 @@ __device__ __forceinline__ void split_winners(const ProblemDev &pr, const int s,
 // call: one at a time 535 / 209 us, two 521 / 203, four, which take a workgroup's registers off each compute
 // unit, 552 / 219.  Totals next to each other instead of eight apart, with a sliding window of times in
 // registers instead of two LDS reads per candidate: 207 us alone, but 588 for the driver, whose waves then
-// wait for the one with the most candidates at every row.)
+// wait for the one with the most candidates at every row.)  TWO: not for 64-bit values at 16 and 64 devices, where it
+// takes 82 registers instead of 68, two workgroups to a compute unit instead of three, and 210 instead of 166 (256
+// searches of 128 blocks, 16 devices 2.66 instead of 2.65 ms, in the next level's launch 3.35 instead of 2.93; 1024
+// blocks, 64 devices 11.8 instead of 9.6 ms).
 template <typename VT, int KP, int K0, int U>
 __device__ __forceinline__ void split_candidates(int dp, int d0, int lane, VT F, VT B, const VT *sf, const VT *sb, VT (&row_v)[KP]) {
   VT af[U], ab[U];
@@ -219,34 +223,39 @@ __device__ __forceinline__ void split_candidates(int dp, int d0, int lane, VT F,
       row_v[k] = vmin(row_v[k], split_sum(vmax(af[u], f[(kSplitWaves * k - u) * 64]), vmax(ab[u], b[(kSplitWaves * k - u) * 64])));
   }
 }
-template <typename VT, int KP, int K0>
+template <typename VT, int KP, int K0, bool TWO>
 __device__ __forceinline__ void split_segment(int lo, int hi, int d0, int lane, VT F, VT B, const VT *sf, const VT *sb,
                                               VT (&row_v)[KP]) {
   int dp = lo;
+  if constexpr (TWO) {
 #pragma unroll 1
-  for (; dp + 1 <= hi; dp += 2) split_candidates<VT, KP, K0, 2>(dp, d0, lane, F, B, sf, sb, row_v);
+    for (; dp + 1 <= hi; dp += 2) split_candidates<VT, KP, K0, 2>(dp, d0, lane, F, B, sf, sb, row_v);
+  }
 #pragma unroll 1
   for (; dp <= hi; ++dp) split_candidates<VT, KP, K0, 1>(dp, d0, lane, F, B, sf, sb, row_v);
 }
 
-template <typename VT, int KP, int K0>
+template <typename VT, int KP, int K0, bool TWO>
 __device__ __forceinline__ void split_row(int dlo, int D, int d0, int lane, VT F, VT B, const VT *sf, const VT *sb,
                                           VT (&row_v)[KP]) {
   if constexpr (K0 < KP) {
     // d' in [d_{K0-1}, d_{K0} - 1]: exactly the totals d_k with k >= K0 lie above it
     const int lo = K0 == 0 ? dlo : max(dlo, d0 + kSplitWaves * (K0 - 1));
     const int hi = min(d0 + kSplitWaves * K0 - 1, D - 1);
-    split_segment<VT, KP, K0>(lo, hi, d0, lane, F, B, sf, sb, row_v);
-    split_row<VT, KP, K0 + 1>(dlo, D, d0, lane, F, B, sf, sb, row_v);
+    split_segment<VT, KP, K0, TWO>(lo, hi, d0, lane, F, B, sf, sb, row_v);
+    split_row<VT, KP, K0 + 1, TWO>(dlo, D, d0, lane, F, B, sf, sb, row_v);
   }
 }
 
 // The rows of one work item.  KP: device totals per wave, and replica counts it computes the times of:
 // the D-s+1 totals (and counts) that are left at level s, over eight waves.
-template <typename VT, int DP, int KP>
+// rowF, rowB: the two maxima of row i_lo at level s - 1, the next row's `stride` values behind them.
+template <typename VT, int DP, int KP, typename RP>
 __device__ __forceinline__ void split_rows(const ProblemDev &pr, const int s, const int c, const int i_lo, const int i_hi,
-                                           VT (*sf)[DP * 64], VT (*sb)[DP * 64], const int n_buf, const VT *rowF, const VT *rowB) {
+                                           VT (*sf)[DP * 64], VT (*sb)[DP * 64], const int n_buf, const RP rowF, const RP rowB,
+                                           const int stride) {
   constexpr VT INF = Lim<VT>::inf;
+  constexpr bool kTwo = sizeof(VT) == 4 || (DP != 16 && DP != 64);
   const int N = pr.N, D = pr.D, nch = pr.nch;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -260,8 +269,8 @@ __device__ __forceinline__ void split_rows(const ProblemDev &pr, const int s, co
   auto load = [&](int i) -> Row {  // the next row's, while one is worked on (clamped into the item)
     const int ic = min(i, i_hi);
     Row r;
-    r.F = rowF[(ic - i_lo) * DP + min(lane, D - 1)];  // lane q holds d' = q + 1
-    r.B = rowB[(ic - i_lo) * DP + min(lane, D - 1)];
+    r.F = rowF[(ic - i_lo) * stride + min(lane, D - 1)];  // lane q holds d' = q + 1
+    r.B = rowB[(ic - i_lo) * stride + min(lane, D - 1)];
     r.rmn = rmin[unit_index(nch, ic, c) * 64 + lane];
     return r;
   };
@@ -312,7 +321,7 @@ __device__ __forceinline__ void split_rows(const ProblemDev &pr, const int s, co
     VT row_v[KP];
 #pragma unroll
     for (int k = 0; k < KP; ++k) row_v[k] = INF;
-    split_row<VT, KP, 0>(dlo, D, d0, lane, r.F, r.B, f, b, row_v);
+    split_row<VT, KP, 0, kTwo>(dlo, D, d0, lane, r.F, r.B, f, b, row_v);
 #pragma unroll
     for (int k = 0; k < KP; ++k) {  // rows ascend: an equal sum keeps the earlier one
       const bool ok = row_v[k] < best_v[k];
@@ -335,18 +344,22 @@ __device__ __forceinline__ void split_rows(const ProblemDev &pr, const int s, co
 
 // items: workgroups of the grid that work on the level's items; the others, `blocks` to a device total from
 // s - 2 on, finish level s - 1.  Most rows of an item: kSplitMaxRows.
-template <typename VT, int DP>
+// APART: level s - 1 has been finished by a launch of its own (split_apart); the grid has items only, which read
+// their rows' maxima from memory, a row ahead.
+template <typename VT, int DP, bool APART>
 __global__ __launch_bounds__(kSplitThreads) void level_split_fast_kernel(
     const ProblemDev *__restrict__ probs, const int s, const int items, const int blocks) {
   const ProblemDev &pr = probs[blockIdx.z];
-  __shared__ double inv[65];
-  if (threadIdx.x < 64) inv[threadIdx.x + 1] = 1.0 / (double)(threadIdx.x + 1);
-  if ((int)blockIdx.x >= items) {
-    if (s - 1 > pr.S_eff || s == 2) return;  // (level 1 has no keys)
-    __syncthreads();
-    const int at = (int)blockIdx.x - items;
-    split_winners<VT>(pr, s - 1, at % blocks, s - 2 + at / blocks, inv);
-    return;
+  __shared__ double inv[APART ? 1 : 65];
+  if constexpr (!APART) {
+    if (threadIdx.x < 64) inv[threadIdx.x + 1] = 1.0 / (double)(threadIdx.x + 1);
+    if ((int)blockIdx.x >= items) {
+      if (s - 1 > pr.S_eff || s == 2) return;  // (level 1 has no keys)
+      __syncthreads();
+      const int at = (int)blockIdx.x - items;
+      split_winners<VT>(pr, s - 1, at % blocks, s - 2 + at / blocks, inv);
+      return;
+    }
   }
   if (s > pr.S_eff) return;
   const int N = pr.N, D = pr.D;
@@ -364,34 +377,40 @@ __global__ __launch_bounds__(kSplitThreads) void level_split_fast_kernel(
   constexpr int BUF = 4 * DP * 64 * (int)sizeof(VT) <= 64 * 1024 ? 2 : 1;
   __shared__ VT sf[BUF][DP * 64], sb[BUF][DP * 64];
   // the two maxima of the item's rows at level s - 1
-  __shared__ VT rowF[kSplitMaxRows * DP], rowB[kSplitMaxRows * DP];
-  const int n = i_hi - i_lo + 1;
-  if (s == 2) {
-    const VT RANNC_GLOBAL *F = gptr((const VT *)pr.VF) + (int64_t)i_lo * pr.DP, *B = gptr((const VT *)pr.VB) + (int64_t)i_lo * pr.DP;
-    for (int e = threadIdx.x; e < n * DP; e += kSplitThreads) {
-      const int64_t at = (int64_t)(e / DP) * pr.DP + min(e % DP, pr.DP - 1);
-      rowF[e] = F[at];
-      rowB[e] = B[at];
+  [[maybe_unused]] __shared__ VT rowF[APART ? 1 : kSplitMaxRows * DP], rowB[APART ? 1 : kSplitMaxRows * DP];
+  const VT RANNC_GLOBAL *const F = gptr((const VT *)pr.VF) + ((int64_t)(s - 2) * (N + 1) + i_lo) * pr.DP;
+  const VT RANNC_GLOBAL *const B = gptr((const VT *)pr.VB) + ((int64_t)(s - 2) * (N + 1) + i_lo) * pr.DP;
+  if constexpr (!APART) {
+    const int n = i_hi - i_lo + 1;
+    if (s == 2) {
+      for (int e = threadIdx.x; e < n * DP; e += kSplitThreads) {
+        const int64_t at = (int64_t)(e / DP) * pr.DP + min(e % DP, pr.DP - 1);
+        rowF[e] = F[at];
+        rowB[e] = B[at];
+      }
+    } else {
+      for (int e = threadIdx.x; e < n * DP; e += kSplitThreads) rowF[e] = rowB[e] = Lim<VT>::inf;
+      __syncthreads();
+      const unsigned long long RANNC_GLOBAL *K = split_keys(pr, s - 1);
+      const int nd = D - s + 1;  // d' = s-1 .. D-1
+      for (int e = (int)(threadIdx.x / kFinalizeLanes); e < n * nd; e += kSplitThreads / kFinalizeLanes) {
+        const int q = e / nd, d = s - 1 + e - q * nd;
+        const unsigned long long key = K[(int64_t)(d - 1) * (N + 1) + i_lo + q];
+        if (key != ~0ull)
+          split_winner<VT>(pr, s - 1, i_lo + q, d, key, inv, [&](VT, VT f, VT b) {
+            rowF[q * DP + d - 1] = f;
+            rowB[q * DP + d - 1] = b;
+          });
+      }
     }
-  } else {
-    for (int e = threadIdx.x; e < n * DP; e += kSplitThreads) rowF[e] = rowB[e] = Lim<VT>::inf;
     __syncthreads();
-    const unsigned long long RANNC_GLOBAL *K = split_keys(pr, s - 1);
-    const int nd = D - s + 1;  // d' = s-1 .. D-1
-    for (int e = (int)(threadIdx.x / kFinalizeLanes); e < n * nd; e += kSplitThreads / kFinalizeLanes) {
-      const int q = e / nd, d = s - 1 + e - q * nd;
-      const unsigned long long key = K[(int64_t)(d - 1) * (N + 1) + i_lo + q];
-      if (key != ~0ull)
-        split_winner<VT>(pr, s - 1, i_lo + q, d, key, inv, [&](VT, VT f, VT b) {
-          rowF[q * DP + d - 1] = f;
-          rowB[q * DP + d - 1] = b;
-        });
-    }
   }
-  __syncthreads();
-#define RANNC_ROWS(K)                                                                                          \
-  case K:                                                                                                      \
-    if constexpr (kSplitWaves * K <= DP) split_rows<VT, DP, K>(pr, s, c, i_lo, i_hi, sf, sb, BUF, rowF, rowB); \
+#define RANNC_ROWS(K)                                                                                              \
+  case K:                                                                                                          \
+    if constexpr (kSplitWaves * K <= DP) {                                                                         \
+      if constexpr (APART) split_rows<VT, DP, K>(pr, s, c, i_lo, i_hi, sf, sb, BUF, F, B, pr.DP);                  \
+      else split_rows<VT, DP, K>(pr, s, c, i_lo, i_hi, sf, sb, BUF, (const VT *)rowF, (const VT *)rowB, (int)DP);  \
+    }                                                                                                              \
     break;
   switch ((D - s + kSplitWaves) / kSplitWaves) {
     RANNC_ROWS(1) RANNC_ROWS(2) RANNC_ROWS(3) RANNC_ROWS(4)
@@ -401,11 +420,11 @@ __global__ __launch_bounds__(kSplitThreads) void level_split_fast_kernel(
 #undef RANNC_ROWS
 }
 
-// The winners of a launch's last level.
+// The winners of level s: of a launch's last level (those of shorter searches are done), or of every one.
 template <typename VT>
-__global__ __launch_bounds__(kSplitThreads) void split_finalize_kernel(const ProblemDev *__restrict__ probs, const int s) {
+__global__ __launch_bounds__(kSplitThreads) void split_finalize_kernel(const ProblemDev *__restrict__ probs, const int s, const int every) {
   const ProblemDev &pr = probs[blockIdx.z];
-  if (s != pr.S_eff) return;  // (those of shorter searches are done)
+  if (every ? s > pr.S_eff : s != pr.S_eff) return;
   __shared__ double inv[65];
   if (threadIdx.x < 64) inv[threadIdx.x + 1] = 1.0 / (double)(threadIdx.x + 1);
   __syncthreads();
@@ -455,19 +474,37 @@ int split_rows_per_item(const LaunchShape &sh, int DP) {
   return (int)std::max<int64_t>(most > kSplitSmallRows ? 4 : 1, rows);
 }
 
+// Whether every level's winners are unpacked by a launch of their own.  A row of a level is listed once per column
+// chunk, so with the unpacking in the next level's launch every row is unpacked by several workgroups and once more for
+// memory, which costs a launch that fills the device more than the chain of one launch fewer per level saves.  Per
+// call, in the next level's launch / apart, 32-bit values: 64 devices 128 blocks 447 / 505 us, 256 (640 rows) 946 / 932,
+// 1024 5.62 / 4.88 ms, 32 searches of 128 2.75 / 2.22; 32 devices: outer driver at 128 blocks (1 728 rows) 623 / 631 us,
+// 12 searches of 128 (2 304) 463 / 382, 700 blocks (4 200) 688 / 627; 16 devices: 900 blocks (7 620) 394 / 408, 64
+// searches of 128 (12 288) 708 / 631; 8 devices: 900 blocks 196 / 203, 256 searches of 128 (49 152) 678 / 633.  64-bit
+// values, whose workgroups take longer: 32 devices: 256 blocks (640 rows) 258 / 287, 4 searches of 128 (768) 326 / 309;
+// 16 devices: 500 blocks (2 304) 268 / 311, 64 searches of 40 (2 560) 315 / 308; 8 devices: 16 searches of 128 (3 072)
+// 193 / 196, 64 of them (12 288) 325 / 292.
+static bool split_apart(const LaunchShape &sh, int bits, int DP) {
+  const int64_t from = DP == 64 ? 512 : DP == 32 ? (bits == 64 ? 768 : 2048) : DP == 16 ? (bits == 64 ? 2560 : 8192) : 10240;
+  return sh.wide_rows >= from;
+}
+
 template <typename VT>
 static void split_fast_go(const ProblemDev *p, const LaunchShape &sh, int DP, int s, int items, hipStream_t st) {
   constexpr int cells = kSplitThreads / kFinalizeLanes;
   const int blocks = (sh.max_N + cells) / cells;
+  const bool apart = split_apart(sh, (int)sizeof(VT) * 8, DP);
   for (int q0 = 0; q0 < sh.nprob; q0 += 65535) {
     const int nq = min(65535, sh.nprob - q0);
-    const dim3 grid((unsigned)(items + (s > 2 ? blocks * (sh.max_D - s + 3) : 0)), 1, nq), block(kSplitThreads);
-    if (DP == 8) hipLaunchKernelGGL((level_split_fast_kernel<VT, 8>), grid, block, 0, st, p + q0, s, items, blocks);
-    else if (DP == 16) hipLaunchKernelGGL((level_split_fast_kernel<VT, 16>), grid, block, 0, st, p + q0, s, items, blocks);
-    else if (DP == 32) hipLaunchKernelGGL((level_split_fast_kernel<VT, 32>), grid, block, 0, st, p + q0, s, items, blocks);
-    else hipLaunchKernelGGL((level_split_fast_kernel<VT, 64>), grid, block, 0, st, p + q0, s, items, blocks);
-    if (s == sh.max_S_eff)
-      hipLaunchKernelGGL((split_finalize_kernel<VT>), dim3(blocks, sh.max_D, nq), block, 0, st, p + q0, s);
+    const dim3 grid((unsigned)(items + (s > 2 && !apart ? blocks * (sh.max_D - s + 3) : 0)), 1, nq), block(kSplitThreads);
+#define GO(W, X)             \
+  if (DP == W && apart == X) \
+    hipLaunchKernelGGL((level_split_fast_kernel<VT, W, X>), grid, block, 0, st, p + q0, s, items, blocks);
+    GO(8, false) GO(16, false) GO(32, false) GO(64, false)
+    GO(8, true) GO(16, true) GO(32, true) GO(64, true)
+#undef GO
+    if (apart || s == sh.max_S_eff)
+      hipLaunchKernelGGL((split_finalize_kernel<VT>), dim3(blocks, sh.max_D, nq), block, 0, st, p + q0, s, apart ? 1 : 0);
   }
 }
 

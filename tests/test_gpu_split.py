@@ -201,3 +201,25 @@ def test_split_64bit_packed_at_size():
         for k in ra:
             assert np.array_equal(ra[k], rb[k]), k
         assert_tables_match(pr, sa, 0, args=False)
+
+
+# A launch whose widest class has at least so many rows (a chain of N <= 64 blocks has N) finishes every level's
+# winners in a launch of its own: either side of each line, chains of different stage counts together.
+@pytest.mark.parametrize("width,D,rows", [(WIDTHS[0], 57, 512), (1 << 41, 64, 512), (WIDTHS[0], 32, 2048), (1 << 41, 29, 768),
+                                          (WIDTHS[0], 13, 8192), (1 << 41, 16, 2560), (WIDTHS[0], 8, 10240), (1 << 41, 7, 10240)])
+@pytest.mark.parametrize("N", [63, 64])
+def test_winners_in_the_next_level_or_apart(width, D, rows, N):
+    Q = rows // 64
+    distinct = [_case(5100 + k, N, D, [2, 5, 3, 7, 4][k], (1.5, 3.0)[k % 2], 5000, comm=D % 2 == 0) for k in range(5)]
+    if width > B.NARROW_MAX_TOTAL_TIME:
+        for pr in distinct:
+            for key in ("time_ns", "time_bwd_ns", "cut_bytes"):
+                if key in pr:
+                    pr[key] = pr[key] << 20
+    probs = [distinct[q % 5] for q in range(Q)]
+    res, sess = gpu_run(probs, max_total_time_ns=width)
+    with sess:
+        want = [oracle.solve(pr) for pr in distinct]
+        assert_results_match(probs, res, oracle_results=[want[q % 5] for q in range(Q)])
+        for q in (1, Q - 1):
+            assert_tables_match(probs[q], sess, q, args=False)

@@ -73,3 +73,17 @@ def test_level_kernels_fit_the_workgroups_that_size_their_items(kernels, tmp_pat
         if workgroups_per_cu(k, 256) < expected:
             wrong.append((name, k["vgpr_count"], k["sgpr_count"], workgroups_per_cu(k, 256), expected))
     assert seen == 2 * 2 * (5 + 3) and not wrong, wrong
+
+
+def test_split_kernels_fit_the_workgroups_their_form_was_chosen_for(kernels):
+    # (bits, class) -> workgroups of eight waves on a compute unit, winners unpacked in the launch or apart
+    expected = {(32, 8): 4, (32, 16): 4, (32, 32): 3, (32, 64): 2, (64, 8): 4, (64, 16): 3, (64, 32): 2, (64, 64): 1}
+    seen, wrong = 0, []
+    for name, k in kernels.items():
+        m = re.search(r"level_split_fast_kernelI([jm])Li(\d+)E", name)
+        if not m:
+            continue
+        seen += 1
+        if workgroups_per_cu(k, 512) < expected[32 if m.group(1) == "j" else 64, int(m.group(2))]:
+            wrong.append((name, k["vgpr_count"], workgroups_per_cu(k, 512)))
+    assert seen == 2 * 2 * 4 and not wrong, wrong
