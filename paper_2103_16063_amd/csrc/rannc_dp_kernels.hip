@@ -2263,15 +2263,20 @@ constexpr int kSmallMaxN = 128;
 constexpr int kSmallWavesMax = 16;
 template <typename VT, int DP> constexpr int small_waves() { return sizeof(VT) * DP >= 256 ? 8 : kSmallWavesMax; }
 
-// Waves per SIMD the one-launch kernel is compiled for.  The recomputing form on 32-bit values at 16
-// devices needs 70 registers left alone, one wave per SIMD short of TWO workgroups per compute unit
-// (16 waves each); held to 64 registers the two rounds of a batch of 512 searches run side by side.
-template <typename VT, int DP, bool DIRECT> constexpr int small_waves_per_simd() {
-  return (DIRECT && sizeof(VT) == 4 && DP == 16) ? 8 : small_waves<VT, DP>() / 4;
+// Waves per SIMD the one-launch kernel is compiled for.  A batch of hundreds of searches wants TWO workgroups of
+// sixteen waves on a compute unit, 64 registers.  The recomputing form on 32-bit values at 16 devices is held to them
+// (70 left alone).  The forms at 8 devices, and the table form on 32-bit values at 16, get there without the plan
+// recovery, which takes 10 to 25 registers and is for few searches: they have an instance without it (PLAN = false) and
+// one with.  (Both as one had 52 to 77 registers and one workgroup to a compute unit: 2000 searches of 17 blocks at 8
+// devices 179 us a call instead of 159, 1000 of 100 blocks 242 instead of 204, with send times 520 instead of 392, at 16
+// devices 743 instead of 673.)
+template <typename VT, int DP, bool DIRECT> constexpr bool small_plan_apart() { return DP == 8 || (DP == 16 && sizeof(VT) == 4 && !DIRECT); }
+template <typename VT, int DP, bool DIRECT, bool PLAN> constexpr int small_waves_per_simd() {
+  return !PLAN || (DIRECT && sizeof(VT) == 4 && DP == 16) ? 8 : small_waves<VT, DP>() / 4;
 }
 
-template <typename VT, int DP, bool DIRECT>
-__global__ __launch_bounds__((64 * small_waves<VT, DP>())) __attribute__((amdgpu_waves_per_eu((small_waves_per_simd<VT, DP, DIRECT>()))))
+template <typename VT, int DP, bool DIRECT, bool PLAN>
+__global__ __launch_bounds__((64 * small_waves<VT, DP>())) __attribute__((amdgpu_waves_per_eu((small_waves_per_simd<VT, DP, DIRECT, PLAN>()))))
 void solve_small_kernel(
     const ProblemDev *src, ProblemDev *probs, int64_t *d_opt, int32_t *d_n_stages, int64_t *d_est,
     int32_t *d_status, const ProblemDev one, int use_one, int plan_stride, const PlanResults results) {
@@ -2305,6 +2310,11 @@ void solve_small_kernel(
   const int per_level = (N + 1) * LS;
   const int bufs = DIRECT ? min(max(S_eff, kLevelBufs), kLevelBufs * (kSmallMaxN + 1) * LS / per_level) : kLevelBufs;
   auto level = [&](int s) -> VT * { return levels + (s - 1) % bufs * per_level; };
+  // (inside the levels: what is formed from it is formed there again and takes no register for the whole loop)
+  auto opaque = [](int x) -> int {
+    if constexpr (!PLAN) asm volatile("" : "+v"(x));
+    return x;
+  };
 
   // ---- prefix sums and validation (as setup_kernel) ----
   if (tid == 0) {
@@ -2458,7 +2468,7 @@ void solve_small_kernel(
       // rows, stages that do not fit among them, 32 blocks took nine passes a level; the outer driver's
       // searches of that size hold two passes of stages that fit.)
       for (int f = wave; f < passes; f += kSmallWaves) {
-        const uint32_t word = s_word[64 * f + lane];
+        const uint32_t word = s_word[64 * f + opaque(lane)];
         const int row = (int)(word & 255u), j = (int)(word >> 8) & 255, rmn = (int)(word >> 16);
         // some (s-1)-stage plan covers blocks 1..row
         const bool act = rmn <= rl && row >= s - 1 && prev[row * LS + D - 1] != INF;
@@ -2525,12 +2535,12 @@ void solve_small_kernel(
       // same threads before their passes of level s-1.
       if (s < S_eff) {
         VT *next = level(s + 1);
-        for (int e = tid; e < (N + 1) * LS; e += NT) next[e] = ((e % LS) < D) ? INF : (VT)0;
+        for (int e = opaque(tid); e < (N + 1) * LS; e += NT) next[e] = ((e % LS) < D) ? INF : (VT)0;
       }
     }
     lds_barrier();
     VT RANNC_GLOBAL *Vs = Vg + (int64_t)(s - 1) * lvl;
-    for (int e = tid; e < (N + 1) * DP; e += NT) Vs[e] = cur[(e / DP) * LS + (e % DP)];
+    for (int e = opaque(tid); e < (N + 1) * DP; e += NT) Vs[e] = cur[(e / DP) * LS + (e % DP)];
     if (tid == 0) s_top[s - 1] = cur[N * LS + D - 1];
   }
   __syncthreads();
@@ -2545,6 +2555,7 @@ void solve_small_kernel(
     const Chosen chosen = select_finish(pr, v, st, d_opt, d_n_stages, d_est, d_status);
     if (tid == 0) s_chosen = chosen;
   }
+  if constexpr (!PLAN) return;
   if (!results.d_stage_end) return;
   if constexpr (DIRECT) asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 2, 2), 0" ::);  // (direct_consts_init)
   // ---- plan recovery, where the caller wants it from this launch: out of LDS, but for levels that had to make room
@@ -2824,10 +2835,13 @@ hipError_t launch_solve_small(const ProblemDev *src, ProblemDev *p, int Q, int b
   const ProblemDev one = host_one ? *host_one : ProblemDev{};
   const PlanResults plan = results ? *results : PlanResults{};
   if (direct && DP > 32) return hipErrorInvalidValue;
-#define GO(B, T, W, X)                                                                                 \
-  if (bits == B && DP == W && direct == X)                                                             \
-    hipLaunchKernelGGL((solve_small_kernel<T, W, X>), dim3(Q), dim3(64 * small_waves<T, W>()), 0, st, src, p, d_opt, \
-                       d_n_stages, d_est, d_status, one, host_one ? 1 : 0, plan_stride, plan);
+#define GO(B, T, W, X)                                                                                                  \
+  if (bits == B && DP == W && direct == X) {                                                                            \
+    constexpr bool apart = small_plan_apart<T, W, X>();                                                                 \
+    auto *const kernel = apart && !results ? solve_small_kernel<T, W, X, !apart> : solve_small_kernel<T, W, X, true>;   \
+    hipLaunchKernelGGL(kernel, dim3(Q), dim3(64 * small_waves<T, W>()), 0, st, src, p, d_opt, d_n_stages, d_est,        \
+                       d_status, one, host_one ? 1 : 0, plan_stride, plan);                                             \
+  }
   GO(32, uint32_t, 8, false) GO(32, uint32_t, 16, false) GO(32, uint32_t, 32, false) GO(32, uint32_t, 64, false)
   GO(64, uint64_t, 8, false) GO(64, uint64_t, 16, false) GO(64, uint64_t, 32, false) GO(64, uint64_t, 64, false)
   GO(32, uint32_t, 8, true) GO(32, uint32_t, 16, true) GO(32, uint32_t, 32, true)

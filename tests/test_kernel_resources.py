@@ -87,3 +87,14 @@ def test_split_kernels_fit_the_workgroups_their_form_was_chosen_for(kernels):
         if workgroups_per_cu(k, 512) < expected[32 if m.group(1) == "j" else 64, int(m.group(2))]:
             wrong.append((name, k["vgpr_count"], workgroups_per_cu(k, 512)))
     assert seen == 2 * 2 * 4 and not wrong, wrong
+
+
+def test_one_launch_kernels_of_batches_fit_twice_on_a_compute_unit(kernels):
+    # (bits, class, times recomputed): sixteen waves each, 64 registers
+    twice = {(32, 8, 0), (32, 8, 1), (64, 8, 0), (64, 8, 1), (32, 16, 0), (32, 16, 1)}
+    fits = set()
+    for name, k in kernels.items():
+        m = re.search(r"solve_small_kernelI([jm])Li(\d+)ELb([01])E", name)
+        if m and workgroups_per_cu(k, 1024) >= 2:
+            fits.add((32 if m.group(1) == "j" else 64, int(m.group(2)), int(m.group(3))))
+    assert twice <= fits, twice - fits
