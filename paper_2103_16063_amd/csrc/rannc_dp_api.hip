@@ -736,7 +736,8 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
       ok = rannc::launch_setup(src + cls_start[k], cp, sh.nprob, rows_for_list, merge_items[k], slots, recompute_cls[k],
                                max_rows, host_one, st) == hipSuccess;
       ok = ok && staging_read();
-      ok = ok && rannc::launch_build(cp, sh, h->bits, kClasses[k], parts, st) == hipSuccess;
+      ok = ok && (recompute_cls[k] ? rannc::launch_build_passes(cp, sh, h->bits, kClasses[k], st)
+                                   : rannc::launch_build(cp, sh, h->bits, kClasses[k], parts, st)) == hipSuccess;
       if (split) ok = ok && rannc::launch_split_level1(cp, sh, h->bits, st) == hipSuccess;
     }
   }

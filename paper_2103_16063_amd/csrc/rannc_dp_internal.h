@@ -143,6 +143,9 @@ struct LaunchShape {
 // `probs` points at the first ProblemDev of the launch; problems of one launch are contiguous.
 // parts: 1 = fits-in-memory tables (rmin, ufit) and level 1 of V, 2 = the stage-time table, 3 = both
 hipError_t launch_build(const ProblemDev *probs, const LaunchShape &sh, int bits, int DP, int parts, hipStream_t st);
+// launch_build for the searches whose level kernel recomputes the stage times: parts = 1, and the entries of the
+// pass list that launch_setup has laid out
+hipError_t launch_build_passes(const ProblemDev *probs, const LaunchShape &sh, int bits, int DP, hipStream_t st);
 // prefix sums, validation, initial V, windows and work list of the searches of a launch.
 // rows_per_item: > 0 fixed, -1 chosen on the device for the sorted-merge kernel (the smallest item size
 // whose item count fits max_items)

@@ -232,13 +232,8 @@ void build_kernel(const ProblemDev *__restrict__ probs, const int parts, const i
   if (c >= pr.nch) return;
   auto one_row = [&](const int i) {
     const bool level1 = i == 0 && (parts & 1);
-    UnitStages<VT> st;
     (void)build_unit<VT, DP, true>(pr, pr.T, pr.P, pr.A, pr.C, i, c, lane, level1 ? tile : nullptr, DP + 1, 64 * c + 1,
-                                   pr.TB, (parts & 2) != 0, &st);
-    if ((parts & 1) && pr.ends && pr.S_eff > 1) {
-      const uint32_t *const rec = pass_chunks(pr) + 4 * c;
-      pass_entries<VT>(pr, i, c, lane, st.fits, st.rmin, st.tij, pr.wlo[c], PassChunk{rec[0], rec[1], rec[2], rec[3]}, pr.ends + pr.N);
-    }
+                                   pr.TB, (parts & 2) != 0);
     if (level1) {
       // rows j = 64c+1 .. of level 1 are contiguous in V: written with consecutive lanes on
       // consecutive words (columns d > D keep the zeros of the fill)
@@ -262,6 +257,105 @@ void build_kernel(const ProblemDev *__restrict__ probs, const int parts, const i
       one_row(i);
     }
   }
+}
+
+// whether bytes P (not divided) + ceil(A / D) fit M
+__device__ __forceinline__ bool fits_at(uint64_t P, uint64_t A, uint64_t M, int D) {
+  if (P > M) return false;
+  const uint64_t slack = M - P;
+  return A <= slack * (uint64_t)D || __umul64hi(slack, (uint64_t)D) != 0;  // ceil(A/D) <= slack  <=>  A <= slack D
+}
+
+// Of row i the first chunk without a stage that fits (row 0 has its units written in any case, and a chunk's last row
+// closes the chunk's passes).  end: the row's last block that fits.
+__device__ __forceinline__ int row_units_behind(int i, int end, int N) {
+  return max((end + 63) >> 6, (i >> 6) + (i == 0 || i == min(i | 63, N - 1) ? 1 : 0));
+}
+
+// The units of row i from chunk `behind` on, "fits nowhere" for all of their stages: one wave, or `parts` of them.
+// FEW: at most sixteen chunks, one wave.  (The loops make the compiler spill eighty more scalar registers in
+// prepare_kernel: 96 blocks 11.3 -> 13.6 us.)
+template <bool FEW>
+__device__ __forceinline__ void units_that_fit_nowhere(const ProblemDev &pr, int i, int behind, int part, int parts) {
+  const int lane = threadIdx.x & 63, from = max(behind, i >> 6), rest = pr.nch - from;
+  if (rest <= 0) return;
+  const int64_t u = unit_index(pr.nch, i, from);
+  typedef uint32_t Quad __attribute__((ext_vector_type(4)));
+  Quad RANNC_GLOBAL *const rm = (Quad RANNC_GLOBAL *)(gptr(pr.rmin) + u * 64);
+  uint8_t RANNC_GLOBAL *const uf = gptr(pr.ufit) + u;
+  if constexpr (FEW) {
+    if (lane < 4 * rest) rm[lane] = Quad{~0u, ~0u, ~0u, ~0u};
+    if (lane < rest) uf[lane] = 0;
+  } else {
+    for (int e = 64 * part + lane; e < 4 * rest; e += 64 * parts) rm[e] = Quad{~0u, ~0u, ~0u, ~0u};
+    for (int e = 64 * part + lane; e < rest; e += 64 * parts) uf[e] = 0;
+  }
+}
+
+// Level 1: one stage on d devices, an entry per thread and turn (a thread keeps its d), by workgroup `group` of `groups`
+// of nt threads.  C, TB: looked at with send (comm) and backward (bwd) times.
+template <typename VT>
+__device__ __forceinline__ void level_one(const ProblemDev &pr, const int64_t *T, const int64_t *P, const int64_t *A, const int64_t *C,
+                                          const int64_t *TB, bool comm, bool bwd, int group, int groups, int nt) {
+  constexpr VT INF = Lim<VT>::inf;
+  const int N = pr.N, D = pr.D, VD = pr.DP, tid = threadIdx.x, d = (tid & (VD - 1)) + 1;
+  const double inv = 1.0 / (double)d;
+  auto share = [&](int64_t x) -> VT {
+    if constexpr (sizeof(VT) == 4) return ceil_div<VT>((VT)x, d, inv);
+    else return (VT)(((uint64_t)x + (uint64_t)(d - 1)) / (uint64_t)d);
+  };
+  auto *const V = gptr((VT *)pr.V), *const VF = gptr((VT *)pr.VF), *const VB = gptr((VT *)pr.VB);
+  const int per = nt / VD;  // rows of a turn
+  for (int j = group * per + tid / VD; j <= N; j += groups * per) {
+    const int64_t e = (int64_t)j * VD + d - 1;
+    const bool fit = j > 0 && d <= D && fits_at((uint64_t)P[j], (uint64_t)A[j], (uint64_t)pr.M, d);
+    const VT none = d <= D ? INF : (VT)0;  // (padding columns hold 0, so that padded rows stay sorted)
+    VT f = 0, b = 0;
+    if (fit) {
+      f = share(T[j]);
+      if (comm) f += share(C[j]);
+      if (bwd) b = share(TB[j]);
+    }
+    V[e] = fit ? f + b : none;
+    if (bwd) {
+      VF[e] = fit ? f : none;
+      VB[e] = fit ? b : none;
+    }
+  }
+}
+
+// The same for the searches of more than kSetupLdsN blocks whose level kernel recomputes the stage times: the
+// fits-in-memory part, level 1 and the entries of the pass list.  `parts` waves to a row, which take the row's units that
+// hold a stage that fits in turn; the others, most of a long chain, hold only "fits nowhere" and are written
+// 16 bytes to a lane.  The workgroups behind `groups` write level 1.  A wave to eight rows of one chunk was bound by
+// the rate at which waves start: 64 searches of 1100 blocks 151 us, now 83; 16 of 2000 154, now 42; one of 4096 at 8
+// devices 41, now 17.
+constexpr int kPassBuildThreads = 64 * kBuildWaves;
+template <typename VT>
+__global__ __launch_bounds__(kPassBuildThreads) void build_passes_kernel(const ProblemDev *__restrict__ probs, const int groups,
+                                                                         const int parts) {
+  const ProblemDev &pr = probs[blockIdx.y];
+  const int N = pr.N, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if ((int)blockIdx.x >= groups) {
+    level_one<VT>(pr, pr.T, pr.P, pr.A, nullptr, nullptr, false, false, (int)blockIdx.x - groups, (int)gridDim.x - groups, kPassBuildThreads);
+    return;
+  }
+  const int id = (int)blockIdx.x * kBuildWaves + wave, i = id / parts, part = id - i * parts;
+  if (i >= N) return;
+  const bool listed = pr.S_eff > 1;
+  const uint32_t *const esum = pr.ends + N;
+  const int own = i >> 6;
+  const int behind = row_units_behind(i, (int)pr.ends[i], N);
+  for (int c = own + part; c < behind; c += parts) {
+    UnitStages<VT> st;
+    (void)build_unit<VT, 8, true>(pr, pr.T, pr.P, pr.A, nullptr, i, c, lane, nullptr, 0, 0, nullptr, false, &st);
+    if (!listed) continue;
+    const int w = pr.wlo[c];
+    const uint32_t *const r = pass_chunks(pr) + 4 * c;
+    const PassChunk rec = {r[0], r[1], r[2], r[3]};
+    pass_entries<VT>(pr, i, c, lane, st.fits, st.rmin, st.tij, w, rec, esum);
+  }
+  units_that_fit_nowhere<false>(pr, i, behind, part, parts);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -292,12 +386,11 @@ void build_kernel(const ProblemDev *__restrict__ probs, const int parts, const i
 // size for all of them: merge_grid_items.)
 // paired (the level kernel that recomputes the stage times): the list is of passes instead of rows
 // (pass_entries), an item of at most that many passes of one chunk; workgroup 0 finds ends[], its
-// running sums and every chunk's share of the list, the table builder writes the entries.
+// running sums and every chunk's share of the list (setup_passes), build_passes_kernel writes the entries.
 //
-// Bound by latency (a chain of a few memory round trips and barriers): 7.4 us at 96 blocks, 8.3 us at
-// 251 with send times, 12 us at 1024.  With saturating sums, binary searches by a thread per chunk and the
-// send times four to a thread it took 10.7, 15.6 and 15 us; as four launches 15 us at 96 blocks and 24 us
-// at 1024, and every launch costs the host 3 us more.
+// Searches of up to kSetupLdsN blocks come here only where hundreds of them build tables at 64 devices
+// (prepare_kernel takes the others).  Bound by latency, a chain of memory round trips and barriers: with send times 22
+// us at 2048 blocks and 39 at 4096, a list of passes 19 and 35.
 // ---------------------------------------------------------------------------------------
 constexpr int kSetupThreads = 256;
 
@@ -330,13 +423,6 @@ __device__ __forceinline__ ProblemDev fetch_problem(const ProblemDev *src, Probl
   return x.p;
 }
 constexpr int kSetupLdsN = 1024;  // up to this many blocks the windows are searched in LDS
-
-// whether bytes P (not divided) + ceil(A / D) fit M
-__device__ __forceinline__ bool fits_at(uint64_t P, uint64_t A, uint64_t M, int D) {
-  if (P > M) return false;
-  const uint64_t slack = M - P;
-  return A <= slack * (uint64_t)D || __umul64hi(slack, (uint64_t)D) != 0;  // ceil(A/D) <= slack  <=>  A <= slack D
-}
 
 // Inclusive sums over the workgroup of NW values per thread.  Values stay below 2^62; the upper halves
 // of all partial sums are collected in `high`: the total reaches 2^62 iff one of them has bit 30 or 31 set
@@ -388,126 +474,159 @@ __device__ void setup_fill(const ProblemDev &pr, int levels_done, int64_t t0, in
   }
 }
 
-// The item size, in fours, for items whose number at size 4 (k + 1) is count[k] (see above).
-__device__ __forceinline__ int setup_item_size(const int *count, int most, int max_items, int batch, int slots, bool passes) {
-  int pick = most - 1;
-  for (int k = most - 1; k >= 0; --k)
-    if (count[k] <= max_items) pick = k;
-  if ((long long)count[pick] * batch <= slots) return pick;
-  for (int k = pick + 1; k < most; ++k) {
-    const long long then = (long long)count[k] * batch;
-    if (then <= slots) {
-      if (2 * then >= slots) return k;
-      break;
-    }
+// The last block of the largest stage behind block i for which fits(j) holds (i if there is none; the empty
+// stage fits).
+template <typename F> __device__ __forceinline__ int prepare_end(int i, int N, F fits) {
+  int lo = i, hi = N;
+  while (__any(lo < hi)) {
+    const int mid = (lo + hi + 1) >> 1;  // lo itself once they meet
+    if (fits(mid)) lo = mid;
+    else hi = mid - 1;
   }
-  // one large search of the recomputing form with many rounds: the largest items that still leave one and a
-  // half rounds, by the passes that are really there (the host, which fixes the size for a launch over
-  // many searches, cannot see the pruning of a single one)
-  if (passes && batch == 1)
-    for (int k = most - 1; k > pick; --k)
-      if (2 * count[k] >= 3 * slots) return k;
-  return pick;
+  return lo;
 }
 
-// ends[], its running sums, the windows and every chunk's share of the pass list (see pass_entries), by
-// one workgroup.  E: where this function reads ends (N entries) and the sums (N + 1) back; the workspace
-// gets them as well.  cpass: LDS, 1024 words.  bad: the sums P, A may have wrapped.
-template <typename SP, typename EP>
-__device__ __forceinline__ void setup_passes(const ProblemDev &pr, SP P, SP A, EP E, int *cpass, bool bad, int rows, int max_items,
+// pick_item_size by one wave: lane k < 16 holds the number of items of size 4 (k + 1).
+__device__ __forceinline__ int wave_item_size(int cnt, int most, int max_items, int batch, int slots, bool passes) {
+  const long long then = (long long)cnt * batch;
+  return pick_item_size((uint32_t)__ballot(cnt <= max_items), (uint32_t)__ballot(then <= slots), (uint32_t)__ballot(2 * then >= slots),
+                        (uint32_t)__ballot(2 * cnt >= 3 * slots), most, passes && batch == 1);
+}
+
+// ends[], its running sums, the windows and every chunk's share of the pass list (see pass_entries) of a search of more
+// than kSetupLdsN blocks, by one workgroup.  pool: LDS of kSetupPool words; marks: of 2 nch 16-bit words.  bad: the sums
+// P, A may have wrapped.
+//
+// Bound by latency, a chain of dependent reads per step of the search for the ends: the sums Z (prepare_kernel) of up to
+// kSetupZ blocks are held in LDS; of longer chains every 64th row's end is found first and bounds the others.  A thread
+// searches for eight rows at a time.  (Two rows at a time out of memory, and the windows by binary searches in what had been
+// written, took the launch 26 us at 1100 blocks, 35 at 2048, 66 at 4096; now 17, 19 and 35.)
+constexpr int kSetupZ = 4096;
+constexpr int kSetupPool = 2 * (kSetupLdsN + 1) + 2 * 1024;  // (the sums and the segments of a list of rows, or Z)
+static_assert(kSetupPool > kSetupZ, "Z has an entry more than there are blocks");
+
+__device__ __forceinline__ void setup_passes(const ProblemDev &pr, uint64_t *pool, uint16_t *marks, bool bad, int rows, int max_items,
                                              int batch, int slots, int most) {
-  constexpr int U = 2;  // consecutive rows of a thread
-  __shared__ uint32_t part[kSetupThreads / 64];
+  constexpr int U = 8;  // consecutive rows of a thread
+  __shared__ uint32_t part[kSetupThreads / 64], behind[kSetupThreads / 64];
   __shared__ int count[16];
   const int N = pr.N, D = pr.D, nch = pr.nch, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const uint64_t M = (uint64_t)pr.M;
-  uint32_t *const ends = pr.ends, *const esum = ends + N;
-  uint32_t carry = 0;
-  for (int base = 0; base < N; base += U * kSetupThreads) {
-    const int i0 = base + U * tid;
-    int lo[U], hi[U];  // the last block known to fit (the empty stage does), the last that may
-    uint64_t Pi[U], Ai[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int i = min(i0 + u, N - 1);
-      lo[u] = i; hi[u] = bad || i0 + u >= N ? i : N;
-      Pi[u] = P[i]; Ai[u] = A[i];
-    }
-    bool more = true;
-    while (__any(more)) {
-      more = false;
+  const uint64_t RANNC_GLOBAL *const P = gptr((const uint64_t *)pr.P), *const A = gptr((const uint64_t *)pr.A);
+  uint32_t RANNC_GLOBAL *const ends = gptr(pr.ends), *const esum = ends + N;
+  uint16_t *const window = marks, *const full_of = marks + nch;
+  for (int c = tid; c < nch; c += kSetupThreads) {
+    window[c] = 0xFFFF;  // (no row: N <= 65535)
+    full_of[c] = (uint16_t)min(64 * c + 64, N);
+  }
+  if (tid < 16) count[tid] = 0;
+  uint32_t carry = 0, before_base = 0;
+  // bound(i): a block up to which the stage behind block i is known to fit (or i), and one behind which it does not;
+  // key(i), fits(key, j): whether the stage i+1..j fits
+  auto find_ends = [&](auto bound, auto key, auto fits) {
+    for (int base = 0; base < N; base += U * kSetupThreads) {
+      const int i0 = base + U * tid;
+      int lo[U], hi[U];
+      decltype(key(0)) of[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int mid = (lo[u] + hi[u] + 1) >> 1;  // lo itself once they meet
-        if (fits_at(P[mid] - Pi[u], A[mid] - Ai[u], M, D)) lo[u] = mid;
-        else hi[u] = mid - 1;
-        hi[u] = max(hi[u], lo[u]);
-        more = more || lo[u] < hi[u];
+        const int i = min(i0 + u, N - 1);
+        lo[u] = hi[u] = i;
+        if (!bad && i0 + u < N) bound(i, lo[u], hi[u]);
+        of[u] = key(i);
       }
-    }
-    uint32_t sum = 0;
+      bool more = true;
+      while (__any(more)) {
+        more = false;
 #pragma unroll
-    for (int u = 0; u < U; ++u) sum += i0 + u < N ? (uint32_t)lo[u] : 0u;
-    uint32_t run = sum;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const uint32_t x = __shfl_up(run, o);
-      if (lane >= o) run += x;
-    }
-    if (lane == 63) part[wave] = run;
-    __syncthreads();
-    uint32_t at = carry + run - sum;
-#pragma unroll
-    for (int k = 0; k < kSetupThreads / 64; ++k) {
-      if (k < wave) at += part[k];
-      carry += part[k];
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int i = i0 + u;
-      if (i < N) {
-        ends[i] = (uint32_t)lo[u];
-        esum[i] = at;
-        E[i] = (uint32_t)lo[u];
-        E[N + i] = at;
-        at += (uint32_t)lo[u];
+        for (int u = 0; u < U; ++u) {
+          const int mid = (lo[u] + hi[u] + 1) >> 1;  // lo itself once they meet
+          if (fits(of[u], mid)) lo[u] = mid;
+          else hi[u] = mid - 1;
+          hi[u] = max(hi[u], lo[u]);
+          more = more || lo[u] < hi[u];
+        }
       }
+      uint32_t sum = 0;
+#pragma unroll
+      for (int u = 0; u < U; ++u) sum += i0 + u < N ? (uint32_t)lo[u] : 0u;
+      uint32_t run = sum;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t x = __shfl_up(run, o);
+        if (lane >= o) run += x;
+      }
+      if (lane == 63) { part[wave] = run; behind[wave] = (uint32_t)lo[U - 1]; }
+      __syncthreads();
+      uint32_t before = __shfl_up((uint32_t)lo[U - 1], 1);  // the end of the row in front of this thread's
+      if (lane == 0) before = wave == 0 ? before_base : behind[wave - 1];
+      uint32_t at = carry + run - sum;
+#pragma unroll
+      for (int k = 0; k < kSetupThreads / 64; ++k) {
+        if (k < wave) at += part[k];
+        carry += part[k];
+      }
+      before_base = behind[kSetupThreads / 64 - 1];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int i = i0 + u;
+        if (i < N) {
+          const uint32_t end = (uint32_t)lo[u];
+          ends[i] = end;
+          esum[i] = at;
+          at += end;
+          mark_windows(N, nch, i, before, end, window, full_of);
+          before = end;
+        }
+      }
+      __syncthreads();
+    }
+  };
+  const bool small = P[N] < (1ull << 55) && A[N] < (1ull << 60);
+  const uint64_t DM = __umul64hi(M, (uint64_t)D) ? ~0ull : M * (uint64_t)D;
+  auto Z_of = [&](int j) { return (uint64_t)D * P[j] + A[j]; };  // (below 2^62 where `small`)
+  auto limit = [&](uint64_t z) { return z + DM < z ? ~0ull : z + DM; };
+  if (small && N <= kSetupZ) {
+    for (int i = tid; i <= N; i += kSetupThreads) pool[i] = Z_of(i);
+    __syncthreads();
+    find_ends([&](int, int &, int &hi) { hi = N; }, [&](int i) { return limit(pool[i]); },
+              [&](uint64_t most_z, int j) { return pool[j] <= most_z; });
+  } else {
+    struct Sums { uint64_t P, A; };
+    auto fits = [&](const Sums &s, int j) { return fits_at(P[j] - s.P, A[j] - s.A, M, D); };
+    int *const coarse = (int *)pool;  // the ends of rows 0, 64, ...
+    for (int c0 = 0; c0 < nch; c0 += kSetupThreads) {
+      if (c0 + 64 * wave >= nch) break;
+      const int c = min(c0 + tid, nch - 1);
+      const Sums s = {P[64 * c], A[64 * c]};
+      const int end = bad ? 64 * c : prepare_end(64 * c, N, [&](int j) { return fits(s, j); });
+      if (c0 + tid < nch) coarse[c] = end;
     }
     __syncthreads();
+    auto bound = [&](int i, int &lo, int &hi) {  // (ends never decrease)
+      const int c = i >> 6;
+      lo = max(i, coarse[c]);
+      hi = c + 1 < nch ? coarse[c + 1] : N;
+    };
+    if (small)
+      find_ends(bound, [&](int i) { return limit(Z_of(i)); }, [&](uint64_t most_z, int j) { return Z_of(j) <= most_z; });
+    else
+      find_ends(bound, [&](int i) { return Sums{P[i], A[i]}; }, fits);
   }
-  if (tid == 0) { esum[N] = carry; E[2 * N] = carry; }
-  if (tid < 16) count[tid] = 0;
-  __syncthreads();
+  if (tid == 0) esum[N] = carry;
+  __syncthreads();  // (the ends in memory are visible to the whole workgroup; pool is free)
+  int *const cpass = (int *)pool;
   for (int c = tid; c < nch; c += kSetupThreads) {
-    const int b = 64 * c, last = min(b + 63, N - 1);
-    const uint32_t X = (uint32_t)min(b + 64, N);
-    int w = kNoRow, full = 0;
-    uint32_t all = 0;
-    if (E[b] > (uint32_t)b) {  // the first row whose stages reach into the chunk
-      int lo = 0, hi = b;
-      while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (E[mid] > (uint32_t)b) hi = mid;
-        else lo = mid + 1;
-      }
-      w = lo;
-    } else {  // the chunk's first block fits no device by itself: the first later one that does
-      for (int i = b + 1; i <= last; ++i)
-        if (E[i] > (uint32_t)i) { w = i; break; }
-    }
+    const int last = min(64 * c + 63, N - 1);
+    const int w = window_start(ends, N, c, window[c] == 0xFFFF ? kNoRow : (int)window[c], kNoRow);
+    uint32_t all = 0, full = 0;
     if (w != kNoRow) {
-      int lo = w, hi = last + 1;
-      while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (E[mid] >= X) hi = mid;
-        else lo = mid + 1;
-      }
-      full = lo;
-      all = stages_before(E + N, N, c, (uint32_t)w, (uint32_t)full, (uint32_t)last + 1u);
+      full = (uint32_t)max((int)full_of[c], w);
+      all = stages_before(esum, N, c, (uint32_t)w, full, (uint32_t)last + 1u);
     }
     pr.wlo[c] = w;
-    pass_chunks(pr)[4 * c] = (uint32_t)full;
-    cpass[c] = (int)((all + 63u) >> 6);  // nch <= 1024 (N <= 65535)
+    pass_chunks(pr)[4 * c] = full;
+    cpass[c] = (int)((all + 63u) >> 6);
   }
   __syncthreads();
   if (rows <= 0) {
@@ -517,7 +636,7 @@ __device__ __forceinline__ void setup_passes(const ProblemDev &pr, SP P, SP A, E
     for (int c = tid / 16; c < nch; c += kSetupThreads / 16) cnt += (cpass[c] + r - 1) / r;
     if (cnt) atomicAdd(&count[k], cnt);
     __syncthreads();
-    rows = 4 * (setup_item_size(count, most, max_items, batch, slots, true) + 1);
+    rows = 4 * (wave_item_size(count[k], most, max_items, batch, slots, true) + 1);
   }
   // passes and items in front of every chunk; the passes of a chunk dealt evenly over its items
   if (wave == 0) {
@@ -558,7 +677,8 @@ __global__ __launch_bounds__(kSetupThreads) void setup_kernel(const ProblemDev *
   // waves per SIMD: over 1024 searches of 128 blocks that takes 40 us instead of 71 with four entries.
   constexpr int U = 2;
   __shared__ uint64_t part[kSetupThreads / 64][4], last[4];
-  __shared__ uint64_t sP[kSetupLdsN + 1], sA[kSetupLdsN + 1];  // (reused for the work list)
+  __shared__ __align__(16) uint64_t pool[kSetupPool];
+  uint64_t *const sP = pool, *const sA = pool + kSetupLdsN + 1;
   __shared__ int flags;
   __shared__ unsigned long long max_cut;
   if (tid == 0) { flags = 0; max_cut = 0ull; sP[0] = 0; sA[0] = 0; }
@@ -652,15 +772,13 @@ __global__ __launch_bounds__(kSetupThreads) void setup_kernel(const ProblemDev *
 
   // ---- windows ----
   __shared__ int start[1025];  // nch <= 1024 (N <= 65535)
-  __shared__ RunSegments seg[1024];  // every chunk's window
   if (paired) {
-    const bool bad = flags != 0;  // (sums that may have wrapped: no stage fits)
-    static_assert(sizeof(seg) >= 4 * (2 * kSetupLdsN + 1), "ends and their sums");
-    if (in_lds) setup_passes(pr, (const uint64_t *)sP, (const uint64_t *)sA, (uint32_t *)seg, start, bad, rows, max_items, batch, slots, max_rows / 4);
-    else setup_passes(pr, (const uint64_t RANNC_GLOBAL *)out[1], (const uint64_t RANNC_GLOBAL *)out[2], pr.ends, start, bad, rows,
-                      max_items, batch, slots, max_rows / 4);
+    // (sums that may have wrapped: no stage fits)
+    setup_passes(pr, pool, (uint16_t *)start, flags != 0, rows, max_items, batch, slots, max_rows / 4);
     return;
   }
+  RunSegments *const seg = (RunSegments *)(pool + 2 * (kSetupLdsN + 1));  // every chunk's window
+  static_assert(1024 * sizeof(RunSegments) <= 2 * 1024 * sizeof(uint64_t) && 2 * (kSetupLdsN + 1) % 2 == 0, "aligned, and room for them");
   constexpr int NC = 16;  // candidate item sizes 4, 8, ..., 64 rows, up to max_rows
   const int most = max_rows / 4;
   __shared__ int count[NC];
@@ -718,7 +836,7 @@ __global__ __launch_bounds__(kSetupThreads) void setup_kernel(const ProblemDev *
       if (cnt) atomicAdd(&count[k], cnt);
     }
     __syncthreads();
-    rows = 4 * (setup_item_size(count, most, max_items, batch, slots, false) + 1);
+    rows = 4 * (wave_item_size(count[tid % NC], most, max_items, batch, slots, false) + 1);
   }
   // per chunk: its items, the rows dealt evenly over them (33 rows in items of up to 16: three items of 11,
   // not 16 + 16 + 1)
@@ -793,32 +911,6 @@ __device__ __forceinline__ void prepare_sums(const int64_t RANNC_GLOBAL *in, int
   if (lane == 0) s[0] = 0;
 }
 
-// The last block of the largest stage behind block i for which fits(j) holds (i if there is none; the empty
-// stage fits).
-template <typename F> __device__ __forceinline__ int prepare_end(int i, int N, F fits) {
-  int lo = i, hi = N;
-  while (__any(lo < hi)) {
-    const int mid = (lo + hi + 1) >> 1;  // lo itself once they meet
-    if (fits(mid)) lo = mid;
-    else hi = mid - 1;
-  }
-  return lo;
-}
-
-// setup_item_size by one wave: lane k < 16 holds the number of items of size 4 (k + 1).
-__device__ __forceinline__ int prepare_item_size(int cnt, int most, int max_items, int batch, int slots, bool passes) {
-  const int lane = threadIdx.x & 63;
-  const uint32_t listed = (uint32_t)__ballot(lane < most && cnt <= max_items);
-  const int pick = listed ? __ffs((int)listed) - 1 : most - 1;
-  const long long then = (long long)cnt * batch;
-  if ((long long)__builtin_amdgcn_readlane(cnt, pick) * batch <= slots) return pick;
-  const uint32_t round = (uint32_t)__ballot(lane > pick && lane < most && then <= slots);
-  const uint32_t full = (uint32_t)__ballot(2 * then >= slots);
-  if (round && ((full >> (__ffs((int)round) - 1)) & 1u)) return __ffs((int)round) - 1;
-  const uint32_t many = (uint32_t)__ballot(lane > pick && lane < most && 2 * cnt >= 3 * slots);
-  if (passes && batch == 1 && many) return 31 - __clz((int)many);
-  return pick;
-}
 // ceil(x / r) for x, r < 2^16 (the sum's half keeps the product off the whole numbers by more than its error)
 __device__ __forceinline__ int prepare_ceil(int x, int r, float inv) { return (int)(((float)(x + r - 1) + 0.5f) * inv); }
 
@@ -829,7 +921,6 @@ __device__ __forceinline__ int prepare_ceil(int x, int r, float inv) { return (i
 template <typename VT, int DP, bool TIMES, int NT>
 __global__ __launch_bounds__(NT) void prepare_kernel(const ProblemDev *src, ProblemDev *probs, const PrepareIn in,
                                                                const ProblemDev one, int use_one) {
-  constexpr VT INF = Lim<VT>::inf;
   constexpr int WAVES = NT / 64;
   __shared__ __align__(8) uint32_t desc[sizeof(ProblemDev) / 4];
   __shared__ int s_flags, s_w[kPrepareChunks], s_full[kPrepareChunks];
@@ -928,13 +1019,7 @@ __global__ __launch_bounds__(NT) void prepare_kernel(const ProblemDev *src, Prob
     for (int i = Q * tid; i < min(Q * tid + Q, N); ++i) {
       const uint32_t end = sE[i], before = i ? sE[i - 1] : 0u;
       sum += end;
-      // the chunks whose begin, and whose end, this row is the first to pass
-      for (int c = i ? (int)(before + 63u) >> 6 : 0; c < nch && 64u * (uint32_t)c < end; ++c) s_w[c] = i;
-      for (int c = i ? (int)(before >> 6) : 0; c < nch; ++c) {
-        const uint32_t X = (uint32_t)min(64 * c + 64, N);
-        if (X > end) break;
-        if (i == 0 || X > before) s_full[c] = min(s_full[c], i);
-      }
+      mark_windows(N, nch, i, before, end, s_w, s_full);
     }
     uint32_t run = sum;
 #pragma unroll
@@ -953,12 +1038,7 @@ __global__ __launch_bounds__(NT) void prepare_kernel(const ProblemDev *src, Prob
     }
     if (tid < nch) {
       const int c = tid;
-      int w = s_w[c];
-      if (w > 64 * c) {  // the chunk's first block fits no device by itself: the first later one that does
-        w = kNoRow;
-        for (int i = 64 * c + 1; i <= min(64 * c + 63, N - 1); ++i)
-          if (sE[i] > (uint32_t)i) { w = i; break; }
-      }
+      const int w = window_start(sE, N, c, s_w[c], kNoRow);
       s_w[c] = w;
       if (w != kNoRow) s_full[c] = max(s_full[c], w);
       if (writes) pr.wlo[c] = w;
@@ -976,7 +1056,7 @@ __global__ __launch_bounds__(NT) void prepare_kernel(const ProblemDev *src, Prob
         const float inv = 1.0f / (float)r;
         int cnt = 0;
         for (int c = 0; c < nch; ++c) cnt += prepare_ceil((int)lane_bcast(np, c), r, inv);
-        rows = 4 * (prepare_item_size(cnt, in.max_rows / 4, in.max_items, in.batch, in.slots, true) + 1);
+        rows = 4 * (wave_item_size(cnt, in.max_rows / 4, in.max_items, in.batch, in.slots, true) + 1);
       }
       const uint32_t ni = (np + (uint32_t)rows - 1u) / (uint32_t)rows;
       uint32_t p = np, t = ni;
@@ -996,52 +1076,17 @@ __global__ __launch_bounds__(NT) void prepare_kernel(const ProblemDev *src, Prob
   const bool passes = in.paired && pr.S_eff > 1;
   for (int id = (int)blockIdx.x * WAVES + wave; id < N * in.parts; id += in.groups * WAVES) {  // wave-uniform
     const int i = id / in.parts, part = id - i * in.parts;
-    const int own = i >> 6, last = min(i | 63, N - 1);
-    // the first chunk without such a stage (row 0 has its units written in any case, and a chunk's last row closes
-    // the chunk's passes)
-    const int behind = max((int)(sE[i] + 63u) >> 6, own + (i == 0 || i == last ? 1 : 0));
+    const int own = i >> 6;
+    const int behind = row_units_behind(i, (int)sE[i], N);
     for (int c = own + part; c < behind; c += in.parts) {
       UnitStages<VT> st;
       (void)build_unit<VT, DP, true>(pr, sT, sP, sA, comm ? sC : nullptr, i, c, lane, nullptr, 0, 0, bwd ? sTB : nullptr, TIMES,
                                      &st);
       if (passes) pass_entries<VT>(pr, i, c, lane, st.fits, st.rmin, st.tij, s_w[c], s_rec[c], esum);
     }
-    if (part != 0) continue;
-    const int from = max(behind, own), rest = nch - from;
-    if (rest <= 0) continue;
-    const int64_t u = unit_index(nch, i, from);
-    typedef uint32_t Quad __attribute__((ext_vector_type(4)));
-    Quad RANNC_GLOBAL *const rm = (Quad RANNC_GLOBAL *)(gptr(pr.rmin) + u * 64);
-    if (lane < 4 * rest) rm[lane] = Quad{~0u, ~0u, ~0u, ~0u};  // (at most sixteen chunks)
-    if (lane < rest) pr.ufit[u + lane] = 0;
+    if (part == 0) units_that_fit_nowhere<true>(pr, i, behind, 0, 1);
   }
-  // ---- level 1: one stage on d devices, an entry per thread and turn (a thread keeps its d) ----
-  {
-    const int VD = pr.DP, d = (tid & (VD - 1)) + 1;
-    const double inv = 1.0 / (double)d;
-    auto share = [&](int64_t x) -> VT {
-      if constexpr (sizeof(VT) == 4) return ceil_div<VT>((VT)x, d, inv);
-      else return (VT)(((uint64_t)x + (uint64_t)(d - 1)) / (uint64_t)d);
-    };
-    auto *const V = gptr((VT *)pr.V), *const VF = gptr((VT *)pr.VF), *const VB = gptr((VT *)pr.VB);
-    const int per = NT / VD;  // rows of a turn
-    for (int j = (int)blockIdx.x * per + tid / VD; j <= N; j += in.groups * per) {
-      const int64_t e = (int64_t)j * VD + d - 1;
-      const bool fit = j > 0 && d <= D && fits_at((uint64_t)sP[j], (uint64_t)sA[j], (uint64_t)pr.M, d);
-      const VT none = d <= D ? INF : (VT)0;  // (padding columns hold 0, so that padded rows stay sorted)
-      VT f = 0, b = 0;
-      if (fit) {
-        f = share(sT[j]);
-        if (comm) f += share(sC[j]);
-        if (bwd) b = share(sTB[j]);
-      }
-      V[e] = fit ? f + b : none;
-      if (bwd) {
-        VF[e] = fit ? f : none;
-        VB[e] = fit ? b : none;
-      }
-    }
-  }
+  level_one<VT>(pr, sT, sP, sA, sC, sTB, comm, bwd, (int)blockIdx.x, in.groups, NT);
   if (in.paired || !writes) return;
 
   // ---- work list of rows (of the first workgroup; nch <= 16) ----
@@ -1054,7 +1099,7 @@ __global__ __launch_bounds__(NT) void prepare_kernel(const ProblemDev *src, Prob
       const float inv = 1.0f / (float)r;
       int cnt = 0;
       for (int c = 0; c < nch; ++c) cnt += prepare_ceil((int)lane_bcast((uint32_t)n0, c), r, inv);
-      rows = 4 * (prepare_item_size(cnt, in.max_rows / 4, in.max_items, in.batch, in.slots, false) + 1);
+      rows = 4 * (wave_item_size(cnt, in.max_rows / 4, in.max_items, in.batch, in.slots, false) + 1);
     }
     int run = (n0 + rows - 1) / rows;
     const int mine = run;
@@ -2726,6 +2771,22 @@ hipError_t launch_build(const ProblemDev *p, const LaunchShape &sh, int bits, in
   GO(32, uint32_t)
   GO(64, uint64_t)
 #undef GO
+  return hipGetLastError();
+}
+
+hipError_t launch_build_passes(const ProblemDev *p, const LaunchShape &sh, int bits, int DP, hipStream_t st) {
+  if (sh.max_N > 65535) return hipErrorInvalidValue;
+  for (int q0 = 0; q0 < sh.nprob; q0 += 65535) {
+    const int nq = min(65535, sh.nprob - q0);
+    // waves to a row: as many as leave some 32 thousand, and a wave at most 64 units
+    const int64_t rows = (int64_t)sh.max_N * nq;
+    const int parts = max((sh.max_nch + 63) / 64, (int)std::min<int64_t>(sh.max_nch / 4, 32768 / rows));
+    const int groups = (int)(((int64_t)sh.max_N * parts + kBuildWaves - 1) / kBuildWaves);
+    const int per = kPassBuildThreads / DP, first = min((sh.max_N + per) / per, max(1, 1024 / nq));  // of level 1
+    const dim3 grid((unsigned)(groups + first), (unsigned)nq);
+    if (bits == 32) hipLaunchKernelGGL((build_passes_kernel<uint32_t>), grid, dim3(kPassBuildThreads), 0, st, p + q0, groups, parts);
+    else hipLaunchKernelGGL((build_passes_kernel<uint64_t>), grid, dim3(kPassBuildThreads), 0, st, p + q0, groups, parts);
+  }
   return hipGetLastError();
 }
 

@@ -55,6 +55,44 @@ __host__ __device__ inline uint32_t stages_before(EP esum, int N, int c, uint32_
   return esum[i < full ? i : full] - esum[w] + (i > full ? (i - full) * X : 0u) - starts;
 }
 
+// A row's part in the windows of the chunks: row i is the first whose stages end behind `first` (the last block that
+// fits behind the row before it; 0 for row 0) and up to `end`, its own.  window[c] becomes the first row that reaches
+// into chunk c, full[c] (before: the row behind the chunk's last) the first whose stages reach the chunk's end.
+template <typename WP, typename FP>
+__host__ __device__ inline void mark_windows(int N, int nch, int i, uint32_t first, uint32_t end, WP window, FP full) {
+  for (int c = i ? (int)(first + 63u) >> 6 : 0; c < nch && 64u * (uint32_t)c < end; ++c) window[c] = i;
+  for (int c = i ? (int)(first >> 6) : 0; c < nch; ++c) {
+    const uint32_t X = (uint32_t)(64 * c + 64 < N ? 64 * c + 64 : N);
+    if (X > end) break;
+    if ((i == 0 || X > first) && i < (int)full[c]) full[c] = i;
+  }
+}
+// The window's first row: the marked one (none: any number above 64 c), or, if the chunk's first block fits no device by
+// itself, the first later row with a stage; `none` if there is none.
+template <typename EP>
+__host__ __device__ inline int window_start(EP ends, int N, int c, int marked, int none) {
+  if (marked <= 64 * c) return marked;
+  const int last = 64 * c + 63 < N - 1 ? 64 * c + 63 : N - 1;
+  for (int i = 64 * c + 1; i <= last; ++i)
+    if (ends[i] > (uint32_t)i) return i;
+  return none;
+}
+
+// The item size, in fours, less one: from the sizes 4 (k + 1), k < most, as bits of what holds for them: their items fit the
+// grid (listed), take at most one round of workgroups over the launch (round), at least half of one (half), at least
+// one and a half (many; only looked at for one large search of the recomputing form, `lone`).
+__host__ __device__ inline int pick_item_size(uint32_t listed, uint32_t round, uint32_t half, uint32_t many, int most, bool lone) {
+  const uint32_t all = (1u << most) - 1u;
+  const int pick = listed & all ? __builtin_ctz(listed & all) : most - 1;
+  if ((round >> pick) & 1u) return pick;
+  const uint32_t above = all & ~((2u << pick) - 1u);
+  if ((round & above) && ((half >> __builtin_ctz(round & above)) & 1u)) return __builtin_ctz(round & above);
+  // the largest items that still leave one and a half rounds, by the passes that are really there (the host, which
+  // fixes the size for a launch over many searches, cannot see the pruning of a single one)
+  if (lone && (many & above)) return 31 - __builtin_clz(many & above);
+  return pick;
+}
+
 // rows of the searches of a launch if nothing is pruned (every chunk c holds rows 0 .. 64c+63)
 inline int64_t merge_launch_rows(const LaunchShape &sh) {
   int64_t all_rows = 0;
