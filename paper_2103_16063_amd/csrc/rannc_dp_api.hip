@@ -509,8 +509,10 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
         sh.max_nch = std::max(sh.max_nch, p.nch);
         sh.max_D = std::max(sh.max_D, p.D);
         sh.max_S_eff = std::max(sh.max_S_eff, p.S_eff);
-        if (rannc::dp_class(D) == p.DP)
+        if (rannc::dp_class(D) == p.DP) {
           for (int c = 0; c < p.nch; ++c) sh.wide_rows += std::min(64 * c + 64, N);
+          sh.wide_chunks += p.nch;
+        }
       }
   }
 
@@ -1345,13 +1347,13 @@ int rannc_dp_read_table(rannc_dp_t *h, int which, int32_t problem, void *d_dst, 
   if (h->no_times[cls] && (which == RANNC_DP_TABLE_COST || which == RANNC_DP_TABLE_COST_BWD || which == RANNC_DP_TABLE_ARG_I || which == RANNC_DP_TABLE_ARG_D)) {
     // the solve recomputed the stage times instead of tabulating them: tabulate this search's now
     LaunchShape one;
-    one.nprob = 1; one.max_N = p.N; one.max_nch = p.nch; one.max_D = p.D; one.max_S_eff = p.S_eff; one.wide_rows = 0;
+    one.nprob = 1; one.max_N = p.N; one.max_nch = p.nch; one.max_D = p.D; one.max_S_eff = p.S_eff; one.wide_rows = 0; one.wide_chunks = 0;
     ok = rannc::launch_build(h->d_probs + pos, one, p.bits, p.DP, 2, st) == hipSuccess;
   }
   ok = ok && rannc::launch_export(h->d_probs + pos, which, p.bits, d_dst, st) == hipSuccess;
   if (which == RANNC_DP_TABLE_ARG_I || which == RANNC_DP_TABLE_ARG_D) {
     LaunchShape sh;
-    sh.nprob = 1; sh.max_N = p.N; sh.max_nch = p.nch; sh.max_D = p.D; sh.max_S_eff = p.S_eff; sh.wide_rows = 0;
+    sh.nprob = 1; sh.max_N = p.N; sh.max_nch = p.nch; sh.max_D = p.D; sh.max_S_eff = p.S_eff; sh.wide_rows = 0; sh.wide_chunks = 0;
     int32_t *ai = which == RANNC_DP_TABLE_ARG_I ? (int32_t *)d_dst : nullptr;
     int32_t *ad = which == RANNC_DP_TABLE_ARG_D ? (int32_t *)d_dst : nullptr;
     for (int s = 2; s <= p.S_eff && ok; ++s)

@@ -137,6 +137,7 @@ struct LaunchShape {
   int max_D;
   int max_S_eff;
   int64_t wide_rows;  // rows (unpruned) of the searches of its widest device-count class
+  int wide_chunks;    // and their column chunks
 };
 
 // Kernel launchers (rannc_dp_kernels.hip, rannc_dp_split.hip, rannc_dp_compact.hip).  All enqueue on `st` and return the launch status.

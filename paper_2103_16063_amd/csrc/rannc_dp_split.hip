@@ -206,9 +206,8 @@ __device__ __forceinline__ void split_winners(const ProblemDev &pr, const int s,
 // unit, 552 / 219.  Totals next to each other instead of eight apart, with a sliding window of times in
 // registers instead of two LDS reads per candidate: 207 us alone, but 588 for the driver, whose waves then
 // wait for the one with the most candidates at every row.)  TWO: not for 64-bit values at 16 and 64 devices, where it
-// takes 82 registers instead of 68, two workgroups to a compute unit instead of three, and 210 instead of 166 (256
-// searches of 128 blocks, 16 devices 2.66 instead of 2.65 ms, in the next level's launch 3.35 instead of 2.93; 1024
-// blocks, 64 devices 11.8 instead of 9.6 ms).
+// takes 82 registers instead of 68, two workgroups to a compute unit instead of three, and 210 instead of 166 (500 blocks
+// at 16 devices 309 instead of 268 us, 1024 at 64 11.8 instead of 9.6 ms).
 template <typename VT, int KP, int K0, int U>
 __device__ __forceinline__ void split_candidates(int dp, int d0, int lane, VT F, VT B, const VT *sf, const VT *sb, VT (&row_v)[KP]) {
   VT af[U], ab[U];
@@ -476,17 +475,22 @@ int split_rows_per_item(const LaunchShape &sh, int DP) {
 
 // Whether every level's winners are unpacked by a launch of their own.  A row of a level is listed once per column
 // chunk, so with the unpacking in the next level's launch every row is unpacked by several workgroups and once more for
-// memory, which costs a launch that fills the device more than the chain of one launch fewer per level saves.  Per
-// call, in the next level's launch / apart, 32-bit values: 64 devices 128 blocks 447 / 505 us, 256 (640 rows) 946 / 932,
-// 1024 5.62 / 4.88 ms, 32 searches of 128 2.75 / 2.22; 32 devices: outer driver at 128 blocks (1 728 rows) 623 / 631 us,
-// 12 searches of 128 (2 304) 463 / 382, 700 blocks (4 200) 688 / 627; 16 devices: 900 blocks (7 620) 394 / 408, 64
-// searches of 128 (12 288) 708 / 631; 8 devices: 900 blocks 196 / 203, 256 searches of 128 (49 152) 678 / 633.  64-bit
-// values, whose workgroups take longer: 32 devices: 256 blocks (640 rows) 258 / 287, 4 searches of 128 (768) 326 / 309;
-// 16 devices: 500 blocks (2 304) 268 / 311, 64 searches of 40 (2 560) 315 / 308; 8 devices: 16 searches of 128 (3 072)
-// 193 / 196, 64 of them (12 288) 325 / 292.
+// memory: work that costs a full device more than one launch fewer per level saves.  The host does not know how many
+// rows the memory leaves of a chunk, about two hundred in a long chain, so the line counts chunks, times the mean
+// square of the share of the devices that a level still deals with.  Per call, in the next level's launch / apart:
+//   32-bit values, 64 devices (line at 2): 128 blocks (1.2) 447 / 505 us, 256 (2.3) 946 / 932, 1024 (9) 5.62 / 4.88 ms;
+//     32 devices (6.2, several searches 10): 512 blocks (4.6) 417 / 425, 700 (6.4) 688 / 627, outer driver at 96 blocks
+//     (5.9) 534 / 563, at 160 (8.9) 759 / 800, at 200 (11.8) 952 / 907, 12 searches of 128 (14) 463 / 382; 16 devices (20): 900 blocks (5) 394 / 408, 4 searches of 500 (19) 229 / 256, 20 of
+//     120 (23) 201 / 191, 8 of 500 (37) 333 / 273, 100 of 40 (58) 235 / 213; 8 devices (48): 4 searches of 500 (10) 176 /
+//     189, 60 of 120 (37) 240 / 245, 200 of 40 (62) 268 / 248.
+//   64-bit values, whose workgroups take longer: 32 devices (3.5): 256 blocks (2.3) 258 / 287, 4 searches of 128 (4.6)
+//     326 / 309; 16 devices (20): 4 searches of 500 (19) 286 / 300, 60 of 64 (35) 285 / 262, 8 of 500 (37) 439 / 407; 8
+//     devices (34): 4 of 500 (10) 203 / 213, 60 of 120 (37) 305 / 281.
 static bool split_apart(const LaunchShape &sh, int bits, int DP) {
-  const int64_t from = DP == 64 ? 512 : DP == 32 ? (bits == 64 ? 768 : 2048) : DP == 16 ? (bits == 64 ? 2560 : 8192) : 10240;
-  return sh.wide_rows >= from;
+  double share = 0.0;  // sum over the levels
+  for (int s = 2; s <= sh.max_S_eff; ++s) share += (double)(sh.max_D - s + 1) * (sh.max_D - s + 1) / (DP * DP);
+  const double line = DP == 64 ? 2.0 : DP == 32 ? (bits == 64 ? 3.5 : sh.nprob == 1 ? 6.2 : 10.0) : DP == 16 ? 20.0 : bits == 64 ? 34.0 : 48.0;
+  return sh.wide_chunks * share >= line * (sh.max_S_eff - 1);
 }
 
 template <typename VT>
