@@ -726,10 +726,13 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
                                                max_rows, &rows_for_list);
     const ProblemDev *host_one = sh.nprob == 1 ? &probs[cls_start[k]] : nullptr;
     const int parts = recompute_cls[k] || split_fast ? 1 : 3;
-    // (Hundreds of searches' tables at 64 devices are bound by their stores, and the builder on its own keeps more
-    // waves on them: 512 searches of 128 blocks 546 against 583 us, 64-bit values 878 against 1024; at 32 devices
-    // 243 against 226 and 458 against 437.)
-    const bool apart = parts == 3 && kClasses[k] == 64 && sh.nprob > 64;
+    // Tables of several searches as two launches, sums and builder, where the one launch pays more for the sums, which each
+    // of its workgroups forms again, or for the waves it keeps on the stores: up to sixteen searches of more than 512
+    // blocks (4 of 1000 with send times, 8 devices, as one launch / two: 124 / 108 us, 32 devices 158 / 144; 7 of 500 104 /
+    // 102, 30 of 1000 231 / 234), hundreds of short ones (100 of 120 at 8 devices 142 / 133, 200 of 80 at 32 325 / 312;
+    // 100 of 250 at 32 609 / 617), and at 64 devices (512 of 128 blocks 583 / 546, 64-bit values 1024 / 878).
+    const bool apart = parts == 3 && ((sh.nprob > 1 && sh.nprob <= 16 && sh.max_N > 512) || (sh.nprob >= 64 && sh.max_N <= 128) ||
+                                      (sh.nprob > 64 && kClasses[k] == 64));
     if (rannc::can_prepare(sh) && !apart) {
       ok = rannc::launch_prepare(src + cls_start[k], cp, sh, h->bits, kClasses[k], parts, rows_for_list, merge_items[k], slots,
                                  recompute_cls[k], max_rows, split, b->cut_bytes != nullptr, host_one, st) == hipSuccess;

@@ -915,9 +915,9 @@ __device__ __forceinline__ void prepare_sums(const int64_t RANNC_GLOBAL *in, int
 __device__ __forceinline__ int prepare_ceil(int x, int r, float inv) { return (int)(((float)(x + r - 1) + 0.5f) * inv); }
 
 // TIMES: the stage-time tables as well (DP then is the class they are unrolled for; otherwise any).
-// NT: threads of a workgroup, 1024 for few searches (a thread per row, a unit or two per wave: 24 -> 19 us at
-// 1024 blocks), 256 for many (five workgroups to a compute unit instead of one: the sweep of 2048 searches of 128
-// blocks 1854 -> 1741 us a call).
+// NT: threads of a workgroup, 1024 for one search (a thread per row, a unit or two per wave: 24 -> 19 us at
+// 1024 blocks), 256 for several (five workgroups to a compute unit instead of one: the sweep of 2048 searches of 128
+// blocks 1854 -> 1741 us a call; 7 of 500 blocks at 8 devices 89 -> 79, with send times 115 -> 103).
 template <typename VT, int DP, bool TIMES, int NT>
 __global__ __launch_bounds__(NT) void prepare_kernel(const ProblemDev *src, ProblemDev *probs, const PrepareIn in,
                                                                const ProblemDev one, int use_one) {
@@ -2792,7 +2792,6 @@ hipError_t launch_build_passes(const ProblemDev *p, const LaunchShape &sh, int b
 
 bool can_prepare(const LaunchShape &sh) { return sh.max_N <= kSetupLdsN; }
 
-constexpr int kPrepareMany = 8;  // searches of a launch
 
 template <typename VT, int DP, bool TIMES>
 static hipError_t prepare_go(const ProblemDev *src, ProblemDev *probs, const LaunchShape &sh, PrepareIn in, size_t lds, int fill,
@@ -2800,7 +2799,7 @@ static hipError_t prepare_go(const ProblemDev *src, ProblemDev *probs, const Lau
   const ProblemDev one = host_one ? *host_one : ProblemDev{};
   for (int q0 = 0; q0 < sh.nprob; q0 += 65535) {
     const dim3 grid(in.groups + fill, min(65535, sh.nprob - q0));
-    if (sh.nprob < kPrepareMany)
+    if (sh.nprob == 1)
       hipLaunchKernelGGL((prepare_kernel<VT, DP, TIMES, 1024>), grid, dim3(1024), lds, st, src + q0, probs + q0, in, one, host_one ? 1 : 0);
     else
       hipLaunchKernelGGL((prepare_kernel<VT, DP, TIMES, 256>), grid, dim3(256), lds, st, src + q0, probs + q0, in, one, host_one ? 1 : 0);
@@ -2817,9 +2816,9 @@ hipError_t launch_prepare(const ProblemDev *src, ProblemDev *probs, const Launch
   in.paired = paired ? 1 : 0; in.max_rows = max_rows;
   // Workgroups that build: four waves to a row of a lone search, whole rows where there are many searches and
   // every further workgroup would only form the sums once more.
-  const bool many = sh.nprob >= kPrepareMany;
+  const bool many = sh.nprob > 1;
   in.parts = many ? 1 : 4;
-  in.groups = many ? max(1, min((sh.max_N + 3) / 4, 1280 / sh.nprob)) : max(1, min((sh.max_N * in.parts + 15) / 16, 512 / sh.nprob));
+  in.groups = many ? max(1, min((sh.max_N + 3) / 4, 1280 / sh.nprob)) : max(1, (sh.max_N * in.parts + 15) / 16);
   const int fill = many ? (sh.nprob >= 256 ? 4 : 16) : 32;  // workgroups that fill a search's V
   static_assert((kSetupLdsN + 1) * 8 * 6 + (2 * kSetupLdsN + 1) * 4 <= 60 * 1024, "dynamic LDS that need not be asked for");
   const size_t lds = (size_t)(sh.max_N + 1) * 8 * (4 + (split ? 1 : 0) + (comm ? 1 : 0)) + (size_t)(2 * sh.max_N + 1) * 4;

@@ -74,6 +74,22 @@ def test_lists_of_long_chains(N, huge):
             assert np.array_equal(sess.table(B.TABLE_FIT, q), o["fit"]), q
 
 
+@pytest.mark.parametrize("Q,N", [(2, 512), (2, 513), (16, 513), (17, 513), (63, 128), (64, 128), (64, 129)])
+def test_tables_of_several_searches(Q, N):
+    """Sums and tables as one launch or two: either side of the lines, with send times."""
+    distinct = [synth.with_cut_bytes(synth.random_small(7 * N + k, N - k, (6, 8, 7)[k], 3, tight=(1.5, 3.0, 40.0)[k], tmax=99), k, 1000)
+                for k in range(3)]
+    probs = [distinct[q % 3] for q in range(Q)]
+    res, sess = gpu_run(probs, one_launch_small=1)
+    with sess:
+        rc, info = B.rannc_dp_solve_info(sess.h)
+        assert rc == B.OK and info.level_kernel[0] == B.KERNEL_MERGE_TABLE
+        want = [oracle.solve(pr) for pr in distinct]
+        assert_results_match(probs, res, oracle_results=[want[q % 3] for q in range(Q)])
+        for q in (1, Q - 1):
+            assert_tables_match(probs[q], sess, q, args=False)
+
+
 @pytest.mark.parametrize("width", [NARROW, WIDE])
 @pytest.mark.parametrize("N,D,S", [(64, 8, 8), (100, 64, 64), (130, 32, 32), (700, 16, 16)])
 def test_passes_of_many_rows(N, D, S, width):
