@@ -478,7 +478,8 @@ int split_rows_per_item(const LaunchShape &sh, int DP) {
 // memory: work that costs a full device more than one launch fewer per level saves.  The host does not know how many
 // rows the memory leaves of a chunk, about two hundred in a long chain, so the line counts chunks, times the mean
 // square of the share of the devices that a level still deals with.  Per call, in the next level's launch / apart:
-//   32-bit values, 64 devices (line at 2): 128 blocks (1.2) 447 / 505 us, 256 (2.3) 946 / 932, 1024 (9) 5.62 / 4.88 ms;
+//   32-bit values, 64 devices (line at 4): 128 blocks (1.2) 447 / 505 us, 256 (2.3) 946 / 932, 4 searches of 40 (3.5)
+//     152 / 159, of 128 (6.2) 531 / 486, 1024 blocks (9) 5.62 / 4.88 ms;
 //     32 devices (6.2, several searches 10): 512 blocks (4.6) 417 / 425, 700 (6.4) 688 / 627, outer driver at 96 blocks
 //     (5.9) 534 / 563, at 160 (8.9) 759 / 800, at 200 (11.8) 952 / 907, 12 searches of 128 (14) 463 / 382; 16 devices (20): 900 blocks (5) 394 / 408, 4 searches of 500 (19) 229 / 256, 20 of
 //     120 (23) 201 / 191, 8 of 500 (37) 333 / 273, 100 of 40 (58) 235 / 213; 8 devices (48): 4 searches of 500 (10) 176 /
@@ -489,7 +490,7 @@ int split_rows_per_item(const LaunchShape &sh, int DP) {
 static bool split_apart(const LaunchShape &sh, int bits, int DP) {
   double share = 0.0;  // sum over the levels
   for (int s = 2; s <= sh.max_S_eff; ++s) share += (double)(sh.max_D - s + 1) * (sh.max_D - s + 1) / (DP * DP);
-  const double line = DP == 64 ? 2.0 : DP == 32 ? (bits == 64 ? 3.5 : sh.nprob == 1 ? 6.2 : 10.0) : DP == 16 ? 20.0 : bits == 64 ? 34.0 : 48.0;
+  const double line = DP == 64 ? 4.0 : DP == 32 ? (bits == 64 ? 3.5 : sh.nprob == 1 ? 6.2 : 10.0) : DP == 16 ? 20.0 : bits == 64 ? 34.0 : 48.0;
   return sh.wide_chunks * share >= line * (sh.max_S_eff - 1);
 }
 

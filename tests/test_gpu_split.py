@@ -206,13 +206,13 @@ def test_split_64bit_packed_at_size():
 # A launch with enough column chunks in its widest class (one to a chain here), weighted by the devices that its levels
 # still deal with, finishes every level's winners in a launch of its own: either side of each line, chains of
 # different stage counts together.
-@pytest.mark.parametrize("width,D,below", [(WIDTHS[0], 57, 2), (1 << 41, 64, 2), (WIDTHS[0], 32, 12), (1 << 41, 29, 5),
+@pytest.mark.parametrize("width,D,below", [(WIDTHS[0], 57, 5), (1 << 41, 64, 4), (WIDTHS[0], 32, 12), (1 << 41, 29, 5),
                                            (WIDTHS[0], 13, 54), (1 << 41, 16, 32), (WIDTHS[0], 8, 132), (1 << 41, 7, 143)])
 @pytest.mark.parametrize("apart", [0, 1])
 def test_winners_in_the_next_level_or_apart(width, D, below, apart):
     Q, S = below + apart, [7, 2, 5, 3, 4]
     share = sum((D - s + 1) ** 2 for s in range(2, 8)) / (8 if D <= 8 else 16 if D <= 16 else 32 if D <= 32 else 64) ** 2 / 6
-    line = {57: 2, 64: 2, 32: 10, 29: 3.5, 13: 20, 16: 20, 8: 48, 7: 34}[D]
+    line = {57: 4, 64: 4, 32: 10, 29: 3.5, 13: 20, 16: 20, 8: 48, 7: 34}[D]
     assert (Q * share >= line) == bool(apart)
     distinct = [_case(5100 + k, 60 + k, D, S[k], (1.5, 3.0)[k % 2], 5000, comm=D % 2 == 0) for k in range(5)]
     if width > B.NARROW_MAX_TOTAL_TIME:
