@@ -756,7 +756,7 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
       ok = ok && rannc::launch_solve_small(src + cls_start[k], dp + cls_start[k], shape[k].nprob, h->bits, kClasses[k], fused_direct[k], d_opt,
                                            d_n_stages, d_est_iter_ns, d_status,
                                            shape[k].nprob == 1 ? &probs[cls_start[k]] : nullptr, plan_stride,
-                                           recover ? results : nullptr, cs[k]) == hipSuccess;
+                                           recover ? results : nullptr, h->n_cus, cs[k]) == hipSuccess;
       ok = ok && staging_read();
       h->level_launches++;
     } else {

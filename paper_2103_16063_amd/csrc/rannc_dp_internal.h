@@ -179,10 +179,10 @@ bool small_can_recompute(int bits, int DP, int64_t max_total_time);
 // whether the level kernel can recompute the stage times
 bool can_recompute_times(int bits, int64_t max_total_time);
 // src: as in launch_setup.  results: the launch also recovers the plans of its searches and writes them there
-// (and to the host's mirror with h_flag), or null
+// (and to the host's mirror with h_flag), or null.  cus: compute units of the device
 hipError_t launch_solve_small(const ProblemDev *src, ProblemDev *probs, int Q, int bits, int DP, bool direct, int64_t *d_opt,
                               int32_t *d_n_stages, int64_t *d_est, int32_t *d_status, const ProblemDev *host_one,
-                              int plan_stride, const PlanResults *results, hipStream_t st);
+                              int plan_stride, const PlanResults *results, int cus, hipStream_t st);
 hipError_t launch_level_scan(const ProblemDev *probs, const LaunchShape &sh, int bits, int s,
                              int write_v, int32_t *arg_i, int32_t *arg_d, hipStream_t st);
 // Algorithm 1 with forward and backward maxima carried separately (problems with tb != null):

@@ -2312,9 +2312,10 @@ template <typename VT, int DP> constexpr int small_waves() { return sizeof(VT) *
 // sixteen waves on a compute unit, 64 registers.  The recomputing form on 32-bit values at 16 devices is held to them
 // (70 left alone).  The forms at 8 devices, and the table form on 32-bit values at 16, get there without the plan
 // recovery, which takes 10 to 25 registers and is for few searches: they have an instance without it (PLAN = false) and
-// one with.  (Both as one had 52 to 77 registers and one workgroup to a compute unit: 2000 searches of 17 blocks at 8
-// devices 179 us a call instead of 159, 1000 of 100 blocks 242 instead of 204, with send times 520 instead of 392, at 16
-// devices 743 instead of 673.)
+// one with, which launches of up to a search to a compute unit take as well (100 searches of 40 blocks, 16 devices, send
+// times 73 us a call, held to 64 registers 78).  (Both as one had 52 to 77 registers and one workgroup to a compute
+// unit: 2000 searches of 17 blocks at 8 devices 179 us a call instead of 159, 1000 of 100 blocks 242 instead of 204,
+// with send times 520 instead of 392, at 16 devices 743 instead of 673.)
 template <typename VT, int DP, bool DIRECT> constexpr bool small_plan_apart() { return DP == 8 || (DP == 16 && sizeof(VT) == 4 && !DIRECT); }
 template <typename VT, int DP, bool DIRECT, bool PLAN> constexpr int small_waves_per_simd() {
   return !PLAN || (DIRECT && sizeof(VT) == 4 && DP == 16) ? 8 : small_waves<VT, DP>() / 4;
@@ -2891,16 +2892,17 @@ bool small_can_recompute(int bits, int DP, int64_t max_total_time) {
 
 hipError_t launch_solve_small(const ProblemDev *src, ProblemDev *p, int Q, int bits, int DP, bool direct, int64_t *d_opt,
                               int32_t *d_n_stages, int64_t *d_est, int32_t *d_status, const ProblemDev *host_one,
-                              int plan_stride, const PlanResults *results, hipStream_t st) {
+                              int plan_stride, const PlanResults *results, int cus, hipStream_t st) {
   const ProblemDev one = host_one ? *host_one : ProblemDev{};
   const PlanResults plan = results ? *results : PlanResults{};
   if (direct && DP > 32) return hipErrorInvalidValue;
-#define GO(B, T, W, X)                                                                                                  \
-  if (bits == B && DP == W && direct == X) {                                                                            \
-    constexpr bool apart = small_plan_apart<T, W, X>();                                                                 \
-    auto *const kernel = apart && !results ? solve_small_kernel<T, W, X, !apart> : solve_small_kernel<T, W, X, true>;   \
-    hipLaunchKernelGGL(kernel, dim3(Q), dim3(64 * small_waves<T, W>()), 0, st, src, p, d_opt, d_n_stages, d_est,        \
-                       d_status, one, host_one ? 1 : 0, plan_stride, plan);                                             \
+#define GO(B, T, W, X)                                                                                           \
+  if (bits == B && DP == W && direct == X) {                                                                     \
+    constexpr bool apart = small_plan_apart<T, W, X>();                                                          \
+    auto *kernel = solve_small_kernel<T, W, X, true>;                                                            \
+    if (apart && !results && Q > cus) kernel = solve_small_kernel<T, W, X, !apart>;                              \
+    hipLaunchKernelGGL(kernel, dim3(Q), dim3(64 * small_waves<T, W>()), 0, st, src, p, d_opt, d_n_stages, d_est, \
+                       d_status, one, host_one ? 1 : 0, plan_stride, plan);                                      \
   }
   GO(32, uint32_t, 8, false) GO(32, uint32_t, 16, false) GO(32, uint32_t, 32, false) GO(32, uint32_t, 64, false)
   GO(64, uint64_t, 8, false) GO(64, uint64_t, 16, false) GO(64, uint64_t, 32, false) GO(64, uint64_t, 64, false)
