@@ -1450,10 +1450,12 @@ __device__ __forceinline__ bool merge_passes(VT *tile, VT *mine, const VT RANNC_
 // than the size of the items counts on (1024 blocks at 32 devices where memory never binds 300 -> 271 us a call).
 // (64-bit values at 64 devices: loop-invariant addresses and one time, 20 bytes, go to scratch.  With addresses formed
 // for every load and the times asked for behind the merge nothing does, and the call takes 741 us instead of 726.)
+// (Table form on 64-bit values at 8 devices: 76 registers left alone, six workgroups to a compute unit; asked for seven
+// waves it takes 60, and eight run: 600 searches of 200 blocks with send times 946 -> 873 us a call, 100 of 500 434 -> 417.)
 template <typename VT, int HMAX, bool DIRECT> constexpr int merge_waves_per_simd() {
   if (DIRECT && sizeof(VT) == 4) return HMAX == 64 ? 4 : HMAX == 48 ? 5 : 6;
   if (DIRECT) return HMAX >= 48 ? 3 : HMAX == 32 ? 5 : 8;
-  return HMAX == 64 ? 3 : 1;
+  return HMAX == 64 ? 3 : sizeof(VT) == 8 && HMAX == 8 ? 7 : 1;
 }
 
 // The rows i0+wave, i0+wave+4, ... <= i_hi of one work item, folded into acc (running minimum of the

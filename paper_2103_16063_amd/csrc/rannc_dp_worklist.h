@@ -144,7 +144,7 @@ inline int merge_workgroups_per_cu(int bits, int DP, bool recompute) {
     return DP == 64 ? 3 : DP == 32 ? 4 : DP == 16 ? 6 : 8;
   }
   if (recompute) return DP == 64 ? 3 : DP == 32 ? 5 : 8;
-  return DP == 64 ? 2 : DP == 32 ? 3 : DP == 16 ? 4 : 6;
+  return DP == 64 ? 2 : DP == 32 ? 3 : DP == 16 ? 4 : 8;
 }
 
 // One-launch kernel, a workgroup per search and per compute unit: whether its rounds leave little of the device
