@@ -624,7 +624,14 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
           else us += rl <= 8 ? 0.42 + 0.20 * work : rl <= 16 ? 0.84 + 0.37 * work : 0.76 + 0.65 * work;
         }
         est_one[k] = us;
-        tiny = us <= levels_us(sh);
+        // Up to a search to a compute unit the one launch takes as long as one search; the launches per level take longer
+        // with every search of theirs, in proportion to the devices that a level still deals with (66 to 128 blocks, 8
+        // stages, 8 to 127 searches: 0.2 to 0.26 us a search at 8 devices, 0.35 to 0.6 at 32).  8 stages, 64 searches of 80
+        // blocks at 16 devices: one launch 76 us, levels 98; 127 of 100 at 8 devices 79 and 114; 48 of 80 at 32 devices 95
+        // and 106, 64 of 128 143 and 131.  (Beside other classes the launches per level hide behind one another.)
+        const double share = levels * (sh.max_D - 0.5 * sh.max_S_eff) / cls;
+        const double more = sh.nprob == Q && sh.nprob < 128 ? (sh.nprob - 1) * share * (0.035 + 1.4e-5 * sh.max_N * cls) : 0.0;
+        tiny = us <= levels_us(sh) + more;
       } else if (heavy) {
         // 64 devices, or 64-bit values from 32 devices on, stage times from the table: a level costs
         // about 7 us plus 1.7 us per pass of eight rows, more than a launch; only two or three levels
@@ -729,9 +736,10 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
     // Tables of several searches as two launches, sums and builder, where the one launch pays more for the sums, which each
     // of its workgroups forms again, or for the waves it keeps on the stores: up to sixteen searches of more than 512
     // blocks (4 of 1000 with send times, 8 devices, as one launch / two: 124 / 108 us, 32 devices 158 / 144; 7 of 500 104 /
-    // 102, 30 of 1000 231 / 234), hundreds of short ones (100 of 120 at 8 devices 142 / 133, 200 of 80 at 32 325 / 312;
-    // 100 of 250 at 32 609 / 617), and at 64 devices (512 of 128 blocks 583 / 546, 64-bit values 1024 / 878).
-    const bool apart = parts == 3 && ((sh.nprob > 1 && sh.nprob <= 16 && sh.max_N > 512) || (sh.nprob >= 64 && sh.max_N <= 128) ||
+    // 102, 30 of 1000 231 / 234), hundreds of short ones (100 of 120 at 8 devices 142 / 133, of 250 216 / 212, 200 of 80 at
+    // 32 325 / 312; 100 of 250 at 32 609 / 617), and at 64 devices (512 of 128 blocks 583 / 546, 64-bit values 1024 / 878).
+    const bool apart = parts == 3 && ((sh.nprob > 1 && sh.nprob <= 16 && sh.max_N > 512) ||
+                                      (sh.nprob >= 64 && sh.max_N <= (kClasses[k] == 8 ? 256 : 128)) ||
                                       (sh.nprob > 64 && kClasses[k] == 64));
     if (rannc::can_prepare(sh) && !apart) {
       ok = rannc::launch_prepare(src + cls_start[k], cp, sh, h->bits, kClasses[k], parts, rows_for_list, merge_items[k], slots,
