@@ -29,7 +29,7 @@ constexpr int kBuildWaves = 4;
 
 // ceil(x / r) for every r = 1..DP of a 32-bit x, without integer division: for odd r one
 // double-precision add and one fused multiply-add whose low word is the quotient (the derivation
-// stands at DirectConsts below), for even r an add and a shift from ceil(x / (r/2)).
+// stands at CeilDiv), for even r an add and a shift from ceil(x / (r/2)).
 template <int DP>
 __device__ __forceinline__ void ceil_div_all(uint32_t x, uint32_t (&q)[DP + 1]) {
   const double xf = (double)x;
@@ -502,8 +502,8 @@ __device__ __forceinline__ int wave_item_size(int cnt, int most, int max_items, 
 // searches for eight rows at a time.  (Two rows at a time out of memory, and the windows by binary searches in what had been
 // written, took the launch 26 us at 1100 blocks, 35 at 2048, 66 at 4096; now 17, 19 and 35.)
 constexpr int kSetupZ = 4096;
-constexpr int kSetupPool = 2 * (kSetupLdsN + 1) + 2 * 1024;  // (the sums and the segments of a list of rows, or Z)
-static_assert(kSetupPool > kSetupZ, "Z has an entry more than there are blocks");
+constexpr int kSetupPool = kSetupZ + 1;
+static_assert(kSetupPool >= 2 * (kSetupLdsN + 1) + 1024, "room for two sums and the windows of a list of rows");
 
 __device__ __forceinline__ void setup_passes(const ProblemDev &pr, uint64_t *pool, uint16_t *marks, bool bad, int rows, int max_items,
                                              int batch, int slots, int most) {
@@ -777,8 +777,8 @@ __global__ __launch_bounds__(kSetupThreads) void setup_kernel(const ProblemDev *
     setup_passes(pr, pool, (uint16_t *)start, flags != 0, rows, max_items, batch, slots, max_rows / 4);
     return;
   }
-  RunSegments *const seg = (RunSegments *)(pool + 2 * (kSetupLdsN + 1));  // every chunk's window
-  static_assert(1024 * sizeof(RunSegments) <= 2 * 1024 * sizeof(uint64_t) && 2 * (kSetupLdsN + 1) % 2 == 0, "aligned, and room for them");
+  RunRows *const seg = (RunRows *)(pool + 2 * (kSetupLdsN + 1));  // every chunk's window
+  static_assert(sizeof(RunRows) == sizeof(uint64_t), "a chunk to a word");
   constexpr int NC = 16;  // candidate item sizes 4, 8, ..., 64 rows, up to max_rows
   const int most = max_rows / 4;
   __shared__ int count[NC];
@@ -813,7 +813,7 @@ __global__ __launch_bounds__(kSetupThreads) void setup_kernel(const ProblemDev *
       }
       if (c < nch && sub == 0) {
         pr.wlo[c] = lo;
-        seg[c] = run_segments(N, c, lo, false);
+        seg[c] = run_rows(N, c, lo);
       }
     }
   };
@@ -858,10 +858,10 @@ __global__ __launch_bounds__(kSetupThreads) void setup_kernel(const ProblemDev *
       else hi = mid;
     }
     const int c = lo, k = e - start[c];
-    const RunSegments g = seg[c];
-    const int items = start[c + 1] - start[c], per = (g.n0 + items - 1) / items;
-    const int take = max(min(per, g.n0 - k * per), 1);  // (never below one row: the word stays well-formed)
-    runs[1 + e] = ((take - 1) << 26) | (c << 16) | (g.lo0 + k * per);
+    const RunRows g = seg[c];
+    const int items = start[c + 1] - start[c], per = (g.n + items - 1) / items;
+    const int take = max(min(per, g.n - k * per), 1);  // (never below one row: the word stays well-formed)
+    runs[1 + e] = ((take - 1) << 26) | (c << 16) | (g.lo + k * per);
   }
 }
 
@@ -1093,7 +1093,7 @@ __global__ __launch_bounds__(NT) void prepare_kernel(const ProblemDev *src, Prob
   int32_t *const runs = pr.runs;
   __shared__ int start[kPrepareChunks + 1];
   if (wave == 0) {
-    const int n0 = lane < nch ? run_segments(N, lane, s_w[lane], false).n0 : 0;
+    const int n0 = lane < nch ? run_rows(N, lane, s_w[lane]).n : 0;
     if (rows <= 0) {
       const int r = 4 * (lane & 15) + 4;
       const float inv = 1.0f / (float)r;
@@ -1113,11 +1113,11 @@ __global__ __launch_bounds__(NT) void prepare_kernel(const ProblemDev *src, Prob
   }
   __syncthreads();
   for (int c = 0; c < nch; ++c) {
-    const RunSegments g = run_segments(N, c, s_w[c], false);
-    const int items = start[c + 1] - start[c], per = items ? (g.n0 + items - 1) / items : 0;
+    const RunRows g = run_rows(N, c, s_w[c]);
+    const int items = start[c + 1] - start[c], per = items ? (g.n + items - 1) / items : 0;
     for (int k = tid; k < items; k += NT) {
-      const int take = max(min(per, g.n0 - k * per), 1);  // (never below one row: the word stays well-formed)
-      runs[1 + start[c] + k] = ((take - 1) << 26) | (c << 16) | (g.lo0 + k * per);
+      const int take = max(min(per, g.n - k * per), 1);  // (never below one row: the word stays well-formed)
+      runs[1 + start[c] + k] = ((take - 1) << 26) | (c << 16) | (g.lo + k * per);
     }
   }
 }
@@ -1932,8 +1932,7 @@ constexpr int kTracebackSums = 2048;
 template <typename VT, bool STAGED>
 __device__ void traceback_body(const ProblemDev &pr, TracebackLds &sh, int forced, char *lds, const PlanResults &results, bool choose) {
   const int N = pr.N, D = pr.D, DP = pr.DP, nch = pr.nch;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nt = blockDim.x;
+  const int tid = threadIdx.x, nt = blockDim.x;
   const int64_t lvl = (int64_t)(N + 1) * DP;
   const VT RANNC_GLOBAL *Vg = gptr((const VT *)pr.V);
   using VP = std::conditional_t<STAGED, const VT *, const VT RANNC_GLOBAL *>;

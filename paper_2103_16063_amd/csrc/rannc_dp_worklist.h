@@ -9,35 +9,21 @@
 
 namespace rannc {
 
-// The recomputing form works on passes of 64 stages that fit.  The host does not know which ones fit and sizes
-// its grid as if all did: a row in front of a chunk's diagonal block is one pass, and in the block two rows (p
-// and 64 - p) fill one together.  An item of that bound holds at most this many rows, a pair counting as two.
-__host__ __device__ constexpr int merge_item_rows(int bits) { return merge_max_rows(bits) + 2; }
-__host__ __device__ constexpr int merge_max_pairs(int max_rows) { return max_rows / 2 + 1; }
-
-// The rows of one chunk's window as the work list cuts them (see setup_kernel): n0 rows from lo0 on; paired, for
-// the bound above: n1 entries from lo1 on that stand for the rows of the diagonal block.
-struct RunSegments { int lo0, n0, lo1, n1; };
-__host__ __device__ inline RunSegments run_segments(int N, int c, int lo, bool paired) {
-  RunSegments g;
+// The rows of one chunk's window that the work list of rows cuts (setup_kernel): n rows from lo on.
+struct RunRows { int lo, n; };
+__host__ __device__ inline RunRows run_rows(int N, int c, int lo) {
   const int last = 64 * c + 63, hi = last < N - 1 ? last : N - 1;
-  g.lo0 = lo; g.n0 = lo <= hi ? hi - lo + 1 : 0; g.lo1 = 0; g.n1 = 0;
-  if (paired && lo <= hi && hi >= 64 * c) {
-    const int w = lo > 64 * c ? lo - 64 * c : 0, hmax = hi - 64 * c;  // window start and last row inside the block
-    g.n0 = lo < 64 * c ? 64 * c - lo : 0;
-    // pairs p_lo .. p_top: every pair that holds a row of the window (a few more when the window
-    // starts inside the block; their rows have no stage that fits and cost a skipped pass)
-    const int p_lo = w == 0 ? 0 : 1, p_top = w <= 32 ? (hmax < 32 ? hmax : 32) : (64 - w < 31 ? 64 - w : 31);
-    g.lo1 = 64 * c + p_lo;
-    g.n1 = p_top >= p_lo ? p_top - p_lo + 1 : 0;
-  }
-  return g;
+  return {lo, lo <= hi ? hi - lo + 1 : 0};
 }
-// items of the two segments (items of at most `rows` rows, in launches whose items have at most max_rows)
-__host__ __device__ inline int items_of_rows(const RunSegments &g, int rows) { return (g.n0 + rows - 1) / rows; }
-__host__ __device__ inline int items_of_pairs(const RunSegments &g, int rows, int max_rows) {
-  const int most = rows < merge_max_pairs(max_rows) ? rows : merge_max_pairs(max_rows);
-  return (g.n1 + most - 1) / most;
+__host__ __device__ inline int items_of_rows(const RunRows &g, int rows) { return (g.n + rows - 1) / rows; }
+
+// Items of a chunk if every stage of it fits, in items of at most `rows` rows, or passes (the recomputing form's passes
+// of 64 stages that fit; the host does not know which ones do): in front of the chunk's diagonal block a row has at
+// most one pass, and in the block two rows, p and 64 - p, have one together.
+inline int items_at_most(int N, int c, int rows, bool passes) {
+  if (!passes) return items_of_rows(run_rows(N, c, 0), rows);
+  const int columns = std::min(64, N - 64 * c);
+  return (64 * c + rows - 1) / rows + (std::min(columns, 33) + rows - 1) / rows;
 }
 
 // What the recomputing form's list knows of a chunk (rannc_dp_kernels.hip, pass_entries): its first row whose
@@ -107,15 +93,11 @@ inline int64_t merge_launch_rows(const LaunchShape &sh) {
 // smallest item size that fits this grid.
 // rows_for_list: what launch_setup is to be given as rows_per_item (the size the host fixed, or -1)
 inline int merge_grid_items(const LaunchShape &sh, int rows_per_item, int slots, bool paired, int max_rows, int *rows_for_list) {
-  // items of the largest search of the launch if nothing is pruned, in items of `rows` rows: the
-  // segments of run_segments for windows that start at row 0 (a pruned window has no more rows in
-  // either segment, so no more items at any size)
+  // items of the largest search of the launch if nothing is pruned (a pruned window has no more rows or passes, so no more
+  // items at any size)
   auto items_at = [&](int rows) {
     int64_t items = 0;
-    for (int c = 0; c < sh.max_nch; ++c) {
-      const RunSegments g = run_segments(sh.max_N, c, 0, paired);
-      items += items_of_rows(g, rows) + items_of_pairs(g, rows, max_rows);
-    }
+    for (int c = 0; c < sh.max_nch; ++c) items += items_at_most(sh.max_N, c, rows, paired);
     return std::max<int64_t>(1, items);
   };
   int rows = std::min(rows_per_item, max_rows);
@@ -125,10 +107,9 @@ inline int merge_grid_items(const LaunchShape &sh, int rows_per_item, int slots,
     rows = launch_rows >= kMergeRows16From ? 16 : launch_rows >= kMergeRows8From ? 8 : kMergeMinRows;
     // A launch of the recomputing form over several searches with many rounds of workgroups: the
     // largest items that still fill the device one and a quarter times if nothing is pruned, the same
-    // size for every search of the launch.  Copying the rows in, clearing the tile and the atomics are
-    // paid per item (config 5: 16 -> 64 rows, 157 -> 115 us per level when an item held its minimum in
-    // registers; six workgroups per compute unit at 32 devices since: one and a quarter rounds 2.13 ms
-    // for all levels, two 2.13, three 2.25; over ragged batches of 100 to 1 500 searches within 5 %).
+    // size for every search of the launch.  Clearing the tile and the atomics are paid per item (2048 searches of
+    // 128 blocks, with earlier forms of the kernel: 16 -> 64 rows 157 -> 115 us per level; one and a quarter rounds
+    // 2.13 ms for all levels, two 2.13, three 2.25; over ragged batches of 100 to 1 500 searches within 5 %).
     if (paired && sh.nprob > 1 && items_at(rows) * sh.nprob > slots)
       for (int r = max_rows; r > rows; r -= 4)
         if (4 * items_at(r) * sh.nprob >= 5ll * slots) { rows = r; *rows_for_list = r; break; }
