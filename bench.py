@@ -25,9 +25,8 @@ import numpy as np  # noqa: E402
 HBM_PEAK_GBS = 8000.0
 # plain vector ALU rate of the chip: 256 compute units x 4 SIMDs x 16 lanes x 2.4 GHz
 ALU_PEAK_TLANEOPS = 256 * 4 * 16 * 2.4e9 / 1e12
-# vector instructions per candidate in the split-objective level kernel's loop body (ISA of
-# level_split_fast_kernel<64>: 57 per 8 candidates: 16 max, 8 add, 16 compares, 16 selects, 1 move)
-SPLIT_VALU_PER_UPDATE = 57 / 8
+# vector instructions per candidate of the split-objective level kernel: two maxima, a sum, a minimum
+SPLIT_VALU_PER_UPDATE = 4
 ESIZE = 4  # bytes per table entry in the 32-bit mode all benchmark configurations run in
 
 # HBM bytes per level-kernel launch as rocprofv3 --pmc measured them (FETCH_SIZE x 2.000 + WRITE_SIZE x
@@ -47,7 +46,8 @@ PMC_TRAFFIC = {
     ("c5", False, False): (811.8e6, "profiles/level_merge_config5_batched_table.md"),
 }
 # useful vector instructions of the sorted-merge level kernel per (i, j) stage: DP maxima that form
-# the bitonic sequence, then log2(DP) compare-exchange stages of DP/2 (max, min) pairs
+# the bitonic sequence, then log2(DP) compare-exchange stages of DP/2 (max, min) pairs.  (A count of the method; the
+# kernels on 32-bit values run a network with columns of three, 246 operations for 384 at DP = 64.)
 def merge_valu_per_stage(DP):
     return DP * (DP.bit_length() - 1 + 1)
 
@@ -232,7 +232,7 @@ def run_workload(name, steps, warmup, wide=False, algo="auto"):
             tot["cands"] += lv["cands"]
             # sorted merge per stage; when the stage times are recomputed, two more instructions for
             # each of the D-s+1 replica counts the level can use
-            tot["valu"] += lv["stages"] * merge_valu_per_stage(DP) + (2 * lv["entries"] if recompute else 0)
+            tot["valu"] += lv["stages"] * merge_valu_per_stage(DP) + (lv["entries"] if recompute else 0)
     sess.close()
     n_tables = 2 if split else 1                  # the split objective reads a backward table too
     n_vals = 3 if split else 1                    # ... and carries two maxima beside each value

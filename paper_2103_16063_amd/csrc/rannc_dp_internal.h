@@ -61,16 +61,18 @@ __host__ __device__ inline int64_t max_run_words(int nch) {
 // kMergeRows16From rows (unpruned), of 8 from kMergeRows8From, of 4 below.
 constexpr int kMergeWaves = 4;
 constexpr int kMergeMinRows = 4;
-// largest work item: rows, or passes of the recomputing form
+// Largest work item of the recomputing form, in passes.  64-bit values, 32 / 64 passes: 600 searches of 200 blocks at 64
+// devices 1802 / 1689 us a call, at 16 devices 552 / 547; 200 of them at 16 devices 267 / 273, at 8 209 / 215; single
+// searches the same.
 __host__ __device__ constexpr int merge_max_rows(int bits) { return bits == 64 ? 32 : 64; }
-// (and, with two rows to an entry of a diagonal block's segment, cuts those shorter: rannc_dp_worklist.h)
 constexpr int kMergeRows8From = 6144;
 constexpr int kMergeRows16From = 16384;
 // From this many rows (unpruned) in a launch on, a search without a communication term has its
 // stage times recomputed in the level kernel (RANNC_DP_ALGO_AUTO), which also saves building their
-// table.  Measured per solve, table against recomputed: 1024 blocks at 64 devices 410 / 397 us where
-// memory binds and 800 / 555 us where it does not, 700 blocks at 48 devices 289 / 268 us, 300 at 64
-// (1 500 rows) 233 / 227, 251 at 24 (640 rows) 146 / 147, 96 at 16 the table form by some microseconds.
+// table.  Measured per call, table against recomputed: 1024 blocks at 64 devices 357 / 305 us where
+// memory binds and 773 / 466 us where it does not, 701 at 48 261 / 211, 400 (1 744 rows) at 64 193 / 154, at 16
+// 120 / 109.  The line was drawn with kernels that were level at 1 000 rows; with these the recomputing form is ahead
+// below it as well: 300 blocks (940 rows) at 64 179 / 144, 251 at 24 124 / 110, 96 at 16 105 / 95.
 constexpr int kRecomputeRowsFrom = 1024;
 
 __host__ __device__ inline int dp_class(int D) { return D <= 8 ? 8 : D <= 16 ? 16 : D <= 32 ? 32 : 64; }
