@@ -35,3 +35,26 @@ def test_one_launch_of_many_searches_in_full_rounds(Q, D, comm, one):
     cls = {32: 2, 64: 3}[D]
     _run(_chains(Q, [66, 65, 70, 68, 66, 67, 72], D, comm), lambda info: info.level_kernel[cls] == kernel,
          max_total_time_ns=WIDE)
+
+
+# Fewer searches than make a batch: one launch where the launches per level would take longer, which they do with every
+# further search (not beside another class).
+@pytest.mark.parametrize("Q,N,D,beside,one", [
+    (34, 128, 8, False, False), (35, 128, 8, False, True), (8, 80, 16, False, False), (16, 80, 16, False, True),
+    (35, 128, 8, True, False),
+])
+def test_one_launch_of_some_tens_of_searches(Q, N, D, beside, one):
+    probs = _chains(Q, [N, N - 1, N - 15, 66, N, 70, N], D, S=8)
+    if beside:
+        probs = probs[:7] * 5 + [synth.random_small(3, 40, 64, 8, tight=2.5)] * 40
+    kernel = B.KERNEL_ONE_LAUNCH_RECOMPUTE if one else B.KERNEL_MERGE_RECOMPUTE
+    cls = {8: 0, 16: 1}[D]
+    if not beside:
+        _run(probs, lambda info: info.level_kernel[cls] == kernel)
+        return
+    with B.Session(synth.concat_batch(probs)) as s:
+        res = s.run()
+        distinct = oracle_solve_many(probs[:7] + probs[-1:])
+        assert_results_match(probs, res, oracle_results=[distinct[q % 7] for q in range(35)] + [distinct[7]] * 40)
+        rc, info = B.rannc_dp_solve_info(s.h)
+        assert rc == B.OK and info.level_kernel[cls] != B.KERNEL_ONE_LAUNCH_RECOMPUTE

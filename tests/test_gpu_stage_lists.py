@@ -46,11 +46,12 @@ def test_setup_and_tables(N, width):
 def test_lists_of_long_chains(N, huge):
     """Searches of more than 1024 blocks: the ends searched in LDS (up to 4096 blocks), out of memory, and with bytes
     whose sums per device would wrap.  Memory for half the chain, for some forty blocks, the same with blocks that fit
-    nowhere (the first one of a chunk, and all of another), memory that never binds, and a flagged search beside
-    them."""
+    nowhere (the first one of a chunk, and all of another), memory that never binds, short chains and a flagged
+    search beside them."""
     def case(k, D, tight, S=3):
         return synth.random_small(17 * N + k, N, D, S, tight=tight, tmax=9)
-    probs = [case(0, 4, 1.5), case(1, 3, 1.0), case(2, 8, 60.0), case(4, 8, 1.0, 8), case(3, 5, 2.0)]
+    short = [synth.random_small(3, n, 6, 3, tight=2.0, tmax=9) for n in (1, 65)]
+    probs = [case(0, 4, 1.5), case(1, 3, 1.0), case(2, 8, 60.0), case(4, 8, 1.0, 8), *short, case(3, 5, 2.0)]
     for few in (probs[1], probs[3]):
         few["mem_capacity"] = int((few["param_bytes"].mean() + few["act_bytes"].mean()) * 40)
     few = probs[1]
@@ -61,17 +62,19 @@ def test_lists_of_long_chains(N, huge):
             up = (1 << 57) // int(pr["param_bytes"].sum() + pr["act_bytes"].sum())
             for key in ("param_bytes", "act_bytes", "mem_capacity"):
                 pr[key] = pr[key] * up
-    probs[4]["act_bytes"][N // 3] = -1
+    probs[6]["act_bytes"][N // 3] = -1
     res, sess = gpu_run(probs)
     with sess:
         rc, info = B.rannc_dp_solve_info(sess.h)
         assert rc == B.OK and info.level_kernel[0] == B.KERNEL_MERGE_RECOMPUTE
-        assert list(res["status"]) == [B.PROBLEM_OK] * 4 + [B.PROBLEM_NEGATIVE_INPUT]
-        assert_results_match(probs[:4], {k: v[:4] for k, v in res.items()})
-        for q in range(4):
+        assert list(res["status"]) == [B.PROBLEM_OK] * 6 + [B.PROBLEM_NEGATIVE_INPUT]
+        assert_results_match(probs[:6], {k: v[:6] for k, v in res.items()})
+        for q in range(6):
             o = oracle.solve(probs[q], keep_tables=True)
             assert np.array_equal(sess.table(B.TABLE_V, q), o["V"]), q
             assert np.array_equal(sess.table(B.TABLE_FIT, q), o["fit"]), q
+        if N < 1200:
+            assert_tables_match(probs[0], sess, 0, args=False)
 
 
 @pytest.mark.parametrize("Q,N", [(2, 512), (2, 513), (16, 513), (17, 513), (63, 128), (64, 128), (64, 256), (64, 257)])
