@@ -734,13 +734,14 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
     const ProblemDev *host_one = sh.nprob == 1 ? &probs[cls_start[k]] : nullptr;
     const int parts = recompute_cls[k] || split_fast ? 1 : 3;
     // Tables of several searches as two launches, sums and builder, where the one launch pays more for the sums, which each
-    // of its workgroups forms again, or for the waves it keeps on the stores: up to sixteen searches of more than 512
-    // blocks (4 of 1000 with send times, 8 devices, as one launch / two: 124 / 108 us, 32 devices 158 / 144; 7 of 500 104 /
-    // 102, 30 of 1000 231 / 234), hundreds of short ones (100 of 120 at 8 devices 142 / 133, of 250 216 / 212, 200 of 80 at
-    // 32 325 / 312; 100 of 250 at 32 609 / 617), and at 64 devices (512 of 128 blocks 583 / 546, 64-bit values 1024 / 878).
+    // of its workgroups forms again, or for the waves it keeps on the stores.  Per call with send times, as one launch /
+    // two: up to sixteen searches of more than 512 blocks (4 of 1000, 8 devices 124 / 108 us, 32 devices 158 / 144; 7 of
+    // 500 104 / 102, 30 of 1000 231 / 234); more than 64 (whose descriptors are copied to the device in front of the
+    // first launch, which takes as long) of up to 256 blocks (64 of 100 at 8 devices 91 / 101, 66 103 / 98, 100 of 130 at
+    // 16 172 / 165, 300 of 160 at 8 311 / 278, at 32 969 / 936, 64-bit values 1773 / 1581; 100 of 500 at 8 375 / 388),
+    // and at 64 devices (512 of 128 blocks 583 / 546, 64-bit values 1024 / 878).
     const bool apart = parts == 3 && ((sh.nprob > 1 && sh.nprob <= 16 && sh.max_N > 512) ||
-                                      (sh.nprob >= 64 && sh.max_N <= (kClasses[k] == 8 ? 256 : 128)) ||
-                                      (sh.nprob > 64 && kClasses[k] == 64));
+                                      (sh.nprob > 64 && (sh.max_N <= 256 || kClasses[k] == 64)));
     if (rannc::can_prepare(sh) && !apart) {
       ok = rannc::launch_prepare(src + cls_start[k], cp, sh, h->bits, kClasses[k], parts, rows_for_list, merge_items[k], slots,
                                  recompute_cls[k], max_rows, split, b->cut_bytes != nullptr, host_one, st) == hipSuccess;

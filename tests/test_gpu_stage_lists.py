@@ -77,7 +77,7 @@ def test_lists_of_long_chains(N, huge):
             assert_tables_match(probs[0], sess, 0, args=False)
 
 
-@pytest.mark.parametrize("Q,N", [(2, 512), (2, 513), (16, 513), (17, 513), (63, 128), (64, 128), (64, 256), (64, 257)])
+@pytest.mark.parametrize("Q,N", [(2, 512), (2, 513), (16, 513), (17, 513), (64, 256), (65, 256), (65, 257)])
 def test_tables_of_several_searches(Q, N):
     """Sums and tables as one launch or two: either side of the lines, with send times."""
     distinct = [synth.with_cut_bytes(synth.random_small(7 * N + k, N - k, (6, 8, 7)[k], 3, tight=(1.5, 3.0, 40.0)[k], tmax=99), k, 1000)
