@@ -152,7 +152,7 @@ typedef struct {
                                     the send time of a cut belongs to the forward pass), NULL otherwise */
 } rannc_dp_batch_t;
 
-/* Bytes of device workspace that any batch within `limits` fits in (worst case).
+/* Bytes of device workspace that any batch within `limits` fits in (worst case), copies of its inputs included.
  * Returns 0 if limits is NULL or invalid. */
 RANNC_DP_API size_t rannc_dp_workspace_bytes(const rannc_dp_limits_t *limits);
 
@@ -202,9 +202,12 @@ RANNC_DP_API int rannc_dp_traceback(rannc_dp_t *h, void *hip_stream, int32_t pla
  * with the meaning they have above.
  *   d_results  DEVICE, h_results HOST (pinned memory is copied to faster in large batches), 8-byte aligned,
  *              results_bytes bytes each
- * Synchronous: everything before it on hip_stream has completed when it returns.  Allocates nothing,
- * except where plan_stride is beyond the handle's longest plan (max_stages, at most 64): then pinned
- * host memory, at the first such call and at any later one that needs more, freed by destroy.
+ * Synchronous: everything before it on hip_stream has completed when it returns.  A batch of min-max searches of up to
+ * 4096 blocks without a communication term, on a handle with algo AUTO and no tuning fields, is normally answered without
+ * the tables of rannc_dp_solve; the first rannc_dp_traceback, _traceback_at, _level_values or _read_table behind it makes
+ * them, from copies of the inputs kept in the workspace, and waits for that.  Allocates nothing but host memory for
+ * copies of the batch's HOST members, except where plan_stride is beyond the handle's longest plan (max_stages, at
+ * most 64): then pinned host memory, at the first such call and at any later one that needs more, freed by destroy.
  * Errors as rannc_dp_solve and rannc_dp_traceback; INVALID_ARG if results_bytes is too small. */
 RANNC_DP_API int rannc_dp_solve_to_host(rannc_dp_t *h, const rannc_dp_batch_t *batch, void *hip_stream,
                                         int32_t plan_stride, void *d_results, void *h_results,
@@ -356,7 +359,8 @@ RANNC_DP_API int rannc_dp_compact_static(void *hip_stream, int32_t n_groups, int
 RANNC_DP_API int rannc_dp_read_table(rannc_dp_t *h, int which, int32_t problem, void *d_dst, size_t bytes,
                         void *hip_stream);
 
-/* Which level kernel the last solve ran for each device-count class (D <= 8, 16, 32, 64) of its batch. */
+/* Which level kernel the last solve ran for each device-count class (D <= 8, 16, 32, 64) of its batch; behind a call that
+ * was answered without tables, the one that makes them when they are asked for. */
 #define RANNC_DP_KERNEL_NONE 0            /* no search of that class in the batch */
 #define RANNC_DP_KERNEL_MERGE_TABLE 1     /* sorted merge, stage times read from their table */
 #define RANNC_DP_KERNEL_MERGE_RECOMPUTE 2 /* sorted merge, stage times recomputed */

@@ -118,6 +118,8 @@ bool packed_of(const rannc_dp_limits_t *l) { return l->max_total_time_ns <= rann
 int bits_of(const rannc_dp_limits_t *l) { return l->max_total_time_ns <= kNarrowMax ? 32 : 64; }
 
 size_t header_bytes(int Q) { return align_up((size_t)Q * sizeof(ProblemDev)); }
+// the copies of the inputs behind the searches' regions (rannc_dp_reach.hip)
+size_t saved_bytes(size_t blocks) { return align_up(3 * 8 * blocks) + kAlign; }
 
 // Host-side validation of the batch descriptors against the limits.
 int check_batch(const rannc_dp_limits_t *l, const rannc_dp_batch_t *b) {
@@ -211,6 +213,14 @@ struct rannc_dp {
   int fused_small;  // one-launch kernel for classes of small searches: 1 = where it pays (default),
                     // 0 = never, 2 = whenever N <= 128 (RANNC_DP_FUSED_SMALL)
   int64_t call_total_bound;  // > 0 during the outer driver's solve: no search's total time exceeds it
+  // The last batch, where it was answered without its tables (solved, but not tabled): what makes them when they are
+  // asked for.  Its inputs are at ws + saved_at, three arrays.
+  bool tabled;
+  struct {
+    std::vector<int32_t> N, D, S, MB;
+    std::vector<int64_t> M, off;
+    size_t saved_at;
+  } kept;
 };
 
 extern "C" {
@@ -237,14 +247,15 @@ size_t rannc_dp_workspace_bytes(const rannc_dp_limits_t *l) {
                      packed_of(l), &sz))
     return 0;
   const unsigned __int128 tot =
-      (unsigned __int128)sz.total() * (unsigned)l->max_problems + header_bytes(l->max_problems);
+      (unsigned __int128)sz.total() * (unsigned)l->max_problems + header_bytes(l->max_problems) +
+      saved_bytes((size_t)l->max_blocks * (size_t)l->max_problems);
   if (tot > ((unsigned __int128)1 << 47)) return 0;
   return (size_t)tot;
 }
 
 size_t rannc_dp_workspace_bytes_for(const rannc_dp_limits_t *l, const rannc_dp_batch_t *b) {
   if (!limits_ok(l) || check_batch(l, b) != RANNC_DP_OK) return 0;
-  size_t tot = header_bytes(l->max_problems);
+  size_t tot = header_bytes(l->max_problems) + saved_bytes((size_t)(b->block_offset[b->n_problems] - b->block_offset[0]));
   const int all = widest_class(b);  // (room for the group, whichever way the batch then runs)
   for (int q = 0; q < b->n_problems; ++q) {
     Sizes sz;
@@ -274,6 +285,7 @@ int rannc_dp_create(const rannc_dp_limits_t *l, void *d_workspace, size_t worksp
   h->next_slot = 0;
   h->solved = false;
   h->unchosen = false;
+  h->tabled = false;
   h->Q = 0;
   h->timing = false;
   h->ev_valid = false;
@@ -400,10 +412,10 @@ int rannc_dp_get_timing(rannc_dp_t *h, float *out_ms, int32_t *out_level_launche
 // behind it can choose the stage counts; *chosen = whether that has been done here already.
 // results != null: a solve that is one launch over few searches recovers their plans there as well;
 // *recovered = whether it has.
+// info_only: nothing is launched, and only what rannc_dp_solve_info reports is found out.
 static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream, int64_t *d_opt, int32_t *d_n_stages,
                       int64_t *d_est_iter_ns, int32_t *d_status, bool *chosen, int32_t plan_stride = 0,
-                      const rannc::PlanResults *results = nullptr, bool *recovered = nullptr) {
-  if (!h || !d_opt || !d_n_stages) return RANNC_DP_INVALID_ARG;
+                      const rannc::PlanResults *results = nullptr, bool *recovered = nullptr, bool info_only = false) {
   int rc = check_batch(&h->lim, b);
   if (rc != RANNC_DP_OK) return rc;
   if (!b->time_ns || !b->param_bytes || !b->act_bytes) return RANNC_DP_INVALID_ARG;
@@ -538,39 +550,6 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
     for (int k = 0; k < 4; ++k)
       if (probs[q].DP == kClasses[k] && !recompute_cls[k]) probs[q].ends = nullptr;
 
-  // ---- descriptors to the device ---------------------------------------------------
-  const int slot = h->next_slot;
-  h->next_slot = (slot + 1) % kStagingSlots;
-  if (h->staging_used[slot] && hipEventSynchronize(h->staging_free[slot]) != hipSuccess)
-    return RANNC_DP_HIP_ERROR;
-  const size_t probs_bytes = (size_t)Q * sizeof(ProblemDev);
-  std::memcpy(h->staging[slot], probs.data(), probs_bytes);
-  h->solved = false;
-  // one group: its first launch reads the descriptors out of the staging memory and stores them
-  const bool in_place = all != 0 && h->staging_dev[slot] != nullptr;
-  h->staging_used[slot] = false;
-  if (!in_place) {
-    if (hipMemcpyAsync(h->ws, h->staging[slot], probs_bytes, hipMemcpyHostToDevice, st) != hipSuccess ||
-        hipEventRecord(h->staging_free[slot], st) != hipSuccess) {
-      (void)hipGetLastError();
-      return RANNC_DP_HIP_ERROR;
-    }
-    h->staging_used[slot] = true;
-  }
-  auto staging_read = [&]() -> bool {  // behind the launch that has read the staging memory
-    if (!in_place || chosen) return true;  // (a caller that waits has the slot back by then)
-    h->staging_used[slot] = hipEventRecord(h->staging_free[slot], st) == hipSuccess;
-    return h->staging_used[slot];
-  };
-
-  // ---- kernels ---------------------------------------------------------------------------
-  ProblemDev *const dp = h->d_probs;
-  const ProblemDev *const src = in_place ? (const ProblemDev *)h->staging_dev[slot] : dp;
-  bool ok = true;
-  const bool timing = h->timing;
-  h->ev_valid = false;
-  h->level_launches = 0;
-  if (timing) ok = ok && hipEventRecord(h->ev[0], st) == hipSuccess;
   bool fused[4] = {false, false, false, false};
   bool fused_direct[4] = {false, false, false, false};  // one-launch kernel that recomputes the stage times
   // estimated time of a class of few small searches (us): as one launch with recomputed stage times
@@ -674,7 +653,7 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
   // few searches that is not the longest and would finish as ONE launch within the longest class's
   // time takes the one-launch kernel even where its own launches per level would be faster.
   bool share_stream = true;  // the one-launch classes besides the first share one stream
-  if (h->fused_small == 1 && h->multi_stream && !timing) {
+  if (h->fused_small == 1 && h->multi_stream && !h->timing) {
     double longest = 0.0;
     int crit = -1;
     for (int k = 0; k < 4; ++k) {
@@ -691,6 +670,64 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
       if (shape[k].nprob && fused[k] && k != crit && est_one[k] >= 0.0) sum += est_one[k];
     share_stream = sum <= longest;
   }
+  auto report = [&]() {
+    int kernel_of[4];
+    for (int k = 0; k < 4; ++k) {
+      kernel_of[k] = fused[k]           ? (fused_direct[k] ? RANNC_DP_KERNEL_ONE_LAUNCH_RECOMPUTE : RANNC_DP_KERNEL_ONE_LAUNCH)
+                     : split_fast       ? RANNC_DP_KERNEL_SPLIT
+                     : split            ? RANNC_DP_KERNEL_SPLIT_SCAN
+                     : scan             ? RANNC_DP_KERNEL_SCAN
+                     : recompute_cls[k] ? RANNC_DP_KERNEL_MERGE_RECOMPUTE
+                                        : RANNC_DP_KERNEL_MERGE_TABLE;
+      h->info.n_problems[k] = 0;
+      h->info.level_kernel[k] = RANNC_DP_KERNEL_NONE;
+    }
+    for (int q = 0; q < Q; ++q) {  // reported by the searches' own classes, also where they ran as one group
+      int own = 0, ran = 0;
+      while (kClasses[own] != rannc::dp_class(b->n_devices[q])) ++own;
+      while (kClasses[ran] != dp_of(q)) ++ran;
+      h->info.n_problems[own]++;
+      h->info.level_kernel[own] = kernel_of[ran];
+    }
+  };
+  if (info_only) {
+    report();
+    return RANNC_DP_OK;
+  }
+
+  // ---- descriptors to the device ---------------------------------------------------
+  const int slot = h->next_slot;
+  h->next_slot = (slot + 1) % kStagingSlots;
+  if (h->staging_used[slot] && hipEventSynchronize(h->staging_free[slot]) != hipSuccess)
+    return RANNC_DP_HIP_ERROR;
+  const size_t probs_bytes = (size_t)Q * sizeof(ProblemDev);
+  std::memcpy(h->staging[slot], probs.data(), probs_bytes);
+  h->solved = false;
+  // one group: its first launch reads the descriptors out of the staging memory and stores them
+  const bool in_place = all != 0 && h->staging_dev[slot] != nullptr;
+  h->staging_used[slot] = false;
+  if (!in_place) {
+    if (hipMemcpyAsync(h->ws, h->staging[slot], probs_bytes, hipMemcpyHostToDevice, st) != hipSuccess ||
+        hipEventRecord(h->staging_free[slot], st) != hipSuccess) {
+      (void)hipGetLastError();
+      return RANNC_DP_HIP_ERROR;
+    }
+    h->staging_used[slot] = true;
+  }
+  auto staging_read = [&]() -> bool {  // behind the launch that has read the staging memory
+    if (!in_place || chosen) return true;  // (a caller that waits has the slot back by then)
+    h->staging_used[slot] = hipEventRecord(h->staging_free[slot], st) == hipSuccess;
+    return h->staging_used[slot];
+  };
+
+  // ---- kernels ---------------------------------------------------------------------------
+  ProblemDev *const dp = h->d_probs;
+  const ProblemDev *const src = in_place ? (const ProblemDev *)h->staging_dev[slot] : dp;
+  bool ok = true;
+  const bool timing = h->timing;
+  h->ev_valid = false;
+  h->level_launches = 0;
+  if (timing) ok = ok && hipEventRecord(h->ev[0], st) == hipSuccess;
   // one stream per device-count class: the largest class stays on the caller's stream
   hipStream_t cs[4] = {st, st, st, st};
   int n_aux = 0;
@@ -813,35 +850,63 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
     return RANNC_DP_HIP_ERROR;
   }
   h->ev_valid = timing;
-  int kernel_of[4];
-  for (int k = 0; k < 4; ++k) {
-    h->no_times[k] = fused[k] ? fused_direct[k] : recompute_cls[k] || split_fast;
-    kernel_of[k] = fused[k]           ? (fused_direct[k] ? RANNC_DP_KERNEL_ONE_LAUNCH_RECOMPUTE : RANNC_DP_KERNEL_ONE_LAUNCH)
-                   : split_fast       ? RANNC_DP_KERNEL_SPLIT
-                   : split            ? RANNC_DP_KERNEL_SPLIT_SCAN
-                   : scan             ? RANNC_DP_KERNEL_SCAN
-                   : recompute_cls[k] ? RANNC_DP_KERNEL_MERGE_RECOMPUTE
-                                      : RANNC_DP_KERNEL_MERGE_TABLE;
-    h->info.n_problems[k] = 0;
-    h->info.level_kernel[k] = RANNC_DP_KERNEL_NONE;
-  }
-  for (int q = 0; q < Q; ++q) {  // reported by the searches' own classes, also where they ran as one group
-    int own = 0, ran = 0;
-    while (kClasses[own] != rannc::dp_class(b->n_devices[q])) ++own;
-    while (kClasses[ran] != dp_of(q)) ++ran;
-    h->info.n_problems[own]++;
-    h->info.level_kernel[own] = kernel_of[ran];
-  }
+  for (int k = 0; k < 4; ++k) h->no_times[k] = fused[k] ? fused_direct[k] : recompute_cls[k] || split_fast;
+  report();
   h->host_probs.swap(probs);
   h->pos_of.swap(pos_of);
   h->Q = Q;
   h->solved = true;
+  h->tabled = true;
   h->unchosen = choose_later;
   return RANNC_DP_OK;
 }
 
+// The last batch as it was answered without its tables, over the copies of its inputs.
+static void kept_batch(const rannc_dp_t *h, rannc_dp_batch_t *b) {
+  *b = {};
+  b->n_problems = h->Q;
+  b->n_blocks = h->kept.N.data(); b->n_devices = h->kept.D.data(); b->max_stages = h->kept.S.data();
+  b->n_microbatches = h->kept.MB.data(); b->mem_capacity = h->kept.M.data(); b->block_offset = h->kept.off.data();
+  const int64_t blocks = h->kept.off[h->Q];
+  b->time_ns = (const int64_t *)(h->ws + h->kept.saved_at);
+  b->param_bytes = b->time_ns + blocks;
+  b->act_bytes = b->param_bytes + blocks;
+}
+
+// Makes the tables of the last batch if it was answered without them.  Behind it they are there for work on any stream, as
+// they are behind a call that returns with its results.  Where the caller's stream is being recorded they are made on a
+// stream of the handle, at once: the recording holds what it would hold behind a call that had made them.
+static int ensure_tables(rannc_dp_t *h, void *hip_stream) {
+  if (!h->solved || h->tabled) return RANNC_DP_OK;
+  hipStream_t st = (hipStream_t)hip_stream;
+  hipStreamCaptureStatus recording = hipStreamCaptureStatusNone;
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  bool ok = hipStreamIsCapturing(st, &recording) == hipSuccess;
+  const bool aside = ok && recording != hipStreamCaptureStatusNone;
+  if (aside) {
+    st = h->aux[0];
+    ok = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+  }
+  int rc = RANNC_DP_HIP_ERROR;
+  if (ok) {
+    rannc_dp_batch_t b;
+    kept_batch(h, &b);
+    const size_t ws_bytes = h->ws_bytes;
+    h->ws_bytes = h->kept.saved_at;
+    rc = solve_impl(h, &b, st, nullptr, nullptr, nullptr, nullptr, nullptr);
+    h->ws_bytes = ws_bytes;
+    if (rc == RANNC_DP_OK && hipStreamSynchronize(st) != hipSuccess) rc = RANNC_DP_HIP_ERROR;
+    if (aside) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  }
+  if (rc != RANNC_DP_OK) (void)hipGetLastError();
+  h->solved = true;
+  h->tabled = rc == RANNC_DP_OK;
+  return rc;
+}
+
 int rannc_dp_solve(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream, int64_t *d_opt,
                    int32_t *d_n_stages, int64_t *d_est_iter_ns, int32_t *d_status) {
+  if (!h || !d_opt || !d_n_stages) return RANNC_DP_INVALID_ARG;
   return solve_impl(h, b, hip_stream, d_opt, d_n_stages, d_est_iter_ns, d_status, nullptr);
 }
 
@@ -852,6 +917,12 @@ constexpr size_t kFsReadInPlaceMax = 32 << 10;
 int rannc_dp_solve_info(rannc_dp_t *h, rannc_dp_solve_info_t *out) {
   if (!h || !out) return RANNC_DP_INVALID_ARG;
   if (!h->solved) return RANNC_DP_BAD_STATE;
+  if (!h->tabled) {  // answered without tables: what they will be made with
+    rannc_dp_batch_t b;
+    kept_batch(h, &b);
+    const int rc = solve_impl(h, &b, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0, nullptr, nullptr, true);
+    if (rc != RANNC_DP_OK) return rc;
+  }
   *out = h->info;
   return RANNC_DP_OK;
 }
@@ -890,6 +961,9 @@ static int traceback_impl(rannc_dp_t *h, void *hip_stream, const int32_t *d_leve
 
 int rannc_dp_traceback_at(rannc_dp_t *h, void *hip_stream, const int32_t *d_levels, int32_t plan_stride,
                           int32_t *d_stage_end, int32_t *d_replicas) {
+  if (!h || !d_stage_end || !d_replicas || plan_stride < 1) return RANNC_DP_INVALID_ARG;
+  const int rc = ensure_tables(h, hip_stream);
+  if (rc != RANNC_DP_OK) return rc;
   return traceback_impl(h, hip_stream, d_levels, plan_stride, d_stage_end, d_replicas, nullptr);
 }
 
@@ -922,6 +996,85 @@ int wait_flags(hipStream_t st, const uint64_t *flags, int n, uint64_t seq) {
     (void)hipGetLastError();
     return RANNC_DP_HIP_ERROR;
   }
+  return RANNC_DP_OK;
+}
+
+}  // namespace
+
+namespace {
+
+// Whether a batch can be answered without its tables: min-max searches without send times, on a handle that leaves the
+// choice of the kernels to the library.  *saved_at: where the copies of its inputs go, behind the regions that its
+// tables take (in a workspace without that room, and in one that the tables themselves would not fit, the tables are
+// made and decide).
+bool reach_applies(const rannc_dp_t *h, const rannc_dp_batch_t *b, size_t *saved_at) {
+  if (h->lim.algo != RANNC_DP_ALGO_AUTO || split_of(&h->lim) || b->cut_bytes || h->tune_spw != 0 || h->fused_small != 1 || h->timing ||
+      !h->staging_dev[h->next_slot] || !b->time_ns || !b->param_bytes || !b->act_bytes || b->time_bwd_ns)
+    return false;
+  size_t need = header_bytes(h->lim.max_problems), last = 0;
+  for (int q = 0; q < b->n_problems; ++q) {
+    const int N = b->n_blocks[q], D = b->n_devices[q];
+    if (N > rannc::kReachMaxBlocks) return false;
+    if (!q || N != b->n_blocks[q - 1] || D != b->n_devices[q - 1] || b->max_stages[q] != b->max_stages[q - 1]) {
+      Sizes sz;
+      if (!problem_sizes(N, D, rannc::dp_class(D), std::min(b->max_stages[q], std::min(N, D)), h->bits, false, false, &sz)) return false;
+      last = sz.total();
+    }
+    need += last;
+  }
+  const size_t saved = saved_bytes((size_t)(b->block_offset[b->n_problems] - b->block_offset[0]));
+  if (need + saved > h->ws_bytes) return false;
+  *saved_at = (h->ws_bytes - saved + kAlign) / kAlign * kAlign;
+  return true;
+}
+
+// Enqueues the searches and keeps what makes their tables later.  The caller waits for them.
+int reach_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, hipStream_t st, int32_t plan_stride, const rannc::PlanResults &r, size_t saved_at) {
+  const int Q = b->n_problems;
+  const int slot = h->next_slot;
+  if (h->staging_used[slot] && hipEventSynchronize(h->staging_free[slot]) != hipSuccess) {
+    (void)hipGetLastError();
+    return RANNC_DP_HIP_ERROR;
+  }
+  h->staging_used[slot] = false;
+  h->solved = false;
+  static_assert(sizeof(rannc::ReachIn) <= sizeof(ProblemDev), "the staging memory holds a descriptor per search");
+  rannc::ReachIn *const in = (rannc::ReachIn *)h->staging[slot];
+  LaunchShape sh = {};
+  sh.nprob = Q;
+  for (int q = 0; q < Q; ++q) {
+    const int N = b->n_blocks[q], D = b->n_devices[q], S = std::min(b->max_stages[q], std::min(N, D));
+    in[q] = {N, D, S, b->n_microbatches[q], b->mem_capacity[q], b->block_offset[q]};
+    sh.max_N = std::max(sh.max_N, N);
+    sh.max_D = std::max(sh.max_D, D);
+    sh.max_S_eff = std::max(sh.max_S_eff, S);
+  }
+  rannc::ReachArgs args = {};
+  args.t = b->time_ns; args.p = b->param_bytes; args.a = b->act_bytes;
+  args.save = (int64_t *)(h->ws + saved_at);
+  args.first = b->block_offset[0];
+  args.blocks = b->block_offset[Q] - args.first;
+  args.time_limit = h->lim.max_total_time_ns;
+  args.plan_stride = plan_stride;
+  args.results = r;
+  if (rannc::launch_reach((const rannc::ReachIn *)h->staging_dev[slot], Q == 1 ? in : nullptr, Q, sh, args, st) != hipSuccess) {
+    (void)hipGetLastError();
+    return RANNC_DP_HIP_ERROR;
+  }
+  h->ev_valid = false;
+  h->level_launches = 0;
+  try {
+    h->kept.N.assign(b->n_blocks, b->n_blocks + Q);
+    h->kept.D.assign(b->n_devices, b->n_devices + Q);
+    h->kept.S.assign(b->max_stages, b->max_stages + Q);
+    h->kept.MB.assign(b->n_microbatches, b->n_microbatches + Q);
+    h->kept.M.assign(b->mem_capacity, b->mem_capacity + Q);
+    h->kept.off.resize(Q + 1);
+    for (int q = 0; q <= Q; ++q) h->kept.off[q] = b->block_offset[q] - b->block_offset[0];
+  } catch (...) {
+    return RANNC_DP_NO_HOST_MEMORY;
+  }
+  h->kept.saved_at = saved_at;
   return RANNC_DP_OK;
 }
 
@@ -975,6 +1128,31 @@ int rannc_dp_solve_to_host(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_s
     // (a call of another layout may have left a result here that equals seq, which starts at 1)
     std::memset(flags, 0, 8 * (size_t)Q);
   }
+  size_t saved_at = 0;
+  if (reach_applies(h, b, &saved_at)) {
+    rc = reach_impl(h, b, st, plan_stride, r, saved_at);
+    if (rc == RANNC_DP_OK && !poll &&
+        (hipMemcpyAsync(h_results, d_results, at.total, hipMemcpyDeviceToHost, st) != hipSuccess || hipStreamSynchronize(st) != hipSuccess)) {
+      (void)hipGetLastError();
+      rc = RANNC_DP_HIP_ERROR;
+    }
+    if (rc == RANNC_DP_OK && poll) rc = wait_flags(st, flags, Q, r.seq);
+    if (rc != RANNC_DP_OK) {
+      (void)hipStreamSynchronize(st);
+      return rc;
+    }
+    const char *const out = poll ? h->res_pin : (const char *)h_results;
+    const int32_t *const status = (const int32_t *)(out + at.status);
+    if (std::find(status, status + Q, rannc::kReachUndecided) == status + Q) {
+      if (poll) std::memcpy(h_results, h->res_pin, at.total);
+      h->Q = Q;
+      h->solved = true;
+      h->tabled = false;
+      h->unchosen = false;
+      return RANNC_DP_OK;
+    }
+    r.seq = ++h->seq;  // left to the tables
+  }
   bool chosen = false, recovered = false;
   rc = solve_impl(h, b, hip_stream, r.d_opt, r.d_n_stages, r.d_est, r.d_status, &chosen, plan_stride, poll ? &r : nullptr, &recovered);
   if (rc == RANNC_DP_OK && !recovered)
@@ -999,6 +1177,8 @@ int rannc_dp_solve_to_host(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_s
 int rannc_dp_level_values(rannc_dp_t *h, void *hip_stream, int32_t stride, int64_t *d_values) {
   if (!h || !d_values || stride < 1) return RANNC_DP_INVALID_ARG;
   if (!h->solved) return RANNC_DP_BAD_STATE;
+  const int rc = ensure_tables(h, hip_stream);
+  if (rc != RANNC_DP_OK) return rc;
   for (int q = 0; q < h->Q; ++q)
     if (h->host_probs[q].S_eff > stride) return RANNC_DP_INVALID_ARG;
   if (rannc::launch_level_values(h->d_probs, h->Q, stride, d_values, (hipStream_t)hip_stream) != hipSuccess) {
@@ -1329,6 +1509,8 @@ int rannc_dp_read_table(rannc_dp_t *h, int which, int32_t problem, void *d_dst, 
   if (!h || !d_dst) return RANNC_DP_INVALID_ARG;
   if (!h->solved) return RANNC_DP_BAD_STATE;
   if (problem < 0 || problem >= h->Q) return RANNC_DP_INVALID_ARG;
+  const int made = ensure_tables(h, hip_stream);
+  if (made != RANNC_DP_OK) return made;
   const int pos = h->pos_of[problem];
   const ProblemDev &p = h->host_probs[pos];
   const size_t tri = (size_t)p.N * (size_t)(p.N + 1) / 2 * (size_t)p.D;

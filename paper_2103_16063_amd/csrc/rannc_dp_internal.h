@@ -219,6 +219,26 @@ hipError_t launch_traceback(const ProblemDev *probs, int Q, int plan_stride, int
                             int32_t *d_replicas, const int32_t *d_levels, int64_t lds_bytes,
                             const FormStageIn *form_stage, const PlanResults *results, bool choose, hipStream_t st);
 hipError_t launch_level_values(const ProblemDev *probs, int Q, int stride, int64_t *d_out, hipStream_t st);
+// Min-max searches without send times answered without their tables (rannc_dp_reach.hip): optimum, fewest stages,
+// plan, by one workgroup each.  Copies of the inputs go to `save` (three arrays of `blocks` entries, the searches one
+// after the other), from which the tables can be made later.
+constexpr int kReachMaxBlocks = 4096;   // the sums of a search are held in LDS
+constexpr int kReachUndecided = -1;     // status of a search that is left to the tables
+struct ReachIn {
+  int32_t N, D, S, MB;
+  int64_t M;
+  int64_t first;  // index of its first block in the input arrays
+};
+struct ReachArgs {
+  const int64_t *t, *p, *a;  // DEVICE
+  int64_t *save;
+  int64_t blocks, first;  // of the batch: entries of a saved array, index of the first block
+  int64_t time_limit;
+  int plan_stride;
+  PlanResults results;
+};
+// src: the descriptors in memory the device can read (pinned); host_one: of a launch over one search, by value, or null
+hipError_t launch_reach(const ReachIn *src, const ReachIn *host_one, int Q, const LaunchShape &sh, const ReachArgs &args, hipStream_t st);
 // compaction step of the block-level phase on a chain of G groups (one workgroup).  Short chains are
 // held in LDS; longer ones keep arrays of G + 1 entries in the workspace: three of 8 bytes and two of 4
 constexpr size_t compact_array_bytes(int G, int entry) { return ((size_t)(G + 1) * entry + 255) / 256 * 256; }

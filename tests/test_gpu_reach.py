@@ -1,0 +1,113 @@
+"""Searches answered without their tables (rannc_dp_solve_to_host on a handle that leaves the kernels to the library)
+against the oracle, where the kernel can go wrong: sizes at the edges of its loops and of what it takes, ties, chains
+whose optimum leaves many cells open, too few stages, sums beyond its range.  And what such a call leaves behind: tables
+made when they are asked for."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2103_16063_amd import binding as B
+from paper_2103_16063_amd import synth
+from tests.gpu_util import assert_results_match, oracle_solve_many
+
+pytestmark = pytest.mark.gpu
+
+
+def _search(seed, N, D, S, kind="plain", share=1.6, scale=1):
+    g = np.random.default_rng([seed, N, D, S])
+    t, p, a = (g.integers(1, 1000, N).astype(np.int64) for _ in range(3))
+    if kind == "equal":
+        t[:], p[:], a[:] = 7, 11, 13
+    if kind == "one long":
+        t[N // 3] = 2 * t.sum()
+    if kind == "zeros":
+        t[:] = 0
+    if kind == "transient":
+        a *= 50
+    M = int((p.sum() + a.sum()) / max(1, min(S, D, N)) * share) * scale
+    return {"name": f"{kind}_{seed}_{N}_{D}_{S}", "time_ns": t, "param_bytes": p * scale, "act_bytes": a * scale, "n_devices": D,
+            "max_stages": S, "n_microbatches": 8, "mem_capacity": M}
+
+
+def _check(probs, **kw):
+    with B.Session(synth.concat_batch(probs), **kw) as s:
+        assert_results_match(probs, s.run(), oracle_results=oracle_solve_many(probs))
+
+
+@pytest.mark.parametrize("N,D,S", [(1, 1, 1), (1, 64, 3), (2, 2, 2), (63, 33, 9), (64, 16, 8), (65, 17, 64), (192, 64, 12), (193, 8, 8), (576, 24, 6),
+                                   (577, 3, 3), (1088, 5, 4), (1089, 40, 3), (4096, 2, 2), (4097, 2, 2)])
+@pytest.mark.parametrize("share", [1.05, 1.6, 8.0])
+def test_edges_of_the_sizes(N, D, S, share):
+    _check([_search(1, N, D, S, share=share)])
+    _check([_search(2, N, D, S, share=share)], max_total_time_ns=1 << 50)
+
+
+@pytest.mark.parametrize("kind", ["equal", "one long", "zeros", "transient"])
+@pytest.mark.parametrize("Q", [1, 64, 65, 513])   # each number of waves, with and without results in host memory
+def test_open_plans_and_ties(kind, Q):
+    g = np.random.default_rng(Q)
+    probs = [_search(q, int(g.integers(2, 60)), int(g.integers(1, 65)), int(g.choice([1, 2, 3, 5, 64])), kind,
+                     share=float(g.choice([0.8, 1.02, 1.3, 2.5]))) for q in range(Q)]
+    _check(probs)
+
+
+def test_beyond_the_exact_range_the_tables_decide():
+    """Bytes of 2^46 and more in all, and times of 2^44 ns."""
+    big = _search(3, 90, 12, 6, scale=1 << 31)
+    assert big["param_bytes"].sum() > 1 << 46
+    _check([big, _search(4, 80, 12, 6)])
+    late = _search(5, 70, 20, 6)
+    late["time_ns"] = late["time_ns"] << 29
+    assert late["time_ns"].sum() > 1 << 44
+    _check([late], max_total_time_ns=1 << 60)
+
+
+def test_flagged_searches_among_others():
+    probs = [_search(q, 50 + q, 9, 5) for q in range(4)]
+    probs[1]["time_ns"][3] = -1
+    probs[2]["param_bytes"][:] = 1 << 61
+    probs[3]["time_ns"][:] = 1 << 30
+    with B.Session(synth.concat_batch(probs)) as s:
+        res = s.run()
+        assert list(res["status"]) == [0, B.PROBLEM_NEGATIVE_INPUT, B.PROBLEM_SUM_OVERFLOW, B.PROBLEM_TIME_TOO_LARGE]
+        assert (res["opt"][1:] == B.INT64_MAX).all() and not res["n_stages"][1:].any() and (res["stage_end"][1:] == -1).all()
+        assert_results_match(probs[:1], {k: v[:1] for k, v in res.items()})
+
+
+def test_tables_are_made_from_what_the_call_was_given():
+    """Inputs overwritten behind the call; the tables, level values and plans are still those of the searches it solved."""
+    probs = [_search(q, 40 + 9 * q, (5, 16, 30, 64)[q % 4], 7) for q in range(6)]
+    with B.Session(synth.concat_batch(probs)) as s:
+        res = s.run()
+        for x in s.d_in:
+            x.fill_(-1)
+        d_v = torch.full((6, s.plan_stride), -5, dtype=torch.int64, device="cuda:0")
+        assert B.rannc_dp_level_values(s.h, s.stream(), s.plan_stride, d_v) == B.OK
+        s.d_se.fill_(-3)
+        s.traceback()
+        torch.cuda.synchronize()
+        assert np.array_equal(s.d_se.cpu().numpy(), res["stage_end"])
+        for q, pr in enumerate(probs):
+            o = oracle.solve(pr, keep_tables=True)
+            N, D, L = len(pr["time_ns"]), pr["n_devices"], o["n_levels"]
+            assert np.array_equal(s.table(B.TABLE_V, q), o["V"])
+            assert np.array_equal(d_v.cpu().numpy()[q, :L], o["V"][1:L + 1, N, D])
+
+
+def test_plan_recovery_recorded_behind_the_call():
+    probs = [_search(q, 60, 12, 6) for q in range(3)]
+    with B.Session(synth.concat_batch(probs)) as s:
+        res = s.run()
+        stream = torch.cuda.Stream()
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            assert B.rannc_dp_traceback(s.h, torch.cuda.current_stream().cuda_stream, s.plan_stride, s.d_se, s.d_rp) == B.OK
+        for _ in range(3):
+            s.d_se.fill_(-3)
+            s.d_rp.fill_(-3)
+            graph.replay()
+            torch.cuda.synchronize()
+            assert np.array_equal(s.d_se.cpu().numpy(), res["stage_end"]) and np.array_equal(s.d_rp.cpu().numpy(), res["replicas"])
+        assert np.array_equal(s.table(B.TABLE_V, 1), oracle.solve(probs[1], keep_tables=True)["V"])
