@@ -118,8 +118,8 @@ bool packed_of(const rannc_dp_limits_t *l) { return l->max_total_time_ns <= rann
 int bits_of(const rannc_dp_limits_t *l) { return l->max_total_time_ns <= kNarrowMax ? 32 : 64; }
 
 size_t header_bytes(int Q) { return align_up((size_t)Q * sizeof(ProblemDev)); }
-// the copies of the inputs behind the searches' regions (rannc_dp_reach.hip)
-size_t saved_bytes(size_t blocks) { return align_up(3 * 8 * blocks) + kAlign; }
+// the copies of the inputs behind the searches' regions, from which tables are made later: up to five arrays
+size_t saved_bytes(size_t blocks) { return align_up(5 * 8 * blocks) + kAlign; }
 
 // Host-side validation of the batch descriptors against the limits.
 int check_batch(const rannc_dp_limits_t *l, const rannc_dp_batch_t *b) {
@@ -214,11 +214,14 @@ struct rannc_dp {
                     // 0 = never, 2 = whenever N <= 128 (RANNC_DP_FUSED_SMALL)
   int64_t call_total_bound;  // > 0 during the outer driver's solve: no search's total time exceeds it
   // The last batch, where it was answered without its tables (solved, but not tabled): what makes them when they are
-  // asked for.  Its inputs are at ws + saved_at, three arrays.
+  // asked for.  Its inputs are at ws + saved_at (times, persistent, transient bytes, bytes per cut, backward times), or, of
+  // the outer driver, they come from its own per sample (`sample`, the same arrays; search q times samples[q]).
   bool tabled;
   struct {
     std::vector<int32_t> N, D, S, MB;
-    std::vector<int64_t> M, off;
+    std::vector<int64_t> M, off, bw, sample, samples;
+    bool comm, split;
+    int64_t total_bound;
     size_t saved_at;
   } kept;
 };
@@ -871,6 +874,11 @@ static void kept_batch(const rannc_dp_t *h, rannc_dp_batch_t *b) {
   b->time_ns = (const int64_t *)(h->ws + h->kept.saved_at);
   b->param_bytes = b->time_ns + blocks;
   b->act_bytes = b->param_bytes + blocks;
+  if (h->kept.comm) {
+    b->cut_bytes = b->act_bytes + blocks;
+    b->bandwidth_bytes_per_us = h->kept.bw.data();
+  }
+  if (h->kept.split) b->time_bwd_ns = b->act_bytes + 2 * blocks;
 }
 
 // Makes the tables of the last batch if it was answered without them.  Behind it they are there for work on any stream, as
@@ -891,10 +899,27 @@ static int ensure_tables(rannc_dp_t *h, void *hip_stream) {
   if (ok) {
     rannc_dp_batch_t b;
     kept_batch(h, &b);
-    const size_t ws_bytes = h->ws_bytes;
-    h->ws_bytes = h->kept.saved_at;
-    rc = solve_impl(h, &b, st, nullptr, nullptr, nullptr, nullptr, nullptr);
-    h->ws_bytes = ws_bytes;
+    std::vector<int64_t> scaled;
+    if (!h->kept.sample.empty()) {
+      const size_t N = (size_t)h->kept.N[0], Q = (size_t)h->Q;
+      try {
+        scaled.resize(5 * Q * N);
+      } catch (...) {
+        ok = false;
+      }
+      for (size_t w = 0; w < 5 && ok; ++w)
+        for (size_t q = 0; q < Q; ++q)
+          for (size_t k = 0; k < N; ++k) scaled[(w * Q + q) * N + k] = h->kept.sample[w * N + k] * (w == 1 ? 1 : h->kept.samples[q]);
+      ok = ok && hipMemcpyAsync(h->ws + h->kept.saved_at, scaled.data(), scaled.size() * 8, hipMemcpyHostToDevice, st) == hipSuccess;
+    }
+    if (ok) {
+      const size_t ws_bytes = h->ws_bytes;
+      h->ws_bytes = h->kept.saved_at;
+      h->call_total_bound = h->kept.total_bound;
+      rc = solve_impl(h, &b, st, nullptr, nullptr, nullptr, nullptr, nullptr);
+      h->call_total_bound = 0;
+      h->ws_bytes = ws_bytes;
+    }
     if (rc == RANNC_DP_OK && hipStreamSynchronize(st) != hipSuccess) rc = RANNC_DP_HIP_ERROR;
     if (aside) (void)hipThreadExchangeStreamCaptureMode(&mode);
   }
@@ -920,7 +945,9 @@ int rannc_dp_solve_info(rannc_dp_t *h, rannc_dp_solve_info_t *out) {
   if (!h->tabled) {  // answered without tables: what they will be made with
     rannc_dp_batch_t b;
     kept_batch(h, &b);
+    h->call_total_bound = h->kept.total_bound;
     const int rc = solve_impl(h, &b, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0, nullptr, nullptr, true);
+    h->call_total_bound = 0;
     if (rc != RANNC_DP_OK) return rc;
   }
   *out = h->info;
@@ -1003,29 +1030,41 @@ int wait_flags(hipStream_t st, const uint64_t *flags, int n, uint64_t seq) {
 
 namespace {
 
-// Whether a batch can be answered without its tables: min-max searches without send times, on a handle that leaves the
-// choice of the kernels to the library.  *saved_at: where the copies of its inputs go, behind the regions that its
-// tables take (in a workspace without that room, and in one that the tables themselves would not fit, the tables are
-// made and decide).
-bool reach_applies(const rannc_dp_t *h, const rannc_dp_batch_t *b, size_t *saved_at) {
-  if (h->lim.algo != RANNC_DP_ALGO_AUTO || split_of(&h->lim) || b->cut_bytes || h->tune_spw != 0 || h->fused_small != 1 || h->timing ||
-      !h->staging_dev[h->next_slot] || !b->time_ns || !b->param_bytes || !b->act_bytes || b->time_bwd_ns)
-    return false;
+// Whether the kernels are left to the library, and how a call is answered with them.
+bool library_chooses(const rannc_dp_t *h) {
+  return h->lim.algo == RANNC_DP_ALGO_AUTO && h->tune_spw == 0 && h->fused_small == 1 && !h->timing && h->staging_dev[h->next_slot];
+}
+
+// Where the copies of a batch's inputs go: behind the regions that its tables take.  False: the workspace has no such room,
+// or none for the tables themselves (which then find that out).  shape(q): blocks, devices, stages of search q.
+struct SearchShape { int N, D, S; };
+extern "C++" template <typename Shape> bool room_for_inputs(const rannc_dp_t *h, int Q, Shape shape, size_t blocks, size_t *saved_at) {
   size_t need = header_bytes(h->lim.max_problems), last = 0;
-  for (int q = 0; q < b->n_problems; ++q) {
-    const int N = b->n_blocks[q], D = b->n_devices[q];
-    if (N > rannc::kReachMaxBlocks) return false;
-    if (!q || N != b->n_blocks[q - 1] || D != b->n_devices[q - 1] || b->max_stages[q] != b->max_stages[q - 1]) {
+  SearchShape before = {};
+  for (int q = 0; q < Q; ++q) {
+    const SearchShape x = shape(q);
+    if (!q || x.N != before.N || x.D != before.D || x.S != before.S) {
       Sizes sz;
-      if (!problem_sizes(N, D, rannc::dp_class(D), std::min(b->max_stages[q], std::min(N, D)), h->bits, false, false, &sz)) return false;
+      if (!problem_sizes(x.N, x.D, rannc::dp_class(x.D), std::min(x.S, std::min(x.N, x.D)), h->bits, split_of(&h->lim), packed_of(&h->lim), &sz))
+        return false;
       last = sz.total();
+      before = x;
     }
     need += last;
   }
-  const size_t saved = saved_bytes((size_t)(b->block_offset[b->n_problems] - b->block_offset[0]));
+  const size_t saved = saved_bytes(blocks);
   if (need + saved > h->ws_bytes) return false;
   *saved_at = (h->ws_bytes - saved + kAlign) / kAlign * kAlign;
   return true;
+}
+
+// Whether a batch can be answered without its tables: min-max searches without send times that the kernel holds.
+bool reach_applies(const rannc_dp_t *h, const rannc_dp_batch_t *b, size_t *saved_at) {
+  if (!library_chooses(h) || split_of(&h->lim) || b->cut_bytes || !b->time_ns || !b->param_bytes || !b->act_bytes || b->time_bwd_ns) return false;
+  for (int q = 0; q < b->n_problems; ++q)
+    if (b->n_blocks[q] > rannc::kReachMaxBlocks) return false;
+  return room_for_inputs(h, b->n_problems, [&](int q) { return SearchShape{b->n_blocks[q], b->n_devices[q], b->max_stages[q]}; },
+                         (size_t)(b->block_offset[b->n_problems] - b->block_offset[0]), saved_at);
 }
 
 // Enqueues the searches and keeps what makes their tables later.  The caller waits for them.
@@ -1074,6 +1113,9 @@ int reach_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, hipStream_t st, int32_t
   } catch (...) {
     return RANNC_DP_NO_HOST_MEMORY;
   }
+  h->kept.sample.clear();
+  h->kept.comm = h->kept.split = false;
+  h->kept.total_bound = 0;
   h->kept.saved_at = saved_at;
   return RANNC_DP_OK;
 }
@@ -1224,6 +1266,163 @@ size_t fs_scratch(int Q, int N, int stride) {
 
 }  // namespace
 
+namespace {
+
+// The outer driver without the tables of its searches.  False: left to them, with whatever is wrong with the inputs.
+// *rc: status of the call otherwise.
+bool form_direct(rannc_dp_t *h, const rannc_dp_form_stage_in_t *in, const std::vector<FsPair> &pairs, int max_D, hipStream_t st,
+                 rannc_dp_form_stage_out_t *out, int32_t *stage_end, int32_t *replicas, int32_t plan_stride, int *rc) {
+  const int N = in->n_blocks, Q = (int)pairs.size(), per = in->devices_per_node;
+  const bool comm = in->cut_bytes_per_sample != nullptr, split = in->time_bwd_per_sample_ns != nullptr;
+  if (!library_chooses(h) || Q > kPollMaxProblems || N > rannc::kFormMaxBlocks || per > rannc::kFormMaxSpare || !h->fs_pin_dev || !h->res_pin_dev)
+    return false;
+  size_t saved_at = 0;
+  if (!room_for_inputs(h, Q, [&](int q) { return SearchShape{N, per * pairs[q].n, per * pairs[q].n}; }, (size_t)Q * N, &saved_at)) return false;
+  // ---- inputs within the exact range of the kernel, and persistent bytes alone: the fewest stages that hold them ----
+  int64_t samples = 0;  // of the largest microbatch
+  for (const FsPair &p : pairs) samples = std::max(samples, p.b);
+  constexpr int64_t kBytes = (int64_t)1 << 46, kTime = (int64_t)1 << 44;
+  int64_t time = 0, param = 0, act = 0, cut = 0, stage = 0;
+  int fewest = 1;
+  for (int k = 0; k < N; ++k) {
+    const int64_t t = in->time_per_sample_ns[k], a = in->act_bytes_per_sample[k], p = in->param_bytes[k];
+    const int64_t o = comm ? in->cut_bytes_per_sample[k] : 0, tb = split ? in->time_bwd_per_sample_ns[k] : 0;
+    if (t < 0 || a < 0 || p < 0 || o < 0 || tb < 0 || t >= kTime || tb >= kTime || a >= kBytes || p >= kBytes || o >= kBytes) return false;
+    time += t + tb;
+    act += a;
+    param += p;
+    cut = std::max(cut, o);
+    if (time >= kTime || act >= kBytes || param >= kBytes) return false;
+    if (stage + p > in->mem_capacity) { stage = 0; ++fewest; }
+    stage += p;  // (a block that fits no device by itself: more stages than there are, or none that the kernel finds)
+  }
+  if ((__int128)time * samples >= kTime || (__int128)act * samples >= kBytes || (__int128)cut * samples >= kBytes) return false;
+  const int64_t send = comm ? (int64_t)(((__int128)cut * samples * 1000 + in->bandwidth_bytes_per_us - 1) / in->bandwidth_bytes_per_us) : 0;
+  if (time * samples + send >= kTime || time * samples + send > h->lim.max_total_time_ns) return false;
+  // ---- the searches whose stage counts can hold the chain ----
+  const int stride = std::min(max_D, N);
+  int64_t *const arrays = (int64_t *)h->fs_pin;  // per sample; the scratch's mirror has room for them and the descriptors
+  const size_t arrays_bytes = 5 * 8 * (size_t)N;
+  rannc::FormIn *const desc = (rannc::FormIn *)(h->fs_pin + arrays_bytes);
+  int of[kPollMaxProblems], searches = 0;
+  const size_t found_at = arrays_bytes + (size_t)Q * sizeof(rannc::FormIn);
+  if (found_at + 8 * (size_t)Q > h->fs_pin_bytes) return false;
+  for (int q = 0; q < Q; ++q) {
+    const int lo = per * (pairs[q].n - 1) + 1, hi = std::min(per * pairs[q].n, N);
+    if (hi < lo || hi < fewest) continue;
+    desc[searches] = {per * pairs[q].n, std::max(lo, fewest), hi, __builtin_ctz((unsigned)pairs[q].n), pairs[q].b};
+    of[searches++] = q;
+  }
+  const ResultLayout at((size_t)std::max(searches, 1), (size_t)stride);
+  if (at.total + 8 * (size_t)searches > h->res_pin_bytes) return false;
+  std::memcpy(arrays, in->time_per_sample_ns, 8 * (size_t)N);
+  std::memcpy(arrays + N, in->param_bytes, 8 * (size_t)N);
+  std::memcpy(arrays + 2 * N, in->act_bytes_per_sample, 8 * (size_t)N);
+  if (comm) std::memcpy(arrays + 3 * N, in->cut_bytes_per_sample, 8 * (size_t)N);
+  if (split) std::memcpy(arrays + 4 * N, in->time_bwd_per_sample_ns, 8 * (size_t)N);
+  h->solved = false;
+  h->ev_valid = false;
+  h->level_launches = 0;
+  const char *const m = h->res_pin;
+  if (searches) {
+    const int64_t *const dev = (const int64_t *)h->fs_pin_dev;
+    rannc::FormArgs args = {};
+    args.t = dev; args.p = dev + N; args.a = dev + 2 * N;
+    args.o = comm ? dev + 3 * N : nullptr;
+    args.tb = split ? dev + 4 * N : nullptr;
+    args.pairs = (const rannc::FormIn *)(h->fs_pin_dev + arrays_bytes);
+    args.M = in->mem_capacity; args.bw = comm ? in->bandwidth_bytes_per_us : 1;
+    args.N = N; args.searches = searches; args.plan_stride = stride;
+    char *const d = h->res_pin_dev;
+    args.results.h_opt = (int64_t *)(d + at.opt);
+    args.results.h_n_stages = (int32_t *)(d + at.n_stages);
+    args.results.h_status = (int32_t *)(d + at.status);
+    args.results.h_stage_end = (int32_t *)(d + at.stage_end);
+    args.results.h_replicas = (int32_t *)(d + at.replicas);
+    args.results.h_flag = (uint64_t *)(d + at.total);
+    args.results.seq = ++h->seq;
+    args.found = (uint64_t *)(h->fs_pin_dev + found_at);
+    std::memset(h->fs_pin + found_at, 0, 8 * (size_t)searches);
+    std::memset(h->res_pin + at.total, 0, 8 * (size_t)searches);  // (as in rannc_dp_solve_to_host)
+    if (rannc::launch_form(searches, per, args, st) != hipSuccess) {
+      (void)hipGetLastError();
+      *rc = RANNC_DP_HIP_ERROR;
+      return true;
+    }
+  }
+  bool kept = true;
+  try {
+    h->kept.N.assign(Q, N);
+    h->kept.D.resize(Q); h->kept.S.resize(Q); h->kept.MB.resize(Q); h->kept.samples.resize(Q); h->kept.off.resize(Q + 1);
+    h->kept.M.assign(Q, in->mem_capacity);
+    h->kept.bw.assign(Q, in->bandwidth_bytes_per_us);
+    h->kept.sample.assign(5 * (size_t)N, 0);
+  } catch (...) {
+    kept = false;
+  }
+  if (kept) {
+    for (int q = 0; q < Q; ++q) {
+      h->kept.D[q] = h->kept.S[q] = per * pairs[q].n;
+      h->kept.MB[q] = pairs[q].MB;
+      h->kept.samples[q] = pairs[q].b;
+      h->kept.off[q] = (int64_t)q * N;
+    }
+    h->kept.off[Q] = (int64_t)Q * N;
+    std::memcpy(h->kept.sample.data(), arrays, (split ? 5 : comm ? 4 : 3) * 8 * (size_t)N);
+    h->kept.comm = comm;
+    h->kept.split = split;
+    int64_t forward = 0;
+    for (int k = 0; k < N; ++k) forward += in->time_per_sample_ns[k];
+    h->kept.total_bound = std::max<int64_t>(forward * samples, 0);
+    h->kept.saved_at = saved_at;
+  }
+  if (searches) *rc = wait_flags(st, (const uint64_t *)(m + at.total), searches, h->seq);
+  else *rc = hipStreamSynchronize(st) == hipSuccess ? RANNC_DP_OK : RANNC_DP_HIP_ERROR;
+  if (*rc == RANNC_DP_OK && !kept) *rc = RANNC_DP_NO_HOST_MEMORY;
+  if (*rc != RANNC_DP_OK) {
+    (void)hipStreamSynchronize(st);
+    (void)hipGetLastError();
+    return true;
+  }
+  // ---- Algorithm 2's loops: the first n with a plan, its fewest stages, the smallest estimate, the first search ----
+  const int64_t *const value = (const int64_t *)(m + at.opt);
+  const int32_t *const n_stages = (const int32_t *)(m + at.n_stages), *const status = (const int32_t *)(m + at.status);
+  int pick = -1;
+  int64_t best = 0;
+  for (int k0 = 0, k1; k0 < searches && pick < 0; k0 = k1) {  // (n ascends)
+    int open = INT32_MAX;  // fewest stages that a search of this n has left open
+    for (k1 = k0; k1 < searches && pairs[of[k1]].n == pairs[of[k0]].n; ++k1) {
+      if (status[k1] != RANNC_DP_PROBLEM_OK) { open = std::min(open, n_stages[k1]); continue; }
+      if (n_stages[k1] == 0) continue;
+      const int64_t f = (int64_t)pairs[of[k1]].MB + n_stages[k1] - 1;
+      const int64_t est = value[k1] != 0 && f > INT64_MAX / value[k1] ? INT64_MAX : f * value[k1];
+      if (pick < 0 || n_stages[k1] < n_stages[pick] || (n_stages[k1] == n_stages[pick] && est < best)) { pick = k1; best = est; }
+    }
+    if (open != INT32_MAX && (pick < 0 || open <= n_stages[pick])) return false;
+  }
+  h->Q = Q;
+  h->solved = true;
+  h->tabled = false;
+  h->unchosen = false;
+  std::memset(out, 0, sizeof(*out));
+  for (int u = 0; u < plan_stride; ++u) stage_end[u] = replicas[u] = -1;
+  if (pick < 0) return true;
+  const FsPair &p = pairs[of[pick]];
+  out->feasible = 1;
+  out->n = p.n;
+  out->devices = per * p.n;
+  out->replica_factor = in->n_nodes / p.n;
+  out->n_stages = n_stages[pick];
+  out->n_microbatches = p.MB;
+  out->stage_time_ns = value[pick];
+  out->est_iter_ns = best;
+  const int32_t *const se = (const int32_t *)(m + at.stage_end) + (size_t)pick * stride, *const rp = (const int32_t *)(m + at.replicas) + (size_t)pick * stride;
+  for (int u = 0; u < std::min(stride, (int)plan_stride); ++u) { stage_end[u] = se[u]; replicas[u] = rp[u]; }
+  return true;
+}
+
+}  // namespace
+
 int32_t rannc_dp_form_stage_problems(const rannc_dp_form_stage_in_t *in) {
   std::vector<FsPair> pairs;
   int max_D = 0;
@@ -1296,6 +1495,8 @@ int rannc_dp_form_stage(rannc_dp_t *h, const rannc_dp_form_stage_in_t *in, void 
       h->fs_pin_dev = nullptr;
     }
   }
+  int direct = RANNC_DP_OK;
+  if (form_direct(h, in, pairs, max_D, st, out, stage_end, replicas, plan_stride, &direct)) return direct;
   try {
     if (comm) hbw.assign(Q, in->bandwidth_bytes_per_us);
     hM.assign(Q, in->mem_capacity); hoff.resize(Q + 1);

@@ -239,6 +239,25 @@ struct ReachArgs {
 };
 // src: the descriptors in memory the device can read (pinned); host_one: of a launch over one search, by value, or null
 hipError_t launch_reach(const ReachIn *src, const ReachIn *host_one, int Q, const LaunchShape &sh, const ReachArgs &args, hipStream_t st);
+// The outer driver's searches, each the smallest stage count of lo..hi with a plan of exactly so many stages on D devices,
+// and that plan (rannc_dp_form.hip): one workgroup each, results in pinned host memory.
+constexpr int kFormMaxBlocks = 1024, kFormMaxSpare = 8;  // spare: devices of a node
+constexpr int kFormWide = 256;  // split objective: rows of a level
+struct FormIn {
+  int32_t D, lo, hi, group;  // group: searches of as many nodes; of a smaller group a plan is taken first
+  int64_t b;                 // samples of a microbatch
+};
+struct FormArgs {
+  const int64_t *t, *p, *a, *o, *tb;  // per sample, in memory the device can read; o, tb: or null
+  const FormIn *pairs;
+  int64_t M, bw;
+  int N, searches, plan_stride, cells;
+  uint64_t *found;      // pinned host memory, a word per search: results.seq << 16 | group << 8 | stages of its plan
+  PlanResults results;  // h_opt, h_n_stages (of a search left to the tables: the stage count that is open), h_status,
+                        // h_stage_end, h_replicas, h_flag
+};
+// spare: largest D - lo + 1 of the pairs
+hipError_t launch_form(int Q, int spare, const FormArgs &args, hipStream_t st);
 // compaction step of the block-level phase on a chain of G groups (one workgroup).  Short chains are
 // held in LDS; longer ones keep arrays of G + 1 entries in the workspace: three of 8 bytes and two of 4
 constexpr size_t compact_array_bytes(int G, int entry) { return ((size_t)(G + 1) * entry + 255) / 256 * 256; }

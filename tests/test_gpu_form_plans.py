@@ -1,0 +1,72 @@
+"""The outer driver answered by one workgroup per (n, MB) pair, at the edges of what that kernel takes: chains at the
+ends of its loops and beyond them, one to nine devices a node, searches whose stage counts lie far above what the memory
+asks for; and the tables that are made behind such a call."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2103_16063_amd import binding as B
+from paper_2103_16063_amd import synth
+from tests.test_gpu_form_stage import _assert_same
+
+pytestmark = pytest.mark.gpu
+
+
+def _case(seed, N, nodes, per, BS, tight, form):
+    c = synth.form_stage_case(seed, N, nodes, per, BS, tight=tight, tmax=3000, layered=N > 8)
+    g = np.random.default_rng(seed)
+    more = {}
+    if "comm" in form:
+        more = {"cut_bytes_per_sample": g.integers(0, 1 << 18, N), "bandwidth_bytes_per_us": 100_000}
+    if "split" in form:
+        more["time_bwd_per_sample_ns"] = g.integers(1, 4000, N)
+    if "ties" in form:
+        for k in ("time_per_sample_ns", "act_bytes_per_sample", "param_bytes"):
+            c[k] = np.full(N, 5, np.int64)
+        c["mem_capacity"] = int(5 * N * (1 + BS) * tight / (nodes * per)) + 1
+    want = oracle.form_stage(c["time_per_sample_ns"], c["act_bytes_per_sample"], c["param_bytes"], nodes, per, BS, c["mem_capacity"],
+                             n_threads=8, **more)
+    fs = B.FormStageSession(N, nodes, per, BS, split="split" in form, max_total_time_ns=1 << 42)
+    _assert_same(c, fs.run(c["time_per_sample_ns"], c["act_bytes_per_sample"], c["param_bytes"], c["mem_capacity"], **more), want,
+                 fs.plan_stride)
+    return c, more, fs, want
+
+
+@pytest.mark.parametrize("form", ["plain", "comm", "split", "split comm", "ties", "ties split"])
+@pytest.mark.parametrize("N,nodes,per,BS,tight", [(1, 1, 1, 1, 3.0), (64, 4, 4, 16, 1.3), (65, 2, 5, 8, 2.2), (193, 4, 8, 16, 1.6),
+                                                  (40, 8, 8, 16, 1.1), (40, 3, 9, 16, 1.4), (33, 4, 2, 300, 6.0)])
+def test_drivers(N, nodes, per, BS, tight, form):
+    if "split" in form and N > 100:
+        N = 100
+    _case(3, N, nodes, per, BS, tight, form)[2].close()
+
+
+@pytest.mark.parametrize("N,per", [(577, 2), (1024, 1), (1025, 1)])
+def test_long_chains(N, per):
+    _case(5, N, 2, per, 4, 2.5, "plain")[2].close()
+
+
+@pytest.mark.parametrize("form", ["plain", "comm", "split comm"])
+def test_tables_behind_the_driver(form):
+    c, more, fs, want = _case(11, 48, 2, 6, 16, 1.8, form)
+    assert want is not None
+    q = 0
+    for n in (1, 2):            # search q of the batch: the pairs in the loops' order
+        for MB in (1, 2, 4, 8, 16):
+            if MB <= 16 // (2 // n):
+                if (n, MB) == (want["n"], want["n_microbatches"]):
+                    found = q
+                q += 1
+    N, D, S = 48, want["devices"], want["n_stages"]
+    se, rp = (torch.full((fs.Q, fs.plan_stride), -7, dtype=torch.int32, device="cuda:0") for _ in range(2))
+    levels = torch.full((fs.Q,), -1, dtype=torch.int32, device="cuda:0")
+    levels[found] = S
+    stream = torch.cuda.current_stream().cuda_stream
+    assert B.rannc_dp_traceback_at(fs.h, stream, levels, fs.plan_stride, se, rp) == B.OK
+    values = torch.zeros((fs.Q, fs.plan_stride), dtype=torch.int64, device="cuda:0")
+    assert B.rannc_dp_level_values(fs.h, stream, fs.plan_stride, values) == B.OK
+    torch.cuda.synchronize()
+    assert list(se[found, :S].cpu()) == list(want["stage_end"]) and list(rp[found, :S].cpu()) == list(want["replicas"])
+    assert int(values[found, S - 1]) == want["stage_time_ns"]
+    fs.close()
