@@ -3,6 +3,9 @@
 #include "rannc_dp_device.h"
 #include "rannc_dp_once.h"
 
+#include <algorithm>
+#include <type_traits>
+
 namespace rannc {
 
 // ---------------------------------------------------------------------------------------
@@ -36,18 +39,31 @@ namespace rannc {
 //
 // Where few turns are possible at a time, one wave goes on without barriers (kFewTurns).
 //
-// Bound by latency and by one compute unit's issue rate.  15 000 groups to 32 blocks: 19.7 ms with one
-// lane following a sorted list through memory, 0.30 ms here (41 us of it the sums in front of the
-// groups, 115 us the first walk); 400 groups 330 -> 60 us; ascending times 20.8 -> 14.6 ms at 15 000
-// groups (1 us per turn), 0.37 -> 0.39 ms at 400.
+// On times without an order along the chain a group's turn depends on few positions to either side, so a walk is first
+// tried in windows, a wave to each (compact_window_walk), without barriers: walks of up to kCompactWindows groups by the
+// waves of one workgroup, those of longer chains as launches over the whole device (compact_first_kernel,
+// compact_walk_kernel), which leave a bit per group; a walk of which any window was too small, or which would go to k groups or below, is
+// done again by one workgroup in rounds as above (a walk that stops at k by its windows, where they are large enough).
+//
+// Bound by latency: a round of a window is some 80 instructions and one round of LDS permutes, 0.35 us, six to nine rounds to
+// a walk; a launched walk is 8 to 10 us, of which 3 are four dependent reads (words of the walk before, first
+// group, sums) and the workgroup's scan.  15 000 groups to 32 blocks, per call: 19.7 ms with one lane following a sorted list
+// through memory, 0.30 ms in rounds by one workgroup, 62 us here (9 the first walk and the sums, 3 x 9 the next walks,
+// 22 the rest).  In rounds / here: 65 535 groups 1 110 / 115 us, 5 000 158 / 55, 1 600 129 / 72, 400 71 / 46, 64 51 / 33;
+// ascending times, 15 000 groups, 14.6 ms (a turn after the other by one wave, 1 us each).
 // ---------------------------------------------------------------------------------------
 constexpr int kCompactSmall = 1600;     // up to here everything is in LDS and four waves do the work
 constexpr int kCompactTimesLds = 16384; // up to here the times (and the bit maps) are in LDS
 
-template <int MODE> struct CompactShape;  // threads; mask of the groups a thread looks after (u = tid + b * threads)
-template <> struct CompactShape<0> { static constexpr int NT = 256; using Mask = uint32_t; static constexpr int kMax = kCompactSmall; };
-template <> struct CompactShape<1> { static constexpr int NT = 1024; using Mask = uint32_t; static constexpr int kMax = kCompactTimesLds; };
-template <> struct CompactShape<2> { static constexpr int NT = 1024; using Mask = uint64_t; static constexpr int kMax = 65535; };
+constexpr int kCompactWindows = 1600;  // up to here a walk of one workgroup goes in windows
+// Above, a walk of a long chain gets a launch of its own (9 us; by one workgroup's windows 500 groups take as long, 1 600
+// 20 us).
+constexpr int kCompactLaunch = 500;
+
+template <int MODE> struct CompactShape;  // mask of the groups a thread looks after (u = tid + b * threads)
+template <> struct CompactShape<0> { using Mask = uint32_t; static constexpr int kMax = kCompactSmall; };
+template <> struct CompactShape<1> { using Mask = uint32_t; static constexpr int kMax = kCompactTimesLds; };
+template <> struct CompactShape<2> { using Mask = uint64_t; static constexpr int kMax = 65535; };
 
 // inclusive sum over the workgroup of one value per thread; part: one word per wave
 template <int NT, typename X> __device__ __forceinline__ X compact_scan(X v, X *part) {
@@ -149,37 +165,326 @@ __device__ __forceinline__ bool compact_turn(TP T, MP M, const CompactAround &c,
   return ahead;
 }
 
-template <int MODE>
-__global__ __launch_bounds__(CompactShape<MODE>::NT) void compact_kernel(
-    int G, int k, int64_t mem, int max_walks, const int64_t *__restrict__ t_in, const int64_t *__restrict__ p_in,
-    const int64_t *__restrict__ a_in, char *__restrict__ ws, int32_t *n_out, int32_t *block_end,
-    int64_t *t_out, int64_t *p_out, int64_t *a_out, int32_t *status) {
-  constexpr int NT = CompactShape<MODE>::NT;
-  constexpr int kMax = CompactShape<MODE>::kMax;
-  constexpr int kWords = (kMax + 31) / 32 + 3;  // a bit per group, an empty word in front and two behind
+// ---- a walk in windows ----
+// What a turn sees depends on turns a few positions away, those on a few more, and so on, each ahead of the one before: on
+// times without an order along the chain rarely more than twenty positions in all.  A wave takes 63 consecutive groups, one
+// to a lane, with everything it needs in registers, and walks them as far as it can: a group whose turn could be
+// preceded by one outside the window never gets there, and neither does what depends on it.  If the groups in the
+// window's middle have all had their turns, and the head in front of them too (whose turn could remove the first one's
+// boundary), what became of them is what the walk makes of them.
+struct CompactWindow { uint64_t heads, self; bool whole; };  // self: boundaries removed by the turn of the group behind them
+constexpr int kWindow = 63;                                  // (the last lane holds the end of the last group)
+constexpr uint32_t kCompactOpen = ~0u;                       // a chunk whose window was too small
+// t, m: time and bytes of the group of this lane; groups: lanes with one; the middle: lanes [first, last)
+__device__ __forceinline__ CompactWindow compact_window_walk(uint64_t t, uint64_t m, int groups, bool open_left, bool open_right,
+                                                             uint64_t mem, int first, int last) {
+  const int lane = threadIdx.x & 63;
+  const uint64_t all = (1ull << groups) - 1ull, middle = all & ((1ull << last) - (1ull << first)), in_front = (1ull << first) - 1ull;
+  const uint64_t below = (1ull << lane) - 1ull, above = ~((2ull << lane) - 1ull);
+  auto has = [](uint64_t mask, int u) { return (mask >> (u & 63) & 1ull) != 0ull; };
+  uint64_t head = all, waits = all, self = 0ull;
+  for (;;) {
+    const uint64_t hf = head & in_front, needed = middle | (hf ? 1ull << (63 - __clzll((long long)hf)) : 0ull);
+    if (!(waits & needed)) return {head, self, true};
+    const uint64_t hb = head & below, ha = head & above;
+    const int l = 63 - __clzll((long long)hb), r = __ffsll((long long)ha) - 1;  // next heads (-1: none)
+    const uint64_t hb2 = hb & ~(1ull << (l & 63)), ha2 = ha & (ha - 1ull);
+    const int ll = 63 - __clzll((long long)hb2), rr = __ffsll((long long)ha2) - 1;
+    const uint64_t listed = has(waits, lane) ? t : ~0ull;  // place in the list; behind all others where the group is not in it any more
+    const uint64_t tl = __shfl(t, l & 63), tr = __shfl(t, r & 63), kll = __shfl(listed, ll & 63), krr = __shfl(listed, rr & 63);
+    const uint64_t ml = __shfl(m, l & 63), mr = __shfl(m, r & 63);
+    // equal times: the one further left is ahead in the list
+    const bool known = (hb2 != 0ull || !open_left) && (ha2 != 0ull || !open_right);
+    const bool l_first = hb != 0ull && has(waits, l) && tl <= t, ll_first = hb2 != 0ull && kll <= t;
+    const bool r_first = ha != 0ull && has(waits, r) && tr < t, rr_first = ha2 != 0ull && krr < t;
+    const bool turn = has(waits, lane) && known && !(l_first | ll_first | r_first | rr_first);
+    const bool left = !((ha != 0ull ? tr : ~0ull) < (hb != 0ull ? tl : ~0ull));
+    const bool join = m + (left ? ml : mr) <= mem;
+    const uint64_t turns = __ballot(turn), to_left = __ballot(turn & join & left), to_right = __ballot(turn & join & !left);
+    if (turns == 0ull) return {head, self, false};
+    const bool takes = ha != 0ull && has(to_left, r);  // the next head joins this one
+    if (takes || has(to_right, lane)) {
+      t += tr;
+      m += mr;
+    }
+    // (a group that waits is as listed: its right neighbour is the next lane)
+    waits &= ~(turns | __ballot(takes) | to_right << 1);
+    head &= ~(to_left | to_right << 1);
+    self |= to_left;
+  }
+}
+
+// What becomes of `size` (at most 32) of the n groups from `at` on, by one wave: bits of heads and self, or whole = false.
+// load(u, t, m): time and bytes of group u (any u; collective).  Where the window is too small for all of them, for half as
+// many at a time.  (Of windows with a middle of 16 groups three in a million are too small on times without an order,
+// with a middle of 32 one in a hundred.)
+constexpr int kLeastMiddle = 2;
+constexpr int kWindowReach = kWindow / 2 + 1;  // groups in front of `at`, and from at + size on, that load may be asked for
+template <typename Load> __device__ __forceinline__ CompactWindow compact_range(int at, int size, int n, uint64_t mem, Load load) {
+  const int lane = threadIdx.x & 63, end = min(at + size, n);
+  CompactWindow all = {0ull, 0ull, true};
+#pragma unroll 1
+  for (int pos = at; pos < end;) {
+    const int start = max(pos - (kWindow - size) / 2 - 1, 0), groups = min(kWindow, n - start), first = pos - start;
+    uint64_t t, m;
+    load(start + lane, t, m);
+    const CompactWindow w = compact_window_walk(t, m, groups, start > 0, start + groups < n, mem, first, first + size);
+    if (w.whole) {
+      const uint64_t here = (1ull << min(size, end - pos)) - 1ull;
+      all.heads |= (w.heads >> first & here) << (pos - at);
+      all.self |= (w.self >> first & here) << (pos - at);
+      pos += size;
+    } else if (size > kLeastMiddle) {
+      size /= 2;
+    } else {
+      all.whole = false;
+      break;
+    }
+  }
+  return all;
+}
+
+// Where the state of a chain of more than kCompactSmall groups stands in the workspace.  Sums in front of a group of the
+// input: A, P, T; those of a walk's groups, by walk's parity: the input group each begins with (first), and what became
+// of them, sixteen to a word: heads, self << 16 (or kCompactOpen).
+struct CompactState {
+  uint64_t *A, *P, *T;
+  int32_t *first[2], *turn;
+  uint32_t *became[2];
+  uint64_t *totals;      // of times, persistent and transient bytes: upper halves, lower halves, flags
+  int32_t *left;         // [w]: groups left by walk w, or -1: that walk does not count
+};
+constexpr int kCompactMostWalks = 24;
+constexpr int kCompactChunk = 16;  // groups in the middle of a window
+constexpr size_t compact_state_bytes(int G) {
+  return 3 * compact_array_bytes(G, 8) + 3 * compact_array_bytes(G, 4) + 2 * compact_array_bytes(G / kCompactChunk, 4) + 9 * 8 +
+         4 * (kCompactMostWalks + 1);
+}
+__host__ __device__ inline CompactState compact_state(void *ws, int G) {
+  const size_t a8 = compact_array_bytes(G, 8), a4 = compact_array_bytes(G, 4), aw = compact_array_bytes(G / kCompactChunk, 4);
+  char *const b = (char *)ws, *const c = b + 3 * a8, *const d = c + 3 * a4;
+  return {(uint64_t *)b, (uint64_t *)(b + a8), (uint64_t *)(b + 2 * a8), {(int32_t *)c, (int32_t *)(c + a4)}, (int32_t *)(c + 2 * a4),
+          {(uint32_t *)d, (uint32_t *)(d + aw)}, (uint64_t *)(d + 2 * aw), (int32_t *)(d + 2 * aw + 9 * 8)};
+}
+static_assert(compact_state_bytes(kCompactSmall + 1) <= compact_workspace_bytes(kCompactSmall + 1) &&
+              compact_state_bytes(2049) <= compact_workspace_bytes(2049) && compact_state_bytes(4096) <= compact_workspace_bytes(4096) &&
+              compact_state_bytes(16384) <= compact_workspace_bytes(16384) && compact_state_bytes(65535) <= compact_workspace_bytes(65535),
+              "what callers have been told holds it");
+
+// The groups that a walk has left of n, from what became of them: expand(rank, group) is called for those whose rank
+// (number among the groups left) lies in [lo, hi).  Returns how many are left, or -1 where a chunk is open.
+template <int NT, typename Expand>
+__device__ __forceinline__ int compact_left(const uint32_t *became, int n, int lo, int hi, int *part, Expand expand) {
+  const int words = (n + kCompactChunk - 1) / kCompactChunk, per = (words + NT - 1) / NT;
+  const int at = min((int)threadIdx.x * per, words), end = min(at + per, words);
+  int sum = 0;
+  bool open = false;
+#pragma unroll 4
+  for (int e = at; e < end; ++e) {
+    const uint32_t w = became[e];
+    open |= w == kCompactOpen;
+    sum += __popc(w & 0xFFFFu);
+  }
+  const int upto = compact_scan<NT>(sum, part);
+  if (upto > lo && upto - sum < hi) {
+    int rank = upto - sum;
+#pragma unroll 1
+    for (int e = at; e < end; ++e)
+#pragma unroll 1
+      for (uint32_t x = became[e] & 0xFFFFu; x; x &= x - 1u, ++rank)
+        if (rank >= lo && rank < hi) expand(rank, e * kCompactChunk + __ffs((int)x) - 1);
+  }
+  if ((int)threadIdx.x == NT - 1) part[NT / 64] = upto;
+  const bool bad = __syncthreads_or(open);
+  return bad ? -1 : part[NT / 64];
+}
+
+constexpr int kCompactWalkNT = 256;
+template <typename Load> __device__ __forceinline__ void compact_chunk(int at, int n, uint64_t mem, uint32_t *became, Load load) {
+  const CompactWindow w = compact_range(at, kCompactChunk, n, mem, load);
+  if ((threadIdx.x & 63) == 0) became[at / kCompactChunk] = w.whole ? (uint32_t)w.heads | (uint32_t)w.self << 16 : kCompactOpen;
+}
+
+// First walk of a long chain, a window to a wave, and, by the first workgroups, the sums in front of its groups.
+// Every workgroup of the sums adds up what lies in front of its own 1024 groups again.
+constexpr int kCompactSumsPer = 4;
+__global__ __launch_bounds__(kCompactWalkNT) void compact_first_kernel(int G, int64_t mem, const int64_t *__restrict__ t_in,
+                                                                       const int64_t *__restrict__ p_in,
+                                                                       const int64_t *__restrict__ a_in, const CompactState st) {
+  constexpr int NT = kCompactWalkNT, PER = kCompactSumsPer, U = 32;  // U: reads in flight
+  __shared__ uint64_t part[NT / 64], s_front;
+  __shared__ unsigned long long s_sum[2];
+  __shared__ int s_flags;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int stretches = (G + NT * PER - 1) / (NT * PER), b = blockIdx.x;
+  if (b >= 3 * stretches) {
+    const int at = ((b - 3 * stretches) * (NT / 64) + (tid >> 6)) * kCompactChunk;
+    if (at >= G) return;
+    compact_chunk(at, G, (uint64_t)mem, st.became[1], [&](int u, uint64_t &t, uint64_t &m) {
+      u = min(u, G - 1);
+      t = (uint64_t)t_in[u];
+      m = (uint64_t)p_in[u] + (uint64_t)a_in[u];
+    });
+    return;
+  }
+  // (the longest ones first)
+  const int which = b % 3, stretch = stretches - 1 - b / 3;
+  const int64_t *const in = which == 0 ? t_in : which == 1 ? p_in : a_in;
+  uint64_t *const out = which == 0 ? st.T : which == 1 ? st.P : st.A;
+  const int lo = stretch * NT * PER, hi = min(lo + NT * PER, G);
+  if (tid < 2) s_sum[tid] = 0ull;
+  if (tid == 0) s_flags = 0;
+  // totals as sums of the upper and of the lower halves: neither can overflow before the check
+  uint64_t high = 0, low = 0;
+  int flags = 0;
+  auto take = [&](int64_t v) {
+    if (v < 0) flags |= 1;
+    else if ((uint64_t)v >= kSumLimit) flags |= 2;
+    high += (uint64_t)v >> 32;
+    low += (uint32_t)v;
+  };
+  int64_t mine[PER];
+#pragma unroll
+  for (int u = 0; u < PER; ++u) mine[u] = lo + tid * PER + u < hi ? in[lo + tid * PER + u] : 0;
+  for (int g0 = tid; g0 < lo; g0 += U * NT) {
+    int64_t v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = in[min(g0 + u * NT, lo - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (g0 + u * NT < lo) take(v[u]);
+  }
+  const uint64_t upto = compact_scan<NT>((high << 32) + low, part);
+  if (tid == NT - 1) s_front = upto;
+  uint64_t own = 0;
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    take(mine[u]);
+    own += (uint64_t)mine[u];
+  }
+  own = compact_scan<NT>(own, part) - own;
+  uint64_t run = s_front + own;  // (behind the barriers of the scan)
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int g = lo + tid * PER + u;
+    if (g < hi) out[g] = run;
+    run += (uint64_t)mine[u];
+    if (g + 1 == G) out[G] = run;
+  }
+  if (stretch != stretches - 1) return;
+  // ---- this workgroup has seen the whole array: what its validation needs ----
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    high += __shfl_xor(high, o);
+    low += __shfl_xor(low, o);
+    flags |= __shfl_xor(flags, o);
+  }
+  if (lane == 0) {
+    atomicAdd(&s_sum[0], (unsigned long long)high);
+    atomicAdd(&s_sum[1], (unsigned long long)low);
+    if (flags) atomicOr(&s_flags, flags);
+  }
+  __syncthreads();
+  if (tid < 2) st.totals[3 * which + tid] = s_sum[tid];
+  if (tid == 2) st.totals[3 * which + 2] = (uint64_t)s_flags;
+}
+
+// Walk w of a long chain, w >= 2; does nothing where the one before does not count (a window was too small, nothing
+// merged, or it would have gone to k groups or below: left to compact_resume_kernel).
+__global__ __launch_bounds__(kCompactWalkNT) void compact_walk_kernel(int G, int k, int64_t mem, int w, const CompactState st) {
+  constexpr int NT = kCompactWalkNT, kRanks = NT / 64 * kCompactChunk;  // of a workgroup
+  __shared__ int part[NT / 64 + 1];
+  __shared__ int group[kRanks + 2 * kWindowReach];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int before = w == 2 ? G : st.left[w - 2];
+  const int lo = (int)blockIdx.x * kRanks - kWindowReach, hi = lo + kRanks + 2 * kWindowReach;
+  int n = -1;
+  if (before >= 0) {
+    n = compact_left<NT>(st.became[(w - 1) & 1], before, lo, hi, part, [&](int rank, int u) { group[rank - lo] = u; });
+    if (n <= k || n >= before) n = -1;
+  }
+  if (blockIdx.x == 0 && tid == 0) st.left[w - 1] = n;
+  const int at = ((int)blockIdx.x * (NT / 64) + (tid >> 6)) * kCompactChunk;
+  if (at >= n) return;
+  compact_chunk(at, n, (uint64_t)mem, st.became[w & 1], [&](int u, uint64_t &t, uint64_t &m) {
+    int from = G;
+    if (u < n) {
+      from = group[u - lo];
+      if (w > 2) from = st.first[w & 1][from];
+    }
+    const uint64_t T = st.T[from], M = st.P[from] + st.A[from];
+    if (u >= at && u < min(at + kCompactChunk, n)) st.first[(w - 1) & 1][u] = from;
+    t = __shfl(T, (lane + 1) & 63) - T;
+    m = __shfl(M, (lane + 1) & 63) - M;
+  });
+}
+
+constexpr int kCompactFewRemoved = 256;  // walks up to here: the merge to stop at is found by comparing all pairs
+
+template <int MODE, int NT> struct CompactShared {
+  static constexpr int kMax = CompactShape<MODE>::kMax;
+  static constexpr int kWords = (kMax + 31) / 32 + 3;  // a bit per group, an empty word in front and two behind
   using Mask = typename CompactShape<MODE>::Mask;
+  uint64_t removed_time[kCompactFewRemoved], part[NT / 64], s_key;
+  unsigned long long s_sum[4];
+  uint64_t s_last[3];
+  Mask look[2][NT];                   // groups a thread has to look at in this round / in the next one
+  uint32_t head[kWords], waits[kWords];
+  int first[kWords];                  // heads in front of a word of the bit map
+  int hist[256], parti[NT / 64], few[64], removed_place[kCompactFewRemoved];
+  int s_turns[3], s_flags, s_left, s_few, s_open;
+};
+
+// RESUME: n groups are left of a chain whose sums stand in `state`; the input group u begins with is from(u), for
+// u <= n (a collective call is not needed).
+template <int MODE, int NT, bool RESUME, typename From>
+__device__ __forceinline__ void compact_body(
+    CompactShared<MODE, NT> &sh, int G, int n, int k, int64_t mem, int walk, int max_walks, const int64_t *__restrict__ t_in, const int64_t *__restrict__ p_in,
+    const int64_t *__restrict__ a_in, char *__restrict__ ws, const CompactState &state, From from, int32_t *n_out, int32_t *block_end,
+    int64_t *t_out, int64_t *p_out, int64_t *a_out, int32_t *status) {
+  constexpr int kMax = CompactShape<MODE>::kMax, kWords = CompactShared<MODE, NT>::kWords;
+  using Mask = typename CompactShape<MODE>::Mask;
+  constexpr int kFewTurns = 12;  // their neighbours, five each, fill a wave
   static_assert((kMax + NT - 1) / NT <= 8 * (int)sizeof(Mask), "a thread's groups fit its mask");
   extern __shared__ __align__(16) char lds[];
-  __shared__ uint32_t head[kWords], waits[kWords];
-  __shared__ Mask look[2][NT];        // groups a thread has to look at in this round / in the next one
-  __shared__ int first[kWords];       // heads in front of a word of the bit map
-  __shared__ uint64_t part[NT / 64], s_key;
-  __shared__ int hist[256], parti[NT / 64], s_flags, s_turns[3], s_left;
-  constexpr int kFewTurns = 12;  // their neighbours, five each, fill a wave
-  __shared__ int few[64], s_few;
-  __shared__ unsigned long long s_sum[4];
-  [[maybe_unused]] __shared__ uint64_t s_last[3];
+  auto &removed_time = sh.removed_time;
+  auto &part = sh.part;
+  auto &s_last = sh.s_last;
+  auto &s_sum = sh.s_sum;
+  auto &s_key = sh.s_key;
+  auto &look = sh.look;
+  auto &head = sh.head, &waits = sh.waits;
+  auto &first = sh.first;
+  auto &hist = sh.hist;
+  auto &parti = sh.parti;
+  auto &few = sh.few;
+  auto &removed_place = sh.removed_place;
+  auto &s_turns = sh.s_turns;
+  int &s_flags = sh.s_flags, &s_left = sh.s_left, &s_few = sh.s_few, &s_open = sh.s_open;
   const int tid = threadIdx.x, lane = tid & 63;
   // arrays of G + 1 entries: times and bytes in front of a group (the bytes of the inputs as well), its
   // first input group; and which turn removed a boundary
-  const size_t a8 = compact_array_bytes(G, 8), a4 = compact_array_bytes(G, 4);
+  const int entries = RESUME && MODE == 0 ? kCompactSmall : G;
+  const size_t a8 = compact_array_bytes(entries, 8), a4 = compact_array_bytes(entries, 4);
   char *const arrays = MODE == 0 ? lds : ws;
   uint64_t *const M = (uint64_t *)arrays;
-  uint64_t *const P = (uint64_t *)(arrays + a8);
-  int32_t *const orig = (int32_t *)(arrays + 2 * a8);
-  int32_t *const turn = (int32_t *)(arrays + 2 * a8 + a4);
-  uint64_t *const T = (uint64_t *)(MODE == 1 ? lds : arrays + 2 * a8 + 2 * a4);
+  uint64_t *const T = (uint64_t *)(MODE == 0 ? lds + a8 : MODE == 1 ? lds : ws + 2 * a8);
+  uint64_t *const P = RESUME ? state.P : (uint64_t *)(arrays + (MODE == 0 ? 2 : 1) * a8);
+  int32_t *const orig = (int32_t *)(arrays + 3 * a8);
+  int32_t *const turn = (int32_t *)(arrays + 3 * a8 + (MODE == 0 ? 1 : 2) * a4);
 
+  if constexpr (RESUME) {
+    // (in place where they stand in the workspace: a group never begins in front of its own number)
+    for (int u0 = 0; u0 <= n; u0 += NT) {
+      const int u = u0 + tid;
+      int at = 0;
+      uint64_t tv = 0, mv = 0;
+      if (u <= n) { at = from(u); tv = state.T[at]; mv = state.P[at] + state.A[at]; }
+      __syncthreads();
+      if (u <= n) { orig[u] = at; T[u] = tv; M[u] = mv; }
+    }
+    __syncthreads();
+  } else {
   // ---- validation, and the sums in front of every group ----
   if (tid < 4) s_sum[tid] = 0ull;
   if (tid == 0) s_flags = 0;
@@ -293,10 +598,36 @@ __global__ __launch_bounds__(CompactShape<MODE>::NT) void compact_kernel(
       return;
     }
   }
+  }
 
-  int n = G;  // groups as they stand
-  for (int walk = 1; n > k && (max_walks <= 0 || walk <= max_walks); ++walk) {
+  for (; n > k && (max_walks <= 0 || walk <= max_walks); ++walk) {  // (n: groups as they stand)
     const int nw = (n + 31) >> 5;  // words of the bit maps that hold groups: 1 .. nw
+    if (tid == 0) { s_left = 0; s_open = 0; }
+    bool open = true;
+    if (n <= kCompactWindows) {
+      // ---- the walk, in windows: 32 groups to a wave and turn ----
+      if (tid == 0) { head[0] = 0u; head[nw + 1] = 0u; head[nw + 2] = 0u; }
+      __syncthreads();
+      for (int at = 32 * (tid >> 6); at < n; at += NT / 2) {
+        const CompactWindow w = compact_range(at, 32, n, (uint64_t)mem, [&](int u, uint64_t &t, uint64_t &m) {
+          const uint64_t Tu = T[min(u, n)], Mu = M[min(u, n)];
+          t = __shfl(Tu, (lane + 1) & 63) - Tu;
+          m = __shfl(Mu, (lane + 1) & 63) - Mu;
+        });
+        if (!w.whole) { if (lane == 0) s_open = 1; break; }
+        const uint32_t here = (uint32_t)(n - at >= 32 ? ~0u : (1u << (n - at)) - 1u), heads = (uint32_t)w.heads & here;
+        if (lane == 0) {
+          head[(at + 32) >> 5] = heads;
+          atomicAdd(&s_left, __popc(here & ~heads));
+        }
+        if (lane < 32 && at + lane < n && !(heads >> lane & 1u)) turn[at + lane] = at + lane - ((uint32_t)w.self >> lane & 1u ? 0 : 1);
+      }
+      __syncthreads();
+      open = s_open != 0;
+      __syncthreads();
+      if (tid == 0 && open) s_left = 0;
+    }
+    if (open) {
     for (int w = tid; w < nw + 3 && w < kWords; w += NT) {
       const uint32_t all = w == 0 || w > nw ? 0u : (w == nw && (n & 31)) ? (1u << (n & 31)) - 1u : ~0u;
       head[w] = all;
@@ -309,7 +640,6 @@ __global__ __launch_bounds__(CompactShape<MODE>::NT) void compact_kernel(
       look[1][tid] = 0;
     }
     if (tid < 3) s_turns[tid] = tid == 2;  // ("the round before the first one had a turn")
-    if (tid == 0) s_left = 0;
     __syncthreads();
     // ---- the walk, in rounds ----
     int merged = 0;
@@ -421,12 +751,32 @@ __global__ __launch_bounds__(CompactShape<MODE>::NT) void compact_kernel(
     }
     if (merged) atomicAdd(&s_left, merged);
     __syncthreads();
+    }
     const int total = s_left;
     if (total == 0) break;
     // ---- stop at k groups: undo the merges behind the (n-k)-th in list order ----
     int now = n - total;
     if (now < k) {
       auto removed = [&](int u) { return !compact_bit(head, u); };
+      if (total <= kCompactFewRemoved) {
+        if (tid == 0) s_few = 0;
+        __syncthreads();
+        for (int u = tid; u < n; u += NT)
+          if (removed(u)) {
+            const int e = atomicAdd(&s_few, 1), v = turn[u];
+            removed_time[e] = T[v + 1] - T[v];
+            removed_place[e] = v << 1 | (u != v ? 1 : 0);
+          }
+        __syncthreads();
+        if (tid < total) {
+          const uint64_t tv = removed_time[tid];
+          const int v = removed_place[tid];  // (one merge to a turn: no two are equal)
+          int ahead = 0;
+          for (int e = 0; e < total; ++e) ahead += (removed_time[e] < tv) | ((removed_time[e] == tv) & (removed_place[e] < v)) ? 1 : 0;
+          const int u = (v >> 1) + (v & 1);
+          if (ahead >= n - k) atomicOr(&head[(u + 32) >> 5], 1u << (u & 31));
+        }
+      } else {
       int want = n - k;  // the want-th smallest (time, position) among the turns that merged, 1-based
       uint64_t found = 0;  // the digits of that place so far: the time, then the position
       uint64_t top = 0;
@@ -483,6 +833,7 @@ __global__ __launch_bounds__(CompactShape<MODE>::NT) void compact_kernel(
         const uint64_t tv = T[v + 1] - T[v];
         if (tv > at || (tv == at && (uint64_t)v > found)) atomicOr(&head[(u + 32) >> 5], 1u << (u & 31));
       }
+      }
       now = k;
       __syncthreads();
     }
@@ -534,33 +885,114 @@ __global__ __launch_bounds__(CompactShape<MODE>::NT) void compact_kernel(
   if (tid == 0) { *n_out = n; *status = RANNC_DP_PROBLEM_OK; }
 }
 
-template <int MODE>
-static hipError_t compact_go(size_t lds, int G, int k, int64_t M, int max_walks, const int64_t *t, const int64_t *p,
-                             const int64_t *a, void *ws, int32_t *n_out, int32_t *block_end, int64_t *t_out,
-                             int64_t *p_out, int64_t *a_out, int32_t *status, hipStream_t st) {
-  // more than the default 64 KiB of dynamic LDS has to be asked for
-  constexpr size_t most = MODE == 0 ? 3 * compact_array_bytes(kCompactSmall, 8) + 2 * compact_array_bytes(kCompactSmall, 4)
-                          : MODE == 1 ? compact_array_bytes(kCompactTimesLds, 8) : 0;
-  if constexpr (most > 64 * 1024) {
-    static std::atomic<uint64_t> asked{0};
-    const hipError_t attr = allow_lds(asked, (const void *)compact_kernel<MODE>, (int)most);
-    if (attr != hipSuccess) return attr;
-  }
-  if (lds > most) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((compact_kernel<MODE>), dim3(1), dim3(CompactShape<MODE>::NT), lds, st, G, k, M, max_walks, t, p, a,
-                     (char *)ws, n_out, block_end, t_out, p_out, a_out, status);
-  return hipGetLastError();
+template <int MODE, int NT>
+__global__ __launch_bounds__(NT) void compact_kernel(int G, int k, int64_t mem, int max_walks, const int64_t *__restrict__ t_in,
+                                                     const int64_t *__restrict__ p_in, const int64_t *__restrict__ a_in,
+                                                     char *__restrict__ ws, int32_t *n_out, int32_t *block_end, int64_t *t_out,
+                                                     int64_t *p_out, int64_t *a_out, int32_t *status) {
+  __shared__ CompactShared<MODE, NT> sh;
+  compact_body<MODE, NT, false>(sh, G, G, k, mem, 1, max_walks, t_in, p_in, a_in, ws, CompactState{}, [](int u) { return u; }, n_out, block_end,
+                                t_out, p_out, a_out, status);
 }
+
+// What is left to do behind `walks` launched walks of a long chain.
+template <int MODE>
+__global__ __launch_bounds__(1024) void compact_resume_kernel(int G, int k, int64_t mem, int max_walks, int walks, char *__restrict__ ws,
+                                                              const CompactState state, int32_t *n_out, int32_t *block_end, int64_t *t_out,
+                                                              int64_t *p_out, int64_t *a_out, int32_t *status) {
+  constexpr int NT = 1024;
+  extern __shared__ __align__(16) char lds[];
+  __shared__ int part[NT / 64 + 1];
+  __shared__ union { CompactShared<0, NT> small; CompactShared<MODE, NT> large; } sh;
+  const int tid = threadIdx.x;
+  const uint64_t *const x = state.totals;
+  int flags = (int)(x[2] | x[5] | x[8]);
+  if (x[0] + (x[1] >> 32) >= (kSumLimit >> 32) || x[3] + x[6] + ((x[4] + x[7]) >> 32) >= (kSumLimit >> 32)) flags |= 2;
+  if (flags) {  // (the sums may have wrapped: they are not looked at)
+    if (tid == 0) {
+      *status = (flags & 1) ? RANNC_DP_PROBLEM_NEGATIVE_INPUT : RANNC_DP_PROBLEM_SUM_OVERFLOW;
+      *n_out = 0;
+    }
+    return;
+  }
+  int done = 0, n = G;  // walks that count
+  while (done + 1 < walks && state.left[done + 1] >= 0) n = state.left[++done];
+  const int32_t *const first = done ? state.first[done & 1] : nullptr;
+  auto plain = [&](int u) { return u >= n ? G : first ? first[u] : u; };
+  int at[2] = {G, G};  // of a thread's groups, where the last walk counts, whose groups nobody has gathered yet
+  static_assert(kCompactSmall < 2 * NT, "two of a thread");
+  bool picked = false;
+  if (done == walks - 1) {
+    int *const group = (int *)lds;
+    const int left = compact_left<NT>(state.became[walks & 1], n, 0, kCompactSmall, part, [&](int rank, int u) { group[rank] = u; });
+    picked = left >= k && left < n && left <= kCompactSmall;
+    if (picked) {
+#pragma unroll
+      for (int e = 0; e < 2; ++e)
+        if (e * NT + tid < left) at[e] = plain(group[e * NT + tid]);
+      n = left;
+      ++done;
+    }
+    __syncthreads();
+  }
+  if (n <= kCompactSmall)
+    compact_body<0, NT, true>(sh.small, G, n, k, mem, done + 1, max_walks, nullptr, nullptr, nullptr, ws, state,
+                              [&](int u) { return picked ? (u < NT ? at[0] : at[1]) : plain(u); }, n_out, block_end, t_out, p_out, a_out,
+                              status);
+  else
+    compact_body<MODE, NT, true>(sh.large, G, n, k, mem, done + 1, max_walks, nullptr, nullptr, nullptr, ws, state, plain, n_out, block_end,
+                                 t_out, p_out, a_out, status);
+}
+
+constexpr size_t kCompactSmallLds = 3 * compact_array_bytes(kCompactSmall, 8) + 2 * compact_array_bytes(kCompactSmall, 4);
 
 hipError_t launch_compact(int G, int k, int64_t M, int max_walks, const int64_t *t, const int64_t *p,
                           const int64_t *a, void *ws, int32_t *n_out, int32_t *block_end, int64_t *t_out,
                           int64_t *p_out, int64_t *a_out, int32_t *status, hipStream_t st) {
-  const size_t a8 = compact_array_bytes(G, 8), a4 = compact_array_bytes(G, 4);
-  if (G <= kCompactSmall)
-    return compact_go<0>(3 * a8 + 2 * a4, G, k, M, max_walks, t, p, a, ws, n_out, block_end, t_out, p_out, a_out, status, st);
-  if (G <= kCompactTimesLds)
-    return compact_go<1>(a8, G, k, M, max_walks, t, p, a, ws, n_out, block_end, t_out, p_out, a_out, status, st);
-  return compact_go<2>(0, G, k, M, max_walks, t, p, a, ws, n_out, block_end, t_out, p_out, a_out, status, st);
+  constexpr size_t kTimesLds = compact_array_bytes(kCompactTimesLds, 8);
+  static_assert(kTimesLds >= kCompactSmallLds, "either form of the state");
+  auto go = [&](auto width) -> hipError_t {
+    constexpr int NT = decltype(width)::value;
+    hipLaunchKernelGGL((compact_kernel<0, NT>), dim3(1), dim3(NT), 3 * compact_array_bytes(G, 8) + 2 * compact_array_bytes(G, 4), st, G, k, M,
+                       max_walks, t, p, a, (char *)ws, n_out, block_end, t_out, p_out, a_out, status);
+    return hipGetLastError();
+  };
+  if (G <= kCompactSmall) return G <= 256 ? go(std::integral_constant<int, 256>()) : go(std::integral_constant<int, 1024>());
+  // Walks with launches of their own: as long as a walk, which leaves some 35 of a hundred groups, is expected to leave more than
+  // k and there are more groups than one workgroup takes as fast.
+  int walks = 0;
+  for (int left = G; left > kCompactLaunch && left * 2 / 5 > k && walks < kCompactMostWalks && (max_walks <= 0 || walks < max_walks); ++walks)
+    left = left * 9 / 25;
+  const bool times_lds = G <= kCompactTimesLds;
+  static std::atomic<uint64_t> asked[2];
+  if (walks == 0) {
+    if (times_lds) {
+      const hipError_t e = allow_lds(asked[0], (const void *)compact_kernel<1, 1024>, (int)kTimesLds);
+      if (e != hipSuccess) return e;
+      hipLaunchKernelGGL((compact_kernel<1, 1024>), dim3(1), dim3(1024), compact_array_bytes(G, 8), st, G, k, M, max_walks, t, p, a,
+                         (char *)ws, n_out, block_end, t_out, p_out, a_out, status);
+    } else {
+      hipLaunchKernelGGL((compact_kernel<2, 1024>), dim3(1), dim3(1024), 0, st, G, k, M, max_walks, t, p, a, (char *)ws, n_out, block_end,
+                         t_out, p_out, a_out, status);
+    }
+    return hipGetLastError();
+  }
+  const CompactState state = compact_state(ws, G);
+  constexpr int kWaves = kCompactWalkNT / 64, kStretch = kCompactWalkNT * kCompactSumsPer;
+  const int blocks = ((G + kCompactChunk - 1) / kCompactChunk + kWaves - 1) / kWaves, stretches = (G + kStretch - 1) / kStretch;
+  hipLaunchKernelGGL(compact_first_kernel, dim3(3 * stretches + blocks), dim3(kCompactWalkNT), 0, st, G, M, t, p, a, state);
+  for (int w = 2; w <= walks; ++w)
+    hipLaunchKernelGGL(compact_walk_kernel, dim3(blocks), dim3(kCompactWalkNT), 0, st, G, k, M, w, state);
+  if (times_lds) {
+    const hipError_t e = allow_lds(asked[1], (const void *)compact_resume_kernel<1>, (int)kTimesLds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(compact_resume_kernel<1>, dim3(1), dim3(1024), std::max(compact_array_bytes(G, 8), kCompactSmallLds), st, G, k, M,
+                       max_walks, walks, (char *)ws, state, n_out, block_end, t_out, p_out, a_out, status);
+  } else {
+    hipLaunchKernelGGL(compact_resume_kernel<2>, dim3(1), dim3(1024), kCompactSmallLds, st, G, k, M, max_walks, walks, (char *)ws, state,
+                       n_out, block_end, t_out, p_out, a_out, status);
+  }
+  return hipGetLastError();
 }
 
 }  // namespace rannc

@@ -77,6 +77,52 @@ def test_compact_state_layouts(G, order):
             assert np.array_equal(have.cpu().numpy()[:n], want)
 
 
+# walks in windows of 63 groups, and the walks of long chains that have a launch of their own: chains on which every
+# window is large enough (random), too small in a few places (runs of ascending and descending times among random
+# ones), and everywhere (a zigzag that rises slowly: each turn waits for the one two places before it)
+@pytest.mark.parametrize("G", [17, 62, 63, 64, 80, 96, 700, 1600, 1601, 2048, 5003, 16384, 16385, 30001])
+@pytest.mark.parametrize("order", ["random", "runs", "zigzag"])
+def test_compact_windows(G, order):
+    if G > 16384 and order == "zigzag":
+        G = 16900
+    g = np.random.default_rng(7 * G)
+    t = g.integers(0, 1 << 30, G)
+    if order == "runs":
+        for at in g.integers(0, G, max(1, G // 2000)):
+            n = min(int(g.integers(30, 200)), G - at)
+            t[at:at + n] = (np.arange(n) if g.integers(2) else n - np.arange(n)) * 1000
+    elif order == "zigzag":
+        t = np.arange(G) * 5 + np.where(np.arange(G) % 2, 7, 0)
+    p, a = g.integers(0, 50, G), g.integers(0, 50, G)
+    for k, M, walks in ((max(1, G // 40), 10**9, 0), (5, 10**9, 1), (5, 10**9, 2), (max(1, (2 * G) // 5), 10**9, 0), (8, 150, 0),
+                        (3, 0, 0)):
+        rc, n, st, d_end, d_out = gpu_compact(t, p, a, k, M, walks)
+        assert rc == B.OK and st == B.PROBLEM_OK
+        end, tt, pp, aa = oracle.compact(t, p, a, k, M, max_passes=walks)
+        assert n == len(end) and np.array_equal(d_end.cpu().numpy()[:n], end), (k, M, walks)
+        for have, want in zip(d_out, (tt, pp, aa)):
+            assert np.array_equal(have.cpu().numpy()[:n], want)
+
+
+@pytest.mark.parametrize("G", [1700, 9000])
+def test_compact_refuses_long_chains_that_overflow(G):
+    """The sums of a long chain are made by many workgroups: each kind of input, at either end of the chain."""
+    for at in (0, G // 2, G - 1):
+        for which, value, want in ((0, -1, B.PROBLEM_NEGATIVE_INPUT), (1, -5, B.PROBLEM_NEGATIVE_INPUT), (2, -1, B.PROBLEM_NEGATIVE_INPUT),
+                                   (0, 1 << 62, B.PROBLEM_SUM_OVERFLOW), (1, (1 << 62) - 1000, B.PROBLEM_SUM_OVERFLOW),
+                                   (2, (1 << 62) - 1, B.PROBLEM_SUM_OVERFLOW)):
+            arrays = [np.full(G, 3) for _ in range(3)]
+            arrays[which][at] = value
+            rc, n, st, *_ = gpu_compact(*arrays, 20, 10**9)
+            assert rc == B.OK and st == want and n == 0, (at, which, value)
+    arrays = [np.full(G, 3) for _ in range(3)]
+    arrays[1][0], arrays[2][G - 1] = 1 << 61, 1 << 61   # neither alone
+    assert gpu_compact(*arrays, 20, 10**9)[2] == B.PROBLEM_SUM_OVERFLOW
+    arrays[2][G - 1] = (1 << 61) - 6 * G
+    rc, n, st, *_ = gpu_compact(*arrays, 20, (1 << 62) - 1)
+    assert rc == B.OK and st == B.PROBLEM_OK and n == 20
+
+
 def test_compact_status_and_rejections():
     t, p, a = np.array([3, 1, 2]), np.array([1, 1, 1]), np.array([1, 1, 1])
     neg = t.copy(); neg[1] = -1
