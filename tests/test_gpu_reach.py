@@ -52,6 +52,21 @@ def test_open_plans_and_ties(kind, Q):
     _check(probs)
 
 
+@pytest.mark.parametrize("N,D,S", [(40, 7, 6), (130, 17, 9), (251, 24, 15), (400, 64, 5), (1024, 40, 9), (2000, 33, 4)])
+@pytest.mark.parametrize("grow", [1.0, 3.0])
+@pytest.mark.parametrize("share", [1.01, 1.15, 1.4])
+def test_many_open_cells_and_full_stages(N, D, S, grow, share):
+    """Bytes that grow along the chain, so that a few blocks at its end take most stages (the bound leaves many cells, few of them
+    reached), and stages nearly full, so that the stage limit binds; also as one of many searches."""
+    pr = _search(9, N, D, S, share=share)
+    weight = np.linspace(0.05, 1.0, N) ** grow
+    pr["param_bytes"] = (pr["param_bytes"] * weight * 1000).astype(np.int64) + 1
+    pr["mem_capacity"] = int((pr["param_bytes"].sum() + pr["act_bytes"].sum()) / min(S, D, N) * share)
+    _check([pr])
+    if N <= 251:
+        _check([_search(q, 30, 5, 4) for q in range(66)] + [pr])
+
+
 def test_beyond_the_exact_range_the_tables_decide():
     """Bytes of 2^46 and more in all, and times of 2^44 ns."""
     big = _search(3, 90, 12, 6, scale=1 << 31)
