@@ -1058,11 +1058,13 @@ extern "C++" template <typename Shape> bool room_for_inputs(const rannc_dp_t *h,
   return true;
 }
 
-// Whether a batch can be answered without its tables: min-max searches without send times that the kernel holds.
+// Whether a batch can be answered without its tables: searches that the kernels hold.
 bool reach_applies(const rannc_dp_t *h, const rannc_dp_batch_t *b, size_t *saved_at) {
-  if (!library_chooses(h) || split_of(&h->lim) || b->cut_bytes || !b->time_ns || !b->param_bytes || !b->act_bytes || b->time_bwd_ns) return false;
+  if (!library_chooses(h) || !b->time_ns || !b->param_bytes || !b->act_bytes || split_of(&h->lim) != (b->time_bwd_ns != nullptr)) return false;
+  const bool bound = b->time_bwd_ns || b->cut_bytes;
+  if (bound && b->n_problems > kPollMaxProblems) return false;
   for (int q = 0; q < b->n_problems; ++q)
-    if (b->n_blocks[q] > rannc::kReachMaxBlocks) return false;
+    if (b->n_blocks[q] > (bound ? rannc::kBoundMaxBlocks : rannc::kReachMaxBlocks)) return false;
   return room_for_inputs(h, b->n_problems, [&](int q) { return SearchShape{b->n_blocks[q], b->n_devices[q], b->max_stages[q]}; },
                          (size_t)(b->block_offset[b->n_problems] - b->block_offset[0]), saved_at);
 }
@@ -1083,20 +1085,21 @@ int reach_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, hipStream_t st, int32_t
   sh.nprob = Q;
   for (int q = 0; q < Q; ++q) {
     const int N = b->n_blocks[q], D = b->n_devices[q], S = std::min(b->max_stages[q], std::min(N, D));
-    in[q] = {N, D, S, b->n_microbatches[q], b->mem_capacity[q], b->block_offset[q]};
+    in[q] = {N, D, S, b->n_microbatches[q], b->mem_capacity[q], b->block_offset[q], b->cut_bytes ? b->bandwidth_bytes_per_us[q] : 1};
     sh.max_N = std::max(sh.max_N, N);
     sh.max_D = std::max(sh.max_D, D);
     sh.max_S_eff = std::max(sh.max_S_eff, S);
   }
   rannc::ReachArgs args = {};
-  args.t = b->time_ns; args.p = b->param_bytes; args.a = b->act_bytes;
+  args.t = b->time_ns; args.p = b->param_bytes; args.a = b->act_bytes; args.o = b->cut_bytes; args.tb = b->time_bwd_ns;
   args.save = (int64_t *)(h->ws + saved_at);
   args.first = b->block_offset[0];
   args.blocks = b->block_offset[Q] - args.first;
   args.time_limit = h->lim.max_total_time_ns;
   args.plan_stride = plan_stride;
   args.results = r;
-  if (rannc::launch_reach((const rannc::ReachIn *)h->staging_dev[slot], Q == 1 ? in : nullptr, Q, sh, args, st) != hipSuccess) {
+  const auto launch = args.o || args.tb ? rannc::launch_bound : rannc::launch_reach;
+  if (launch((const rannc::ReachIn *)h->staging_dev[slot], Q == 1 ? in : nullptr, Q, sh, args, st) != hipSuccess) {
     (void)hipGetLastError();
     return RANNC_DP_HIP_ERROR;
   }
@@ -1110,11 +1113,13 @@ int reach_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, hipStream_t st, int32_t
     h->kept.M.assign(b->mem_capacity, b->mem_capacity + Q);
     h->kept.off.resize(Q + 1);
     for (int q = 0; q <= Q; ++q) h->kept.off[q] = b->block_offset[q] - b->block_offset[0];
+    if (b->cut_bytes) h->kept.bw.assign(b->bandwidth_bytes_per_us, b->bandwidth_bytes_per_us + Q);
   } catch (...) {
     return RANNC_DP_NO_HOST_MEMORY;
   }
   h->kept.sample.clear();
-  h->kept.comm = h->kept.split = false;
+  h->kept.comm = b->cut_bytes != nullptr;
+  h->kept.split = b->time_bwd_ns != nullptr;
   h->kept.total_bound = 0;
   h->kept.saved_at = saved_at;
   return RANNC_DP_OK;

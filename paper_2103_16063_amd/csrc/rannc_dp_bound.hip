@@ -1,0 +1,184 @@
+// gfx950 kernel that answers searches with send times, and with forward and backward maxima apart, without their value
+// tables: optimum, fewest stages and the canonical plan (rannc_dp_solve_to_host), one workgroup to a search.  The tables
+// themselves are made by the kernels in rannc_dp_kernels.hip and rannc_dp_split.hip, when they are asked for.
+//
+// The levels of rannc_dp_reach.h, among the cells that a bound leaves.  The bound comes from the plan that is best for the sums of all
+// times, without what is sent, priced with send times and the two maxima: for one objective it is an upper bound by
+// itself, with the two apart (Algorithm 1 as printed may miss that plan) the levels say whether it is.
+//
+// Bound by latency, as rannc_dp_reach.hip: of a call's 43 us at 256 blocks and 32 devices the search over the sums
+// takes 12, the windows of the bound 10, five levels 9.  Per call, tables / this kernel: 256 blocks at 32 devices, maxima apart,
+// 202 / 43 us; with send times 165 at 24 86 / 44, 531 at 8 81 / 19, 251 at 24 with bytes that grow along the chain 100 / 95;
+// both 191 at 27 148 / 39; 87 at 7 in 4 stages with send times 38 / 40.
+#include "rannc_dp_reach.h"
+
+namespace rannc {
+
+constexpr int kBoundThreads = 1024, kBoundWaves = kBoundThreads / 64;
+constexpr int kBoundCells = 3584;    // of the windows
+constexpr int kBoundSources = 768;   // of a level
+constexpr int kBoundRecords = 3072;  // of all levels
+
+template <bool SPLIT, bool COMM>
+__global__ __launch_bounds__(kBoundThreads) void bound_kernel(const ReachIn *src, const ReachIn one, const int use_one, const ReachArgs args,
+                                                              const ReachDims dims) {
+  constexpr int NT = kBoundThreads, WAVES = kBoundWaves;
+  extern __shared__ __align__(16) char lds[];
+  constexpr int W = (int)sizeof(ReachIn) / 4;
+  __shared__ __align__(8) uint32_t s_in[W];
+  __shared__ int s_flags, s_status;
+  __shared__ uint64_t s_total[4];
+  __shared__ unsigned long long s_cut;
+  __shared__ ReachShared<WAVES> sh;
+  const int tid = threadIdx.x, lane = tid & 63, q = blockIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  ReachIn in = one;
+  if (tid < 3) sh.mask[tid] = 0u;
+  if (tid == 0) { s_flags = 0; s_status = RANNC_DP_PROBLEM_OK; s_cut = 0ull; }
+  if (tid < 4) s_total[tid] = 0ull;
+  if (wave == 3) sh.inverse[lane] = 1.0 / (double)(lane + 1);
+  if (!use_one && tid < W) s_in[tid] = ((const uint32_t *)(src + q))[tid];
+  __syncthreads();
+  if (!use_one) {
+    const uint32_t mine = s_in[lane % W];
+    union { ReachIn p; uint32_t u[W]; } x;
+#pragma unroll
+    for (int k = 0; k < W; ++k) x.u[k] = lane_bcast(mine, k);
+    in = x.p;
+  }
+  const int N = in.N, D = in.D;
+  const int entries = dims.N + 2 + kReachPad, shape = dims.S * dims.D;
+  double *const sT = (double *)lds + kReachPad, *const sP = sT + entries, *const sA = sP + entries;
+  double *const sB = sA + entries, *const sC = sB + (SPLIT ? entries : 0);
+  char *const rest = (char *)(sC + (COMM ? entries : 0) - kReachPad);
+  // what the search over T needs, and then the levels
+  double *const value = (double *)rest;
+  uint16_t *const reach = (uint16_t *)(value + dims.cells), *const first_of = reach + shape, *const base = first_of + shape;
+  const LevelSpace space = {dims.level_cells, dims.level_sources, dims.level_records, rest};
+
+  // ---- sums ----
+  {
+    int flags = 0;
+    uint32_t high = 0;
+    const int64_t from = in.first, to = in.first - args.first;
+    if (wave < 3 || (SPLIT && wave == 3)) {
+      const int64_t RANNC_GLOBAL *const x = gptr(wave == 0 ? args.t : wave == 1 ? args.p : wave == 2 ? args.a : args.tb) + from;
+      int64_t RANNC_GLOBAL *const save = gptr(args.save) + (int64_t)(wave < 3 ? wave : 4) * args.blocks + to;
+      double *const s = wave == 0 ? sT : wave == 1 ? sP : wave == 2 ? sA : sB;
+      uint64_t total;
+      if (N <= 64) total = reach_sums<1>(x, save, s, N, flags, high);
+      else if (N <= 192) total = reach_sums<3>(x, save, s, N, flags, high);
+      else if (N <= 576) total = reach_sums<9>(x, save, s, N, flags, high);
+      else total = reach_sums<17>(x, save, s, N, flags, high);
+      if (high >> 30) flags |= 2;
+      if (lane < kReachPad) s[-1 - lane] = wave == 0 ? -__builtin_inf() : 0.0;
+      if (lane == 0) {
+        s[N + 1] = wave == 0 ? __builtin_inf() : 0.0;
+        s_total[wave] = total;
+      }
+    } else if (COMM && wave >= 4) {
+      unsigned long long most = 0ull;
+      for (int k = tid - 256; k < N; k += NT - 256) {
+        const int64_t o = args.o[from + k];
+        args.save[3 * args.blocks + to + k] = o;
+        const uint64_t c = cut_time(o, in.bw, flags);
+        sC[k + 1] = k + 1 < N ? (double)c : 0.0;
+        if (k + 1 < N && c > most) most = c;
+      }
+      if (tid == 256) sC[0] = 0.0;
+      if (most) atomicMax(&s_cut, most);
+    }
+    if (flags) atomicOr(&s_flags, flags);
+  }
+  __syncthreads();
+  const uint64_t total = lane_bcast((uint64_t)(s_total[0] + (SPLIT ? s_total[3] : 0ull)), 0);
+  int status = RANNC_DP_PROBLEM_OK;
+  if (s_flags & 1) status = RANNC_DP_PROBLEM_NEGATIVE_INPUT;
+  else if (s_flags & 2) status = RANNC_DP_PROBLEM_SUM_OVERFLOW;
+  else if (total + s_cut > (uint64_t)args.time_limit) status = RANNC_DP_PROBLEM_TIME_TOO_LARGE;
+  else if (total + s_cut >= (uint64_t)kReachMaxTime || s_total[1] >= (uint64_t)kReachMaxBytes || s_total[2] >= (uint64_t)kReachMaxBytes)
+    status = kReachUndecided;
+
+  uint64_t opt = (uint64_t)INT64_MAX, window = 0;
+  int n_stages = 0;
+  if (status == RANNC_DP_PROBLEM_OK) {
+    if (SPLIT) {
+      for (int e = tid; e <= N; e += NT) sT[e] += sB[e];
+      __syncthreads();
+    }
+    const double M = (double)min(in.M, (int64_t)(2 * kReachMaxBytes));  // (as good as unlimited)
+    reach_search<WAVES, true>(in, M, total, sT, sP, sA, value, reach, first_of, base, dims, space, sh, opt, n_stages, status, window);
+    if (wave == 0 && status != RANNC_DP_PROBLEM_OK && lane == 0) s_status = status;
+    __syncthreads();
+    status = s_status;
+    const LevelSums all = {sT, sP, sA, sB, sC};
+    auto times = [&](int i, int j, int r, double &f, double &b) { level_times<SPLIT, COMM>(all, sh.inverse, i, j, r, f, b); };
+    if (status == RANNC_DP_PROBLEM_OK && n_stages == 1) {  // one stage sends nothing, and shares everything evenly: no plan is better
+      double f, b;
+      times(0, N, D, f, b);
+      opt = (uint64_t)(f + b);
+    } else if (status == RANNC_DP_PROBLEM_OK && n_stages != 0) {
+      // ---- U: that plan's value here; or where many cells were left, so that it has not been looked for, the bound itself ----
+      const double least = (double)opt;  // (no value is smaller, or that bound)
+      const bool asked = n_stages < 0;
+      double U = least;
+      if (!asked) {
+        double f = 0.0, b = 0.0;
+        if (lane < n_stages) times(lane ? sh.plan.end[lane - 1] : 0, sh.plan.end[lane], sh.plan.replicas[lane], f, b);
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          f = dmax(f, __shfl_xor(f, o));
+          b = dmax(b, __shfl_xor(b, o));
+        }
+        U = f + b;
+      }
+      n_stages = 0;
+      opt = (uint64_t)INT64_MAX;
+      status = kReachUndecided;
+#pragma unroll 1
+      for (int attempt = 0; attempt < 4; ++attempt) {
+        double v = 0.0;
+        int s = 0;
+        const bool kept = U <= (double)window;
+        const LevelState state = reach_levels<WAVES, SPLIT, COMM>(all, N, D, M, U, kept, in.S, space, sh, v, s);
+        if (state == kLevelsFound) {
+          opt = (uint64_t)v;
+          n_stages = s;
+          status = RANNC_DP_PROBLEM_OK;
+        }
+        if (!kept) window = (uint64_t)U;
+        // (too many cells are too many at larger bounds; at a smaller one they may do)
+        if (state == kLevelsFound || (state == kLevelsOpen && attempt)) break;
+        U = state == kLevelsOpen ? least + floor((U - least) * 0.25) : asked && attempt == 0 ? U + floor(U * 0.015625) + 1.0 : least + (U - least + 1.0) * 2.0;
+        if (state == kLevelsOpen) window = 0;
+      }
+    }
+  }
+  reach_results(in, args, q, sh.plan, opt, n_stages, status);
+}
+
+hipError_t launch_bound(const ReachIn *src, const ReachIn *host_one, int Q, const LaunchShape &sh, const ReachArgs &args, hipStream_t st) {
+  if (sh.max_N > kBoundMaxBlocks) return hipErrorInvalidValue;
+  const bool split = args.tb != nullptr, comm = args.o != nullptr;
+  const int cells = std::min(kBoundCells, (sh.max_N * sh.max_D + 15) / 8 * 8);  // (a multiple of 8: aligned arrays)
+  // (with send times alone the tables are fast where few stages fit)
+  const ReachDims dims = {sh.max_N, sh.max_D, sh.max_S_eff, 1024, cells, kBoundSources, kBoundRecords, 0, split ? 32768 : 8192};
+  const size_t sums = (size_t)(dims.N + 2 + kReachPad) * 8 * (3 + (split ? 1 : 0) + (comm ? 1 : 0));
+  const size_t search = (size_t)dims.cells * 8 + (size_t)dims.S * dims.D * 6;
+  const size_t levels = level_bytes(cells, kBoundSources, kBoundRecords, split);
+  const ReachIn one = host_one ? *host_one : ReachIn{};
+  auto go = [&](auto apart, auto sends) -> hipError_t {
+    constexpr bool X = decltype(apart)::value, Y = decltype(sends)::value;
+    static std::atomic<uint64_t> asked{0};
+    const hipError_t e = allow_lds(asked, (const void *)bound_kernel<X, Y>, 148 * 1024);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((bound_kernel<X, Y>), dim3(Q), dim3(kBoundThreads), sums + std::max(search, levels), st, src, one, host_one ? 1 : 0, args, dims);
+    return hipGetLastError();
+  };
+  if (split && comm) return go(std::true_type(), std::true_type());
+  if (split) return go(std::true_type(), std::false_type());
+  if (comm) return go(std::false_type(), std::true_type());
+  return hipErrorInvalidValue;
+}
+
+}  // namespace rannc

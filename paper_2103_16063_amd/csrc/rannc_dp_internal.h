@@ -228,9 +228,10 @@ struct ReachIn {
   int32_t N, D, S, MB;
   int64_t M;
   int64_t first;  // index of its first block in the input arrays
+  int64_t bw;     // bytes per microsecond between stages, where the batch has send times
 };
 struct ReachArgs {
-  const int64_t *t, *p, *a;  // DEVICE
+  const int64_t *t, *p, *a, *o, *tb;  // DEVICE; o, tb: of launch_bound, or null
   int64_t *save;
   int64_t blocks, first;  // of the batch: entries of a saved array, index of the first block
   int64_t time_limit;
@@ -239,6 +240,9 @@ struct ReachArgs {
 };
 // src: the descriptors in memory the device can read (pinned); host_one: of a launch over one search, by value, or null
 hipError_t launch_reach(const ReachIn *src, const ReachIn *host_one, int Q, const LaunchShape &sh, const ReachArgs &args, hipStream_t st);
+// The same for searches with send times, or with forward and backward maxima apart (rannc_dp_bound.hip); five arrays are saved.
+constexpr int kBoundMaxBlocks = 1024;  // (a row is ten bits of a key)
+hipError_t launch_bound(const ReachIn *src, const ReachIn *host_one, int Q, const LaunchShape &sh, const ReachArgs &args, hipStream_t st);
 // The outer driver's searches, each the smallest stage count of lo..hi with a plan of exactly so many stages on D devices,
 // and that plan (rannc_dp_form.hip): one workgroup each, results in pinned host memory.
 constexpr int kFormMaxBlocks = 1024, kFormMaxSpare = 8;  // spare: devices of a node
