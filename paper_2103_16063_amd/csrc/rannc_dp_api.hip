@@ -1063,8 +1063,17 @@ bool reach_applies(const rannc_dp_t *h, const rannc_dp_batch_t *b, size_t *saved
   if (!library_chooses(h) || !b->time_ns || !b->param_bytes || !b->act_bytes || split_of(&h->lim) != (b->time_bwd_ns != nullptr)) return false;
   const bool bound = b->time_bwd_ns || b->cut_bytes;
   if (bound && b->n_problems > kPollMaxProblems) return false;
-  for (int q = 0; q < b->n_problems; ++q)
-    if (b->n_blocks[q] > (bound ? rannc::kBoundMaxBlocks : rannc::kReachMaxBlocks)) return false;
+  int longest = 0, widest = 0;
+  for (int q = 0; q < b->n_problems; ++q) {
+    longest = std::max(longest, b->n_blocks[q]);
+    widest = std::max(widest, b->n_devices[q] * std::min(b->max_stages[q], b->n_devices[q]));
+  }
+  if (longest > (bound ? rannc::kBoundMaxBlocks : rannc::kReachMaxBlocks)) return false;
+  // Every stage boundary sends, so where memory makes many of them the plan that the bound is taken from is a loose one, and the
+  // levels take longer than the tables: 130 blocks at 12 devices in at most 12 stages 77 us with tables, 148 without; 400 at 24 in
+  // 12 91 and 85, at 64 125 and 651.  With few devices or stages they do not: 260 at 6 in 6 53 and 45, 1000 at 12 in 4 62 and 41.
+  // Up to 128 blocks the tables are one launch with one objective: 12 blocks at 6 devices 23 us, without tables 30; 130 at 6 in 6 49 and 55.
+  if (b->cut_bytes && (widest > 64 || (!b->time_bwd_ns && longest <= 160))) return false;
   return room_for_inputs(h, b->n_problems, [&](int q) { return SearchShape{b->n_blocks[q], b->n_devices[q], b->max_stages[q]}; },
                          (size_t)(b->block_offset[b->n_problems] - b->block_offset[0]), saved_at);
 }

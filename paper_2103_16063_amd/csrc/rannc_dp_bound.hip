@@ -8,16 +8,15 @@
 //
 // Bound by latency, as rannc_dp_reach.hip: of a call's 43 us at 256 blocks and 32 devices the search over the sums
 // takes 12, the windows of the bound 10, five levels 9.  Per call, tables / this kernel: 256 blocks at 32 devices, maxima apart,
-// 202 / 43 us; with send times 165 at 24 86 / 44, 531 at 8 81 / 19, 251 at 24 with bytes that grow along the chain 100 / 95;
-// both 191 at 27 148 / 39; 87 at 7 in 4 stages with send times 38 / 40.
+// 202 / 43 us; with send times 531 at 8 81 / 19, 1000 at 6 in at most 12 stages 67 / 37; both 362 at 8 74 / 19.
 #include "rannc_dp_reach.h"
 
 namespace rannc {
 
 constexpr int kBoundThreads = 1024, kBoundWaves = kBoundThreads / 64;
 constexpr int kBoundCells = 3584;    // of the windows
-constexpr int kBoundSources = 768;   // of a level
-constexpr int kBoundRecords = 3072;  // of all levels
+constexpr int kBoundSources = 384;   // of a level
+constexpr int kBoundRecords = 2048;  // of all levels
 
 template <bool SPLIT, bool COMM>
 __global__ __launch_bounds__(kBoundThreads) void bound_kernel(const ReachIn *src, const ReachIn one, const int use_one, const ReachArgs args,
@@ -99,6 +98,11 @@ __global__ __launch_bounds__(kBoundThreads) void bound_kernel(const ReachIn *src
   else if (total + s_cut >= (uint64_t)kReachMaxTime || s_total[1] >= (uint64_t)kReachMaxBytes || s_total[2] >= (uint64_t)kReachMaxBytes)
     status = kReachUndecided;
 
+  // Where memory makes many stages of a long chain on many devices, more cells are left than the tables take time for: 1000
+  // blocks at 64 devices, memory makes 13 stages, 1176 us with tables, 1732 without; 500 616 and 981.
+  const double forced = (sP[N] + sA[N] / (double)D) / fmax((double)in.M, 1.0);
+  if (status == RANNC_DP_PROBLEM_OK && N * D > 24576 && forced > 8.0 && forced <= 1.01 * (double)in.S) status = kReachUndecided;
+
   uint64_t opt = (uint64_t)INT64_MAX, window = 0;
   int n_stages = 0;
   if (status == RANNC_DP_PROBLEM_OK) {
@@ -161,8 +165,7 @@ hipError_t launch_bound(const ReachIn *src, const ReachIn *host_one, int Q, cons
   if (sh.max_N > kBoundMaxBlocks) return hipErrorInvalidValue;
   const bool split = args.tb != nullptr, comm = args.o != nullptr;
   const int cells = std::min(kBoundCells, (sh.max_N * sh.max_D + 15) / 8 * 8);  // (a multiple of 8: aligned arrays)
-  // (with send times alone the tables are fast where few stages fit)
-  const ReachDims dims = {sh.max_N, sh.max_D, sh.max_S_eff, 1024, cells, kBoundSources, kBoundRecords, 0, split ? 32768 : 8192};
+  const ReachDims dims = {sh.max_N, sh.max_D, sh.max_S_eff, 1024, cells, kBoundSources, kBoundRecords, 0, 32768};
   const size_t sums = (size_t)(dims.N + 2 + kReachPad) * 8 * (3 + (split ? 1 : 0) + (comm ? 1 : 0));
   const size_t search = (size_t)dims.cells * 8 + (size_t)dims.S * dims.D * 6;
   const size_t levels = level_bytes(cells, kBoundSources, kBoundRecords, split);

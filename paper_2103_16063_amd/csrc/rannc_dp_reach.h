@@ -730,8 +730,8 @@ __device__ __forceinline__ void reach_search(const ReachIn &in, const double M, 
     done = true;
   } else if (const double full = (sP[N] + sA[N] / (double)D) / ((double)in.S * M); !dims.patient && N * D > dims.tight && full > 0.75 && full <= 1.01) {
     // Stages nearly full of bytes, so that the best plan of any number of stages takes more than there are, and at the bound that
-    // they allow many cells are left: 1024 blocks at 64 devices, 9 stages 85 % full, tables 101 us, here 426; 300 at 32 with send
-    // times, 4 stages 78 % full, 52 and 84.  (Fuller than full: there is no plan, which is found soon.)
+    // they allow many cells are left: 1024 blocks at 64 devices, 9 stages 85 % full, tables 101 us, here 426.
+    // (Fuller than full: there is no plan, which is found soon.)
     status = kReachUndecided;
     return;
   } else {
