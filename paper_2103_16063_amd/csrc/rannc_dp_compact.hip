@@ -600,11 +600,12 @@ __device__ __forceinline__ void compact_body(
   }
   }
 
+  bool windows = true;  // none was too small so far (an order along the chain is still one in the next walk)
   for (; n > k && (max_walks <= 0 || walk <= max_walks); ++walk) {  // (n: groups as they stand)
     const int nw = (n + 31) >> 5;  // words of the bit maps that hold groups: 1 .. nw
     if (tid == 0) { s_left = 0; s_open = 0; }
     bool open = true;
-    if (n <= kCompactWindows) {
+    if (windows && n <= kCompactWindows) {
       // ---- the walk, in windows: 32 groups to a wave and turn ----
       if (tid == 0) { head[0] = 0u; head[nw + 1] = 0u; head[nw + 2] = 0u; }
       __syncthreads();
@@ -624,6 +625,7 @@ __device__ __forceinline__ void compact_body(
       }
       __syncthreads();
       open = s_open != 0;
+      windows = !open;
       __syncthreads();
       if (tid == 0 && open) s_left = 0;
     }

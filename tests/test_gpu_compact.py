@@ -179,3 +179,35 @@ def test_compaction_feeds_the_search_on_the_device():
     o = oracle.solve(blocks, n_threads=0)
     assert int(d_opt.item()) == o["opt"] and int(d_ns.item()) == o["n_stages"] and o["n_stages"] >= 1
     assert np.array_equal(d_se.cpu().numpy()[0], o["stage_end"]) and np.array_equal(d_rp.cpu().numpy()[0], o["replicas"])
+
+
+def test_long_chain_recorded_and_replayed():
+    """The launches of a long chain in a captured graph, replayed on other inputs (whose windows may be too small) with eager work
+    in between."""
+    G, k = 5003, 40
+    d_in = [torch.zeros(G, dtype=torch.int64, device=DEV) for _ in range(3)]
+    nbytes = B.rannc_dp_compact_workspace_bytes(G)
+    ws = torch.empty(nbytes, dtype=torch.uint8, device=DEV)
+    d_n, d_st = (torch.full((1,), -5, dtype=torch.int32, device=DEV) for _ in range(2))
+    d_end = torch.full((G,), -5, dtype=torch.int32, device=DEV)
+    d_out = [torch.full((G,), -5, dtype=torch.int64, device=DEV) for _ in range(3)]
+    M = 10**9
+    graph, stream = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=stream):
+        assert B.rannc_dp_compact(torch.cuda.current_stream().cuda_stream, G, k, 0, M, *d_in, ws, nbytes, d_n, d_end, *d_out, d_st) == B.OK
+    for seed in range(4):
+        g = np.random.default_rng(seed)
+        t, p, a = g.integers(0, 1 << 30, G), g.integers(0, 50, G), g.integers(0, 50, G)
+        if seed == 2:
+            t[1000:1200] = np.arange(200) * 1000
+        for x, y in zip(d_in, (t, p, a)):
+            x.copy_(torch.from_numpy(y))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        end, tt, pp, aa = oracle.compact(t, p, a, k, M)
+        n = int(d_n.item())
+        assert int(d_st.item()) == B.PROBLEM_OK and n == len(end) and np.array_equal(d_end.cpu().numpy()[:n], end)
+        for have, want in zip(d_out, (tt, pp, aa)):
+            assert np.array_equal(have.cpu().numpy()[:n], want)
