@@ -206,7 +206,8 @@ RANNC_DP_API int rannc_dp_traceback(rannc_dp_t *h, void *hip_stream, int32_t pla
  * up to 64 of them of up to 1024 blocks with RANNC_DP_FLAG_SPLIT_OBJECTIVE or (few devices or stages) a communication
  * term, on a handle with algo AUTO and no tuning fields, is normally answered without the tables of rannc_dp_solve; the
  * first rannc_dp_traceback, _traceback_at, _level_values or _read_table behind it makes
- * them, from copies of the inputs kept in the workspace, and waits for that.  Allocates nothing but host memory for
+ * them, from copies of the inputs kept in the workspace, and waits for that.  Once a call on the handle has been recorded
+ * into a graph every call makes its tables: replays find, or write, those they did when all calls made them.  Allocates nothing but host memory for
  * copies of the batch's HOST members, except where plan_stride is beyond the handle's longest plan (max_stages, at
  * most 64): then pinned host memory, at the first such call and at any later one that needs more, freed by destroy.
  * Errors as rannc_dp_solve and rannc_dp_traceback; INVALID_ARG if results_bytes is too small. */

@@ -217,6 +217,9 @@ struct rannc_dp {
   // asked for.  Its inputs are at ws + saved_at (times, persistent, transient bytes, bytes per cut, backward times), or, of
   // the outer driver, they come from its own per sample (`sample`, the same arrays; search q times samples[q]).
   bool tabled;
+  // A call on the handle has been recorded into a graph, whose replays read the tables of whatever call came before
+  // them, or write them: from then on every call makes its tables.
+  bool recorded;
   struct {
     std::vector<int32_t> N, D, S, MB;
     std::vector<int64_t> M, off, bw, sample, samples;
@@ -289,6 +292,7 @@ int rannc_dp_create(const rannc_dp_limits_t *l, void *d_workspace, size_t worksp
   h->solved = false;
   h->unchosen = false;
   h->tabled = false;
+  h->recorded = false;
   h->Q = 0;
   h->timing = false;
   h->ev_valid = false;
@@ -881,16 +885,26 @@ static void kept_batch(const rannc_dp_t *h, rannc_dp_batch_t *b) {
   if (h->kept.split) b->time_bwd_ns = b->act_bytes + 2 * blocks;
 }
 
+// Whether the caller's stream is being recorded into a graph; the handle remembers that it was.
+static bool recording(rannc_dp_t *h, hipStream_t st) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &status) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  if (status != hipStreamCaptureStatusNone) h->recorded = true;
+  return status != hipStreamCaptureStatusNone;
+}
+
 // Makes the tables of the last batch if it was answered without them.  Behind it they are there for work on any stream, as
 // they are behind a call that returns with its results.  Where the caller's stream is being recorded they are made on a
 // stream of the handle, at once: the recording holds what it would hold behind a call that had made them.
 static int ensure_tables(rannc_dp_t *h, void *hip_stream) {
-  if (!h->solved || h->tabled) return RANNC_DP_OK;
   hipStream_t st = (hipStream_t)hip_stream;
-  hipStreamCaptureStatus recording = hipStreamCaptureStatusNone;
+  const bool aside = recording(h, st);
+  if (!h->solved || h->tabled) return RANNC_DP_OK;
   hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-  bool ok = hipStreamIsCapturing(st, &recording) == hipSuccess;
-  const bool aside = ok && recording != hipStreamCaptureStatusNone;
+  bool ok = true;
   if (aside) {
     st = h->aux[0];
     ok = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
@@ -932,6 +946,7 @@ static int ensure_tables(rannc_dp_t *h, void *hip_stream) {
 int rannc_dp_solve(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream, int64_t *d_opt,
                    int32_t *d_n_stages, int64_t *d_est_iter_ns, int32_t *d_status) {
   if (!h || !d_opt || !d_n_stages) return RANNC_DP_INVALID_ARG;
+  (void)recording(h, (hipStream_t)hip_stream);
   return solve_impl(h, b, hip_stream, d_opt, d_n_stages, d_est_iter_ns, d_status, nullptr);
 }
 
@@ -1030,9 +1045,9 @@ int wait_flags(hipStream_t st, const uint64_t *flags, int n, uint64_t seq) {
 
 namespace {
 
-// Whether the kernels are left to the library, and how a call is answered with them.
+// Whether the kernels are left to the library, and whether a call makes tables to the library alone.
 bool library_chooses(const rannc_dp_t *h) {
-  return h->lim.algo == RANNC_DP_ALGO_AUTO && h->tune_spw == 0 && h->fused_small == 1 && !h->timing && h->staging_dev[h->next_slot];
+  return !h->recorded && h->lim.algo == RANNC_DP_ALGO_AUTO && h->tune_spw == 0 && h->fused_small == 1 && !h->timing && h->staging_dev[h->next_slot];
 }
 
 // Where the copies of a batch's inputs go: behind the regions that its tables take.  False: the workspace has no such room,

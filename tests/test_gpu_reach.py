@@ -126,3 +126,63 @@ def test_plan_recovery_recorded_behind_the_call():
             torch.cuda.synchronize()
             assert np.array_equal(s.d_se.cpu().numpy(), res["stage_end"]) and np.array_equal(s.d_rp.cpu().numpy(), res["replicas"])
         assert np.array_equal(s.table(B.TABLE_V, 1), oracle.solve(probs[1], keep_tables=True)["V"])
+
+
+@pytest.mark.parametrize("form", ["", "s"])
+def test_a_recorded_recovery_follows_later_calls(form):
+    """Plans and level values recorded behind one call and replayed behind later ones of the same shapes: each replay is of the call
+    in front of it."""
+    def batch(seed):
+        probs = [_search(seed + q, 60, 12, 6) for q in range(3)]
+        for pr in probs if form else []:
+            pr["time_bwd_ns"] = pr["time_ns"][::-1].copy()
+        return probs
+    with B.Session(synth.concat_batch(batch(0))) as s:
+        s.run()
+        d_v = torch.zeros((3, s.plan_stride), dtype=torch.int64, device="cuda:0")
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+            st = torch.cuda.current_stream().cuda_stream
+            assert B.rannc_dp_traceback(s.h, st, s.plan_stride, s.d_se, s.d_rp) == B.OK
+            assert B.rannc_dp_level_values(s.h, st, s.plan_stride, d_v) == B.OK
+        for seed in (0, 10, 20):
+            probs = batch(seed)
+            b = synth.concat_batch(probs)
+            for x, key in zip(s.d_in + [s.d_bwd] * bool(form), ("time_ns", "param_bytes", "act_bytes", "time_bwd_ns")):
+                x.copy_(torch.from_numpy(np.ascontiguousarray(b[key], dtype=np.int64)))
+            s.hb.keep[4][:] = b["mem_capacity"]
+            res = s.run()
+            assert_results_match(probs, res)
+            for x in (s.d_se, s.d_rp):
+                x.fill_(-3)
+            graph.replay()
+            torch.cuda.synchronize()
+            assert np.array_equal(s.d_se.cpu().numpy(), res["stage_end"]) and np.array_equal(s.d_rp.cpu().numpy(), res["replicas"])
+            for q, pr in enumerate(probs):
+                o = oracle.solve(pr, keep_tables=True)
+                assert np.array_equal(d_v.cpu().numpy()[q, :o["n_levels"]], o["V"][1:o["n_levels"] + 1, 60, 12])
+
+
+def test_a_recorded_solve_behind_other_calls():
+    """A whole solve recorded and replayed behind a call of its own: the recovery behind the replay is of the replay's inputs."""
+    first, second = [_search(1, 60, 12, 6)], [_search(2, 60, 12, 6)]
+    want = oracle.solve(first[0])
+    with B.Session(synth.concat_batch(first)) as s:
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+            st = torch.cuda.current_stream().cuda_stream
+            assert B.rannc_dp_solve(s.h, s.hb, st, s.d_opt, s.d_ns, s.d_est, s.d_status) == B.OK
+        b = synth.concat_batch(second)
+        others = [torch.from_numpy(np.ascontiguousarray(b[k], dtype=np.int64)).to("cuda:0") for k in ("time_ns", "param_bytes", "act_bytes")]
+        hb = B.HostBatch(b["n_blocks"], b["n_devices"], b["max_stages"], b["n_microbatches"], b["mem_capacity"], b["block_offset"], *others)
+        out = np.zeros(s._out_dev.numel(), np.uint8)
+        for _ in range(2):
+            assert B.rannc_dp_solve_to_host(s.h, hb, s.stream(), s.plan_stride, s._out_dev, out, out.nbytes) == B.OK
+            assert int(out[:8].view(np.int64)[0]) == oracle.solve(second[0])["opt"]
+            graph.replay()
+            s.traceback()
+            torch.cuda.synchronize()
+            assert int(s.d_opt.item()) == want["opt"]
+            assert np.array_equal(s.d_se.cpu().numpy()[0][:want["n_levels"]], want["stage_end"])
