@@ -25,7 +25,11 @@
  *    current when the call is made.  The library never allocates or frees device memory: the
  *    caller passes a workspace at create time; the handle sub-allocates inside it.
  *  - `hip_stream` is a hipStream_t passed as void* (NULL = the null stream).  solve and
- *    traceback only enqueue work on that stream and return; they never synchronise the device.
+ *    traceback (and traceback_at, level_values, read_table) only enqueue work on that stream and
+ *    return; they never synchronise the device.  Behind a solve_to_host or form_stage that was
+ *    answered without tables the first of them enqueues the making of the tables as well: a whole
+ *    solve.  Where the stream is being recorded into a graph that solve runs at once, on a stream of the
+ *    handle, and is waited for; it is not part of the graph.
  *    Inputs may be released once the stream has passed the end of solve.
  *  - A handle serves one solve at a time: a later solve reuses the workspace, so calls on one
  *    handle must be issued in stream order from one host thread.
@@ -202,14 +206,16 @@ RANNC_DP_API int rannc_dp_traceback(rannc_dp_t *h, void *hip_stream, int32_t pla
  * with the meaning they have above.
  *   d_results  DEVICE, h_results HOST (pinned memory is copied to faster in large batches), 8-byte aligned,
  *              results_bytes bytes each
- * Synchronous: everything before it on hip_stream has completed when it returns.  A batch of searches of up to 4096 blocks, or
- * up to 64 of them of up to 1024 blocks with RANNC_DP_FLAG_SPLIT_OBJECTIVE or (few devices or stages) a communication
- * term, on a handle with algo AUTO and no tuning fields, is normally answered without the tables of rannc_dp_solve; the
- * first rannc_dp_traceback, _traceback_at, _level_values or _read_table behind it makes
- * them, from copies of the inputs kept in the workspace, and waits for that.  Once a call on the handle has been recorded
- * into a graph every call makes its tables: replays find, or write, those they did when all calls made them.  Allocates nothing but host memory for
- * copies of the batch's HOST members, except where plan_stride is beyond the handle's longest plan (max_stages, at
- * most 64): then pinned host memory, at the first such call and at any later one that needs more, freed by destroy.
+ * Synchronous: everything before it on hip_stream has completed when it returns.
+ * A batch of searches of up to 4096 blocks, or up to 64 of them of up to 1024 blocks with RANNC_DP_FLAG_SPLIT_OBJECTIVE or (few
+ * devices or stages) a communication term, on a handle with algo AUTO and no tuning fields, is normally answered without the
+ * tables of rannc_dp_solve.  The first rannc_dp_traceback, _traceback_at, _level_values or _read_table behind it has them made, from
+ * copies of the inputs kept in the workspace, in front of its own work on its stream; work that later calls put on other streams waits for
+ * them there.  Once a call on the handle has been recorded into a graph every call makes its tables: replays find, or write,
+ * those they did when all calls made them.
+ * Allocates nothing but host memory for copies of the batch's HOST members, except where plan_stride is beyond the handle's
+ * longest plan (max_stages, at most 64): then pinned host memory, at the first such call and at any later one that needs more,
+ * freed by destroy.
  * Errors as rannc_dp_solve and rannc_dp_traceback; INVALID_ARG if results_bytes is too small. */
 RANNC_DP_API int rannc_dp_solve_to_host(rannc_dp_t *h, const rannc_dp_batch_t *batch, void *hip_stream,
                                         int32_t plan_stride, void *d_results, void *h_results,
@@ -234,9 +240,11 @@ RANNC_DP_API int rannc_dp_level_values(rannc_dp_t *h, void *hip_stream, int32_t 
  * R = n_nodes / n), stage counts S ascending over (devices_per_node*(n-1), devices_per_node*n] and
  * microbatch counts MB = 1, 2, 4, ... <= floor(batch_size / R), form_stage_dp is asked for a plan
  * of exactly S stages; the first S with any feasible MB returns the best of its solutions.
- * All these searches run as ONE batch through rannc_dp_solve on the given handle; the loops then
- * run over the per-level values in a small kernel, the chosen plan is recovered on the device and
- * one copy brings the result to the host.  Readings where the paper is silent: a block's time
+ * Up to 64 searches of up to 1024 blocks and 8 devices a node (algo AUTO, no tuning fields) normally run as one launch, a
+ * workgroup to a search, which makes no tables; what asks for them behind the call has them made as behind
+ * rannc_dp_solve_to_host, for the whole batch of searches.  Otherwise all searches run as ONE batch through rannc_dp_solve on
+ * the given handle; the loops then run over the per-level values in a small kernel and the chosen plan is recovered on the
+ * device.  Readings where the paper is silent: a block's time
  * and transient bytes are linear in the b = floor(batch_size / R / MB) samples of a microbatch on
  * one pipeline replica (inputs are per sample), persistent bytes are not scaled; "best" is the
  * smallest (MB + S - 1) * V (one synchronous pipeline iteration, Fig. 1), the smallest MB among

@@ -215,14 +215,17 @@ struct rannc_dp {
   int64_t call_total_bound;  // > 0 during the outer driver's solve: no search's total time exceeds it
   // The last batch, where it was answered without its tables (solved, but not tabled): what makes them when they are
   // asked for.  Its inputs are at ws + saved_at (times, persistent, transient bytes, bytes per cut, backward times), or, of
-  // the outer driver, they come from its own per sample (`sample`, the same arrays; search q times samples[q]).
+  // the outer driver, they come from its own per sample (`sample`, the same arrays, and how many samples each search has).
   bool tabled;
+  // They may still be under way on the stream of the call that asked for them: behind this event they are there.
+  hipEvent_t tables_ev;
+  bool tables_pending;
   // A call on the handle has been recorded into a graph, whose replays read the tables of whatever call came before
   // them, or write them: from then on every call makes its tables.
   bool recorded;
   struct {
     std::vector<int32_t> N, D, S, MB;
-    std::vector<int64_t> M, off, bw, sample, samples;
+    std::vector<int64_t> M, off, bw, sample;
     bool comm, split;
     int64_t total_bound;
     size_t saved_at;
@@ -292,6 +295,7 @@ int rannc_dp_create(const rannc_dp_limits_t *l, void *d_workspace, size_t worksp
   h->solved = false;
   h->unchosen = false;
   h->tabled = false;
+  h->tables_pending = false;
   h->recorded = false;
   h->Q = 0;
   h->timing = false;
@@ -321,7 +325,7 @@ int rannc_dp_create(const rannc_dp_limits_t *l, void *d_workspace, size_t worksp
   h->multi_stream = l->single_stream == 0;
   if (const char *e = std::getenv("RANNC_DP_STREAMS")) h->multi_stream = std::atoi(e) != 0;
   int made_ev_s = 0, made_ev = 0, made_aux = 0, made_join = 0;
-  bool made_fork = false;
+  bool made_fork = false, made_tables = false;
   bool ok = true;
   {
     const size_t polled = (size_t)std::min(l->max_problems, kPollMaxProblems);
@@ -365,10 +369,15 @@ int rannc_dp_create(const rannc_dp_limits_t *l, void *d_workspace, size_t worksp
     ok = hipEventCreateWithFlags(&h->fork_ev, hipEventDisableTiming) == hipSuccess;
     made_fork = ok;
   }
+  if (ok) {
+    ok = hipEventCreateWithFlags(&h->tables_ev, hipEventDisableTiming) == hipSuccess;
+    made_tables = ok;
+  }
   if (!ok) {
     for (int k = 0; k < made_aux; ++k) (void)hipStreamDestroy(h->aux[k]);
     for (int k = 0; k < made_join; ++k) (void)hipEventDestroy(h->join_ev[k]);
     if (made_fork) (void)hipEventDestroy(h->fork_ev);
+    if (made_tables) (void)hipEventDestroy(h->tables_ev);
     if (h->pin) (void)hipHostFree(h->pin);
     for (int k = 0; k < made_ev_s; ++k) (void)hipEventDestroy(h->staging_free[k]);
     for (int k = 0; k < made_ev; ++k) (void)hipEventDestroy(h->ev[k]);
@@ -393,6 +402,8 @@ void rannc_dp_destroy(rannc_dp_t *h) {
     (void)hipEventDestroy(h->join_ev[k]);
   }
   (void)hipEventDestroy(h->fork_ev);
+  if (h->tables_pending) (void)hipEventSynchronize(h->tables_ev);  // (they may be made from the outer driver's mirror)
+  (void)hipEventDestroy(h->tables_ev);
   if (h->fs_pin) (void)hipHostFree(h->fs_pin);
   if (h->res_pin_own) (void)hipHostFree(h->res_pin);
   (void)hipHostFree(h->pin);
@@ -896,37 +907,32 @@ static bool recording(rannc_dp_t *h, hipStream_t st) {
   return status != hipStreamCaptureStatusNone;
 }
 
-// Makes the tables of the last batch if it was answered without them.  Behind it they are there for work on any stream, as
-// they are behind a call that returns with its results.  Where the caller's stream is being recorded they are made on a
-// stream of the handle, at once: the recording holds what it would hold behind a call that had made them.
+// Enqueues what makes the tables of the last batch, if it was answered without them; work on this stream comes behind them, and
+// work that a later call puts on another stream waits for them (tables_ev).  Where the caller's stream is being recorded they
+// are made on a stream of the handle, and waited for: the recording holds what it would hold behind a call that had made them.
 static int ensure_tables(rannc_dp_t *h, void *hip_stream) {
   hipStream_t st = (hipStream_t)hip_stream;
   const bool aside = recording(h, st);
-  if (!h->solved || h->tabled) return RANNC_DP_OK;
+  if (!h->solved || (h->tabled && !h->tables_pending)) return RANNC_DP_OK;
   hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-  bool ok = true;
-  if (aside) {
-    st = h->aux[0];
-    ok = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+  if (aside && hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) {
+    (void)hipGetLastError();
+    return RANNC_DP_HIP_ERROR;
   }
-  int rc = RANNC_DP_HIP_ERROR;
-  if (ok) {
+  int rc = RANNC_DP_OK;
+  if (!h->tabled) {
+    if (aside) st = h->aux[0];
     rannc_dp_batch_t b;
     kept_batch(h, &b);
-    std::vector<int64_t> scaled;
-    if (!h->kept.sample.empty()) {
-      const size_t N = (size_t)h->kept.N[0], Q = (size_t)h->Q;
-      try {
-        scaled.resize(5 * Q * N);
-      } catch (...) {
-        ok = false;
-      }
-      for (size_t w = 0; w < 5 && ok; ++w)
-        for (size_t q = 0; q < Q; ++q)
-          for (size_t k = 0; k < N; ++k) scaled[(w * Q + q) * N + k] = h->kept.sample[w * N + k] * (w == 1 ? 1 : h->kept.samples[q]);
-      ok = ok && hipMemcpyAsync(h->ws + h->kept.saved_at, scaled.data(), scaled.size() * 8, hipMemcpyHostToDevice, st) == hipSuccess;
+    if (!h->kept.sample.empty()) {  // (through the driver's mirror, which no call uses until it has waited for this)
+      const int N = h->kept.N[0];
+      const int64_t *const from = (const int64_t *)h->fs_pin_dev;
+      if (from) std::memcpy(h->fs_pin, h->kept.sample.data(), 8 * h->kept.sample.size());
+      if (!from || rannc::launch_form_inputs(from, from + 5 * (size_t)N, (int64_t *)(h->ws + h->kept.saved_at), N, h->Q, h->kept.comm,
+                                             h->kept.split, st) != hipSuccess)
+        rc = RANNC_DP_HIP_ERROR;
     }
-    if (ok) {
+    if (rc == RANNC_DP_OK) {
       const size_t ws_bytes = h->ws_bytes;
       h->ws_bytes = h->kept.saved_at;
       h->call_total_bound = h->kept.total_bound;
@@ -934,12 +940,23 @@ static int ensure_tables(rannc_dp_t *h, void *hip_stream) {
       h->call_total_bound = 0;
       h->ws_bytes = ws_bytes;
     }
-    if (rc == RANNC_DP_OK && hipStreamSynchronize(st) != hipSuccess) rc = RANNC_DP_HIP_ERROR;
-    if (aside) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (rc == RANNC_DP_OK && hipEventRecord(h->tables_ev, st) != hipSuccess) rc = RANNC_DP_HIP_ERROR;
+    h->solved = true;
+    h->tabled = rc == RANNC_DP_OK;
+    if (h->tabled) h->tables_pending = true;
+    else (void)hipStreamSynchronize(st);  // nothing of it runs on, and it can be asked for again
+  } else {
+    const hipError_t e = hipEventQuery(h->tables_ev);
+    if (e == hipSuccess) h->tables_pending = false;
+    else if (e != hipErrorNotReady || (!aside && hipStreamWaitEvent(st, h->tables_ev, 0) != hipSuccess)) rc = RANNC_DP_HIP_ERROR;
+    else (void)hipGetLastError();
   }
+  if (rc == RANNC_DP_OK && aside && h->tables_pending) {
+    if (hipEventSynchronize(h->tables_ev) == hipSuccess) h->tables_pending = false;
+    else rc = RANNC_DP_HIP_ERROR;
+  }
+  if (aside) (void)hipThreadExchangeStreamCaptureMode(&mode);
   if (rc != RANNC_DP_OK) (void)hipGetLastError();
-  h->solved = true;
-  h->tabled = rc == RANNC_DP_OK;
   return rc;
 }
 
@@ -1382,10 +1399,10 @@ bool form_direct(rannc_dp_t *h, const rannc_dp_form_stage_in_t *in, const std::v
   bool kept = true;
   try {
     h->kept.N.assign(Q, N);
-    h->kept.D.resize(Q); h->kept.S.resize(Q); h->kept.MB.resize(Q); h->kept.samples.resize(Q); h->kept.off.resize(Q + 1);
+    h->kept.D.resize(Q); h->kept.S.resize(Q); h->kept.MB.resize(Q); h->kept.off.resize(Q + 1);
+    h->kept.sample.assign(5 * (size_t)N + (size_t)Q, 0);
     h->kept.M.assign(Q, in->mem_capacity);
     h->kept.bw.assign(Q, in->bandwidth_bytes_per_us);
-    h->kept.sample.assign(5 * (size_t)N, 0);
   } catch (...) {
     kept = false;
   }
@@ -1393,7 +1410,7 @@ bool form_direct(rannc_dp_t *h, const rannc_dp_form_stage_in_t *in, const std::v
     for (int q = 0; q < Q; ++q) {
       h->kept.D[q] = h->kept.S[q] = per * pairs[q].n;
       h->kept.MB[q] = pairs[q].MB;
-      h->kept.samples[q] = pairs[q].b;
+      h->kept.sample[5 * (size_t)N + q] = pairs[q].b;
       h->kept.off[q] = (int64_t)q * N;
     }
     h->kept.off[Q] = (int64_t)Q * N;
@@ -1503,6 +1520,13 @@ int rannc_dp_form_stage(rannc_dp_t *h, const rannc_dp_form_stage_in_t *in, void 
   // pinned host mirror of the device scratch: same layout, so inputs go up and results come down
   // in one copy each
   const size_t pin_need = need + 8;  // and the flag word behind it
+  if (h->tables_pending) {  // they may be made from the mirror
+    if (hipEventSynchronize(h->tables_ev) != hipSuccess) {
+      (void)hipGetLastError();
+      return RANNC_DP_HIP_ERROR;
+    }
+    h->tables_pending = false;
+  }
   if (h->fs_pin_bytes < pin_need) {
     if (h->fs_pin) {
       if (hipStreamSynchronize(st) != hipSuccess) return RANNC_DP_HIP_ERROR;  // an earlier call's copies

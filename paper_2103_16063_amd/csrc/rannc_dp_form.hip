@@ -373,6 +373,19 @@ __global__ __launch_bounds__(kFormThreads) void form_kernel(const FormArgs args)
   if (lane == 0) __hip_atomic_store(&r.h_flag[q], r.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// (Persistent bytes do not grow with the samples.)  A search to blockIdx.y, an array to blockIdx.z; read across the bus.
+__global__ __launch_bounds__(256) void form_inputs_kernel(const int64_t *per_sample, const int64_t *samples, int64_t *out, int N, int Q, int arrays) {
+  const int k = blockIdx.x * 256 + threadIdx.x, q = blockIdx.y, w = blockIdx.z;
+  if (k >= N || !(arrays >> w & 1)) return;
+  out[((int64_t)w * Q + q) * N + k] = per_sample[(int64_t)w * N + k] * (w == 1 ? 1 : samples[q]);
+}
+
+hipError_t launch_form_inputs(const int64_t *per_sample, const int64_t *samples, int64_t *out, int N, int Q, bool comm, bool split, hipStream_t st) {
+  hipLaunchKernelGGL(form_inputs_kernel, dim3((N + 255) / 256, Q, 5), dim3(256), 0, st, per_sample, samples, out, N, Q,
+                     7 | (comm ? 8 : 0) | (split ? 16 : 0));
+  return hipGetLastError();
+}
+
 hipError_t launch_form(int Q, int spare, const FormArgs &in, hipStream_t st) {
   if (in.N > kFormMaxBlocks || spare > 8 || spare < 1) return hipErrorInvalidValue;
   const bool split = in.tb != nullptr;

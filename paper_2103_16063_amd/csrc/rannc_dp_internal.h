@@ -262,6 +262,9 @@ struct FormArgs {
 };
 // spare: largest D - lo + 1 of the pairs
 hipError_t launch_form(int Q, int spare, const FormArgs &args, hipStream_t st);
+// The inputs of all Q searches of the outer driver, one after the other, from its own per sample: five arrays of N entries (times,
+// persistent, transient bytes, bytes per cut, backward times) to as many of Q * N; samples[q] of search q.
+hipError_t launch_form_inputs(const int64_t *per_sample, const int64_t *samples, int64_t *out, int N, int Q, bool comm, bool split, hipStream_t st);
 // compaction step of the block-level phase on a chain of G groups (one workgroup).  Short chains are
 // held in LDS; longer ones keep arrays of G + 1 entries in the workspace: three of 8 bytes and two of 4
 constexpr size_t compact_array_bytes(int G, int entry) { return ((size_t)(G + 1) * entry + 255) / 256 * 256; }

@@ -9,6 +9,7 @@ import oracle
 from paper_2103_16063_amd import binding as B
 from paper_2103_16063_amd import synth
 from tests.test_gpu_form_stage import _assert_same
+from tests.test_gpu_reach import long_work
 
 pytestmark = pytest.mark.gpu
 
@@ -69,4 +70,36 @@ def test_tables_behind_the_driver(form):
     torch.cuda.synchronize()
     assert list(se[found, :S].cpu()) == list(want["stage_end"]) and list(rp[found, :S].cpu()) == list(want["replicas"])
     assert int(values[found, S - 1]) == want["stage_time_ns"]
+    fs.close()
+
+
+@pytest.mark.parametrize("form", ["plain", "split comm"])
+def test_tables_behind_the_driver_do_not_wait_and_outlive_the_next_call(form):
+    """Recovery behind the driver only enqueues, also where long work is in front of it; a later call of the driver, one that fails
+    among them, leaves what was enqueued as it is."""
+    c, more, fs, want = _case(11, 48, 2, 6, 16, 1.8, form)
+    other, more2, fs2, want2 = _case(12, 48, 2, 6, 16, 2.2, form)
+    fs2.close()
+    pairs = [(n, MB) for n in (1, 2) for MB in (1, 2, 4, 8, 16) if MB <= 16 // (2 // n)]
+    found, S = pairs.index((want["n"], want["n_microbatches"])), want["n_stages"]
+    se, rp = (torch.full((fs.Q, fs.plan_stride), -7, dtype=torch.int32, device="cuda:0") for _ in range(2))
+    levels = torch.full((fs.Q,), -1, dtype=torch.int32, device="cuda:0")
+    levels[found] = S
+    bad = c["time_per_sample_ns"].copy()
+    bad[-1] = -1
+    stream = torch.cuda.current_stream()
+    for later in (None, other):
+        rc, out, *_ = fs.run(c["time_per_sample_ns"], c["act_bytes_per_sample"], c["param_bytes"], c["mem_capacity"], **more)
+        assert rc == B.OK and out.n_stages == S
+        assert fs.run(bad, c["act_bytes_per_sample"], c["param_bytes"], c["mem_capacity"], **more)[0] == B.INVALID_ARG
+        se.fill_(-7)
+        torch.cuda.synchronize()
+        done = long_work(stream)
+        assert B.rannc_dp_traceback_at(fs.h, stream.cuda_stream, levels, fs.plan_stride, se, rp) == B.OK
+        assert not done.query()
+        if later is not None:
+            _assert_same(later, fs.run(later["time_per_sample_ns"], later["act_bytes_per_sample"], later["param_bytes"], later["mem_capacity"],
+                                       **more2), want2, fs.plan_stride)
+        torch.cuda.synchronize()
+        assert list(se[found, :S].cpu()) == list(want["stage_end"]) and list(rp[found, :S].cpu()) == list(want["replicas"])
     fs.close()

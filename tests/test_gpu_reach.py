@@ -186,3 +186,35 @@ def test_a_recorded_solve_behind_other_calls():
             torch.cuda.synchronize()
             assert int(s.d_opt.item()) == want["opt"]
             assert np.array_equal(s.d_se.cpu().numpy()[0][:want["n_levels"]], want["stage_end"])
+
+
+def long_work(stream):
+    """Work of tens of milliseconds on the stream; the event behind it has not happened behind a call that does not wait."""
+    with torch.cuda.stream(stream):
+        torch.cuda._sleep(200_000_000)
+        return stream.record_event()
+
+
+def test_recovery_behind_the_call_does_not_wait():
+    """Plan recovery, level values and tables behind a call answered without tables only enqueue, as behind a solve; work on another
+    stream behind them waits for the tables on the device."""
+    probs = [_search(q, 60, (12, 60)[q % 2], 6) for q in range(4)]
+    with B.Session(synth.concat_batch(probs)) as s:
+        one, other = torch.cuda.Stream(), torch.cuda.Stream()
+        with torch.cuda.stream(one):
+            res = s.run()
+        s.d_se.fill_(-3)
+        s.d_rp.fill_(-3)
+        d_v = torch.full((4, s.plan_stride), -5, dtype=torch.int64, device="cuda:0")
+        torch.cuda.synchronize()
+        done = long_work(one)
+        assert B.rannc_dp_traceback(s.h, one.cuda_stream, s.plan_stride, s.d_se, s.d_rp) == B.OK
+        assert B.rannc_dp_level_values(s.h, other.cuda_stream, s.plan_stride, d_v) == B.OK
+        assert not done.query()
+        other.synchronize()
+        for q, pr in enumerate(probs):
+            o = oracle.solve(pr, keep_tables=True)
+            N, D, L = len(pr["time_ns"]), pr["n_devices"], o["n_levels"]
+            assert np.array_equal(d_v.cpu().numpy()[q, :L], o["V"][1:L + 1, N, D])
+        torch.cuda.synchronize()
+        assert np.array_equal(s.d_se.cpu().numpy(), res["stage_end"]) and np.array_equal(s.d_rp.cpu().numpy(), res["replicas"])
