@@ -211,7 +211,8 @@ RANNC_DP_API int rannc_dp_traceback(rannc_dp_t *h, void *hip_stream, int32_t pla
  * devices or stages) a communication term, on a handle with algo AUTO and no tuning fields, is normally answered without the
  * tables of rannc_dp_solve.  The first rannc_dp_traceback, _traceback_at, _level_values or _read_table behind it has them made, from
  * copies of the inputs kept in the workspace, in front of its own work on its stream; work that later calls put on other streams waits for
- * them there.  Once a call on the handle has been recorded into a graph every call makes its tables: replays find, or write,
+ * them there.  The next call to the host on such a handle makes its tables itself, so that a program that reads them behind every
+ * call pays for one search each.  Once a call on the handle has been recorded into a graph every call makes its tables: replays find, or write,
  * those they did when all calls made them.
  * Allocates nothing but host memory for copies of the batch's HOST members, except where plan_stride is beyond the handle's
  * longest plan (max_stages, at most 64): then pinned host memory, at the first such call and at any later one that needs more,
@@ -385,6 +386,10 @@ typedef struct {
 } rannc_dp_solve_info_t;
 /* RANNC_DP_BAD_STATE before the first successful solve. */
 RANNC_DP_API int rannc_dp_solve_info(rannc_dp_t *h, rannc_dp_solve_info_t *out);
+
+/* 1: the last call on the handle was a rannc_dp_solve_to_host or rannc_dp_form_stage that was answered without tables (whether or
+ * not they have been made since), 0: it made them; RANNC_DP_BAD_STATE before the first successful one. */
+RANNC_DP_API int rannc_dp_answered_without_tables(rannc_dp_t *h);
 
 /* Waits for the handle's own streams, frees host state, events and streams; the workspace remains
  * the caller's.  NULL is allowed. */

@@ -35,7 +35,7 @@ EXPORTS = ["rannc_dp_workspace_bytes", "rannc_dp_workspace_bytes_for", "rannc_dp
            "rannc_dp_traceback_at", "rannc_dp_level_values", "rannc_dp_form_stage_problems",
            "rannc_dp_form_stage_scratch_bytes", "rannc_dp_form_stage",
            "rannc_dp_compact_workspace_bytes", "rannc_dp_compact", "rannc_dp_compact_static",
-           "rannc_dp_solve_info", "rannc_dp_solve_to_host"]
+           "rannc_dp_solve_info", "rannc_dp_solve_to_host", "rannc_dp_answered_without_tables"]
 
 
 class Limits(C.Structure):
@@ -131,6 +131,8 @@ def lib():
         L.rannc_dp_solve_to_host.restype = C.c_int
         L.rannc_dp_solve_info.argtypes = [vp, C.POINTER(SolveInfo)]
         L.rannc_dp_solve_info.restype = C.c_int
+        L.rannc_dp_answered_without_tables.argtypes = [vp]
+        L.rannc_dp_answered_without_tables.restype = C.c_int
         L.rannc_dp_compact_workspace_bytes.argtypes = [C.c_int32]
         L.rannc_dp_compact_workspace_bytes.restype = sz
         L.rannc_dp_compact.argtypes = [vp, C.c_int32, C.c_int32, C.c_int32, C.c_int64, vp, vp, vp, vp, sz, vp, vp, vp,
@@ -171,6 +173,11 @@ def rannc_dp_solve_info(handle):
     info = SolveInfo()
     rc = lib().rannc_dp_solve_info(handle, C.byref(info))
     return rc, info
+
+
+def rannc_dp_answered_without_tables(handle) -> int:
+    """1 or 0, or a negative status."""
+    return lib().rannc_dp_answered_without_tables(handle)
 
 
 class HostBatch:

@@ -218,3 +218,22 @@ def test_recovery_behind_the_call_does_not_wait():
             assert np.array_equal(d_v.cpu().numpy()[q, :L], o["V"][1:L + 1, N, D])
         torch.cuda.synchronize()
         assert np.array_equal(s.d_se.cpu().numpy(), res["stage_end"]) and np.array_equal(s.d_rp.cpu().numpy(), res["replicas"])
+
+
+def test_a_program_that_reads_the_tables_pays_for_one_search():
+    """Where the tables were asked for behind a call, the next one makes its own; where they were not, it is answered without."""
+    probs = [_search(3, 60, 12, 6)]
+    want = oracle.solve(probs[0], keep_tables=True)
+    with B.Session(synth.concat_batch(probs)) as s:
+        assert B.rannc_dp_answered_without_tables(s.h) == B.BAD_STATE
+        for ask, direct in ((False, 1), (True, 1), (True, 0), (False, 0), (True, 1), (False, 0), (False, 1), (False, 1)):
+            assert_results_match(probs, s.run(), oracle_results=[want])
+            assert B.rannc_dp_answered_without_tables(s.h) == direct
+            if ask:
+                assert np.array_equal(s.table(B.TABLE_V, 0), want["V"])
+                assert B.rannc_dp_answered_without_tables(s.h) == direct
+        s.solve()
+        s.traceback()
+        assert B.rannc_dp_answered_without_tables(s.h) == 0
+        s.run()     # (behind a solve that a program reads on the device nothing was put off)
+        assert B.rannc_dp_answered_without_tables(s.h) == 1
