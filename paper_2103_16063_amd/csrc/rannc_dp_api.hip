@@ -886,20 +886,32 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
 }
 
 // The last batch as it was answered without its tables, over the copies of its inputs.
-static void kept_batch(const rannc_dp_t *h, rannc_dp_batch_t *b) {
-  *b = {};
-  b->n_problems = h->Q;
-  b->n_blocks = h->kept.N.data(); b->n_devices = h->kept.D.data(); b->max_stages = h->kept.S.data();
-  b->n_microbatches = h->kept.MB.data(); b->mem_capacity = h->kept.M.data(); b->block_offset = h->kept.off.data();
+static rannc_dp_batch_t kept_batch(const rannc_dp_t *h) {
+  rannc_dp_batch_t b = {};
+  b.n_problems = h->Q;
+  b.n_blocks = h->kept.N.data(); b.n_devices = h->kept.D.data(); b.max_stages = h->kept.S.data();
+  b.n_microbatches = h->kept.MB.data(); b.mem_capacity = h->kept.M.data(); b.block_offset = h->kept.off.data();
   const int64_t blocks = h->kept.off[h->Q];
-  b->time_ns = (const int64_t *)(h->ws + h->kept.saved_at);
-  b->param_bytes = b->time_ns + blocks;
-  b->act_bytes = b->param_bytes + blocks;
+  b.time_ns = (const int64_t *)(h->ws + h->kept.saved_at);
+  b.param_bytes = b.time_ns + blocks;
+  b.act_bytes = b.param_bytes + blocks;
   if (h->kept.comm) {
-    b->cut_bytes = b->act_bytes + blocks;
-    b->bandwidth_bytes_per_us = h->kept.bw.data();
+    b.cut_bytes = b.act_bytes + blocks;
+    b.bandwidth_bytes_per_us = h->kept.bw.data();
   }
-  if (h->kept.split) b->time_bwd_ns = b->act_bytes + 2 * blocks;
+  if (h->kept.split) b.time_bwd_ns = b.act_bytes + 2 * blocks;
+  return b;
+}
+
+// Its tables, in the workspace in front of the copies; or what they will be made with.
+static int solve_kept(rannc_dp_t *h, const rannc_dp_batch_t &b, hipStream_t st, bool info_only) {
+  const size_t ws_bytes = h->ws_bytes;
+  h->ws_bytes = h->kept.saved_at;
+  h->call_total_bound = h->kept.total_bound;
+  const int rc = solve_impl(h, &b, st, nullptr, nullptr, nullptr, nullptr, nullptr, 0, nullptr, nullptr, info_only);
+  h->call_total_bound = 0;
+  h->ws_bytes = ws_bytes;
+  return rc;
 }
 
 // Whether the caller's stream is being recorded into a graph; the handle remembers that it was.
@@ -929,8 +941,7 @@ static int ensure_tables(rannc_dp_t *h, void *hip_stream) {
   int rc = RANNC_DP_OK;
   if (!h->tabled) {
     if (aside) st = h->aux[0];
-    rannc_dp_batch_t b;
-    kept_batch(h, &b);
+    const rannc_dp_batch_t b = kept_batch(h);
     if (!h->kept.sample.empty()) {  // (through the driver's mirror, which no call uses until it has waited for this)
       const int N = h->kept.N[0];
       const int64_t *const from = (const int64_t *)h->fs_pin_dev;
@@ -939,14 +950,7 @@ static int ensure_tables(rannc_dp_t *h, void *hip_stream) {
                                              h->kept.split, st) != hipSuccess)
         rc = RANNC_DP_HIP_ERROR;
     }
-    if (rc == RANNC_DP_OK) {
-      const size_t ws_bytes = h->ws_bytes;
-      h->ws_bytes = h->kept.saved_at;
-      h->call_total_bound = h->kept.total_bound;
-      rc = solve_impl(h, &b, st, nullptr, nullptr, nullptr, nullptr, nullptr);
-      h->call_total_bound = 0;
-      h->ws_bytes = ws_bytes;
-    }
+    if (rc == RANNC_DP_OK) rc = solve_kept(h, b, st, false);
     if (rc == RANNC_DP_OK && hipEventRecord(h->tables_ev, st) != hipSuccess) rc = RANNC_DP_HIP_ERROR;
     h->solved = true;
     h->tabled = rc == RANNC_DP_OK;
@@ -983,11 +987,7 @@ int rannc_dp_solve_info(rannc_dp_t *h, rannc_dp_solve_info_t *out) {
   if (!h || !out) return RANNC_DP_INVALID_ARG;
   if (!h->solved) return RANNC_DP_BAD_STATE;
   if (!h->tabled) {  // answered without tables: what they will be made with
-    rannc_dp_batch_t b;
-    kept_batch(h, &b);
-    h->call_total_bound = h->kept.total_bound;
-    const int rc = solve_impl(h, &b, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0, nullptr, nullptr, true);
-    h->call_total_bound = 0;
+    const int rc = solve_kept(h, kept_batch(h), nullptr, true);
     if (rc != RANNC_DP_OK) return rc;
   }
   *out = h->info;

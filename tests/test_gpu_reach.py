@@ -237,3 +237,30 @@ def test_a_program_that_reads_the_tables_pays_for_one_search():
         assert B.rannc_dp_answered_without_tables(s.h) == 0
         s.run()     # (behind a solve that a program reads on the device nothing was put off)
         assert B.rannc_dp_answered_without_tables(s.h) == 1
+
+
+def test_the_kernels_reported_are_those_that_make_the_tables():
+    """A workspace that holds the batch as one group, or class by class beside the copies of its inputs, but not as a group beside them."""
+    probs = [_search(q, 40, D, 6) for q, D in enumerate((8, 8, 8, 64))]
+    with B.Session(synth.concat_batch(probs)) as s:
+        copies = (5 * 8 * 160 + 255) // 256 * 256 + 256
+        rc, h = B.rannc_dp_create(s.limits, s.ws, s.ws_bytes - copies)
+        assert rc == B.OK
+        try:
+            out = np.zeros(s._out_dev.numel(), np.uint8)
+            assert B.rannc_dp_solve_to_host(h, s.hb, s.stream(), s.plan_stride, s._out_dev, out, out.nbytes) == B.OK
+            assert B.rannc_dp_answered_without_tables(h) == 1
+            rc, before = B.rannc_dp_solve_info(h)
+            assert rc == B.OK
+            d_v = torch.zeros((4, s.plan_stride), dtype=torch.int64, device="cuda:0")
+            assert B.rannc_dp_level_values(h, s.stream(), s.plan_stride, d_v) == B.OK
+            rc, after = B.rannc_dp_solve_info(h)
+            assert rc == B.OK and list(before.n_problems) == list(after.n_problems) == [3, 0, 0, 1]
+            assert list(before.level_kernel) == list(after.level_kernel)
+            torch.cuda.synchronize()
+            for q, pr in enumerate(probs):
+                o = oracle.solve(pr, keep_tables=True)
+                assert np.array_equal(d_v.cpu().numpy()[q, :o["n_levels"]], o["V"][1:o["n_levels"] + 1, 40, pr["n_devices"]])
+        finally:
+            torch.cuda.synchronize()
+            B.rannc_dp_destroy(h)
