@@ -955,6 +955,9 @@ hipError_t launch_compact(int G, int k, int64_t M, int max_walks, const int64_t 
   static_assert(kTimesLds >= kCompactSmallLds, "either form of the state");
   auto go = [&](auto width) -> hipError_t {
     constexpr int NT = decltype(width)::value;
+    static std::atomic<uint64_t> asked{0};
+    const hipError_t e = allow_lds(asked, (const void *)compact_kernel<0, NT>, (int)kCompactSmallLds);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL((compact_kernel<0, NT>), dim3(1), dim3(NT), 3 * compact_array_bytes(G, 8) + 2 * compact_array_bytes(G, 4), st, G, k, M,
                        max_walks, t, p, a, (char *)ws, n_out, block_end, t_out, p_out, a_out, status);
     return hipGetLastError();
@@ -966,7 +969,7 @@ hipError_t launch_compact(int G, int k, int64_t M, int max_walks, const int64_t 
   for (int left = G; left > kCompactLaunch && left * 2 / 5 > k && walks < kCompactMostWalks && (max_walks <= 0 || walks < max_walks); ++walks)
     left = left * 9 / 25;
   const bool times_lds = G <= kCompactTimesLds;
-  static std::atomic<uint64_t> asked[2];
+  static std::atomic<uint64_t> asked[3];
   if (walks == 0) {
     if (times_lds) {
       const hipError_t e = allow_lds(asked[0], (const void *)compact_kernel<1, 1024>, (int)kTimesLds);
@@ -991,6 +994,8 @@ hipError_t launch_compact(int G, int k, int64_t M, int max_walks, const int64_t 
     hipLaunchKernelGGL(compact_resume_kernel<1>, dim3(1), dim3(1024), std::max(compact_array_bytes(G, 8), kCompactSmallLds), st, G, k, M,
                        max_walks, walks, (char *)ws, state, n_out, block_end, t_out, p_out, a_out, status);
   } else {
+    const hipError_t e = allow_lds(asked[2], (const void *)compact_resume_kernel<2>, (int)kCompactSmallLds);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(compact_resume_kernel<2>, dim3(1), dim3(1024), kCompactSmallLds, st, G, k, M, max_walks, walks, (char *)ws, state,
                        n_out, block_end, t_out, p_out, a_out, status);
   }

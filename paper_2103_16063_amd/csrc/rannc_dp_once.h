@@ -22,7 +22,8 @@ hipError_t once_per_device(std::atomic<uint64_t> &done, CurrentDevice current, A
   return r;
 }
 
-// A kernel whose dynamic LDS exceeds the default 64 KiB: the limit belongs to its function on one device.
+// A kernel whose LDS, its own and the dynamic part, can exceed the default 64 KiB: the limit belongs to its function on one device.
+// (Asked for whatever a launch needs: how much a kernel has of its own changes with its code.)
 inline hipError_t allow_lds(std::atomic<uint64_t> &done, const void *kernel, int bytes) {
   return once_per_device(done, [](int *dev) { return hipGetDevice(dev); }, [&] {
     return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);

@@ -114,11 +114,9 @@ hipError_t launch_reach(const ReachIn *src, const ReachIn *host_one, int Q, cons
   const ReachIn one = host_one ? *host_one : ReachIn{};
   auto go = [&](auto waves) -> hipError_t {
     constexpr int W = decltype(waves)::value;
-    if (lds > 56 * 1024) {  // (with the 8 KB and more of the kernel's own, what need not be asked for)
-      static std::atomic<uint64_t> asked{0};
-      const hipError_t e = allow_lds(asked, (const void *)reach_kernel<W>, 148 * 1024);
-      if (e != hipSuccess) return e;
-    }
+    static std::atomic<uint64_t> asked{0};
+    const hipError_t e = allow_lds(asked, (const void *)reach_kernel<W>, 148 * 1024);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(reach_kernel<W>, dim3(Q), dim3(64 * W), lds, st, src, one, host_one ? 1 : 0, args, dims);
     return hipGetLastError();
   };

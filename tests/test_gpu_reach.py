@@ -264,3 +264,8 @@ def test_the_kernels_reported_are_those_that_make_the_tables():
         finally:
             torch.cuda.synchronize()
             B.rannc_dp_destroy(h)
+
+
+@pytest.mark.parametrize("N,D,S", [(51, 64, 20), (185, 17, 9), (215, 16, 8)])
+def test_sizes_whose_lds_lies_about_64_kib(N, D, S):
+    _check([_search(1, N, D, S, share=1.3)])

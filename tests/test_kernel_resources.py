@@ -53,6 +53,23 @@ def workgroups_per_cu(k, threads):
     return min(by_waves, LDS // lds if lds else by_waves)
 
 
+def test_dynamic_lds_beyond_64_kib_is_asked_for(kernels):
+    """Every kernel that needs more than 64 KiB of a compute unit's LDS at some size is asked for at every size: how much a kernel has of
+    its own changes with its code.  (prepare_kernel holds 60 KiB at most, which its launch asserts.)"""
+    csrc = os.path.join(os.path.dirname(HERE), "paper_2103_16063_amd", "csrc")
+    assert all(k["group_segment_fixed_size"] <= 4 * 1024 for n, k in kernels.items() if "prepare_kernel" in n)
+    launched = set()
+    for file in sorted(os.listdir(csrc)):
+        text = open(os.path.join(csrc, file)).read()
+        asked = {m.replace(" ", "") for m in re.findall(r"allow_lds\(\w+(?:\[\d\])?, \(const void \*\)([\w<>, ]+),", text)}
+        assert not re.search(r"if \(lds[^;{]*> [\d* ]+\) \{[^}]*allow_lds", text), file
+        for kernel, lds in re.findall(r"hipLaunchKernelGGL\(\(?(\w+_kernel(?:<[^;]*?>)?)\)?, dim3\([^;]*?dim3\([^;]*?\), (?!dim3)([^;]*?), st, ", text):
+            if lds != "0":
+                launched.add(kernel.replace(" ", ""))
+                assert kernel.replace(" ", "") in asked, (file, kernel)
+    assert len(launched) >= 8
+
+
 def test_level_kernels_fit_the_workgroups_that_size_their_items(kernels, tmp_path):
     exe = str(tmp_path / "occupancy_model")
     subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "-x", "hip", "--offload-host-only", "-O1", "-std=c++17",
