@@ -387,8 +387,9 @@ typedef struct {
 /* RANNC_DP_BAD_STATE before the first successful solve. */
 RANNC_DP_API int rannc_dp_solve_info(rannc_dp_t *h, rannc_dp_solve_info_t *out);
 
-/* 1: the last call on the handle was a rannc_dp_solve_to_host or rannc_dp_form_stage that was answered without tables (whether or
- * not they have been made since), 0: it made them; RANNC_DP_BAD_STATE before the first successful one. */
+/* Searches of the last rannc_dp_solve_to_host that were answered without tables (those that its kernel leaves open are solved with
+ * theirs, which are not kept), or of the last rannc_dp_form_stage all or none; 0 behind rannc_dp_solve.  Tables made behind the call
+ * do not change it.  RANNC_DP_BAD_STATE before the first successful call. */
 RANNC_DP_API int rannc_dp_answered_without_tables(rannc_dp_t *h);
 
 /* Waits for the handle's own streams, frees host state, events and streams; the workspace remains

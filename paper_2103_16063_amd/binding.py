@@ -176,7 +176,7 @@ def rannc_dp_solve_info(handle):
 
 
 def rannc_dp_answered_without_tables(handle) -> int:
-    """1 or 0, or a negative status."""
+    """A number of searches, or a negative status."""
     return lib().rannc_dp_answered_without_tables(handle)
 
 

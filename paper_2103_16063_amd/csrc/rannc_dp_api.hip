@@ -220,11 +220,11 @@ struct rannc_dp {
   // They may still be under way on the stream of the call that asked for them: behind this event they are there.
   hipEvent_t tables_ev;
   bool tables_pending;
-  // Whether the last call brought its results to the host, was answered without its tables, and whether these (or those it
-  // made) were asked for behind it.  Then the next call to the host makes its own at once: a program that reads them
+  // Whether the last call brought its results to the host, and whether its tables were asked for behind it.  Then the next call to the host makes its own at once: a program that reads them
   // behind every call pays for one search each, not for one without tables and one with them (a call and rannc_dp_traceback, the
   // stream waited for: 96 blocks at 16 devices 96 -> 86 us, 1024 at 64 360 -> 323).
-  bool to_host, direct, asked;
+  bool to_host, asked;
+  int direct;  // searches of it that were
   // A call on the handle has been recorded into a graph, whose replays read the tables of whatever call came before
   // them, or write them: from then on every call makes its tables.
   bool recorded;
@@ -301,7 +301,8 @@ int rannc_dp_create(const rannc_dp_limits_t *l, void *d_workspace, size_t worksp
   h->unchosen = false;
   h->tabled = false;
   h->tables_pending = false;
-  h->to_host = h->direct = h->asked = false;
+  h->to_host = h->asked = false;
+  h->direct = 0;
   h->recorded = false;
   h->Q = 0;
   h->timing = false;
@@ -437,9 +438,13 @@ int rannc_dp_get_timing(rannc_dp_t *h, float *out_ms, int32_t *out_level_launche
 // results != null: a solve that is one launch over few searches recovers their plans there as well;
 // *recovered = whether it has.
 // info_only: nothing is launched, and only what rannc_dp_solve_info reports is found out.
+// part != null: the batch is a part of another one, whose arrays of blocks it has and in whose results its searches have
+// their places.
+struct BatchPart { std::vector<int32_t> place; std::vector<int64_t> first; };  // in the results; of the blocks
 static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream, int64_t *d_opt, int32_t *d_n_stages,
                       int64_t *d_est_iter_ns, int32_t *d_status, bool *chosen, int32_t plan_stride = 0,
-                      const rannc::PlanResults *results = nullptr, bool *recovered = nullptr, bool info_only = false) {
+                      const rannc::PlanResults *results = nullptr, bool *recovered = nullptr, bool info_only = false,
+                      const BatchPart *part = nullptr) {
   int rc = check_batch(&h->lim, b);
   if (rc != RANNC_DP_OK) return rc;
   if (!b->time_ns || !b->param_bytes || !b->act_bytes) return RANNC_DP_INVALID_ARG;
@@ -503,13 +508,14 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
     p.DP = dp_of(q);
     p.nch = (N + 63) / 64;
     p.bits = h->bits;
-    p.q = q;
+    p.q = part ? part->place[q] : q;
     p.M = b->mem_capacity[q];
     p.time_limit = h->lim.max_total_time_ns;
-    p.t = b->time_ns + b->block_offset[q];
-    p.p = b->param_bytes + b->block_offset[q];
-    p.a = b->act_bytes + b->block_offset[q];
-    p.o = b->cut_bytes ? b->cut_bytes + b->block_offset[q] : nullptr;
+    const int64_t first = part ? part->first[q] : b->block_offset[q];
+    p.t = b->time_ns + first;
+    p.p = b->param_bytes + first;
+    p.a = b->act_bytes + first;
+    p.o = b->cut_bytes ? b->cut_bytes + first : nullptr;
     p.bw = b->cut_bytes ? b->bandwidth_bytes_per_us[q] : 0;
     char *base = h->ws + off;
     p.T = (int64_t *)base; base += sz.prefix;
@@ -519,7 +525,7 @@ static int solve_impl(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream
     p.ends = (uint32_t *)base;  // (where the level kernel recomputes the stage times: set below)
     base += sz.prefix;
     if (split) {
-      p.tb = b->time_bwd_ns + b->block_offset[q];
+      p.tb = b->time_bwd_ns + first;
       p.TB = (int64_t *)base; base += sz.prefix;
     }
     p.wlo = (int32_t *)base; base += sz.wlo;
@@ -975,7 +981,8 @@ int rannc_dp_solve(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_stream, i
                    int32_t *d_n_stages, int64_t *d_est_iter_ns, int32_t *d_status) {
   if (!h || !d_opt || !d_n_stages) return RANNC_DP_INVALID_ARG;
   (void)recording(h, (hipStream_t)hip_stream);
-  h->to_host = h->direct = h->asked = false;
+  h->to_host = h->asked = false;
+  h->direct = 0;
   return solve_impl(h, b, hip_stream, d_opt, d_n_stages, d_est_iter_ns, d_status, nullptr);
 }
 
@@ -997,7 +1004,7 @@ int rannc_dp_solve_info(rannc_dp_t *h, rannc_dp_solve_info_t *out) {
 int rannc_dp_answered_without_tables(rannc_dp_t *h) {
   if (!h) return RANNC_DP_INVALID_ARG;
   if (!h->solved) return RANNC_DP_BAD_STATE;
-  return h->direct ? 1 : 0;
+  return h->direct;
 }
 
 static int traceback_impl(rannc_dp_t *h, void *hip_stream, const int32_t *d_levels, int32_t plan_stride,
@@ -1230,53 +1237,89 @@ int rannc_dp_solve_to_host(rannc_dp_t *h, const rannc_dp_batch_t *b, void *hip_s
     // (a call of another layout may have left a result here that equals seq, which starts at 1)
     std::memset(flags, 0, 8 * (size_t)Q);
   }
-  size_t saved_at = 0;
-  const bool direct = reach_applies(h, b, &saved_at);
-  h->to_host = true;
-  h->direct = h->asked = false;
-  if (direct) {
-    rc = reach_impl(h, b, st, plan_stride, r, saved_at);
+  // the tables of a batch, or of a part of this one, and its results
+  auto by_tables = [&](const rannc_dp_batch_t *which, const BatchPart *part) -> int {
+    bool chosen = false, recovered = false;
+    int rc = solve_impl(h, which, hip_stream, r.d_opt, r.d_n_stages, r.d_est, r.d_status, &chosen, plan_stride, poll ? &r : nullptr, &recovered, false, part);
+    if (rc == RANNC_DP_OK && !recovered)
+      rc = traceback_impl(h, hip_stream, nullptr, plan_stride, r.d_stage_end, r.d_replicas, nullptr, &r, !chosen);
     if (rc == RANNC_DP_OK && !poll &&
-        (hipMemcpyAsync(h_results, d_results, at.total, hipMemcpyDeviceToHost, st) != hipSuccess || hipStreamSynchronize(st) != hipSuccess)) {
+        (hipMemcpyAsync(h_results, d_results, at.total, hipMemcpyDeviceToHost, st) != hipSuccess ||
+         hipStreamSynchronize(st) != hipSuccess)) {
       (void)hipGetLastError();
       rc = RANNC_DP_HIP_ERROR;
     }
-    if (rc == RANNC_DP_OK && poll) rc = wait_flags(st, flags, Q, r.seq);
     if (rc != RANNC_DP_OK) {
-      (void)hipStreamSynchronize(st);
+      (void)hipStreamSynchronize(st);  // the staging memory may be refilled by the next call
       return rc;
     }
-    const char *const out = poll ? h->res_pin : (const char *)h_results;
-    const int32_t *const status = (const int32_t *)(out + at.status);
-    if (std::find(status, status + Q, rannc::kReachUndecided) == status + Q) {
-      if (poll) std::memcpy(h_results, h->res_pin, at.total);
-      h->Q = Q;
-      h->solved = true;
-      h->direct = true;
-      h->tabled = false;
-      h->unchosen = false;
-      return RANNC_DP_OK;
-    }
-    r.seq = ++h->seq;  // left to the tables
-  }
-  bool chosen = false, recovered = false;
-  rc = solve_impl(h, b, hip_stream, r.d_opt, r.d_n_stages, r.d_est, r.d_status, &chosen, plan_stride, poll ? &r : nullptr, &recovered);
-  if (rc == RANNC_DP_OK && !recovered)
-    rc = traceback_impl(h, hip_stream, nullptr, plan_stride, r.d_stage_end, r.d_replicas, nullptr, &r, !chosen);
+    if (poll && part)
+      for (size_t k = 0; k < part->place.size() && rc == RANNC_DP_OK; ++k) rc = wait_flags(st, flags + part->place[k], 1, r.seq);
+    else if (poll)
+      rc = wait_flags(st, flags, Q, r.seq);
+    if (rc == RANNC_DP_OK && poll) std::memcpy(h_results, h->res_pin, at.total);
+    return rc;
+  };
+  size_t saved_at = 0;
+  const bool direct = reach_applies(h, b, &saved_at);
+  h->to_host = true;
+  h->asked = false;
+  h->direct = 0;
+  if (!direct) return by_tables(b, nullptr);
+  rc = reach_impl(h, b, st, plan_stride, r, saved_at);
   if (rc == RANNC_DP_OK && !poll &&
-      (hipMemcpyAsync(h_results, d_results, at.total, hipMemcpyDeviceToHost, st) != hipSuccess ||
-       hipStreamSynchronize(st) != hipSuccess)) {
+      (hipMemcpyAsync(h_results, d_results, at.total, hipMemcpyDeviceToHost, st) != hipSuccess || hipStreamSynchronize(st) != hipSuccess)) {
     (void)hipGetLastError();
     rc = RANNC_DP_HIP_ERROR;
   }
+  if (rc == RANNC_DP_OK && poll) rc = wait_flags(st, flags, Q, r.seq);
   if (rc != RANNC_DP_OK) {
-    (void)hipStreamSynchronize(st);  // the staging memory may be refilled by the next call
+    (void)hipStreamSynchronize(st);
     return rc;
   }
-  if (!poll) return RANNC_DP_OK;
-  rc = wait_flags(st, flags, Q, r.seq);
-  if (rc != RANNC_DP_OK) return rc;
-  std::memcpy(h_results, h->res_pin, at.total);
+  const int32_t *const status = (const int32_t *)((poll ? h->res_pin : (const char *)h_results) + at.status);
+  const int open = (int)std::count(status, status + Q, rannc::kReachUndecided);
+  if (open) r.seq = ++h->seq;  // left to the tables
+  if (open == Q) return by_tables(b, nullptr);
+  if (open) {
+    // Those of the open searches alone, in front of the copies of the inputs, as a batch of their own.  (With one of them in a
+    // batch of many all tables would be made: 2 047 of 128 blocks and one of bytes beyond the kernel's range 1 790 us, so 290; 63 and one 323, so 121.)
+    BatchPart part;
+    std::vector<int32_t> N, D, S, MB;
+    std::vector<int64_t> M, off, bw;
+    try {
+      off.push_back(0);
+      for (int q = 0; q < Q; ++q) {
+        if (status[q] != rannc::kReachUndecided) continue;
+        part.place.push_back(q);
+        part.first.push_back(b->block_offset[q]);
+        N.push_back(b->n_blocks[q]); D.push_back(b->n_devices[q]); S.push_back(b->max_stages[q]); MB.push_back(b->n_microbatches[q]);
+        M.push_back(b->mem_capacity[q]);
+        off.push_back(off.back() + b->n_blocks[q]);
+        bw.push_back(b->cut_bytes ? b->bandwidth_bytes_per_us[q] : 1);
+      }
+    } catch (...) {
+      return RANNC_DP_NO_HOST_MEMORY;
+    }
+    rannc_dp_batch_t some = *b;
+    some.n_problems = open;
+    some.n_blocks = N.data(); some.n_devices = D.data(); some.max_stages = S.data(); some.n_microbatches = MB.data();
+    some.mem_capacity = M.data(); some.block_offset = off.data();
+    if (b->cut_bytes) some.bandwidth_bytes_per_us = bw.data();
+    const size_t ws_bytes = h->ws_bytes;
+    h->ws_bytes = saved_at;
+    rc = by_tables(&some, &part);
+    h->ws_bytes = ws_bytes;
+    h->solved = false;  // (what stands in the workspace is a part)
+    if (rc != RANNC_DP_OK) return rc;
+  } else if (poll) {
+    std::memcpy(h_results, h->res_pin, at.total);
+  }
+  h->Q = Q;
+  h->solved = true;
+  h->direct = Q - open;
+  h->tabled = false;
+  h->unchosen = false;
   return RANNC_DP_OK;
 }
 
@@ -1466,7 +1509,7 @@ bool form_direct(rannc_dp_t *h, const rannc_dp_form_stage_in_t *in, const std::v
   }
   h->Q = Q;
   h->solved = true;
-  h->direct = true;
+  h->direct = Q;
   h->tabled = false;
   h->unchosen = false;
   std::memset(out, 0, sizeof(*out));
@@ -1569,7 +1612,8 @@ int rannc_dp_form_stage(rannc_dp_t *h, const rannc_dp_form_stage_in_t *in, void 
   }
   const bool may = library_chooses(h);
   h->to_host = true;
-  h->direct = h->asked = false;
+  h->asked = false;
+  h->direct = 0;
   int direct = RANNC_DP_OK;
   if (may && form_direct(h, in, pairs, max_D, st, out, stage_end, replicas, plan_stride, &direct)) return direct;
   try {

@@ -249,7 +249,7 @@ def test_the_kernels_reported_are_those_that_make_the_tables():
         try:
             out = np.zeros(s._out_dev.numel(), np.uint8)
             assert B.rannc_dp_solve_to_host(h, s.hb, s.stream(), s.plan_stride, s._out_dev, out, out.nbytes) == B.OK
-            assert B.rannc_dp_answered_without_tables(h) == 1
+            assert B.rannc_dp_answered_without_tables(h) == 4
             rc, before = B.rannc_dp_solve_info(h)
             assert rc == B.OK
             d_v = torch.zeros((4, s.plan_stride), dtype=torch.int64, device="cuda:0")
@@ -269,3 +269,34 @@ def test_the_kernels_reported_are_those_that_make_the_tables():
 @pytest.mark.parametrize("N,D,S", [(51, 64, 20), (185, 17, 9), (215, 16, 8)])
 def test_sizes_whose_lds_lies_about_64_kib(N, D, S):
     _check([_search(1, N, D, S, share=1.3)])
+
+
+@pytest.mark.parametrize("Q", [2, 8, 64, 65, 200])
+@pytest.mark.parametrize("comm", [False, True])
+def test_open_searches_are_solved_by_themselves(Q, comm):
+    """Searches whose sums lie beyond the kernel's range among others, at both ends and in between: their tables alone are made, every
+    result stands in its place on the host and on the device, and tables asked for behind the call are the whole batch's."""
+    probs = [_search(q, 161 if comm else 30 + q % 40, (4, 5, 8)[q % 3], 5) for q in range(Q)]
+    odd = sorted({0, Q // 2, Q - 1} if Q > 2 else {1})
+    for q in odd:
+        probs[q] = _search(1000 + q, 161 if comm else 50, 7, 6, scale=1 << 33)
+    if comm and Q > 64:
+        pytest.skip("send times of more than 64 searches are solved with tables")
+    for pr in probs if comm else []:
+        g = np.random.default_rng(pr["n_devices"])
+        pr["cut_bytes"], pr["bandwidth_bytes_per_us"] = g.integers(0, 300, len(pr["time_ns"])), 1000
+    want = oracle_solve_many(probs)
+    with B.Session(synth.concat_batch(probs)) as s:
+        for again in range(2):
+            s._out_dev.fill_(77)
+            res = s.run()
+            assert B.rannc_dp_answered_without_tables(s.h) == Q - len(odd)
+            assert_results_match(probs, res, oracle_results=want)
+            if Q > 64:   # (few searches write their results to the host alone)
+                assert np.array_equal(s.d_opt.cpu().numpy(), res["opt"]) and np.array_equal(s.d_se.cpu().numpy(), res["stage_end"])
+        for q in (odd[0], (odd[0] + 1) % Q):
+            assert np.array_equal(s.table(B.TABLE_V, q), oracle.solve(probs[q], keep_tables=True)["V"])
+        s.d_se.fill_(-3)
+        s.traceback()
+        torch.cuda.synchronize()
+        assert np.array_equal(s.d_se.cpu().numpy(), res["stage_end"])
