@@ -25,7 +25,7 @@ __global__ __launch_bounds__(kBoundThreads) void bound_kernel(const ReachIn *src
   extern __shared__ __align__(16) char lds[];
   constexpr int W = (int)sizeof(ReachIn) / 4;
   __shared__ __align__(8) uint32_t s_in[W];
-  __shared__ int s_flags, s_status;
+  __shared__ int s_flags;
   __shared__ uint64_t s_total[4];
   __shared__ unsigned long long s_cut;
   __shared__ ReachShared<WAVES> sh;
@@ -33,7 +33,7 @@ __global__ __launch_bounds__(kBoundThreads) void bound_kernel(const ReachIn *src
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   ReachIn in = one;
   if (tid < 3) sh.mask[tid] = 0u;
-  if (tid == 0) { s_flags = 0; s_status = RANNC_DP_PROBLEM_OK; s_cut = 0ull; }
+  if (tid == 0) { s_flags = 0; s_cut = 0ull; }
   if (tid < 4) s_total[tid] = 0ull;
   if (wave == 3) sh.inverse[lane] = 1.0 / (double)(lane + 1);
   if (!use_one && tid < W) s_in[tid] = ((const uint32_t *)(src + q))[tid];
@@ -46,13 +46,10 @@ __global__ __launch_bounds__(kBoundThreads) void bound_kernel(const ReachIn *src
     in = x.p;
   }
   const int N = in.N, D = in.D;
-  const int entries = dims.N + 2 + kReachPad, shape = dims.S * dims.D;
+  const int entries = dims.N + 2 + kReachPad;
   double *const sT = (double *)lds + kReachPad, *const sP = sT + entries, *const sA = sP + entries;
   double *const sB = sA + entries, *const sC = sB + (SPLIT ? entries : 0);
   char *const rest = (char *)(sC + (COMM ? entries : 0) - kReachPad);
-  // what the search over T needs, and then the levels
-  double *const value = (double *)rest;
-  uint16_t *const reach = (uint16_t *)(value + dims.cells), *const first_of = reach + shape, *const base = first_of + shape;
   const LevelSpace space = {dims.level_cells, dims.level_sources, dims.level_records, rest};
 
   // ---- sums ----
@@ -111,10 +108,8 @@ __global__ __launch_bounds__(kBoundThreads) void bound_kernel(const ReachIn *src
       __syncthreads();
     }
     const double M = (double)min(in.M, (int64_t)(2 * kReachMaxBytes));  // (as good as unlimited)
-    reach_search<WAVES, true>(in, M, total, sT, sP, sA, value, reach, first_of, base, dims, space, sh, opt, n_stages, status, window);
-    if (wave == 0 && status != RANNC_DP_PROBLEM_OK && lane == 0) s_status = status;
+    reach_search<WAVES, true, SPLIT>(in, M, total, sT, sP, sA, space, 0, sh, opt, n_stages, status, window);
     __syncthreads();
-    status = s_status;
     const LevelSums all = {sT, sP, sA, sB, sC};
     auto times = [&](int i, int j, int r, double &f, double &b) { level_times<SPLIT, COMM>(all, sh.inverse, i, j, r, f, b); };
     if (status == RANNC_DP_PROBLEM_OK && n_stages == 1) {  // one stage sends nothing, and shares everything evenly: no plan is better
@@ -140,7 +135,7 @@ __global__ __launch_bounds__(kBoundThreads) void bound_kernel(const ReachIn *src
       opt = (uint64_t)INT64_MAX;
       status = kReachUndecided;
 #pragma unroll 1
-      for (int attempt = 0; attempt < 4; ++attempt) {
+      for (int attempt = 0; attempt < (N <= 64 && D <= 8 ? 4 : 6); ++attempt) {
         double v = 0.0;
         int s = 0;
         const bool kept = U <= (double)window;
@@ -165,9 +160,8 @@ hipError_t launch_bound(const ReachIn *src, const ReachIn *host_one, int Q, cons
   if (sh.max_N > kBoundMaxBlocks) return hipErrorInvalidValue;
   const bool split = args.tb != nullptr, comm = args.o != nullptr;
   const int cells = std::min(kBoundCells, (sh.max_N * sh.max_D + 15) / 8 * 8);  // (a multiple of 8: aligned arrays)
-  const ReachDims dims = {sh.max_N, sh.max_D, sh.max_S_eff, 1024, cells, kBoundSources, kBoundRecords, 0, 32768};
+  const ReachDims dims = {sh.max_N, cells, kBoundSources, kBoundRecords, 0};
   const size_t sums = (size_t)(dims.N + 2 + kReachPad) * 8 * (3 + (split ? 1 : 0) + (comm ? 1 : 0));
-  const size_t search = (size_t)dims.cells * 8 + (size_t)dims.S * dims.D * 6;
   const size_t levels = level_bytes(cells, kBoundSources, kBoundRecords, split);
   const ReachIn one = host_one ? *host_one : ReachIn{};
   auto go = [&](auto apart, auto sends) -> hipError_t {
@@ -175,7 +169,7 @@ hipError_t launch_bound(const ReachIn *src, const ReachIn *host_one, int Q, cons
     static std::atomic<uint64_t> asked{0};
     const hipError_t e = allow_lds(asked, (const void *)bound_kernel<X, Y>, 148 * 1024);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((bound_kernel<X, Y>), dim3(Q), dim3(kBoundThreads), sums + std::max(search, levels), st, src, one, host_one ? 1 : 0, args, dims);
+    hipLaunchKernelGGL((bound_kernel<X, Y>), dim3(Q), dim3(kBoundThreads), sums + levels, st, src, one, host_one ? 1 : 0, args, dims);
     return hipGetLastError();
   };
   if (split && comm) return go(std::true_type(), std::true_type());

@@ -10,197 +10,11 @@
 
 namespace rannc {
 
-// One bound X, by one wave; lane l holds the reach of d = l + 1 devices.
-// A reach is of use only if the D - d devices that are left could take the rest within X, memory aside: T[reach] >=
-// T[N] - (D - d) X.  Just above the optimum few blocks lie between that floor and the block that d devices reach
-// without any waste, T <= d X, and a source that extends no lane beyond its floor costs one comparison.
-struct Reach {
-  const double *T, *P, *A;  // sums; T[N + 1] is infinite
-  int N, D;
-  double M, X;
-  int most, next, reach;             // block reached without waste; the next one to be reached; the one reached
-  double Tn, Pn, An, Tr, Pr, Ar;     // sums at the two
-
-  __device__ __forceinline__ void start(double x) {
-    X = x;
-    const int lane = threadIdx.x & 63;
-    const double d = (double)(lane + 1), cap = d * X, least = T[N] - ((double)D - d) * X;
-    int lo = 0, below = 0;
-    for (int bit = 1 << (31 - __clz(N)); bit; bit >>= 1) {  // (two independent chains of reads)
-      const int j = min(lo + bit, N + 1), k = min(below + bit, N + 1);
-      const double tj = T[j], tk = T[k];
-      lo = tj <= cap ? j : lo;
-      below = tk < least ? k : below;
-    }
-    most = lo;
-    next = lane < D ? below + 1 : N + 1;  // (row 0 is no reach; least <= T[N], so that below < N)
-    reach = 0;
-    Tn = T[next]; Pn = P[next]; An = A[next];
-    Tr = Pr = Ar = 0.0;
-  }
-  // the stage behind the block with sums Ti, Pi, Ai that d' devices reach: the lanes whose reach it extends
-  __device__ __forceinline__ uint64_t push(int devices, double Ti, double Pi, double Ai) {
-    const int lane = threadIdx.x & 63;
-    const double r = (double)(lane + 1 - devices), until = __builtin_fma(r, X, Ti), room = M + Pi;
-    // bytes P + ceil(A / r) <= M  <=>  r (M - P) - A >= 0
-    auto fits = [&](double t, double p, double a) { return t <= until && __builtin_fma(r, room - p, Ai - a) >= 0.0; };
-    const bool ok = lane >= devices && fits(Tn, Pn, An);
-    const uint64_t m = lanes(ok);
-    if (m == 0ull) return m;
-    int lo = next, hi = ok ? most : next;
-    while (lanes(lo < hi) != 0ull) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (fits(T[mid], P[mid], A[mid])) lo = mid;
-      else hi = mid - 1;
-    }
-    if (ok) {
-      reach = lo;
-      next = lo + 1;
-      Tr = T[lo]; Pr = P[lo]; Ar = A[lo];
-      Tn = T[next]; Pn = P[next]; An = A[next];
-    }
-    return m;
-  }
-  // the fewest stages, at most S, in which D devices reach N, or 0; table: R_s(d) of the levels below, 0 where no
-  // reach is of use, at table[(s - 1) * stride + d - 1] (or null)
-  __device__ __forceinline__ int stages(double x, int S, uint16_t *table, int stride) {
-    const int lane = threadIdx.x & 63;
-    start(x);
-    uint64_t changed = push(0, 0.0, 0.0, 0.0);
-    for (int s = 1;; ++s) {
-      if (lanes(reach == N) != 0ull) return s;
-      if (s == S || changed == 0ull) return 0;
-      if (table && lane < D) table[(s - 1) * stride + lane] = (uint16_t)reach;
-      const int reach0 = reach;
-      const double T0 = Tr, P0 = Pr, A0 = Ar;
-      uint64_t todo = changed;
-      changed = 0ull;
-      for (int row = 0; todo; todo &= todo - 1ull) {
-        const int from = __ffsll((long long)todo) - 1;
-        const int i = (int)lane_bcast((uint32_t)reach0, from);
-        if (i == row) continue;
-        row = i;
-        changed |= push(from + 1, lane_double(T0, from), lane_double(P0, from), lane_double(A0, from));
-      }
-    }
-  }
-};
-
 struct ReachPlan {
   int32_t end[RANNC_DP_MAX_DEVICES], replicas[RANNC_DP_MAX_DEVICES];
 };
 
-// The canonical plan of s stages and value v over all blocks and devices, by one wave.  reach: R_1 .. R_{s-1} at v;
-// first, base: the same shape; value: `cells` entries.  False: more live cells than that.
-__device__ __forceinline__ bool reach_plan(const Reach &w, int s_all, double v, const uint16_t *reach, uint16_t *first, uint16_t *base,
-                                           int stride, double *value, int cells, ReachPlan &plan) {
-  const int lane = threadIdx.x & 63, N = w.N, D = w.D;
-  const double *const T = w.T, *const P = w.P, *const A = w.A;
-  const double M = w.M;
-  auto stage = [&](int i, int j, int r, double x) {  // takes at most x and fits
-    return T[j] - T[i] <= (double)r * x && __builtin_fma((double)r, M + P[i] - P[j], A[i] - A[j]) >= 0.0;
-  };
-  auto lds_order = [] {  // what this wave has written to LDS is what it reads
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-  };
-  // live cells, from the top: (s, i, lane + 1) for first[s][lane] <= i <= reach[s][lane]
-  int total = 0;
-  for (int s = s_all - 1; s >= 1; --s) {
-    const int last = lane < D ? (int)reach[(s - 1) * stride + lane] : 0;
-    int least = 0xFFFF;
-    auto into = [&](int j, int d) {  // the candidates of the live cell (s + 1, j, d)
-      const int r = d - (lane + 1);
-      const bool ok = r >= 1 && last >= 1 && last < j && stage(last, j, max(r, 1), v);
-      if (lanes(ok) == 0ull) return;
-      int lo = 1, hi = ok ? last : 1;
-      while (lanes(lo < hi) != 0ull) {
-        const int mid = (lo + hi) >> 1;
-        if (stage(mid, j, max(r, 1), v)) hi = mid;
-        else lo = mid + 1;
-        lo = min(lo, hi);
-      }
-      if (ok) least = min(least, lo);
-    };
-    if (s == s_all - 1) {
-      into(N, D);
-    } else {
-      const int above_first = lane < D ? (int)first[s * stride + lane] : 0xFFFF, above_last = lane < D ? (int)reach[s * stride + lane] : 0;
-      for (uint64_t m = lanes(above_first <= above_last); m; m &= m - 1ull) {
-        const int d = __ffsll((long long)m) - 1;
-        const int j0 = (int)lane_bcast((uint32_t)above_first, d), j1 = (int)lane_bcast((uint32_t)above_last, d);
-        for (int j = j0; j <= j1; ++j) into(j, d + 1);
-      }
-    }
-    const int mine = least <= last ? last - least + 1 : 0;
-    int run = mine;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int x = __shfl_up(run, o);
-      if (lane >= o) run += x;
-    }
-    const int count = (int)lane_bcast((uint32_t)run, 63);
-    if (total + count > cells) return false;
-    if (lane < D) {
-      first[(s - 1) * stride + lane] = (uint16_t)least;
-      base[(s - 1) * stride + lane] = (uint16_t)(total + run - mine);
-    }
-    total += count;
-    lds_order();
-  }
-  // their values, from the bottom.  (One cell to a level: nothing is left to choose.)
-  const bool choose = total > s_all - 1;
-  for (int s = 1; s < s_all; ++s) {
-    const int from = lane < D ? (int)first[(s - 1) * stride + lane] : 0xFFFF, last = lane < D ? (int)reach[(s - 1) * stride + lane] : 0;
-    const int at = lane < D ? (int)base[(s - 1) * stride + lane] : 0;
-    if (!choose || s == 1) {
-      for (int i = from; i <= last; ++i) value[at + i - from] = choose ? ceil(T[i] / (double)(lane + 1)) : 0.0;
-    } else {
-      const int below_first = lane < D ? (int)first[(s - 2) * stride + lane] : 0xFFFF, below_last = lane < D ? (int)reach[(s - 2) * stride + lane] : 0;
-      const int below_at = lane < D ? (int)base[(s - 2) * stride + lane] : 0;
-      for (uint64_t m = lanes(from <= last); m; m &= m - 1ull) {
-        const int d = __ffsll((long long)m) - 1;
-        const int j0 = (int)lane_bcast((uint32_t)from, d), j1 = (int)lane_bcast((uint32_t)last, d), to = (int)lane_bcast((uint32_t)at, d);
-        const int r = d - lane;
-        for (int j = j0; j <= j1; ++j) {
-          double best = __builtin_inf();
-          if (r >= 1)
-            for (int i = below_first; i <= min(below_last, j - 1); ++i)
-              if (stage(i, j, r, v)) best = fmin(best, fmax(value[below_at + i - below_first], ceil((T[j] - T[i]) / (double)r)));
-          const uint64_t least = wave_min((uint64_t)__double_as_longlong(best));  // (no value is negative)
-          if (lane == 0) value[to + j - j0] = __longlong_as_double((long long)least);
-        }
-      }
-    }
-    lds_order();
-  }
-  // the walk
-  int j = N, d = D;
-  double x = v;
-  for (int s = s_all; s >= 2; --s) {
-    const int from = lane < D ? (int)first[(s - 2) * stride + lane] : 0xFFFF, last = lane < D ? (int)reach[(s - 2) * stride + lane] : 0;
-    const int at = lane < D ? (int)base[(s - 2) * stride + lane] : 0;
-    uint32_t key = ~0u;
-    double mine = 0.0;
-    if (lane + 1 < d)
-      for (int i = from; i <= min(last, j - 1); ++i) {
-        mine = value[at + i - from];
-        if (mine <= x && stage(i, j, d - lane - 1, x)) { key = (uint32_t)i << 8 | (uint32_t)(lane + 1); break; }
-      }
-    const uint32_t best = wave_min(key);
-    if (best == ~0u) return false;  // (there is one; left to the tables)
-    const int before = (int)(best & 255u);
-    if (lane == 0) { plan.end[s - 1] = j; plan.replicas[s - 1] = d - before; }
-    if (choose) x = lane_double(mine, before - 1);
-    j = (int)(best >> 8);
-    d = before;
-  }
-  if (lane == 0) { plan.end[0] = j; plan.replicas[0] = d; }
-  lds_order();
-  return true;
-}
-
-// The same from the chain's end: lane l holds the first block behind which e = l + 1 devices can take the rest, in any
+// One bound x, by one wave; lane l holds the first block behind which e = l + 1 devices can take the rest, in any
 // number of stages.  (Rows count from the front: blocks i + 1 .. N.)  Of use are the rows that the D - e devices in
 // front could reach without waste, T[row] <= (D - e) X: the window, from there down to T[row] >= T[N] - e X.  A lane holds
 // the sums of the four rows that are next, which is what most pushes extend a row by at most.
@@ -393,7 +207,7 @@ __device__ __forceinline__ int reach_finish(const double *T, const double *P, co
   return stages;
 }
 
-struct ReachDims { int N, D, S, cells, level_cells, level_sources, level_records, patient, tight; };  // largest of the launch, room, and lines
+struct ReachDims { int N, level_cells, level_sources, level_records, grow; };  // longest of the launch, and room for the levels
 static_assert(kReachMaxBlocks < 0xFFFF, "16-bit rows");
 
 template <int WAVES> struct ReachShared {
@@ -638,30 +452,30 @@ __device__ __forceinline__ LevelState reach_levels(const LevelSums &x, int N, in
 }
 
 // The search over sums in LDS (pads in front and the infinite time behind them included), by a workgroup: optimum,
-// fewest stages (0: no plan), plan.  status: kReachUndecided, in wave 0, where it is left to the tables.  mask, inverse: made.
-// space: of the levels, and of value, reach, first_of and base, which are not used at the same time.  window: the bound that
-// sh.kept holds the windows of (or 0).  ASK: where many cells are left at a bound,
+// fewest stages (0: no plan), plan.  status: kReachUndecided where it is left to the tables.  mask, inverse: made.
+// window: the bound that sh.kept holds the windows of (or 0).  ASK: where many cells are left at a bound,
 // that is opt, and n_stages is -1: the caller asks the levels itself.
-template <int WAVES, bool ASK>
+//
+// Left to the tables as soon as it seems that it will be: where the stages there are do not suffice at the optimum of any number of
+// them (the smallest bound at which they do lies far above: 175 blocks at 11 devices in at most 5 stages that are 98 % full 46 us with
+// tables, 96 to 215 by larger bounds, 67 to 78 left at once), and where more cells are left at the optimum than the levels
+// have room for, which the windows of a bound below it tell.
+template <int WAVES, bool ASK_MANY, bool ASK_FEW>
 __device__ __forceinline__ void reach_search(const ReachIn &in, const double M, const uint64_t total, const double *const sT, const double *const sP,
-                                             const double *const sA, double *const value, uint16_t *const reach, uint16_t *const first_of,
-                                             uint16_t *const base, const ReachDims &dims, const LevelSpace &space,
+                                             const double *const sA, const LevelSpace &space, const int grow,
                                              ReachShared<WAVES> &sh, uint64_t &opt, int &n_stages, int &status, uint64_t &window) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int N = in.N, D = in.D;
-  Reach w;
-  w.T = sT; w.P = sP; w.A = sA; w.N = N; w.D = D;
-  w.M = M;
   const uint64_t share = (total + (uint64_t)D - 1) / (uint64_t)D;  // of one device: no plan is better
   Completion back;
-  back.T = sT; back.P = sP; back.A = sA; back.N = N; back.D = D; back.M = w.M;
+  back.T = sT; back.P = sP; back.A = sA; back.N = N; back.D = D; back.M = M;
   // A bound per wave and round.  lo .. hi - 1: the bounds that are left (all below fail, hi holds).
   uint64_t lo = share, hi = max(total, share);
   int round = 0;
-  // The round's bounds are bound(0) <= bound(1) <= ...; holds(x, mask): sets this wave's bit if its bound does.  Returns the first one that
-  // does (WAVES: none).
-  auto ask = [&](auto bound, auto holds) -> int {
-    holds((double)bound(wave), &sh.mask[round % 3]);
+  // The round's bounds are bound(0) <= bound(1) <= ...; returns the first one that holds (WAVES: none).
+  auto ask = [&](auto bound) -> int {
+    back.run((double)bound(wave), &sh.mask[round % 3], wave);
+    sh.rows[round & 1][wave][lane] = (uint32_t)back.row | (uint32_t)(back.top & 0xffff) << 16;
     if (tid == 0) sh.mask[(round + 1) % 3] = 0u;
     lds_barrier();
     const uint32_t mask = lane_bcast(sh.mask[round % 3], 0);
@@ -672,173 +486,139 @@ __device__ __forceinline__ void reach_search(const ReachIn &in, const double M, 
     ++round;
     return k;
   };
-  // v of n bounds between lo and hi, excesses over `over` in geometric steps (of at most an eighth of the range at
+  // v of n bounds between lo and hi, excesses over the share in geometric steps (of at most an eighth of the range at
   // first); every one if there are no more
-  auto between = [&](uint64_t over, int v, int n) -> uint64_t {
+  auto between = [&](int v, int n) -> uint64_t {
     const uint64_t gap = hi - lo;
     if (gap <= (uint64_t)n) return min(lo + (uint64_t)v, hi - 1);
     if (round > 10) return lo + gap * (uint64_t)(v + 1) / (uint64_t)(n + 1);
-    const float high = (float)(hi - over), low = fmaxf((float)(lo - over), 0.125f * high);
+    const float high = (float)(hi - share), low = fmaxf((float)(lo - share), 0.125f * high);
     const float at = low * __builtin_amdgcn_exp2f(__builtin_amdgcn_logf(high / low) * (float)(v + 1) / (float)(n + 1));
-    return min(max(over + (uint64_t)at, lo), hi - 1);
+    return min(max(share + (uint64_t)at, lo), hi - 1);
   };
-  int first = 1, last = 0, widest = 0;  // cells of a lane at hi (wave 0)
-  // whether the cells that are left at hi are few; k: the wave that has asked for hi in this round
-  auto few = [&](int k) -> bool {
+  // a lane's window at the bound of wave k in the last round: first cell, and how many
+  auto cells_of = [&](int k, int &first, int &last) -> int {
     const uint32_t r = sh.rows[(round - 1) & 1][k][max(D - 2 - lane, 0)];  // devices behind this lane's d: D - 1 - lane
-    if (wave == 0) sh.kept[lane] = sh.rows[(round - 1) & 1][k][lane];
-    window = hi;
     first = lane < D - 1 ? max((int)(r & 0xffffu), 1) : N;
     last = lane < D - 1 ? (int)(r >> 16) : N;
-    const int width = lane < D ? max(last - first + 1, 0) : 0;
-    widest = 1;
-    int cells = 0;
-#pragma unroll
-    for (int n = 1; n <= kReachPad; ++n) {
-      const uint64_t m = lanes(width >= n);
-      if (m) widest = n;
-      cells += __popcll(m);
-    }
-    return lanes(width > kReachPad) == 0ull && (cells <= 2 * D || lo >= hi);
-  };
-  auto completes = [&](double x, uint32_t *mask) {
-    back.run(x, mask, wave);
-    sh.rows[round & 1][wave][lane] = (uint32_t)back.row | (uint32_t)(back.top & 0xffff) << 16;
-  };
-  auto staged = [&](double x, uint32_t *mask) {
-    const int s = w.stages(x, in.S, nullptr, 0);
-    if (s && lane == 0) atomicOr(mask, 1u << wave);
-  };
-  // Algorithm 1's levels at hi or, where it takes more stages, at larger bounds
-  const LevelSums sums = {sT, sP, sA, nullptr, nullptr};
-  auto levels = [&](uint64_t bound) -> LevelState {
-    double v = 0.0;
-    int s = 0;
-    const bool kept = bound == window;
-    const LevelState state = reach_levels<WAVES, false, false>(sums, N, D, M, (double)bound, kept, in.S, space, sh, v, s);
-    if (!kept) window = bound;
-    if (state == kLevelsFound) { hi = lane_bcast((uint64_t)v, 0); n_stages = s; }
-    __syncthreads();
-    return state;
+    return lane < D ? max(last - first + 1, 0) : 0;
   };
   window = 0;
-  bool found = true, done = false;
-  if (__builtin_fma((double)D, w.M - sP[N], -sA[N]) >= 0.0) {  // one stage of everything
-    hi = share;
+  const double full = (sP[N] + sA[N] / (double)D) / ((double)in.S * M);  // of the bytes of all stages
+  if (__builtin_fma((double)D, M - sP[N], -sA[N]) >= 0.0) {  // one stage of everything
+    opt = share;
     n_stages = 1;
     if (tid == 0) { sh.plan.end[0] = N; sh.plan.replicas[0] = D; }
-    done = true;
-  } else if (const double full = (sP[N] + sA[N] / (double)D) / ((double)in.S * M); !dims.patient && N * D > dims.tight && full > 0.75 && full <= 1.01) {
+    return;
+  }
+  if (full > 1.0 + 0x1p-40) return;  // (what the stages hold, with all devices to each; and the rounding of that)
+  if (N * D > 32768 && full > 0.75) {
     // Stages nearly full of bytes, so that the best plan of any number of stages takes more than there are, and at the bound that
     // they allow many cells are left: 1024 blocks at 64 devices, 9 stages 85 % full, tables 101 us, here 426.
-    // (Fuller than full: there is no plan, which is found soon.)
     status = kReachUndecided;
     return;
-  } else {
-    // First the excess over a share that is usual, up to eight of the chain's mean blocks over all devices together; then
-    // up to everything; then between.
-    constexpr float step = WAVES >= 16 ? 0.5f : WAVES >= 8 ? 1.0f : 2.5f;
-    const float block = 8.0f * (float)share / (float)N;
-    // (every turn ends the loop, narrows lo .. hi - 1, or grows the bound of the levels, which it does twice at most)
-    uint64_t bound_of_levels = 0;
-    bool by_levels = false;
-    int kind = 0, grown = 0;
+  }
+  // First the excess over a share that is usual, up to eight of the chain's mean blocks over all devices together; then
+  // up to everything; then between.
+  constexpr float step = WAVES >= 16 ? 0.5f : WAVES >= 8 ? 1.0f : 2.5f;
+  const float block = 8.0f * (float)share / (float)N;
+  bool few_stages = false;
 #pragma unroll 1
-    for (;;) {
-      if (!by_levels) {
-        const uint64_t from = lo;
-        auto bound = [&](int v) -> uint64_t {
-          if (kind == 0) return v == 0 ? share : min(share + (uint64_t)(block * __builtin_amdgcn_exp2f(step * (float)(v - (WAVES - 1)))), total);
-          if (kind == 1) {
-            if (v == WAVES - 1) return total;
-            const float most = (float)(total - share), least = fmaxf((float)(from - share), 1.0f);
-            const float at = least * __builtin_amdgcn_exp2f(__builtin_amdgcn_logf(fmaxf(most / least, 1.0f)) * (float)(v + 1) / (float)WAVES);
-            return min(max(share + (uint64_t)at, from), total);
-          }
-          return between(share, v, WAVES);
-        };
-        const int k = ask(bound, completes);
-        if (kind < 2 && k == WAVES) {
-          found = ++kind < 2 && lo <= total;
-          if (!found) break;
-          continue;
-        }
-        const bool fits = k < WAVES && few(k);
-        if (fits && widest <= 2) {
-          if (wave == 0) {
-            double opt_at = 0.0;
-            const double x = (double)hi;
-            const int s = widest == 1 ? reach_finish<1>(sT, sP, sA, N, D, w.M, x, first, last, sh.inverse, opt_at, sh.plan, in.S)
-                                    : reach_finish<2>(sT, sP, sA, N, D, w.M, x, first, last, sh.inverse, opt_at, sh.plan, in.S);
-            if (lane == 0) { sh.stages = s; sh.opt = (uint64_t)opt_at; }
-          }
-          lds_barrier();
-          n_stages = (int)lane_bcast((uint32_t)sh.stages, 0);
-          hi = lane_bcast(sh.opt, 0);
-          done = n_stages >= 1 && n_stages <= in.S;
-          if (done) break;
-          n_stages = 0;
-          lds_barrier();
-          grown = 1;  // more stages than there are
-          bound_of_levels = hi;
-          by_levels = true;
-        } else if (fits || kind == 2 || lo >= hi) {
-          // Many cells, though few may be reached (memory, or a long block, costs more than the share): the levels tell.
-          bound_of_levels = hi;
-          by_levels = true;
-        }
-        kind = 2;
+  for (int kind = 0;;) {  // (kind grows in every turn but the last)
+    const uint64_t from = lo;
+    auto bound = [&](int v) -> uint64_t {
+      if (kind == 0) return v == 0 ? share : min(share + (uint64_t)(block * __builtin_amdgcn_exp2f(step * (float)(v - (WAVES - 1)))), total);
+      if (kind == 1) {
+        if (v == WAVES - 1) return total;
+        const float most = (float)(total - share), least = fmaxf((float)(from - share), 1.0f);
+        const float at = least * __builtin_amdgcn_exp2f(__builtin_amdgcn_logf(fmaxf(most / least, 1.0f)) * (float)(v + 1) / (float)WAVES);
+        return min(max(share + (uint64_t)at, from), total);
       }
-      if (grown) bound_of_levels = min(bound_of_levels + 4 * (bound_of_levels - share) + (share >> 6) + 1, total);
-      if (ASK && by_levels && !grown && hi == window) {
-        opt = hi;
-        n_stages = -1;
+      return between(v, WAVES);
+    };
+    const int k = ask(bound);
+    if (kind < 2 && k == WAVES) {
+      if (++kind == 2 || lo > total) return;  // no plan
+      continue;
+    }
+    if (k > 0 && k < WAVES) {  // at the optimum there are as many cells as at a bound below it, or more
+      int first, last, run = cells_of(k - 1, first, last);
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) run += __shfl_xor(run, o);
+      if (__builtin_amdgcn_readfirstlane(run) > space.cells) {
+        status = kReachUndecided;
         return;
       }
-      if (by_levels) {
-        const LevelState state = levels(bound_of_levels);
-        done = state == kLevelsFound;
-        if (state == kLevelsNone && bound_of_levels == total) found = false;  // (no plan takes longer)
-        if (done || !found || (state == kLevelsOpen ? grown || lo >= hi : grown == 2)) break;
-        if (state == kLevelsNone) ++grown;  // the stages do not suffice at the bound: the optimum is larger
-        else by_levels = false;
-      }
     }
-  }
-  // More cells than the levels have room for.  A search by itself is left to the tables; one of many, for which all their tables would
-  // be made, is taken stage by stage.
-  if (found && !done && (WAVES >= 16 || !dims.patient)) {
-    found = false;
-    status = kReachUndecided;
-  }
-  if constexpr (WAVES < 16) {
-    for (int turn = 0; found && !done; ++turn) {
+    int first = 1, last = 0, widest = 0;  // cells of a lane at hi
+    bool fits = false;
+    if (k < WAVES) {
+      const int width = cells_of(k, first, last);
+      if (wave == 0) sh.kept[lane] = sh.rows[(round - 1) & 1][k][lane];
+      window = hi;
+      widest = 1;
+      int cells = 0;
+#pragma unroll
+      for (int n = 1; n <= kReachPad; ++n) {
+        const uint64_t m = lanes(width >= n);
+        if (m) widest = n;
+        cells += __popcll(m);
+      }
+      fits = lanes(width > kReachPad) == 0ull && (cells <= 2 * D || lo >= hi);
+    }
+    if (fits && widest <= 2) {
       if (wave == 0) {
-        const int s = w.stages((double)hi, in.S, reach, dims.D);
-        if (lane == 0) sh.stages = s;
+        double opt_at = 0.0;
+        const double x = (double)hi;
+        const int s = widest == 1 ? reach_finish<1>(sT, sP, sA, N, D, M, x, first, last, sh.inverse, opt_at, sh.plan, in.S)
+                                  : reach_finish<2>(sT, sP, sA, N, D, M, x, first, last, sh.inverse, opt_at, sh.plan, in.S);
+        if (lane == 0) { sh.stages = s; sh.opt = (uint64_t)opt_at; }
       }
       lds_barrier();
-      n_stages = sh.stages;
-      lds_barrier();
-      if (n_stages || turn) break;
-      // the stages do not suffice there: the bound is larger
-      const uint64_t over = hi;
-      lo = hi + 1;
-      hi = total;
-      found = lo <= total && ask([&](int) { return total; }, staged) < WAVES;
-      lo = over + 1;  // (every wave has asked for the same)
-      while (found && lo < hi)
-        ask([&](int v) { return between(over, v, WAVES); }, staged);
+      const int s = (int)lane_bcast((uint32_t)sh.stages, 0);
+      if (s >= 1 && s <= in.S) {
+        n_stages = s;
+        opt = lane_bcast(sh.opt, 0);
+        return;
+      }
+      few_stages = true;
+    } else if (!fits && kind != 2 && lo < hi) {
+      kind = 2;
+      continue;
     }
-    if (found && n_stages && wave == 0 && !done) {
-      const bool ok = n_stages == 1 || reach_plan(w, n_stages, (double)hi, reach, first_of, base, dims.D, value, dims.cells, sh.plan);
-      if (n_stages == 1 && lane == 0) { sh.plan.end[0] = N; sh.plan.replicas[0] = D; }
-      if (!ok) status = kReachUndecided;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
+    break;
   }
-  if (found && n_stages) opt = hi;
+  // Many cells, though few may be reached (memory, or a long block, costs more than the share), or the stages do not suffice: the
+  // levels tell, at hi and, where the stages do not suffice there, at one larger bound.
+  if (few_stages ? ASK_FEW : ASK_MANY) {
+    opt = hi;
+    n_stages = -1;
+    return;
+  }
+  const LevelSums sums = {sT, sP, sA, nullptr, nullptr};
+#pragma unroll 1
+  for (int turn = 0; turn < 2; ++turn) {
+    if (few_stages && in.S * D > grow) break;
+    const uint64_t U = few_stages ? min(hi + 4 * (hi - share) + (share >> 6) + 1, total) : hi;
+    double v = 0.0;
+    int s = 0;
+    const LevelState state = reach_levels<WAVES, false, false>(sums, N, D, M, (double)U, U == hi, in.S, space, sh, v, s);
+    __syncthreads();
+    if (state == kLevelsFound) {
+      n_stages = s;
+      opt = lane_bcast((uint64_t)v, 0);
+      return;
+    }
+    if (state == kLevelsNone && U >= total) return;  // (no plan takes longer)
+    if (state == kLevelsNone && ASK_FEW) {
+      opt = hi;
+      n_stages = -1;
+      return;
+    }
+    if (state == kLevelsOpen || few_stages) break;
+    few_stages = true;
+  }
+  status = kReachUndecided;
 }
 
 // Results of search q, by the workgroup's first wave.

@@ -2,30 +2,30 @@
 // plan, for callers that want nothing else (rannc_dp_solve_to_host).  The tables themselves are made by the kernels in
 // rannc_dp_kernels.hip, when they are asked for.
 //
-// Without send times the stage time h(i, j, r) of Sec. III-C and its bytes grow with the stage and fall with r, so
-// for a given bound X the largest j for which the stage (i, j) on r replicas takes at most X and fits memory never
-// falls as i grows.  Let R_s(d) be the last block that at most s stages on at most d devices reach, no stage above X:
-//     R_s(d) = max over d' < d of (the end of the longest stage behind R_{s-1}(d') on d - d' replicas)
-// D (D + 1) / 2 stages per level instead of N (N + 1) / 2 merges of D values, and the optimum is the smallest X with
-// R_S(D) = N.  The stage counts of a plan are found the same way: the fewest s with R_s(D) = N at the optimum.
+// Without send times the stage time h(i, j, r) of Sec. III-C and its bytes grow with the stage and fall with r, so for a given
+// bound X the first row behind which e devices can take the rest, no stage above X, in any number of stages,
+//     B(e) = min over f < e of (the beginning of the longest stage in front of B(f) on e - f replicas),
+// takes D (D + 1) / 2 stages instead of N (N + 1) / 2 merges of D values per level, and the smallest X with B(D) = 0 is the
+// optimum over any number of stages.  A round asks for one bound per wave.  What can be part of a plan within X are the cells
+// (i, d) with B(D - d) <= i and T[i] <= d X.
 //
-// Exactly s stages (the cells V[s][j][d] of the tables) against at most s: let s* be the fewest stages of a plan of
+// Exactly s stages (the cells V[s][j][d] of the tables) against any number: let s* be the fewest stages of a plan of
 // value v = V[s*][N][D].  A cell (s, i, d) from which s* - s further stages reach N within v has no plan of fewer
-// than s stages within v, or the whole would have fewer than s*.  For these LIVE cells "at most s stages" and
-// "exactly s stages" are the same, their i are the interval from the first row that completes the plan to R_s(d), and
-// every candidate of a live cell of value at most v lies in a live cell.  The walk of Algorithm 1's argmin (smallest
-// i, then smallest d', of the candidates that attain the cell's value) therefore stays among them, and so does the
-// recurrence for their values.  There are few: at the optimum the devices just suffice.
+// than s stages within v, or the whole would have fewer than s*.  For these cells "fewest stages" and
+// "exactly s stages" are the same, and every candidate of such a cell of value at most v is such a cell.  The walk of
+// Algorithm 1's argmin (smallest i, then smallest d', of the candidates that attain the cell's value) therefore stays
+// among them, and so does the recurrence for their values.  Where a bound leaves one or two cells to a device they are all that
+// is looked at (reach_finish).
 //
-// Where the bound leaves many cells (a long block, or bytes that crowd at one end, cost more than an even share), or the stages
-// there are do not suffice for it, Algorithm 1's levels run among the cells that a bound leaves instead (reach_levels).
+// Where it leaves more (a long block, or bytes that crowd at one end, cost more than an even share), Algorithm 1's levels run
+// among the cells that the bound leaves instead (reach_levels).  Where these are too many, or the stages do not suffice at the bound,
+// the search is left to the tables (reach_search).
 //
 // Bound by latency: the devices are taken one after the other, some 350 ns each (sums of a row from lanes to scalars,
 // a dozen dependent double-precision instructions, the next rows from LDS), where windows are wide up to 1 us (searches through
-// rows).  Per call, tables / this kernel: 96 blocks at 16 devices 56 / 22 us, 1024 at 64 275 / 59 where memory binds and
-// 454 / 17 where one stage holds everything, 701 at 48 with 64-bit values 249 / 30, 2048 searches of 128 blocks 1630 / 155;
-// 251 blocks whose bytes grow along the chain, at 24 devices, 94 / 81 (172 by bounds alone, without the levels); 300 at 32 in
-// at most 4 stages that are 78 % full 49 / 50 (199).
+// rows).  Per call, tables / this kernel: 96 blocks at 16 devices 51 / 14 us, 1024 at 64 282 / 55 where memory binds, 2048 searches of
+// 128 blocks 1720 / 163.  Slower than with tables where nothing is to spare: 60 at 24 in at most 24 stages, 23 or 24 needed, 66 / 83;
+// and by what it took to find out where they are left to them: 22 at 15 without a plan 25 / 56, 1024 at 64 in 9 stages 104 / 118.
 #include "rannc_dp_reach.h"
 
 namespace rannc {
@@ -56,9 +56,8 @@ __global__ __launch_bounds__(64 * WAVES) void reach_kernel(const ReachIn *src, c
     in = x.p;
   }
   const int N = in.N;
-  const int entries = dims.N + 2 + kReachPad, shape = dims.S * dims.D;
-  double *const sT = (double *)lds + kReachPad, *const sP = sT + entries, *const sA = sP + entries, *const value = sA + entries - kReachPad;
-  uint16_t *const reach = (uint16_t *)(value + dims.cells), *const first_of = reach + shape, *const base = first_of + shape;
+  const int entries = dims.N + 2 + kReachPad;
+  double *const sT = (double *)lds + kReachPad, *const sP = sT + entries, *const sA = sP + entries, *const rest = sA + entries - kReachPad;
 
   // ---- sums ----
   if (wave < 3) {
@@ -91,26 +90,30 @@ __global__ __launch_bounds__(64 * WAVES) void reach_kernel(const ReachIn *src, c
 
   uint64_t opt = (uint64_t)INT64_MAX, window;
   int n_stages = 0;
-  const LevelSpace space = {dims.level_cells, dims.level_sources, dims.level_records, (char *)value};
+  const LevelSpace space = {dims.level_cells, dims.level_sources, dims.level_records, (char *)rest};
   if (status == RANNC_DP_PROBLEM_OK)
-    reach_search<WAVES, false>(in, (double)min(in.M, (int64_t)(2 * kReachMaxBytes)) /* as good as unlimited */, lane_bcast(s_total, 0), sT, sP, sA, value, reach, first_of,
-                        base, dims, space, sh, opt, n_stages, status, window);
+    reach_search<WAVES, false, false>(in, (double)min(in.M, (int64_t)(2 * kReachMaxBytes)) /* as good as unlimited */, lane_bcast(s_total, 0), sT, sP, sA, space, dims.grow, sh, opt,
+                        n_stages, status, window);
   reach_results(in, args, q, sh.plan, opt, n_stages, status);
 }
 
 hipError_t launch_reach(const ReachIn *src, const ReachIn *host_one, int Q, const LaunchShape &sh, const ReachArgs &args, hipStream_t st) {
   if (sh.max_N > kReachMaxBlocks) return hipErrorInvalidValue;
-  // Room for the levels: of few searches, which have a compute unit to themselves, what is left of its LDS; of many, so
-  // much that it does not keep the workgroups that registers allow (five of four waves) from a compute unit.
+  // Room for the levels, as much as keeps no workgroup that registers allow from a compute unit (131 of them: three waves to a SIMD):
+  // one of eight or sixteen waves, three of four.
+  // grow: stages times devices up to which a search of several whose stages do not suffice is asked at one larger bound; left open it
+  // costs tables of its own (15 ragged searches of 32 blocks at up to 32 devices in 6 stages: 60 us without, 52 with).  By itself a search
+  // is no slower with the tables.
   const size_t sums = (size_t)(sh.max_N + 2 + kReachPad) * 24;
-  ReachDims dims = {sh.max_N, sh.max_D, sh.max_S_eff, Q > 64 ? 256 : 1024, 1024, 160, 512, Q > 8 ? 1 : 0, 32768};
-  if (Q <= 64) {
-    dims.level_sources = 256;
-    dims.level_records = 1024;
+  ReachDims dims = {sh.max_N, 1536, 256, 1024, Q > 1 ? 512 : 0};
+  if (Q <= 512) {
+    if (Q == 1 && sh.max_N <= 1024) {  // (504 equal blocks at 47 devices 523 -> 318 us; beside others it is the quicker half that waits)
+      dims.level_sources = 512;
+      dims.level_records = 4096;
+    }
     dims.level_cells = (int)std::min<size_t>(std::min(3584, (sh.max_N * sh.max_D + 15) / 8 * 8), (144 * 1024 - sums - level_bytes(0, dims.level_sources, dims.level_records, false)) / 12);
   }
-  const size_t lds = sums + std::max((size_t)dims.cells * 8 + (size_t)dims.S * dims.D * 6,
-                                     level_bytes(dims.level_cells, dims.level_sources, dims.level_records, false));
+  const size_t lds = sums + level_bytes(dims.level_cells, dims.level_sources, dims.level_records, false);
   const ReachIn one = host_one ? *host_one : ReachIn{};
   auto go = [&](auto waves) -> hipError_t {
     constexpr int W = decltype(waves)::value;
@@ -120,11 +123,11 @@ hipError_t launch_reach(const ReachIn *src, const ReachIn *host_one, int Q, cons
     hipLaunchKernelGGL(reach_kernel<W>, dim3(Q), dim3(64 * W), lds, st, src, one, host_one ? 1 : 0, args, dims);
     return hipGetLastError();
   };
-  // Waves of a search, each with a bound of its own: as many as the device has places for (100 registers: four waves per
-  // SIMD), and no more than eight for up to sixteen devices, whose bounds take little longer than the start of a wave.
-  // Per call, 4 / 8 / 16 waves: 16 blocks at 4 devices 29 / 30 / 32 us, 96 at 16 34 / 33 / 32, 300 at 32 41 / 50 / 42,
-  // 1024 at 64 99 / 65 / 65, 32 searches of 1000 at 64 148 / 119 / 105, 200 of 128 at 64 85 / 49 / 47, 512 93 / 56 / 63,
-  // 1024 of 128 at 16 66 / 77 / 95, 2000 of 60 at 32 106 / 110 / 132.
+  // Waves of a search, each with a bound of its own: as many as the device has places for, and no more than eight for up to
+  // sixteen devices, whose bounds take little longer than the start of a wave.
+  // Per call, 4 / 8 / 16 waves: 16 blocks at 4 devices 24 / 21 / 22 us, 300 at 32 40 / 27 / 28, 1024 at 64 46 / 70 / 50, 32 searches of
+  // 1000 at 64 192 / 103 / 95, 200 of 128 at 64 94 / 50 / 47, 512 97 / 64 / 64, 600 of 100 at 32 67 / 66 / 69, 768 of 128 at 64
+  // 100 / 82 / 78, 1024 of 128 at 16 75 / 93 / 94, 2000 of 60 at 32 112 / 136 / 139.
   if (Q > 512) return go(std::integral_constant<int, 4>());
   if (Q > 64 || sh.max_D <= 16) return go(std::integral_constant<int, 8>());
   return go(std::integral_constant<int, 16>());

@@ -300,3 +300,16 @@ def test_open_searches_are_solved_by_themselves(Q, comm):
         s.traceback()
         torch.cuda.synchronize()
         assert np.array_equal(s.d_se.cpu().numpy(), res["stage_end"])
+
+
+@pytest.mark.parametrize("N,D,S,kind,share", [(175, 11, 5, "plain", 0.78), (22, 15, 7, "plain", 0.82), (668, 33, 33, "one long", 1.3),
+                                              (1400, 23, 23, "one long", 1.3), (1024, 64, 9, "plain", 0.65)])
+def test_what_is_left_to_the_tables(N, D, S, kind, share):
+    """Stages that hardly hold the bytes, and a block longer than the others: as soon as it shows that the tables are
+    quicker the kernel leaves the search to them, alone and among others; with room to spare it does not."""
+    pr, others = _search(7, N, D, S, kind, share), [_search(q, 40, 8, 5, share=3.0) for q in range(70)]
+    for probs, least, most in (([pr], 0, 0), ([pr] + others, 70, 71), ([_search(7, N, D, S, share=6.0)], 1, 1)):
+        with B.Session(synth.concat_batch(probs)) as s:
+            res = s.run()
+            assert least <= B.rannc_dp_answered_without_tables(s.h) <= most
+            assert_results_match(probs, res, oracle_results=oracle_solve_many(probs))
