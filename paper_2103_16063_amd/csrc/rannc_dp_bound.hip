@@ -6,9 +6,10 @@
 // times, without what is sent, priced with send times and the two maxima: for one objective it is an upper bound by
 // itself, with the two apart (Algorithm 1 as printed may miss that plan) the levels say whether it is.
 //
-// Bound by latency, as rannc_dp_reach.hip: of a call's 43 us at 256 blocks and 32 devices the search over the sums
-// takes 12, the windows of the bound 10, five levels 9.  Per call, tables / this kernel: 256 blocks at 32 devices, maxima apart,
-// 202 / 43 us; with send times 531 at 8 81 / 19, 1000 at 6 in at most 12 stages 67 / 37; both 362 at 8 74 / 19.
+// Bound by latency, as rannc_dp_reach.hip.  Per call, tables / this kernel: maxima apart 256 blocks at 32 devices 9.7 ms / 62 to 103 us
+// (64-bit handle); with send times 531 at 8 69 / 38 to 52 us, 1000 at 6 81 / 36, 664 at 11 in at most 5 stages that are 85 % full
+// 69 / 145; both 362 at 8 2.4 ms / 43 to 68.
+#include "rannc_dp_attempts.h"
 #include "rannc_dp_reach.h"
 
 namespace rannc {
@@ -108,7 +109,7 @@ __global__ __launch_bounds__(kBoundThreads) void bound_kernel(const ReachIn *src
       __syncthreads();
     }
     const double M = (double)min(in.M, (int64_t)(2 * kReachMaxBytes));  // (as good as unlimited)
-    reach_search<WAVES, true, SPLIT>(in, M, total, sT, sP, sA, space, 0, sh, opt, n_stages, status, window);
+    reach_search<WAVES, !(SPLIT && COMM), SPLIT>(in, M, total, sT, sP, sA, space, 0, sh, opt, n_stages, status, window);
     __syncthreads();
     const LevelSums all = {sT, sP, sA, sB, sC};
     auto times = [&](int i, int j, int r, double &f, double &b) { level_times<SPLIT, COMM>(all, sh.inverse, i, j, r, f, b); };
@@ -118,10 +119,9 @@ __global__ __launch_bounds__(kBoundThreads) void bound_kernel(const ReachIn *src
       opt = (uint64_t)(f + b);
     } else if (status == RANNC_DP_PROBLEM_OK && n_stages != 0) {
       // ---- U: that plan's value here; or where many cells were left, so that it has not been looked for, the bound itself ----
-      const double least = (double)opt;  // (no value is smaller, or that bound)
-      const bool asked = n_stages < 0;
-      double U = least;
-      if (!asked) {
+      const Attempts bounds = {(double)opt, n_stages < 0, SPLIT, N <= 64 && D <= 8};
+      double price = 0.0;
+      if (!bounds.asked) {
         double f = 0.0, b = 0.0;
         if (lane < n_stages) times(lane ? sh.plan.end[lane - 1] : 0, sh.plan.end[lane], sh.plan.replicas[lane], f, b);
 #pragma unroll
@@ -129,13 +129,14 @@ __global__ __launch_bounds__(kBoundThreads) void bound_kernel(const ReachIn *src
           f = dmax(f, __shfl_xor(f, o));
           b = dmax(b, __shfl_xor(b, o));
         }
-        U = f + b;
+        price = f + b;
       }
+      double U = bounds.first(price);
       n_stages = 0;
       opt = (uint64_t)INT64_MAX;
       status = kReachUndecided;
 #pragma unroll 1
-      for (int attempt = 0; attempt < (N <= 64 && D <= 8 ? 4 : 6); ++attempt) {
+      for (int attempt = 0; U >= 0.0; ++attempt) {
         double v = 0.0;
         int s = 0;
         const bool kept = U <= (double)window;
@@ -145,11 +146,8 @@ __global__ __launch_bounds__(kBoundThreads) void bound_kernel(const ReachIn *src
           n_stages = s;
           status = RANNC_DP_PROBLEM_OK;
         }
-        if (!kept) window = (uint64_t)U;
-        // (too many cells are too many at larger bounds; at a smaller one they may do)
-        if (state == kLevelsFound || (state == kLevelsOpen && attempt)) break;
-        U = state == kLevelsOpen ? least + floor((U - least) * 0.25) : asked && attempt == 0 ? U + floor(U * 0.015625) + 1.0 : least + (U - least + 1.0) * 2.0;
-        if (state == kLevelsOpen) window = 0;
+        window = state == kLevelsOpen ? 0 : kept ? window : (uint64_t)U;
+        U = bounds.next(attempt, U, state);
       }
     }
   }

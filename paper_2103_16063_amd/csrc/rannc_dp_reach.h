@@ -2,6 +2,7 @@
 // such searches with it, and rannc_dp_bound.hip, which starts from its plan.
 #pragma once
 
+#include "rannc_dp_attempts.h"
 #include "rannc_dp_once.h"
 #include "rannc_dp_sums.h"
 
@@ -245,8 +246,6 @@ constexpr size_t level_bytes(int cells, int sources, int records, bool split) {
   return (size_t)cells * (split ? 14 : 12) + (size_t)sources * (split ? 40 : 24) + (size_t)records * 8;
 }
 struct LevelSums { const double *T, *P, *A, *B, *C; };  // B: backward times alone; C: send times by the block in front of the cut
-
-enum LevelState { kLevelsNone, kLevelsFound, kLevelsOpen };  // open: more cells than there is room for
 
 // forward time (with what is sent) and backward time of the stage i+1 .. j on r replicas
 template <bool SPLIT, bool COMM>
