@@ -919,7 +919,7 @@ __global__ __launch_bounds__(1024) void compact_resume_kernel(int G, int k, int6
   }
   int done = 0, n = G;  // walks that count
   while (done + 1 < walks && state.left[done + 1] >= 0) n = state.left[++done];
-  const int32_t *const first = done ? state.first[done & 1] : nullptr;
+  const int32_t *first = done ? state.first[done & 1] : nullptr;
   auto plain = [&](int u) { return u >= n ? G : first ? first[u] : u; };
   int at[2] = {G, G};  // of a thread's groups, where the last walk counts, whose groups nobody has gathered yet
   static_assert(kCompactSmall < 2 * NT, "two of a thread");
@@ -934,6 +934,13 @@ __global__ __launch_bounds__(1024) void compact_resume_kernel(int G, int k, int6
         if (e * NT + tid < left) at[e] = plain(group[e * NT + tid]);
       n = left;
       ++done;
+    } else if (left > kCompactSmall && left >= k && left < n) {
+      // (in rounds again it would take longest: 15 000 groups to 1 000 142 us, so 86; 65 535, one walk only, 566 / 111)
+      int32_t *const next = state.first[(done + 1) & 1];
+      compact_left<NT>(state.became[walks & 1], n, 0, left, part, [&](int rank, int u) { next[rank] = plain(u); });
+      n = left;
+      ++done;
+      first = next;
     }
     __syncthreads();
   }

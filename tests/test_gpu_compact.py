@@ -104,6 +104,25 @@ def test_compact_windows(G, order):
             assert np.array_equal(have.cpu().numpy()[:n], want)
 
 
+@pytest.mark.parametrize("G,k,walks", [(1700, 1650, 0), (5000, 1601, 0), (15000, 1000, 0), (15000, 2500, 0), (16384, 40, 1), (16385, 40, 1), (30001, 1500, 0),
+                                       (30001, 7, 2), (65535, 9000, 0), (65535, 5, 3), (65535, 5, 1)])
+@pytest.mark.parametrize("order", ["random", "runs"])
+def test_compact_long_chains_to_many_blocks(G, k, walks, order):
+    """The last walk with a launch of its own leaves more groups than one workgroup holds in LDS: what k or the limit on the walks leaves."""
+    g = np.random.default_rng(G + k)
+    t, p, a = g.integers(0, 1 << 30, G), g.integers(0, 50, G), g.integers(0, 50, G)
+    if order == "runs":
+        for at in g.integers(0, G - 100, 3):
+            t[at:at + 100] = np.arange(100) * 1000
+    for M in (10**9, 400):
+        rc, n, st, d_end, d_out = gpu_compact(t, p, a, k, M, walks)
+        assert rc == B.OK and st == B.PROBLEM_OK
+        end, tt, pp, aa = oracle.compact(t, p, a, k, M, max_passes=walks)
+        assert n == len(end) and np.array_equal(d_end.cpu().numpy()[:n], end), M
+        for have, want in zip(d_out, (tt, pp, aa)):
+            assert np.array_equal(have.cpu().numpy()[:n], want)
+
+
 @pytest.mark.parametrize("G", [1700, 9000])
 def test_compact_refuses_long_chains_that_overflow(G):
     """The sums of a long chain are made by many workgroups: each kind of input, at either end of the chain."""
