@@ -110,3 +110,68 @@ def test_tables_are_made_from_what_the_call_was_given(form):
             N, D, L = len(pr["time_ns"]), pr["n_devices"], o["n_levels"]
             assert np.array_equal(s.table(B.TABLE_V, q), o["V"])
             assert np.array_equal(d_v.cpu().numpy()[q, :L], o["V"][1:L + 1, N, D])
+
+
+def _in_line(g, form):
+    """Blocks, devices, stages of a search that the kernel is asked for: with send times few devices or stages, and with one
+    objective chains that are not one launch with tables."""
+    while True:
+        D, S = int(g.integers(1, 33)), int(g.choice([1, 2, 3, 5, 8]))
+        if "c" not in form or D * min(S, D) <= 64:
+            return (int(g.integers(161, 300)) if form == "c" else int(g.integers(2, 60))), D, S
+
+
+@pytest.mark.parametrize("form", ["c", "s", "cs"])
+@pytest.mark.parametrize("kind", ["plain", "equal", "small", "one long", "opposed"])
+@pytest.mark.parametrize("Q", [1, 7, 64])
+def test_searches_that_the_kernel_answers(form, kind, Q):
+    """With room to spare every one is answered without tables; nearly full, with long send times, and without a plan results agree
+    whichever way they come."""
+    g = np.random.default_rng([Q, len(kind), len(form)])
+    for share, cut, settled in ((2.5, 3, True), (2.5, 300, True), (6.0, 300, True), (1.02, 50000, False), (0.8, 300, False)):
+        probs = [_search(int(g.integers(1 << 30)), *_in_line(g, form), form, kind, share=share, cut=cut) for q in range(Q)]
+        with B.Session(synth.concat_batch(probs), max_total_time_ns=1 << 42) as s:
+            res = s.run()
+            if settled:
+                assert B.rannc_dp_answered_without_tables(s.h) >= Q - Q // 16   # (ties can leave more cells than there is room for)
+            assert_results_match(probs, res, oracle_results=oracle_solve_many(probs))
+
+
+@pytest.mark.parametrize("form,N,D,S,Q,n", [("c", 160, 4, 3, 1, 0), ("c", 161, 4, 3, 1, 1), ("c", 300, 13, 5, 1, 0), ("c", 300, 32, 2, 1, 1), ("c", 200, 4, 3, 65, 0),
+                                            ("c", 1024, 4, 3, 1, 1), ("c", 1025, 4, 3, 1, 0), ("cs", 20, 8, 8, 1, 1), ("cs", 20, 9, 8, 1, 0),
+                                            ("s", 20, 40, 20, 64, 64), ("s", 20, 4, 4, 65, 0), ("s", 1025, 3, 3, 1, 0)])
+def test_which_searches_the_kernel_is_asked_for(form, N, D, S, Q, n):
+    probs = [_search(q, N, D, S, form, share=3.0) for q in range(Q)]
+    with B.Session(synth.concat_batch(probs), max_total_time_ns=1 << 42) as s:
+        res = s.run()
+        assert B.rannc_dp_answered_without_tables(s.h) == n
+        if N < 1000:
+            assert_results_match(probs[:2], {k: v[:2] for k, v in res.items()}, oracle_results=oracle_solve_many(probs[:2]))
+
+
+@pytest.mark.parametrize("form", ["c", "cs"])
+def test_flags_and_tables_of_searches_the_kernel_answers(form):
+    """Inputs that are refused, and tables made from the saved bytes per cut and bandwidths, inside of what the kernel takes."""
+    probs = [_search(q, 170 + 9 * q, (3, 8, 20, 5)[q % 4], (5, 8, 3, 5)[q % 4], form, share=3.0) for q in range(4)]
+    for q, pr in enumerate(probs):
+        pr["bandwidth_bytes_per_us"] = 500 + 300 * q
+    with B.Session(synth.concat_batch(probs)) as s:
+        res = s.run()
+        assert B.rannc_dp_answered_without_tables(s.h) == 4
+        assert_results_match(probs, res, oracle_results=oracle_solve_many(probs))
+        for x in s.d_in + [s.d_cut] + ([s.d_bwd] if "s" in form else []):
+            x.fill_(-1)
+        s.d_se.fill_(-3)
+        s.traceback()
+        torch.cuda.synchronize()
+        assert np.array_equal(s.d_se.cpu().numpy(), res["stage_end"])
+        for q, pr in enumerate(probs):
+            assert np.array_equal(s.table(B.TABLE_V, q), oracle.solve(pr, keep_tables=True)["V"])
+    probs[0]["cut_bytes"][-2] = 1 << 60
+    probs[1]["cut_bytes"][0] = -1
+    probs[2]["time_ns"][:] = 1 << 30
+    with B.Session(synth.concat_batch(probs)) as s:
+        res = s.run()
+        assert B.rannc_dp_answered_without_tables(s.h) == 4
+        assert list(res["status"]) == [B.PROBLEM_SUM_OVERFLOW, B.PROBLEM_NEGATIVE_INPUT, B.PROBLEM_TIME_TOO_LARGE, B.PROBLEM_OK]
+        assert_results_match(probs[3:], {k: v[3:] for k, v in res.items()})

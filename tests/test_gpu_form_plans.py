@@ -103,3 +103,13 @@ def test_tables_behind_the_driver_do_not_wait_and_outlive_the_next_call(form):
         torch.cuda.synchronize()
         assert list(se[found, :S].cpu()) == list(want["stage_end"]) and list(rp[found, :S].cpu()) == list(want["replicas"])
     fs.close()
+
+
+@pytest.mark.parametrize("form", ["plain", "comm", "split comm", "ties"])
+@pytest.mark.parametrize("N,nodes,per,BS,tight,taken", [(1, 1, 1, 1, 3.0, True), (64, 4, 4, 16, 1.3, True), (40, 8, 8, 16, 1.1, True), (32, 4, 8, 256, 1.3, True),
+                                                        (96, 4, 8, 256, 2.0, True), (40, 3, 9, 16, 1.4, False)])
+def test_which_drivers_the_kernel_answers(N, nodes, per, BS, tight, taken, form):
+    """Results are the same where the batched solve takes over: here whether it does."""
+    fs = _case(3, N, nodes, per, BS, tight, form)[2]
+    assert B.rannc_dp_answered_without_tables(fs.h) == (fs.Q if taken else 0)
+    fs.close()

@@ -313,3 +313,24 @@ def test_what_is_left_to_the_tables(N, D, S, kind, share):
             res = s.run()
             assert least <= B.rannc_dp_answered_without_tables(s.h) <= most
             assert_results_match(probs, res, oracle_results=oracle_solve_many(probs))
+
+
+@pytest.mark.parametrize("kind", ["plain", "equal", "one long", "transient"])
+@pytest.mark.parametrize("Q", [1, 64, 65, 512])
+def test_usual_searches_are_answered_by_the_kernel(kind, Q):
+    """Results are the same where the tables take over: here that they do not."""
+    g = np.random.default_rng([Q, 3])
+    probs = [_search(q, int(g.integers(2, 60)), int(g.integers(1, 65)), int(g.choice([1, 2, 3, 5, 64])), kind if q % 2 else "plain", share=2.5)
+             for q in range(Q)]
+    with B.Session(synth.concat_batch(probs)) as s:
+        res = s.run()
+        assert B.rannc_dp_answered_without_tables(s.h) >= Q - Q // 50   # (of equal blocks a few leave more cells than there is room for)
+        assert_results_match(probs, res, oracle_results=oracle_solve_many(probs))
+
+
+@pytest.mark.parametrize("N,D,S,n", [(1, 1, 1, 1), (64, 16, 8, 1), (192, 64, 12, 1), (577, 3, 3, 1), (1089, 40, 3, 1), (4096, 2, 2, 1), (4097, 2, 2, 0)])
+def test_sizes_that_the_kernel_takes(N, D, S, n):
+    for algo, want in ((B.ALGO_AUTO, n), (B.ALGO_MERGE, 0)):
+        with B.Session(synth.concat_batch([_search(1, N, D, S)]), algo=algo) as s:
+            s.run()
+            assert B.rannc_dp_answered_without_tables(s.h) == want
