@@ -540,15 +540,6 @@ __device__ __forceinline__ void reach_search(const ReachIn &in, const double M, 
       if (++kind == 2 || lo > total) return;  // no plan
       continue;
     }
-    if (k > 0 && k < WAVES) {  // at the optimum there are as many cells as at a bound below it, or more
-      int first, last, run = cells_of(k - 1, first, last);
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) run += __shfl_xor(run, o);
-      if (__builtin_amdgcn_readfirstlane(run) > space.cells) {
-        status = kReachUndecided;
-        return;
-      }
-    }
     int first = 1, last = 0, widest = 0;  // cells of a lane at hi
     bool fits = false;
     if (k < WAVES) {
@@ -581,9 +572,20 @@ __device__ __forceinline__ void reach_search(const ReachIn &in, const double M, 
         return;
       }
       few_stages = true;
-    } else if (!fits && kind != 2 && lo < hi) {
-      kind = 2;
-      continue;
+    } else {
+      if (k > 0 && k < WAVES) {  // at the optimum there are as many cells as at a bound below it, or more
+        int run = cells_of(k - 1, first, last);
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) run += __shfl_xor(run, o);
+        if (__builtin_amdgcn_readfirstlane(run) > space.cells) {
+          status = kReachUndecided;
+          return;
+        }
+      }
+      if (!fits && kind != 2 && lo < hi) {
+        kind = 2;
+        continue;
+      }
     }
     break;
   }

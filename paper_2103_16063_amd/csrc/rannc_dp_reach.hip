@@ -107,7 +107,9 @@ hipError_t launch_reach(const ReachIn *src, const ReachIn *host_one, int Q, cons
   const size_t sums = (size_t)(sh.max_N + 2 + kReachPad) * 24;
   ReachDims dims = {sh.max_N, 1536, 256, 1024, Q > 1 ? 512 : 0};
   if (Q <= 512) {
-    if (Q == 1 && sh.max_N <= 1024) {  // (504 equal blocks at 47 devices 523 -> 318 us; beside others it is the quicker half that waits)
+    // (504 equal blocks at 47 devices 523 -> 318 us, 196 searches of 35 at 32 with a long one 238 -> 190; of a few searches the launch waits
+    // for the one that goes on longest)
+    if ((Q == 1 || Q > 64) && sh.max_N <= 1024) {
       dims.level_sources = 512;
       dims.level_records = 4096;
     }

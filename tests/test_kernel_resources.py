@@ -115,3 +115,23 @@ def test_one_launch_kernels_of_batches_fit_twice_on_a_compute_unit(kernels):
         if m and workgroups_per_cu(k, 1024) >= 2:
             fits.add((32 if m.group(1) == "j" else 64, int(m.group(2)), int(m.group(3))))
     assert twice <= fits, twice - fits
+
+
+def test_kernels_without_tables_fit_as_their_launches_count_on(kernels):
+    """Workgroups of a search to a compute unit, by registers, and with the LDS that their launches take: three of four waves
+    (1536 cells, 256 sources, 1024 records and the sums of 600 blocks), one of eight or sixteen."""
+    sums, levels = lambda n: (n + 6) * 24, lambda cells, sources, records: cells * 12 + sources * 24 + records * 8
+    seen = set()
+    for name, k in kernels.items():
+        m = re.search(r"(reach|bound|form)_kernelI(?:Li(\d+)E|L)", name)
+        if not m:
+            continue
+        seen.add((m.group(1), m.group(2)))
+        if m.group(2) == "4":
+            assert workgroups_per_cu(k, 256) >= 3, name
+            assert 3 * (k["group_segment_fixed_size"] + sums(600) + levels(1536, 256, 1024)) <= LDS, name
+        else:
+            assert workgroups_per_cu(k, 512 if m.group(2) == "8" else 1024) >= 1, name
+        # at sixteen waves to a workgroup 128 registers are all there are
+        assert k.get("vgpr_spill_count", 0) <= 3, (name, k["vgpr_spill_count"])
+    assert seen == {("reach", "4"), ("reach", "8"), ("reach", "16"), ("bound", None), ("form", None)}, seen
