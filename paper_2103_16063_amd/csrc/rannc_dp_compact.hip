@@ -1,4 +1,4 @@
-// gfx950 kernel of the compaction step of RaNNC's block-level phase (Sec. III-B) on a chain, and
+// gfx950 kernels of the compaction step of RaNNC's block-level phase (Sec. III-B) on a chain, and
 // its launcher.
 #include "rannc_dp_device.h"
 #include "rannc_dp_once.h"
@@ -15,8 +15,8 @@ namespace rannc {
 // neighbour whose current time is smaller if the union fits the device memory; the procedure ends
 // as soon as k groups are left.  When a walk ends above k groups the groups are listed again by
 // their current times and walked again, until k is reached, a walk merges nothing, or the caller's
-// limit on the number of walks is met.  The kernel exists so that the chain stays on the device
-// between the two phases.  One workgroup.
+// limit on the number of walks is met.  The kernels exist so that the chain stays on the device
+// between the two phases.  One workgroup, and for the walks of long chains launches over the device.
 //
 // The walk follows a list, but a turn of it reads and changes only its own neighbourhood: the turn
 // of group v looks at its neighbours l and r and merges v with one of them, and the only turns that

@@ -220,8 +220,8 @@ hipError_t launch_traceback(const ProblemDev *probs, int Q, int plan_stride, int
                             const FormStageIn *form_stage, const PlanResults *results, bool choose, hipStream_t st);
 hipError_t launch_level_values(const ProblemDev *probs, int Q, int stride, int64_t *d_out, hipStream_t st);
 // Min-max searches without send times answered without their tables (rannc_dp_reach.hip): optimum, fewest stages,
-// plan, by one workgroup each.  Copies of the inputs go to `save` (three arrays of `blocks` entries, the searches one
-// after the other), from which the tables can be made later.
+// plan, by one workgroup each.  Copies of the inputs go to `save` (times, persistent, transient bytes; there is room for five arrays
+// of `blocks` entries, the searches one after the other), from which the tables can be made later.
 constexpr int kReachMaxBlocks = 4096;   // the sums of a search are held in LDS
 constexpr int kReachUndecided = -1;     // status of a search that is left to the tables
 struct ReachIn {
@@ -240,8 +240,9 @@ struct ReachArgs {
 };
 // src: the descriptors in memory the device can read (pinned); host_one: of a launch over one search, by value, or null
 hipError_t launch_reach(const ReachIn *src, const ReachIn *host_one, int Q, const LaunchShape &sh, const ReachArgs &args, hipStream_t st);
-// The same for searches with send times, or with forward and backward maxima apart (rannc_dp_bound.hip); five arrays are saved.
-constexpr int kBoundMaxBlocks = 1024;  // (a row is ten bits of a key)
+// The same for searches with send times, or with forward and backward maxima apart (rannc_dp_bound.hip); bytes per cut and
+// backward times are saved as the fourth and fifth array.
+constexpr int kBoundMaxBlocks = 1024;  // (the LDS: up to five arrays of sums, and room for the levels)
 hipError_t launch_bound(const ReachIn *src, const ReachIn *host_one, int Q, const LaunchShape &sh, const ReachArgs &args, hipStream_t st);
 // The outer driver's searches, each the smallest stage count of lo..hi with a plan of exactly so many stages on D devices,
 // and that plan (rannc_dp_form.hip): one workgroup each, results in pinned host memory.
@@ -265,8 +266,9 @@ hipError_t launch_form(int Q, int spare, const FormArgs &args, hipStream_t st);
 // The inputs of all Q searches of the outer driver, one after the other, from its own per sample: five arrays of N entries (times,
 // persistent, transient bytes, bytes per cut, backward times) to as many of Q * N; samples[q] of search q.
 hipError_t launch_form_inputs(const int64_t *per_sample, const int64_t *samples, int64_t *out, int N, int Q, bool comm, bool split, hipStream_t st);
-// compaction step of the block-level phase on a chain of G groups (one workgroup).  Short chains are
-// held in LDS; longer ones keep arrays of G + 1 entries in the workspace: three of 8 bytes and two of 4
+// compaction step of the block-level phase on a chain of G groups.  Chains of up to kCompactLds groups are held in the LDS of one
+// workgroup; longer ones keep arrays in the workspace: three of 8 bytes and three of 4 of G + 1 entries, and a word per
+// sixteen groups for what the last two walks have left (compact_state in rannc_dp_compact.hip)
 constexpr size_t compact_array_bytes(int G, int entry) { return ((size_t)(G + 1) * entry + 255) / 256 * 256; }
 // (the size callers have been given since the first version of the step; more than the arrays need)
 constexpr int kCompactLds = 1600;

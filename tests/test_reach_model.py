@@ -1,6 +1,7 @@
 """The method of the kernel that answers a min-max search without its tables (csrc/rannc_dp_reach.hip), written down
 from its definition and compared with the oracle: the bound within which D devices take the chain in at most S
-stages, the fewest stages, and the canonical plan found among the cells that can complete one."""
+stages, the fewest stages, and the canonical plan found among the cells that can complete one.  (The kernel takes the bound
+of any number of stages and leaves a search for which S do not suffice there to others.)"""
 import numpy as np
 import pytest
 
